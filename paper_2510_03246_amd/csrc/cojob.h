@@ -22,6 +22,7 @@ struct CoJob {
   unsigned int* ticket;    // next unit to hand out (device counter, zero when the job starts); null = no job
   unsigned int units;      // nrows * segs
   int take;                // units a spare workgroup takes before it exits
+  int per_launch;          // units one launch of the factorisation chains should take
   const int32_t* rows;     // the pruned rows, ascending
   int nrows, segs;
   long long seg_tokens;    // tokens per unit (a multiple of 4)

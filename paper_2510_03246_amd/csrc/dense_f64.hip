@@ -1,194 +1,221 @@
-// fp64 dense kernels for the ridge systems: blocked Cholesky, inversion of the triangular factor by
-// recursive doubling, right-side solves as two triangular-aware GEMMs, and small cast / scatter helpers.
-// The Gram systems reach condition numbers ~1e4, so factor and solve stay in fp64.  The GEMM runs on the
-// fp64 matrix cores (v_mfma_f64_16x16x4_f64): same peak as the vector unit, far less LDS traffic per flop.
+// fp64 dense kernels for the ridge systems: one launch chain that factors an SPD matrix and inverts its triangular
+// factor at the same time, right-side solves as two triangular-aware GEMMs, and small cast / scatter helpers.
+// The Gram systems reach condition numbers ~1e4, so factor and solve stay in fp64.  Everything runs on the fp64
+// matrix cores: v_mfma_f64_16x16x4_f64 sustains 73-77 TFLOP/s here with four or more independent accumulators per
+// SIMD (plain v_fma_f64 67; the two share their units, a mix of both is no faster), far above what LDS or L2 can feed
+// to a naive tiling -- so the kernels below are about operand traffic, loads in flight and launches, not arithmetic.
 #include "cojob.h"
 #include "strp_internal.h"
 
 namespace strp {
 
 typedef double doublex4 __attribute__((ext_vector_type(4)));
+typedef double doublex2 __attribute__((ext_vector_type(2)));
 
-// ---------------------------------------------------------------------------------------------
-// dgemm: C = alpha * A * B + beta * C, element strides for A(m,k) and B(k,n), C row-major.
-//   block = 4 wavefronts (2x2), wavefront tile = WT x WT MFMA tiles of 16x16, K staged 16 at a time.
-//   batch (grid.z): operand pointers advance by sa / sb / sc elements per batch entry and the batch
-//   entry's M and K are clamped to lim_base - z * lim_step (ragged last block of a blocked algorithm).
-//   tri restricts the K range of a tile to where a triangular operand is non-zero:
-//     1: k < n0 + tile (B upper in (k, n)),  2: k >= n0 (B lower),  3: k >= m0 (A upper in (m, k)),
-//     4: k < m0 + tile (A lower).
-//   lower != 0 skips output tiles entirely above the diagonal.
 // MFMA lane layout: A operand lane l = A[i = l % 16][k = l / 16], B operand lane l = B[k = l / 16][j = l % 16],
 // result register r of lane l = D[i = 4 r + l / 16][j = l % 16].
+__device__ __forceinline__ doublex4 mma_f64(double a, double b, doublex4 c) { return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0); }
+
+// Barrier of a workgroup whose wavefronts exchange data through LDS only: unlike __syncthreads it does not wait for the
+// global loads and stores in flight (a store acknowledgement costs a step of the factorisation chain about 1 us).
+__device__ __forceinline__ void lds_barrier() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+  __builtin_amdgcn_s_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
+
+// LDS images of an operand tile of R rows and K contraction steps:
+//   KC (the source is contiguous in k):   [k / 2][R + 1][2]: a lane takes two k at once (16 bytes)
+//   RC (the source is contiguous in rows): [k][R + 4]
+// Eight contraction steps are two matrix-core instructions: instruction s multiplies k = 8 c + 2 (l / 16) + s, the same
+// order for both operands, so a 16-byte KC read feeds both.  The odd pitches keep writes and reads free of bank conflicts.
+template <int R>
+__device__ __forceinline__ int kc_off(int k, int r) { return ((k >> 1) * (R + 1) + r) * 2 + (k & 1); }
+template <int R>
+__device__ __forceinline__ int rc_off(int k, int r) { return k * (R + 4) + r; }
+
+// ---------------------------------------------------------------------------------------------
+// dgemm: C[m, n] = sum_k A(m, k) B(k, n), C row-major.
+//   block = 4 wavefronts (2 x 2), TM x TN output tile, K staged DK at a time through double-buffered LDS; the next
+//   stage's 16-byte loads are in flight while a stage is multiplied.
+//   A: AKC ? A[m * lda + k] : A[k * lda + m];   B: BKC ? B[n * ldb + k] : B[k * ldb + n].
+//   tri restricts the K range of a tile to where a triangular operand is non-zero:
+//     1: k < n0 + TN (B upper in (k, n)),  2: k >= n0 (B lower),  3: k >= m0 (A upper in (m, k), with lower).
+//   lower != 0 skips output tiles entirely above the diagonal.
 // ---------------------------------------------------------------------------------------------
 struct DgemmP {
   int M, N, K;
-  double alpha, beta;
-  const double* A; long long rsa, csa;
-  const double* B; long long rsb, csb;
+  const double* A; long long lda;
+  const double* B; long long ldb;
   double* C; long long ldc;
   int lower, tri;
-  long long sa, sb, sc;
-  int lim_base, lim_step;   // lim_step == 0: no clamping
-  int clamp_k;              // clamp K like M (square ragged block)
-  int own_x;                // blocks with blockIdx.x >= own_x are spare workgroups for the ride-along job (0: there are none)
+  int vec;                  // 16-byte loads: leading dimensions even and bases aligned
 };
 
-template <int WT>
-__global__ __launch_bounds__(256) void dgemm_kernel(const DgemmP p, const CoJob job) {
-  constexpr int TS = 32 * WT;      // block tile (rows and columns)
-  constexpr int DK = 16;
-  constexpr int LD = TS + 4;
-  // double-buffered operand tiles: one barrier per K tile
-  __shared__ double As[2][DK][LD];
-  __shared__ double Bs[2][DK][LD];
-  if (p.own_x && (int)blockIdx.x >= p.own_x) {
-    cojob_help(job);
-    return;
+template <int R, int DK, bool KC>
+struct F64Loader {
+  static constexpr int NCH = R * DK / 512;   // 16-byte pieces per thread and stage
+  doublex2 r[NCH];
+  // rows [0, rv) and k in [k0, kend) are valid; src points at row 0
+  __device__ __forceinline__ void load(const double* src, long long ld, int rv, int k0, int kend, bool full) {
+#pragma unroll
+    for (int q = 0; q < NCH; ++q) {
+      const int e = (int)threadIdx.x + 256 * q;
+      if (KC) {
+        const int ch = e % (DK / 2), row = e / (DK / 2);
+        const int k = k0 + 2 * ch;
+        const double* p = src + (long long)row * ld + k;
+        if (full) r[q] = *(const doublex2*)p;
+        else r[q] = doublex2{(row < rv && k < kend) ? p[0] : 0.0, (row < rv && k + 1 < kend) ? p[1] : 0.0};
+      } else {
+        const int pr = e % (R / 2), kk = k0 + e / (R / 2);
+        const int row = 2 * pr;
+        const double* p = src + (long long)kk * ld + row;
+        if (full) r[q] = *(const doublex2*)p;
+        else r[q] = doublex2{(row < rv && kk < kend) ? p[0] : 0.0, (row + 1 < rv && kk < kend) ? p[1] : 0.0};
+      }
+    }
   }
-  const int z = blockIdx.z;
-  int M = p.M, K = p.K;
-  if (p.lim_step) {
-    const int lim = p.lim_base - z * p.lim_step;
-    M = M < lim ? M : lim;
-    if (p.clamp_k) K = K < lim ? K : lim;
+  __device__ __forceinline__ void store(double* img) const {
+#pragma unroll
+    for (int q = 0; q < NCH; ++q) {
+      const int e = (int)threadIdx.x + 256 * q;
+      if (KC) *(doublex2*)(img + kc_off<R>(2 * (e % (DK / 2)), e / (DK / 2))) = r[q];
+      else *(doublex2*)(img + rc_off<R>(e / (R / 2), 2 * (e % (R / 2)))) = r[q];
+    }
   }
-  const int N = p.N;
-  // blockIdx.x walks the rows of C; blockIdx.y walks column tiles in order of decreasing K range
-  const int ntile = (p.tri == 1) ? (int)(gridDim.y - 1 - blockIdx.y) : (int)blockIdx.y;
-  const int m0 = blockIdx.x * TS, n0 = ntile * TS;
-  if (M <= 0 || m0 >= M) return;
-  if (p.lower && n0 >= m0 + TS) return;
-  const double* A = p.A + (long long)z * p.sa;
-  const double* B = p.B + (long long)z * p.sb;
-  double* C = p.C + (long long)z * p.sc;
-  int kbeg = 0, kend = K;
-  if (p.tri == 1) kend = (n0 + TS < K) ? n0 + TS : K;
-  if (p.tri == 2) kbeg = n0;            // multiples of TS, hence of DK
+};
+template <int R, int DK, bool KC>
+constexpr int f64_img_elems() { return KC ? DK / 2 * (R + 1) * 2 : DK * (R + 4); }
+
+template <int TM, int TN, int DK, bool AKC, bool BKC>
+__global__ __launch_bounds__(256, 2) void dgemm_kernel(const DgemmP p) {
+  constexpr int WM = TM / 32, WN = TN / 32;     // 16 x 16 tiles per wavefront
+  __shared__ __attribute__((aligned(16))) double As[2][f64_img_elems<TM, DK, AKC>()];
+  __shared__ __attribute__((aligned(16))) double Bs[2][f64_img_elems<TN, DK, BKC>()];
+  const int tilesM = (p.M + TM - 1) / TM, tilesN = (p.N + TN - 1) / TN;
+  // the rows of C walk fastest; column tiles go in order of decreasing K range
+  const int tn_ = (int)blockIdx.x / tilesM, tm_ = (int)blockIdx.x - tn_ * tilesM;
+  const int m0 = tm_ * TM, n0 = (p.tri == 1 ? tilesN - 1 - tn_ : tn_) * TN;
+  if (p.lower && n0 >= m0 + TM) return;
+  int kbeg = 0, kend = p.K;
+  if (p.tri == 1) kend = n0 + TN < p.K ? n0 + TN : p.K;
+  if (p.tri == 2) kbeg = n0;
   if (p.tri == 3) kbeg = m0;
-  if (p.tri == 4) kend = (m0 + TS < K) ? m0 + TS : K;
 
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int wm = wave >> 1, wn = wave & 1;
-  constexpr int EPT = TS * DK / 256;   // elements per thread per operand tile (8 or 4)
-  doublex4 acc[WT][WT];
+  const int wm = (wave >> 1) * (TM / 2), wn = (wave & 1) * (TN / 2);
+  const int l16 = lane & 15, lq = lane >> 4;
+  doublex4 acc[WM][WN];
 #pragma unroll
-  for (int i = 0; i < WT; ++i)
+  for (int i = 0; i < WM; ++i)
 #pragma unroll
-    for (int j = 0; j < WT; ++j) acc[i][j] = doublex4{0.0, 0.0, 0.0, 0.0};
+    for (int j = 0; j < WN; ++j) acc[i][j] = doublex4{0.0, 0.0, 0.0, 0.0};
 
-  double ra[EPT], rb[EPT];
-  auto gload = [&](int k0) {
-#pragma unroll
-    for (int i = 0; i < EPT; ++i) {
-      const int e = tid + 256 * i;
-      int m, k;
-      if (p.csa == 1) { m = e / DK; k = e % DK; } else { k = e / TS; m = e % TS; }
-      ra[i] = (m0 + m < M && k0 + k < kend) ? A[(long long)(m0 + m) * p.rsa + (long long)(k0 + k) * p.csa] : 0.0;
-      int n, kb;
-      if (p.csb == 1) { kb = e / TS; n = e % TS; } else { n = e / DK; kb = e % DK; }
-      rb[i] = (n0 + n < N && k0 + kb < kend) ? B[(long long)(k0 + kb) * p.rsb + (long long)(n0 + n) * p.csb] : 0.0;
-    }
+  const double* A = AKC ? p.A + (long long)m0 * p.lda : p.A + m0;
+  const double* B = BKC ? p.B + (long long)n0 * p.ldb : p.B + n0;
+  const int rvm = p.M - m0, rvn = p.N - n0;
+  const bool fa = p.vec && rvm >= TM, fb = p.vec && rvn >= TN;
+  // two stages in flight in registers besides the one in LDS that is multiplied: with few workgroups per CU a stage is
+  // multiplied in less time than a load takes
+  F64Loader<TM, DK, AKC> la[2];
+  F64Loader<TN, DK, BKC> lb[2];
+  auto gload = [&](int set, int k0) {
+    if (k0 >= kend) return;
+    const bool fk = k0 + DK <= kend;
+    la[set].load(A, p.lda, rvm, k0, kend, fa && fk);
+    lb[set].load(B, p.ldb, rvn, k0, kend, fb && fk);
   };
-  auto sstore = [&](int buf) {
+  auto stage = [&](int buf, int k0) {       // multiply the stage at k0, held in As[buf]; the next one is in set buf ^ 1
+    gload(buf, k0 + 2 * DK);
+    const double* as = As[buf];
+    const double* bs = Bs[buf];
 #pragma unroll
-    for (int i = 0; i < EPT; ++i) {
-      const int e = tid + 256 * i;
-      int m, k;
-      if (p.csa == 1) { m = e / DK; k = e % DK; } else { k = e / TS; m = e % TS; }
-      As[buf][k][m] = ra[i];
-      int n, kb;
-      if (p.csb == 1) { kb = e / TS; n = e % TS; } else { n = e / DK; kb = e % DK; }
-      Bs[buf][kb][n] = rb[i];
+    for (int c = 0; c < DK / 8; ++c) {
+      doublex2 af[WM], bf[WN];
+      const int k = 8 * c + 2 * lq;
+#pragma unroll
+      for (int i = 0; i < WM; ++i) {
+        if (AKC) af[i] = *(const doublex2*)(as + kc_off<TM>(k, wm + 16 * i + l16));
+        else af[i] = doublex2{as[rc_off<TM>(k, wm + 16 * i + l16)], as[rc_off<TM>(k + 1, wm + 16 * i + l16)]};
+      }
+#pragma unroll
+      for (int j = 0; j < WN; ++j) {
+        if (BKC) bf[j] = *(const doublex2*)(bs + kc_off<TN>(k, wn + 16 * j + l16));
+        else bf[j] = doublex2{bs[rc_off<TN>(k, wn + 16 * j + l16)], bs[rc_off<TN>(k + 1, wn + 16 * j + l16)]};
+      }
+#pragma unroll
+      for (int i = 0; i < WM; ++i)
+#pragma unroll
+        for (int j = 0; j < WN; ++j) acc[i][j] = mma_f64(af[i].x, bf[j].x, acc[i][j]);
+#pragma unroll
+      for (int i = 0; i < WM; ++i)
+#pragma unroll
+        for (int j = 0; j < WN; ++j) acc[i][j] = mma_f64(af[i].y, bf[j].y, acc[i][j]);
     }
+    if (k0 + DK < kend) {                   // the other buffer: its readers finished before the previous barrier
+      la[buf ^ 1].store(As[buf ^ 1]);
+      lb[buf ^ 1].store(Bs[buf ^ 1]);
+    }
+    lds_barrier();
   };
   if (kbeg < kend) {
-    gload(kbeg);
-    sstore(0);
+    gload(0, kbeg);
+    gload(1, kbeg + DK);
+    la[0].store(As[0]);
+    lb[0].store(Bs[0]);
   }
-  __syncthreads();
-  int buf = 0;
-  for (int k0 = kbeg; k0 < kend; k0 += DK) {
-    const bool more = k0 + DK < kend;
-    if (more) gload(k0 + DK);
-#pragma unroll
-    for (int ks = 0; ks < DK / 4; ++ks) {
-      double af[WT], bf[WT];
-      const int kk = ks * 4 + (lane >> 4);
-#pragma unroll
-      for (int i = 0; i < WT; ++i) af[i] = As[buf][kk][wm * 16 * WT + i * 16 + (lane & 15)];
-#pragma unroll
-      for (int j = 0; j < WT; ++j) bf[j] = Bs[buf][kk][wn * 16 * WT + j * 16 + (lane & 15)];
-#pragma unroll
-      for (int i = 0; i < WT; ++i)
-#pragma unroll
-        for (int j = 0; j < WT; ++j) acc[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(af[i], bf[j], acc[i][j], 0, 0, 0);
-    }
-    if (more) sstore(buf ^ 1);   // the other buffer: its readers finished before the previous barrier
-    __syncthreads();
-    buf ^= 1;
+  lds_barrier();
+  for (int k0 = kbeg; k0 < kend; k0 += 2 * DK) {
+    stage(0, k0);
+    if (k0 + DK < kend) stage(1, k0 + DK);
   }
 #pragma unroll
-  for (int i = 0; i < WT; ++i)
+  for (int i = 0; i < WM; ++i)
 #pragma unroll
-    for (int j = 0; j < WT; ++j) {
-      const int n = n0 + wn * 16 * WT + j * 16 + (lane & 15);
+    for (int j = 0; j < WN; ++j) {
+      const int n = n0 + wn + 16 * j + l16;
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
-        const int m = m0 + wm * 16 * WT + i * 16 + 4 * r + (lane >> 4);
-        if (m < M && n < N) {
-          double* c = C + (long long)m * p.ldc + n;
-          const double v = p.alpha * acc[i][j][r];
-          *c = (p.beta == 0.0) ? v : v + p.beta * (*c);
-        }
+        const int m = m0 + wm + 16 * i + 4 * r + lq;
+        if (m < p.M && n < p.N) p.C[(long long)m * p.ldc + n] = acc[i][j][r];
       }
     }
 }
 
-// spare workgroups a short launch of the factorisation chain carries for the ride-along job: about as many units as
-// HBM moves in the ~30 us such a launch takes (1024, 1536 and 2048 units per launch with 2, 3 and 4 per workgroup were
-// timed on the benchmark's module: 1536 at 3 is the best by a little; the launches grow by about half of what they hide)
-static int cojob_spare_blocks(const CoJob* cj, int own, int cap) {
-  if (!cj || !cj->ticket || cj->take <= 0) return 0;
-  int h = 1536 / cj->take;
-  if (h > cap - own) h = cap - own;
-  return h > 0 ? h : 0;
-}
+// Tile of a product by its grid: 128 x 128 tiles read the fewest operand bytes per flop but need enough of them to fill
+// the chip; below that the longest tile (whole K) sets the run time and a smaller one ends sooner.
+constexpr int DGEMM_T128 = 1000, DGEMM_T64 = 2000;
 
-static strp_status dgemm_launch(strp_ctx* ctx, const DgemmP& pin, int batch, const CoJob* cj = nullptr) {
+static inline bool aligned_vec(const void* p, long long ld) { return ((uintptr_t)p & 15u) == 0 && (ld & 1) == 0; }
+
+template <bool AKC, bool BKC>
+static strp_status dgemm_launch(strp_ctx* ctx, const DgemmP& pin) {
   DgemmP p = pin;
-  if (p.M <= 0 || p.N <= 0 || batch <= 0) return STRP_OK;
-  // 64 x 64 tiles throughout: a block is a serial chain of fp64 matrix-core instructions, the grids here are a few
-  // thousand tiles at most, and with triangular K ranges small tiles balance far better (measured 20 % faster than
-  // 128 x 128 tiles on the 4096 x 4915 solves)
-  constexpr int ts = 64;
-  dim3 grid((p.M + ts - 1) / ts, (p.N + ts - 1) / ts, batch);
-  p.own_x = 0;
-  CoJob job;
-  memset(&job, 0, sizeof(job));
-  const int own = (int)(grid.x * grid.y * grid.z);
-  const int spare = cojob_spare_blocks(cj, own, 1024);   // four workgroups of this kernel fit a CU
-  if (spare > 0) {
-    job = *cj;
-    p.own_x = (int)grid.x;
-    grid.x += (unsigned)((spare + grid.y * grid.z - 1) / (grid.y * grid.z));
-  }
-  hipLaunchKernelGGL((dgemm_kernel<2>), grid, dim3(256), 0, ctx->stream, p, job);
+  if (p.M <= 0 || p.N <= 0) return STRP_OK;
+  p.vec = aligned_vec(p.A, p.lda) && aligned_vec(p.B, p.ldb);
+  auto tiles = [&](int tm, int tn) { return (long long)((p.M + tm - 1) / tm) * ((p.N + tn - 1) / tn) / (p.lower ? 2 : 1); };
+  const long long t128 = tiles(128, 128), t64 = tiles(64, 64);
+  if (t128 >= DGEMM_T128)
+    hipLaunchKernelGGL((dgemm_kernel<128, 128, 16, AKC, BKC>), dim3(((p.M + 127) / 128) * ((p.N + 127) / 128)), dim3(256), 0, ctx->stream, p);
+  else if (t64 >= DGEMM_T64)
+    hipLaunchKernelGGL((dgemm_kernel<64, 64, 32, AKC, BKC>), dim3(((p.M + 63) / 64) * ((p.N + 63) / 64)), dim3(256), 0, ctx->stream, p);
+  else
+    hipLaunchKernelGGL((dgemm_kernel<64, 32, 32, AKC, BKC>), dim3(((p.M + 63) / 64) * ((p.N + 31) / 32)), dim3(256), 0, ctx->stream, p);
   STRP_HIP(ctx, hipGetLastError());
   return STRP_OK;
 }
 
-strp_status dgemm(strp_ctx* ctx, int M, int N, int K, double alpha, const double* A, long long rsa, long long csa,
-                  const double* B, long long rsb, long long csb, double beta, double* C, long long ldc, int lower, int tri) {
+// Lower triangle (128-row tiles on or below the diagonal) of S = Linv^T Linv, Linv lower triangular.
+strp_status gram_of_inverse(strp_ctx* ctx, const double* Linv, int n, long long ldl, double* S, long long lds) {
   DgemmP p;
   memset(&p, 0, sizeof(p));
-  p.M = M; p.N = N; p.K = K; p.alpha = alpha; p.beta = beta;
-  p.A = A; p.rsa = rsa; p.csa = csa; p.B = B; p.rsb = rsb; p.csb = csb; p.C = C; p.ldc = ldc; p.lower = lower; p.tri = tri;
-  return dgemm_launch(ctx, p, 1);
+  p.M = n; p.N = n; p.K = n; p.A = Linv; p.lda = ldl; p.B = Linv; p.ldb = ldl; p.C = S; p.ldc = lds; p.lower = 1; p.tri = 3;
+  return dgemm_launch<false, false>(ctx, p);
 }
 
 // ---------------------------------------------------------------------------------------------
-// Diagonal block: Cholesky of a jb x jb block (jb <= 64) and the inverse of its factor
+// 64 x 64 tiles of the factorisation chain
 // ---------------------------------------------------------------------------------------------
 __device__ __forceinline__ double rsqrt_f64(double d) {
   double y = __builtin_amdgcn_rsq(d);
@@ -196,317 +223,692 @@ __device__ __forceinline__ double rsqrt_f64(double d) {
   y = y * (1.5 - 0.5 * d * y * y);
   return y;
 }
+// lane L of every 16-lane row, to that row's lanes
+template <int L>
+__device__ __forceinline__ double row_bcast(double x) { return __builtin_amdgcn_mov_dpp(x, 0x150 + L, 0xf, 0xf, true); }
 
-// Thread (ty, tx) of the 16x16 block keeps the 16 elements (ty + 16 ii, tx + 16 kk) of the working block AND of
-// the inverse being built in registers for the whole factorisation.  Four columns are eliminated per barrier:
-// the four columns of the block and rows j0..j0+3 of the inverse go through LDS (double buffered), every thread
-// factors the 4 x 4 pivot block redundantly (A = Lu D Lu^T, Lu unit lower), eliminates the four panel entries of
-// the eight row indices it needs (p_c(x) = P(x,c) - sum_{c'<c} p_c'(x) u_{c,c'}), and applies the rank-4 update
-//   a_ik -= sum_c (p_c(i) / d_c) p_c(k)            (unpredicated: entries of finished columns are never re-read)
-//   V_i. -= sum_c (p_c(i) / d_c) q_c(.)  for i > j0 + c,   q_c = row j0 + c of the inverse, eliminated likewise
-// so that V ends as Lu^-1 and L^-1 = D^-1/2 Lu^-1.
-struct PotrfShared {
-  double colb[2][4][NB];
-  double rowb[2][4][NB];
-  double rsd[NB];          // d_j^-1/2
+constexpr int F64_IMG = NB * (NB + 4);    // doubles of the larger image of a 64 x 64 tile
+constexpr int SL = NB + 1;                // pitch of the square working tiles of the diagonal block
+struct StepShared {
+  double a[F64_IMG];
+  double b[F64_IMG];
+  double piv[NB];
 };
 
-// On return (after its closing barrier): sh.rsd holds the inverse square roots of the pivots and v the unit-lower
-// inverse (L^-1 = diag(rsd) v) at this thread's 16 positions.  The factor of the block itself is not formed: every
-// consumer (panel multiplication, triangular inverse) works with the inverse.  report: this block raises ENOTPD.
-__device__ __forceinline__ void potrf_block(const double* A, long long ld, int jb, PotrfShared& sh, double (&v)[4][4], int32_t* status,
-                                            bool report) {
-  auto& colb = sh.colb;
-  auto& rowb = sh.rowb;
-  auto& rsd = sh.rsd;
-  const int tid = threadIdx.x, tx = tid & 15, ty = tid >> 4;
-  double a[4][4];
+// Diagonal block: A = Lu D Lu^T (Lu unit lower) by 16-column panels, and W = Lu^-1.
+//   in : S = sh.a, pitch SL, lower triangle (rows past a ragged edge are the identity)
+//   out: sh.b, pitch SL: W (strict upper part of the 16 x 16 diagonal blocks zero, blocks above them untouched);
+//        sh.piv: the pivots D.  L^-1 = D^-1/2 W.
+// The chain of 64 dependent pivots is what bounds it, so one wavefront runs it out of registers: every 16-lane row of
+// the wavefront holds a copy of the panel's 16 x 16 diagonal block (d: lane = row, register = column), so pivots and
+// multiplier rows are broadcast by row_newbcast moves (no LDS, no barrier, no scalar registers); beside it lanes 16 .. 63
+// hold the rows below (a) and lanes 0 .. 15 the columns of an identity, which the same operation turns into the inverse of
+// the diagonal block.  The three other wavefronts meanwhile form the
+// finished rows of W on the matrix cores, and all four apply a finished panel to the columns behind it.
+// Source order is issue order here (sched_barrier): one piece of the next pivot's chain (broadcast, reciprocal, its
+// refinement) after each column update, so that its latency runs under the updates.
+struct PanelRegs {
+  double d[16], a[16];
+  double dj, y, e;      // pivot, its reciprocal (in the making)
+};
+// v_rcp_f64 is good to 2^-23; y (1 + e + e^2), e = 1 - d y, leaves e^3
+constexpr int PIVOT_STAGES = 5;
+template <int STAGE>
+__device__ __forceinline__ void pivot_stage(PanelRegs& g, double next, double* piv) {
+  if constexpr (STAGE == 0) {
+    g.dj = next;
+    *piv = next;
+  }
+  if constexpr (STAGE == 1) g.y = __builtin_amdgcn_rcp(g.dj);
+  if constexpr (STAGE == 2) g.e = __builtin_fma(-g.dj, g.y, 1.0);
+  if constexpr (STAGE == 3) g.e = __builtin_fma(g.e, g.e, g.e);
+  if constexpr (STAGE == 4) g.y = __builtin_fma(g.e, g.y, g.y);
+  __builtin_amdgcn_sched_barrier(0);
+}
+template <int STAGE>
+__device__ __forceinline__ void pivot_rest(PanelRegs& g, double next, double* piv) {
+  if constexpr (STAGE < PIVOT_STAGES) {
+    pivot_stage<STAGE>(g, next, piv);
+    pivot_rest<STAGE + 1>(g, next, piv);
+  }
+}
+// x: the broadcast for column K, already under way
+template <int J, int K>
+__device__ __forceinline__ void panel_cols(PanelRegs& g, double x, double md, double ma, double* piv) {
+  if constexpr (K < 16) {
+    double xn = 0.0;
+    if constexpr (K < 15) xn = row_bcast<(K < 15 ? K + 1 : 15)>(g.d[J]);
+    g.d[K] = __builtin_fma(md, x, g.d[K]);
+    g.a[K] = __builtin_fma(ma, x, g.a[K]);
+    double next = 0.0;
+    if constexpr (K == J + 1) next = row_bcast<K>(g.d[K]);
+    if constexpr (K - J - 1 < PIVOT_STAGES) pivot_stage<K - J - 1>(g, next, piv + J + 1);
+    panel_cols<J, K + 1>(g, xn, md, ma, piv);
+  } else if constexpr (J < 15 && 15 - J < PIVOT_STAGES) {
+    pivot_rest<15 - J>(g, 0.0, piv + J + 1);
+  }
+}
+template <int J>
+__device__ __forceinline__ void panel_steps(PanelRegs& g, double* lrow, double* piv) {
+  if constexpr (J < 16) {
+    double x = 0.0;
+    if constexpr (J < 15) x = row_bcast<(J < 15 ? J + 1 : 15)>(g.d[J]);
+    const double md = -(g.d[J] * g.y), ma = g.a[J] * g.y;
+    lrow[J] = ma;
+    panel_cols<J, J + 1>(g, x, md, -ma, piv);
+    panel_steps<J + 1>(g, lrow, piv);
+  }
+}
+
+__device__ __forceinline__ void diag_block(StepShared& sh, int tid) {
+  double* S = sh.a;
+  double* W = sh.b;
+  const int lane = tid & 63, wave = tid >> 6;
+  const int l16 = lane & 15, lq = lane >> 4;
+  // W(i, c) = -W(i, i) sum_{k = c}^{i-1} Lu(i, k) W(k, c), 16 x 16 blocks; one wavefront
+  auto w_block = [&](int i, int c) {
+    doublex4 ts[4];
 #pragma unroll
-  for (int ii = 0; ii < 4; ++ii)
+    for (int s = 0; s < 4; ++s) ts[s] = doublex4{0.0, 0.0, 0.0, 0.0};
+    for (int k = c; k < i; ++k)
 #pragma unroll
-    for (int kk = 0; kk < 4; ++kk) {
-      const int i = ty + 16 * ii, k = tx + 16 * kk;
-      a[ii][kk] = (i < jb && k <= i) ? A[(long long)i * ld + k] : ((i == k) ? 1.0 : 0.0);
-      v[ii][kk] = (i == k) ? 1.0 : 0.0;
+      for (int s = 0; s < 4; ++s)
+        ts[s] = mma_f64(S[(16 * i + l16) * SL + 16 * k + 4 * s + lq], W[(16 * k + 4 * s + lq) * SL + 16 * c + l16], ts[s]);
+    const doublex4 t = (ts[0] + ts[1]) + (ts[2] + ts[3]);
+    doublex4 u[2];
+    u[0] = u[1] = doublex4{0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+    for (int s = 0; s < 4; ++s)
+      u[s & 1] = mma_f64(W[(16 * i + l16) * SL + 16 * i + 4 * s + lq], t[s], u[s & 1]);     // a result register is the next B operand
+#pragma unroll
+    for (int r = 0; r < 4; ++r) W[(16 * i + 4 * r + lq) * SL + 16 * c + l16] = -(u[0][r] + u[1][r]);
+  };
+  // S(i, k) -= Lu(i, p) D Lu(k, p)^T, one 16 x 16 block by one wavefront
+  auto s_update = [&](int i, int k, int p) {
+    doublex4 acc[2];
+    acc[0] = acc[1] = doublex4{0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+    for (int s = 0; s < 4; ++s) {
+      const int kk = 16 * p + 4 * s + lq;
+      acc[s & 1] = mma_f64(S[(16 * i + l16) * SL + kk], S[(16 * k + l16) * SL + kk] * sh.piv[kk], acc[s & 1]);
     }
-  // rounds j0 = 16 hi + lo16: the outer loop is unrolled so that the register rows and columns a round publishes
-  // (index hi) are compile-time choices
 #pragma unroll
-  for (int hi = 0; hi < 4; ++hi)
+    for (int r = 0; r < 4; ++r) S[(16 * i + 4 * r + lq) * SL + 16 * k + l16] -= acc[0][r] + acc[1][r];
+  };
 #pragma unroll 1
-  for (int lo16 = 0; lo16 < 16; lo16 += 4) {
-    const int j0 = 16 * hi + lo16, buf = (j0 >> 2) & 1;
-    if (tx >= lo16 && tx < lo16 + 4) {      // owners of columns j0 .. j0+3 publish them (rows ty + 16 ii)
+  for (int p = 0; p < 4; ++p) {
+    if (wave == 3) {
+      const int row = (lane + 16 * p) & 63;       // rows below the panel sit in lanes 16 .. 63 - 16 p
+      PanelRegs g;
 #pragma unroll
-      for (int kk = 0; kk < 4; ++kk)
-        if (kk == hi) {
-#pragma unroll
-          for (int ii = 0; ii < 4; ++ii) colb[buf][tx - lo16][ty + 16 * ii] = a[ii][kk];
-        }
-    }
-    if (ty >= lo16 && ty < lo16 + 4) {      // owners of rows j0 .. j0+3 of the inverse publish them
-#pragma unroll
-      for (int ii = 0; ii < 4; ++ii)
-        if (ii == hi) {
-#pragma unroll
-          for (int kk = 0; kk < 4; ++kk) rowb[buf][ty - lo16][tx + 16 * kk] = v[ii][kk];
-        }
-    }
-    __syncthreads();
-    // ---- 4 x 4 pivot block (every thread, redundantly) --------------------------------------------
-    const double (*cb)[NB] = colb[buf];
-    const double D00 = cb[0][j0], D10 = cb[0][j0 + 1], D20 = cb[0][j0 + 2], D30 = cb[0][j0 + 3];
-    const double D11 = cb[1][j0 + 1], D21 = cb[1][j0 + 2], D31 = cb[1][j0 + 3];
-    const double D22 = cb[2][j0 + 2], D32 = cb[2][j0 + 3], D33 = cb[3][j0 + 3];
-    bool ok = true;
-    double rs[4], id[4];
-    ok = ok && D00 > 0.0;
-    rs[0] = rsqrt_f64(D00 > 0.0 ? D00 : 1.0);
-    id[0] = rs[0] * rs[0];
-    const double u10 = D10 * id[0], u20 = D20 * id[0], u30 = D30 * id[0];
-    const double E11 = D11 - D10 * u10, E21 = D21 - D20 * u10, E31 = D31 - D30 * u10;
-    ok = ok && E11 > 0.0;
-    rs[1] = rsqrt_f64(E11 > 0.0 ? E11 : 1.0);
-    id[1] = rs[1] * rs[1];
-    const double u21 = E21 * id[1], u31 = E31 * id[1];
-    const double F22 = D22 - D20 * u20 - E21 * u21, F32 = D32 - D30 * u20 - E31 * u21;
-    ok = ok && F22 > 0.0;
-    rs[2] = rsqrt_f64(F22 > 0.0 ? F22 : 1.0);
-    id[2] = rs[2] * rs[2];
-    const double u32 = F32 * id[2];
-    const double G33 = D33 - D30 * u30 - E31 * u31 - F32 * u32;
-    ok = ok && G33 > 0.0;
-    rs[3] = rsqrt_f64(G33 > 0.0 ? G33 : 1.0);
-    id[3] = rs[3] * rs[3];
-    if (tid == 0) {
-#pragma unroll
-      for (int c = 0; c < 4; ++c) rsd[j0 + c] = rs[c];
-      if (report && !ok) {   // in a ragged block only the pivots inside jb count (the padding is the identity)
-        const bool bad = j0 + 3 < jb || (0 < jb - j0 && !(D00 > 0.0)) || (1 < jb - j0 && !(E11 > 0.0)) || (2 < jb - j0 && !(F22 > 0.0));
-        if (bad) atomicCAS(status, 0, (int)STRP_ENOTPD);
+      for (int c = 0; c < 16; ++c) {
+        g.d[c] = S[(16 * p + l16) * SL + 16 * p + c];
+        g.a[c] = S[row * SL + 16 * p + c];
+        if (lane < 16) g.a[c] = l16 == c ? 1.0 : 0.0;
       }
+      // lanes without a row below write their multipliers to the image's unused tail: no branches in the chain
+      double* lrow = S + (lane >= 16 && lane < 64 - 16 * p ? row * SL + 16 * p : NB * SL + lane);
+      pivot_rest<0>(g, row_bcast<0>(g.d[0]), sh.piv + 16 * p);
+      panel_steps<0>(g, lrow, sh.piv + 16 * p);
+      if (lane < 16) {
+#pragma unroll
+        for (int k = 0; k < 16; ++k) W[(16 * p + k) * SL + 16 * p + lane] = g.a[k];
+      }
+    } else {
+      // beside panel p: the updates by panel p - 1 that panel p does not need, and the next finished row of W
+      if (p == 1) s_update(wave == 0 ? 2 : 3, wave == 2 ? 3 : 2, 0);
+      if (p == 2 && wave == 2) s_update(3, 3, 1);
+      if (p >= 2 && wave < p - 1) w_block(p - 1, wave);
     }
-    // ---- eliminated panel entries of this thread's rows (pi) and columns (pk) --------------------------
-    double pi[4][4], pk[4][4];   // [c][ii] and [c][kk]
+    lds_barrier();
+    if (p == 3) break;
+    if (wave < 3 - p) s_update(p + 1 + wave, p + 1, p);     // the next panel's columns
+    lds_barrier();
+  }
+  if (wave < 3) w_block(3, wave);
+  lds_barrier();
+}
+
+// One launch of the chain: everything that step t can do once the steps before it are complete.  Panels are 64 columns
+// (tile index = row or column / 64); A is factored in place below its diagonal tiles, Linv is built beside it by
+// carrying the identity through the same elimination (its row i holds partial sums V until step i).  Panel t - 1 is
+// applied to the tiles behind it by launch t ("pending"):
+//   P(t + 1):  L(t+1, t) = A(t+1, t) L(t, t)^-T,  A(t+1, t+1) -= L(t+1, t) L(t+1, t)^T, and the factor of that diagonal
+//              tile, inverted: Linv(t+1, t+1)
+//   P(i):      L(i, t) = (A(i, t) - L(i, t-1) L(t, t-1)^T) L(t, t)^-T,  A(i, i) -= L(i, t) L(i, t)^T
+//   P(t + 2):  the same, and what the next launch's first task would otherwise have to begin with: both panels' part of
+//              A(t+2, t+1), for which it forms L(t+1, t) a second time
+//   R(c):      Linv(t, c) = L(t, t)^-1 (V(t, c) - L(t, t-1) Linv(t-1, c)),  c < t
+//   TA(i, k):  A(i, k) -= L(i, t-1) L(k, t-1)^T,  i > k > t, (i, k) != (t + 2, t + 1)
+//   TV(i, c):  V(i, c) -= L(i, t-1) Linv(t-1, c),  i > t, c < t
+// No workgroup of a launch reads what another one of it writes: the tiles L(t+1, t) go to a buffer of their own (sub)
+// because P(t + 2) reads what they would replace.  A launch costs what P(t + 1) does while the others fit beside it: one
+// and a half 64^3 products at the 0.3 TFLOP/s of one CU and the diagonal tile's chain of 64 pivots.
+// Groups of two or four panels (fewer passes over the tiles behind) were slower at every order up to 4915.
+struct StepP {
+  double* A; long long ld;
+  double* V; long long ldv;     // Linv
+  double* sub;                  // [tiles][NB * NB] L(t, t - 1)
+  int n, N;                     // order, tiles
+  int t;
+  int each;                     // tiles of TA and TV per workgroup
+  int own;                      // workgroups past own are spare ones for the ride-along job
+  int32_t* status;
+};
+
+// 64 x 64 global tile (row-major) -> registers; rows [0, rv) and columns [0, cv) are valid
+struct TileRegs {
+  doublex2 r[8];
+  __device__ __forceinline__ void load(const double* src, long long ld, int rv, int cv) {
+    const int ch = threadIdx.x & 31, row0 = threadIdx.x >> 5;
+    if (rv >= NB && cv >= NB) {
 #pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      const int xi = ty + 16 * q, xk = tx + 16 * q;
-      pi[0][q] = cb[0][xi];
-      pi[1][q] = cb[1][xi] - pi[0][q] * u10;
-      pi[2][q] = cb[2][xi] - pi[0][q] * u20 - pi[1][q] * u21;
-      pi[3][q] = cb[3][xi] - pi[0][q] * u30 - pi[1][q] * u31 - pi[2][q] * u32;
-      pk[0][q] = cb[0][xk];
-      pk[1][q] = cb[1][xk] - pk[0][q] * u10;
-      pk[2][q] = cb[2][xk] - pk[0][q] * u20 - pk[1][q] * u21;
-      pk[3][q] = cb[3][xk] - pk[0][q] * u30 - pk[1][q] * u31 - pk[2][q] * u32;
-    }
-    // rows j0 + c of the inverse, eliminated among themselves, at this thread's columns
-    const double (*rb)[NB] = rowb[buf];
-    double qk[4][4];
+      for (int q = 0; q < 8; ++q) r[q] = *(const doublex2*)(src + (long long)(row0 + 8 * q) * ld + 2 * ch);
+    } else {
 #pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      const int xk = tx + 16 * q;
-      qk[0][q] = rb[0][xk];
-      qk[1][q] = rb[1][xk] - u10 * qk[0][q];
-      qk[2][q] = rb[2][xk] - u20 * qk[0][q] - u21 * qk[1][q];
-      qk[3][q] = rb[3][xk] - u30 * qk[0][q] - u31 * qk[1][q] - u32 * qk[2][q];
-    }
-    // ---- rank-4 updates ------------------------------------------------------------------------
-#pragma unroll
-    for (int ii = 0; ii < 4; ++ii) {
-      const int row = ty + 16 * ii;
-#pragma unroll
-      for (int c = 0; c < 4; ++c) {
-        const double m = pi[c][ii] * id[c];
-        const double mv = row > j0 + c ? m : 0.0;
-#pragma unroll
-        for (int kk = 0; kk < 4; ++kk) {
-          a[ii][kk] = __builtin_fma(-m, pk[c][kk], a[ii][kk]);
-          v[ii][kk] = __builtin_fma(-mv, qk[c][kk], v[ii][kk]);
-        }
+      for (int q = 0; q < 8; ++q) {
+        const int row = row0 + 8 * q;
+        const double* p = src + (long long)row * ld + 2 * ch;
+        r[q] = doublex2{(row < rv && 2 * ch < cv) ? p[0] : 0.0, (row < rv && 2 * ch + 1 < cv) ? p[1] : 0.0};
       }
     }
   }
-  __syncthreads();
+  __device__ __forceinline__ void store_kc(double* img) const {
+    const int ch = threadIdx.x & 31, row0 = threadIdx.x >> 5;
+#pragma unroll
+    for (int q = 0; q < 8; ++q) *(doublex2*)(img + kc_off<NB>(2 * ch, row0 + 8 * q)) = r[q];
+  }
+  __device__ __forceinline__ void store_rc(double* img) const {
+    const int ch = threadIdx.x & 31, row0 = threadIdx.x >> 5;
+#pragma unroll
+    for (int q = 0; q < 8; ++q) *(doublex2*)(img + rc_off<NB>(row0 + 8 * q, 2 * ch)) = r[q];
+  }
+};
+
+// acc += tile product over contraction steps [8 c0, 8 c1) of two LDS images (A always KC)
+template <bool BKC>
+__device__ __forceinline__ void tile_mma(const double* ia, const double* ib, int wm, int wn, int lane, int c0, int c1, doublex4 (&acc)[2][2]) {
+  const int l16 = lane & 15, lq = lane >> 4;
+#pragma unroll 2
+  for (int c = c0; c < c1; ++c) {
+    const int k = 8 * c + 2 * lq;
+    doublex2 af[2], bf[2];
+#pragma unroll
+    for (int i = 0; i < 2; ++i) af[i] = *(const doublex2*)(ia + kc_off<NB>(k, wm + 16 * i + l16));
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+      if (BKC) bf[j] = *(const doublex2*)(ib + kc_off<NB>(k, wn + 16 * j + l16));
+      else bf[j] = doublex2{ib[rc_off<NB>(k, wn + 16 * j + l16)], ib[rc_off<NB>(k + 1, wn + 16 * j + l16)]};
+    }
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+      for (int j = 0; j < 2; ++j) acc[i][j] = mma_f64(af[i].x, bf[j].x, acc[i][j]);
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+      for (int j = 0; j < 2; ++j) acc[i][j] = mma_f64(af[i].y, bf[j].y, acc[i][j]);
+  }
 }
 
-// One 64-column step of the factorisation in one launch.  Every block factors the (already updated) diagonal block
-// itself -- the chip is idle during these steps, and a separate one-block launch would only add a kernel boundary to
-// the critical path.  Block 0 stores the inverse of the block's factor; block b >= 1 multiplies rows [64 (b-1), +64)
-// of the panel below the diagonal block by L^-T in place.  The diagonal block itself is only read (all blocks load
-// it; nobody writes it), so blocks that start at different times cannot see each other's output.
-// Blocks past `own` are spare workgroups for the ride-along job (cojob.h).
-__global__ __launch_bounds__(256) void potrf_panel_kernel(double* Ajj, long long ld, int jb, int rest, double* invd, int32_t* status, int own,
-                                                          const CoJob job) {
-  __shared__ PotrfShared sh;
-  __shared__ double Ms[NB][NB + 1];   // Ms[k][c] = Linv[c][k]
-  __shared__ double Xs[NB][NB + 1];
-  if ((int)blockIdx.x >= own) {
+// Products with a triangular operand: the wavefront pair that shares it takes 16-wide tiles {0, 3} and {1, 2} of the
+// triangular side, 10 eight-step chunks each, instead of 6 against 14.
+__device__ __forceinline__ int tri_tile(int half, int j) { return half ? 1 + j : 3 * j; }
+// acc[i][j] = T (rows wm + 16 i) times M^T (columns 16 tri_tile(half, j)), M lower triangular; both KC images.  Even and odd
+// contraction steps are summed apart: a chain on one accumulator runs at the instruction's latency, four keep it busy.
+__device__ __forceinline__ void mma_lower_t(const double* it, const double* im, int wm, int half, int lane, doublex4 (&acc)[2][2]) {
+  const int l16 = lane & 15, lq = lane >> 4;
+#pragma unroll
+  for (int j = 0; j < 2; ++j) {
+    const int nt = tri_tile(half, j);
+    doublex4 s[2][2];
+#pragma unroll
+    for (int i = 0; i < 2; ++i) s[i][0] = s[i][1] = doublex4{0.0, 0.0, 0.0, 0.0};
+#pragma unroll 2
+    for (int c = 0; c < 2 * (nt + 1); ++c) {
+      const int k = 8 * c + 2 * lq;
+      const doublex2 b = *(const doublex2*)(im + kc_off<NB>(k, 16 * nt + l16));
+#pragma unroll
+      for (int i = 0; i < 2; ++i) {
+        const doublex2 a = *(const doublex2*)(it + kc_off<NB>(k, wm + 16 * i + l16));
+        s[i][0] = mma_f64(a.x, b.x, s[i][0]);
+        s[i][1] = mma_f64(a.y, b.y, s[i][1]);
+      }
+    }
+#pragma unroll
+    for (int i = 0; i < 2; ++i) acc[i][j] = s[i][0] + s[i][1];
+  }
+}
+// acc[i][j] = M (rows 16 tri_tile(half, i), lower triangular, KC image) times T (columns wn + 16 j, RC image)
+__device__ __forceinline__ void mma_lower(const double* im, const double* it, int half, int wn, int lane, doublex4 (&acc)[2][2]) {
+  const int l16 = lane & 15, lq = lane >> 4;
+#pragma unroll
+  for (int i = 0; i < 2; ++i) {
+    const int mt = tri_tile(half, i);
+    doublex4 s[2][2];
+#pragma unroll
+    for (int j = 0; j < 2; ++j) s[j][0] = s[j][1] = doublex4{0.0, 0.0, 0.0, 0.0};
+#pragma unroll 2
+    for (int c = 0; c < 2 * (mt + 1); ++c) {
+      const int k = 8 * c + 2 * lq;
+      const doublex2 a = *(const doublex2*)(im + kc_off<NB>(k, 16 * mt + l16));
+#pragma unroll
+      for (int j = 0; j < 2; ++j) {
+        s[j][0] = mma_f64(a.x, it[rc_off<NB>(k, wn + 16 * j + l16)], s[j][0]);
+        s[j][1] = mma_f64(a.y, it[rc_off<NB>(k + 1, wn + 16 * j + l16)], s[j][1]);
+      }
+    }
+#pragma unroll
+    for (int j = 0; j < 2; ++j) acc[i][j] = s[j][0] + s[j][1];
+  }
+}
+
+// the 64 x 64 tile at `src` in the accumulator layout (this lane's 16 elements; past a ragged edge the edge's)
+__device__ __forceinline__ void load_acc(const double* src, long long ld, int rv, int cv, int wm, int wn, int lane, doublex4 (&c)[2][2]) {
+  const int l16 = lane & 15, lq = lane >> 4;
+  const bool full = rv >= NB && cv >= NB;
+#pragma unroll
+  for (int i = 0; i < 2; ++i)
+#pragma unroll
+    for (int j = 0; j < 2; ++j)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        // a clamped address keeps the ragged case free of branches
+        int m = wm + 16 * i + 4 * r + lq, k = wn + 16 * j + l16;
+        if (!full) {
+          m = m < rv ? m : rv - 1;
+          k = k < cv ? k : cv - 1;
+        }
+        c[i][j][r] = src[(long long)m * ld + k];
+      }
+}
+__device__ __forceinline__ void store_acc(double* dst, long long ld, int rv, int cv, int wm, int wn, int lane, const doublex4 (&c)[2][2]) {
+  const int l16 = lane & 15, lq = lane >> 4;
+  const bool full = rv >= NB && cv >= NB;
+#pragma unroll
+  for (int i = 0; i < 2; ++i)
+#pragma unroll
+    for (int j = 0; j < 2; ++j)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int m = wm + 16 * i + 4 * r + lq, k = wn + 16 * j + l16;
+        if (full || (m < rv && k < cv)) dst[(long long)m * ld + k] = c[i][j][r];
+      }
+}
+__device__ __forceinline__ void zero_acc(doublex4 (&c)[2][2]) {
+#pragma unroll
+  for (int i = 0; i < 2; ++i)
+#pragma unroll
+    for (int j = 0; j < 2; ++j) c[i][j] = doublex4{0.0, 0.0, 0.0, 0.0};
+}
+
+// factor the diagonal tile in sh.a and write the inverse of its factor to Linv's diagonal tile
+template <typename Beside>
+__device__ __forceinline__ void finish_diag(const StepP& p, int t, StepShared& sh, Beside beside) {
+  const int tid = threadIdx.x;
+  if (tid < 192) beside();            // what the wavefronts off the pivot chain still have to store
+  diag_block(sh, tid);
+  if (tid >= 192) beside();
+  const int jb = p.n - t * NB < NB ? p.n - t * NB : NB;
+  if (tid < NB) {
+    const double d = sh.piv[tid];
+    const bool ok = d > 0.0;
+    if (__any(!ok) && tid == 0) atomicCAS(p.status, 0, (int)STRP_ENOTPD);
+    sh.piv[tid] = rsqrt_f64(ok ? d : 1.0);
+  }
+  lds_barrier();
+  double* vd = p.V + (long long)t * NB * p.ldv + (long long)t * NB;
+  const int k = 2 * (tid & 31), i0 = tid >> 5;
+#pragma unroll
+  for (int q = 0; q < 8; ++q) {
+    const int i = i0 + 8 * q;
+    const double rs = sh.piv[i], w0 = sh.b[i * SL + k], w1 = sh.b[i * SL + k + 1];      // read whether used or not: no branch
+    const doublex2 v = doublex2{k <= i ? w0 * rs : 0.0, k + 1 <= i ? w1 * rs : 0.0};
+    if (i < jb && k + 1 < jb) *(doublex2*)(vd + (long long)i * p.ldv + k) = v;
+    else if (i < jb && k < jb) vd[(long long)i * p.ldv + k] = v.x;
+  }
+}
+
+// this lane's elements of a result whose columns are 16 tri_tile(half, j), into a KC image (row = m, k = n)
+__device__ __forceinline__ void put_kc_tri(double* img, int wm, int half, int lane, const doublex4 (&acc)[2][2]) {
+#pragma unroll
+  for (int i = 0; i < 2; ++i)
+#pragma unroll
+    for (int j = 0; j < 2; ++j)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) img[kc_off<NB>(16 * tri_tile(half, j) + (lane & 15), wm + 16 * i + 4 * r + (lane >> 4))] = acc[i][j][r];
+}
+
+// P(i) of launch t.  FIRST: i = t + 1 (nothing pending, factors the diagonal tile).  lookahead: i = t + 2.
+template <bool FIRST>
+__device__ __forceinline__ void step_panel(const StepP& p, StepShared& sh, int i, bool lookahead) {
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int wm = (wave >> 1) * 32, wn = (wave & 1) * 32, half = wave & 1;
+  const int l16 = lane & 15, lq = lane >> 4;
+  const int t = p.t;
+  const int rows = p.n - i * NB, jb = rows < NB ? rows : NB;
+  auto At = [&](int r, int c) { return p.A + (long long)r * NB * p.ld + (long long)c * NB; };
+  const double* inv_t = p.V + (long long)t * NB * (p.ldv + 1);     // L(t, t)^-1
+  TileRegs ra, rb;
+  doublex4 acc[2][2], acc2[2][2];
+  zero_acc(acc2);
+  if (FIRST || t == 0) {                  // nothing is pending: the tile goes to LDS as it is
+    ra.load(At(i, t), p.ld, rows, NB);
+    rb.load(inv_t, p.ldv, NB, NB);
+    ra.store_kc(sh.a);
+    rb.store_kc(sh.b);
+  } else {
+    doublex4 c[2][2];
+    ra.load(At(i, t - 1), p.ld, rows, NB);
+    rb.load(p.sub + (long long)t * NB * NB, NB, NB, NB);
+    load_acc(At(i, t), p.ld, rows, NB, wm, wn, lane, c);
+    ra.store_kc(sh.a);
+    rb.store_kc(sh.b);
+    lds_barrier();
+    if (lookahead) ra.load(At(t + 1, t - 1), p.ld, NB, NB);
+    rb.load(inv_t, p.ldv, NB, NB);
+    zero_acc(acc);
+    tile_mma<true>(sh.a, sh.b, wm, wn, lane, 0, 8, acc);
+    lds_barrier();
+    if (lookahead) {
+      ra.store_kc(sh.b);
+      lds_barrier();
+      tile_mma<true>(sh.a, sh.b, wm, wn, lane, 0, 8, acc2);
+      lds_barrier();
+    }
+#pragma unroll
+    for (int ii = 0; ii < 2; ++ii)
+#pragma unroll
+      for (int j = 0; j < 2; ++j)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) sh.a[kc_off<NB>(wn + 16 * j + l16, wm + 16 * ii + 4 * r + lq)] = c[ii][j][r] - acc[ii][j][r];
+    rb.store_kc(sh.b);
+  }
+  if (!FIRST && lookahead) ra.load(At(t + 1, t), p.ld, NB, NB);
+  // lower 16 x 16 tiles of the diagonal tile A(i, i): three for wavefronts 0 and 1, two (and one of them again) for 2 and 3
+  const int dn = wave < 2 ? 3 : 2;
+  const auto drow = [&](int q) { return wave == 0 ? (q > 0) : wave == 1 ? 2 : 3; };
+  const auto dcol = [&](int q) { return wave == 0 ? (q > 1) : wave == 1 ? q : wave == 2 ? q : 2 + (q & 1); };
+  doublex4 dc[3];
+#pragma unroll
+  for (int q = 0; q < 3; ++q)
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      int m = 16 * drow(q) + 4 * r + lq, k = 16 * dcol(q) + l16;
+      m = m < jb ? m : jb - 1;
+      k = k < jb ? k : jb - 1;
+      dc[q][r] = At(i, i)[(long long)m * p.ld + k];
+    }
+  lds_barrier();
+  mma_lower_t(sh.a, sh.b, wm, half, lane, acc);
+  lds_barrier();
+  put_kc_tri(sh.a, wm, half, lane, acc);
+  auto store_l = [&] {
+    double* out = FIRST ? p.sub + (long long)i * NB * NB : At(i, t);
+    const long long ldo = FIRST ? NB : p.ld;
+#pragma unroll
+    for (int ii = 0; ii < 2; ++ii)
+#pragma unroll
+      for (int j = 0; j < 2; ++j)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          const int m = wm + 16 * ii + 4 * r + lq;
+          if (FIRST || m < jb) out[(long long)m * ldo + 16 * tri_tile(half, j) + l16] = acc[ii][j][r];
+        }
+  };
+  if (!FIRST) store_l();
+  lds_barrier();
+  {
+    doublex4 s[3][2];
+#pragma unroll
+    for (int q = 0; q < 3; ++q) s[q][0] = s[q][1] = doublex4{0.0, 0.0, 0.0, 0.0};
+#pragma unroll 2
+    for (int cc = 0; cc < 8; ++cc) {
+      const int k = 8 * cc + 2 * lq;
+      doublex2 x[3], y[3];
+#pragma unroll
+      for (int q = 0; q < 3; ++q) {
+        x[q] = *(const doublex2*)(sh.a + kc_off<NB>(k, 16 * drow(q) + l16));
+        y[q] = *(const doublex2*)(sh.a + kc_off<NB>(k, 16 * dcol(q) + l16));
+      }
+#pragma unroll
+      for (int q = 0; q < 3; ++q) s[q][0] = mma_f64(x[q].x, y[q].x, s[q][0]);
+#pragma unroll
+      for (int q = 0; q < 3; ++q) s[q][1] = mma_f64(x[q].y, y[q].y, s[q][1]);
+    }
+#pragma unroll
+    for (int q = 0; q < 3; ++q) dc[q] -= s[q][0] + s[q][1];
+  }
+  if (FIRST) {
+    lds_barrier();
+#pragma unroll
+    for (int q = 0; q < 3; ++q)
+      if (q < dn)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          const int m = 16 * drow(q) + 4 * r + lq, k = 16 * dcol(q) + l16;
+          sh.a[m * SL + k] = m < jb && k < jb ? dc[q][r] : (m == k ? 1.0 : 0.0);
+        }
+    lds_barrier();
+    finish_diag(p, i, sh, store_l);
+    return;
+  }
+#pragma unroll
+  for (int q = 0; q < 3; ++q)
+    if (q < dn)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int m = 16 * drow(q) + 4 * r + lq, k = 16 * dcol(q) + l16;
+        if (m < jb && k < jb) At(i, i)[(long long)m * p.ld + k] = dc[q][r];
+      }
+  if (!lookahead) return;
+  // A(t+2, t+1) -= L(t+2, t-1) L(t+1, t-1)^T (in acc2) + L(t+2, t) L(t+1, t)^T
+  doublex4 c[2][2], lx[2][2];
+  load_acc(At(i, t + 1), p.ld, rows, NB, wm, wn, lane, c);
+  lds_barrier();
+  ra.store_kc(sh.a);
+  lds_barrier();
+  mma_lower_t(sh.a, sh.b, wm, half, lane, lx);
+  lds_barrier();
+  put_kc_tri(sh.a, wm, half, lane, acc);
+  put_kc_tri(sh.b, wm, half, lane, lx);
+  lds_barrier();
+  tile_mma<true>(sh.a, sh.b, wm, wn, lane, 0, 8, acc2);
+#pragma unroll
+  for (int ii = 0; ii < 2; ++ii)
+#pragma unroll
+    for (int j = 0; j < 2; ++j) c[ii][j] -= acc2[ii][j];
+  store_acc(At(i, t + 1), p.ld, rows, NB, wm, wn, lane, c);
+}
+
+__global__ __launch_bounds__(256, 2) void chol_step_kernel(const StepP p, const CoJob job) {
+  __shared__ __attribute__((aligned(16))) StepShared sh;
+  int b = blockIdx.x;
+  if (b >= p.own) {
     cojob_help(job);
     return;
   }
-  const int tid = threadIdx.x, tx = tid & 15, ty = tid >> 4;
-  const int b = blockIdx.x;
-  double* X = Ajj + (long long)jb * ld;          // panel below the diagonal block
-  const int r0 = (b - 1) * NB;
-  // this block's panel rows, requested before the factorisation so that their latency hides behind it
-  double xr[16];
-  if (b > 0) {
-#pragma unroll
-    for (int q = 0; q < 16; ++q) {
-      const int e = tid + 256 * q, i = e >> 6, j = e & 63;
-      xr[q] = (r0 + i < rest && j < jb) ? X[(long long)(r0 + i) * ld + j] : 0.0;
-    }
-  }
-  double v[4][4];
-  potrf_block(Ajj, ld, jb, sh, v, status, b == 0);
-  if (b == 0) {
-#pragma unroll
-    for (int ii = 0; ii < 4; ++ii)
-#pragma unroll
-      for (int kk = 0; kk < 4; ++kk) {
-        const int i = ty + 16 * ii, k = tx + 16 * kk;
-        const bool in = i < jb && k < jb;
-        invd[i * NB + k] = (in && k <= i) ? v[ii][kk] * sh.rsd[i] : 0.0;
-      }
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int wm = (wave >> 1) * 32, wn = (wave & 1) * 32;
+  const int n = p.n, N = p.N, t = p.t;
+  auto rows_of = [&](int i) { return n - i * NB; };
+  auto At = [&](int i, int k) { return p.A + (long long)i * NB * p.ld + (long long)k * NB; };
+  auto Vt = [&](int i, int k) { return p.V + (long long)i * NB * p.ldv + (long long)k * NB; };
+  const int nP = N - 1 - t;
+  if (b < nP) {
+    if (b == 0) step_panel<true>(p, sh, t + 1, false);
+    else step_panel<false>(p, sh, t + 1 + b, b == 1);
     return;
   }
+  b -= nP;
+  doublex4 acc[2][2], c[2][2];
+  zero_acc(acc);
+  zero_acc(c);
+  TileRegs ra, rb;
+  if (b < t) {                                                        // ---- R(c)
+    const int cc = b;
+    ra.load(p.sub + (long long)t * NB * NB, NB, NB, NB);
+    rb.load(Vt(t - 1, cc), p.ldv, NB, NB);
+    if (cc < t - 1) load_acc(Vt(t, cc), p.ldv, rows_of(t), NB, wm, wn, lane, c);
+    ra.store_kc(sh.a);
+    rb.store_rc(sh.b);
+    lds_barrier();
+    ra.load(Vt(t, t), p.ldv, rows_of(t), rows_of(t));
+    tile_mma<false>(sh.a, sh.b, wm, wn, lane, 0, 8, acc);
+    lds_barrier();
 #pragma unroll
-  for (int ii = 0; ii < 4; ++ii)
+    for (int ii = 0; ii < 2; ++ii)
 #pragma unroll
-    for (int kk = 0; kk < 4; ++kk) {
-      const int i = ty + 16 * ii, k = tx + 16 * kk;
-      Ms[k][i] = (i < jb && k <= i) ? v[ii][kk] * sh.rsd[i] : 0.0;
+      for (int j = 0; j < 2; ++j)
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+          sh.b[rc_off<NB>(wm + 16 * ii + 4 * r + (lane >> 4), wn + 16 * j + (lane & 15))] = c[ii][j][r] - acc[ii][j][r];
+    ra.store_kc(sh.a);
+    lds_barrier();
+    mma_lower(sh.a, sh.b, wave >> 1, wn, lane, acc);
+#pragma unroll
+    for (int ii = 0; ii < 2; ++ii)
+#pragma unroll
+      for (int j = 0; j < 2; ++j)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          const int m = 16 * tri_tile(wave >> 1, ii) + 4 * r + (lane >> 4);
+          if (m < rows_of(t)) Vt(t, cc)[(long long)m * p.ldv + wn + 16 * j + (lane & 15)] = acc[ii][j][r];
+        }
+    return;
+  }
+  b -= t;
+  // what is left goes to each workgroup `each` tiles at a time
+  const int m = N - 1 - t;                       // tile rows (and columns of A) behind column t
+  const int nTA = m * (m - 1) / 2 - (m > 1);     // without (t + 2, t + 1), the first of the enumeration
+  const int total = nTA + m * t;
+  for (int e = b * p.each, e1 = e + p.each < total ? e + p.each : total; e < e1; ++e) {
+    if (e > b * p.each) {
+      lds_barrier();
+      zero_acc(acc);
+      zero_acc(c);
     }
+    if (e < nTA) {                                                    // ---- TA(i, k)
+      int i = (int)((__builtin_sqrtf(8.0f * (float)(e + 1) + 1.0f) - 1.0f) * 0.5f);
+      while (i * (i + 1) / 2 > e + 1) --i;
+      while ((i + 1) * (i + 2) / 2 <= e + 1) ++i;
+      const int k = e + 1 - i * (i + 1) / 2 + t + 1;
+      i += t + 2;
+      ra.load(At(i, t - 1), p.ld, rows_of(i), NB);
+      rb.load(At(k, t - 1), p.ld, NB, NB);
+      load_acc(At(i, k), p.ld, rows_of(i), NB, wm, wn, lane, c);
+      ra.store_kc(sh.a);
+      rb.store_kc(sh.b);
+      lds_barrier();
+      tile_mma<true>(sh.a, sh.b, wm, wn, lane, 0, 8, acc);
 #pragma unroll
-  for (int q = 0; q < 16; ++q) {
-    const int e = tid + 256 * q;
-    Xs[e >> 6][e & 63] = xr[q];
-  }
-  __syncthreads();
-  double acc[4][4];
+      for (int ii = 0; ii < 2; ++ii)
 #pragma unroll
-  for (int i = 0; i < 4; ++i)
+        for (int j = 0; j < 2; ++j) c[ii][j] -= acc[ii][j];
+      store_acc(At(i, k), p.ld, rows_of(i), NB, wm, wn, lane, c);
+    } else {                                                          // ---- TV(i, c)
+      const int i = t + 1 + (e - nTA) / t, cc = (e - nTA) % t;
+      ra.load(At(i, t - 1), p.ld, rows_of(i), NB);
+      rb.load(Vt(t - 1, cc), p.ldv, NB, NB);
+      if (cc < t - 1) load_acc(Vt(i, cc), p.ldv, rows_of(i), NB, wm, wn, lane, c);
+      ra.store_kc(sh.a);
+      rb.store_rc(sh.b);
+      lds_barrier();
+      tile_mma<false>(sh.a, sh.b, wm, wn, lane, 0, 8, acc);
 #pragma unroll
-    for (int j = 0; j < 4; ++j) acc[i][j] = 0.0;
-  for (int k = 0; k < jb; ++k) {
-    double a[4], bb[4];
+      for (int ii = 0; ii < 2; ++ii)
 #pragma unroll
-    for (int i = 0; i < 4; ++i) a[i] = Xs[ty * 4 + i][k];
-#pragma unroll
-    for (int j = 0; j < 4; ++j) bb[j] = Ms[k][tx * 4 + j];
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-#pragma unroll
-      for (int j = 0; j < 4; ++j) acc[i][j] = __builtin_fma(a[i], bb[j], acc[i][j]);
-  }
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const int r = r0 + ty * 4 + i;
-    if (r >= rest) continue;
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const int c = tx * 4 + j;
-      if (c < jb) X[(long long)r * ld + c] = acc[i][j];
+        for (int j = 0; j < 2; ++j) c[ii][j] -= acc[ii][j];
+      store_acc(Vt(i, cc), p.ldv, rows_of(i), NB, wm, wn, lane, c);
     }
   }
 }
 
-// Two-level right-looking blocking: 64-column steps (diagonal block + panel) update only the rest of their
-// 256-column outer panel; the trailing matrix is updated once per outer panel with K = 256, which quarters the
-// read-modify-write traffic of the trailing matrix (a rank-64 update of a 4915 x 4915 matrix is memory bound).
-strp_status chol_factor(strp_ctx* ctx, double* A, int n, long long ld, double* invd, int32_t* status) {
-  ProfScope ps(ctx, "chol_factor_f64", (double)n * n * n / 3.0, 8.0 * (double)n * n);
-  constexpr int NB2 = 4 * NB;
-  const CoJob* cj = ctx->cojob;
-  CoJob nojob;
-  memset(&nojob, 0, sizeof(nojob));
-  for (int J0 = 0; J0 < n; J0 += NB2) {
-    const int Jend = (n - J0 < NB2) ? n : J0 + NB2;
-    for (int j0 = J0; j0 < Jend; j0 += NB) {
-      const int jb = (n - j0 < NB) ? (n - j0) : NB;
-      double* Ajj = A + (long long)j0 * ld + j0;
-      double* inv = invd + (long long)(j0 / NB) * NB * NB;
-      const int rest = n - j0 - jb;
-      const int own = 1 + (rest + NB - 1) / NB;
-      const int spare = cojob_spare_blocks(cj, own, 512);   // two workgroups of this kernel fit a CU
-      hipLaunchKernelGGL(potrf_panel_kernel, dim3(own + spare), dim3(256), 0, ctx->stream, Ajj, ld, jb, rest, inv, status, own, spare ? *cj : nojob);
-      STRP_HIP(ctx, hipGetLastError());
-      if (rest <= 0) continue;
-      double* A21 = A + (long long)(j0 + jb) * ld + j0;
-      const int pc = Jend - (j0 + jb);   // columns of the outer panel still to be factored
-      if (pc > 0) {
-        double* A22 = A + (long long)(j0 + jb) * ld + (j0 + jb);
-        DgemmP u;
-        memset(&u, 0, sizeof(u));
-        u.M = rest; u.N = pc; u.K = jb; u.alpha = -1.0; u.beta = 1.0;
-        u.A = A21; u.rsa = ld; u.csa = 1; u.B = A21; u.rsb = 1; u.csb = ld; u.C = A22; u.ldc = ld; u.lower = 1;
-        STRP_TRY(dgemm_launch(ctx, u, 1, cj));
-      }
+// First launch of the chain: block 0 factors diagonal tile 0, the others clear the tiles of Linv above the diagonal.
+__global__ __launch_bounds__(256, 2) void chol_begin_kernel(const StepP p) {
+  __shared__ __attribute__((aligned(16))) StepShared sh;
+  const int tid = threadIdx.x;
+  if (blockIdx.x == 0) {
+    const int jb = p.n < NB ? p.n : NB;
+    const int k = tid & 63;
+#pragma unroll 4
+    for (int q = 0; q < 16; ++q) {
+      const int i = (tid >> 6) + 4 * q;
+      sh.a[i * SL + k] = i < jb && k <= i ? p.A[(long long)i * p.ld + k] : (i == k ? 1.0 : 0.0);
     }
-    const int rest2 = n - Jend;
-    if (rest2 > 0) {
-      const double* P = A + (long long)Jend * ld + J0;
-      double* C = A + (long long)Jend * ld + Jend;
-      STRP_TRY(dgemm(ctx, rest2, rest2, Jend - J0, -1.0, P, ld, 1, P, 1, ld, 1.0, C, ld, 1));
-    }
+    lds_barrier();
+    finish_diag(p, 0, sh, [] {});
+    return;
   }
-  return STRP_OK;
+  const int nt = p.N * (p.N - 1) / 2;
+  for (int e = (int)blockIdx.x - 1; e < nt; e += (int)gridDim.x - 1) {
+    int c = (int)((__builtin_sqrtf(8.0f * (float)e + 1.0f) - 1.0f) * 0.5f);      // tile (r, c + 1), r <= c
+    while (c * (c + 1) / 2 > e) --c;
+    while ((c + 1) * (c + 2) / 2 <= e) ++c;
+    const int r0 = (e - c * (c + 1) / 2) * NB, col = (c + 1) * NB + (tid & 63);
+    if (col < p.n)
+      for (int r = r0 + (tid >> 6); r < r0 + NB; r += 4) p.V[(long long)r * p.ldv + col] = 0.0;
+  }
 }
 
-// Linv = L^-1 (lower triangular, n x n, leading dimension n) from the factor and its inverted 64-blocks.
-// tmp: n x n fp64 scratch.  Doubling: for block size b = 64, 128, ...: V21 = -V22 (L21 V11) for every pair of
-// adjacent diagonal blocks, all pairs of a level in one batched launch.
-__global__ __launch_bounds__(256) void place_diag_blocks_kernel(const double* invd, int n, double* Linv) {
-  const long long e = (long long)blockIdx.x * 256 + threadIdx.x;
-  if (e >= (long long)n * n) return;
-  const int i = (int)(e / n), j = (int)(e % n);
-  double v = 0.0;
-  if ((i / NB) == (j / NB)) v = invd[(long long)(i / NB) * NB * NB + (i % NB) * NB + (j % NB)];
-  Linv[e] = v;
+// spare workgroups of one launch of the chain for the ride-along job: enough for the whole job to be taken within the
+// launches of the iteration's two chains (job.per_launch units each), at two workgroups of this kernel per CU
+static int cojob_spare_blocks(const CoJob* cj, int own, int* take) {
+  if (!cj || !cj->ticket || cj->per_launch <= 0) return 0;
+  int h = 512 - own;
+  if (h < 256) h = 256;
+  *take = (cj->per_launch + h - 1) / h;
+  return (cj->per_launch + *take - 1) / *take;
 }
 
-strp_status tri_inverse(strp_ctx* ctx, const double* L, int n, long long ldl, const double* invd, double* Linv, double* tmp) {
-  ProfScope ps(ctx, "tri_inverse_f64", (double)n * n * n / 3.0, 24.0 * (double)n * n);
-  hipLaunchKernelGGL(place_diag_blocks_kernel, dim3((unsigned)(((long long)n * n + 255) / 256)), dim3(256), 0, ctx->stream, invd, n, Linv);
+int chol_launches(int n) { return (n + NB - 1) / NB + 1; }
+
+// Linv [n x n, ldv] = L^-1 of A = L L^T (lower part of A [n x n, ld], destroyed); upper part of Linv zero.
+// sub: ceil(n / NB) * NB * NB doubles of scratch.  ld and ldv even, A and Linv 16-byte aligned.
+strp_status chol_inverse(strp_ctx* ctx, double* A, int n, long long ld, double* sub, double* Linv, long long ldv, int32_t* status) {
+  if (!aligned_vec(A, ld) || !aligned_vec(Linv, ldv)) return fail(ctx, STRP_EINVAL, "chol_inverse: operands not 16-byte aligned or odd leading dimension");
+  ProfScope ps(ctx, "chol_factor_f64", 2.0 * (double)n * n * n / 3.0, 16.0 * (double)n * n);
+  StepP p;
+  memset(&p, 0, sizeof(p));
+  p.A = A; p.ld = ld; p.V = Linv; p.ldv = ldv; p.sub = sub; p.n = n; p.N = (n + NB - 1) / NB; p.status = status;
+  const int nt = p.N * (p.N - 1) / 2;
+  hipLaunchKernelGGL(chol_begin_kernel, dim3(1 + (nt < 1024 ? nt : 1024)), dim3(256), 0, ctx->stream, p);
+  for (int t = 0; t < p.N; ++t) {
+    p.t = t;
+    const int m = p.N - 1 - t;
+    // up to three tiles each, so that a launch of a small system leaves the critical workgroup a CU of its own
+    const int total = t > 0 ? m * (m - 1) / 2 - (m > 1) + m * t : 0;
+    p.each = (total + 191) / 192;
+    if (p.each > 3) p.each = total > 1024 ? 1 : 3;
+    if (p.each < 1) p.each = 1;
+    p.own = m + t + (total + p.each - 1) / p.each;
+    if (p.own == 0) continue;      // a single tile: the first launch was all
+    CoJob job;
+    memset(&job, 0, sizeof(job));
+    int take = 0;
+    const int spare = cojob_spare_blocks(ctx->cojob, p.own, &take);
+    if (spare > 0) {
+      job = *ctx->cojob;
+      job.take = take;
+    }
+    hipLaunchKernelGGL(chol_step_kernel, dim3(p.own + spare), dim3(256), 0, ctx->stream, p, job);
+  }
   STRP_HIP(ctx, hipGetLastError());
-  for (int b = NB; b < n; b <<= 1) {
-    const int pairs = (n - b + 2 * b - 1) / (2 * b);   // pairs whose second block is non-empty
-    DgemmP p;
-    memset(&p, 0, sizeof(p));
-    // tmp21 = L21 V11
-    p.M = b; p.N = b; p.K = b; p.alpha = 1.0; p.beta = 0.0;
-    p.A = L + (long long)b * ldl; p.rsa = ldl; p.csa = 1;
-    p.B = Linv; p.rsb = n; p.csb = 1;
-    p.C = tmp + (long long)b * n; p.ldc = n;
-    p.sa = 2LL * b * ldl + 2LL * b; p.sb = 2LL * b * n + 2LL * b; p.sc = p.sb;
-    p.lim_base = n - b; p.lim_step = 2 * b; p.lower = 0;
-    p.tri = 2;   // V11 is lower triangular
-    STRP_TRY(dgemm_launch(ctx, p, pairs));
-    // V21 = -V22 tmp21   (M and K both limited to the rows of the second block)
-    p.alpha = -1.0;
-    p.A = Linv + (long long)b * n + b; p.rsa = n; p.csa = 1; p.sa = p.sb;
-    p.B = tmp + (long long)b * n; p.rsb = n; p.csb = 1;
-    p.C = Linv + (long long)b * n; p.ldc = n;
-    p.clamp_k = 1;
-    p.tri = 4;   // V22 is lower triangular
-    STRP_TRY(dgemm_launch(ctx, p, pairs));
-  }
   return STRP_OK;
 }
 
-// X <- X (L L^T)^-1 = (X Linv^T) Linv for X [m x n] (leading dimension n); tmp: m x n scratch.
-strp_status apply_inverse_right(strp_ctx* ctx, const double* Linv, int n, double* X, int m, double* tmp) {
+// X <- X (L L^T)^-1 = (X Linv^T) Linv for X [m x n] (leading dimension ldx); tmp: m x ldx scratch.
+strp_status apply_inverse_right(strp_ctx* ctx, const double* Linv, int n, long long ldl, double* X, int m, long long ldx, double* tmp) {
   ProfScope ps(ctx, "chol_solve_f64", 2.0 * (double)m * n * n, 8.0 * ((double)n * n + 4.0 * (double)m * n));
   DgemmP p;
   memset(&p, 0, sizeof(p));
-  p.M = m; p.N = n; p.K = n; p.alpha = 1.0; p.beta = 0.0;
+  p.M = m; p.N = n; p.K = n;
   // tmp[m, j] = sum_{k <= j} X[m, k] Linv[j, k]
-  p.A = X; p.rsa = n; p.csa = 1; p.B = Linv; p.rsb = 1; p.csb = n; p.C = tmp; p.ldc = n; p.tri = 1;
-  STRP_TRY(dgemm_launch(ctx, p, 1));
+  p.A = X; p.lda = ldx; p.B = Linv; p.ldb = ldl; p.C = tmp; p.ldc = ldx; p.tri = 1;
+  STRP_TRY((dgemm_launch<true, true>(ctx, p)));
   // X[m, j] = sum_{k >= j} tmp[m, k] Linv[k, j]
-  p.A = tmp; p.B = Linv; p.rsb = n; p.csb = 1; p.C = X; p.tri = 2;
-  return dgemm_launch(ctx, p, 1);
+  p.A = tmp; p.C = X; p.tri = 2;
+  return dgemm_launch<true, false>(ctx, p);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -527,6 +929,19 @@ strp_status f32_to_f64_ridge(strp_ctx* ctx, const float* Af, long long ldf, doub
   const long long tot = (long long)n * n;
   hipLaunchKernelGGL(f32_to_f64_ridge_kernel, dim3((unsigned)((tot + 255) / 256)), dim3(256), 0, ctx->stream, Af, ldf,
                      Ad, ld, n, lam, lam_dev);
+  STRP_HIP(ctx, hipGetLastError());
+  return STRP_OK;
+}
+
+__global__ __launch_bounds__(256) void copy_f64_kernel(const double* src, long long lds, double* dst, long long ldd, int n) {
+  const long long e = (long long)blockIdx.x * 256 + threadIdx.x;
+  if (e >= (long long)n * n) return;
+  const int i = (int)(e / n), j = (int)(e % n);
+  dst[(long long)i * ldd + j] = src[(long long)i * lds + j];
+}
+
+strp_status copy_f64(strp_ctx* ctx, const double* src, long long lds, double* dst, long long ldd, int n) {
+  hipLaunchKernelGGL(copy_f64_kernel, dim3((unsigned)(((long long)n * n + 255) / 256)), dim3(256), 0, ctx->stream, src, lds, dst, ldd, n);
   STRP_HIP(ctx, hipGetLastError());
   return STRP_OK;
 }

@@ -694,35 +694,35 @@ static strp_status nt_product(strp_ctx* ctx, Arena arena, const PlaneOp& P, cons
 // [m x n] (leading dimension n) in *sol_out; it lives in the arena passed by reference.
 struct RefitIn {
   const float* Gram; long long ldg;       // fp32 Gram (used when sys_ready == 0)
-  double* sys; int sys_ready;             // [n x n] fp64 scratch: 0 = empty, 1 = holds Gram + lam I
-  double* Linv; int linv_ready;           // [n x n] fp64 inverse of the Cholesky factor (output, or input if linv_ready)
+  double* sys; int sys_ready;             // [n x f64_ld(n)] fp64 scratch: 0 = empty, 1 = holds Gram + lam I
+  double* Linv; long long ldl; int linv_ready;   // [n x ldl] fp64 inverse of the Cholesky factor (output, or input if linv_ready)
   double lam; const double* lam_dev;
   PlaneOp Lhs, Rhs;
   int m, n; long long T;
 };
 
-// Factor the system in `sys` (which must hold Gram + lam I) and leave the inverse of its Cholesky factor in Linv.
-static strp_status factor_and_invert(strp_ctx* ctx, Arena arena, double* sys, int n, double* Linv) {
+// Factor the system in `sys` (leading dimension f64_ld(n), holds Gram + lam I) and leave the inverse of its Cholesky factor in Linv.
+static strp_status factor_and_invert(strp_ctx* ctx, Arena arena, double* sys, int n, double* Linv, long long ldl) {
   const int nblk = (n + NB - 1) / NB;
-  STRP_TAKE(ctx, arena, invd, double, (size_t)nblk * NB * NB);
-  STRP_TAKE(ctx, arena, tmp, double, (size_t)n * n);
-  STRP_TRY(chol_factor(ctx, sys, n, n, invd, ctx->status_dev));
-  return tri_inverse(ctx, sys, n, n, invd, Linv, tmp);
+  STRP_TAKE(ctx, arena, sub, double, (size_t)nblk * NB * NB);
+  return chol_inverse(ctx, sys, n, f64_ld(n), sub, Linv, ldl, ctx->status_dev);
 }
 
+// *sol_out: [m x f64_ld(n)]
 static strp_status ridge_solve(strp_ctx* ctx, Arena& arena, const RefitIn& in, double** sol_out) {
   const int n = in.n, m = in.m;
+  const long long ld = f64_ld(n);
   const bool factor = !in.linv_ready;
   if (factor) {
-    if (in.sys_ready == 0) STRP_TRY(f32_to_f64_ridge(ctx, in.Gram, in.ldg, in.sys, n, n, in.lam, in.lam_dev));
-    const size_t fbytes = (((size_t)((n + NB - 1) / NB) * NB * NB * 8 + 255) & ~size_t(255)) + (((size_t)n * n * 8 + 255) & ~size_t(255));
+    if (in.sys_ready == 0) STRP_TRY(f32_to_f64_ridge(ctx, in.Gram, in.ldg, in.sys, ld, n, in.lam, in.lam_dev));
+    const size_t fbytes = ((size_t)((n + NB - 1) / NB) * NB * NB * 8 + 255) & ~size_t(255);
     STRP_TAKE(ctx, arena, fscratch, char, fbytes);
-    STRP_TRY(factor_and_invert(ctx, Arena(fscratch, fbytes), in.sys, n, in.Linv));
+    STRP_TRY(factor_and_invert(ctx, Arena(fscratch, fbytes), in.sys, n, in.Linv, in.ldl));
   }
-  STRP_TAKE(ctx, arena, R, double, (size_t)m * n);
-  STRP_TAKE(ctx, arena, tmp, double, (size_t)m * n);
-  STRP_TRY(nt_product(ctx, arena, in.Lhs, in.Rhs, m, n, in.T, 0, nullptr, 0, R, n, nullptr, 0));
-  STRP_TRY(apply_inverse_right(ctx, in.Linv, n, R, m, tmp));
+  STRP_TAKE(ctx, arena, R, double, (size_t)m * ld);
+  STRP_TAKE(ctx, arena, tmp, double, (size_t)m * ld);
+  STRP_TRY(nt_product(ctx, arena, in.Lhs, in.Rhs, m, n, in.T, 0, nullptr, 0, R, ld, nullptr, 0));
+  STRP_TRY(apply_inverse_right(ctx, in.Linv, n, in.ldl, R, m, ld, tmp));
   *sol_out = R;
   return STRP_OK;
 }
@@ -848,15 +848,19 @@ strp_status strp_refit(strp_ctx* ctx, strp_side side, const float* Gram, int32_t
   RefitIn ri;
   memset(&ri, 0, sizeof(ri));
   ri.Gram = Gram; ri.ldg = ldg; ri.lam = lambda; ri.lam_dev = nullptr;
-  if (chol) {
+  // the factorisation wants aligned rows of even length: a caller's cache of odd order gets a copy of the result
+  const bool chol_direct = chol && (chol_valid || (n % 2 == 0 && aligned16(chol)));
+  if (chol_direct) {
     ri.Linv = chol;
+    ri.ldl = n;
   } else {
-    STRP_TAKE(ctx, arena, Linv, double, (size_t)n * n);
+    STRP_TAKE(ctx, arena, Linv, double, (size_t)n * f64_ld(n));
     ri.Linv = Linv;
+    ri.ldl = f64_ld(n);
   }
   ri.linv_ready = chol_valid ? 1 : 0;
   if (!chol_valid) {
-    STRP_TAKE(ctx, arena, sys, double, (size_t)n * n);
+    STRP_TAKE(ctx, arena, sys, double, (size_t)n * f64_ld(n));
     ri.sys = sys;
   }
   const int prec = ctx->precision;
@@ -870,7 +874,8 @@ strp_status strp_refit(strp_ctx* ctx, strp_side side, const float* Gram, int32_t
   ri.m = m; ri.n = n; ri.T = T;
   double* sol = nullptr;
   STRP_TRY(ridge_solve(ctx, arena, ri, &sol));
-  return scatter_weights(ctx, sol, n, side, idx, s, W, out, in);
+  if (chol && !chol_direct) STRP_TRY(copy_f64(ctx, ri.Linv, ri.ldl, chol, n, n));
+  return scatter_weights(ctx, sol, f64_ld(n), side, idx, s, W, out, in);
 }
 
 strp_status strp_module_init(strp_ctx* ctx, const strp_module_desc* desc, strp_module_state* st, const strp_params* params) {
@@ -944,7 +949,7 @@ strp_status strp_module_init(strp_ctx* ctx, const strp_module_desc* desc, strp_m
     STRP_TRY(nt_product(ctx, a2, cv.Xt, cv.Xt, d, d, T, 1, st->H, d, Hd, d, diag, 0));
     hipLaunchKernelGGL(vec_sum_kernel, dim3(1), dim3(256), 0, ctx->stream, diag, d, params->delta / (double)d, sc + SC_LAM1, sc + SC_TRH);
     hipLaunchKernelGGL(add_diag_kernel, dim3(blocks_for(d)), dim3(256), 0, ctx->stream, Hd, (long long)d, d, 0.0, sc + SC_LAM1);
-    STRP_TRY(factor_and_invert(ctx, a2, Hd, d, st->cholH));
+    STRP_TRY(factor_and_invert(ctx, a2, Hd, d, st->cholH, d));
   }
   STRP_TRY(fill_zero(ctx, st->W1, sizeof(float) * (size_t)f * d));
   STRP_TRY(fill_zero(ctx, st->W2, sizeof(float) * (size_t)f * d));
@@ -1035,7 +1040,7 @@ strp_status strp_admm_step(strp_ctx* ctx, const strp_module_desc* desc, strp_mod
       hipLaunchKernelGGL(pruned_list_kernel, dim3(1), dim3(1024), 0, ctx->stream, st->mask, f, prow);
       pjob.ticket = ticket;
       pjob.units = (unsigned int)(f - s) * (unsigned int)segs;
-      pjob.take = 3;
+      pjob.per_launch = (int)(pjob.units / (unsigned)(chol_launches(s) + chol_launches(d) - 2) + 1u);
       pjob.rows = prow; pjob.nrows = f - s; pjob.segs = segs; pjob.seg_tokens = SEG;
       pjob.Z = st->Z; pjob.A = st->A; pjob.Z0 = wanda ? nullptr : st->Z0;
       pjob.lda = lda; pjob.T = T; pjob.alpha = alpha; pjob.beta = beta; pjob.partial = partial;
@@ -1048,22 +1053,23 @@ strp_status strp_admm_step(strp_ctx* ctx, const strp_module_desc* desc, strp_mod
   // ---- S1/S5: Gram of the kept A rows, fc2 refit -------------------------------------------
   if (stages & STRP_STAGE_REFIT2) {
     Arena a2 = arena;
-    STRP_TAKE(ctx, a2, Gd, double, (size_t)s * s);
+    const long long lds = f64_ld(s);
+    STRP_TAKE(ctx, a2, Gd, double, (size_t)s * lds);
     PlaneOp Arow;
     STRP_TRY(make_t_planes(ctx, a2, st->A, STRP_F32, lda, st->idx, s, T, 0, npa, &Arow));
     STRP_TRY(nt_product(ctx, a2, operand_for(ctx, STRP_PROD_GRAM, 0, Arow), operand_for(ctx, STRP_PROD_GRAM, 1, Arow), s, s, T, 1, nullptr,
-                        0, Gd, s, nullptr, 0));
-    hipLaunchKernelGGL(add_diag_kernel, dim3(blocks_for(s)), dim3(256), 0, ctx->stream, Gd, (long long)s, s, 0.0, sc + SC_LAM2);
+                        0, Gd, lds, nullptr, 0));
+    hipLaunchKernelGGL(add_diag_kernel, dim3(blocks_for(s)), dim3(256), 0, ctx->stream, Gd, lds, s, 0.0, sc + SC_LAM2);
     RefitIn ri;
     memset(&ri, 0, sizeof(ri));
-    STRP_TAKE(ctx, a2, Ginv, double, (size_t)s * s);
-    ri.sys = Gd; ri.sys_ready = 1; ri.Linv = Ginv; ri.linv_ready = 0;
+    STRP_TAKE(ctx, a2, Ginv, double, (size_t)s * lds);
+    ri.sys = Gd; ri.sys_ready = 1; ri.Linv = Ginv; ri.ldl = lds; ri.linv_ready = 0;
     ri.Lhs = operand_for(ctx, STRP_PROD_RHS2, 0, cv.Yt);
     ri.Rhs = operand_for(ctx, STRP_PROD_RHS2, 1, Arow);
     ri.m = d; ri.n = s; ri.T = T;
     double* sol = nullptr;
     STRP_TRY(ridge_solve(ctx, a2, ri, &sol));
-    STRP_TRY(scatter_weights(ctx, sol, s, STRP_SIDE_FC2, st->idx, s, st->W2, d, f));
+    STRP_TRY(scatter_weights(ctx, sol, lds, STRP_SIDE_FC2, st->idx, s, st->W2, d, f));
   }
   // compact kept weights and their planes (shared by the stages below)
   PlaneOp W2Sp, W1Sp;
@@ -1097,17 +1103,17 @@ strp_status strp_admm_step(strp_ctx* ctx, const strp_module_desc* desc, strp_mod
     }
     const size_t al = 255;
     const size_t cbytes = ((nt_partial_elems(d, d, sp, 1) * 4 + al) & ~al) + (((size_t)((d + NB - 1) / NB) * NB * NB * 8 + al) & ~al) +
-                          (((size_t)d * d * 8 + al) & ~al) + (512 + 2 * ((plane_elems(s, d) * 2 + al) & ~al)) +
+                          (512 + 2 * ((plane_elems(s, d) * 2 + al) & ~al)) +
                           (512 + 2 * ((plane_elems(d, d) * 2 + al) & ~al)) + 4096;
     STRP_TAKE(ctx, arena, cblock, char, cbytes);
     Arena a2(cblock, cbytes);
     STRP_TRY(nt_product(ctx, a2, W2Sp, W2Sp, d, d, sp, 1, nullptr, 0, Md, d, nullptr, 0));
     hipLaunchKernelGGL(add_diag_kernel, dim3(blocks_for(d)), dim3(256), 0, ctx->stream, Md, (long long)d, d, params->beta / params->alpha, (const double*)nullptr);
-    STRP_TRY(factor_and_invert(ctx, a2, Md, d, Linv));
+    STRP_TRY(factor_and_invert(ctx, a2, Md, d, Linv, d));
     // M is well conditioned (its spectrum lies in [beta/alpha, beta/alpha + |W|^2]): form M^-1 = Linv^T Linv
     // (lower half, fp64) and B = W^T M^-1 on the fp16-split matrix cores instead of a third fp64 solve
     STRP_TRY(fill_zero(ctx, Md, sizeof(double) * (size_t)d * d));
-    STRP_TRY(dgemm(ctx, d, d, d, 1.0, Linv, 1, d, Linv, d, 1, 0.0, Md, d, 1, 3));
+    STRP_TRY(gram_of_inverse(ctx, Linv, d, d, Md, d));
     {
       Arena a3 = a2;
       PlaneOp Wt, Mi;
@@ -1164,7 +1170,7 @@ strp_status strp_admm_step(strp_ctx* ctx, const strp_module_desc* desc, strp_mod
     }
     RefitIn ri;
     memset(&ri, 0, sizeof(ri));
-    ri.Linv = st->cholH; ri.linv_ready = 1;
+    ri.Linv = st->cholH; ri.ldl = d; ri.linv_ready = 1;
     ri.Lhs = operand_for(ctx, STRP_PROD_RHS1, 0, Zrow);
     ri.Rhs = operand_for(ctx, STRP_PROD_RHS1, 1, cv.Xt);
     ri.m = s; ri.n = d; ri.T = T;

@@ -166,21 +166,19 @@ strp_status weight_scale(strp_ctx* ctx, const void* src, int src_kind, long long
 
 // ---- fp64 dense kernels (dense_f64.hip) ---------------------------------------------------
 constexpr int NB = 64;  // block order of the factorisation
-// In-place lower Cholesky of the n x n fp64 matrix A (ld); the caller has added the ridge.  On return the blocks of A
-// below the NB x NB diagonal blocks hold L; the diagonal blocks themselves are left as they were when their step
-// began (never needed: invd has their inverses).  invd: [ceil(n/NB)][NB*NB] inverses of the diagonal blocks of L.
-// status: device word.
-strp_status chol_factor(strp_ctx* ctx, double* A, int n, long long ld, double* invd, int32_t* status);
-// Linv [n x n, ld n] = L^-1 from the off-diagonal blocks of the factor and its inverted diagonal blocks; tmp: n x n scratch.
-strp_status tri_inverse(strp_ctx* ctx, const double* L, int n, long long ldl, const double* invd, double* Linv, double* tmp);
-// In place X <- X (L L^T)^-1 = (X Linv^T) Linv for X [m x n] (ld n); tmp: m x n scratch.
-strp_status apply_inverse_right(strp_ctx* ctx, const double* Linv, int n, double* X, int m, double* tmp);
-// C[M x N] = alpha * A * B + beta * C with arbitrary element strides; lower != 0 skips tiles above
-// the diagonal; tri limits a tile's K range to the non-zero part of a triangular operand: 1: k < n0 + tile,
-// 2: k >= n0 (B), 3: k >= m0, 4: k < m0 + tile (A).
-strp_status dgemm(strp_ctx* ctx, int M, int N, int K, double alpha, const double* A, long long rsa,
-                  long long csa, const double* B, long long rsb, long long csb, double beta, double* C,
-                  long long ldc, int lower, int tri = 0);
+// leading dimension of the fp64 work matrices: rows 16-byte aligned whatever the order
+static inline long long f64_ld(long long n) { return (n + 7) & ~7LL; }
+// Linv [n x n, ldv] = L^-1 (upper part zero) of the SPD matrix A [n x n, ld] = L L^T whose lower triangle is given (the
+// caller has added the ridge) and destroyed.  sub: ceil(n / NB) * NB * NB doubles of scratch.  ld and ldv even, A and Linv
+// 16-byte aligned.  A pivot that is not positive sets ENOTPD in status (device word).
+strp_status chol_inverse(strp_ctx* ctx, double* A, int n, long long ld, double* sub, double* Linv, long long ldv, int32_t* status);
+int chol_launches(int n);   // launches of chol_inverse that can carry spare workgroups, and one
+// In place X <- X (L L^T)^-1 = (X Linv^T) Linv for X [m x n] (ldx); tmp: m x ldx scratch.
+strp_status apply_inverse_right(strp_ctx* ctx, const double* Linv, int n, long long ldl, double* X, int m, long long ldx, double* tmp);
+// Tiles on or below the diagonal of S [n x n, lds] = Linv^T Linv.
+strp_status gram_of_inverse(strp_ctx* ctx, const double* Linv, int n, long long ldl, double* S, long long lds);
+// dst [n x n, ldd] = src [n x n, lds]
+strp_status copy_f64(strp_ctx* ctx, const double* src, long long lds, double* dst, long long ldd, int n);
 // Ad[i*ld+j] = (double)Af[i*ldf+j] + (i==j ? lam (or *lam_dev if non-null) : 0)
 strp_status f32_to_f64_ridge(strp_ctx* ctx, const float* Af, long long ldf, double* Ad, long long ld, int n,
                              double lam, const double* lam_dev);

@@ -1,0 +1,48 @@
+"""The fp64 factorisation chain (factor and inverse of the triangular factor in one pass over 64 x 64 tiles) and the two-stage
+solve, through strp_refit, at the orders where the tiling can go wrong."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2510_03246_amd import strp
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def ctx():
+    c = strp.Context(0)
+    c.set_workspace(64 << 20)
+    return c
+
+
+@pytest.mark.parametrize("n,m", [(1, 5), (31, 64), (63, 3), (64, 33), (65, 129), (127, 200), (128, 1), (129, 65), (191, 70), (193, 64), (257, 40),
+                                 (450, 300), (833, 161)])
+def test_factor_inverse_and_solve(ctx, n, m):
+    """chol = inverse of the lower Cholesky factor of Gram + lam I, upper part zero; W[:, S] = (Lhs Rhs^T)(Gram + lam I)^-1.
+    The system is well conditioned (kappa below 1e3), so the fp64 factor and its inverse are good to about n * kappa * 2^-53
+    < 1e-10; W is rounded to fp32 from a right-hand side the library sums in fp32 (T = 24 exact products of small
+    integers), hence 1e-6."""
+    rng = np.random.default_rng(n)
+    T = 24
+    lhs = rng.integers(-4, 5, size=(m, T)).astype(np.float32)
+    rhs = rng.integers(-4, 5, size=(n, T)).astype(np.float32)
+    B = rng.normal(size=(n, n + 8)) / np.sqrt(n + 8)
+    G = (B @ B.T).astype(np.float32)
+    lam = 0.05
+    dev = lambda x: torch.from_numpy(x).cuda()
+    idx = torch.arange(n, dtype=torch.int32, device="cuda")
+    W = torch.full((m, n), 7.0, device="cuda")
+    chol = torch.full((n, n), 3.0, dtype=torch.float64, device="cuda")
+    ctx.strp_refit(strp.SIDE_FC2, dev(G), lam, dev(lhs), dev(rhs), T, idx, W, chol=chol, chol_valid=False)
+    assert ctx.poll() == strp.OK
+    S = np.tril(G.astype(np.float64)) + np.tril(G.astype(np.float64), -1).T + lam * np.eye(n)
+    ref = np.linalg.inv(np.linalg.cholesky(S))
+    got = chol.cpu().numpy()
+    assert np.count_nonzero(np.triu(got, 1)) == 0
+    assert np.linalg.norm(got - ref) <= 1e-10 * np.linalg.norm(ref)
+    Wref = np.linalg.solve(S, (lhs.astype(np.float64) @ rhs.astype(np.float64).T).T).T
+    assert np.linalg.norm(W.cpu().numpy() - Wref) <= 1e-6 * np.linalg.norm(Wref)
+    W2 = torch.zeros_like(W)
+    ctx.strp_refit(strp.SIDE_FC2, None, lam, dev(lhs), dev(rhs), T, idx, W2, chol=chol, chol_valid=True)
+    assert torch.equal(W, W2)
