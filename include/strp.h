@@ -214,8 +214,7 @@ strp_status strp_alloc_softmax(strp_ctx* ctx, const double* energies, int32_t L,
  *   tau (optional) = lowest kept score.
  * One module's scores (n up to 65536) are selected by one block; a longer vector -- the scores of every layer
  * at once for the single global threshold of Alg. 4 (K = floor(r n L) kept over all L n units) -- is selected
- * by a multi-block path that needs strp_topk_workspace_bytes(n) bytes of the context's workspace (group must
- * be 1 there).
+ * by a multi-block path that needs strp_topk_workspace_bytes(n) bytes of the context's workspace.
  * Errors: STRP_EINVAL (k < 0, k > n, n <= 0, group <= 0, null pointers), STRP_ENOMEM (workspace).
  */
 strp_status strp_mask_topk(strp_ctx* ctx, const float* score, int32_t n, int32_t k, int32_t group,
@@ -226,10 +225,10 @@ size_t strp_topk_workspace_bytes(int32_t n);
 /*
  * strp_mask_topk_static -- strp_mask_topk (group = 1) for callers that cannot allocate or hand over device memory:
  * code under HIP graph capture, tight serving loops, harnesses that forbid hipMalloc.  Same kernels, same results
- * (mask, ascending idx, tau) and the same argument meaning; the select's scratch (per-block histograms, candidate
- * lists, counters) is a fixed array inside the library instead of the context's workspace, so the call needs no
+ * (mask, ascending idx, tau) and the same argument meaning; the select's scratch (histograms and counters) is
+ * a fixed array inside the library instead of the context's workspace, so the call needs no
  * workspace and allocates nothing on the host or the device (it also records no profile entry).  The array takes
- * 16 * STRP_TOPK_STATIC_MAX_N + 8 MiB = 32 MiB of device memory on every GPU the library is used on, from the moment
+ * 1 MiB of device memory on every GPU the library is used on, from the moment
  * the library is loaded until the process ends.
  * Limits: n <= STRP_TOPK_STATIC_MAX_N (enough for the 48 x 28672 unit scores of the largest configuration at once);
  * more returns STRP_EINVAL and nothing is enqueued.  All calls on one GPU share the one array, which keeps the last

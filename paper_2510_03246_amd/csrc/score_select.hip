@@ -4,6 +4,8 @@
 //   unit_scores   : WANDA / LEMMA / GAIN unit scores (+ group sums for heads) and the layer energy
 //   alloc         : softmax allocation with clipping, rescale and largest-remainder prune counts
 //   topk          : radix select on order-preserving keys, ballot/prefix compaction, ties -> lower index
+#include <stddef.h>
+
 #include "strp_internal.h"
 
 namespace strp {
@@ -25,6 +27,24 @@ __device__ __forceinline__ double wave_allmax_d(double v) {
 }
 __device__ __forceinline__ float bf16lo(unsigned int w) { return __builtin_bit_cast(float, w << 16); }
 __device__ __forceinline__ float bf16hi(unsigned int w) { return __builtin_bit_cast(float, w & 0xffff0000u); }
+
+// ---------------------------------------------------------------------------------------------
+// "The last workgroup does the rest": true in every thread of the last workgroup of the grid to get here.  What the
+// workgroups hand to it goes through agent-scope atomics (agent_put / agent_get / atomicAdd), which act at the level all
+// XCDs share, so it is enough that they have completed before the counter moves: an agent-scope fence would
+// write back and invalidate the XCD's L2 from every workgroup, which took 45 of a launch's 50 us.
+// ---------------------------------------------------------------------------------------------
+template <typename T>
+__device__ __forceinline__ void agent_put(T* p, T v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+template <typename T>
+__device__ __forceinline__ T agent_get(const T* p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+__device__ __forceinline__ bool last_block(unsigned int* done, unsigned int* flag) {
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  __syncthreads();
+  if (threadIdx.x == 0) *flag = atomicAdd(done, 1u) + 1u == gridDim.x;
+  __syncthreads();
+  return *flag != 0;
+}
 
 // ---------------------------------------------------------------------------------------------
 // per-channel token sums: sums[0][r] = sum A^2, [1][r] = sum A*relu(Z0), [2][r] = sum Z0*Z, [3][r] = sum Z0^2
@@ -436,8 +456,7 @@ strp_status launch_alloc(strp_ctx* ctx, const double* energies, int L, const int
 }
 
 // ---------------------------------------------------------------------------------------------
-// top-k select: one block of 1024 threads; 4 radix passes of 8 bits find the k-th largest key, then an
-// index-ordered compaction (ballot + popcount prefix) writes mask and ascending kept indices.
+// top-k select.  Scores are compared as order-preserving integer keys; equal keys keep the lower index.
 // ---------------------------------------------------------------------------------------------
 __device__ __forceinline__ unsigned int score_key(float x) {
   const unsigned int u = __builtin_bit_cast(unsigned int, x + 0.0f);   // -0 and +0 are one value: both map to +0
@@ -448,411 +467,25 @@ __device__ __forceinline__ float key_score(unsigned int k) {
   return __builtin_bit_cast(float, u);
 }
 
-__global__ __launch_bounds__(1024) void topk_kernel(const float* score, int n, int k, int group, uint8_t* mask, int32_t* idx,
-                                                    float* tau) {
-  __shared__ unsigned int hist[256];
-  __shared__ unsigned int sel_prefix, sel_krem;
-  __shared__ int wave_tot[16][2];
-  __shared__ int run_eq, run_kept;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-
-  if (k <= 0 || k >= n) {  // degenerate: nothing or everything kept
-    const int keep = k >= n;
-    for (int i = tid; i < n; i += 1024) {
-      mask[i] = (uint8_t)keep;
-      if (keep)
-        for (int c = 0; c < group; ++c) idx[(long long)i * group + c] = i * group + c;
-    }
-    if (tid == 0 && tau) {
-      float t = __builtin_inff();
-      if (keep) {
-        t = score[0];
-        for (int i = 1; i < n; ++i) t = fminf(t, score[i]);
-      }
-      *tau = t;
-    }
-    return;
-  }
-
-  unsigned int prefix = 0, pmask = 0;
-  unsigned int krem = (unsigned int)k;
-  for (int pass = 0; pass < 4; ++pass) {
-    const int shift = 24 - 8 * pass;
-    if (tid < 256) hist[tid] = 0;
-    __syncthreads();
-    for (int i = tid; i < n; i += 1024) {
-      const unsigned int key = score_key(score[i]);
-      if ((key & pmask) == prefix) atomicAdd(&hist[(key >> shift) & 255u], 1u);
-    }
-    __syncthreads();
-    if (tid < 64) {
-      // the bucket d with  #(keys in buckets above d) < krem <= #(keys in buckets d and above): lane l owns buckets
-      // 4 l .. 4 l + 3, a wavefront suffix scan gives the count above its group, exactly one (lane, bucket) matches
-      unsigned int h[4];
-#pragma unroll
-      for (int j = 0; j < 4; ++j) h[j] = hist[4 * tid + j];
-      const unsigned int own = h[0] + h[1] + h[2] + h[3];
-      unsigned int suf = own;   // inclusive suffix sum over lanes >= tid
-#pragma unroll
-      for (int o = 1; o < 64; o <<= 1) {
-        const unsigned int v = __shfl_down(suf, o, 64);
-        if (tid + o < 64) suf += v;
-      }
-      unsigned int cum = suf - own;   // keys in the groups above this lane's
-#pragma unroll
-      for (int j = 3; j >= 0; --j) {
-        if (cum < krem && cum + h[j] >= krem) {
-          sel_prefix = prefix | ((unsigned int)(4 * tid + j) << shift);
-          sel_krem = krem - cum;
-        }
-        cum += h[j];
-      }
-    }
-    __syncthreads();
-    prefix = sel_prefix;
-    krem = sel_krem;
-    pmask |= 255u << shift;
-    __syncthreads();
-  }
-  // prefix is the k-th largest key; krem of the keys equal to it are kept (lowest indices first)
-  if (tid == 0) {
-    run_eq = 0;
-    run_kept = 0;
-    if (tau) *tau = key_score(prefix);
-  }
-  __syncthreads();
-  for (int base = 0; base < n; base += 1024) {
-    const int i = base + tid;
-    unsigned int key = 0;
-    const bool in = i < n;
-    if (in) key = score_key(score[i]);
-    const bool gt = in && key > prefix;
-    const bool eq = in && key == prefix;
-    const unsigned long long beq = __ballot(eq);
-    const unsigned long long lt_mask = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
-    const int eq_before = __popcll(beq & lt_mask);
-    if (lane == 0) wave_tot[wave][0] = __popcll(beq);
-    __syncthreads();
-    int eq_off = run_eq;
-    for (int w = 0; w < wave; ++w) eq_off += wave_tot[w][0];
-    const bool keep = gt || (eq && (unsigned int)(eq_off + eq_before) < krem);
-    const unsigned long long bk = __ballot(keep);
-    const int k_before = __popcll(bk & lt_mask);
-    if (lane == 0) wave_tot[wave][1] = __popcll(bk);
-    __syncthreads();
-    int k_off = run_kept;
-    for (int w = 0; w < wave; ++w) k_off += wave_tot[w][1];
-    if (in) {
-      mask[i] = (uint8_t)keep;
-      if (keep) {
-        const long long pos = (long long)(k_off + k_before) * group;
-        for (int c = 0; c < group; ++c) idx[pos + c] = i * group + c;
-      }
-    }
-    __syncthreads();
-    if (tid == 0) {
-      int te = 0, tk = 0;
-      for (int w = 0; w < 16; ++w) {
-        te += wave_tot[w][0];
-        tk += wave_tot[w][1];
-      }
-      run_eq += te;
-      run_kept += tk;
-    }
-    __syncthreads();
-  }
-}
-
-// One module's scores (n <= 16384, 0 < k < n): the 16 keys of a thread (elements tid + 1024 j) stay in registers.
-// The k-th largest key is built bit by bit from the top (32 counting rounds: ballots + one barrier each; a radix
-// histogram in LDS serialises on the few exponent buckets real scores fall into).  The index-ordered compaction
-// takes two table scans instead of a barrier chain per 1024 elements: per (round j, wavefront) counts of the keys
-// equal to the threshold, then of the kept keys, scanned in (j, wavefront) order = index order.
-__device__ __forceinline__ int table_scan_256(int val, int* wtot, int tid) {
-  // exclusive prefix of val over threads 0..255 (called by every thread of the block; others pass 0 and ignore)
-  const int lane = tid & 63, wave = tid >> 6;
-  int inc = val;
-#pragma unroll
-  for (int o = 1; o < 64; o <<= 1) {
-    const int v = __shfl_up(inc, o, 64);
-    if (lane >= o) inc += v;
-  }
-  if (lane == 63 && wave < 4) wtot[wave] = inc;
-  __syncthreads();
-  int off = 0;
-  for (int w = 0; w < wave && w < 4; ++w) off += wtot[w];
-  __syncthreads();
-  return off + inc - val;
-}
-
-__global__ __launch_bounds__(1024) void topk_small_kernel(const float* score, int n, int k, int group, uint8_t* mask, int32_t* idx,
-                                                          float* tau) {
-  __shared__ int wcnt[2][16];
-  __shared__ int table[256];      // [round j][wavefront]
-  __shared__ int wtot[4];
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  unsigned int kreg[16];
-#pragma unroll
-  for (int j = 0; j < 16; ++j) {
-    const int i = tid + 1024 * j;
-    kreg[j] = i < n ? score_key(score[i]) : 0u;   // a candidate always has a bit set, so padding is never counted
-  }
-  auto count_ge = [&](unsigned int cand, int buf) {
-    int c = 0;
-#pragma unroll
-    for (int j = 0; j < 16; ++j) c += __popcll(__ballot(kreg[j] >= cand));
-    if (lane == 0) wcnt[buf][wave] = c;
-    __syncthreads();
-    int tot = 0;
-#pragma unroll
-    for (int w = 0; w < 16; ++w) tot += wcnt[buf][w];
-    return tot;
-  };
-  unsigned int v = 0;
-  for (int b = 31; b >= 0; --b) {
-    const unsigned int cand = v | (1u << b);
-    if (count_ge(cand, b & 1) >= k) v = cand;
-  }
-  // v = k-th largest key.  Keys above it are kept, of the keys equal to it the krem with the lowest indices.
-  int n_gt = 0;
-  if (v != 0xffffffffu) n_gt = count_ge(v + 1u, 1);   // buffer 1: round b = 0 may still be read from buffer 0
-  const int krem = k - n_gt;
-  if (tid == 0 && tau) *tau = key_score(v);
-  const unsigned long long lt_mask = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
-  // counts of equal keys per (round, wavefront)
-  __syncthreads();
-#pragma unroll
-  for (int j = 0; j < 16; ++j) {
-    const unsigned long long beq = __ballot(tid + 1024 * j < n && kreg[j] == v);
-    if (lane == 0) table[j * 16 + wave] = __popcll(beq);
-  }
-  __syncthreads();
-  const int eq_pref = table_scan_256(tid < 256 ? table[tid] : 0, wtot, tid);
-  if (tid < 256) table[tid] = eq_pref;
-  __syncthreads();
-  unsigned int keepbits = 0;
-  int kcnt[16];
-#pragma unroll
-  for (int j = 0; j < 16; ++j) {
-    const bool in = tid + 1024 * j < n;
-    const bool eq = in && kreg[j] == v;
-    const unsigned long long beq = __ballot(eq);
-    const int rank = table[j * 16 + wave] + __popcll(beq & lt_mask);
-    const bool keep = in && (kreg[j] > v || (eq && rank < krem));
-    keepbits |= (unsigned int)keep << j;
-    const unsigned long long bk = __ballot(keep);
-    kcnt[j] = __popcll(bk & lt_mask);
-  }
-  __syncthreads();
-#pragma unroll
-  for (int j = 0; j < 16; ++j) {
-    const unsigned long long bk = __ballot((keepbits >> j) & 1u);
-    if (lane == 0) table[j * 16 + wave] = __popcll(bk);
-  }
-  __syncthreads();
-  const int kp_pref = table_scan_256(tid < 256 ? table[tid] : 0, wtot, tid);
-  if (tid < 256) table[tid] = kp_pref;
-  __syncthreads();
-#pragma unroll
-  for (int j = 0; j < 16; ++j) {
-    const int i = tid + 1024 * j;
-    if (i >= n) continue;
-    const bool keep = (keepbits >> j) & 1u;
+// nothing (k = 0) or everything (k = n) is kept
+__global__ __launch_bounds__(1024) void topk_all_kernel(const float* score, int n, int keep, int group, uint8_t* mask, int32_t* idx, float* tau) {
+  __shared__ float wmin[16];
+  const int tid = threadIdx.x;
+  float t = __builtin_inff();
+  for (int i = tid; i < n; i += 1024) {
     mask[i] = (uint8_t)keep;
     if (keep) {
-      const long long pos = (long long)(table[j * 16 + wave] + kcnt[j]) * group;
-      for (int c = 0; c < group; ++c) idx[pos + c] = i * group + c;
+      t = fminf(t, score[i]);
+      for (int c = 0; c < group; ++c) idx[(long long)i * group + c] = i * group + c;
     }
   }
-}
-
-// ---------------------------------------------------------------------------------------------
-// top-k select over a long score vector (all layers' scores at once for a global threshold, or a stress
-// input): several blocks, two reads of the scores and one of the mask.
-//   level 0 (top 11 key bits: sign, exponent, 2 mantissa bits), over the scores
-//     hist    every block histograms its contiguous chunk (kept per block and summed)
-//     pick    one block picks the bucket that holds the k-th largest key; keys above it are kept, below dropped
-//     gather  every block re-reads its chunk, writes the mask of the decided keys and appends the keys of the
-//             bucket (a few per cent of n: the bucket is a 2^(1/4)-wide value range) to a candidate list, in
-//             index order (the per-block histograms give the offsets)
-//   level 1 (next 11 bits), over the candidates: the same three steps; what survives is ~n / 10^5 keys
-//   resolve   one block selects among those on the last 10 bits, ties to the lower index, completes the mask and
-//             scans the per-block kept counts
-//   compact   every block turns its part of the mask into ascending indices
-// A vector of equal scores degenerates to candidate lists of length n and a single-block resolve: correct, slow.
-// ---------------------------------------------------------------------------------------------
-namespace big {
-constexpr int BINS = 2048;          // 11 bits
-constexpr int THREADS = 512;
-constexpr int MAXBLOCKS = 1024;
-constexpr int L1BLOCKS = 256;
-struct State {
-  unsigned int bucket;      // chosen digit at this level
-  unsigned int krem;        // keys still to keep inside the bucket
-  unsigned int ncand;       // keys in the bucket
-  unsigned int pad;
-};
-}  // namespace big
-
-struct BigLevel {
-  unsigned int* bhist;      // [blocks][BINS]
-  unsigned int* ghist;      // [BINS]
-  big::State* state;        // this level's choice
-  unsigned int* coff;       // [blocks] offset of the block's candidates in the output list
-  unsigned int* cand_key;   // output list
-  int* cand_idx;
-  int blocks;
-};
-
-struct BigTopkPlan {
-  int blocks0;
-  long long chunk0;         // elements per block at level 0 (multiple of big::THREADS)
-  BigLevel lv[2];
-  unsigned int* gtcnt;      // [blocks0] keys above the level-0 bucket in the block's chunk
-  unsigned int* kept_cand;  // [blocks0] kept candidates per level-0 chunk (levels 1 and 2)
-  unsigned int* kpre;       // [blocks0] kept entries before the block's chunk
-  int vec;                  // scores 16-byte aligned and mask 8-byte aligned: vector accesses allowed
-};
-
-static void big_plan(long long n, int* blocks, long long* chunk) {
-  long long b = (n + 8 * big::THREADS - 1) / (8 * big::THREADS);
-  if (b > big::MAXBLOCKS) b = big::MAXBLOCKS;
-  if (b < 1) b = 1;
-  long long c = (n + b - 1) / b;
-  c = (c + big::THREADS - 1) / big::THREADS * big::THREADS;
-  *blocks = (int)((n + c - 1) / c);
-  *chunk = c;
-}
-
-size_t topk_scratch_bytes(int n) {
-  if (n <= 65536) return 0;
-  int blocks;
-  long long chunk;
-  big_plan(n, &blocks, &chunk);
-  auto al = [](size_t b) { return (b + 255) & ~size_t(255); };
-  return al((size_t)blocks * big::BINS * 4) + al((size_t)big::L1BLOCKS * big::BINS * 4) + 2 * al(big::BINS * 4) + 2 * al(sizeof(big::State)) +
-         al((size_t)blocks * 4) + al((size_t)big::L1BLOCKS * 4) + 3 * al((size_t)blocks * 4) + 4 * al((size_t)n * 4) + 256;
-}
-
-// chunk of block blk at level LEVEL: level 0 splits [0, n) by plan.chunk0; level 1 splits the candidate list, whose
-// length is a device value
-template <int LEVEL>
-__device__ __forceinline__ void level_range(const BigTopkPlan& pl, long long n, long long* beg, long long* end) {
-  if (LEVEL == 0) {
-    *beg = (long long)blockIdx.x * pl.chunk0;
-    *end = *beg + pl.chunk0 < n ? *beg + pl.chunk0 : n;
-  } else {
-    const long long m = pl.lv[0].state->ncand;
-    long long c = (m + gridDim.x - 1) / gridDim.x;
-    c = (c + big::THREADS - 1) / big::THREADS * big::THREADS;
-    *beg = (long long)blockIdx.x * c < m ? (long long)blockIdx.x * c : m;
-    *end = *beg + c < m ? *beg + c : m;
-  }
-}
-template <int LEVEL>
-__device__ __forceinline__ unsigned int level_key(const BigTopkPlan& pl, const float* score, long long i) {
-  return LEVEL == 0 ? score_key(score[i]) : pl.lv[0].cand_key[i];
-}
-template <int LEVEL>
-__device__ __forceinline__ unsigned int level_digit(unsigned int key) {
-  return LEVEL == 0 ? key >> 21 : (key >> 10) & 0x7ffu;
-}
-
-template <int LEVEL>
-__global__ __launch_bounds__(big::THREADS) void topk_hist_kernel(const float* score, long long n, BigTopkPlan pl) {
-  __shared__ unsigned int hist[big::BINS];
-  for (int i = threadIdx.x; i < big::BINS; i += big::THREADS) hist[i] = 0;
+  for (int o = 32; o > 0; o >>= 1) t = fminf(t, __shfl_down(t, o, 64));
+  if ((tid & 63) == 0) wmin[tid >> 6] = t;
   __syncthreads();
-  long long beg, end;
-  level_range<LEVEL>(pl, n, &beg, &end);
-  if (LEVEL == 0 && pl.vec) {   // beg is a multiple of 512: float4 loads stay aligned
-    const long long nv = (end - beg) >> 2;
-    const float4* s4 = (const float4*)(score + beg);
-    for (long long v = threadIdx.x; v < nv; v += big::THREADS) {
-      const float4 x = s4[v];
-      atomicAdd(&hist[score_key(x.x) >> 21], 1u);
-      atomicAdd(&hist[score_key(x.y) >> 21], 1u);
-      atomicAdd(&hist[score_key(x.z) >> 21], 1u);
-      atomicAdd(&hist[score_key(x.w) >> 21], 1u);
-    }
-    for (long long i = beg + (nv << 2) + threadIdx.x; i < end; i += big::THREADS) atomicAdd(&hist[score_key(score[i]) >> 21], 1u);
-  } else {
-    for (long long i = beg + threadIdx.x; i < end; i += big::THREADS) atomicAdd(&hist[level_digit<LEVEL>(level_key<LEVEL>(pl, score, i))], 1u);
+  if (tid == 0 && tau) {
+    for (int w = 1; w < 16; ++w) t = fminf(t, wmin[w]);
+    *tau = t;
   }
-  __syncthreads();
-  const BigLevel& lv = pl.lv[LEVEL];
-  for (int i = threadIdx.x; i < big::BINS; i += big::THREADS) {
-    const unsigned int h = hist[i];
-    lv.bhist[(long long)blockIdx.x * big::BINS + i] = h;
-    if (h) atomicAdd(&lv.ghist[i], h);
-  }
-}
-
-// One block: bucket choice at this level and the per-block candidate offsets.  The number to keep is k at level 0
-// and what level 0 left to its bucket at level 1.
-template <int LEVEL>
-__global__ __launch_bounds__(1024) void topk_pick_kernel(long long k0, BigTopkPlan pl) {
-  __shared__ unsigned long long suf[big::BINS];   // suf[d] = number of keys with digit >= d
-  __shared__ unsigned int sb;
-  __shared__ unsigned int scan[1024];
-  const int tid = threadIdx.x;
-  const BigLevel& lv = pl.lv[LEVEL];
-  const unsigned long long k = LEVEL == 0 ? (unsigned long long)k0 : (unsigned long long)pl.lv[0].state->krem;
-  suf[tid] = lv.ghist[tid];
-  suf[tid + 1024] = lv.ghist[tid + 1024];
-  if (tid == 0) sb = 0;
-  __syncthreads();
-  for (int o = 1; o < big::BINS; o <<= 1) {   // inclusive suffix scan, two bins per thread
-    const unsigned long long v0 = tid + o < big::BINS ? suf[tid + o] : 0ull;
-    const unsigned long long v1 = tid + 1024 + o < big::BINS ? suf[tid + 1024 + o] : 0ull;
-    __syncthreads();
-    suf[tid] += v0;
-    suf[tid + 1024] += v1;
-    __syncthreads();
-  }
-  // the bucket is the largest digit whose suffix count reaches k (digit 0 always does: k <= n)
-#pragma unroll
-  for (int h = 0; h < 2; ++h) {
-    const int d = tid + 1024 * h;
-    const unsigned long long above = d + 1 < big::BINS ? suf[d + 1] : 0ull;
-    if (suf[d] >= k && above < k) {
-      sb = (unsigned int)d;
-      lv.state->bucket = (unsigned int)d;
-      lv.state->krem = (unsigned int)(k - above);
-      lv.state->ncand = (unsigned int)(suf[d] - above);
-    }
-  }
-  __syncthreads();
-  const unsigned int b = sb;
-  const unsigned int mine = tid < lv.blocks ? lv.bhist[(long long)tid * big::BINS + b] : 0u;
-  scan[tid] = mine;
-  __syncthreads();
-  for (int o = 1; o < 1024; o <<= 1) {   // inclusive scan
-    const unsigned int v = tid >= o ? scan[tid - o] : 0;
-    __syncthreads();
-    scan[tid] += v;
-    __syncthreads();
-  }
-  if (tid < lv.blocks) lv.coff[tid] = scan[tid] - mine;
-}
-
-// position of a flagged thread among the flagged threads of the block, in thread order; *total = their number
-__device__ __forceinline__ int block_rank(bool flag, int* wave_tot, int* total) {
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const unsigned long long bal = __ballot(flag);
-  const unsigned long long lt = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
-  if (lane == 0) wave_tot[wave] = __popcll(bal);
-  __syncthreads();
-  int off = 0, tot = 0;
-  const int nw = blockDim.x >> 6;
-  for (int w = 0; w < nw; ++w) {
-    const int c = wave_tot[w];
-    if (w < wave) off += c;
-    tot += c;
-  }
-  __syncthreads();
-  *total = tot;
-  return off + __popcll(bal & lt);
 }
 
 // exclusive prefix, in thread order, of a per-thread count over the block; *total = the block's sum
@@ -878,232 +511,446 @@ __device__ __forceinline__ int block_scan(int cnt, int* wave_tot, int* total) {
   return off + inc - cnt;
 }
 
-// kept candidates are counted per level-0 chunk (for the final compaction): LDS counters, flushed at the end
-__device__ __forceinline__ void kept_flush(unsigned int* lds_cnt, unsigned int* global_cnt, int blocks0) {
+// Suffix scan of a histogram of B * 1024 bins (or B * 512, by blockDim) for the bin that holds the krem-th largest entry:
+// thread t owns bins B t .. B t + B - 1.  out[0] = bin, out[1] = entries above it, out[2] = entries in it (LDS).
+template <int B, int WAVES>
+__device__ __forceinline__ void pick_bin(const unsigned int (&h)[B], unsigned int krem, unsigned int* wave_tot, unsigned int* out) {
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  unsigned int own = 0;
+#pragma unroll
+  for (int b = 0; b < B; ++b) own += h[b];
+  unsigned int suf = own;     // inclusive suffix sum over the lanes >= this one
+#pragma unroll
+  for (int o = 1; o < 64; o <<= 1) {
+    const unsigned int v = __shfl_down(suf, o, 64);
+    if (lane + o < 64) suf += v;
+  }
+  if (lane == 0) wave_tot[wave] = suf;
   __syncthreads();
-  for (int i = threadIdx.x; i < blocks0; i += blockDim.x) {
-    const unsigned int c = lds_cnt[i];
-    if (c) atomicAdd(&global_cnt[i], c);
+  unsigned int above = suf - own;
+  for (int w = wave + 1; w < WAVES; ++w) above += wave_tot[w];
+#pragma unroll
+  for (int b = B - 1; b >= 0; --b) {
+    if (above < krem && above + h[b] >= krem) {
+      out[0] = (unsigned int)(B * tid + b);
+      out[1] = above;
+      out[2] = h[b];
+    }
+    above += h[b];
+  }
+  __syncthreads();
+}
+
+// One vector of up to 1024 KPT scores (0 < k < n) by one block of 1024 threads, element tid + 1024 j in thread tid: REGS keeps
+// the keys in registers, otherwise (beyond 16 keys a thread) each phase reads the scores again, from the L2.  What bounds it is the number of dependent block-wide phases, so the threshold is found in few of them: a
+// histogram of 2048 bins stretched over the keys that are there (real scores share a handful of exponents: bins at
+// fixed bit positions would put them, and the LDS atomics that count them, in a few places), the bin with the k-th
+// largest key, and the rank of each of the bin's at most 1024 keys among themselves; a fuller bin is stretched again.
+// The k-th key and its index decide every element: kept = larger, or equal with no higher index.  Ascending
+// indices come from one scan of the counts per (round j, wavefront).  n = 16384: 26 -> 14 us with the launch; it was
+// 32 counting rounds.
+template <int KPT, bool REGS>
+__global__ __launch_bounds__(1024) void topk_small_kernel(const float* score, int n, int k, int group, uint8_t* mask, int32_t* idx,
+                                                          float* tau) {
+  __shared__ unsigned int hist[2048];
+  __shared__ unsigned int ckey[1024];
+  __shared__ int cidx[1024];
+  __shared__ unsigned int wt[2][16];
+  __shared__ unsigned int sel[3], ncand, cut[2];
+  __shared__ int table[16 * KPT];
+  __shared__ int wtot[16];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  unsigned int key[REGS ? KPT : 1];
+  if constexpr (REGS) {
+#pragma unroll
+    for (int j = 0; j < KPT; ++j) {
+      const int i = tid + 1024 * j;
+      key[j] = score_key(score[i < n ? i : n - 1]);
+    }
+  }
+  // f(j, index, key, index < n): every thread of the block makes the same calls
+  const auto each = [&](auto f) {
+    if constexpr (REGS) {
+#pragma unroll
+      for (int j = 0; j < KPT; ++j) f(j, tid + 1024 * j, key[j], tid + 1024 * j < n);
+    } else {
+#pragma unroll 4
+      for (int j = 0; j < (n + 1023) / 1024; ++j) {
+        const int i = tid + 1024 * j;
+        f(j, i, score_key(score[i < n ? i : n - 1]), i < n);
+      }
+    }
+  };
+  // entries of `table` no call of `each` writes
+  if constexpr (!REGS)
+    for (int q = tid; q < 16 * KPT; q += 1024) table[q] = 0;
+  unsigned int lo = 0xffffffffu, hi = 0u;
+  each([&](int, int, unsigned int x, bool) {
+    lo = x < lo ? x : lo;
+    hi = x > hi ? x : hi;
+  });
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) {
+    const unsigned int a = __shfl_xor(lo, o, 64), b = __shfl_xor(hi, o, 64);
+    lo = a < lo ? a : lo;
+    hi = b > hi ? b : hi;
+  }
+  if (lane == 0) {
+    wt[0][wave] = lo;
+    wt[1][wave] = hi;
+  }
+  hist[tid] = 0;
+  hist[tid + 1024] = 0;
+  if (tid == 0) ncand = 0;
+  __syncthreads();
+  for (int w = 0; w < 16; ++w) {
+    lo = wt[0][w] < lo ? wt[0][w] : lo;
+    hi = wt[1][w] > hi ? wt[1][w] : hi;
+  }
+  unsigned int krem = (unsigned int)k, count;
+  int shift;
+  for (;;) {
+    // the keys in [lo, hi] by 2048 bins
+    const unsigned int range = hi - lo;
+    shift = range ? 32 - __builtin_clz(range) - 11 : 0;
+    shift = shift > 0 ? shift : 0;
+    each([&](int, int, unsigned int x, bool in) {
+      if (in && x >= lo && x <= hi) atomicAdd(&hist[(x - lo) >> shift], 1u);
+    });
+    __syncthreads();
+    const unsigned int h[2] = {hist[2 * tid], hist[2 * tid + 1]};
+    pick_bin<2, 16>(h, krem, wt[0], sel);
+    krem -= sel[1];
+    count = sel[2];
+    lo += sel[0] << shift;
+    const unsigned int width = (1u << shift) - 1u;
+    hi = hi - lo > width ? lo + width : hi;
+    if (count <= 1024 || shift == 0) break;
+    hist[tid] = 0;
+    hist[tid + 1024] = 0;
+    __syncthreads();
+  }
+  // the krem largest of the `count` keys in [lo, hi]
+  if (count <= 1024) {
+    each([&](int, int i, unsigned int x, bool in) {
+      if (in && x >= lo && x <= hi) {
+        const unsigned int q = atomicAdd(&ncand, 1u);
+        ckey[q] = x;
+        cidx[q] = i;
+      }
+    });
+    __syncthreads();
+    // rank of each candidate: four lanes share one when there are few
+    const int quad = count <= 256 ? 4 : 1;
+    const int c = tid / quad;
+    if (c < (int)count) {
+      const unsigned int kc = ckey[c];
+      const int ic = cidx[c];
+      int rank = 0;
+      for (int q = tid & (quad - 1); q < (int)count; q += quad) rank += (ckey[q] > kc || (ckey[q] == kc && cidx[q] < ic)) ? 1 : 0;
+      if (quad == 4) {
+        rank += __shfl_xor(rank, 1, 64);
+        rank += __shfl_xor(rank, 2, 64);
+      }
+      if (rank == (int)krem - 1) {
+        cut[0] = kc;
+        cut[1] = (unsigned int)ic;
+      }
+    }
+    __syncthreads();
+  } else {
+    // more than 1024 equal keys (lo == hi): the krem-th in index order
+    each([&](int j, int, unsigned int x, bool in) {
+      const unsigned long long beq = __ballot(in && x == lo);
+      if (lane == 0) table[j * 16 + wave] = __popcll(beq);
+    });
+    __syncthreads();
+    int tot;
+    const int pref = block_scan(tid < 16 * KPT ? table[tid] : 0, wtot, &tot);
+    if (tid < 16 * KPT) table[tid] = pref;
+    __syncthreads();
+    each([&](int j, int i, unsigned int x, bool in) {
+      const bool eq = in && x == lo;
+      const unsigned long long beq = __ballot(eq);
+      const int rank = table[j * 16 + wave] + __popcll(beq & ((1ull << lane) - 1ull));
+      if (eq && rank == (int)krem - 1) {
+        cut[0] = lo;
+        cut[1] = (unsigned int)i;
+      }
+    });
+    __syncthreads();
+  }
+  const unsigned int ckth = cut[0];
+  const int ikth = (int)cut[1];
+  if (tid == 0 && tau) *tau = key_score(ckth);
+  each([&](int j, int i, unsigned int x, bool in) {
+    const bool keep = in && (x > ckth || (x == ckth && i <= ikth));
+    const unsigned long long bk = __ballot(keep);
+    if (lane == 0) table[j * 16 + wave] = __popcll(bk);
+    if (in) mask[i] = (uint8_t)keep;
+  });
+  __syncthreads();
+  int tot;
+  const int pref = block_scan(tid < 16 * KPT ? table[tid] : 0, wtot, &tot);
+  if (tid < 16 * KPT) table[tid] = pref;
+  __syncthreads();
+  each([&](int j, int i, unsigned int x, bool in) {
+    const bool keep = in && (x > ckth || (x == ckth && i <= ikth));
+    const unsigned long long bk = __ballot(keep);
+    if (keep) {
+      const long long pos = (long long)(table[j * 16 + wave] + __popcll(bk & ((1ull << lane) - 1ull))) * group;
+      for (int c = 0; c < group; ++c) idx[pos + c] = i * group + c;
+    }
+  });
+}
+
+// ---------------------------------------------------------------------------------------------
+// top-k select over a long score vector (all layers' scores at once for a global threshold, or a stress input), in four
+// launches, each reading the scores once; the last workgroup of each of the first three (device counter) makes the choice
+// that the next one needs, so no launch is spent on it:
+//   hist 0   histogram of the top 13 key bits (sign, exponent, 4 mantissa bits); the bin of the k-th largest key
+//   hist 1   of the keys in that bin, the next 13 bits
+//   count    per workgroup: keys above the 26-bit prefix, and (few) keys that have it by their last 6 bits;
+//            then the threshold itself, and per workgroup where its kept entries go and how many of its entries equal to
+//            the threshold are kept (lower indices first)
+//   write    mask and ascending indices
+// Every input takes the same path, also one of equal scores.  48 x 28672 scores: 79 -> 34 us.
+// ---------------------------------------------------------------------------------------------
+namespace big {
+constexpr int BINS = 8192;          // 13 bits
+constexpr int THREADS = 512;
+constexpr int MAXBLOCKS = 512;
+struct State {
+  unsigned int ghist[2][BINS];      // these and the counters are cleared before every select
+  unsigned int glow[64];            // keys with the 26-bit prefix, by their last 6 bits
+  unsigned int done[3];             // workgroups that have finished, per launch
+  unsigned int clear_end;
+  unsigned int prefix[2];           // chosen 13-bit and 26-bit prefix
+  unsigned int krem[2];             // keys still to keep among those that have it
+  unsigned int thr;                 // the k-th largest key
+  unsigned int gt[MAXBLOCKS];       // keys above the 26-bit prefix in the workgroup's chunk
+  unsigned int suf[MAXBLOCKS][65];  // keys with the prefix whose last 6 bits are not below the index
+  unsigned int kpre[MAXBLOCKS];     // kept entries before the chunk
+  unsigned int eqkeep[MAXBLOCKS];   // entries equal to the threshold that the chunk keeps
+};
+}  // namespace big
+
+static void big_plan(long long n, int* blocks, long long* chunk) {
+  // two trips per workgroup and more: every workgroup adds its counts of the same few hundred bins to the global histogram,
+  // and adds to one address go one after another
+  long long b = n / (16 * big::THREADS);
+  if (b > big::MAXBLOCKS) b = big::MAXBLOCKS;
+  if (b < 1) b = 1;
+  long long c = (n + b - 1) / b;
+  c = (c + 8 * big::THREADS - 1) / (8 * big::THREADS) * (8 * big::THREADS);
+  *blocks = (int)((n + c - 1) / c);
+  *chunk = c;
+}
+
+size_t topk_scratch_bytes(int n) { return n <= 65536 ? 0 : ((sizeof(big::State) + 255) & ~size_t(255)); }
+
+// f(key, index) for this workgroup's chunk: eight consecutive scores per thread and trip
+template <typename F>
+__device__ __forceinline__ void big_scan(const float* score, long long beg, long long end, int vec, F f) {
+  for (long long i0 = beg + 8 * (long long)threadIdx.x; i0 < end; i0 += 8 * big::THREADS) {
+    float x[8];
+    if (vec && i0 + 8 <= end) {
+      const float4 a = *(const float4*)(score + i0), b = *(const float4*)(score + i0 + 4);
+      x[0] = a.x; x[1] = a.y; x[2] = a.z; x[3] = a.w; x[4] = b.x; x[5] = b.y; x[6] = b.z; x[7] = b.w;
+#pragma unroll
+      for (int e = 0; e < 8; ++e) f(score_key(x[e]));
+    } else {
+      for (long long i = i0; i < end && i < i0 + 8; ++i) f(score_key(score[i]));
+    }
+  }
+}
+template <int LEVEL>
+__global__ __launch_bounds__(big::THREADS) void topk_hist_kernel(const float* score, long long n, long long k, long long chunk, int vec, big::State* st) {
+  __shared__ unsigned int hist[big::BINS];
+  __shared__ unsigned int wt[8], sel[3], flag;
+  const int tid = threadIdx.x;
+  for (int i = tid; i < big::BINS; i += big::THREADS) hist[i] = 0;
+  const unsigned int prefix = LEVEL ? st->prefix[0] : 0u;
+  __syncthreads();
+  const long long beg = (long long)blockIdx.x * chunk, end = beg + chunk < n ? beg + chunk : n;
+  big_scan(score, beg, end, vec, [&](unsigned int key) {
+    if (LEVEL == 0) atomicAdd(&hist[key >> 19], 1u);
+    else if (key >> 19 == prefix) atomicAdd(&hist[(key >> 6) & 8191u], 1u);
+  });
+  __syncthreads();
+  for (int i = tid; i < big::BINS; i += big::THREADS) {
+    const unsigned int h = hist[i];
+    if (h) atomicAdd(&st->ghist[LEVEL][i], h);
+  }
+  if (!last_block(&st->done[LEVEL], &flag)) return;
+  // through LDS: consecutive threads read consecutive counts
+  unsigned int h[16];
+#pragma unroll
+  for (int b = 0; b < 16; ++b) h[b] = agent_get(&st->ghist[LEVEL][tid + big::THREADS * b]);
+#pragma unroll
+  for (int b = 0; b < 16; ++b) hist[tid + big::THREADS * b] = h[b];
+  __syncthreads();
+#pragma unroll
+  for (int b = 0; b < 16; ++b) h[b] = hist[16 * tid + b];
+  const unsigned int krem = LEVEL ? st->krem[0] : (unsigned int)k;
+  pick_bin<16, 8>(h, krem, wt, sel);
+  if (tid == 0) {
+    st->prefix[LEVEL] = LEVEL ? (prefix << 13) | sel[0] : sel[0];
+    st->krem[LEVEL] = krem - sel[1];
   }
 }
 
-// Each thread takes EPT consecutive entries per round (index order is thread order), so a round costs one block
-// scan for EPT * THREADS entries.
-template <int LEVEL>
-__global__ __launch_bounds__(big::THREADS) void topk_gather_kernel(const float* score, long long n, uint8_t* mask, BigTopkPlan pl) {
-  constexpr int EPT = 8;
-  __shared__ int wave_tot[16];
-  __shared__ unsigned int kept_blk[big::MAXBLOCKS];
-  const BigLevel& lv = pl.lv[LEVEL];
-  const unsigned int b = lv.state->bucket;
-  if (LEVEL == 1) {
-    for (int i = threadIdx.x; i < big::MAXBLOCKS; i += big::THREADS) kept_blk[i] = 0;
-    __syncthreads();
+__global__ __launch_bounds__(big::THREADS) void topk_count_kernel(const float* score, long long n, long long chunk, int vec, float* tau, big::State* st) {
+  __shared__ unsigned int low[64], gts, flag, s_low, s_above;
+  __shared__ int wtot[8];
+  const int tid = threadIdx.x;
+  if (tid < 64) low[tid] = 0;
+  if (tid == 0) gts = 0;
+  const unsigned int prefix = st->prefix[1];
+  __syncthreads();
+  const long long beg = (long long)blockIdx.x * chunk, end = beg + chunk < n ? beg + chunk : n;
+  unsigned int above = 0;
+  big_scan(score, beg, end, vec, [&](unsigned int key) {
+    const unsigned int p = key >> 6;
+    above += p > prefix ? 1u : 0u;
+    if (p == prefix) atomicAdd(&low[key & 63u], 1u);
+  });
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) above += __shfl_down(above, o, 64);
+  if ((tid & 63) == 0) atomicAdd(&gts, above);
+  __syncthreads();
+  if (tid < 64) {
+    const unsigned int c = low[tid];
+    unsigned int suf = c;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+      const unsigned int v = __shfl_down(suf, o, 64);
+      if (tid + o < 64) suf += v;
+    }
+    agent_put(&st->suf[blockIdx.x][tid], suf);
+    if (c) atomicAdd(&st->glow[tid], c);
   }
-  long long beg, end;
-  level_range<LEVEL>(pl, n, &beg, &end);
-  unsigned int run = lv.coff[blockIdx.x];
-  unsigned int n_above = 0;   // level 0: this thread's keys above the bucket
-  for (long long base = beg; base < end; base += (long long)EPT * big::THREADS) {
-    const long long i0 = base + (long long)threadIdx.x * EPT;
-    unsigned int key[EPT];
-    int id[EPT];
-    int cnt = 0;
-    unsigned int isc = 0, above = 0;
-    const bool whole = LEVEL == 0 && pl.vec && i0 + EPT <= end;   // i0 is a multiple of 8
-    float xv[EPT];
+  if (tid == 64) agent_put(&st->gt[blockIdx.x], gts);
+  if (tid == 65) agent_put(&st->suf[blockIdx.x][64], 0u);
+  if (!last_block(&st->done[2], &flag)) return;
+  const int blocks = (int)gridDim.x;
+  // the last six bits of the threshold
+  if (tid < 64) {
+    const unsigned int krem = st->krem[1];
+    const unsigned int c = agent_get(&st->glow[tid]);
+    unsigned int suf = c;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+      const unsigned int v = __shfl_down(suf, o, 64);
+      if (tid + o < 64) suf += v;
+    }
+    const unsigned int over = suf - c;
+    if (over < krem && suf >= krem) {
+      s_low = (unsigned int)tid;
+      s_above = krem - over;             // entries equal to the threshold that are kept
+      st->thr = (prefix << 6) | (unsigned int)tid;
+      if (tau) *tau = key_score((prefix << 6) | (unsigned int)tid);
+    }
+  }
+  __syncthreads();
+  // per workgroup (one thread each): entries above the threshold and equal to it, then their prefixes
+  unsigned int g = 0, e = 0;
+  if (tid < blocks) {
+    const unsigned int over = agent_get(&st->suf[tid][s_low + 1]);
+    e = agent_get(&st->suf[tid][s_low]) - over;
+    g = agent_get(&st->gt[tid]) + over;
+  }
+  int tot;
+  const unsigned int ebefore = (unsigned int)block_scan((int)e, wtot, &tot);
+  const unsigned int ekeep = ebefore >= s_above ? 0u : (e < s_above - ebefore ? e : s_above - ebefore);
+  const unsigned int kpre = (unsigned int)block_scan((int)(g + ekeep), wtot, &tot);
+  if (tid < blocks) {
+    st->kpre[tid] = kpre;
+    st->eqkeep[tid] = ekeep;
+  }
+}
+
+__global__ __launch_bounds__(big::THREADS) void topk_write_kernel(const float* score, long long n, long long chunk, int vec, int group, uint8_t* mask,
+                                                                  int32_t* idx, const big::State* st) {
+  __shared__ int wtot[8];
+  const long long beg = (long long)blockIdx.x * chunk, end = beg + chunk < n ? beg + chunk : n;
+  const unsigned int thr = st->thr, eqkeep = st->eqkeep[blockIdx.x];
+  unsigned int run = st->kpre[blockIdx.x], eqrun = 0;
+  for (long long base = beg; base < end; base += 8 * big::THREADS) {
+    const long long i0 = base + 8 * (long long)threadIdx.x;
+    const bool whole = vec && i0 + 8 <= end;
+    unsigned int gt = 0, eq = 0;
     if (whole) {
-      const float4 x0 = *(const float4*)(score + i0), x1 = *(const float4*)(score + i0 + 4);
-      xv[0] = x0.x; xv[1] = x0.y; xv[2] = x0.z; xv[3] = x0.w;
-      xv[4] = x1.x; xv[5] = x1.y; xv[6] = x1.z; xv[7] = x1.w;
-    }
+      const float4 a = *(const float4*)(score + i0), b = *(const float4*)(score + i0 + 4);
+      const float x[8] = {a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w};
 #pragma unroll
-    for (int e = 0; e < EPT; ++e) {
-      const long long i = i0 + e;
-      const bool in = i < end;
-      key[e] = whole ? score_key(xv[e]) : (in ? level_key<LEVEL>(pl, score, i) : 0u);
-      id[e] = LEVEL == 0 ? (int)i : (in ? pl.lv[0].cand_idx[i] : 0);
-      const unsigned int dgt = level_digit<LEVEL>(key[e]);
-      if (in && dgt == b) { isc |= 1u << e; ++cnt; }
-      if (in && dgt > b) above |= 1u << e;
+      for (int e = 0; e < 8; ++e) {
+        const unsigned int key = score_key(x[e]);
+        gt |= (key > thr ? 1u : 0u) << e;
+        eq |= (key == thr ? 1u : 0u) << e;
+      }
+    } else {
+      for (int e = 0; e < 8; ++e)
+        if (i0 + e < end) {
+          const unsigned int key = score_key(score[i0 + e]);
+          gt |= (key > thr ? 1u : 0u) << e;
+          eq |= (key == thr ? 1u : 0u) << e;
+        }
     }
+    // both prefixes in one scan: at most 4096 entries each
     int tot;
-    unsigned int pos = run + (unsigned int)block_scan(cnt, wave_tot, &tot);
-    if (LEVEL == 0) {
-      n_above += (unsigned int)__popc(above);
-      if (whole) {   // eight mask bytes in one store
-        unsigned long long m8 = 0;
+    const int pre = block_scan((int)((unsigned)__popc(gt) | ((unsigned)__popc(eq) << 16)), wtot, &tot);
+    const unsigned int gpre = (unsigned)pre & 0xffffu, epre = eqrun + ((unsigned)pre >> 16);
+    unsigned int ekept_before = epre < eqkeep ? epre : eqkeep, keep = gt;
+    unsigned int pos = run + gpre + (ekept_before - (eqrun < eqkeep ? eqrun : eqkeep));
+    unsigned int left = eqkeep - ekept_before;
+    for (unsigned int q = eq; q && left; q &= q - 1, --left) keep |= q & (0u - q);
+    if (whole) {   // eight mask bytes in one store
+      unsigned long long m8 = 0;
 #pragma unroll
-        for (int e = 0; e < EPT; ++e) m8 |= (unsigned long long)((above >> e) & 1u) << (8 * e);
-        *(unsigned long long*)(mask + i0) = m8;
-      }
+      for (int e = 0; e < 8; ++e) m8 |= (unsigned long long)((keep >> e) & 1u) << (8 * e);
+      *(unsigned long long*)(mask + i0) = m8;
+    } else {
+      for (int e = 0; e < 8; ++e)
+        if (i0 + e < end) mask[i0 + e] = (uint8_t)((keep >> e) & 1u);
     }
 #pragma unroll
-    for (int e = 0; e < EPT; ++e) {
-      const long long i = i0 + e;
-      if (LEVEL == 0) {
-        if (!whole && i < end) mask[i] = (uint8_t)((above >> e) & 1u);
-      } else if ((above >> e) & 1u) {
-        mask[id[e]] = 1;
-        atomicAdd(&kept_blk[(long long)id[e] / pl.chunk0], 1u);
-      }
-      if ((isc >> e) & 1u) {
-        lv.cand_key[pos] = key[e];
-        lv.cand_idx[pos] = id[e];
+    for (int e = 0; e < 8; ++e)
+      if ((keep >> e) & 1u) {
+        for (int c = 0; c < group; ++c) idx[(long long)pos * group + c] = (int)(i0 + e) * group + c;
         ++pos;
       }
-    }
-    run += (unsigned int)tot;
-  }
-  if (LEVEL == 1) kept_flush(kept_blk, pl.kept_cand, pl.blocks0);
-  if (LEVEL == 0) {
-    int tot;
-    (void)block_scan((int)n_above, wave_tot, &tot);
-    if (threadIdx.x == 0) pl.gtcnt[blockIdx.x] = (unsigned int)tot;
-  }
-}
-
-// One block: the krem largest of the level-1 candidates on their last 10 key bits, ties to the lower index (the
-// list is in index order), then the exclusive scan of the per-chunk kept counts.
-__global__ __launch_bounds__(1024) void topk_resolve_kernel(uint8_t* mask, float* tau, BigTopkPlan pl) {
-  __shared__ unsigned int hist[1024];
-  __shared__ unsigned int sel_low, sel_krem;
-  __shared__ int wave_tot[16];
-  __shared__ unsigned int kept_blk[big::MAXBLOCKS];
-  const int tid = threadIdx.x;
-  const BigLevel& lv = pl.lv[1];
-  const unsigned int ncand = lv.state->ncand;
-  hist[tid] = 0;
-  kept_blk[tid] = 0;
-  __syncthreads();
-  for (unsigned int i = tid; i < ncand; i += 1024) atomicAdd(&hist[lv.cand_key[i] & 0x3ffu], 1u);
-  __syncthreads();
-  if (tid == 0) {
-    const unsigned int krem = lv.state->krem;
-    unsigned int cum = 0;
-    int d = 1023;
-    for (; d > 0; --d) {
-      if (cum + hist[d] >= krem) break;
-      cum += hist[d];
-    }
-    sel_low = (unsigned int)d;
-    sel_krem = krem - cum;
-    if (tau) *tau = key_score((pl.lv[0].state->bucket << 21) | (lv.state->bucket << 10) | (unsigned int)d);
-  }
-  __syncthreads();
-  const unsigned int low = sel_low, krem = sel_krem;   // krem of the candidates equal to the threshold are kept
-  unsigned int run_eq = 0;
-  for (unsigned int base = 0; base < ncand; base += 1024) {
-    const unsigned int i = base + tid;
-    const bool in = i < ncand;
-    unsigned int key = 0;
-    int id = 0;
-    if (in) {
-      key = lv.cand_key[i] & 0x3ffu;
-      id = lv.cand_idx[i];
-    }
-    const bool eq = in && key == low;
-    int tot;
-    const int r = block_rank(eq, wave_tot, &tot);
-    const bool keep = in && (key > low || (eq && run_eq + (unsigned int)r < krem));
-    if (keep) {
-      mask[id] = 1;
-      atomicAdd(&kept_blk[(long long)id / pl.chunk0], 1u);
-    }
-    run_eq += (unsigned int)tot;
-  }
-  __syncthreads();
-  // exclusive scan of kept = above the level-0 bucket + kept candidates, per level-0 chunk (<= 1024 = one per thread)
-  const unsigned int mine = tid < pl.blocks0 ? pl.gtcnt[tid] + pl.kept_cand[tid] + kept_blk[tid] : 0;
-  __syncthreads();
-  kept_blk[tid] = mine;
-  __syncthreads();
-  for (int o = 1; o < 1024; o <<= 1) {
-    const unsigned int v = tid >= o ? kept_blk[tid - o] : 0;
-    __syncthreads();
-    kept_blk[tid] += v;
-    __syncthreads();
-  }
-  if (tid < pl.blocks0) pl.kpre[tid] = kept_blk[tid] - mine;
-}
-
-__global__ __launch_bounds__(big::THREADS) void topk_compact_kernel(const uint8_t* mask, long long n, int32_t* idx, BigTopkPlan pl) {
-  constexpr int EPT = 8;   // eight consecutive mask bytes per thread: chunk0 and every round start are multiples of 8
-  __shared__ int wave_tot[16];
-  const long long beg = (long long)blockIdx.x * pl.chunk0;
-  const long long end = beg + pl.chunk0 < n ? beg + pl.chunk0 : n;
-  unsigned int run = pl.kpre[blockIdx.x];
-  for (long long base = beg; base < end; base += (long long)EPT * big::THREADS) {
-    const long long i0 = base + (long long)threadIdx.x * EPT;
-    unsigned int bits = 0;
-    if (pl.vec && i0 + EPT <= end) {
-      const unsigned long long m8 = *(const unsigned long long*)(mask + i0);
-#pragma unroll
-      for (int e = 0; e < EPT; ++e)
-        if ((m8 >> (8 * e)) & 0xffull) bits |= 1u << e;
-    } else {
-#pragma unroll
-      for (int e = 0; e < EPT; ++e)
-        if (i0 + e < end && mask[i0 + e]) bits |= 1u << e;
-    }
-    int tot;
-    unsigned int pos = run + (unsigned int)block_scan(__popc(bits), wave_tot, &tot);
-#pragma unroll
-    for (int e = 0; e < EPT; ++e)
-      if ((bits >> e) & 1u) idx[pos++] = (int)(i0 + e);
-    run += (unsigned int)tot;
+    const unsigned int etot = eqrun + ((unsigned)tot >> 16);
+    run += ((unsigned)tot & 0xffffu) + ((etot < eqkeep ? etot : eqkeep) - (eqrun < eqkeep ? eqrun : eqkeep));
+    eqrun = etot;
   }
 }
 
 strp_status launch_topk(strp_ctx* ctx, const float* score, int n, int k, int group, uint8_t* mask, int32_t* idx, float* tau,
                         void* scratch, size_t scratch_bytes) {
   ProfScope ps(ctx, "topk", 0.0, 5.0 * (double)n + 4.0 * (double)k * group);
-  const bool big_path = n > 65536 && group == 1 && k > 0 && k < n;
-  if (!big_path) {
-    if (n <= 16 * 1024 && k > 0 && k < n)
-      hipLaunchKernelGGL(topk_small_kernel, dim3(1), dim3(1024), 0, ctx->stream, score, n, k, group, mask, idx, tau);
-    else
-      hipLaunchKernelGGL(topk_kernel, dim3(1), dim3(1024), 0, ctx->stream, score, n, k, group, mask, idx, tau);
-    STRP_HIP(ctx, hipGetLastError());
-    return STRP_OK;
+  if (k <= 0 || k >= n) {
+    hipLaunchKernelGGL(topk_all_kernel, dim3(1), dim3(1024), 0, ctx->stream, score, n, k >= n ? 1 : 0, group, mask, idx, tau);
+  } else if (n <= 65536) {
+    const auto one = [&](auto kernel) { hipLaunchKernelGGL(kernel, dim3(1), dim3(1024), 0, ctx->stream, score, n, k, group, mask, idx, tau); };
+    if (n <= 4096) one(topk_small_kernel<4, true>);
+    else if (n <= 16384) one(topk_small_kernel<16, true>);
+    else one(topk_small_kernel<64, false>);
+  } else {
+    if (!scratch || scratch_bytes < topk_scratch_bytes(n))
+      return fail(ctx, STRP_ENOMEM, "top-k over %d scores needs %zu bytes of workspace", n, topk_scratch_bytes(n));
+    int blocks;
+    long long chunk;
+    big_plan(n, &blocks, &chunk);
+    const int vec = (((uintptr_t)score & 15) == 0 && ((uintptr_t)mask & 7) == 0) ? 1 : 0;
+    big::State* st = (big::State*)scratch;
+    STRP_TRY(fill_zero(ctx, st, offsetof(big::State, clear_end)));
+    const dim3 b(blocks), th(big::THREADS);
+    hipLaunchKernelGGL((topk_hist_kernel<0>), b, th, 0, ctx->stream, score, (long long)n, (long long)k, chunk, vec, st);
+    hipLaunchKernelGGL((topk_hist_kernel<1>), b, th, 0, ctx->stream, score, (long long)n, (long long)k, chunk, vec, st);
+    hipLaunchKernelGGL(topk_count_kernel, b, th, 0, ctx->stream, score, (long long)n, chunk, vec, tau, st);
+    hipLaunchKernelGGL(topk_write_kernel, b, th, 0, ctx->stream, score, (long long)n, chunk, vec, group, mask, idx, (const big::State*)st);
   }
-  if (!scratch || scratch_bytes < topk_scratch_bytes(n))
-    return fail(ctx, STRP_ENOMEM, "top-k over %d scores needs %zu bytes of workspace", n, topk_scratch_bytes(n));
-  BigTopkPlan pl;
-  big_plan(n, &pl.blocks0, &pl.chunk0);
-  pl.vec = (((uintptr_t)score & 15) == 0 && ((uintptr_t)mask & 7) == 0) ? 1 : 0;
-  char* p = (char*)scratch;
-  auto take = [&](size_t bytes) { char* q = p; p += (bytes + 255) & ~size_t(255); return q; };
-  pl.lv[0].blocks = pl.blocks0;
-  pl.lv[1].blocks = big::L1BLOCKS;
-  pl.lv[0].bhist = (unsigned int*)take((size_t)pl.blocks0 * big::BINS * 4);
-  pl.lv[1].bhist = (unsigned int*)take((size_t)big::L1BLOCKS * big::BINS * 4);
-  // contiguous from here to kept_cand: cleared by one fill
-  char* z0 = p;
-  pl.lv[0].ghist = (unsigned int*)take(big::BINS * 4);
-  pl.lv[1].ghist = (unsigned int*)take(big::BINS * 4);
-  pl.lv[0].state = (big::State*)take(sizeof(big::State));
-  pl.lv[1].state = (big::State*)take(sizeof(big::State));
-  pl.kept_cand = (unsigned int*)take((size_t)pl.blocks0 * 4);
-  const size_t zbytes = (size_t)(p - z0);
-  pl.lv[0].coff = (unsigned int*)take((size_t)pl.blocks0 * 4);
-  pl.lv[1].coff = (unsigned int*)take((size_t)big::L1BLOCKS * 4);
-  pl.gtcnt = (unsigned int*)take((size_t)pl.blocks0 * 4);
-  pl.kpre = (unsigned int*)take((size_t)pl.blocks0 * 4);
-  for (int l = 0; l < 2; ++l) {
-    pl.lv[l].cand_key = (unsigned int*)take((size_t)n * 4);
-    pl.lv[l].cand_idx = (int*)take((size_t)n * 4);
-  }
-  STRP_TRY(fill_zero(ctx, z0, zbytes));
-  const dim3 b0(pl.blocks0), b1(big::L1BLOCKS), th(big::THREADS);
-  hipLaunchKernelGGL((topk_hist_kernel<0>), b0, th, 0, ctx->stream, score, (long long)n, pl);
-  hipLaunchKernelGGL((topk_pick_kernel<0>), dim3(1), dim3(1024), 0, ctx->stream, (long long)k, pl);
-  hipLaunchKernelGGL((topk_gather_kernel<0>), b0, th, 0, ctx->stream, score, (long long)n, mask, pl);
-  hipLaunchKernelGGL((topk_hist_kernel<1>), b1, th, 0, ctx->stream, score, (long long)n, pl);
-  hipLaunchKernelGGL((topk_pick_kernel<1>), dim3(1), dim3(1024), 0, ctx->stream, (long long)k, pl);
-  hipLaunchKernelGGL((topk_gather_kernel<1>), b1, th, 0, ctx->stream, score, (long long)n, mask, pl);
-  hipLaunchKernelGGL(topk_resolve_kernel, dim3(1), dim3(1024), 0, ctx->stream, mask, tau, pl);
-  hipLaunchKernelGGL(topk_compact_kernel, b0, th, 0, ctx->stream, (const uint8_t*)mask, (long long)n, idx, pl);
   STRP_HIP(ctx, hipGetLastError());
   return STRP_OK;
 }

@@ -30,11 +30,11 @@ struct Profiler {
   }
 };
 
-// Scratch of strp_mask_topk_static (the entry point for callers that cannot allocate): per-block histograms, candidate
-// lists and counters of the multi-block select, for up to STRP_TOPK_STATIC_MAX_N scores.  Every GPU the library runs on
+// Scratch of strp_mask_topk_static (the entry point for callers that cannot allocate): histograms and counters of the
+// multi-block select.  Every GPU the library runs on
 // holds its own copy of the array until the process ends; in host code the array's name is only a handle for
 // hipGetSymbolAddress, the device address is resolved once per device in strp_create and kept in g_topk_scratch.
-constexpr size_t TOPK_STATIC_BYTES = 16 * (size_t)STRP_TOPK_STATIC_MAX_N + (8u << 20);
+constexpr size_t TOPK_STATIC_BYTES = 1u << 20;
 static __device__ __align__(256) unsigned char topk_static_scratch[TOPK_STATIC_BYTES];
 constexpr int MAX_DEVICES = 64;
 static void* g_topk_scratch[MAX_DEVICES];
@@ -505,7 +505,7 @@ strp_status strp_mask_topk(strp_ctx* ctx, const float* score, int32_t n, int32_t
   if (!ctx) return STRP_EINVAL;
   if (!score || !mask || !idx) return fail(ctx, STRP_EINVAL, "mask_topk: null argument");
   if (n <= 0 || k < 0 || k > n || group <= 0) return fail(ctx, STRP_EINVAL, "mask_topk: need n > 0, 0 <= k <= n, group > 0");
-  const size_t need = (group == 1 && k > 0 && k < n) ? topk_scratch_bytes(n) : 0;
+  const size_t need = (k > 0 && k < n) ? topk_scratch_bytes(n) : 0;
   void* scratch = nullptr;
   if (need) {
     Arena arena(ctx);
@@ -549,7 +549,10 @@ strp_status strp_alloc_softmax(strp_ctx* ctx, const double* energies, int32_t L,
   return launch_alloc(ctx, energies, L, n_units, group_id, rbar, temperature, rmax, 0, r_out, nprune_out);
 }
 
-size_t strp_topk_workspace_bytes(int32_t n) { return n > 0 ? topk_scratch_bytes(n) + 512 : 0; }
+size_t strp_topk_workspace_bytes(int32_t n) {
+  const size_t b = n > 0 ? topk_scratch_bytes(n) : 0;
+  return b ? b + 512 : 0;
+}
 
 strp_status strp_mask_topk_static(strp_ctx* ctx, const float* score, int32_t n, int32_t k, uint8_t* mask, int32_t* idx, float* tau) {
   if (!ctx) return STRP_EINVAL;
