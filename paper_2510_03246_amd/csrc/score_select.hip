@@ -202,36 +202,79 @@ strp_status launch_rowsum_reduce(strp_ctx* ctx, const float* part, int nq, int s
 }
 
 // ---------------------------------------------------------------------------------------------
-// squared column norms: block = 64 columns x 4 row lanes
+// squared column norms: block = 64 columns, each wavefront 8 rows x 8 groups of 8 columns at a time (128 rows per trip of
+// the block: a weight matrix has too few 64-column blocks to fill the chip, so the depth of one block's loop is what it
+// takes: 3072 columns of 768 rows 75 -> 9 us).  vec: 16-byte loads of 8 bf16 or 2 x 4 fp32 columns.
 // ---------------------------------------------------------------------------------------------
 template <bool BF16>
-__global__ __launch_bounds__(256) void colnorm2_kernel(const void* Wv, int rows, int cols, long long ldw, double* n2) {
-  const int c = blockIdx.x * 64 + (threadIdx.x & 63);
-  const int rl = threadIdx.x >> 6;
-  double acc = 0.0;
-  if (c < cols) {
-    for (int r = rl; r < rows; r += 4) {
-      double x;
-      if (BF16) {
-        x = (double)__builtin_bit_cast(float, (unsigned int)((const unsigned short*)Wv)[(long long)r * ldw + c] << 16);
-      } else {
-        x = (double)((const float*)Wv)[(long long)r * ldw + c];
-      }
-      acc = __builtin_fma(x, x, acc);
+__device__ __forceinline__ void load8(const void* W, long long off, float (&x)[8]) {
+  if (BF16) {
+    const uint4 w = *(const uint4*)((const unsigned short*)W + off);
+    const unsigned int u[4] = {w.x, w.y, w.z, w.w};
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      x[2 * q] = bf16lo(u[q]);
+      x[2 * q + 1] = bf16hi(u[q]);
     }
+  } else {
+    const float4 a = *(const float4*)((const float*)W + off), b = *(const float4*)((const float*)W + off + 4);
+    x[0] = a.x; x[1] = a.y; x[2] = a.z; x[3] = a.w; x[4] = b.x; x[5] = b.y; x[6] = b.z; x[7] = b.w;
   }
-  __shared__ double sh[4][64];
-  sh[rl][threadIdx.x & 63] = acc;
+}
+template <bool BF16>
+__device__ __forceinline__ float load1(const void* W, long long off) {
+  return BF16 ? __builtin_bit_cast(float, (unsigned int)((const unsigned short*)W)[off] << 16) : ((const float*)W)[off];
+}
+
+template <bool BF16>
+__global__ __launch_bounds__(1024) void colnorm2_kernel(const void* W, int rows, int cols, long long ldw, int vec, double* n2) {
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int c0 = blockIdx.x * 64 + 8 * (lane & 7);
+  const int row0 = wave * 8 + (lane >> 3);
+  double acc[8];
+#pragma unroll
+  for (int q = 0; q < 8; ++q) acc[q] = 0.0;
+  if (vec && c0 + 8 <= cols) {
+#pragma unroll 4
+    for (int r = row0; r < rows; r += 128) {
+      float x[8];
+      load8<BF16>(W, (long long)r * ldw + c0, x);
+#pragma unroll
+      for (int q = 0; q < 8; ++q) acc[q] = __builtin_fma((double)x[q], (double)x[q], acc[q]);
+    }
+  } else {
+    for (int r = row0; r < rows; r += 128)
+      for (int q = 0; q < 8 && c0 + q < cols; ++q) {
+        const double x = load1<BF16>(W, (long long)r * ldw + c0 + q);
+        acc[q] = __builtin_fma(x, x, acc[q]);
+      }
+  }
+  __shared__ double sh[16][64];
+#pragma unroll
+  for (int q = 0; q < 8; ++q) {
+    acc[q] += __shfl_xor(acc[q], 8, 64);
+    acc[q] += __shfl_xor(acc[q], 16, 64);
+    acc[q] += __shfl_xor(acc[q], 32, 64);
+  }
+  if (lane < 8)
+#pragma unroll
+    for (int q = 0; q < 8; ++q) sh[wave][8 * lane + q] = acc[q];
   __syncthreads();
-  if (rl == 0 && c < cols) n2[c] = sh[0][threadIdx.x] + sh[1][threadIdx.x] + sh[2][threadIdx.x] + sh[3][threadIdx.x];
+  if (tid < 64 && blockIdx.x * 64 + tid < cols) {
+    double t = 0.0;
+#pragma unroll
+    for (int w = 0; w < 16; ++w) t += sh[w][tid];
+    n2[blockIdx.x * 64 + tid] = t;
+  }
 }
 
 strp_status launch_colnorm2(strp_ctx* ctx, const void* W, int w_dtype, int rows, int cols, long long ldw, double* n2) {
-  dim3 grid((cols + 63) / 64), block(256);
+  dim3 grid((cols + 63) / 64), block(1024);
+  const int vec = ((uintptr_t)W & 15) == 0 && ldw % 8 == 0;
   if (w_dtype == STRP_BF16)
-    hipLaunchKernelGGL((colnorm2_kernel<true>), grid, block, 0, ctx->stream, W, rows, cols, ldw, n2);
+    hipLaunchKernelGGL((colnorm2_kernel<true>), grid, block, 0, ctx->stream, W, rows, cols, ldw, vec, n2);
   else
-    hipLaunchKernelGGL((colnorm2_kernel<false>), grid, block, 0, ctx->stream, W, rows, cols, ldw, n2);
+    hipLaunchKernelGGL((colnorm2_kernel<false>), grid, block, 0, ctx->stream, W, rows, cols, ldw, vec, n2);
   STRP_HIP(ctx, hipGetLastError());
   return STRP_OK;
 }
@@ -285,73 +328,129 @@ strp_status launch_unit_scores(strp_ctx* ctx, const double* sums, const double* 
 }
 
 // ---------------------------------------------------------------------------------------------
-// softmax allocation: one wavefront, fp64, layers strided over lanes
-// ---------------------------------------------------------------------------------------------
-// ---------------------------------------------------------------------------------------------
 // weight statistics of a parameter group (Alg. 2 step 1): sum |w|, sum w, sum w^2 over every entry of a list of
-// matrices.  Block b keeps its own partial [3] (launches on one stream add to it in order: deterministic);
-// weight_energy_kernel folds the partials into  scale (|W|_1 + cv Var(W) + c2 |W|_2)  and adds it to the energy.
+// matrices, folded into  energy += scale (|W|_1 + cv Var(W) + c2 |W|_2).
+// A model has a few hundred small groups (a head's four slices are 0.4 MB), so a call costs its launches: one launch takes
+// up to eight matrices, and its last workgroup (device counter) adds the workgroups' partial sums in order.
+// 12 layers of d = 768: 168 calls 3.5 -> 1.0 ms.
 // ---------------------------------------------------------------------------------------------
-constexpr int WSTAT_BLOCKS = 256;
+constexpr int WSTAT_BLOCKS = 256, WSTAT_MATS = 8;
+
+struct WeightList {
+  const void* W[WSTAT_MATS];
+  long long ld[WSTAT_MATS];
+  int rows[WSTAT_MATS], cols[WSTAT_MATS];
+  int block0[WSTAT_MATS + 1];            // workgroups block0[m] .. block0[m + 1] - 1 take matrix m
+  unsigned char bf16[WSTAT_MATS], vec[WSTAT_MATS];
+  int n;
+  int first, last;                       // first / last launch of the call
+  double count, var_coef, l2_coef, scale;
+};
 
 template <bool BF16>
-__global__ __launch_bounds__(256) void weight_stats_kernel(const void* W, int rows, int cols, long long ld, double* partial) {
-  double s1 = 0.0, s = 0.0, s2 = 0.0;
-  const long long n = (long long)rows * cols;
-  for (long long e = (long long)blockIdx.x * 256 + threadIdx.x; e < n; e += (long long)WSTAT_BLOCKS * 256) {
-    const long long r = e / cols, c = e - r * cols;
-    float x;
-    if (BF16) x = __builtin_bit_cast(float, (unsigned int)((const unsigned short*)W)[r * ld + c] << 16);
-    else x = ((const float*)W)[r * ld + c];
+__device__ __forceinline__ void weight_sums(const WeightList& l, int m, unsigned int b, unsigned int blocks, double& s1, double& s, double& s2) {
+  const void* W = l.W[m];
+  const int cols = l.cols[m];
+  const long long ld = l.ld[m];
+  const unsigned int step = blocks * 256u;
+  auto add = [&](float x) {
     const double v = (double)x;
     s1 += fabs(v);
     s += v;
-    s2 += v * v;
-  }
-  __shared__ double red[4][3];
-  s1 = wave_allsum_d(s1);
-  s = wave_allsum_d(s);
-  s2 = wave_allsum_d(s2);
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  if (lane == 0) { red[wave][0] = s1; red[wave][1] = s; red[wave][2] = s2; }
-  __syncthreads();
-  if (threadIdx.x < 3) {
-    const int q = threadIdx.x;
-    partial[3 * blockIdx.x + q] += red[0][q] + red[1][q] + red[2][q] + red[3][q];
+    s2 = __builtin_fma(v, v, s2);
+  };
+  if (l.vec[m]) {                        // groups of eight columns; below 2^35 entries
+    const unsigned int per = (unsigned int)cols >> 3, n = (unsigned int)l.rows[m] * per;
+#pragma unroll 4
+    for (unsigned int g = b * 256u + threadIdx.x; g < n; g += step) {
+      const unsigned int r = g / per;
+      float x[8];
+      load8<BF16>(W, (long long)r * ld + 8 * (long long)(g - r * per), x);
+#pragma unroll
+      for (int q = 0; q < 8; ++q) add(x[q]);
+    }
+  } else {
+    const long long n = (long long)l.rows[m] * cols;
+    for (long long e = (long long)b * 256 + threadIdx.x; e < n; e += step) {
+      const long long r = e / cols;
+      add(load1<BF16>(W, r * ld + (e - r * cols)));
+    }
   }
 }
 
-__global__ __launch_bounds__(64) void weight_energy_kernel(const double* partial, double count, double var_coef, double l2_coef,
-                                                           double scale, double* energy) {
-  double a[3] = {0.0, 0.0, 0.0};
-  for (int b = threadIdx.x; b < WSTAT_BLOCKS; b += 64)
-    for (int q = 0; q < 3; ++q) a[q] += partial[3 * b + q];
-  for (int q = 0; q < 3; ++q) a[q] = wave_allsum_d(a[q]);
-  if (threadIdx.x == 0) {
-    const double mean = a[1] / count;
-    const double var = a[2] / count - mean * mean;
-    *energy += scale * (a[0] + var_coef * var + l2_coef * sqrt(a[2]));
+// partial: [WSTAT_BLOCKS][3]; run: the sums of earlier launches of the same call [3]; ticket: zero between launches
+__global__ __launch_bounds__(256) void weight_energy_kernel(const WeightList l, double* partial, double* run, unsigned int* ticket, double* energy) {
+  double s1 = 0.0, s = 0.0, s2 = 0.0;
+  int m = 0;
+  while (m + 1 < l.n && (int)blockIdx.x >= l.block0[m + 1]) ++m;
+  const unsigned int b = blockIdx.x - l.block0[m], blocks = l.block0[m + 1] - l.block0[m];
+  if (l.bf16[m]) weight_sums<true>(l, m, b, blocks, s1, s, s2);
+  else weight_sums<false>(l, m, b, blocks, s1, s, s2);
+  __shared__ double red[4][3];
+  __shared__ unsigned int last;
+  s1 = wave_sum_d(s1);
+  s = wave_sum_d(s);
+  s2 = wave_sum_d(s2);
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  if (lane == 0) {
+    red[wave][0] = s1;
+    red[wave][1] = s;
+    red[wave][2] = s2;
   }
+  __syncthreads();
+  if (tid < 3) agent_put(&partial[3 * blockIdx.x + tid], red[0][tid] + red[1][tid] + red[2][tid] + red[3][tid]);
+  if (!last_block(ticket, &last) || tid >= 64) return;
+  double a[3] = {0.0, 0.0, 0.0};
+  for (int b = tid; b < (int)gridDim.x; b += 64)
+#pragma unroll
+    for (int q = 0; q < 3; ++q) a[q] += agent_get(&partial[3 * b + q]);
+#pragma unroll
+  for (int q = 0; q < 3; ++q) a[q] = wave_allsum_d(a[q]);
+  if (tid != 0) return;
+  *ticket = 0u;
+  if (!l.first)
+    for (int q = 0; q < 3; ++q) a[q] += run[q];
+  if (!l.last) {
+    for (int q = 0; q < 3; ++q) run[q] = a[q];
+    return;
+  }
+  const double mean = a[1] / l.count;
+  const double var = a[2] / l.count - mean * mean;
+  *energy += l.scale * (a[0] + l.var_coef * var + l.l2_coef * sqrt(a[2]));
 }
 
 strp_status launch_weight_energy(strp_ctx* ctx, const strp_weight_ref* mats, int n_mats, double var_coef, double l2_coef, double scale,
-                                 double* energy, double* partial /* [3 * WSTAT_BLOCKS] scratch */) {
-  STRP_TRY(fill_zero(ctx, partial, sizeof(double) * 3 * WSTAT_BLOCKS));
-  double count = 0.0;
-  for (int i = 0; i < n_mats; ++i) {
-    const strp_weight_ref& m = mats[i];
-    if (m.dtype == STRP_BF16)
-      hipLaunchKernelGGL((weight_stats_kernel<true>), dim3(WSTAT_BLOCKS), dim3(256), 0, ctx->stream, m.W, m.rows, m.cols, (long long)m.ld, partial);
-    else
-      hipLaunchKernelGGL((weight_stats_kernel<false>), dim3(WSTAT_BLOCKS), dim3(256), 0, ctx->stream, m.W, m.rows, m.cols, (long long)m.ld, partial);
-    count += (double)m.rows * (double)m.cols;
+                                 double* energy, double* partial) {
+  WeightList l;
+  l.var_coef = var_coef; l.l2_coef = l2_coef; l.scale = scale;
+  l.count = 0.0;
+  for (int i = 0; i < n_mats; ++i) l.count += (double)mats[i].rows * (double)mats[i].cols;
+  unsigned int* ticket = (unsigned int*)ctx->status_dev + WS_TICKET;
+  for (int i0 = 0; i0 < n_mats; i0 += WSTAT_MATS) {
+    l.n = n_mats - i0 < WSTAT_MATS ? n_mats - i0 : WSTAT_MATS;
+    l.first = i0 == 0;
+    l.last = i0 + l.n == n_mats;
+    l.block0[0] = 0;
+    for (int i = 0; i < l.n; ++i) {
+      const strp_weight_ref& m = mats[i0 + i];
+      l.W[i] = m.W; l.rows[i] = m.rows; l.cols[i] = m.cols; l.ld[i] = m.ld;
+      l.bf16[i] = m.dtype == STRP_BF16;
+      l.vec[i] = ((uintptr_t)m.W & 15) == 0 && m.cols % 8 == 0 && m.ld % 8 == 0 && (double)m.rows * m.cols < 3.0e10;
+      // four groups of eight entries per thread and more, all requested at once; few workgroups, which add up one by one
+      const double want = (double)m.rows * m.cols / (32.0 * 256.0);
+      const int most = WSTAT_BLOCKS / (l.n > 2 ? l.n : 2);
+      l.block0[i + 1] = l.block0[i] + (want < 1.0 ? 1 : want > most ? most : (int)want);
+    }
+    hipLaunchKernelGGL(weight_energy_kernel, dim3(l.block0[l.n]), dim3(256), 0, ctx->stream, l, partial, (double*)(ctx->status_dev + WS_SUMS), ticket, energy);
   }
-  hipLaunchKernelGGL(weight_energy_kernel, dim3(1), dim3(64), 0, ctx->stream, (const double*)partial, count, var_coef, l2_coef, scale, energy);
   STRP_HIP(ctx, hipGetLastError());
   return STRP_OK;
 }
 size_t weight_energy_scratch_bytes() { return sizeof(double) * 3 * WSTAT_BLOCKS; }
 
+// ---------------------------------------------------------------------------------------------
+// softmax allocation: one wavefront, fp64, layers strided over lanes
+// ---------------------------------------------------------------------------------------------
 constexpr int ALLOC_MAXL = 1024;
 
 // rule 0: r = rbar L w, clip, conditional rescale (Alg. 1);  rule 1: r = rbar L (1 - w) / sum(1 - w), clip (Alg. 2)
@@ -362,23 +461,24 @@ __global__ __launch_bounds__(64) void alloc_kernel(const double* I, int L, const
   __shared__ double frac[ALLOC_MAXL];
   __shared__ int base[ALLOC_MAXL];
   __shared__ int member[ALLOC_MAXL];
+  __shared__ int gids[ALLOC_MAXL];
   const int lane = threadIdx.x;
+  for (int l = lane; l < L; l += 64) gids[l] = group_id ? group_id[l] : 0;
+  __syncthreads();
   for (int lead = 0; lead < L; ++lead) {
-    const int gid = group_id ? group_id[lead] : 0;
+    // a group is handled by its first member; its members are collected in order, 64 layers at a time
+    const int gid = gids[lead];
+    int Lg = 0;
     bool is_lead = true;
-    if (group_id) {
-      for (int j = 0; j < lead; ++j)
-        if (group_id[j] == gid) { is_lead = false; break; }
-    } else {
-      is_lead = (lead == 0);
+    for (int j0 = 0; j0 < L; j0 += 64) {
+      const int j = j0 + lane;
+      const bool in = j < L && gids[j] == gid;
+      const unsigned long long bal = __ballot(in);
+      if (__ballot(in && j < lead)) is_lead = false;
+      if (in) member[Lg + __popcll(bal & ((1ull << lane) - 1ull))] = j;
+      Lg += __popcll(bal);
     }
     if (!is_lead) continue;                    // uniform across the wavefront
-    int Lg = 0;
-    if (lane == 0) {
-      for (int j = 0; j < L; ++j)
-        if (!group_id || group_id[j] == gid) member[Lg++] = j;
-    }
-    Lg = __shfl(Lg, 0, 64);
     __syncthreads();
     // scale by mean |I|, softmax of -I/T with the maximum subtracted
     double sabs = 0.0;

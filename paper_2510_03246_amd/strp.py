@@ -8,6 +8,7 @@ from __future__ import annotations
 
 import ctypes as C
 import os
+import struct
 
 import torch
 
@@ -70,6 +71,19 @@ class WeightRef(C.Structure):
     _fields_ = [("W", C.c_void_p), ("dtype", C.c_int32), ("rows", C.c_int32), ("cols", C.c_int32), ("ld", C.c_int64)]
 
 
+_packers = {}
+
+
+def _pack_refs(n):
+    """bytes of an array of n WeightRef from its fields in order."""
+    f = _packers.get(n)
+    if f is None:
+        packer = struct.Struct("@" + "Piii4xq" * n)
+        assert packer.size == n * C.sizeof(WeightRef)
+        f = _packers[n] = packer.pack
+    return f
+
+
 class ProfileEntry(C.Structure):
     _fields_ = [("name", C.c_char * 48), ("launches", C.c_int32), ("ms", C.c_double), ("flops", C.c_double),
                 ("bytes", C.c_double)]
@@ -105,7 +119,7 @@ def load_library():
     lib.strp_module_cache_bytes.restype = C.c_size_t
     lib.strp_topk_workspace_bytes.restype = C.c_size_t
     lib.strp_topk_workspace_bytes.argtypes = [C.c_int32]
-    lib.strp_weight_energy.argtypes = [vp, C.POINTER(WeightRef), i32, C.c_double, C.c_double, C.c_double, vp]
+    lib.strp_weight_energy.argtypes = [vp, vp, i32, C.c_double, C.c_double, C.c_double, vp]
     lib.strp_alloc_inverse.argtypes = [vp, vp, i32, vp, vp, C.c_double, C.c_double, C.c_double, vp, vp]
     lib.strp_alloc_softmax.argtypes = [vp, vp, i32, vp, vp, C.c_double, C.c_double, C.c_double, vp, vp]
     lib.strp_gram.argtypes = [vp, vp, C.c_int, i32, i64, i64, vp, i32, vp, i32, vp, C.c_int]
@@ -125,15 +139,17 @@ def load_library():
 
 
 def _ptr(t):
-    return None if t is None else C.c_void_p(t.data_ptr())
+    return None if t is None else t.data_ptr()       # every pointer argument is declared c_void_p
+
+
+_CODES = {torch.bfloat16: BF16, torch.float32: F32}
 
 
 def dtype_code(t: torch.Tensor) -> int:
-    if t.dtype == torch.bfloat16:
-        return BF16
-    if t.dtype == torch.float32:
-        return F32
-    raise TypeError(f"unsupported dtype {t.dtype}")
+    try:
+        return _CODES[t.dtype]
+    except KeyError:
+        raise TypeError(f"unsupported dtype {t.dtype}") from None
 
 
 class Context:
@@ -251,10 +267,13 @@ class Context:
     def strp_weight_energy(self, mats, var_coef, l2_coef, scale, energy):
         """energy (device double, 1 element) += scale (|W|_1 + var_coef Var(W) + l2_coef |W|_2) over the 2-D tensors in mats."""
         self.ensure_workspace(1 << 16)
-        refs = (WeightRef * len(mats))()
-        for r, m in zip(refs, mats):
-            r.W, r.dtype, r.rows, r.cols, r.ld = m.data_ptr(), dtype_code(m), m.shape[0], m.shape[1], m.stride(0)
-        self.check(self.lib.strp_weight_energy(self.h, refs, len(mats), float(var_coef), float(l2_coef), float(scale), _ptr(energy)))
+        # a model has hundreds of small groups, so a call's cost is this marshalling: the WeightRef array is packed in one go
+        args = []
+        for m in mats:
+            rows, cols = m.shape
+            args += (m.data_ptr(), dtype_code(m), rows, cols, m.stride(0))
+        refs = _pack_refs(len(mats))(*args)
+        self.check(self.lib.strp_weight_energy(self.h, refs, len(mats), var_coef, l2_coef, scale, energy.data_ptr()))
 
     def strp_alloc_inverse(self, energies, n_units, rbar, temperature, rmax=0.95, group_id=None):
         L = energies.numel()

@@ -1,4 +1,5 @@
-"""Edges of the select's three forms (keys in registers, scores re-read by one block, several launches) against the oracle."""
+"""Edges of the select's three forms (keys in registers, scores re-read by one block, several launches), of the weight
+statistics' one-launch lists and of the column norms' vector loads, against the oracle."""
 import numpy as np
 import pytest
 import torch
@@ -33,3 +34,41 @@ def test_topk_edges(ctx, n, k, group, kind):
     assert np.array_equal(mask.cpu().numpy(), mo)
     assert np.array_equal(idx.cpu().numpy().astype(np.int64), io)
     assert float(tau.item()) == np.float32(to)
+
+
+@pytest.mark.parametrize("shapes", [[(1, 1)], [(7, 13)], [(64, 768)] * 4, [(33, 40)] * 8, [(5, 8)] * 9, [(3000, 264), (2, 3), (128, 8)] * 6])
+def test_weight_energy_lists(ctx, shapes):
+    """Lists below, at and above what one launch takes; aligned, unaligned and one-entry matrices of both types.  fp64
+    sums of at most 5e6 terms: 1e-12."""
+    g = torch.Generator(device="cuda").manual_seed(len(shapes))
+    mats = []
+    for i, (r, c) in enumerate(shapes):
+        full = torch.randn((r, c + 8 * (i % 2) + i % 3), generator=g, device="cuda") + 0.1
+        m = full.to(torch.bfloat16) if i % 2 else full
+        mats.append(m[:, :c])
+    energy = torch.full((1,), 2.0, dtype=torch.float64, device="cuda")
+    ctx.strp_weight_energy(mats, 0.3, 0.7, 1.5, energy)
+    ctx.strp_weight_energy(mats[:1], 0.3, 0.7, 1.5, energy)
+    assert ctx.poll() == strp.OK
+
+    def ref(ms):
+        w = np.concatenate([m.double().cpu().numpy().ravel() for m in ms])
+        return 1.5 * (np.abs(w).sum() + 0.3 * w.var() + 0.7 * np.sqrt((w * w).sum()))
+    want = 2.0 + ref(mats) + ref(mats[:1])
+    assert abs(float(energy.item()) - want) <= 1e-12 * want
+
+
+@pytest.mark.parametrize("rows,cols,pad,dtype", [(1, 8, 0, torch.bfloat16), (129, 64, 0, torch.bfloat16), (300, 200, 8, torch.float32),
+                                                 (130, 72, 3, torch.bfloat16), (77, 136, 0, torch.float32)])
+def test_scores_with_column_norms(ctx, rows, cols, pad, dtype):
+    """n2 * sum A^2 with the column norms formed by the call; one product of fp64 sums rounded to fp32."""
+    g = torch.Generator(device="cuda").manual_seed(rows)
+    W = torch.randn((rows, cols + pad), generator=g, device="cuda").to(dtype)[:, :cols]
+    A = torch.randn((cols, 40), generator=g, device="cuda")
+    ctx.ensure_workspace(1 << 20)
+    score = torch.empty(cols, device="cuda")
+    e = torch.zeros(1, dtype=torch.float64, device="cuda")
+    ctx.strp_score_alloc(A, 37, strp.WANDA, score, e, 0, 1, What=W)
+    ref = (W.double() ** 2).sum(0) * (A[:, :37].double() ** 2).sum(1)
+    assert torch.allclose(score.double(), ref, rtol=1e-6, atol=0)
+    assert abs(float(e.item()) - float(ref.mean().item())) <= 1e-12 * float(ref.mean().item())
