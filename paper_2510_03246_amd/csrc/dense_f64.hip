@@ -50,6 +50,8 @@ struct DgemmP {
   double* C; long long ldc;
   int lower, tri;
   int vec;                  // 16-byte loads: leading dimensions even and bases aligned
+  unsigned int* maxbits;    // optional: atomic maximum of the bits of |C|
+  WeightsOut w;             // w.W: the result as refitted weights instead of C (one fp64 matrix less to write and read)
 };
 
 template <int R, int DK, bool KC>
@@ -170,17 +172,61 @@ __global__ __launch_bounds__(256, 2) void dgemm_kernel(const DgemmP p) {
     stage(0, k0);
     if (k0 + DK < kend) stage(1, k0 + DK);
   }
-#pragma unroll
-  for (int i = 0; i < WM; ++i)
+  double big = 0.0, sq = 0.0;
+  if (p.w.W) {
+    const bool fc2 = p.w.side == STRP_SIDE_FC2;
 #pragma unroll
     for (int j = 0; j < WN; ++j) {
       const int n = n0 + wn + 16 * j + l16;
+      const long long wcol = n < p.N ? (fc2 ? (long long)p.w.idx[n] : (long long)n) : 0;
 #pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const int m = m0 + wm + 16 * i + 4 * r + lq;
-        if (m < p.M && n < p.N) p.C[(long long)m * p.ldc + n] = acc[i][j][r];
-      }
+      for (int i = 0; i < WM; ++i)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          const int m = m0 + wm + 16 * i + 4 * r + lq;
+          if (m < p.M && n < p.N) {
+            const float v = (float)acc[i][j][r];
+            p.w.W[(fc2 ? (long long)m : (long long)p.w.idx[m]) * p.w.ldw + wcol] = v;
+            if (p.w.Wc) p.w.Wc[(long long)m * p.w.ldc + n] = v;
+            big = fmax(big, fabs((double)v));
+            sq = __builtin_fma((double)v, (double)v, sq);
+          }
+        }
     }
+  } else {
+#pragma unroll
+    for (int i = 0; i < WM; ++i)
+#pragma unroll
+      for (int j = 0; j < WN; ++j) {
+        const int n = n0 + wn + 16 * j + l16;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          const int m = m0 + wm + 16 * i + 4 * r + lq;
+          if (m < p.M && n < p.N) {
+            p.C[(long long)m * p.ldc + n] = acc[i][j][r];
+            big = fmax(big, fabs(acc[i][j][r]));
+          }
+        }
+      }
+  }
+  unsigned int* maxbits = p.w.W ? p.w.maxbits : p.maxbits;
+  if (maxbits || p.w.sumsq) {
+    double* red = As[0];                    // every wavefront is past the last barrier
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) {
+      big = fmax(big, __shfl_down(big, o, 64));
+      sq += __shfl_down(sq, o, 64);
+    }
+    if (lane == 0) {
+      red[2 * wave] = big;
+      red[2 * wave + 1] = sq;
+    }
+    lds_barrier();
+    if (tid == 0) {
+      if (maxbits) atomicMax(maxbits, __builtin_bit_cast(unsigned int, (float)fmax(fmax(red[0], red[2]), fmax(red[4], red[6]))));
+      if (p.w.sumsq) p.w.sumsq[blockIdx.x] = red[1] + red[3] + red[5] + red[7];
+    }
+  }
 }
 
 // Tile of a product by its grid: 128 x 128 tiles read the fewest operand bytes per flop but need enough of them to fill
@@ -189,28 +235,34 @@ constexpr int DGEMM_T128 = 1000, DGEMM_T64 = 2000;
 
 static inline bool aligned_vec(const void* p, long long ld) { return ((uintptr_t)p & 15u) == 0 && (ld & 1) == 0; }
 
+struct DgemmTile { int tm, tn; };
+static DgemmTile dgemm_tile(int M, int N, int lower) {
+  auto tiles = [&](int tm, int tn) { return (long long)((M + tm - 1) / tm) * ((N + tn - 1) / tn) / (lower ? 2 : 1); };
+  if (tiles(128, 128) >= DGEMM_T128) return {128, 128};
+  return tiles(64, 64) >= DGEMM_T64 ? DgemmTile{64, 64} : DgemmTile{64, 32};
+}
+static int dgemm_blocks(int M, int N, DgemmTile t) { return ((M + t.tm - 1) / t.tm) * ((N + t.tn - 1) / t.tn); }
+int weights_out_blocks(int m, int n) { return dgemm_blocks(m, n, dgemm_tile(m, n, 0)); }
+
 template <bool AKC, bool BKC>
 static strp_status dgemm_launch(strp_ctx* ctx, const DgemmP& pin) {
   DgemmP p = pin;
   if (p.M <= 0 || p.N <= 0) return STRP_OK;
   p.vec = aligned_vec(p.A, p.lda) && aligned_vec(p.B, p.ldb);
-  auto tiles = [&](int tm, int tn) { return (long long)((p.M + tm - 1) / tm) * ((p.N + tn - 1) / tn) / (p.lower ? 2 : 1); };
-  const long long t128 = tiles(128, 128), t64 = tiles(64, 64);
-  if (t128 >= DGEMM_T128)
-    hipLaunchKernelGGL((dgemm_kernel<128, 128, 16, AKC, BKC>), dim3(((p.M + 127) / 128) * ((p.N + 127) / 128)), dim3(256), 0, ctx->stream, p);
-  else if (t64 >= DGEMM_T64)
-    hipLaunchKernelGGL((dgemm_kernel<64, 64, 32, AKC, BKC>), dim3(((p.M + 63) / 64) * ((p.N + 63) / 64)), dim3(256), 0, ctx->stream, p);
-  else
-    hipLaunchKernelGGL((dgemm_kernel<64, 32, 32, AKC, BKC>), dim3(((p.M + 63) / 64) * ((p.N + 31) / 32)), dim3(256), 0, ctx->stream, p);
+  const DgemmTile t = dgemm_tile(p.M, p.N, p.lower);
+  const dim3 grid(dgemm_blocks(p.M, p.N, t));
+  if (t.tm == 128) hipLaunchKernelGGL((dgemm_kernel<128, 128, 16, AKC, BKC>), grid, dim3(256), 0, ctx->stream, p);
+  else if (t.tn == 64) hipLaunchKernelGGL((dgemm_kernel<64, 64, 32, AKC, BKC>), grid, dim3(256), 0, ctx->stream, p);
+  else hipLaunchKernelGGL((dgemm_kernel<64, 32, 32, AKC, BKC>), grid, dim3(256), 0, ctx->stream, p);
   STRP_HIP(ctx, hipGetLastError());
   return STRP_OK;
 }
 
 // Lower triangle (128-row tiles on or below the diagonal) of S = Linv^T Linv, Linv lower triangular.
-strp_status gram_of_inverse(strp_ctx* ctx, const double* Linv, int n, long long ldl, double* S, long long lds) {
+strp_status gram_of_inverse(strp_ctx* ctx, const double* Linv, int n, long long ldl, double* S, long long lds, unsigned int* maxbits) {
   DgemmP p;
   memset(&p, 0, sizeof(p));
-  p.M = n; p.N = n; p.K = n; p.A = Linv; p.lda = ldl; p.B = Linv; p.ldb = ldl; p.C = S; p.ldc = lds; p.lower = 1; p.tri = 3;
+  p.M = n; p.N = n; p.K = n; p.A = Linv; p.lda = ldl; p.B = Linv; p.ldb = ldl; p.C = S; p.ldc = lds; p.lower = 1; p.tri = 3; p.maxbits = maxbits;
   return dgemm_launch<false, false>(ctx, p);
 }
 
@@ -425,12 +477,12 @@ struct TileRegs {
   }
 };
 
-// acc += tile product over contraction steps [8 c0, 8 c1) of two LDS images (A always KC)
+// acc += tile product of two LDS images (A always KC)
 template <bool BKC>
-__device__ __forceinline__ void tile_mma(const double* ia, const double* ib, int wm, int wn, int lane, int c0, int c1, doublex4 (&acc)[2][2]) {
+__device__ __forceinline__ void tile_mma(const double* ia, const double* ib, int wm, int wn, int lane, doublex4 (&acc)[2][2]) {
   const int l16 = lane & 15, lq = lane >> 4;
 #pragma unroll 2
-  for (int c = c0; c < c1; ++c) {
+  for (int c = 0; c < 8; ++c) {
     const int k = 8 * c + 2 * lq;
     doublex2 af[2], bf[2];
 #pragma unroll
@@ -464,8 +516,9 @@ __device__ __forceinline__ void mma_lower_t(const double* it, const double* im, 
     doublex4 s[2][2];
 #pragma unroll
     for (int i = 0; i < 2; ++i) s[i][0] = s[i][1] = doublex4{0.0, 0.0, 0.0, 0.0};
-#pragma unroll 2
-    for (int c = 0; c < 2 * (nt + 1); ++c) {
+    for (int c2 = 0; c2 <= nt; ++c2)
+#pragma unroll
+    for (int c = 2 * c2; c < 2 * c2 + 2; ++c) {
       const int k = 8 * c + 2 * lq;
       const doublex2 b = *(const doublex2*)(im + kc_off<NB>(k, 16 * nt + l16));
 #pragma unroll
@@ -488,8 +541,9 @@ __device__ __forceinline__ void mma_lower(const double* im, const double* it, in
     doublex4 s[2][2];
 #pragma unroll
     for (int j = 0; j < 2; ++j) s[j][0] = s[j][1] = doublex4{0.0, 0.0, 0.0, 0.0};
-#pragma unroll 2
-    for (int c = 0; c < 2 * (mt + 1); ++c) {
+    for (int c2 = 0; c2 <= mt; ++c2)
+#pragma unroll
+    for (int c = 2 * c2; c < 2 * c2 + 2; ++c) {
       const int k = 8 * c + 2 * lq;
       const doublex2 a = *(const doublex2*)(im + kc_off<NB>(k, 16 * mt + l16));
 #pragma unroll
@@ -608,12 +662,12 @@ __device__ __forceinline__ void step_panel(const StepP& p, StepShared& sh, int i
     if (lookahead) ra.load(At(t + 1, t - 1), p.ld, NB, NB);
     rb.load(inv_t, p.ldv, NB, NB);
     zero_acc(acc);
-    tile_mma<true>(sh.a, sh.b, wm, wn, lane, 0, 8, acc);
+    tile_mma<true>(sh.a, sh.b, wm, wn, lane, acc);
     lds_barrier();
     if (lookahead) {
       ra.store_kc(sh.b);
       lds_barrier();
-      tile_mma<true>(sh.a, sh.b, wm, wn, lane, 0, 8, acc2);
+      tile_mma<true>(sh.a, sh.b, wm, wn, lane, acc2);
       lds_barrier();
     }
 #pragma unroll
@@ -713,7 +767,7 @@ __device__ __forceinline__ void step_panel(const StepP& p, StepShared& sh, int i
   put_kc_tri(sh.a, wm, half, lane, acc);
   put_kc_tri(sh.b, wm, half, lane, lx);
   lds_barrier();
-  tile_mma<true>(sh.a, sh.b, wm, wn, lane, 0, 8, acc2);
+  tile_mma<true>(sh.a, sh.b, wm, wn, lane, acc2);
 #pragma unroll
   for (int ii = 0; ii < 2; ++ii)
 #pragma unroll
@@ -754,7 +808,7 @@ __global__ __launch_bounds__(256, 2) void chol_step_kernel(const StepP p, const 
     rb.store_rc(sh.b);
     lds_barrier();
     ra.load(Vt(t, t), p.ldv, rows_of(t), rows_of(t));
-    tile_mma<false>(sh.a, sh.b, wm, wn, lane, 0, 8, acc);
+    tile_mma<false>(sh.a, sh.b, wm, wn, lane, acc);
     lds_barrier();
 #pragma unroll
     for (int ii = 0; ii < 2; ++ii)
@@ -800,7 +854,7 @@ __global__ __launch_bounds__(256, 2) void chol_step_kernel(const StepP p, const 
       ra.store_kc(sh.a);
       rb.store_kc(sh.b);
       lds_barrier();
-      tile_mma<true>(sh.a, sh.b, wm, wn, lane, 0, 8, acc);
+      tile_mma<true>(sh.a, sh.b, wm, wn, lane, acc);
 #pragma unroll
       for (int ii = 0; ii < 2; ++ii)
 #pragma unroll
@@ -814,7 +868,7 @@ __global__ __launch_bounds__(256, 2) void chol_step_kernel(const StepP p, const 
       ra.store_kc(sh.a);
       rb.store_rc(sh.b);
       lds_barrier();
-      tile_mma<false>(sh.a, sh.b, wm, wn, lane, 0, 8, acc);
+      tile_mma<false>(sh.a, sh.b, wm, wn, lane, acc);
 #pragma unroll
       for (int ii = 0; ii < 2; ++ii)
 #pragma unroll
@@ -897,8 +951,8 @@ strp_status chol_inverse(strp_ctx* ctx, double* A, int n, long long ld, double* 
   return STRP_OK;
 }
 
-// X <- X (L L^T)^-1 = (X Linv^T) Linv for X [m x n] (leading dimension ldx); tmp: m x ldx scratch.
-strp_status apply_inverse_right(strp_ctx* ctx, const double* Linv, int n, long long ldl, double* X, int m, long long ldx, double* tmp) {
+strp_status apply_inverse_right(strp_ctx* ctx, const double* Linv, int n, long long ldl, const double* X, int m, long long ldx, double* tmp,
+                                const WeightsOut& out) {
   ProfScope ps(ctx, "chol_solve_f64", 2.0 * (double)m * n * n, 8.0 * ((double)n * n + 4.0 * (double)m * n));
   DgemmP p;
   memset(&p, 0, sizeof(p));
@@ -906,8 +960,8 @@ strp_status apply_inverse_right(strp_ctx* ctx, const double* Linv, int n, long l
   // tmp[m, j] = sum_{k <= j} X[m, k] Linv[j, k]
   p.A = X; p.lda = ldx; p.B = Linv; p.ldb = ldl; p.C = tmp; p.ldc = ldx; p.tri = 1;
   STRP_TRY((dgemm_launch<true, true>(ctx, p)));
-  // X[m, j] = sum_{k >= j} tmp[m, k] Linv[k, j]
-  p.A = tmp; p.C = X; p.tri = 2;
+  // result[m, j] = sum_{k >= j} tmp[m, k] Linv[k, j]
+  p.A = tmp; p.C = nullptr; p.tri = 2; p.w = out;
   return dgemm_launch<true, false>(ctx, p);
 }
 
@@ -946,61 +1000,77 @@ strp_status copy_f64(strp_ctx* ctx, const double* src, long long lds, double* ds
   return STRP_OK;
 }
 
-__global__ __launch_bounds__(256) void cast_f64_f32_kernel(const double* src, long long lds, float* dst, long long ldd,
-                                                           int rows, int cols) {
-  const long long e = (long long)blockIdx.x * 256 + threadIdx.x;
-  if (e >= (long long)rows * ldd) return;
-  const int i = (int)(e / ldd), j = (int)(e % ldd);
-  dst[e] = j < cols ? (float)src[(long long)i * lds + j] : 0.0f;
+// The compact weights of an earlier refit, with what apply_inverse_right would have left beside them.
+__global__ __launch_bounds__(256) void gather_weights_kernel(const WeightsOut w, int m, int n) {
+  double big = 0.0, sq = 0.0;
+  for (long long e = (long long)blockIdx.x * 256 + threadIdx.x; e < (long long)m * n; e += (long long)gridDim.x * 256) {
+    const int i = (int)(e / n), j = (int)(e % n);
+    const float v = w.side == STRP_SIDE_FC2 ? w.W[(long long)i * w.ldw + w.idx[j]] : w.W[(long long)w.idx[i] * w.ldw + j];
+    w.Wc[(long long)i * w.ldc + j] = v;
+    big = fmax(big, fabs((double)v));
+    sq = __builtin_fma((double)v, (double)v, sq);
+  }
+  __shared__ double red[4][2];
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) {
+    big = fmax(big, __shfl_down(big, o, 64));
+    sq += __shfl_down(sq, o, 64);
+  }
+  if ((threadIdx.x & 63) == 0) {
+    red[threadIdx.x >> 6][0] = big;
+    red[threadIdx.x >> 6][1] = sq;
+  }
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    if (w.maxbits) atomicMax(w.maxbits, __builtin_bit_cast(unsigned int, (float)fmax(fmax(red[0][0], red[1][0]), fmax(red[2][0], red[3][0]))));
+    if (w.sumsq) w.sumsq[blockIdx.x] = red[0][1] + red[1][1] + red[2][1] + red[3][1];
+  }
 }
-
-strp_status cast_f64_f32(strp_ctx* ctx, const double* src, long long lds, float* dst, long long ldd, int rows, int cols) {
-  const long long tot = (long long)rows * ldd;
-  hipLaunchKernelGGL(cast_f64_f32_kernel, dim3((unsigned)((tot + 255) / 256)), dim3(256), 0, ctx->stream, src, lds, dst,
-                     ldd, rows, cols);
+int gather_blocks(int m, int n) {
+  const long long b = ((long long)m * n + 1023) / 1024;
+  return b > 1024 ? 1024 : (int)b;
+}
+strp_status gather_weights(strp_ctx* ctx, const WeightsOut& io, int m, int n) {
+  hipLaunchKernelGGL(gather_weights_kernel, dim3(gather_blocks(m, n)), dim3(256), 0, ctx->stream, io, m, n);
   STRP_HIP(ctx, hipGetLastError());
   return STRP_OK;
 }
 
-__global__ __launch_bounds__(256) void fill_zero_kernel(uint32_t* p, long long words) {
-  const long long stride = (long long)gridDim.x * 256;
-  for (long long e = (long long)blockIdx.x * 256 + threadIdx.x; e < words; e += stride) p[e] = 0u;
-}
-
-strp_status fill_zero(strp_ctx* ctx, void* ptr, size_t bytes) {
-  if (bytes == 0) return STRP_OK;
-  if (bytes % 4 != 0) return fail(ctx, STRP_EINVAL, "fill_zero: size not a multiple of 4");
-  const long long words = (long long)(bytes / 4);
-  long long blocks = (words + 255) / 256;
-  if (blocks > 8192) blocks = 8192;
-  hipLaunchKernelGGL(fill_zero_kernel, dim3((unsigned)blocks), dim3(256), 0, ctx->stream, (uint32_t*)ptr, words);
-  STRP_HIP(ctx, hipGetLastError());
-  return STRP_OK;
-}
-
-// side FC2: sol [out x s] -> W[o][idx[c]];  side FC1: sol [s x in] -> W[idx[r]][c]
-__global__ __launch_bounds__(256) void scatter_weights_kernel(const double* sol, long long lds, int side, const int32_t* idx,
-                                                              int s, float* W, int out, int in) {
-  const long long e = (long long)blockIdx.x * 256 + threadIdx.x;
-  if (side == STRP_SIDE_FC2) {
-    if (e >= (long long)out * s) return;
-    const int o = (int)(e / s), c = (int)(e % s);
-    W[(long long)o * in + idx[c]] = (float)sol[(long long)o * lds + c];
-  } else {
-    if (e >= (long long)s * in) return;
-    const int r = (int)(e / in), c = (int)(e % in);
-    W[(long long)idx[r] * in + c] = (float)sol[(long long)r * lds + c];
+// several ranges in one launch: a launch costs more than clearing most of what is cleared here
+struct FillRanges {
+  uint32_t* p[5];
+  long long words[5];
+};
+__global__ __launch_bounds__(256) void fill_zero_kernel(const FillRanges f) {
+  const long long stride = (long long)gridDim.x * 256, e0 = (long long)blockIdx.x * 256 + threadIdx.x;
+  for (int r = 0; r < 5; ++r) {
+    uint32_t* p = f.p[r];
+    const long long quads = ((uintptr_t)p & 15) == 0 ? f.words[r] >> 2 : 0;
+    for (long long e = e0; e < quads; e += stride) ((uint4*)p)[e] = make_uint4(0u, 0u, 0u, 0u);
+    for (long long e = 4 * quads + e0; e < f.words[r]; e += stride) p[e] = 0u;
   }
 }
 
-strp_status scatter_weights(strp_ctx* ctx, const double* sol, long long lds, int side, const int32_t* idx, int s, float* W,
-                            int out, int in) {
-  STRP_TRY(fill_zero(ctx, W, sizeof(float) * (size_t)out * (size_t)in));
-  const long long tot = side == STRP_SIDE_FC2 ? (long long)out * s : (long long)s * in;
-  hipLaunchKernelGGL(scatter_weights_kernel, dim3((unsigned)((tot + 255) / 256)), dim3(256), 0, ctx->stream, sol, lds,
-                     side, idx, s, W, out, in);
+strp_status fill_zero(strp_ctx* ctx, const FillRange* ranges, int n) {
+  FillRanges f;
+  memset(&f, 0, sizeof(f));
+  long long most = 0;
+  for (int i = 0; i < n; ++i) {
+    if (ranges[i].bytes % 4 != 0) return fail(ctx, STRP_EINVAL, "fill_zero: size not a multiple of 4");
+    f.p[i] = (uint32_t*)ranges[i].ptr;
+    f.words[i] = (long long)(ranges[i].bytes / 4);
+    most = f.words[i] > most ? f.words[i] : most;
+  }
+  if (most == 0) return STRP_OK;
+  long long blocks = (most + 1023) / 1024;
+  if (blocks > 4096) blocks = 4096;
+  hipLaunchKernelGGL(fill_zero_kernel, dim3((unsigned)blocks), dim3(256), 0, ctx->stream, f);
   STRP_HIP(ctx, hipGetLastError());
   return STRP_OK;
+}
+strp_status fill_zero(strp_ctx* ctx, void* ptr, size_t bytes) {
+  const FillRange r{ptr, bytes};
+  return fill_zero(ctx, &r, 1);
 }
 
 }  // namespace strp

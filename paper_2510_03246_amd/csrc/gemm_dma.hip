@@ -214,8 +214,8 @@ __global__ __launch_bounds__(512, 1) void gemm_dma_kernel(const GemmP p) {
   __syncthreads();
 
   float unscale = 1.0f;
-  if (p.P.scale) unscale /= *p.P.scale;
-  if (p.Q.scale) unscale /= *p.Q.scale;
+  if (p.P.maxbits) unscale /= scale_of_max(*p.P.maxbits);
+  if (p.Q.maxbits) unscale /= scale_of_max(*p.Q.maxbits);
   double red0 = 0.0, red1 = 0.0;
   const int mbase = m0 + wm * 128 + 8 * (lane >> 5), nbase = n0 + wn * 64 + (lane & 31);
   switch (p.epi) {
@@ -226,7 +226,9 @@ __global__ __launch_bounds__(512, 1) void gemm_dma_kernel(const GemmP p) {
     case EPI_AUPD: epilogue16<EPI_AUPD>(p, acc, unscale, mbase, nbase, split, srow, m0, red0, red1); break;
     default: epilogue16<EPI_ZUPD>(p, acc, unscale, mbase, nbase, split, srow, m0, red0, red1); break;
   }
-  if (p.red) {
+  if (p.maxbits) {
+    store_maxbits<NW>(p, red0, sred);
+  } else if (p.red) {
     red0 = wave_sum(red0);
     red1 = wave_sum(red1);
     if (lane == 0) {

@@ -152,6 +152,7 @@ __device__ __forceinline__ void epilogue_tile(const GemmP& p, const floatx16 a16
       } else if (EPI == EPI_STORE) {
         if (ok) p.out[offset(e)] = v;
         outv[r] = ok ? v : 0.0f;
+        s0 = __builtin_fmaxf(s0, __builtin_fabsf(outv[r]));
       } else if (EPI == EPI_INITZ) {
         const float a = __builtin_fmaxf(v, 0.0f);
         if (ok) {
@@ -206,8 +207,24 @@ __device__ __forceinline__ void epilogue_tile(const GemmP& p, const floatx16 a16
     }
     __builtin_amdgcn_sched_barrier(0);   // bounds the live temporaries to one group of four rows
   }
-  red0 += (double)s0;
+  if (EPI == EPI_STORE) red0 = fmax(red0, (double)s0);     // STORE: the largest magnitude
+  else red0 += (double)s0;
   red1 += (double)s1;
+}
+
+// the workgroup's largest magnitude (STORE with p.maxbits): one atomic per workgroup
+template <int NW>
+__device__ __forceinline__ void store_maxbits(const GemmP& p, double m, double (&sred)[NW][2]) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) m = fmax(m, __shfl_down(m, o, 64));
+  if (lane == 0) sred[wave][0] = m;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+#pragma unroll
+    for (int w = 1; w < NW; ++w) m = fmax(m, sred[w][0]);
+    atomicMax(p.maxbits, __builtin_bit_cast(unsigned int, (float)m));
+  }
 }
 
 // Sum rs[e] over the 32 lanes of each half wavefront (= the 32 columns of a tile; the caller has already added the

@@ -189,8 +189,8 @@ __global__ __launch_bounds__(256, WT == 4 ? 1 : 2) void gemm_kernel(const GemmP 
 
   // ---- epilogue (one specialised, fully unrolled body per epilogue kind) -------------------------
   float unscale = 1.0f;
-  if (p.P.scale) unscale /= *p.P.scale;
-  if (p.Q.scale) unscale /= *p.Q.scale;
+  if (p.P.maxbits) unscale /= scale_of_max(*p.P.maxbits);
+  if (p.Q.maxbits) unscale /= scale_of_max(*p.Q.maxbits);
   double red0 = 0.0, red1 = 0.0;
   const int mbase = m0 + wm * WROWS + 4 * (lane >> 5), nbase = n0 + wn * WROWS + (lane & 31);
   switch (p.epi) {
@@ -201,7 +201,9 @@ __global__ __launch_bounds__(256, WT == 4 ? 1 : 2) void gemm_kernel(const GemmP 
     case EPI_AUPD: epilogue<EPI_AUPD, WT, WT>(p, acc, unscale, mbase, nbase, split, srow, m0, red0, red1); break;
     default: epilogue<EPI_ZUPD, WT, WT>(p, acc, unscale, mbase, nbase, split, srow, m0, red0, red1); break;
   }
-  if (p.red) {
+  if (p.maxbits) {
+    store_maxbits<4>(p, red0, sred);
+  } else if (p.red) {
     red0 = wave_sum(red0);
     red1 = wave_sum(red1);
     if (lane == 0) {
@@ -322,22 +324,25 @@ strp_status launch_gemm(strp_ctx* ctx, GemmP& p) {
 // of one row of one partial.  Symmetric products: only tiles on or below the diagonal are reduced; the strict lower
 // part is also written transposed through LDS, so the upper half is a bit-exact mirror and the partials are read once,
 // row-contiguously.
-__global__ __launch_bounds__(256) void splitk_reduce_kernel(const float* part, int splits, int M, int N, int triangle,
-                                                           float* outf, long long ldof, double* outd, long long ldod,
-                                                           double* diag, int accumulate) {
+__global__ __launch_bounds__(256) void splitk_reduce_kernel(const ReduceP r) {
   constexpr int TS = 64;
   __shared__ double tile[TS][TS + 1];
   const int tx = threadIdx.x & 63, ty = threadIdx.x >> 6;
   const int n0 = blockIdx.x * TS, m0 = blockIdx.y * TS;
-  if (triangle && n0 > m0) return;
+  const int M = r.M, N = r.N;
+  if (r.triangle && n0 > m0) {
+    if (r.dot && threadIdx.x == 0) r.red[blockIdx.y * gridDim.x + blockIdx.x] = 0.0;
+    return;
+  }
   const long long MN = (long long)M * N;
+  const double ridge = r.ridge_dev ? *r.ridge_dev : r.ridge;
   auto put = [&](int m, int n, double s) {
-    if (outf) {
-      float* o = outf + (long long)m * ldof + n;
-      *o = accumulate ? (float)((double)*o + s) : (float)s;
+    if (r.outf) {
+      float* o = r.outf + (long long)m * r.ldof + n;
+      *o = r.accumulate ? (float)((double)*o + s) : (float)s;
     }
-    if (outd) outd[(long long)m * ldod + n] = s;
-    if (diag && m == n) diag[m] = s;
+    if (r.outd) r.outd[(long long)m * r.ldod + n] = m == n ? s + ridge : s;
+    if (r.diag && m == n) r.diag[m] = s;
   };
   const int n = n0 + tx;
   double acc[16];
@@ -353,22 +358,37 @@ __global__ __launch_bounds__(256) void splitk_reduce_kernel(const float* part, i
       const int m = m0 + ty + 4 * i;
       ro[i] = (long long)(m < M ? m : M - 1) * N + nc;
     }
-    for (int sp = 0; sp < splits; ++sp) {
-      const float* src = part + (long long)sp * MN;
+    for (int sp = 0; sp < r.splits; ++sp) {
+      const float* src = r.part + (long long)sp * MN;
       float v[16];
 #pragma unroll
       for (int i = 0; i < 16; ++i) v[i] = src[ro[i]];
 #pragma unroll
       for (int i = 0; i < 16; ++i) acc[i] += (double)v[i];
     }
+    if (r.dot) {          // <dot, C>: the strict lower part of this tile stands for its mirror image as well
+      double s = 0.0;
+#pragma unroll
+      for (int i = 0; i < 16; ++i) {
+        const int m = m0 + ty + 4 * i;
+        const double w = (m < M && n < N && n <= m) ? (n < m ? 2.0 : 1.0) : 0.0;
+        s = __builtin_fma(w * (double)r.dot[ro[i]], acc[i], s);
+      }
+#pragma unroll
+      for (int o = 32; o > 0; o >>= 1) s += __shfl_down(s, o, 64);
+      if (tx == 0) tile[0][ty] = s;
+      __syncthreads();
+      if (threadIdx.x == 0) r.red[blockIdx.y * gridDim.x + blockIdx.x] = tile[0][0] + tile[0][1] + tile[0][2] + tile[0][3];
+      return;
+    }
   }
 #pragma unroll
   for (int i = 0; i < 16; ++i) {
     const int m = m0 + ty + 4 * i;
-    if (m < M && n < N && (!triangle || n <= m)) put(m, n, acc[i]);
+    if (m < M && n < N && (!r.triangle || n <= m)) put(m, n, acc[i]);
     tile[ty + 4 * i][tx] = acc[i];
   }
-  if (!triangle) return;
+  if (!r.triangle) return;
   __syncthreads();
 #pragma unroll
   for (int i = 0; i < 16; ++i) {
@@ -377,45 +397,12 @@ __global__ __launch_bounds__(256) void splitk_reduce_kernel(const float* part, i
   }
 }
 
-strp_status launch_splitk_reduce(strp_ctx* ctx, const float* part, int splits, int M, int N, int triangle,
-                                 float* outf, long long ldof, double* outd, long long ldod, double* diag,
-                                 int accumulate) {
-  const long long tot = (long long)M * N;
-  if (triangle && M != N) return fail(ctx, STRP_EINVAL, "split-K reduce: a symmetric product must be square");
-  ProfScope ps(ctx, "splitk_reduce", 0.0, 4.0 * (double)tot * (double)splits * (triangle ? 0.5 : 1.0) + (outf ? 4.0 : 0.0) * tot + (outd ? 8.0 : 0.0) * tot);
-  hipLaunchKernelGGL(splitk_reduce_kernel, dim3((N + 63) / 64, (M + 63) / 64), dim3(256), 0, ctx->stream, part,
-                     splits, M, N, triangle, outf, ldof, outd, ldod, diag, accumulate);
-  STRP_HIP(ctx, hipGetLastError());
-  return STRP_OK;
-}
-
-__global__ __launch_bounds__(256) void block_sum_kernel(const double* red, int nblocks, double* dst0, double* dst1,
-                                                       double scale0, double scale1) {
-  __shared__ double s[256][2];
-  double a = 0.0, b = 0.0;
-  for (int i = threadIdx.x; i < nblocks; i += 256) {
-    a += red[2 * (long long)i];
-    b += red[2 * (long long)i + 1];
-  }
-  s[threadIdx.x][0] = a;
-  s[threadIdx.x][1] = b;
-  __syncthreads();
-  for (int o = 128; o > 0; o >>= 1) {
-    if (threadIdx.x < o) {
-      s[threadIdx.x][0] += s[threadIdx.x + o][0];
-      s[threadIdx.x][1] += s[threadIdx.x + o][1];
-    }
-    __syncthreads();
-  }
-  if (threadIdx.x == 0) {
-    if (dst0) *dst0 = s[0][0] * scale0;
-    if (dst1) *dst1 = s[0][1] * scale1;
-  }
-}
-
-strp_status launch_block_sum(strp_ctx* ctx, const double* red, int nblocks, double* dst0, double* dst1,
-                             double scale0, double scale1) {
-  hipLaunchKernelGGL(block_sum_kernel, dim3(1), dim3(256), 0, ctx->stream, red, nblocks, dst0, dst1, scale0, scale1);
+strp_status launch_splitk_reduce(strp_ctx* ctx, const ReduceP& r) {
+  const double tot = (double)r.M * r.N;
+  if (r.triangle && r.M != r.N) return fail(ctx, STRP_EINVAL, "split-K reduce: a symmetric product must be square");
+  if (r.dot && !r.triangle) return fail(ctx, STRP_EINVAL, "split-K reduce: the inner product is for symmetric products");
+  ProfScope ps(ctx, "splitk_reduce", 0.0, 4.0 * tot * (double)r.splits * (r.triangle ? 0.5 : 1.0) + (r.outf ? 4.0 : 0.0) * tot + (r.outd ? 8.0 : 0.0) * tot);
+  hipLaunchKernelGGL(splitk_reduce_kernel, dim3((r.N + 63) / 64, (r.M + 63) / 64), dim3(256), 0, ctx->stream, r);
   STRP_HIP(ctx, hipGetLastError());
   return STRP_OK;
 }

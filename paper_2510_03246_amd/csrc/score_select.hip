@@ -6,6 +6,8 @@
 //   topk          : radix select on order-preserving keys, ballot/prefix compaction, ties -> lower index
 #include <stddef.h>
 
+#include <type_traits>
+
 #include "strp_internal.h"
 
 namespace strp {
@@ -27,24 +29,6 @@ __device__ __forceinline__ double wave_allmax_d(double v) {
 }
 __device__ __forceinline__ float bf16lo(unsigned int w) { return __builtin_bit_cast(float, w << 16); }
 __device__ __forceinline__ float bf16hi(unsigned int w) { return __builtin_bit_cast(float, w & 0xffff0000u); }
-
-// ---------------------------------------------------------------------------------------------
-// "The last workgroup does the rest": true in every thread of the last workgroup of the grid to get here.  What the
-// workgroups hand to it goes through agent-scope atomics (agent_put / agent_get / atomicAdd), which act at the level all
-// XCDs share, so it is enough that they have completed before the counter moves: an agent-scope fence would
-// write back and invalidate the XCD's L2 from every workgroup, which took 45 of a launch's 50 us.
-// ---------------------------------------------------------------------------------------------
-template <typename T>
-__device__ __forceinline__ void agent_put(T* p, T v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
-template <typename T>
-__device__ __forceinline__ T agent_get(const T* p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
-__device__ __forceinline__ bool last_block(unsigned int* done, unsigned int* flag) {
-  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-  __syncthreads();
-  if (threadIdx.x == 0) *flag = atomicAdd(done, 1u) + 1u == gridDim.x;
-  __syncthreads();
-  return *flag != 0;
-}
 
 // ---------------------------------------------------------------------------------------------
 // per-channel token sums: sums[0][r] = sum A^2, [1][r] = sum A*relu(Z0), [2][r] = sum Z0*Z, [3][r] = sum Z0^2
@@ -155,48 +139,42 @@ strp_status launch_row_sums(strp_ctx* ctx, const void* A, int a_dtype, const flo
 }
 
 // Scoring sums of the kept rows from the strips the a- and z-update epilogues wrote: part[q][strip][m] (fp32, one value
-// per output row m and 64-column strip) -> rowsums[qdst[q] * f + idx[m]] (fp64).  Two fixed-order levels: 16 chunks of
-// strips per row, then the 16 chunk sums.
-constexpr int RS_CHUNKS = 16;
-__global__ __launch_bounds__(256) void rowsum_chunk_kernel(const float* part, int slots, int M, double* chunk_sums) {
-  const int m = blockIdx.x * 256 + threadIdx.x;
-  const int c = blockIdx.y, q = blockIdx.z;
-  if (m >= M) return;
-  const int per = (slots + RS_CHUNKS - 1) / RS_CHUNKS;
-  const int s0 = c * per, s1 = (s0 + per < slots) ? s0 + per : slots;
-  const float* src = part + (long long)q * slots * M + m;
-  double a0 = 0.0, a1 = 0.0, a2 = 0.0, a3 = 0.0;   // four independent chains keep four loads in flight
-  int sidx = s0;
-  for (; sidx + 3 < s1; sidx += 4) {
-    a0 += (double)src[(long long)sidx * M];
-    a1 += (double)src[(long long)(sidx + 1) * M];
-    a2 += (double)src[(long long)(sidx + 2) * M];
-    a3 += (double)src[(long long)(sidx + 3) * M];
-  }
-  for (; sidx < s1; ++sidx) a0 += (double)src[(long long)sidx * M];
-  chunk_sums[((long long)q * RS_CHUNKS + c) * M + m] = (a0 + a1) + (a2 + a3);
-}
-__global__ __launch_bounds__(256) void rowsum_final_kernel(const double* chunk_sums, int M, const int32_t* idx, double* rowsums, int f,
-                                                           int qdst0, int qdst1, int32_t* status) {
-  const int m = blockIdx.x * 256 + threadIdx.x;
-  const int q = blockIdx.y;
-  if (m >= M) return;
-  double t = 0.0;
+// per output row m and 64-column strip) -> rowsums[qdst[q] * f + idx[m]] (fp64).  One workgroup sums 64 rows: a wavefront
+// takes every 16th strip (256 contiguous bytes of each), the sixteen sums are added in order.
+__global__ __launch_bounds__(1024) void rowsum_kernel(const float* part, int slots, int M, const int32_t* idx, double* rowsums, int f, int qdst0,
+                                                      int qdst1, int32_t* status) {
+  __shared__ double sh[16][64];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int m = blockIdx.x * 64 + lane, q = blockIdx.y;
+  const float* src = part + (long long)q * slots * M + (m < M ? m : M - 1);
+  double a[8];
 #pragma unroll
-  for (int c = 0; c < RS_CHUNKS; ++c) t += chunk_sums[((long long)q * RS_CHUNKS + c) * M + m];
-  rowsums[(long long)(q == 0 ? qdst0 : qdst1) * f + idx[m]] = t;
-  if (!(fabs(t) <= 1.79e308)) atomicCAS(status, 0, (int)STRP_ENONFINITE);
+  for (int u = 0; u < 8; ++u) a[u] = 0.0;
+  int sidx = wave;
+  for (; sidx + 7 * 16 < slots; sidx += 8 * 16) {       // eight loads in flight
+    float v[8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) v[u] = src[(long long)(sidx + 16 * u) * M];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) a[u] += (double)v[u];
+  }
+  for (; sidx < slots; sidx += 16) a[0] += (double)src[(long long)sidx * M];
+  sh[wave][lane] = ((a[0] + a[1]) + (a[2] + a[3])) + ((a[4] + a[5]) + (a[6] + a[7]));
+  __syncthreads();
+  if (wave == 0 && m < M) {
+    double t = 0.0;
+#pragma unroll
+    for (int w = 0; w < 16; ++w) t += sh[w][lane];
+    rowsums[(long long)(q == 0 ? qdst0 : qdst1) * f + idx[m]] = t;
+    if (!(fabs(t) <= 1.79e308)) atomicCAS(status, 0, (int)STRP_ENONFINITE);
+  }
 }
-
-size_t rowsum_scratch_bytes(int nq, int M) { return sizeof(double) * (size_t)nq * RS_CHUNKS * (size_t)M; }
 
 strp_status launch_rowsum_reduce(strp_ctx* ctx, const float* part, int nq, int slots, int M, const int32_t* idx, double* rowsums, int f,
-                                 int qdst0, int qdst1, double* chunk_sums) {
+                                 int qdst0, int qdst1) {
   if (nq <= 0 || M <= 0 || slots <= 0) return STRP_OK;
   ProfScope ps(ctx, "rowsum_reduce", 0.0, 4.0 * (double)nq * (double)slots * (double)M);
-  hipLaunchKernelGGL(rowsum_chunk_kernel, dim3((M + 255) / 256, RS_CHUNKS, nq), dim3(256), 0, ctx->stream, part, slots, M, chunk_sums);
-  hipLaunchKernelGGL(rowsum_final_kernel, dim3((M + 255) / 256, nq), dim3(256), 0, ctx->stream, (const double*)chunk_sums, M, idx, rowsums, f,
-                     qdst0, qdst1, ctx->status_dev);
+  hipLaunchKernelGGL(rowsum_kernel, dim3((M + 63) / 64, nq), dim3(1024), 0, ctx->stream, part, slots, M, idx, rowsums, f, qdst0, qdst1, ctx->status_dev);
   STRP_HIP(ctx, hipGetLastError());
   return STRP_OK;
 }
@@ -282,6 +260,13 @@ strp_status launch_colnorm2(strp_ctx* ctx, const void* W, int w_dtype, int rows,
 // ---------------------------------------------------------------------------------------------
 // unit scores + layer energy (single block, fixed summation order)
 // ---------------------------------------------------------------------------------------------
+__device__ __forceinline__ double score_of(int mode, double n2, double g, double e, double u, double v) {
+  const double w = n2 * g;
+  if (mode == STRP_SCORE_WANDA) return w;
+  const double p = u + n2 * e, q = v + w;
+  return mode == STRP_SCORE_LEMMA ? p / q : 2.0 * p - q;
+}
+
 __global__ __launch_bounds__(1024) void unit_scores_kernel(const double* sums, const double* n2, int n_channels, int group,
                                                           int mode, float* score, double* energy_out) {
   const int n = n_channels / group;
@@ -649,9 +634,16 @@ __device__ __forceinline__ void pick_bin(const unsigned int (&h)[B], unsigned in
 // The k-th key and its index decide every element: kept = larger, or equal with no higher index.  Ascending
 // indices come from one scan of the counts per (round j, wavefront).  n = 16384: 26 -> 14 us with the launch; it was
 // 32 counting rounds.
-template <int KPT, bool REGS>
-__global__ __launch_bounds__(1024) void topk_small_kernel(const float* score, int n, int k, int group, uint8_t* mask, int32_t* idx,
-                                                          float* tau) {
+// With in.sums the scores (group = 1) are formed here first, with their mean; rest takes the indices that are not kept.
+struct ScoreSource {
+  const double* sums;       // [4][n], or null: the scores are given
+  const double* n2;
+  int mode;
+  double* energy_out;
+};
+template <int KPT, bool REGS, bool SCORED>
+__global__ __launch_bounds__(1024) void topk_small_kernel(float* score, int n, int k, int group, uint8_t* mask, int32_t* idx, float* tau,
+                                                          const ScoreSource in, int32_t* rest) {
   __shared__ unsigned int hist[2048];
   __shared__ unsigned int ckey[1024];
   __shared__ int cidx[1024];
@@ -659,9 +651,46 @@ __global__ __launch_bounds__(1024) void topk_small_kernel(const float* score, in
   __shared__ unsigned int sel[3], ncand, cut[2];
   __shared__ int table[16 * KPT];
   __shared__ int wtot[16];
+  __shared__ double esums[16];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   unsigned int key[REGS ? KPT : 1];
-  if constexpr (REGS) {
+  if constexpr (SCORED) {
+    const long long nn = n;
+    const double* g = in.sums;
+    double esum = 0.0;
+    const auto one = [&](int i) {
+      const bool full = in.mode != STRP_SCORE_WANDA;
+      const double sc = score_of(in.mode, in.n2[i], g[i], full ? g[nn + i] : 0.0, full ? g[2 * nn + i] : 0.0, full ? g[3 * nn + i] : 0.0);
+      return sc;
+    };
+    if constexpr (REGS) {
+      double sc[KPT];
+#pragma unroll
+      for (int j = 0; j < KPT; ++j) sc[j] = one(tid + 1024 * j < n ? tid + 1024 * j : n - 1);
+#pragma unroll
+      for (int j = 0; j < KPT; ++j) {
+        key[j] = score_key((float)sc[j]);
+        if (tid + 1024 * j < n) {
+          score[tid + 1024 * j] = (float)sc[j];
+          esum += sc[j];
+        }
+      }
+    } else {
+      for (int i = tid; i < n; i += 1024) {
+        const double sc = one(i);
+        score[i] = (float)sc;
+        esum += sc;
+      }
+    }
+    esum = wave_sum_d(esum);
+    if (lane == 0) esums[wave] = esum;
+    __syncthreads();          // and every score is in memory
+    if (tid == 0 && in.energy_out) {
+      double tot = 0.0;
+      for (int w = 0; w < 16; ++w) tot += esums[w];
+      *in.energy_out = tot / (double)n;
+    }
+  } else if constexpr (REGS) {
 #pragma unroll
     for (int j = 0; j < KPT; ++j) {
       const int i = tid + 1024 * j;
@@ -674,10 +703,15 @@ __global__ __launch_bounds__(1024) void topk_small_kernel(const float* score, in
 #pragma unroll
       for (int j = 0; j < KPT; ++j) f(j, tid + 1024 * j, key[j], tid + 1024 * j < n);
     } else {
-#pragma unroll 4
-      for (int j = 0; j < (n + 1023) / 1024; ++j) {
-        const int i = tid + 1024 * j;
-        f(j, i, score_key(score[i < n ? i : n - 1]), i < n);
+      for (int j0 = 0; 1024 * j0 < n; j0 += 8) {       // eight loads in flight; past the end they see the last score
+        unsigned int x[8];
+#pragma unroll
+        for (int q = 0; q < 8; ++q) {
+          const int i = tid + 1024 * (j0 + q);
+          x[q] = score_key(score[i < n ? i : n - 1]);
+        }
+#pragma unroll
+        for (int q = 0; q < 8; ++q) f(j0 + q, tid + 1024 * (j0 + q), x[q], tid + 1024 * (j0 + q) < n);
       }
     }
   };
@@ -783,23 +817,26 @@ __global__ __launch_bounds__(1024) void topk_small_kernel(const float* score, in
   const unsigned int ckth = cut[0];
   const int ikth = (int)cut[1];
   if (tid == 0 && tau) *tau = key_score(ckth);
-  each([&](int j, int i, unsigned int x, bool in) {
-    const bool keep = in && (x > ckth || (x == ckth && i <= ikth));
+  each([&](int j, int i, unsigned int x, bool valid) {
+    const bool keep = valid && (x > ckth || (x == ckth && i <= ikth));
     const unsigned long long bk = __ballot(keep);
     if (lane == 0) table[j * 16 + wave] = __popcll(bk);
-    if (in) mask[i] = (uint8_t)keep;
+    if (valid) mask[i] = (uint8_t)keep;
   });
   __syncthreads();
   int tot;
   const int pref = block_scan(tid < 16 * KPT ? table[tid] : 0, wtot, &tot);
   if (tid < 16 * KPT) table[tid] = pref;
   __syncthreads();
-  each([&](int j, int i, unsigned int x, bool in) {
-    const bool keep = in && (x > ckth || (x == ckth && i <= ikth));
+  each([&](int j, int i, unsigned int x, bool valid) {
+    const bool keep = valid && (x > ckth || (x == ckth && i <= ikth));
     const unsigned long long bk = __ballot(keep);
+    const int before = table[j * 16 + wave] + __popcll(bk & ((1ull << lane) - 1ull));
     if (keep) {
-      const long long pos = (long long)(table[j * 16 + wave] + __popcll(bk & ((1ull << lane) - 1ull))) * group;
+      const long long pos = (long long)before * group;
       for (int c = 0; c < group; ++c) idx[pos + c] = i * group + c;
+    } else if (SCORED && rest && valid) {
+      rest[i - before] = i;
     }
   });
 }
@@ -1026,16 +1063,38 @@ __global__ __launch_bounds__(big::THREADS) void topk_write_kernel(const float* s
   }
 }
 
+static void launch_topk_small(strp_ctx* ctx, float* score, int n, int k, int group, uint8_t* mask, int32_t* idx, float* tau, const ScoreSource& in,
+                              int32_t* rest) {
+  const auto one = [&](auto kernel) { hipLaunchKernelGGL(kernel, dim3(1), dim3(1024), 0, ctx->stream, score, n, k, group, mask, idx, tau, in, rest); };
+  const auto size = [&](auto scored) {
+    constexpr bool S = decltype(scored)::value;
+    if (n <= 4096) one(topk_small_kernel<4, true, S>);
+    else if (n <= 16384) one(topk_small_kernel<16, true, S>);
+    else one(topk_small_kernel<64, false, S>);
+  };
+  if (in.sums) size(std::true_type{});
+  else size(std::false_type{});
+}
+
+strp_status launch_select(strp_ctx* ctx, const double* sums, const double* n2, int mode, int n, int k, float* score, double* energy_out,
+                          uint8_t* mask, int32_t* idx, float* tau, int32_t* rest) {
+  if (k >= n || n > 65536) {        // everything is kept, or too long for one block: in two steps
+    STRP_TRY(launch_unit_scores(ctx, sums, n2, n, 1, mode, score, energy_out));
+    return launch_topk(ctx, score, n, k, 1, mask, idx, tau, nullptr, 0);
+  }
+  ProfScope ps(ctx, "topk", 0.0, 5.0 * (double)n + 4.0 * (double)k);
+  launch_topk_small(ctx, score, n, k, 1, mask, idx, tau, ScoreSource{sums, n2, mode, energy_out}, rest);
+  STRP_HIP(ctx, hipGetLastError());
+  return STRP_OK;
+}
+
 strp_status launch_topk(strp_ctx* ctx, const float* score, int n, int k, int group, uint8_t* mask, int32_t* idx, float* tau,
                         void* scratch, size_t scratch_bytes) {
   ProfScope ps(ctx, "topk", 0.0, 5.0 * (double)n + 4.0 * (double)k * group);
   if (k <= 0 || k >= n) {
     hipLaunchKernelGGL(topk_all_kernel, dim3(1), dim3(1024), 0, ctx->stream, score, n, k >= n ? 1 : 0, group, mask, idx, tau);
   } else if (n <= 65536) {
-    const auto one = [&](auto kernel) { hipLaunchKernelGGL(kernel, dim3(1), dim3(1024), 0, ctx->stream, score, n, k, group, mask, idx, tau); };
-    if (n <= 4096) one(topk_small_kernel<4, true>);
-    else if (n <= 16384) one(topk_small_kernel<16, true>);
-    else one(topk_small_kernel<64, false>);
+    launch_topk_small(ctx, const_cast<float*>(score), n, k, group, mask, idx, tau, ScoreSource{nullptr, nullptr, 0, nullptr}, nullptr);
   } else {
     if (!scratch || scratch_bytes < topk_scratch_bytes(n))
       return fail(ctx, STRP_ENOMEM, "top-k over %d scores needs %zu bytes of workspace", n, topk_scratch_bytes(n));

@@ -209,69 +209,91 @@ __device__ __forceinline__ double small_src(const unsigned short* s, long long i
 }
 
 
-// Small matrices (weights): planes of src * scale with k = column (contraction), r = row:
-// [ceil(rows/128)][ceil(cols/8)][128][8], zero padded.  transpose != 0 reads src[c][r].
-// scale_dev (device, may be null = 1) is a power of two chosen by weight_scale.
-// transpose == 2: src is symmetric and only its lower triangle is valid (reads src[max(r,c)][min(r,c)]).
+// Small matrices (weights): planes of src * scale, [ceil(rows/128)][plane_kg(cols)][128][8], zero padded.  A thread makes one
+// 16-byte chunk (eight k of one row) of each plane, so stores are whole kilobytes per wavefront; sources that are
+// stored along k are read 32 (fp32) bytes at a time, the others along consecutive rows.
+struct SplitJobs {
+  SplitJob j[2];
+  long long chunk0[3];      // first chunk of each job
+};
 template <typename TS>
-__global__ __launch_bounds__(256) void split_small_kernel(const TS* src, long long lds, int rows, int cols, int transpose,
-                                                          const float* scale_dev, unsigned short* hi, unsigned short* lo) {
-  const int KG = (int)((((cols + 7) >> 3) + 3) & ~3);   // = plane_kg(cols)
-  const long long total = (long long)((rows + 127) >> 7) * KG * 1024;
-  const long long e = (long long)blockIdx.x * 256 + threadIdx.x;
-  if (e >= total) return;
-  const int j = (int)(e & 7);
-  const int rr = (int)((e >> 3) & 127);
-  const long long pg = e >> 10;
-  const int g = (int)(pg % KG), pan = (int)(pg / KG);
-  const int r = pan * 128 + rr, c = g * 8 + j;
-  double x = 0.0;
-  if (r < rows && c < cols) {
-    if (transpose == 2) x = r >= c ? small_src(src, (long long)r * lds + c) : small_src(src, (long long)c * lds + r);
-    else x = transpose ? small_src(src, (long long)c * lds + r) : small_src(src, (long long)r * lds + c);
+__device__ __forceinline__ void split_chunk(const SplitJob& b, long long e) {
+  const TS* src = (const TS*)b.src;
+  const int KG = (int)plane_kg(b.cols);
+  const int rr = (int)(e & 127);
+  const long long pg = e >> 7;
+  const int g = (int)(pg % KG), r = (int)(pg / KG) * 128 + rr;
+  double x[8];
+#pragma unroll
+  for (int j = 0; j < 8; ++j) {
+    // clamped addresses: the eight loads are unconditional and in flight together
+    const int rc = r < b.rows ? r : b.rows - 1, c = g * 8 + j < b.cols ? g * 8 + j : b.cols - 1;
+    const bool swap = b.transpose == 2 ? rc < c : b.transpose != 0;
+    x[j] = small_src(src, swap ? (long long)c * b.lds + rc : (long long)rc * b.lds + c);
   }
-  x *= scale_dev ? (double)*scale_dev : 1.0;
-  x = fmin(fmax(x, -65504.0), 65504.0);
-  const _Float16 h = (_Float16)x;
-  hi[e] = __builtin_bit_cast(unsigned short, h);
-  if (lo) {
-    const _Float16 l = (_Float16)(x - (double)h);
-    lo[e] = __builtin_bit_cast(unsigned short, l);
+#pragma unroll
+  for (int j = 0; j < 8; ++j)
+    if (r >= b.rows || g * 8 + j >= b.cols) x[j] = 0.0;
+  const double scale = b.maxbits ? (double)scale_of_max(*b.maxbits) : 1.0;
+  unsigned short h[8], l[8];
+#pragma unroll
+  for (int j = 0; j < 8; ++j) {
+    const double y = fmin(fmax(x[j] * scale, -65504.0), 65504.0);
+    const _Float16 hh = (_Float16)y;
+    h[j] = __builtin_bit_cast(unsigned short, hh);
+    l[j] = __builtin_bit_cast(unsigned short, (_Float16)(y - (double)hh));
   }
+  *(uint4*)(b.hi + e * 8) = make_uint4(sp_pack2(h[0], h[1]), sp_pack2(h[2], h[3]), sp_pack2(h[4], h[5]), sp_pack2(h[6], h[7]));
+  if (b.lo) *(uint4*)(b.lo + e * 8) = make_uint4(sp_pack2(l[0], l[1]), sp_pack2(l[2], l[3]), sp_pack2(l[4], l[5]), sp_pack2(l[6], l[7]));
+}
+__global__ __launch_bounds__(256) void split_small_kernel(const SplitJobs jobs) {
+  const long long e = (long long)blockIdx.x * 256 + threadIdx.x;      // chunk counts are multiples of 128
+  if (e >= jobs.chunk0[2]) return;
+  const int q = e >= jobs.chunk0[1];
+  const SplitJob& b = jobs.j[q];
+  const long long c = e - jobs.chunk0[q];
+  if (b.kind == SRC_F64) split_chunk<double>(b, c);
+  else if (b.kind == SRC_F32) split_chunk<float>(b, c);
+  else split_chunk<unsigned short>(b, c);
 }
 
-strp_status split_small(strp_ctx* ctx, const void* src, int src_kind, long long lds, int rows, int cols, int transpose,
-                        const float* scale_dev, unsigned short* hi, unsigned short* lo) {
-  const long long tot = (long long)plane_elems(rows, cols);
-  dim3 grid((unsigned)((tot + 255) / 256)), block(256);
-  if (src_kind == SRC_F64)
-    hipLaunchKernelGGL((split_small_kernel<double>), grid, block, 0, ctx->stream, (const double*)src, lds, rows, cols, transpose, scale_dev, hi, lo);
-  else if (src_kind == SRC_F32)
-    hipLaunchKernelGGL((split_small_kernel<float>), grid, block, 0, ctx->stream, (const float*)src, lds, rows, cols, transpose, scale_dev, hi, lo);
-  else
-    hipLaunchKernelGGL((split_small_kernel<unsigned short>), grid, block, 0, ctx->stream, (const unsigned short*)src, lds, rows, cols, transpose, scale_dev, hi, lo);
+strp_status split_small(strp_ctx* ctx, const SplitJob* jobs, int n) {
+  SplitJobs s;
+  memset(&s, 0, sizeof(s));
+  for (int i = 0; i < 2; ++i) {
+    if (i < n) s.j[i] = jobs[i];
+    s.chunk0[i + 1] = s.chunk0[i] + (i < n ? (long long)plane_elems(jobs[i].rows, jobs[i].cols) / 8 : 0);
+  }
+  hipLaunchKernelGGL(split_small_kernel, dim3((unsigned)((s.chunk0[2] + 255) / 256)), dim3(256), 0, ctx->stream, s);
   STRP_HIP(ctx, hipGetLastError());
   return STRP_OK;
 }
 
-// scale = 2^e with max|x| * scale in [2^11, 2^12): keeps fp16 hi far from overflow and lo out of the subnormals.
-// Pass 1: grid-wide max of |x| through an integer atomic on the float bits (order-preserving for x >= 0).
+// grid-wide max of |x| through an integer atomic on the float bits (order-preserving for x >= 0)
 template <typename TS>
-__global__ __launch_bounds__(256) void absmax_kernel(const TS* src, long long lds, int rows, int cols, unsigned int* slot) {
+__device__ __forceinline__ float row_max(const TS* row, int cols) {
   float m = 0.0f;
-  for (int r = blockIdx.x; r < rows; r += gridDim.x) {   // a block walks whole rows: no division per element
-    const TS* row = src + (long long)r * lds;
-    // eight independent loads per trip keep enough requests in flight for a latency-bound reduction
-    int c = threadIdx.x;
-    for (; c + 7 * 256 < cols; c += 8 * 256) {
-      float v[8];
+  // eight independent loads per trip keep enough requests in flight for a latency-bound reduction
+  int c = threadIdx.x;
+  for (; c + 7 * 256 < cols; c += 8 * 256) {
+    float v[8];
 #pragma unroll
-      for (int q = 0; q < 8; ++q) v[q] = (float)small_src(row, c + 256 * q);
+    for (int q = 0; q < 8; ++q) v[q] = (float)small_src(row, c + 256 * q);
 #pragma unroll
-      for (int q = 0; q < 8; ++q) m = __builtin_fmaxf(m, __builtin_fabsf(v[q]));
-    }
-    for (; c < cols; c += 256) m = __builtin_fmaxf(m, __builtin_fabsf((float)small_src(row, c)));
+    for (int q = 0; q < 8; ++q) m = __builtin_fmaxf(m, __builtin_fabsf(v[q]));
   }
+  for (; c < cols; c += 256) m = __builtin_fmaxf(m, __builtin_fabsf((float)small_src(row, c)));
+  return m;
+}
+struct MaxJobs {
+  MaxJob j[2];
+};
+__global__ __launch_bounds__(256) void absmax_kernel(const MaxJobs jobs) {
+  const MaxJob& b = jobs.j[blockIdx.y];
+  float m = 0.0f;
+  for (int r = blockIdx.x; r < b.rows; r += gridDim.x)       // a block walks whole rows: no division per element
+    m = __builtin_fmaxf(m, b.kind == SRC_F32 ? row_max((const float*)b.src + (long long)r * b.lds, b.cols)
+                                             : row_max((const unsigned short*)b.src + (long long)r * b.lds, b.cols));
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) m = __builtin_fmaxf(m, __shfl_down(m, o, 64));
   // one atomic per block: thousands of atomics on one address serialise in L2 and were the whole run time
@@ -280,34 +302,19 @@ __global__ __launch_bounds__(256) void absmax_kernel(const TS* src, long long ld
   __syncthreads();
   if (threadIdx.x == 0) {
     m = __builtin_fmaxf(__builtin_fmaxf(wm[0], wm[1]), __builtin_fmaxf(wm[2], wm[3]));
-    if (m > 0.0f) atomicMax(slot, __builtin_bit_cast(unsigned int, m));
+    if (m > 0.0f) atomicMax(b.maxbits, __builtin_bit_cast(unsigned int, m));
   }
-}
-// Pass 2: the slot (max bits) becomes the scale (float) in place.
-__global__ void scale_from_max_kernel(unsigned int* slot) {
-  if (threadIdx.x != 0 || blockIdx.x != 0) return;
-  const float m = __builtin_bit_cast(float, *slot);
-  float s = 1.0f;
-  if (m > 0.0f && m < 3.0e38f) {
-    int e;
-    (void)frexpf(m, &e);        // m = q * 2^e, q in [0.5, 1)
-    s = ldexpf(1.0f, 12 - e);   // m * s in [2^11, 2^12)
-  }
-  *slot = __builtin_bit_cast(unsigned int, s);
 }
 
-strp_status weight_scale(strp_ctx* ctx, const void* src, int src_kind, long long lds, int rows, int cols, float* scale_out) {
-  STRP_TRY(fill_zero(ctx, scale_out, 4));
-  unsigned int* slot = (unsigned int*)scale_out;
-  long long blocks = rows < 1024 ? rows : 1024;
-  dim3 grid((unsigned)blocks), block(256);
-  if (src_kind == SRC_F64)
-    hipLaunchKernelGGL((absmax_kernel<double>), grid, block, 0, ctx->stream, (const double*)src, lds, rows, cols, slot);
-  else if (src_kind == SRC_F32)
-    hipLaunchKernelGGL((absmax_kernel<float>), grid, block, 0, ctx->stream, (const float*)src, lds, rows, cols, slot);
-  else
-    hipLaunchKernelGGL((absmax_kernel<unsigned short>), grid, block, 0, ctx->stream, (const unsigned short*)src, lds, rows, cols, slot);
-  hipLaunchKernelGGL(scale_from_max_kernel, dim3(1), dim3(1), 0, ctx->stream, slot);
+strp_status abs_max(strp_ctx* ctx, const MaxJob* jobs, int n) {
+  MaxJobs m;
+  memset(&m, 0, sizeof(m));
+  int rows = 1;
+  for (int i = 0; i < n; ++i) {
+    m.j[i] = jobs[i];
+    rows = jobs[i].rows > rows ? jobs[i].rows : rows;
+  }
+  hipLaunchKernelGGL(absmax_kernel, dim3(rows < 512 ? rows : 512, n), dim3(256), 0, ctx->stream, m);
   STRP_HIP(ctx, hipGetLastError());
   return STRP_OK;
 }

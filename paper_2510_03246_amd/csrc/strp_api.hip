@@ -69,50 +69,26 @@ static inline long long round_up(long long x, long long a) { return (x + a - 1) 
 static inline bool aligned16(const void* p) { return ((uintptr_t)p & 15u) == 0; }
 
 // ---- small kernels ------------------------------------------------------------------------------
-__global__ __launch_bounds__(256) void add_diag_kernel(double* A, long long ld, int n, double lam, const double* lam_dev) {
-  const int i = blockIdx.x * 256 + threadIdx.x;
-  if (i < n) A[(long long)i * ld + i] += lam_dev ? *lam_dev : lam;
-}
-
-// out[0] = scale * sum(v[0..n)) (single block, fixed order)
-__global__ __launch_bounds__(256) void vec_sum_kernel(const double* v, int n, double scale, double* out, double* raw) {
-  __shared__ double s[256];
+// raw = sum of v[0], v[stride], .. (n of them; single block, fixed order), *out = scale * raw, added to the diagonal of
+// A [nd x nd, ld] when A is given
+__global__ __launch_bounds__(1024) void scaled_sum_kernel(const double* v, int stride, int n, double scale, double* raw, double* out, double* A,
+                                                          long long ld, int nd) {
+  __shared__ double s[1024];
   double a = 0.0;
-  for (int i = threadIdx.x; i < n; i += 256) a += v[i];
+  for (int i = threadIdx.x; i < n; i += 1024) a += v[(long long)i * stride];
   s[threadIdx.x] = a;
   __syncthreads();
-  for (int o = 128; o > 0; o >>= 1) {
+  for (int o = 512; o > 0; o >>= 1) {
     if (threadIdx.x < o) s[threadIdx.x] += s[threadIdx.x + o];
     __syncthreads();
   }
+  const double t = s[0];
   if (threadIdx.x == 0) {
-    if (raw) *raw = s[0];
-    *out = s[0] * scale;
+    *raw = t;
+    *out = t * scale;
   }
-}
-
-// dst[r][c] (fp32, ld ldd, zero padded) = W[r][idx[c]]  (kept columns of fc2)
-__global__ __launch_bounds__(256) void gather_cols_kernel(const float* W, int rows, int in, const int32_t* idx, int s, float* dst,
-                                                          long long ldd) {
-  const long long e = (long long)blockIdx.x * 256 + threadIdx.x;
-  if (e >= (long long)rows * ldd) return;
-  const int r = (int)(e / ldd), c = (int)(e % ldd);
-  dst[e] = c < s ? W[(long long)r * in + idx[c]] : 0.0f;
-}
-// dst[r][c] = W[idx[r]][c]  (kept rows of fc1)
-__global__ __launch_bounds__(256) void gather_rows_kernel(const float* W, int in, const int32_t* idx, int s, float* dst, long long ldd) {
-  const long long e = (long long)blockIdx.x * 256 + threadIdx.x;
-  if (e >= (long long)s * ldd) return;
-  const int r = (int)(e / ldd), c = (int)(e % ldd);
-  dst[e] = c < in ? W[(long long)idx[r] * in + c] : 0.0f;
-}
-// dst[c][r] (fp64, ld ldd) = src[r][c] (fp32, ld lds): r < rows, c < cols
-__global__ __launch_bounds__(256) void transpose_f32_f64_kernel(const float* src, long long lds, int rows, int cols, double* dst,
-                                                                long long ldd) {
-  const long long e = (long long)blockIdx.x * 256 + threadIdx.x;
-  if (e >= (long long)rows * cols) return;
-  const int c = (int)(e / rows), r = (int)(e % rows);
-  dst[(long long)c * ldd + r] = (double)src[(long long)r * lds + c];
+  if (A)
+    for (int i = threadIdx.x; i < nd; i += 1024) A[(long long)i * ld + i] += t * scale;
 }
 
 // The per-element rules of the pruned rows (pruned_elem) are in cojob.h.
@@ -251,68 +227,124 @@ __global__ __launch_bounds__(256) void cojob_drain_kernel(const CoJob job) {
   }
 }
 
-// per pruned row: the units' sums added in segment order -> red[2 j], red[2 j + 1] and the row's scoring sums
-__global__ __launch_bounds__(256) void cojob_finish_kernel(const CoJob job, double* red, double* rowsums, int f) {
-  const int p = blockIdx.x * 256 + threadIdx.x;
-  if (p >= job.nrows) return;
-  const int j = job.rows[p];
-  double t[6] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
-  const double* src = job.partial + (unsigned long long)p * job.segs * 6;
-  for (int g = 0; g < job.segs; ++g)
-#pragma unroll
-    for (int q = 0; q < 6; ++q) t[q] += src[g * 6 + q];
-  red[2 * (long long)j] = t[0];
-  red[2 * (long long)j + 1] = t[1];
-  if (rowsums) {
-    rowsums[j] = t[2];
-    if (job.Z0) {
-      rowsums[(long long)f + j] = t[3];
-      rowsums[2 * (long long)f + j] = t[4];
-      rowsums[3 * (long long)f + j] = t[5];
-    }
-  }
-}
-
-// per-block sum of squares of an fp32 array -> red[block][0] (red[block][1] = 0)
-__global__ __launch_bounds__(256) void sumsq_kernel(const float* x, long long n, double* red) {
-  double a = 0.0;
-  for (long long i = (long long)blockIdx.x * 256 + threadIdx.x; i < n; i += (long long)gridDim.x * 256) a += (double)x[i] * (double)x[i];
-  __shared__ double sh[4];
-  for (int o = 32; o > 0; o >>= 1) a += __shfl_down(a, o, 64);
-  if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = a;
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    red[2 * (long long)blockIdx.x] = sh[0] + sh[1] + sh[2] + sh[3];
-    red[2 * (long long)blockIdx.x + 1] = 0.0;
-  }
-}
-
-// per-block partial of sum_i a[i] b[i] -> red[block][0] (red[block][1] = 0)
-__global__ __launch_bounds__(256) void dot_f32_f64_kernel(const float* a, const double* b, long long n, double* red) {
-  double acc = 0.0;
-  for (long long i = (long long)blockIdx.x * 256 + threadIdx.x; i < n; i += (long long)gridDim.x * 256) acc = __builtin_fma((double)a[i], b[i], acc);
-  __shared__ double sh[4];
-  for (int o = 32; o > 0; o >>= 1) acc += __shfl_down(acc, o, 64);
-  if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = acc;
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    red[2 * (long long)blockIdx.x] = sh[0] + sh[1] + sh[2] + sh[3];
-    red[2 * (long long)blockIdx.x + 1] = 0.0;
-  }
-}
-
-// scalars[dst] = a * scalars[s0] + b * scalars[s1]   (one thread; keeps the objective assembly on device)
-__global__ void axpby_scalar_kernel(double* sc, int dst, double a, int s0, double b, int s1) {
-  if (threadIdx.x == 0 && blockIdx.x == 0) sc[dst] = a * sc[s0] + (s1 >= 0 ? b * sc[s1] : 0.0);
-}
-
-static unsigned blocks_for(long long n) { return (unsigned)((n + 255) / 256); }
+// a small job's units, one workgroup each: no counter to take them from
+__global__ __launch_bounds__(256) void cojob_units_kernel(const CoJob job) { cojob_unit(job, blockIdx.x); }
 
 // scalar slots of strp_module_state::scalars
 // bits of strp_module_state::sums_cached: which token sums cv.rowsums holds for EVERY row of the current state
 enum { SUMS_G = 1, SUMS_EU = 2, SUMS_V = 4 };
 enum { SC_LAM1 = 0, SC_LAM2 = 1, SC_SUMA0 = 2, SC_TRH = 3, SC_T1 = 4, SC_T2 = 5, SC_T3 = 6, SC_T4 = 7, SC_T5 = 8,
-       SC_TAU = 9, SC_ENERGY = 10, SC_TMP0 = 11, SC_TMP1 = 12, SC_TMP2 = 13, SC_TMP3 = 14, SC_W2SQ = 15, SC_W1SQ = 16, SC_COUNT = 32 };
+       SC_TAU = 9, SC_ENERGY = 10, SC_W2SQ = 15, SC_W1SQ = 16, SC_COUNT = 32 };
+
+// ---- the end of a step in one launch -------------------------------------------------------------------------------
+// Every workgroup adds up 256 pruned rows: the units' sums in segment order -> the row's scoring sums, and the rows' share
+// of the objective.  The last one then sums what the step's kernels left per workgroup into the objective's terms, and
+// writes the scalars and the status word to the report's host memory (two copies and their launches otherwise).
+struct FinishP {
+  double* sc;
+  // pruned rows of a fused a/z pass (nrows = 0: none)
+  const int32_t* rows;
+  const double* partial;
+  int nrows, segs, f, z0;
+  double* rowsums;
+  double* blk;                               // [gridDim.x][2]
+  unsigned int* ticket;
+  // per-workgroup sums: terms 2 and 3 (kept rows, pruned rows when their pass was a kernel of its own), term 1, weights
+  const double* red_z; int nz;               // pairs
+  const double* red_p; int np;               // pairs
+  const double* red_1; int n1, stride1;      // every stride1-th
+  const double* w2; int nw2;
+  const double* w1; int nw1;
+  double c1, c2, c3;
+  int do_z, do_1, do_w;
+  double* host;                              // pinned: [SC_COUNT] scalars, then the status word; null: no report
+  const int32_t* status;
+};
+__device__ __forceinline__ double finish_block_sum(double a, double* sh) {
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) a += __shfl_down(a, o, 64);
+  __syncthreads();
+  if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = a;
+  __syncthreads();
+  return sh[0] + sh[1] + sh[2] + sh[3];
+}
+__global__ __launch_bounds__(256) void step_finish_kernel(const FinishP p) {
+  __shared__ double sh[4];
+  __shared__ unsigned int flag;
+  const int tid = threadIdx.x;
+  double r0 = 0.0, r1 = 0.0;
+  if (p.nrows > 0) {
+    const int q = blockIdx.x * 256 + tid;
+    if (q < p.nrows) {
+      const int j = p.rows[q];
+      double t[6] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
+      const double* src = p.partial + (unsigned long long)q * p.segs * 6;
+      for (int g = 0; g < p.segs; ++g)
+#pragma unroll
+        for (int e = 0; e < 6; ++e) t[e] += src[g * 6 + e];
+      if (j >= 0) {
+        r0 = t[0];
+        r1 = t[1];
+        p.rowsums[j] = t[2];
+        if (p.z0) {
+          p.rowsums[(long long)p.f + j] = t[3];
+          p.rowsums[2 * (long long)p.f + j] = t[4];
+          p.rowsums[3 * (long long)p.f + j] = t[5];
+        }
+      }
+    }
+    r0 = finish_block_sum(r0, sh);
+    r1 = finish_block_sum(r1, sh);
+    if (gridDim.x > 1) {
+      if (tid == 0) {
+        agent_put(&p.blk[2 * blockIdx.x], r0);
+        agent_put(&p.blk[2 * blockIdx.x + 1], r1);
+      }
+      if (!last_block(p.ticket, &flag)) return;
+      if (tid == 0) *p.ticket = 0u;
+      r0 = r1 = 0.0;
+      for (int b = tid; b < (int)gridDim.x; b += 256) {
+        r0 += agent_get(&p.blk[2 * b]);
+        r1 += agent_get(&p.blk[2 * b + 1]);
+      }
+      r0 = finish_block_sum(r0, sh);
+      r1 = finish_block_sum(r1, sh);
+    }
+  }
+  auto sum = [&](const double* v, int n, int stride, int off) {
+    double a = 0.0;
+#pragma unroll 8
+    for (int i = tid; i < n; i += 256) a += v[(long long)i * stride + off];
+    return finish_block_sum(a, sh);
+  };
+  if (p.do_z) {
+    const double z0 = sum(p.red_z, p.nz, 2, 0), z1 = sum(p.red_z, p.nz, 2, 1);
+    if (p.np) {
+      r0 = sum(p.red_p, p.np, 2, 0);
+      r1 = sum(p.red_p, p.np, 2, 1);
+    }
+    if (tid == 0) {
+      p.sc[SC_T2] = p.c2 * (z0 + r0);
+      p.sc[SC_T3] = p.c3 * (z1 + r1);
+    }
+  }
+  if (p.do_1) {
+    const double t = sum(p.red_1, p.n1, p.stride1, 0);
+    if (tid == 0) p.sc[SC_T1] = p.c1 * t;
+  }
+  if (p.do_w) {
+    const double a = sum(p.w2, p.nw2, 1, 0), b = sum(p.w1, p.nw1, 1, 0);
+    if (tid == 0) {
+      p.sc[SC_W2SQ] = a;
+      p.sc[SC_W1SQ] = b;
+    }
+  }
+  if (p.host) {
+    __syncthreads();
+    if (tid < SC_COUNT) __hip_atomic_store(&p.host[tid], p.sc[tid], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    if (tid == SC_COUNT) __hip_atomic_store((int32_t*)(p.host + SC_COUNT), agent_get(p.status), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+  }
+}
 
 static strp_status check_desc(strp_ctx* ctx, const strp_module_desc* d) {
   if (!d) return fail(ctx, STRP_EINVAL, "null module descriptor");
@@ -616,20 +648,18 @@ static strp_status make_c_planes(strp_ctx* ctx, Arena& arena, const void* src, i
   return STRP_OK;
 }
 
-// Planes of a small matrix (weights; k = column, r = row), scaled by a device-chosen power of two.
-static strp_status make_weight_planes(strp_ctx* ctx, Arena& arena, const void* src, int src_kind, long long lds, int rows, int cols,
-                                      int transpose, int np, PlaneOp* out) {
+// Room for the planes of a small matrix (weights; k = column, r = row), scaled by the power of two that *maxbits calls for.
+static strp_status weight_planes(strp_ctx* ctx, Arena& arena, const void* src, int src_kind, long long lds, int rows, int cols,
+                                 int transpose, int np, const unsigned int* maxbits, PlaneOp* out, SplitJob* job) {
   const size_t n = plane_elems(rows, cols);
-  STRP_TAKE(ctx, arena, scale, float, 64);
   STRP_TAKE(ctx, arena, hi, unsigned short, n);
   unsigned short* lo = nullptr;
   if (np == 2) {
     STRP_TAKE(ctx, arena, lo2, unsigned short, n);
     lo = lo2;
   }
-  STRP_TRY(weight_scale(ctx, src, src_kind, lds, transpose ? cols : rows, transpose ? rows : cols, scale));
-  STRP_TRY(split_small(ctx, src, src_kind, lds, rows, cols, transpose, scale, hi, lo));
-  *out = PlaneOp{hi, lo, plane_kg(cols), (rows + 127) / 128, scale};
+  *out = PlaneOp{hi, lo, plane_kg(cols), (rows + 127) / 128, maxbits};
+  *job = SplitJob{src, lds, src_kind, rows, cols, transpose, maxbits, hi, lo};
   return STRP_OK;
 }
 
@@ -679,9 +709,8 @@ static size_t nt_partial_elems(int M, int N, long long K, int triangle) {
   return (size_t)p.splits * (size_t)M * (size_t)N;
 }
 
-// C = P Q^T over K (ROW planes); partials in the arena (by value: released on return), fp64 reduction.
-static strp_status nt_product(strp_ctx* ctx, Arena arena, const PlaneOp& P, const PlaneOp& Q, int M, int N, long long K, int triangle,
-                              float* outf, long long ldof, double* outd, long long ldod, double* diag, int accumulate) {
+// C = P Q^T over K (ROW planes); partials in the arena (by value: released on return), fp64 reduction into what r names.
+static strp_status nt_product(strp_ctx* ctx, Arena arena, const PlaneOp& P, const PlaneOp& Q, int M, int N, long long K, int triangle, ReduceP r) {
   GemmP p;
   memset(&p, 0, sizeof(p));
   p.P = P; p.Q = Q; p.M = M; p.N = N; p.K = K; p.triangle = triangle;
@@ -690,11 +719,17 @@ static strp_status nt_product(strp_ctx* ctx, Arena arena, const PlaneOp& P, cons
   STRP_TAKE(ctx, arena, part, float, (size_t)p.splits * M * N);
   p.out = part;
   STRP_TRY(launch_gemm(ctx, p));
-  return launch_splitk_reduce(ctx, part, p.splits, M, N, triangle, outf, ldof, outd, ldod, diag, accumulate);
+  r.part = part; r.splits = p.splits; r.M = M; r.N = N; r.triangle = triangle;
+  return launch_splitk_reduce(ctx, r);
+}
+static ReduceP reduce_to(double* outd, long long ldod) {
+  ReduceP r;
+  memset(&r, 0, sizeof(r));
+  r.outd = outd; r.ldod = ldod;
+  return r;
 }
 
-// Solve Wsub (Gram + lam I) = R with R = Lhs Rhs^T over the tokens.  Returns the fp64 solution
-// [m x n] (leading dimension n) in *sol_out; it lives in the arena passed by reference.
+// Solve Wsub (Gram + lam I) = R with R = Lhs Rhs^T over the tokens.
 struct RefitIn {
   const float* Gram; long long ldg;       // fp32 Gram (used when sys_ready == 0)
   double* sys; int sys_ready;             // [n x f64_ld(n)] fp64 scratch: 0 = empty, 1 = holds Gram + lam I
@@ -711,8 +746,7 @@ static strp_status factor_and_invert(strp_ctx* ctx, Arena arena, double* sys, in
   return chol_inverse(ctx, sys, n, f64_ld(n), sub, Linv, ldl, ctx->status_dev);
 }
 
-// *sol_out: [m x f64_ld(n)]
-static strp_status ridge_solve(strp_ctx* ctx, Arena& arena, const RefitIn& in, double** sol_out) {
+static strp_status ridge_solve(strp_ctx* ctx, Arena& arena, const RefitIn& in, const WeightsOut& out) {
   const int n = in.n, m = in.m;
   const long long ld = f64_ld(n);
   const bool factor = !in.linv_ready;
@@ -724,10 +758,8 @@ static strp_status ridge_solve(strp_ctx* ctx, Arena& arena, const RefitIn& in, d
   }
   STRP_TAKE(ctx, arena, R, double, (size_t)m * ld);
   STRP_TAKE(ctx, arena, tmp, double, (size_t)m * ld);
-  STRP_TRY(nt_product(ctx, arena, in.Lhs, in.Rhs, m, n, in.T, 0, nullptr, 0, R, ld, nullptr, 0));
-  STRP_TRY(apply_inverse_right(ctx, in.Linv, n, in.ldl, R, m, ld, tmp));
-  *sol_out = R;
-  return STRP_OK;
+  STRP_TRY(nt_product(ctx, arena, in.Lhs, in.Rhs, m, n, in.T, 0, reduce_to(R, ld)));
+  return apply_inverse_right(ctx, in.Linv, n, in.ldl, R, m, ld, tmp, out);
 }
 
 // Persistent per-module planes (caller-owned strp_module_state::cache), fixed at initialisation:
@@ -809,7 +841,7 @@ size_t strp_workspace_bytes(const strp_module_desc* desc) {
                 al(nt_partial_elems((int)d, (int)d, (long long)kp, 1) * 4) + al(d * d * 8) + al(invd_max) +
                 2 * (al(256) + 2 * al(plane_elems(km, d) * 2)) + (al(256) + 2 * al(plane_elems(d, d) * 2)) + al(plane_elems(T, km) * 2) + 8192 +
                 /* strip sums of the kept rows from the a- and z-update epilogues */
-                al(2 * (size_t)((T + 63) / 64) * km * 4) + al((size_t)((T + 63) / 64) * km * 4) + al(rowsum_scratch_bytes(2, (int)km));
+                al(2 * (size_t)((T + 63) / 64) * km * 4) + al((size_t)((T + 63) / 64) * km * 4);
   return (init > step ? init : step) + (1 << 20);
 }
 
@@ -826,7 +858,9 @@ strp_status strp_gram(strp_ctx* ctx, const void* A, strp_dtype dt, int32_t C, in
   Arena arena(ctx);
   PlaneOp op;
   STRP_TRY(make_t_planes(ctx, arena, A, dt, ldA, idx, s, T, 0, planes_for(dt, ctx->precision), &op));
-  return nt_product(ctx, arena, op, op, s, s, T, 1, G, ldG, nullptr, 0, diag, accumulate);
+  ReduceP r = reduce_to(nullptr, 0);
+  r.outf = G; r.ldof = ldG; r.diag = diag; r.accumulate = accumulate;
+  return nt_product(ctx, arena, op, op, s, s, T, 1, r);
 }
 
 strp_status strp_refit(strp_ctx* ctx, strp_side side, const float* Gram, int32_t ldg, double lambda, double* chol, int chol_valid,
@@ -875,10 +909,9 @@ strp_status strp_refit(strp_ctx* ctx, strp_side side, const float* Gram, int32_t
     STRP_TRY(make_t_planes(ctx, arena, Rhs, rhs_dtype, ld_rhs, nullptr, in, T, 0, planes_for(rhs_dtype, prec), &ri.Rhs));
   }
   ri.m = m; ri.n = n; ri.T = T;
-  double* sol = nullptr;
-  STRP_TRY(ridge_solve(ctx, arena, ri, &sol));
-  if (chol && !chol_direct) STRP_TRY(copy_f64(ctx, ri.Linv, ri.ldl, chol, n, n));
-  return scatter_weights(ctx, sol, f64_ld(n), side, idx, s, W, out, in);
+  STRP_TRY(fill_zero(ctx, W, sizeof(float) * (size_t)out * (size_t)in));
+  STRP_TRY(ridge_solve(ctx, arena, ri, WeightsOut{side, idx, W, in, nullptr, 0, nullptr, nullptr}));
+  return chol && !chol_direct ? copy_f64(ctx, ri.Linv, ri.ldl, chol, n, n) : STRP_OK;
 }
 
 strp_status strp_module_init(strp_ctx* ctx, const strp_module_desc* desc, strp_module_state* st, const strp_params* params) {
@@ -902,7 +935,12 @@ strp_status strp_module_init(strp_ctx* ctx, const strp_module_desc* desc, strp_m
   cache_layout(desc, prec, (char*)st->cache, &cv);
   Arena arena(ctx);
   double* sc = st->scalars;
-  STRP_TRY(fill_zero(ctx, sc, SC_COUNT * sizeof(double)));
+  STRP_TAKE(ctx, arena, wmax, unsigned int, 64);
+  {
+    const FillRange z[5] = {{sc, SC_COUNT * sizeof(double)}, {wmax, 256}, {st->W1, sizeof(float) * (size_t)f * d}, {st->W2, sizeof(float) * (size_t)f * d},
+                            {st->mask, (size_t)f}};
+    STRP_TRY(fill_zero(ctx, z, 5));
+  }
   STRP_TRY(launch_colnorm2(ctx, st->W2hat, desc->w_dtype, d, f, f, st->n2));
   // X planes (persistent)
   STRP_TRY(split_act(ctx, st->X, desc->x_dtype, desc->ldx, nullptr, d, T, 0, 0, (unsigned short*)cv.Xt.hi, (unsigned short*)cv.Xt.lo,
@@ -910,8 +948,12 @@ strp_status strp_module_init(strp_ctx* ctx, const strp_module_desc* desc, strp_m
   {
     Arena a2 = arena;
     PlaneOp W1p, W2p, A0k8;
-    STRP_TRY(make_weight_planes(ctx, a2, st->W1hat, wkind, d, f, d, 0, npw, &W1p));
-    STRP_TRY(make_weight_planes(ctx, a2, st->W2hat, wkind, f, d, f, 0, npw, &W2p));
+    SplitJob jobs[2];
+    STRP_TRY(weight_planes(ctx, a2, st->W1hat, wkind, d, f, d, 0, npw, wmax, &W1p, &jobs[0]));
+    STRP_TRY(weight_planes(ctx, a2, st->W2hat, wkind, f, d, f, 0, npw, wmax + 1, &W2p, &jobs[1]));
+    const MaxJob mj[2] = {{st->W1hat, d, wkind, f, d, wmax}, {st->W2hat, f, wkind, d, f, wmax + 1}};
+    STRP_TRY(abs_max(ctx, mj, 2));
+    STRP_TRY(split_small(ctx, jobs, 2));
     STRP_TAKE(ctx, a2, a0h, unsigned short, plane_elems(T, f));
     unsigned short* a0l = nullptr;
     if (npa == 2) {
@@ -930,8 +972,8 @@ strp_status strp_module_init(strp_ctx* ctx, const strp_module_desc* desc, strp_m
       STRP_TAKE(ctx, a2, red, double, 2 * (size_t)gemm_grid_blocks(p));
       p.red = red;
       STRP_TRY(launch_gemm(ctx, p));
-      STRP_TRY(launch_block_sum(ctx, red, gemm_grid_blocks(p), sc + SC_SUMA0, nullptr, 1.0, 1.0));
-      hipLaunchKernelGGL(axpby_scalar_kernel, dim3(1), dim3(1), 0, ctx->stream, sc, (int)SC_LAM2, params->delta / (double)f, (int)SC_SUMA0, 0.0, -1);
+      hipLaunchKernelGGL(scaled_sum_kernel, dim3(1), dim3(1024), 0, ctx->stream, (const double*)red, 2, gemm_grid_blocks(p), params->delta / (double)f,
+                         sc + SC_SUMA0, sc + SC_LAM2, (double*)nullptr, 0LL, 0);
     }
     {  // Y = W2hat A
       GemmP p;
@@ -949,14 +991,13 @@ strp_status strp_module_init(strp_ctx* ctx, const strp_module_desc* desc, strp_m
     Arena a2 = arena;
     STRP_TAKE(ctx, a2, diag, double, (size_t)d);
     STRP_TAKE(ctx, a2, Hd, double, (size_t)d * d);
-    STRP_TRY(nt_product(ctx, a2, cv.Xt, cv.Xt, d, d, T, 1, st->H, d, Hd, d, diag, 0));
-    hipLaunchKernelGGL(vec_sum_kernel, dim3(1), dim3(256), 0, ctx->stream, diag, d, params->delta / (double)d, sc + SC_LAM1, sc + SC_TRH);
-    hipLaunchKernelGGL(add_diag_kernel, dim3(blocks_for(d)), dim3(256), 0, ctx->stream, Hd, (long long)d, d, 0.0, sc + SC_LAM1);
+    ReduceP r = reduce_to(Hd, d);
+    r.outf = st->H; r.ldof = d; r.diag = diag;
+    STRP_TRY(nt_product(ctx, a2, cv.Xt, cv.Xt, d, d, T, 1, r));
+    hipLaunchKernelGGL(scaled_sum_kernel, dim3(1), dim3(1024), 0, ctx->stream, (const double*)diag, 1, d, params->delta / (double)d, sc + SC_TRH,
+                       sc + SC_LAM1, Hd, (long long)d, d);
     STRP_TRY(factor_and_invert(ctx, a2, Hd, d, st->cholH, d));
   }
-  STRP_TRY(fill_zero(ctx, st->W1, sizeof(float) * (size_t)f * d));
-  STRP_TRY(fill_zero(ctx, st->W2, sizeof(float) * (size_t)f * d));
-  STRP_TRY(fill_zero(ctx, st->mask, (size_t)f));
   STRP_HIP(ctx, hipGetLastError());
   st->s = 0;
   st->iter = 0;
@@ -1002,57 +1043,90 @@ strp_status strp_admm_step(strp_ctx* ctx, const strp_module_desc* desc, strp_mod
   // those rows, the kept rows' from the epilogues of the a- and z-update products (sum Z0^2 never changes after it has
   // been streamed once) -- so that only a selection on a state the library did not produce streams the rows.
   const bool wanda = params->mode == STRP_SCORE_WANDA;
+  const bool fuse_pruned = (stages & STRP_STAGE_AUPD) && (stages & STRP_STAGE_ZUPD);
+  int32_t* prow = nullptr;
+  bool prow_done = false;
+  if (fuse_pruned) {
+    STRP_TAKE(ctx, arena, prow_, int32_t, (size_t)f);
+    prow = prow_;
+  }
   if (do_select) {
     const bool have = (st->sums_cached & SUMS_G) && (wanda || ((st->sums_cached & SUMS_EU) && (st->sums_cached & SUMS_V)));
     if (!have) {
       STRP_TRY(launch_row_sums(ctx, st->A, STRP_F32, st->Z, st->Z0, lda, T, f, params->mode, cv.rowsums));
       st->sums_cached = wanda ? (st->sums_cached & SUMS_V) | SUMS_G : SUMS_G | SUMS_EU | SUMS_V;
     }
-    STRP_TRY(launch_unit_scores(ctx, cv.rowsums, st->n2, f, 1, params->mode, st->score, sc + SC_ENERGY));
-    STRP_TRY(launch_topk(ctx, st->score, f, params->k, 1, st->mask, st->idx, (float*)(sc + SC_TAU), nullptr, 0));
+    STRP_TRY(launch_select(ctx, cv.rowsums, st->n2, params->mode, f, params->k, st->score, sc + SC_ENERGY, st->mask, st->idx, (float*)(sc + SC_TAU), prow));
     st->s = params->k;
+    prow_done = true;
   }
   // the sums describe the state as it is now: void them before an update changes it (sum Z0^2 stays valid)
   if (stages & (STRP_STAGE_AUPD | STRP_STAGE_ZUPD)) st->sums_cached &= SUMS_V;
   const int s = st->s;
   const long long sp = round_up(s, 8);
 
+  // ---- everything the step needs cleared, in one launch: the refitted weights outside the kept rows and columns, the
+  // maxima of the weights' planes, the counter of the pruned rows' units
+  enum { MAX_W2 = 0, MAX_MI = 1, MAX_B = 2, MAX_W1 = 3 };
+  STRP_TAKE(ctx, arena, wmax, unsigned int, 64);
+  unsigned int* const ticket = wmax + 32;
+  {
+    const size_t wbytes = sizeof(float) * (size_t)f * d;
+    const FillRange z[3] = {{wmax, 256}, {st->W2, (stages & STRP_STAGE_REFIT2) ? wbytes : 0}, {st->W1, (stages & STRP_STAGE_REFIT1) ? wbytes : 0}};
+    STRP_TRY(fill_zero(ctx, z, 3));
+  }
+
   // ---- the pruned rows' fused a/z pass as a ride-along job ------------------------------------------------------
   // It touches only rows outside S, which nothing else in the step reads or writes, so it may run any time from
   // here to the end of the step: the factorisation chains of the fc2 refit and of the a-update carry spare
-  // workgroups for it (chol_factor reads ctx->cojob), and what they leave is drained where the pass used to run.
-  const bool fuse_pruned = (stages & STRP_STAGE_AUPD) && (stages & STRP_STAGE_ZUPD);
+  // workgroups for it (chol_inverse reads ctx->cojob), and what they leave is drained where the pass used to run.
   struct CoJobGuard {
     strp_ctx* c;
     ~CoJobGuard() { c->cojob = nullptr; }
   } cojob_guard{ctx};
   CoJob pjob;
   memset(&pjob, 0, sizeof(pjob));
-  double* red_pruned = nullptr;
-  if (fuse_pruned) {
-    STRP_TAKE(ctx, arena, rp, double, 2 * (size_t)f);
-    red_pruned = rp;
-    STRP_TRY(fill_zero(ctx, red_pruned, 2 * (size_t)f * sizeof(double)));
-    if (s < f) {
-      constexpr long long SEG = 8192;
-      const int segs = (int)((T + SEG - 1) / SEG);
-      STRP_TAKE(ctx, arena, prow, int32_t, (size_t)f);
-      STRP_TAKE(ctx, arena, ticket, unsigned int, 64);
-      STRP_TAKE(ctx, arena, partial, double, (size_t)(f - s) * segs * 6);
-      STRP_TRY(fill_zero(ctx, ticket, 256));
-      hipLaunchKernelGGL(pruned_list_kernel, dim3(1), dim3(1024), 0, ctx->stream, st->mask, f, prow);
-      pjob.ticket = ticket;
-      pjob.units = (unsigned int)(f - s) * (unsigned int)segs;
-      pjob.per_launch = (int)(pjob.units / (unsigned)(chol_launches(s) + chol_launches(d) - 2) + 1u);
-      pjob.rows = prow; pjob.nrows = f - s; pjob.segs = segs; pjob.seg_tokens = SEG;
-      pjob.Z = st->Z; pjob.A = st->A; pjob.Z0 = wanda ? nullptr : st->Z0;
-      pjob.lda = lda; pjob.T = T; pjob.alpha = alpha; pjob.beta = beta; pjob.partial = partial;
-      // a small pass (a module of a few hundred hidden units per kept one, or few tokens) is over before the chains
-      // have taken their first steps and only lengthens those: it is left to the drain (measured on a d = 768 module:
-      // 2 % slower with the ride, against 1-2 % faster from d = 2048 on)
-      if (pjob.units >= 65536u) ctx->cojob = &pjob;
-    }
+  double* finish_blk = nullptr;
+  if (fuse_pruned && s < f) {
+    constexpr long long SEG = 8192;
+    const int segs = (int)((T + SEG - 1) / SEG);
+    STRP_TAKE(ctx, arena, partial, double, (size_t)(f - s) * segs * 6);
+    STRP_TAKE(ctx, arena, blk, double, 2 * (size_t)((f - s + 255) / 256));
+    finish_blk = blk;
+    if (!prow_done) hipLaunchKernelGGL(pruned_list_kernel, dim3(1), dim3(1024), 0, ctx->stream, st->mask, f, prow);
+    pjob.ticket = ticket;
+    pjob.units = (unsigned int)(f - s) * (unsigned int)segs;
+    pjob.per_launch = (int)(pjob.units / (unsigned)(chol_launches(s) + chol_launches(d) - 2) + 1u);
+    pjob.rows = prow; pjob.nrows = f - s; pjob.segs = segs; pjob.seg_tokens = SEG;
+    pjob.Z = st->Z; pjob.A = st->A; pjob.Z0 = wanda ? nullptr : st->Z0;
+    pjob.lda = lda; pjob.T = T; pjob.alpha = alpha; pjob.beta = beta; pjob.partial = partial;
+    // a small pass (a module of a few hundred hidden units per kept one, or few tokens) is over before the chains
+    // have taken their first steps and only lengthens those: it is left to a kernel of its own (measured on a d = 768
+    // module: 2 % slower with the ride, against 1-2 % faster from d = 2048 on)
+    if (pjob.units >= 65536u) ctx->cojob = &pjob;
   }
+  // compact kept weights: written by the refits' last products when those run in this call, gathered otherwise
+  float* W2S = nullptr;
+  float* W1S = nullptr;
+  double* w2sq = nullptr;
+  double* w1sq = nullptr;
+  int nw2 = 0, nw1 = 0;
+  if (stages & (STRP_STAGE_AUPD | STRP_STAGE_OBJ)) {
+    nw2 = (stages & STRP_STAGE_REFIT2) ? weights_out_blocks(d, s) : gather_blocks(d, s);
+    STRP_TAKE(ctx, arena, w2s, float, (size_t)d * sp);
+    STRP_TAKE(ctx, arena, w2sq_, double, (size_t)nw2);
+    W2S = w2s;
+    w2sq = w2sq_;
+  }
+  if (stages & (STRP_STAGE_ZUPD | STRP_STAGE_OBJ)) {
+    nw1 = (stages & STRP_STAGE_REFIT1) ? weights_out_blocks(s, d) : gather_blocks(s, d);
+    STRP_TAKE(ctx, arena, w1s, float, (size_t)s * d);
+    STRP_TAKE(ctx, arena, w1sq_, double, (size_t)nw1);
+    W1S = w1s;
+    w1sq = w1sq_;
+  }
+  const WeightsOut w2out{STRP_SIDE_FC2, st->idx, st->W2, f, W2S, sp, W2S ? wmax + MAX_W2 : nullptr, w2sq};
+  const WeightsOut w1out{STRP_SIDE_FC1, st->idx, st->W1, d, W1S, d, W1S ? wmax + MAX_W1 : nullptr, w1sq};
   // ---- S1/S5: Gram of the kept A rows, fc2 refit -------------------------------------------
   if (stages & STRP_STAGE_REFIT2) {
     Arena a2 = arena;
@@ -1060,9 +1134,9 @@ strp_status strp_admm_step(strp_ctx* ctx, const strp_module_desc* desc, strp_mod
     STRP_TAKE(ctx, a2, Gd, double, (size_t)s * lds);
     PlaneOp Arow;
     STRP_TRY(make_t_planes(ctx, a2, st->A, STRP_F32, lda, st->idx, s, T, 0, npa, &Arow));
-    STRP_TRY(nt_product(ctx, a2, operand_for(ctx, STRP_PROD_GRAM, 0, Arow), operand_for(ctx, STRP_PROD_GRAM, 1, Arow), s, s, T, 1, nullptr,
-                        0, Gd, lds, nullptr, 0));
-    hipLaunchKernelGGL(add_diag_kernel, dim3(blocks_for(s)), dim3(256), 0, ctx->stream, Gd, lds, s, 0.0, sc + SC_LAM2);
+    ReduceP r = reduce_to(Gd, lds);
+    r.ridge_dev = sc + SC_LAM2;
+    STRP_TRY(nt_product(ctx, a2, operand_for(ctx, STRP_PROD_GRAM, 0, Arow), operand_for(ctx, STRP_PROD_GRAM, 1, Arow), s, s, T, 1, r));
     RefitIn ri;
     memset(&ri, 0, sizeof(ri));
     STRP_TAKE(ctx, a2, Ginv, double, (size_t)s * lds);
@@ -1070,21 +1144,21 @@ strp_status strp_admm_step(strp_ctx* ctx, const strp_module_desc* desc, strp_mod
     ri.Lhs = operand_for(ctx, STRP_PROD_RHS2, 0, cv.Yt);
     ri.Rhs = operand_for(ctx, STRP_PROD_RHS2, 1, Arow);
     ri.m = d; ri.n = s; ri.T = T;
-    double* sol = nullptr;
-    STRP_TRY(ridge_solve(ctx, a2, ri, &sol));
-    STRP_TRY(scatter_weights(ctx, sol, lds, STRP_SIDE_FC2, st->idx, s, st->W2, d, f));
+    STRP_TRY(ridge_solve(ctx, a2, ri, w2out));
+  } else if (W2S) {
+    STRP_TRY(gather_weights(ctx, w2out, d, s));
   }
-  // compact kept weights and their planes (shared by the stages below)
-  PlaneOp W2Sp, W1Sp;
+  // planes of the kept weights (shared by the stages below)
+  PlaneOp W2Sp, W2Tp, W1Sp;
   memset(&W2Sp, 0, sizeof(W2Sp));
+  memset(&W2Tp, 0, sizeof(W2Tp));
   memset(&W1Sp, 0, sizeof(W1Sp));
-  float* W2S = nullptr;
-  float* W1S = nullptr;
-  if (stages & (STRP_STAGE_AUPD | STRP_STAGE_OBJ)) {
-    STRP_TAKE(ctx, arena, w2s, float, (size_t)d * sp);
-    W2S = w2s;
-    hipLaunchKernelGGL(gather_cols_kernel, dim3(blocks_for((long long)d * sp)), dim3(256), 0, ctx->stream, st->W2, d, f, st->idx, s, W2S, sp);
-    STRP_TRY(make_weight_planes(ctx, arena, W2S, SRC_F32, sp, d, s, 0, npa, &W2Sp));
+  if (W2S) {
+    SplitJob jobs[2];
+    STRP_TRY(weight_planes(ctx, arena, W2S, SRC_F32, sp, d, s, 0, npa, wmax + MAX_W2, &W2Sp, &jobs[0]));
+    const bool both = (stages & STRP_STAGE_AUPD) != 0;
+    if (both) STRP_TRY(weight_planes(ctx, arena, W2S, SRC_F32, sp, s, d, 1, npa, wmax + MAX_W2, &W2Tp, &jobs[1]));
+    STRP_TRY(split_small(ctx, jobs, both ? 2 : 1));
   }
   // ---- a-update, part 1: B = W^T M^-1 with M = (beta/alpha) I + W W^T, W = W2[:, S] -------------------------
   // Needs only the refitted W2.  Its buffers come from the base arena and stay until the step ends.
@@ -1096,6 +1170,11 @@ strp_status strp_admm_step(strp_ctx* ctx, const strp_module_desc* desc, strp_mod
   // W A_S) and two d x d matrices.  One fp16 plane of E is ample for a sum reported to 1e-3.
   const bool term1_identity = (stages & STRP_STAGE_AUPD) && (stages & STRP_STAGE_OBJ);
   float* M2f = nullptr;
+  double* red_t1 = nullptr;
+  if (term1_identity) {
+    STRP_TAKE(ctx, arena, rt1, double, (size_t)reduce_blocks(d, d));
+    red_t1 = rt1;
+  }
   if (stages & STRP_STAGE_AUPD) {
     STRP_TAKE(ctx, arena, Md, double, (size_t)d * d);
     STRP_TAKE(ctx, arena, Linv, double, (size_t)d * d);
@@ -1106,40 +1185,39 @@ strp_status strp_admm_step(strp_ctx* ctx, const strp_module_desc* desc, strp_mod
     }
     const size_t al = 255;
     const size_t cbytes = ((nt_partial_elems(d, d, sp, 1) * 4 + al) & ~al) + (((size_t)((d + NB - 1) / NB) * NB * NB * 8 + al) & ~al) +
-                          (512 + 2 * ((plane_elems(s, d) * 2 + al) & ~al)) +
-                          (512 + 2 * ((plane_elems(d, d) * 2 + al) & ~al)) + 4096;
+                          
+                          2 * ((plane_elems(d, d) * 2 + al) & ~al) + 4096;
     STRP_TAKE(ctx, arena, cblock, char, cbytes);
     Arena a2(cblock, cbytes);
-    STRP_TRY(nt_product(ctx, a2, W2Sp, W2Sp, d, d, sp, 1, nullptr, 0, Md, d, nullptr, 0));
-    hipLaunchKernelGGL(add_diag_kernel, dim3(blocks_for(d)), dim3(256), 0, ctx->stream, Md, (long long)d, d, params->beta / params->alpha, (const double*)nullptr);
+    ReduceP r = reduce_to(Md, d);
+    r.ridge = params->beta / params->alpha;
+    STRP_TRY(nt_product(ctx, a2, W2Sp, W2Sp, d, d, sp, 1, r));
     STRP_TRY(factor_and_invert(ctx, a2, Md, d, Linv, d));
     // M is well conditioned (its spectrum lies in [beta/alpha, beta/alpha + |W|^2]): form M^-1 = Linv^T Linv
     // (lower half, fp64) and B = W^T M^-1 on the fp16-split matrix cores instead of a third fp64 solve
-    STRP_TRY(fill_zero(ctx, Md, sizeof(double) * (size_t)d * d));
-    STRP_TRY(gram_of_inverse(ctx, Linv, d, d, Md, d));
-    {
-      Arena a3 = a2;
-      PlaneOp Wt, Mi;
-      STRP_TRY(make_weight_planes(ctx, a3, W2S, SRC_F32, sp, s, d, 1, npa, &Wt));
-      STRP_TRY(make_weight_planes(ctx, a3, Md, SRC_F64, d, d, d, 2, npa, &Mi));
-      GemmP p;
-      memset(&p, 0, sizeof(p));
-      p.P = Wt; p.Q = Mi;
-      p.M = s; p.N = d; p.K = d;
-      p.epi = EPI_STORE; p.out = Bf; p.ldo = d;
-      gemm_plan_tiles(p, 1);
-      STRP_TRY(launch_gemm(ctx, p));
-      if (term1_identity) {   // M^-2 for the first objective term (see the a-update below)
-        GemmP q;
-        memset(&q, 0, sizeof(q));
-        q.P = Mi; q.Q = Mi;
-        q.M = d; q.N = d; q.K = d;
-        q.epi = EPI_STORE; q.out = M2f; q.ldo = d;
-        gemm_plan_tiles(q, 1);
-        STRP_TRY(launch_gemm(ctx, q));
-      }
+    STRP_TRY(gram_of_inverse(ctx, Linv, d, d, Md, d, wmax + MAX_MI));
+    SplitJob job;
+    PlaneOp Mi;
+    STRP_TRY(weight_planes(ctx, a2, Md, SRC_F64, d, d, d, 2, npa, wmax + MAX_MI, &Mi, &job));
+    STRP_TRY(split_small(ctx, &job, 1));
+    GemmP p;
+    memset(&p, 0, sizeof(p));
+    p.P = W2Tp; p.Q = Mi;
+    p.M = s; p.N = d; p.K = d;
+    p.epi = EPI_STORE; p.out = Bf; p.ldo = d; p.maxbits = wmax + MAX_B;
+    gemm_plan_tiles(p, 1);
+    STRP_TRY(launch_gemm(ctx, p));
+    if (term1_identity) {   // M^-2 for the first objective term (see the a-update below)
+      GemmP q;
+      memset(&q, 0, sizeof(q));
+      q.P = Mi; q.Q = Mi;
+      q.M = d; q.N = d; q.K = d;
+      q.epi = EPI_STORE; q.out = M2f; q.ldo = d;
+      gemm_plan_tiles(q, 1);
+      STRP_TRY(launch_gemm(ctx, q));
     }
-    STRP_TRY(make_weight_planes(ctx, arena, Bf, SRC_F32, d, s, d, 0, npa, &Bp));
+    STRP_TRY(weight_planes(ctx, arena, Bf, SRC_F32, d, s, d, 0, npa, wmax + MAX_B, &Bp, &job));
+    STRP_TRY(split_small(ctx, &job, 1));
   }
   // Z_S is needed by tokens (fc1 refit) and, with relu, by channels (a-update): when both stages run, one pass over
   // the kept rows of Z writes both sets of planes; the second set stays in the base arena until the a-update.
@@ -1177,32 +1255,31 @@ strp_status strp_admm_step(strp_ctx* ctx, const strp_module_desc* desc, strp_mod
     ri.Lhs = operand_for(ctx, STRP_PROD_RHS1, 0, Zrow);
     ri.Rhs = operand_for(ctx, STRP_PROD_RHS1, 1, cv.Xt);
     ri.m = s; ri.n = d; ri.T = T;
-    double* sol = nullptr;
-    STRP_TRY(ridge_solve(ctx, a2, ri, &sol));
-    STRP_TRY(scatter_weights(ctx, sol, d, STRP_SIDE_FC1, st->idx, s, st->W1, f, d));
+    STRP_TRY(ridge_solve(ctx, a2, ri, w1out));
+  } else if (W1S) {
+    STRP_TRY(gather_weights(ctx, w1out, s, d));
   }
-  if (stages & (STRP_STAGE_ZUPD | STRP_STAGE_OBJ)) {
-    STRP_TAKE(ctx, arena, w1s, float, (size_t)s * d);
-    W1S = w1s;
-    hipLaunchKernelGGL(gather_rows_kernel, dim3(blocks_for((long long)s * d)), dim3(256), 0, ctx->stream, st->W1, d, st->idx, s, W1S, (long long)d);
-    STRP_TRY(make_weight_planes(ctx, arena, W1S, SRC_F32, d, s, d, 0, npa, &W1Sp));
+  if (W1S) {
+    SplitJob job;
+    STRP_TRY(weight_planes(ctx, arena, W1S, SRC_F32, d, s, d, 0, npa, wmax + MAX_W1, &W1Sp, &job));
+    STRP_TRY(split_small(ctx, &job, 1));
   }
 
   // scoring sums of the kept rows, collected by the two epilogues that write those rows (64-column strips, fp32)
   const int rs_slots = (int)((T + 63) / 64);
   float* rsA = nullptr;
   float* rsZ = nullptr;
-  double* rs_chunks = nullptr;
   if (fuse_pruned) {
     STRP_TAKE(ctx, arena, rsa_, float, (size_t)(wanda ? 1 : 2) * rs_slots * s);
-    STRP_TAKE(ctx, arena, rsc_, double, rowsum_scratch_bytes(2, s) / sizeof(double));
     rsA = rsa_;
-    rs_chunks = rsc_;
     if (!wanda) {
       STRP_TAKE(ctx, arena, rsz_, float, (size_t)rs_slots * s);
       rsZ = rsz_;
     }
   }
+  FinishP fin;
+  memset(&fin, 0, sizeof(fin));
+  fin.sc = sc;
   // ---- S7: a-update in residual (Woodbury) form ------------------------------------------------
   //   A_S = relu(Z_S) + W^T M^-1 (Y - W relu(Z_S)),  M = (beta/alpha) I + W W^T,  W = W2[:, S];  A_j = relu(Z_j) for pruned j
   if (stages & STRP_STAGE_AUPD) {
@@ -1231,14 +1308,13 @@ strp_status strp_admm_step(strp_ctx* ctx, const strp_module_desc* desc, strp_mod
     if (term1_identity) {   // (alpha/T) |Y - W A_S|^2 = (alpha/T) (beta/alpha)^2 <M^-2, E E^T>
       Arena a3 = a2;
       STRP_TAKE(ctx, a3, eth, unsigned short, plane_elems(d, T));
-      STRP_TAKE(ctx, a3, Sd, double, (size_t)d * d);
-      STRP_TAKE(ctx, a3, red, double, 2 * 1024);
       STRP_TRY(plane_c_to_t(ctx, ekh, eth, d, T));
       const PlaneOp Et{eth, nullptr, plane_kg(T), (int)((d + 127) / 128), nullptr};
-      STRP_TRY(nt_product(ctx, a3, Et, Et, d, d, T, 1, nullptr, 0, Sd, d, nullptr, 0));
-      hipLaunchKernelGGL(dot_f32_f64_kernel, dim3(1024), dim3(256), 0, ctx->stream, M2f, Sd, (long long)d * d, red);
+      ReduceP r = reduce_to(nullptr, 0);
+      r.dot = M2f; r.red = red_t1;
+      STRP_TRY(nt_product(ctx, a3, Et, Et, d, d, T, 1, r));
       const double c = params->beta / params->alpha;
-      STRP_TRY(launch_block_sum(ctx, red, 1024, sc + SC_T1, nullptr, params->alpha / (double)T * c * c, 1.0));
+      fin.do_1 = 1; fin.red_1 = red_t1; fin.n1 = reduce_blocks(d, d); fin.stride1 = 1; fin.c1 = params->alpha / (double)T * c * c;
     }
     {  // A_S = relu(Z_S) + B E
       GemmP p;
@@ -1250,7 +1326,7 @@ strp_status strp_admm_step(strp_ctx* ctx, const strp_module_desc* desc, strp_mod
       p.rs_out = rsA; p.rs_z0 = (rsA && !wanda) ? st->Z0 : nullptr; p.rs_slots = rs_slots;
       gemm_plan_tiles(p, 1);
       STRP_TRY(launch_gemm(ctx, p));
-      if (rsA) STRP_TRY(launch_rowsum_reduce(ctx, rsA, wanda ? 1 : 2, rs_slots, s, st->idx, cv.rowsums, f, 0, 1, rs_chunks));
+      if (rsA) STRP_TRY(launch_rowsum_reduce(ctx, rsA, wanda ? 1 : 2, rs_slots, s, st->idx, cv.rowsums, f, 0, 1));
     }
     if (!fuse_pruned) {
       ProfScope ps(ctx, "pruned_rows_a", 0.0, 8.0 * (double)(f - s) * (double)T);
@@ -1261,7 +1337,6 @@ strp_status strp_admm_step(strp_ctx* ctx, const strp_module_desc* desc, strp_mod
   // ---- S8 (+ objective terms 2, 3): z-update fused on Z1 = W1 X --------------------------------
   const bool zupd = (stages & STRP_STAGE_ZUPD) != 0;
   if (zupd || (stages & STRP_STAGE_OBJ)) {
-    Arena a2 = arena;
     GemmP p;
     memset(&p, 0, sizeof(p));
     p.P = operand_for(ctx, STRP_PROD_ZUPD, 0, W1Sp);
@@ -1272,67 +1347,66 @@ strp_status strp_admm_step(strp_ctx* ctx, const strp_module_desc* desc, strp_mod
     p.rs_out = (zupd && rsZ) ? rsZ : nullptr; p.rs_z0 = p.rs_out ? st->Z0 : nullptr; p.rs_slots = rs_slots;
     gemm_plan_tiles(p, 1);
     const int nb = gemm_grid_blocks(p);
-    STRP_TAKE(ctx, a2, red, double, 2 * (size_t)(nb > f ? nb : f));
+    STRP_TAKE(ctx, arena, red, double, 2 * (size_t)nb);
     p.red = red;
     STRP_TRY(launch_gemm(ctx, p));
-    STRP_TRY(launch_block_sum(ctx, red, nb, sc + SC_TMP0, sc + SC_TMP1, 1.0, 1.0));
-    if (p.rs_out) STRP_TRY(launch_rowsum_reduce(ctx, rsZ, 1, rs_slots, s, st->idx, cv.rowsums, f, 2, 2, rs_chunks));
+    fin.do_z = 1; fin.red_z = red; fin.nz = nb; fin.c2 = params->beta / (double)T; fin.c3 = params->alpha / (double)T;
+    if (p.rs_out) STRP_TRY(launch_rowsum_reduce(ctx, rsZ, 1, rs_slots, s, st->idx, cv.rowsums, f, 2, 2));
     if (fuse_pruned) {
-      // what the factorisation chains' spare workgroups left of the pruned rows' pass, then the rows' sums
-      ctx->cojob = nullptr;
+      // what the factorisation chains' spare workgroups left of the pruned rows' pass; the rows' sums are added at the end
       if (pjob.ticket) {
-        {
-          ProfScope ps(ctx, "pruned_rows_drain", 0.0, 0.0);
-          CoJob dj = pjob;
-          dj.take = 4;
-          hipLaunchKernelGGL(cojob_drain_kernel, dim3(2048), dim3(256), 0, ctx->stream, dj);
-        }
-        hipLaunchKernelGGL(cojob_finish_kernel, dim3((pjob.nrows + 255) / 256), dim3(256), 0, ctx->stream, pjob, red_pruned, cv.rowsums, f);
+        ProfScope ps(ctx, "pruned_rows_drain", 0.0, 0.0);
+        CoJob dj = pjob;
+        dj.take = 4;
+        if (ctx->cojob) hipLaunchKernelGGL(cojob_drain_kernel, dim3(2048), dim3(256), 0, ctx->stream, dj);
+        else hipLaunchKernelGGL(cojob_units_kernel, dim3(pjob.units), dim3(256), 0, ctx->stream, dj);
+        ctx->cojob = nullptr;
+        fin.rows = prow; fin.partial = pjob.partial; fin.nrows = pjob.nrows; fin.segs = pjob.segs; fin.f = f; fin.z0 = pjob.Z0 != nullptr;
+        fin.rowsums = cv.rowsums; fin.blk = finish_blk; fin.ticket = wmax + 48;
       }
-      // every row's sums are now in place: the kept rows' from the two epilogues, the pruned rows' from this pass
+      // every row's sums are then in place: the kept rows' from the two epilogues, the pruned rows' from this pass
       // (which also rewrites their sum Z0^2; the kept rows' is only there if it was streamed before)
       st->sums_cached = (st->sums_cached & SUMS_V) | SUMS_G | (wanda ? 0 : SUMS_EU);
     } else {
+      STRP_TAKE(ctx, arena, redp, double, 2 * (size_t)f);
       ProfScope ps(ctx, "pruned_rows_z", 0.0, 8.0 * (double)(f - s) * (double)T);
       hipLaunchKernelGGL(pruned_rows_kernel, dim3(f), dim3(256), 0, ctx->stream, st->mask, st->Z, st->A, lda, T, 1, alpha, beta,
-                         zupd ? 1 : 0, red, (const float*)nullptr, (double*)nullptr, f);
+                         zupd ? 1 : 0, redp, (const float*)nullptr, (double*)nullptr, f);
+      fin.red_p = redp; fin.np = f;
     }
-    STRP_TRY(launch_block_sum(ctx, fuse_pruned ? red_pruned : red, f, sc + SC_TMP2, sc + SC_TMP3, 1.0, 1.0));
-    hipLaunchKernelGGL(axpby_scalar_kernel, dim3(1), dim3(1), 0, ctx->stream, sc, (int)SC_T2, params->beta / (double)T, (int)SC_TMP0, params->beta / (double)T, (int)SC_TMP2);
-    hipLaunchKernelGGL(axpby_scalar_kernel, dim3(1), dim3(1), 0, ctx->stream, sc, (int)SC_T3, params->alpha / (double)T, (int)SC_TMP1, params->alpha / (double)T, (int)SC_TMP3);
   }
   // ---- S9: objective term 1 (one fp16 plane per operand is ample for a 1e-3 sum) and ridge terms ----
   if (stages & STRP_STAGE_OBJ) {
-    Arena a2 = arena;
-    STRP_TAKE(ctx, a2, red, double, 2 * 1024);
     if (!term1_identity) {   // A is whatever the caller left: the product itself
-      Arena a3 = a2;
+      Arena a3 = arena;
       PlaneOp Ak8;
-      STRP_TRY(make_c_planes(ctx, a3, st->A, STRP_F32, lda, st->idx, s, T, 0, 1, &Ak8));
       GemmP p;
       memset(&p, 0, sizeof(p));
-      p.P = W2Sp; p.P.lo = nullptr; p.Q = Ak8;
+      p.P = W2Sp; p.P.lo = nullptr;
       p.M = d; p.N = (int)T; p.K = s;
       p.epi = EPI_RESID; p.Yin = st->Y; p.ldy = lda;
       gemm_plan_tiles(p, 1);
       const int nb = gemm_grid_blocks(p);
       STRP_TAKE(ctx, a3, redg, double, 2 * (size_t)nb);
+      STRP_TRY(make_c_planes(ctx, a3, st->A, STRP_F32, lda, st->idx, s, T, 0, 1, &Ak8));
+      p.Q = Ak8;
       p.red = redg;
       STRP_TRY(launch_gemm(ctx, p));
-      STRP_TRY(launch_block_sum(ctx, redg, nb, sc + SC_T1, nullptr, params->alpha / (double)T, 1.0));
+      fin.do_1 = 1; fin.red_1 = redg; fin.n1 = nb; fin.stride1 = 2; fin.c1 = params->alpha / (double)T;
     }
-    hipLaunchKernelGGL(sumsq_kernel, dim3(1024), dim3(256), 0, ctx->stream, W2S, (long long)d * sp, red);
-    STRP_TRY(launch_block_sum(ctx, red, 1024, sc + SC_W2SQ, nullptr, 1.0, 1.0));
-    hipLaunchKernelGGL(sumsq_kernel, dim3(1024), dim3(256), 0, ctx->stream, W1S, (long long)s * d, red);
-    STRP_TRY(launch_block_sum(ctx, red, 1024, sc + SC_W1SQ, nullptr, 1.0, 1.0));
+    fin.do_w = 1; fin.w2 = w2sq; fin.nw2 = nw2; fin.w1 = w1sq; fin.nw1 = nw1;
   }
+  if (report_host) {
+    fin.host = (double*)ctx->pinned;
+    fin.status = ctx->status_dev;
+  }
+  if (fin.nrows || fin.do_z || fin.do_1 || fin.do_w || fin.host)
+    hipLaunchKernelGGL(step_finish_kernel, dim3(fin.nrows ? (fin.nrows + 255) / 256 : 1), dim3(256), 0, ctx->stream, fin);
   STRP_HIP(ctx, hipGetLastError());
   st->iter += 1;
 
   if (report_host) {
     double* h = (double*)ctx->pinned;
-    STRP_HIP(ctx, hipMemcpyAsync(h, sc, SC_COUNT * sizeof(double), hipMemcpyDeviceToHost, ctx->stream));
-    STRP_HIP(ctx, hipMemcpyAsync(h + SC_COUNT, ctx->status_dev, sizeof(int32_t), hipMemcpyDeviceToHost, ctx->stream));
     STRP_HIP(ctx, hipStreamSynchronize(ctx->stream));
     memset(report_host, 0, sizeof(*report_host));
     report_host->lam1 = h[SC_LAM1];

@@ -85,17 +85,24 @@ struct Arena {
 //   offset(k, r) = (((r / 128) * kg + k / 8) * 128 + r % 128) * 8 + k % 8
 // k = contraction index, r = output row (P) or output column (Q); npan panels of 128 rows, kg k-groups of 8
 // (kg = plane_kg(K): a multiple of four, padding zero).
-// scale (device, optional): the planes hold x * scale; the GEMM epilogue divides it out.
+// maxbits (device, optional): the bits of max|x|; the planes hold x * scale_of_max(*maxbits), the GEMM epilogue divides it out.
 struct PlaneOp {
   const unsigned short* hi;
   const unsigned short* lo;
   long long kg;
   int npan;
-  const float* scale;
+  const unsigned int* maxbits;
 };
+// Power of two that brings a maximum (given by its bits) into [2^11, 2^12): keeps fp16 hi far from overflow and lo out of
+// the subnormals.  1 for zero, infinity and NaN.
+__device__ __forceinline__ float scale_of_max(unsigned int bits) {
+  if (bits == 0u || bits > 0x7f61b1e6u) return 1.0f;       // above 3e38
+  const unsigned int e = 265u - (bits >> 23);              // max = q 2^(E - 126), q in [1/2, 1): 2^(12 - (E - 126))
+  return __builtin_bit_cast(float, (e > 254u ? 254u : e) << 23);
+}
 // k-groups allocated for a contraction of length K: a multiple of four, the pad groups zero-filled (the pipelined
 // kernel moves two k-groups per stage and multiplies four per matrix-core instruction, both without tail logic)
-static inline long long plane_kg(long long K) { return (((K + 7) / 8) + 3) & ~3LL; }
+__host__ __device__ static inline long long plane_kg(long long K) { return (((K + 7) / 8) + 3) & ~3LL; }
 static inline size_t plane_elems(long long rows, long long K) {
   return (size_t)((rows + 127) / 128) * (size_t)plane_kg(K) * 1024;
 }
@@ -128,6 +135,7 @@ struct GemmP {
   float alpha, beta;
   double* red;         // per-block partial sums [gridDim.x][2] (INITZ, RESID, ZUPD)
   int write_out;       // ZUPD: 1 = update Z, 0 = only accumulate the objective sums
+  unsigned int* maxbits;  // STORE, optional: atomic maximum of the bits of |C|
   unsigned short* k8_hi;  // optional operand planes of the produced values with k = output row, r = output column
   unsigned short* k8_lo;  //   (STORE: C, INITZ: relu(C), RESID: Y - C; not offered by AUPD / ZUPD); k8_kg = M / 8 groups, ceil(N/128) panels
   long long k8_kg;
@@ -144,14 +152,21 @@ int gemm_grid_blocks(const GemmP& p);
 void gemm_plan_tiles(GemmP& p, int want_splits);
 
 // Sum split-K partials in fp64; optional symmetric completion from the computed lower half.
-// outf / outd (either may be null): [M x ldo]; accumulate adds to outf's previous content.
-strp_status launch_splitk_reduce(strp_ctx* ctx, const float* part, int splits, int M, int N, int triangle,
-                                 float* outf, long long ldof, double* outd, long long ldod, double* diag,
-                                 int accumulate);
-// Sum per-block fp64 partials red[nblocks][2] into dst[0], dst[1] (fixed order).
-strp_status launch_block_sum(strp_ctx* ctx, const double* red, int nblocks, double* dst0, double* dst1,
-                             double scale0, double scale1);
-
+// outf / outd (either may be null): [M x ldo]; accumulate adds to outf's previous content; ridge (or *ridge_dev) is added
+// to outd's diagonal.  dot (symmetric products only, instead of any output): [M x N] fp32, red[workgroup] = its share of
+// <dot, C>; reduce_blocks(M, N) workgroups.
+struct ReduceP {
+  const float* part;
+  int splits, M, N, triangle;
+  float* outf; long long ldof;
+  double* outd; long long ldod;
+  double* diag;
+  int accumulate;
+  double ridge; const double* ridge_dev;
+  const float* dot; double* red;
+};
+strp_status launch_splitk_reduce(strp_ctx* ctx, const ReduceP& r);
+static inline int reduce_blocks(int M, int N) { return ((M + 63) / 64) * ((N + 63) / 64); }
 // fp32 / bf16 activation rows (optionally gathered by idx) -> fp16 planes; any output pair may be null.
 //   t_* : contraction over tokens   (k = token,   r = row):   plane_elems(rows, T)
 //   c_* : contraction over channels (k = row,     r = token): plane_elems(T, rows)
@@ -161,11 +176,25 @@ strp_status split_act(strp_ctx* ctx, const void* src, int src_dtype, long long l
 // One fp16 plane of a [C x T] quantity with k = channel, r = token (plane_elems(T, C)) -> the plane with k = token,
 // r = channel (plane_elems(C, T)); padding tokens zero.
 strp_status plane_c_to_t(strp_ctx* ctx, const unsigned short* src, unsigned short* dst, int C, long long T);
-// Small matrix (weights) -> planes with k = column, r = row: plane_elems(rows, cols); src_kind = SRC_*.
-strp_status split_small(strp_ctx* ctx, const void* src, int src_kind, long long lds, int rows, int cols, int transpose,
-                        const float* scale_dev, unsigned short* hi, unsigned short* lo);
-// *scale_out = power of two that brings max|src| into [2^11, 2^12).
-strp_status weight_scale(strp_ctx* ctx, const void* src, int src_kind, long long lds, int rows, int cols, float* scale_out);
+// Small matrices (weights) -> planes with k = column, r = row: plane_elems(rows, cols); kind = SRC_*.
+// transpose: 1 = the source is stored transposed, 2 = symmetric, only its lower triangle is valid.
+struct SplitJob {
+  const void* src;
+  long long lds;
+  int kind, rows, cols, transpose;
+  const unsigned int* maxbits;
+  unsigned short* hi;
+  unsigned short* lo;
+};
+strp_status split_small(strp_ctx* ctx, const SplitJob* jobs, int n);      // n <= 2, one launch
+// *maxbits[i] = max(*maxbits[i], bits of max|src_i|) for fp32 / bf16 matrices; n <= 2, one launch
+struct MaxJob {
+  const void* src;
+  long long lds;
+  int kind, rows, cols;
+  unsigned int* maxbits;
+};
+strp_status abs_max(strp_ctx* ctx, const MaxJob* jobs, int n);
 
 // ---- fp64 dense kernels (dense_f64.hip) ---------------------------------------------------
 constexpr int NB = 64;  // block order of the factorisation
@@ -176,10 +205,26 @@ static inline long long f64_ld(long long n) { return (n + 7) & ~7LL; }
 // 16-byte aligned.  A pivot that is not positive sets ENOTPD in status (device word).
 strp_status chol_inverse(strp_ctx* ctx, double* A, int n, long long ld, double* sub, double* Linv, long long ldv, int32_t* status);
 int chol_launches(int n);   // launches of chol_inverse that can carry spare workgroups, and one
-// In place X <- X (L L^T)^-1 = (X Linv^T) Linv for X [m x n] (ldx); tmp: m x ldx scratch.
-strp_status apply_inverse_right(strp_ctx* ctx, const double* Linv, int n, long long ldl, double* X, int m, long long ldx, double* tmp);
-// Tiles on or below the diagonal of S [n x n, lds] = Linv^T Linv.
-strp_status gram_of_inverse(strp_ctx* ctx, const double* Linv, int n, long long ldl, double* S, long long lds);
+// X (L L^T)^-1 = (X Linv^T) Linv for X [m x n] (ldx), as refitted weights; tmp: m x ldx scratch.
+//   FC2: W[i, idx[j]] = result[i, j] (m rows of W);  FC1: W[idx[i], j] = result[i, j];  other entries of W are not written.
+//   Wc (optional): the result itself, [m x ldc]; maxbits (optional): atomic maximum of the bits of its magnitudes; sumsq
+//   (optional): [weights_out_blocks(m, n)] sums of squares.
+struct WeightsOut {
+  int side;
+  const int32_t* idx;
+  float* W; long long ldw;
+  float* Wc; long long ldc;
+  unsigned int* maxbits;
+  double* sumsq;
+};
+strp_status apply_inverse_right(strp_ctx* ctx, const double* Linv, int n, long long ldl, const double* X, int m, long long ldx, double* tmp,
+                                const WeightsOut& out);
+int weights_out_blocks(int m, int n);
+// The compact weights Wc [m x ldc] of an earlier refit out of W, with the same by-products (gather_blocks(m, n) sums).
+strp_status gather_weights(strp_ctx* ctx, const WeightsOut& io, int m, int n);
+int gather_blocks(int m, int n);
+// Tiles on or below the diagonal of S [n x n, lds] = Linv^T Linv; maxbits: atomic maximum of the bits of its magnitudes.
+strp_status gram_of_inverse(strp_ctx* ctx, const double* Linv, int n, long long ldl, double* S, long long lds, unsigned int* maxbits);
 // dst [n x n, ldd] = src [n x n, lds]
 strp_status copy_f64(strp_ctx* ctx, const double* src, long long lds, double* dst, long long ldd, int n);
 // Ad[i*ld+j] = (double)Af[i*ldf+j] + (i==j ? lam (or *lam_dev if non-null) : 0)
@@ -189,11 +234,9 @@ strp_status f32_to_f64_ridge(strp_ctx* ctx, const float* Af, long long ldf, doub
 // ---- reductions, scores, allocation, select (score_select.hip) ------------------------------
 strp_status launch_row_sums(strp_ctx* ctx, const void* A, int a_dtype, const float* Z, const float* Z0,
                             long long ld, long long T, int rows, int mode, double* sums /*[4][rows]*/);
-// part[nq][slots][M] fp32 strip sums written by the AUPD / ZUPD epilogues -> rowsums[qdst * f + idx[m]] (fp64);
-// chunk_sums: rowsum_scratch_bytes(nq, M) bytes of scratch.
+// part[nq][slots][M] fp32 strip sums written by the AUPD / ZUPD epilogues -> rowsums[qdst * f + idx[m]] (fp64).
 strp_status launch_rowsum_reduce(strp_ctx* ctx, const float* part, int nq, int slots, int M, const int32_t* idx, double* rowsums, int f,
-                                 int qdst0, int qdst1, double* chunk_sums);
-size_t rowsum_scratch_bytes(int nq, int M);
+                                 int qdst0, int qdst1);
 strp_status launch_colnorm2(strp_ctx* ctx, const void* W, int w_dtype, int rows, int cols, long long ldw,
                             double* n2);
 strp_status launch_unit_scores(strp_ctx* ctx, const double* sums, const double* n2, int n_channels, int group,
@@ -207,14 +250,33 @@ size_t weight_energy_scratch_bytes();
 strp_status launch_topk(strp_ctx* ctx, const float* score, int n, int k, int group, uint8_t* mask, int32_t* idx,
                         float* tau, void* scratch, size_t scratch_bytes);
 size_t topk_scratch_bytes(int n);
+// One module's selection in one launch: unit scores from the token sums (layout of launch_row_sums), their mean, and the k
+// best of them; rest (optional): the n - k other indices, ascending.
+strp_status launch_select(strp_ctx* ctx, const double* sums, const double* n2, int mode, int n, int k, float* score, double* energy_out,
+                          uint8_t* mask, int32_t* idx, float* tau, int32_t* rest);
 
-// ---- small elementwise helpers (dense_f64.hip) -----------------------------------------------
-// dst (fp32, [rows x ldd]) = src (fp64, [rows x lds]) cast; pad columns [cols, ldd) zero-filled.
-strp_status cast_f64_f32(strp_ctx* ctx, const double* src, long long lds, float* dst, long long ldd, int rows,
-                         int cols);
-// W[out x in] dense fp32: scatter compact solution rows/columns by idx, everything else zero.
-strp_status scatter_weights(strp_ctx* ctx, const double* sol, long long lds, int side, const int32_t* idx,
-                            int s, float* W, int out, int in);
+// ---- small helpers -----------------------------------------------------------------------------
 strp_status fill_zero(strp_ctx* ctx, void* ptr, size_t bytes);
+struct FillRange {
+  void* ptr;
+  size_t bytes;      // multiple of 4
+};
+strp_status fill_zero(strp_ctx* ctx, const FillRange* ranges, int n);     // n <= 5, one launch
+
+// "The last workgroup does the rest": true in every thread of the last workgroup of the grid to get here.  What the
+// workgroups hand to it goes through agent-scope atomics (agent_put / agent_get / atomicAdd), which act at the level all
+// XCDs share, so it is enough that they have completed before the counter moves: an agent-scope fence would
+// write back and invalidate the XCD's L2 from every workgroup, which took 45 of a launch's 50 us.
+template <typename T>
+__device__ __forceinline__ void agent_put(T* p, T v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+template <typename T>
+__device__ __forceinline__ T agent_get(const T* p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+__device__ __forceinline__ bool last_block(unsigned int* done, unsigned int* flag) {
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  __syncthreads();
+  if (threadIdx.x == 0) *flag = atomicAdd(done, 1u) + 1u == gridDim.x;
+  __syncthreads();
+  return *flag != 0;
+}
 
 }  // namespace strp
