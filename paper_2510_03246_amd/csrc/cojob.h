@@ -1,11 +1,11 @@
-// A streaming pass that rides along with other kernels.
+// A streaming pass that rides along with another kernel.
 //
-// The factorisation chains of an ADMM iteration are some hundred short launches (a 64-column Cholesky step is a panel
-// kernel of at most 77 workgroups and an update of a few hundred) that leave most of the chip idle, and kernels of two
-// streams do not share the chip usefully on this hardware.  Workgroups of ONE launch do: so a pass that is bound by
-// HBM and independent of the chain is cut into units, and the chain's kernels are launched with spare workgroups that
-// take a few units each from a device counter and exit.  Whatever is left when the chain ends is drained by a kernel
-// of its own.  No workgroup ever waits for another one: the counter only hands out unit numbers.
+// A factorisation chain begins with one workgroup that factors one diagonal tile while the chip is idle, and kernels of
+// two streams do not share the chip usefully on this hardware; workgroups of ONE launch do.  So a pass that is bound by
+// HBM and independent of the chain is cut into units, and the chain's first launch carries workgroups that stream them.
+// Spread over all launches of the chains instead it was slower: every launch then ended with its own ramp of the memory
+// system (n = 2458 and 2048 with a pass of 15 GB: 5.7 ms for 73 launches of 80 us, against 1.5 ms for the chains alone
+// and 2.7 ms for the pass at its 5.8 TB/s).
 //
 // The one pass built this way is the fused a/z update of the PRUNED rows (Appendix A.1 with W2[:, j] = 0, W1[j, :] = 0:
 // A_j = relu(Z_j), then the z rule with z1 = 0), which touches only rows outside S and can therefore run at any time
@@ -19,10 +19,7 @@
 namespace strp {
 
 struct CoJob {
-  unsigned int* ticket;    // next unit to hand out (device counter, zero when the job starts); null = no job
-  unsigned int units;      // nrows * segs
-  int take;                // units a spare workgroup takes before it exits
-  int per_launch;          // units one launch of the factorisation chains should take
+  unsigned int units;      // nrows * segs; 0 = no job
   const int32_t* rows;     // the pruned rows, ascending
   int nrows, segs;
   long long seg_tokens;    // tokens per unit (a multiple of 4)
@@ -84,7 +81,7 @@ __device__ __forceinline__ void cojob_unit(const CoJob& job, unsigned int u) {
   };
   const float4 zero4 = make_float4(0.f, 0.f, 0.f, 0.f);
   // eight independent 16-byte groups per thread and trip (one trip covers 8192 tokens), all loads of a trip issued
-  // before its first store: a spare workgroup is one of only two or four on its CU, so the bytes in flight per
+  // before its first store: a workgroup is one of only two on its CU, so the bytes in flight per
   // workgroup are what sets the rate
   constexpr int NG = 8;
   for (long long c = v0 + tid; c < v1; c += 256 * NG) {
@@ -138,17 +135,9 @@ __device__ __forceinline__ void cojob_unit(const CoJob& job, unsigned int u) {
   __syncthreads();
 }
 
-// A spare workgroup (256 threads, all of them call this) takes up to job.take units and returns.
-__device__ __forceinline__ void cojob_help(const CoJob& job) {
-  __shared__ unsigned int cj_u0;
-  if (!job.ticket) return;
-  if (threadIdx.x == 0) cj_u0 = atomicAdd(job.ticket, (unsigned int)job.take);
-  __syncthreads();
-  const unsigned int u0 = cj_u0;
-  for (int i = 0; i < job.take; ++i) {
-    if (u0 + i >= job.units) break;
-    cojob_unit(job, u0 + i);
-  }
+// Workgroup b of nb (256 threads, all of them call this) takes every nb-th unit.
+__device__ __forceinline__ void cojob_run(const CoJob& job, unsigned int b, unsigned int nb) {
+  for (unsigned int u = b; u < job.units; u += nb) cojob_unit(job, u);
 }
 
 }  // namespace strp

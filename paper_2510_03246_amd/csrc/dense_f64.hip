@@ -444,7 +444,6 @@ struct StepP {
   int n, N;                     // order, tiles
   int t;
   int each;                     // tiles of TA and TV per workgroup
-  int own;                      // workgroups past own are spare ones for the ride-along job
   int32_t* status;
 };
 
@@ -775,13 +774,9 @@ __device__ __forceinline__ void step_panel(const StepP& p, StepShared& sh, int i
   store_acc(At(i, t + 1), p.ld, rows, NB, wm, wn, lane, c);
 }
 
-__global__ __launch_bounds__(256, 2) void chol_step_kernel(const StepP p, const CoJob job) {
+__global__ __launch_bounds__(256, 2) void chol_step_kernel(const StepP p) {
   __shared__ __attribute__((aligned(16))) StepShared sh;
   int b = blockIdx.x;
-  if (b >= p.own) {
-    cojob_help(job);
-    return;
-  }
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int wm = (wave >> 1) * 32, wn = (wave & 1) * 32;
   const int n = p.n, N = p.N, t = p.t;
@@ -878,8 +873,9 @@ __global__ __launch_bounds__(256, 2) void chol_step_kernel(const StepP p, const 
   }
 }
 
-// First launch of the chain: block 0 factors diagonal tile 0, the others clear the tiles of Linv above the diagonal.
-__global__ __launch_bounds__(256, 2) void chol_begin_kernel(const StepP p) {
+// First launch of the chain: block 0 factors diagonal tile 0, the next `clear` ones clear the tiles of Linv above the
+// diagonal, and what is left of the chip streams the ride-along job.
+__global__ __launch_bounds__(256, 2) void chol_begin_kernel(const StepP p, int clear, const CoJob job) {
   __shared__ __attribute__((aligned(16))) StepShared sh;
   const int tid = threadIdx.x;
   if (blockIdx.x == 0) {
@@ -894,8 +890,12 @@ __global__ __launch_bounds__(256, 2) void chol_begin_kernel(const StepP p) {
     finish_diag(p, 0, sh, [] {});
     return;
   }
+  if ((int)blockIdx.x > clear) {
+    cojob_run(job, blockIdx.x - 1 - clear, gridDim.x - 1 - clear);
+    return;
+  }
   const int nt = p.N * (p.N - 1) / 2;
-  for (int e = (int)blockIdx.x - 1; e < nt; e += (int)gridDim.x - 1) {
+  for (int e = (int)blockIdx.x - 1; e < nt; e += clear) {
     int c = (int)((__builtin_sqrtf(8.0f * (float)e + 1.0f) - 1.0f) * 0.5f);      // tile (r, c + 1), r <= c
     while (c * (c + 1) / 2 > e) --c;
     while ((c + 1) * (c + 2) / 2 <= e) ++c;
@@ -904,18 +904,6 @@ __global__ __launch_bounds__(256, 2) void chol_begin_kernel(const StepP p) {
       for (int r = r0 + (tid >> 6); r < r0 + NB; r += 4) p.V[(long long)r * p.ldv + col] = 0.0;
   }
 }
-
-// spare workgroups of one launch of the chain for the ride-along job: enough for the whole job to be taken within the
-// launches of the iteration's two chains (job.per_launch units each), at two workgroups of this kernel per CU
-static int cojob_spare_blocks(const CoJob* cj, int own, int* take) {
-  if (!cj || !cj->ticket || cj->per_launch <= 0) return 0;
-  int h = 512 - own;
-  if (h < 256) h = 256;
-  *take = (cj->per_launch + h - 1) / h;
-  return (cj->per_launch + *take - 1) / *take;
-}
-
-int chol_launches(int n) { return (n + NB - 1) / NB + 1; }
 
 // Linv [n x n, ldv] = L^-1 of A = L L^T (lower part of A [n x n, ld], destroyed); upper part of Linv zero.
 // sub: ceil(n / NB) * NB * NB doubles of scratch.  ld and ldv even, A and Linv 16-byte aligned.
@@ -926,7 +914,13 @@ strp_status chol_inverse(strp_ctx* ctx, double* A, int n, long long ld, double* 
   memset(&p, 0, sizeof(p));
   p.A = A; p.ld = ld; p.V = Linv; p.ldv = ldv; p.sub = sub; p.n = n; p.N = (n + NB - 1) / NB; p.status = status;
   const int nt = p.N * (p.N - 1) / 2;
-  hipLaunchKernelGGL(chol_begin_kernel, dim3(1 + (nt < 1024 ? nt : 1024)), dim3(256), 0, ctx->stream, p);
+  const int clear = nt < 1024 ? nt : 1024;
+  CoJob job;
+  memset(&job, 0, sizeof(job));
+  if (ctx->cojob) job = *ctx->cojob;
+  ctx->cojob = nullptr;
+  const unsigned int ride = job.units < 510u ? job.units : 510u;      // two workgroups of this kernel per CU, one place left to block 0
+  hipLaunchKernelGGL(chol_begin_kernel, dim3(1 + clear + ride), dim3(256), 0, ctx->stream, p, clear, job);
   for (int t = 0; t < p.N; ++t) {
     p.t = t;
     const int m = p.N - 1 - t;
@@ -935,17 +929,8 @@ strp_status chol_inverse(strp_ctx* ctx, double* A, int n, long long ld, double* 
     p.each = (total + 191) / 192;
     if (p.each > 3) p.each = total > 1024 ? 1 : 3;
     if (p.each < 1) p.each = 1;
-    p.own = m + t + (total + p.each - 1) / p.each;
-    if (p.own == 0) continue;      // a single tile: the first launch was all
-    CoJob job;
-    memset(&job, 0, sizeof(job));
-    int take = 0;
-    const int spare = cojob_spare_blocks(ctx->cojob, p.own, &take);
-    if (spare > 0) {
-      job = *ctx->cojob;
-      job.take = take;
-    }
-    hipLaunchKernelGGL(chol_step_kernel, dim3(p.own + spare), dim3(256), 0, ctx->stream, p, job);
+    const int blocks = m + t + (total + p.each - 1) / p.each;
+    if (blocks > 0) hipLaunchKernelGGL(chol_step_kernel, dim3(blocks), dim3(256), 0, ctx->stream, p);      // none: a single tile, the first launch was all
   }
   STRP_HIP(ctx, hipGetLastError());
   return STRP_OK;

@@ -212,24 +212,6 @@ __global__ __launch_bounds__(1024) void pruned_list_kernel(const uint8_t* mask, 
   for (int j = total + tid; j < f; j += 1024) rows[j] = -1;
 }
 
-// takes units until none are left
-__global__ __launch_bounds__(256) void cojob_drain_kernel(const CoJob job) {
-  __shared__ unsigned int u0s;
-  for (;;) {
-    if (threadIdx.x == 0) u0s = atomicAdd(job.ticket, (unsigned int)job.take);
-    __syncthreads();
-    const unsigned int u0 = u0s;
-    if (u0 >= job.units) return;
-    for (int i = 0; i < job.take; ++i) {
-      if (u0 + i >= job.units) break;
-      cojob_unit(job, u0 + i);   // ends with a barrier: u0s may be rewritten afterwards
-    }
-  }
-}
-
-// a small job's units, one workgroup each: no counter to take them from
-__global__ __launch_bounds__(256) void cojob_units_kernel(const CoJob job) { cojob_unit(job, blockIdx.x); }
-
 // scalar slots of strp_module_state::scalars
 // bits of strp_module_state::sums_cached: which token sums cv.rowsums holds for EVERY row of the current state
 enum { SUMS_G = 1, SUMS_EU = 2, SUMS_V = 4 };
@@ -1066,7 +1048,7 @@ strp_status strp_admm_step(strp_ctx* ctx, const strp_module_desc* desc, strp_mod
   const long long sp = round_up(s, 8);
 
   // ---- everything the step needs cleared, in one launch: the refitted weights outside the kept rows and columns, the
-  // maxima of the weights' planes, the counter of the pruned rows' units
+  // maxima of the weights' planes, the finishing kernel's counter
   enum { MAX_W2 = 0, MAX_MI = 1, MAX_B = 2, MAX_W1 = 3 };
   STRP_TAKE(ctx, arena, wmax, unsigned int, 64);
   unsigned int* const ticket = wmax + 32;
@@ -1078,8 +1060,8 @@ strp_status strp_admm_step(strp_ctx* ctx, const strp_module_desc* desc, strp_mod
 
   // ---- the pruned rows' fused a/z pass as a ride-along job ------------------------------------------------------
   // It touches only rows outside S, which nothing else in the step reads or writes, so it may run any time from
-  // here to the end of the step: the factorisation chains of the fc2 refit and of the a-update carry spare
-  // workgroups for it (chol_inverse reads ctx->cojob), and what they leave is drained where the pass used to run.
+  // here to the end of the step: the first launch of the step's first factorisation chain carries it (chol_inverse takes
+  // ctx->cojob; the a-update, which this pass is fused with, always factors a system).
   struct CoJobGuard {
     strp_ctx* c;
     ~CoJobGuard() { c->cojob = nullptr; }
@@ -1094,16 +1076,11 @@ strp_status strp_admm_step(strp_ctx* ctx, const strp_module_desc* desc, strp_mod
     STRP_TAKE(ctx, arena, blk, double, 2 * (size_t)((f - s + 255) / 256));
     finish_blk = blk;
     if (!prow_done) hipLaunchKernelGGL(pruned_list_kernel, dim3(1), dim3(1024), 0, ctx->stream, st->mask, f, prow);
-    pjob.ticket = ticket;
     pjob.units = (unsigned int)(f - s) * (unsigned int)segs;
-    pjob.per_launch = (int)(pjob.units / (unsigned)(chol_launches(s) + chol_launches(d) - 2) + 1u);
     pjob.rows = prow; pjob.nrows = f - s; pjob.segs = segs; pjob.seg_tokens = SEG;
     pjob.Z = st->Z; pjob.A = st->A; pjob.Z0 = wanda ? nullptr : st->Z0;
     pjob.lda = lda; pjob.T = T; pjob.alpha = alpha; pjob.beta = beta; pjob.partial = partial;
-    // a small pass (a module of a few hundred hidden units per kept one, or few tokens) is over before the chains
-    // have taken their first steps and only lengthens those: it is left to a kernel of its own (measured on a d = 768
-    // module: 2 % slower with the ride, against 1-2 % faster from d = 2048 on)
-    if (pjob.units >= 65536u) ctx->cojob = &pjob;
+    ctx->cojob = &pjob;
   }
   // compact kept weights: written by the refits' last products when those run in this call, gathered otherwise
   float* W2S = nullptr;
@@ -1353,16 +1330,9 @@ strp_status strp_admm_step(strp_ctx* ctx, const strp_module_desc* desc, strp_mod
     fin.do_z = 1; fin.red_z = red; fin.nz = nb; fin.c2 = params->beta / (double)T; fin.c3 = params->alpha / (double)T;
     if (p.rs_out) STRP_TRY(launch_rowsum_reduce(ctx, rsZ, 1, rs_slots, s, st->idx, cv.rowsums, f, 2, 2));
     if (fuse_pruned) {
-      // what the factorisation chains' spare workgroups left of the pruned rows' pass; the rows' sums are added at the end
-      if (pjob.ticket) {
-        ProfScope ps(ctx, "pruned_rows_drain", 0.0, 0.0);
-        CoJob dj = pjob;
-        dj.take = 4;
-        if (ctx->cojob) hipLaunchKernelGGL(cojob_drain_kernel, dim3(2048), dim3(256), 0, ctx->stream, dj);
-        else hipLaunchKernelGGL(cojob_units_kernel, dim3(pjob.units), dim3(256), 0, ctx->stream, dj);
-        ctx->cojob = nullptr;
+      if (pjob.units) {      // the rows' sums are added at the end
         fin.rows = prow; fin.partial = pjob.partial; fin.nrows = pjob.nrows; fin.segs = pjob.segs; fin.f = f; fin.z0 = pjob.Z0 != nullptr;
-        fin.rowsums = cv.rowsums; fin.blk = finish_blk; fin.ticket = wmax + 48;
+        fin.rowsums = cv.rowsums; fin.blk = finish_blk; fin.ticket = ticket;
       }
       // every row's sums are then in place: the kept rows' from the two epilogues, the pruned rows' from this pass
       // (which also rewrites their sum Z0^2; the kept rows' is only there if it was streamed before)
@@ -1400,8 +1370,10 @@ strp_status strp_admm_step(strp_ctx* ctx, const strp_module_desc* desc, strp_mod
     fin.host = (double*)ctx->pinned;
     fin.status = ctx->status_dev;
   }
-  if (fin.nrows || fin.do_z || fin.do_1 || fin.do_w || fin.host)
+  if (fin.nrows || fin.do_z || fin.do_1 || fin.do_w || fin.host) {
+    ProfScope ps(ctx, fin.nrows ? "pruned_rows_drain" : "step_finish", 0.0, 0.0);
     hipLaunchKernelGGL(step_finish_kernel, dim3(fin.nrows ? (fin.nrows + 255) / 256 : 1), dim3(256), 0, ctx->stream, fin);
+  }
   STRP_HIP(ctx, hipGetLastError());
   st->iter += 1;
 

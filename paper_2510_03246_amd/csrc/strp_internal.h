@@ -23,8 +23,8 @@ struct strp_ctx {
   char err[512];
   struct Profiler* prof;  // optional per-kernel event timing (host object)
   unsigned char prod_planes[8][2];  // fp16 planes (1 or 2) of the P and Q operand per strp_product of strp_admm_step
-  // Set by strp_admm_step while a streaming job may ride along with the factorisation chains (see cojob.h); null
-  // everywhere else.  chol_factor gives its short launches spare workgroups for it.
+  // Set by strp_admm_step while a streaming job waits for a launch to ride along with (see cojob.h); null everywhere else.
+  // The next chol_inverse takes it.
   const strp::CoJob* cojob;
 };
 
@@ -204,7 +204,6 @@ static inline long long f64_ld(long long n) { return (n + 7) & ~7LL; }
 // caller has added the ridge) and destroyed.  sub: ceil(n / NB) * NB * NB doubles of scratch.  ld and ldv even, A and Linv
 // 16-byte aligned.  A pivot that is not positive sets ENOTPD in status (device word).
 strp_status chol_inverse(strp_ctx* ctx, double* A, int n, long long ld, double* sub, double* Linv, long long ldv, int32_t* status);
-int chol_launches(int n);   // launches of chol_inverse that can carry spare workgroups, and one
 // X (L L^T)^-1 = (X Linv^T) Linv for X [m x n] (ldx), as refitted weights; tmp: m x ldx scratch.
 //   FC2: W[i, idx[j]] = result[i, j] (m rows of W);  FC1: W[idx[i], j] = result[i, j];  other entries of W are not written.
 //   Wc (optional): the result itself, [m x ldc]; maxbits (optional): atomic maximum of the bits of its magnitudes; sumsq
