@@ -67,7 +67,7 @@ __global__ __launch_bounds__(512, 1) void gemm_dma_kernel(const GemmP p) {
   __shared__ int srow[dma::ROWS];
 
   int tm, tn, split;
-  if (!decode_tile(p, (int)blockIdx.x, (int)gridDim.x, tm, tn, split)) return;
+  decode_tile(p, (int)blockIdx.x, (int)gridDim.x, tm, tn, split);
   const int m0 = tm * ROWS, n0 = tn * ROWS;
   const long long k0 = (long long)split * p.kchunk;                 // a multiple of 32
   const long long k1 = (k0 + p.kchunk < p.K) ? (k0 + p.kchunk) : p.K;

@@ -37,17 +37,20 @@ __device__ __forceinline__ double wave_sum(double v) {
 // pipelined kernel resident, starting the next of its blocks when one retires.  Each XCD has its own L2, so the
 // 32 blocks resident on an XCD should share operand panels: the work list is ordered tile group by tile group
 // (gm x gn tiles, all of one K split, then the next split of the same group), and XCD x takes entries
-// [256 c + 32 x, 256 c + 32 x + 32) of it in its c-th round.  A group of gm x gn tiles streams gm + gn panels
-// instead of 2 gm gn.
+// [256 c + 32 x, 256 c + 32 x + 32) of it in its c-th round; the last round's entries are dealt out the same way, as
+// evenly as they go.  A group of gm x gn tiles streams gm + gn panels instead of 2 gm gn.
 // Symmetric products compute the lower triangle of an n x n tile grid; it is folded into a rectangle of
-// ceil(n/2) x (2 ceil(n/2) + 1) tiles (row r holds triangle row r + h followed by triangle row h - 1 - r) so that
-// the same grouping applies.  Returns false for the padding cells of an odd n.
-__device__ __forceinline__ bool decode_tile(const GemmP& p, int bid, int nblocks, int& tm, int& tn, int& split) {
+// ceil(n/2) x (2 h + 1) tiles, h = floor(n/2) (row r holds triangle row r + h followed by triangle row h - 1 - r), so that
+// the same grouping applies and no workgroup is empty.
+__device__ __forceinline__ void decode_tile(const GemmP& p, int bid, int nblocks, int& tm, int& tn, int& split) {
   const int full = nblocks & ~255;
   int q = bid;
   if (bid < full) {
     const int x = bid & 7, j = bid >> 3;
     q = ((j >> 5) << 8) + (x << 5) + (j & 31);
+  } else {
+    const int x = bid & 7, rem = nblocks - full;
+    q = full + x * (rem >> 3) + (x < (rem & 7) ? x : (rem & 7)) + ((bid - full) >> 3);
   }
   const int TM = p.gridM, TN = p.gridN;
   const int row_items = p.gm * TN * p.splits;           // work items of a full row of groups
@@ -64,13 +67,11 @@ __device__ __forceinline__ bool decode_tile(const GemmP& p, int bid, int nblocks
   const int cc = r / hm;
   int a = gi * p.gm + (r - cc * hm), b = gj * p.gn + cc;
   if (p.triangle) {
-    const int h = TM;                                   // = ceil(tilesM / 2)
+    const int h = p.tilesM >> 1;
     if (b <= a + h) { a += h; }
     else { b -= a + h + 1; a = h - 1 - a; }
-    if (a >= p.tilesM) return false;
   }
   tm = a; tn = b;
-  return true;
 }
 
 // Epilogue of one 32 x 32 tile of outputs, 16 values per lane (passed by value so the accumulators never need an address).

@@ -100,7 +100,7 @@ __global__ __launch_bounds__(256, WT == 4 ? 1 : 2) void gemm_kernel(const GemmP 
 
   // ---- which tile, which K range ---------------------------------------------------------
   int tm, tn, split;
-  if (!decode_tile(p, (int)blockIdx.x, (int)gridDim.x, tm, tn, split)) return;
+  decode_tile(p, (int)blockIdx.x, (int)gridDim.x, tm, tn, split);
   const int m0 = tm * ROWS, n0 = tn * ROWS;
   const long long k0 = (long long)split * p.kchunk;
   const long long k1 = (k0 + p.kchunk < p.K) ? (k0 + p.kchunk) : p.K;
@@ -221,13 +221,13 @@ __global__ __launch_bounds__(256, WT == 4 ? 1 : 2) void gemm_kernel(const GemmP 
 // ---------------------------------------------------------------------------------------------
 // host side
 // ---------------------------------------------------------------------------------------------
-void gemm_plan_tiles(GemmP& p, int want_splits) {
-  {
+void gemm_plan_tiles(GemmP& p, int want_splits, int wt) {
+  if (wt) {
+    p.wt = wt;
+  } else {
     // 256x256 tiles with the LDS-DMA pipeline when they still give most CUs a block
-    const long long t4m = (p.M + 255) / 256, t4n = (p.N + 255) / 256;
-    const long long n4 = p.triangle ? t4m * (t4m + 1) / 2 : t4m * t4n;
-    const bool big = p.M >= 256 && p.N >= 256 && n4 * (want_splits > 1 ? want_splits : 1) >= 192 && p.K >= 256;
-    p.wt = (big && p.force_wt != 2) ? 4 : 2;
+    const long long n4 = (long long)((p.M + 255) / 256) * ((p.N + 255) / 256);
+    p.wt = gemm_tile256_ok(p) && n4 >= 192 ? 4 : 2;
   }
   const int ROWS = 64 * p.wt, BK = p.wt == 2 ? 64 : 32;
   p.tilesM = (p.M + ROWS - 1) / ROWS;
@@ -235,7 +235,7 @@ void gemm_plan_tiles(GemmP& p, int want_splits) {
   p.ntiles = p.triangle ? p.tilesM * (p.tilesM + 1) / 2 : p.tilesM * p.tilesN;
   if (p.triangle) {
     p.gridM = (p.tilesM + 1) / 2;
-    p.gridN = 2 * p.gridM + 1;
+    p.gridN = 2 * (p.tilesM / 2) + 1;
   } else {
     p.gridM = p.tilesM;
     p.gridN = p.tilesN;
@@ -320,17 +320,18 @@ strp_status launch_gemm(strp_ctx* ctx, GemmP& p) {
 }
 
 // ---- split-K reduction -----------------------------------------------------------------------
-// One block reduces a 64 x 64 output tile (thread = column tx, rows ty + 4 i): a wavefront load is 256 contiguous bytes
-// of one row of one partial.  Symmetric products: only tiles on or below the diagonal are reduced; the strict lower
+// One block reduces a 16 x 64 output tile (thread = column tx, rows ty + 4 i): a wavefront load is 256 contiguous bytes
+// of one row of one partial.  Symmetric products: only tiles that reach the lower half are reduced; the strict lower
 // part is also written transposed through LDS, so the upper half is a bit-exact mirror and the partials are read once,
-// row-contiguously.
+// row-contiguously.  Bound by HBM where the output is large (4.7 TB/s); a small output (M = 832: 91 tiles of 64 x 64)
+// leaves few workgroups, each with a serial walk over the splits, so tiles are low and four splits are in flight.
 __global__ __launch_bounds__(256) void splitk_reduce_kernel(const ReduceP r) {
-  constexpr int TS = 64;
-  __shared__ double tile[TS][TS + 1];
+  constexpr int TN = REDUCE_TILE_N, TM = REDUCE_TILE_M, NI = TM / 4, AHEAD = 4;
+  __shared__ double tile[TM][TN + 1];
   const int tx = threadIdx.x & 63, ty = threadIdx.x >> 6;
-  const int n0 = blockIdx.x * TS, m0 = blockIdx.y * TS;
+  const int n0 = blockIdx.x * TN, m0 = blockIdx.y * TM;
   const int M = r.M, N = r.N;
-  if (r.triangle && n0 > m0) {
+  if (r.triangle && n0 >= m0 + TM) {
     if (r.dot && threadIdx.x == 0) r.red[blockIdx.y * gridDim.x + blockIdx.x] = 0.0;
     return;
   }
@@ -345,31 +346,36 @@ __global__ __launch_bounds__(256) void splitk_reduce_kernel(const ReduceP r) {
     if (r.diag && m == n) r.diag[m] = s;
   };
   const int n = n0 + tx;
-  double acc[16];
+  double acc[NI];
 #pragma unroll
-  for (int i = 0; i < 16; ++i) acc[i] = 0.0;
+  for (int i = 0; i < NI; ++i) acc[i] = 0.0;
   {
-    // rows and the column are clamped into range (results of clamped lanes are not stored): the 16 loads of a split
-    // are then unconditional and all in flight together
+    // rows and the column are clamped into range (results of clamped lanes are not stored), and so are the splits of the
+    // last group: the loads of a group are then unconditional and all in flight together
     const int nc = n < N ? n : N - 1;
-    long long ro[16];
+    long long ro[NI];
 #pragma unroll
-    for (int i = 0; i < 16; ++i) {
+    for (int i = 0; i < NI; ++i) {
       const int m = m0 + ty + 4 * i;
       ro[i] = (long long)(m < M ? m : M - 1) * N + nc;
     }
-    for (int sp = 0; sp < r.splits; ++sp) {
-      const float* src = r.part + (long long)sp * MN;
-      float v[16];
+    for (int sp = 0; sp < r.splits; sp += AHEAD) {
+      float v[AHEAD][NI];
 #pragma unroll
-      for (int i = 0; i < 16; ++i) v[i] = src[ro[i]];
+      for (int q = 0; q < AHEAD; ++q) {
+        const float* src = r.part + (long long)(sp + q < r.splits ? sp + q : r.splits - 1) * MN;
 #pragma unroll
-      for (int i = 0; i < 16; ++i) acc[i] += (double)v[i];
+        for (int i = 0; i < NI; ++i) v[q][i] = src[ro[i]];
+      }
+#pragma unroll
+      for (int q = 0; q < AHEAD; ++q)
+#pragma unroll
+        for (int i = 0; i < NI; ++i) acc[i] += sp + q < r.splits ? (double)v[q][i] : 0.0;
     }
     if (r.dot) {          // <dot, C>: the strict lower part of this tile stands for its mirror image as well
       double s = 0.0;
 #pragma unroll
-      for (int i = 0; i < 16; ++i) {
+      for (int i = 0; i < NI; ++i) {
         const int m = m0 + ty + 4 * i;
         const double w = (m < M && n < N && n <= m) ? (n < m ? 2.0 : 1.0) : 0.0;
         s = __builtin_fma(w * (double)r.dot[ro[i]], acc[i], s);
@@ -383,7 +389,7 @@ __global__ __launch_bounds__(256) void splitk_reduce_kernel(const ReduceP r) {
     }
   }
 #pragma unroll
-  for (int i = 0; i < 16; ++i) {
+  for (int i = 0; i < NI; ++i) {
     const int m = m0 + ty + 4 * i;
     if (m < M && n < N && (!r.triangle || n <= m)) put(m, n, acc[i]);
     tile[ty + 4 * i][tx] = acc[i];
@@ -391,9 +397,10 @@ __global__ __launch_bounds__(256) void splitk_reduce_kernel(const ReduceP r) {
   if (!r.triangle) return;
   __syncthreads();
 #pragma unroll
-  for (int i = 0; i < 16; ++i) {
-    const int lo_m = m0 + tx, lo_n = n0 + ty + 4 * i;     // element (lo_m, lo_n) of the lower half, mirrored to (lo_n, lo_m)
-    if (lo_n < lo_m && lo_m < M && lo_n < N) put(lo_n, lo_m, tile[tx][ty + 4 * i]);
+  for (int i = 0; i < NI; ++i) {     // element (lo_m, lo_n) of the lower half, mirrored to (lo_n, lo_m)
+    const int e = threadIdx.x + 256 * i;
+    const int lo_m = m0 + (e & (TM - 1)), lo_n = n0 + e / TM;
+    if (lo_n < lo_m && lo_m < M && lo_n < N) put(lo_n, lo_m, tile[e & (TM - 1)][e / TM]);
   }
 }
 
@@ -402,7 +409,7 @@ strp_status launch_splitk_reduce(strp_ctx* ctx, const ReduceP& r) {
   if (r.triangle && r.M != r.N) return fail(ctx, STRP_EINVAL, "split-K reduce: a symmetric product must be square");
   if (r.dot && !r.triangle) return fail(ctx, STRP_EINVAL, "split-K reduce: the inner product is for symmetric products");
   ProfScope ps(ctx, "splitk_reduce", 0.0, 4.0 * tot * (double)r.splits * (r.triangle ? 0.5 : 1.0) + (r.outf ? 4.0 : 0.0) * tot + (r.outd ? 8.0 : 0.0) * tot);
-  hipLaunchKernelGGL(splitk_reduce_kernel, dim3((r.N + 63) / 64, (r.M + 63) / 64), dim3(256), 0, ctx->stream, r);
+  hipLaunchKernelGGL(splitk_reduce_kernel, dim3((r.N + REDUCE_TILE_N - 1) / REDUCE_TILE_N, (r.M + REDUCE_TILE_M - 1) / REDUCE_TILE_M), dim3(256), 0, ctx->stream, r);
   STRP_HIP(ctx, hipGetLastError());
   return STRP_OK;
 }

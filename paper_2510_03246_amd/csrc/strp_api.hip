@@ -645,42 +645,38 @@ static strp_status weight_planes(strp_ctx* ctx, Arena& arena, const void* src, i
   return STRP_OK;
 }
 
-// number of K splits of a token-contraction product: enough blocks to fill the chip and fp32
-// accumulation chains of at most 8192 tokens (partials are then summed in fp64)
-static int plan_splits(int ntiles, long long K) {
-  long long s_chain = (K + 8191) / 8192;
-  long long s_fill = (1024 + ntiles - 1) / ntiles;
-  long long s = s_chain > s_fill ? s_chain : s_fill;
-  long long s_max = K / 256 > 1 ? K / 256 : 1;
-  if (s > s_max) s = s_max;
-  return (int)s;
-}
-
-// Tiles and K splits of a token-contraction product.  A grid of no more than two rounds of workgroups is a matter of
-// how well its last round fills the chip: from the split count of plan_splits upwards (at most a quarter more: shorter
-// chains, never longer ones) the one with the least rounds x chain length is taken (17 % on the Gram of a d = 768
-// module).  Larger grids are left alone: measured, their run time does not follow the round count (workgroups do not run
-// in lockstep, and more splits cost more prologues and partial sums).
+// Tile shape and K splits of a token-contraction product.  fp32 accumulation chains are at most 8192 tokens (partials are
+// summed in fp64); beyond that the split count is a matter of how well the workgroups fill the chip: 256 run at a time
+// with 256x256 tiles, 512 with 128x128 ones, so the candidates are the counts that just fill a number of rounds, and the
+// cheapest of them is taken.  Costs are in contraction steps of 32 by one workgroup with 256x256 tiles (about 2.1 us with
+// four operand planes), fitted to sweeps over 126 .. 2048 workgroups: such a workgroup spends 7 of them on its first loads
+// and its epilogue; one of two with 128x128 tiles takes 1.5 times as long for the same area (its operands pass through
+// registers) and loses 4 steps of 64; a partial costs what it takes to read it back.  Gram of 1536 rows over 65536
+// tokens: 450 us with 17 splits (1.4 rounds), 371 with 12 (0.98).
 static void plan_nt_product(GemmP& p) {
-  gemm_plan_tiles(p, 1);
-  const int s0 = plan_splits(p.ntiles, p.K);
-  gemm_plan_tiles(p, s0);
-  const long long slots0 = p.wt == 4 ? 256 : 512;   // workgroups the chip runs at a time (one or two per CU)
-  if (s0 <= 1 || (long long)p.ntiles * p.splits > 2 * slots0) return;
+  const long long s_chain = (p.K + 8191) / 8192, s_max = p.K / 256 > s_chain ? p.K / 256 : s_chain;
   double best_cost = 0.0;
-  int best = s0;
-  for (int s = s0; s <= s0 + s0 / 4; ++s) {
+  GemmP best;
+  for (int wt = 4; wt >= 2; wt -= 2) {
+    if (wt == 4 && !gemm_tile256_ok(p)) continue;
+    const long long slots = wt == 4 ? 256 : 512;
     GemmP q = p;
-    gemm_plan_tiles(q, s);
-    const long long slots = q.wt == 4 ? 256 : 512;
-    const long long blocks = (long long)q.ntiles * q.splits;
-    const double cost = (double)((blocks + slots - 1) / slots) * (double)q.kchunk;
-    if (s == s0 || cost < best_cost * 0.995) {
-      best_cost = cost;
-      best = s;
+    gemm_plan_tiles(q, 1, wt);
+    const long long r0 = (q.ntiles * s_chain + slots - 1) / slots;
+    for (long long r = r0; r < r0 + 8; ++r) {
+      long long s = r * slots / q.ntiles;
+      s = s < s_chain ? s_chain : (s > s_max ? s_max : s);
+      gemm_plan_tiles(q, (int)s, wt);
+      const double rounds = (double)(((long long)q.ntiles * q.splits + slots - 1) / slots);
+      const double steps = wt == 4 ? (double)q.kchunk / 32.0 + 7.0 : 1.5 * ((double)q.kchunk / 64.0 + 4.0);
+      const double cost = rounds * steps + (double)q.splits * (double)p.M * (double)p.N * (p.triangle ? 0.5 : 1.0) / 1.2e6;
+      if (best_cost == 0.0 || cost < best_cost * 0.995) {
+        best_cost = cost;
+        best = q;
+      }
     }
   }
-  gemm_plan_tiles(p, best);
+  p = best;
 }
 
 static size_t nt_partial_elems(int M, int N, long long K, int triangle) {

@@ -114,7 +114,6 @@ struct GemmP {
   PlaneOp P, Q;        // C[m, n] = sum_k P(k, m) Q(k, n)
   int M, N;
   long long K;
-  int force_wt;        // 2 forces the 128x128 register-staged kernel
   int wt;              // 32x32 MFMA tiles per wavefront per dimension: 2 (128x128 blocks) or 4 (256x256), set by gemm_plan_tiles
   int tilesM, tilesN, ntiles;
   int gridM, gridN;    // tile grid the blocks are laid over: tilesM x tilesN, or the folded triangle (see decode_tile)
@@ -149,7 +148,9 @@ struct GemmP {
 
 strp_status launch_gemm(strp_ctx* ctx, GemmP& p);
 int gemm_grid_blocks(const GemmP& p);
-void gemm_plan_tiles(GemmP& p, int want_splits);
+// tile shape (wt = 0: by the number of tiles), tile grid and K splits of a product
+void gemm_plan_tiles(GemmP& p, int want_splits, int wt = 0);
+static inline bool gemm_tile256_ok(const GemmP& p) { return p.M >= 256 && p.N >= 256 && p.K >= 256; }
 
 // Sum split-K partials in fp64; optional symmetric completion from the computed lower half.
 // outf / outd (either may be null): [M x ldo]; accumulate adds to outf's previous content; ridge (or *ridge_dev) is added
@@ -166,7 +167,8 @@ struct ReduceP {
   const float* dot; double* red;
 };
 strp_status launch_splitk_reduce(strp_ctx* ctx, const ReduceP& r);
-static inline int reduce_blocks(int M, int N) { return ((M + 63) / 64) * ((N + 63) / 64); }
+constexpr int REDUCE_TILE_M = 16, REDUCE_TILE_N = 64;      // output tile of one workgroup of the split-K reduction
+static inline int reduce_blocks(int M, int N) { return ((M + REDUCE_TILE_M - 1) / REDUCE_TILE_M) * ((N + REDUCE_TILE_N - 1) / REDUCE_TILE_N); }
 // fp32 / bf16 activation rows (optionally gathered by idx) -> fp16 planes; any output pair may be null.
 //   t_* : contraction over tokens   (k = token,   r = row):   plane_elems(rows, T)
 //   c_* : contraction over channels (k = row,     r = token): plane_elems(T, rows)

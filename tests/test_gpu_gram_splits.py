@@ -1,0 +1,33 @@
+"""Tile shapes, folded triangles and K splits of the token-contraction product, through strp_gram: every entry, exactly."""
+import pytest
+import torch
+
+from paper_2510_03246_amd import strp
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def ctx():
+    c = strp.Context(0)
+    c.set_workspace(1 << 30)
+    yield c
+    c.close()
+
+
+# both tile shapes with an even and an odd number of tile rows, one token group to several accumulation chains, a split
+# count that is and is not a multiple of what the reduction keeps in flight
+@pytest.mark.parametrize("s,T", [(64, 8), (129, 520), (255, 4104), (256, 256), (257, 264), (512, 8200), (640, 70000), (768, 16384), (1025, 2056),
+                                 (1280, 3000)])
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+def test_gram_is_exact_on_small_integers(ctx, s, T, dtype):
+    """Entries of at most 4: products and their sums stay below 2^24, so no step of the product rounds, in any order."""
+    g = torch.Generator().manual_seed(s + T)
+    ld = (T + 7) // 8 * 8
+    A = torch.randint(-4, 5, (s, ld), generator=g).to(dtype).cuda()
+    diag = torch.empty(s, dtype=torch.float64, device="cuda")
+    G = ctx.strp_gram(A, T, diag=diag)
+    assert ctx.poll() == strp.OK
+    ref = A[:, :T].double() @ A[:, :T].double().T
+    assert torch.equal(G.double(), ref)
+    assert torch.equal(diag, ref.diagonal())
