@@ -3,7 +3,7 @@
 //   colnorm2      : squared column norms of the next linear layer
 //   unit_scores   : WANDA / LEMMA / GAIN unit scores (+ group sums for heads) and the layer energy
 //   alloc         : softmax allocation with clipping, rescale and largest-remainder prune counts
-//   topk          : radix select on order-preserving keys, ballot/prefix compaction, ties -> lower index
+//   topk          : histogram select on order-preserving keys, ballot/prefix compaction, ties -> lower index
 #include <stddef.h>
 
 #include <type_traits>
@@ -626,14 +626,14 @@ __device__ __forceinline__ void pick_bin(const unsigned int (&h)[B], unsigned in
   __syncthreads();
 }
 
-// One vector of up to 1024 KPT scores (0 < k < n) by one block of 1024 threads, element tid + 1024 j in thread tid: REGS keeps
-// the keys in registers, otherwise (beyond 16 keys a thread) each phase reads the scores again, from the L2.  What bounds it is the number of dependent block-wide phases, so the threshold is found in few of them: a
-// histogram of 2048 bins stretched over the keys that are there (real scores share a handful of exponents: bins at
-// fixed bit positions would put them, and the LDS atomics that count them, in a few places), the bin with the k-th
-// largest key, and the rank of each of the bin's at most 1024 keys among themselves; a fuller bin is stretched again.
-// The k-th key and its index decide every element: kept = larger, or equal with no higher index.  Ascending
-// indices come from one scan of the counts per (round j, wavefront).  n = 16384: 26 -> 14 us with the launch; it was
-// 32 counting rounds.
+// One vector of up to 1024 KPT scores (0 < k < n) by one block of 1024 threads, element tid + 1024 j in thread tid: REGS
+// keeps the keys in registers, otherwise (beyond 16 keys a thread) each phase reads the scores again, from the L2.  What
+// bounds it is the number of dependent block-wide phases, so the threshold is found in few of them: a histogram of 2048
+// bins stretched over the keys that are there (real scores share a handful of exponents: bins at fixed bit positions
+// would put them, and the LDS atomics that count them, in a few places), the bin with the k-th largest key, and the rank
+// of each of the bin's at most 1024 keys among themselves; a fuller bin is stretched again.  The k-th key and its index
+// decide every element: kept = larger, or equal with no higher index.  Ascending indices come from one scan of the counts
+// per (round j, wavefront).  n = 16384: 26 -> 14 us with the launch, against 32 counting rounds before.
 // With in.sums the scores (group = 1) are formed here first, with their mean; rest takes the indices that are not kept.
 struct ScoreSource {
   const double* sums;       // [4][n], or null: the scores are given

@@ -33,7 +33,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 
 # kernels whose every launch belongs to one class of the library's records
-KERNEL_CLASS = {"pruned_rows_kernel": "pruned_rows", "cojob_drain_kernel": "pruned_rows_drain", "split_t_kernel": "split_act", "split_c_kernel": "split_act",
+KERNEL_CLASS = {"pruned_rows_kernel": "pruned_rows", "split_t_kernel": "split_act", "split_c_kernel": "split_act",
                 "row_sums_kernel": "row_sums", "plane_c_to_t_kernel": "plane_c_to_t", "splitk_reduce_kernel": "splitk_reduce"}
 
 
@@ -86,10 +86,10 @@ def classify(dispatches, launches):
     tail = gemm_idx[len(gemm_idx) - len(gemm_records):]
     for i, cls in zip(tail, gemm_records):
         dispatches[i]["cls"] = cls
-    # the timed region starts at the selection ahead of its first GEMM (scores, then top-k, then the plane writer)
+    # the timed region starts at the selection ahead of its first GEMM (scores and top-k in one kernel, then the plane writer)
     start = tail[0] if tail else len(dispatches)
     for i in range(start, max(start - 12, -1), -1):
-        if "unit_scores_kernel" in dispatches[i]["name"]:
+        if "topk_small_kernel" in dispatches[i]["name"]:
             start = i
             break
     for d in dispatches[start:]:
@@ -219,8 +219,8 @@ def main():
                       f"{(pc['fetch_gb'] + pc['write_gb']) / n:.2f} |")
             classes[cls] = dict(launches=n, fetch_gb=pc["fetch_gb"] / n, write_gb=pc["write_gb"] / n,
                                 traffic_gb=(pc["fetch_gb"] + pc["write_gb"]) / n, avg_ms_under_counters=pc["ms"] / n)
-        md += ["", "Launches shorter than 0.3 ms of the timed region, summed per kernel (the factorisation chains' panel and update "
-               "launches carry the units of the pruned rows' pass: its 12 GB in and 24 GB out per iteration show up here):", "",
+        md += ["", "Launches shorter than 0.3 ms of the timed region, summed per kernel (the pruned rows' pass rides in "
+               "the first launch of the first factorisation chain, chol_begin_kernel in the table above):", "",
                "| kernel | launches | total ms | fetch GB | write GB |", "|---|---|---|---|---|"]
         for name, sh in sorted(short.items(), key=lambda kv: -(kv[1]["fetch_gb"] + kv[1]["write_gb"])):
             if sh["fetch_gb"] + sh["write_gb"] >= 0.05:
