@@ -214,7 +214,8 @@ strp_status strp_alloc_softmax(strp_ctx* ctx, const double* energies, int32_t L,
  *   tau (optional) = lowest kept score.
  * One module's scores (n up to 65536) are selected by one block; a longer vector -- the scores of every layer
  * at once for the single global threshold of Alg. 4 (K = floor(r n L) kept over all L n units) -- is selected
- * by a multi-block path that needs strp_topk_workspace_bytes(n) bytes of the context's workspace.
+ * by a multi-block path that needs strp_topk_workspace_bytes(n) bytes of the context's workspace.  With group > 1
+ * and less workspace one block selects it, more slowly.
  * Errors: STRP_EINVAL (k < 0, k > n, n <= 0, group <= 0, null pointers), STRP_ENOMEM (workspace).
  */
 strp_status strp_mask_topk(strp_ctx* ctx, const float* score, int32_t n, int32_t k, int32_t group,

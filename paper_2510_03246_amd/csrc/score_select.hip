@@ -1007,12 +1007,10 @@ __global__ __launch_bounds__(big::THREADS) void topk_count_kernel(const float* s
   }
 }
 
-__global__ __launch_bounds__(big::THREADS) void topk_write_kernel(const float* score, long long n, long long chunk, int vec, int group, uint8_t* mask,
-                                                                  int32_t* idx, const big::State* st) {
-  __shared__ int wtot[8];
-  const long long beg = (long long)blockIdx.x * chunk, end = beg + chunk < n ? beg + chunk : n;
-  const unsigned int thr = st->thr, eqkeep = st->eqkeep[blockIdx.x];
-  unsigned int run = st->kpre[blockIdx.x], eqrun = 0;
+// mask and ascending indices of [beg, end): the keys above thr and the first eqkeep equal to it; run = kept entries before beg
+__device__ __forceinline__ void big_write(const float* score, long long beg, long long end, int vec, int group, uint8_t* mask, int32_t* idx,
+                                          unsigned int thr, unsigned int eqkeep, unsigned int run, int* wtot) {
+  unsigned int eqrun = 0;
   for (long long base = beg; base < end; base += 8 * big::THREADS) {
     const long long i0 = base + 8 * (long long)threadIdx.x;
     const bool whole = vec && i0 + 8 <= end;
@@ -1063,6 +1061,42 @@ __global__ __launch_bounds__(big::THREADS) void topk_write_kernel(const float* s
   }
 }
 
+__global__ __launch_bounds__(big::THREADS) void topk_write_kernel(const float* score, long long n, long long chunk, int vec, int group, uint8_t* mask,
+                                                                  int32_t* idx, const big::State* st) {
+  __shared__ int wtot[8];
+  const long long beg = (long long)blockIdx.x * chunk, end = beg + chunk < n ? beg + chunk : n;
+  big_write(score, beg, end, vec, group, mask, idx, st->thr, st->eqkeep[blockIdx.x], st->kpre[blockIdx.x], wtot);
+}
+
+// The same select by one workgroup with its histograms in LDS, for a caller of groups (group > 1) who has set no workspace
+// large enough for the four launches.  One CU's loads bound it, so it is taken for nothing else.
+__global__ __launch_bounds__(big::THREADS) void topk_lone_kernel(const float* score, long long n, long long k, int vec, int group, uint8_t* mask,
+                                                                 int32_t* idx, float* tau) {
+  __shared__ unsigned int hist[big::BINS];
+  __shared__ unsigned int wt[8], sel[3];
+  __shared__ int wtot[8];
+  const int tid = threadIdx.x;
+  unsigned int prefix = 0, krem = (unsigned int)k;
+  for (int level = 0; level < 3; ++level) {      // key bits 31 .. 19, 18 .. 6, 5 .. 0
+    const int shift = level == 0 ? 19 : level == 1 ? 6 : 0, bits = level == 2 ? 6 : 13;
+    for (int i = tid; i < big::BINS; i += big::THREADS) hist[i] = 0;
+    __syncthreads();
+    big_scan(score, 0, n, vec, [&](unsigned int key) {
+      if (level == 0 || key >> (shift + bits) == prefix) atomicAdd(&hist[(key >> shift) & ((1u << bits) - 1u)], 1u);
+    });
+    __syncthreads();
+    unsigned int h[16];
+#pragma unroll
+    for (int b = 0; b < 16; ++b) h[b] = hist[16 * tid + b];
+    pick_bin<16, 8>(h, krem, wt, sel);
+    prefix = (prefix << bits) | sel[0];
+    krem -= sel[1];
+    __syncthreads();
+  }
+  if (tid == 0 && tau) *tau = key_score(prefix);
+  big_write(score, 0, n, vec, group, mask, idx, prefix, krem, 0, wtot);
+}
+
 static void launch_topk_small(strp_ctx* ctx, float* score, int n, int k, int group, uint8_t* mask, int32_t* idx, float* tau, const ScoreSource& in,
                               int32_t* rest) {
   const auto one = [&](auto kernel) { hipLaunchKernelGGL(kernel, dim3(1), dim3(1024), 0, ctx->stream, score, n, k, group, mask, idx, tau, in, rest); };
@@ -1096,12 +1130,16 @@ strp_status launch_topk(strp_ctx* ctx, const float* score, int n, int k, int gro
   } else if (n <= 65536) {
     launch_topk_small(ctx, const_cast<float*>(score), n, k, group, mask, idx, tau, ScoreSource{nullptr, nullptr, 0, nullptr}, nullptr);
   } else {
-    if (!scratch || scratch_bytes < topk_scratch_bytes(n))
-      return fail(ctx, STRP_ENOMEM, "top-k over %d scores needs %zu bytes of workspace", n, topk_scratch_bytes(n));
+    const int vec = (((uintptr_t)score & 15) == 0 && ((uintptr_t)mask & 7) == 0) ? 1 : 0;
+    if (!scratch || scratch_bytes < topk_scratch_bytes(n)) {
+      if (group == 1) return fail(ctx, STRP_ENOMEM, "top-k over %d scores needs %zu bytes of workspace", n, topk_scratch_bytes(n));
+      hipLaunchKernelGGL(topk_lone_kernel, dim3(1), dim3(big::THREADS), 0, ctx->stream, score, (long long)n, (long long)k, vec, group, mask, idx, tau);
+      STRP_HIP(ctx, hipGetLastError());
+      return STRP_OK;
+    }
     int blocks;
     long long chunk;
     big_plan(n, &blocks, &chunk);
-    const int vec = (((uintptr_t)score & 15) == 0 && ((uintptr_t)mask & 7) == 0) ? 1 : 0;
     big::State* st = (big::State*)scratch;
     STRP_TRY(fill_zero(ctx, st, offsetof(big::State, clear_end)));
     const dim3 b(blocks), th(big::THREADS);

@@ -524,7 +524,7 @@ strp_status strp_mask_topk(strp_ctx* ctx, const float* score, int32_t n, int32_t
   if (need) {
     Arena arena(ctx);
     scratch = arena.take(need);
-    if (!scratch) return fail(ctx, STRP_ENOMEM, "mask_topk: %d scores need %zu bytes of workspace (strp_topk_workspace_bytes)", n, need + 256);
+    if (!scratch && group == 1) return fail(ctx, STRP_ENOMEM, "mask_topk: %d scores need %zu bytes of workspace (strp_topk_workspace_bytes)", n, need + 256);
   }
   return launch_topk(ctx, score, n, k, group, mask, idx, tau, scratch, need);
 }

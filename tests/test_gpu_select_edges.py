@@ -36,6 +36,26 @@ def test_topk_edges(ctx, n, k, group, kind):
     assert float(tau.item()) == np.float32(to)
 
 
+@pytest.mark.parametrize("n,k,group", [(65537, 9, 2), (65600, 65599, 3), (140003, 70001, 2)])
+@pytest.mark.parametrize("kind", ["spread", "ties"])
+def test_topk_groups_without_workspace(n, k, group, kind):
+    """A caller of groups needs no workspace at any length; one of single units does.  Whole numbers: exact."""
+    rng = np.random.default_rng(n)
+    score = rng.normal(size=n) * np.exp(rng.normal(size=n) * 4) if kind == "spread" else rng.integers(-1, 2, size=n)
+    score = score.astype(np.float32)
+    bare = strp.Context(0)
+    s = torch.from_numpy(score).cuda()
+    mask = torch.empty(n, dtype=torch.uint8, device="cuda")
+    idx = torch.empty(k * group, dtype=torch.int32, device="cuda")
+    tau = torch.empty(1, device="cuda")
+    bare.check(bare.lib.strp_mask_topk(bare.h, s.data_ptr(), n, k, group, mask.data_ptr(), idx.data_ptr(), tau.data_ptr()))
+    mo, io, to = orc.select_topk(score, k, group)
+    assert np.array_equal(mask.cpu().numpy(), mo)
+    assert np.array_equal(idx.cpu().numpy().astype(np.int64), io)
+    assert float(tau.item()) == np.float32(to)
+    assert bare.lib.strp_mask_topk(bare.h, s.data_ptr(), n, k, 1, mask.data_ptr(), idx.data_ptr(), tau.data_ptr()) == strp.ENOMEM
+
+
 @pytest.mark.parametrize("shapes", [[(1, 1)], [(7, 13)], [(64, 768)] * 4, [(33, 40)] * 8, [(5, 8)] * 9, [(3000, 264), (2, 3), (128, 8)] * 6])
 def test_weight_energy_lists(ctx, shapes):
     """Lists below, at and above what one launch takes; aligned, unaligned and one-entry matrices of both types.  fp64
