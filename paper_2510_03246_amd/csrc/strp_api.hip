@@ -694,6 +694,10 @@ static strp_status nt_product(strp_ctx* ctx, Arena arena, const PlaneOp& P, cons
   p.P = P; p.Q = Q; p.M = M; p.N = N; p.K = K; p.triangle = triangle;
   p.epi = EPI_PARTIAL;
   plan_nt_product(p);
+  // a caller's workspace sized for other row counts may hold fewer partials than the plan's: as many as fit, but no
+  // chain longer than 8192 tokens
+  const long long chain = (K + 8191) / 8192, fit = (long long)(arena.room() / sizeof(float)) / ((long long)M * N);
+  if (fit < p.splits && p.splits > chain) gemm_plan_tiles(p, (int)(fit > chain ? fit : chain), p.wt);
   STRP_TAKE(ctx, arena, part, float, (size_t)p.splits * M * N);
   p.out = part;
   STRP_TRY(launch_gemm(ctx, p));

@@ -67,6 +67,7 @@ struct Arena {
   Arena() : base(nullptr), off(0), cap(0) {}
   explicit Arena(strp_ctx* ctx) : base(ctx->ws), off(256), cap(ctx->ws_bytes) {}
   Arena(void* block, size_t bytes) : base((char*)block), off(0), cap(bytes) {}   // sub-arena over a block taken elsewhere
+  size_t room() const { return base && off < cap ? (cap - off) & ~size_t(255) : 0; }
   void* take(size_t bytes) {
     size_t b = (bytes + 255) & ~size_t(255);
     if (!base || off + b > cap) return nullptr;

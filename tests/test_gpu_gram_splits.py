@@ -31,3 +31,17 @@ def test_gram_is_exact_on_small_integers(ctx, s, T, dtype):
     ref = A[:, :T].double() @ A[:, :T].double().T
     assert torch.equal(G.double(), ref)
     assert torch.equal(diag, ref.diagonal())
+
+
+def test_gram_in_a_small_workspace():
+    """Operand planes and the partials of the longest chains fit, the plan's own count of partials does not.  fp32 sums of
+    8192 terms of like size and 22-bit operands: 1e-5."""
+    ctx = strp.Context(0)
+    s, T = 256, 65536
+    g = torch.Generator(device="cuda").manual_seed(5)
+    A = torch.randn((s, T), generator=g, device="cuda")
+    ctx.set_workspace(2 * 2 * s * T + 4 * s * s * (T // 8192) + (1 << 20))
+    G = ctx.strp_gram(A, T)
+    assert ctx.poll() == strp.OK
+    ref = A.double() @ A.double().T
+    assert float((G.double() - ref).norm() / ref.norm()) <= 1e-5
