@@ -645,16 +645,54 @@ static strp_status weight_planes(strp_ctx* ctx, Arena& arena, const void* src, i
   return STRP_OK;
 }
 
-// Tile shape and K splits of a token-contraction product.  fp32 accumulation chains are at most 8192 tokens (partials are
-// summed in fp64); beyond that the split count is a matter of how well the workgroups fill the chip: 256 run at a time
-// with 256x256 tiles, 512 with 128x128 ones, so the candidates are the counts that just fill a number of rounds, and the
-// cheapest of them is taken.  Costs are in contraction steps of 32 by one workgroup with 256x256 tiles (about 2.1 us with
+// The fewest K splits a token-contraction product may have, and with them its longest accumulation chain.  The partials are
+// added in fp64, so the error of a Gram matrix or right-hand side is that of one fp32 accumulation chain, which grows with its
+// length, and the ridge system passes it on to the weights by its condition: with chains of 5472, 3872 and 2752 tokens the
+// Gram of 1536 rows over 65536 tokens is 2.1e-7, 1.6e-7 and 1.1e-7 from the fp64 sum, and the fc2 weights of that module
+// 1.31e-5, 0.99e-5 and 0.66e-5.  So a chain has at most 8192 tokens, and no more than the splits leave it that give
+// the chip 1024 workgroups, down to 256 tokens (up to a quarter more splits where that makes fewer or shorter rounds of a
+// grid of at most two).
+static int fewest_splits(const GemmP& p, long long* chain) {
+  GemmP q = p;
+  gemm_plan_tiles(q, 1, 4);
+  const long long n4 = q.ntiles;
+  const bool ok4 = gemm_tile256_ok(p);
+  gemm_plan_tiles(q, 1, 2);
+  const long long n2 = q.ntiles, n = ok4 && n4 >= 192 ? n4 : n2;
+  const long long s_chain = (p.K + 8191) / 8192, s_fill = (1024 + n - 1) / n, s_max = p.K >= 512 ? p.K / 256 : 1;
+  long long s = s_chain > s_fill ? s_chain : s_fill;
+  if (s > s_max) s = s_max;
+  // rounds x chain of s splits
+  auto plan = [&](long long s_) {
+    gemm_plan_tiles(q, (int)s_, ok4 && n4 * s_ >= 192 ? 4 : 2);
+    const long long slots = q.wt == 4 ? 256 : 512;
+    return (double)(((long long)q.ntiles * q.splits + slots - 1) / slots) * (double)q.kchunk;
+  };
+  double cost = plan(s);
+  long long best = s;
+  if (s > 1 && (long long)q.ntiles * q.splits <= (q.wt == 4 ? 512 : 1024))
+    for (long long c = s + 1; c <= s + s / 4; ++c) {
+      const double cc = plan(c);
+      if (cc < cost * 0.995) {
+        cost = cc;
+        best = c;
+      }
+    }
+  plan(best);
+  *chain = q.kchunk;
+  return q.splits;
+}
+
+// Tile shape and K splits of a token-contraction product: fewest_splits or more.  Beyond that the split count is a matter of
+// how well the workgroups fill the chip: 256 run at a time with 256x256 tiles, 512 with 128x128 ones, so the candidates are
+// the counts that just fill a number of rounds, and the cheapest of them is taken.  Costs are in contraction steps of 32 by one workgroup with 256x256 tiles (about 2.1 us with
 // four operand planes), fitted to sweeps over 126 .. 2048 workgroups: such a workgroup spends 7 of them on its first loads
 // and its epilogue; one of two with 128x128 tiles takes 1.5 times as long for the same area (its operands pass through
-// registers) and loses 4 steps of 64; a partial costs what it takes to read it back.  Gram of 1536 rows over 65536
-// tokens: 450 us with 17 splits (1.4 rounds), 371 with 12 (0.98).
+// registers) and loses 4 steps of 64; a partial costs what it takes to read it back.
 static void plan_nt_product(GemmP& p) {
-  const long long s_chain = (p.K + 8191) / 8192, s_max = p.K / 256 > s_chain ? p.K / 256 : s_chain;
+  long long chain;
+  const long long s_min = fewest_splits(p, &chain), s_max = p.K / 256 > s_min ? p.K / 256 : s_min;
+  const double area = 16384.0 * (double)((p.M + 127) / 128) * (double)((p.N + 127) / 128) * (p.triangle ? 0.5 : 1.0);
   double best_cost = 0.0;
   GemmP best;
   for (int wt = 4; wt >= 2; wt -= 2) {
@@ -662,14 +700,15 @@ static void plan_nt_product(GemmP& p) {
     const long long slots = wt == 4 ? 256 : 512;
     GemmP q = p;
     gemm_plan_tiles(q, 1, wt);
-    const long long r0 = (q.ntiles * s_chain + slots - 1) / slots;
-    for (long long r = r0; r < r0 + 8; ++r) {
+    const long long r0 = (q.ntiles * s_min + slots - 1) / slots;
+    for (long long r = r0 - 1; r < r0 + 8; ++r) {     // the first is fewest_splits itself
       long long s = r * slots / q.ntiles;
-      s = s < s_chain ? s_chain : (s > s_max ? s_max : s);
-      gemm_plan_tiles(q, (int)s, wt);
+      s = s < s_min ? s_min : (s > s_max ? s_max : s);
+      // a chunk is rounded up to stages of the tile
+      do gemm_plan_tiles(q, (int)s++, wt); while (q.kchunk > chain && q.kchunk > 64);
       const double rounds = (double)(((long long)q.ntiles * q.splits + slots - 1) / slots);
       const double steps = wt == 4 ? (double)q.kchunk / 32.0 + 7.0 : 1.5 * ((double)q.kchunk / 64.0 + 4.0);
-      const double cost = rounds * steps + (double)q.splits * (double)p.M * (double)p.N * (p.triangle ? 0.5 : 1.0) / 1.2e6;
+      const double cost = rounds * steps + (double)q.splits * area / 1.2e6;
       if (best_cost == 0.0 || cost < best_cost * 0.995) {
         best_cost = cost;
         best = q;
@@ -679,13 +718,14 @@ static void plan_nt_product(GemmP& p) {
   p = best;
 }
 
-static size_t nt_partial_elems(int M, int N, long long K, int triangle) {
+static size_t nt_splits(int M, int N, long long K, int triangle) {
   GemmP p;
   memset(&p, 0, sizeof(p));
   p.M = M; p.N = N; p.K = K; p.triangle = triangle;
   plan_nt_product(p);
-  return (size_t)p.splits * (size_t)M * (size_t)N;
+  return (size_t)p.splits;
 }
+static size_t nt_partial_elems(int M, int N, long long K, int triangle) { return nt_splits(M, N, K, triangle) * (size_t)M * (size_t)N; }
 
 // C = P Q^T over K (ROW planes); partials in the arena (by value: released on return), fp64 reduction into what r names.
 static strp_status nt_product(strp_ctx* ctx, Arena arena, const PlaneOp& P, const PlaneOp& Q, int M, int N, long long K, int triangle, ReduceP r) {

@@ -1,0 +1,96 @@
+"""The library's host side (argument checks, plans, workspace carving) on a HIP runtime that launches nothing (fake_hip.c):
+what is enqueued, without a GPU.  Each check runs in a process of its own, where the stand-in is loaded before the library."""
+import ctypes as C
+import os
+import subprocess
+import sys
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+
+# (rows of the result, columns, tokens), the longest fp32 accumulation chain it may have.  Gram matrices first (square):
+# module widths, kept counts and ragged sizes; then right-hand sides.
+CHAINS = [((64, 64, 512), 256), ((128, 128, 2000), 256), ((1536, 1536, 65536), 3872), ((1536, 1536, 16384), 992), ((768, 768, 65536), 1088),
+          ((768, 768, 16384), 288), ((832, 832, 65536), 1440), ((1013, 1013, 30011), 864), ((500, 500, 5000), 256), ((300, 300, 100000), 608),
+          ((3277, 3277, 262144), 8192), ((4915, 4915, 131072), 8192), ((768, 1536, 65536), 3648), ((768, 1536, 16384), 928),
+          ((1000, 1013, 30011), 1888), ((2048, 3277, 262144), 8192), ((4096, 4915, 131072), 8192), ((2048, 832, 65536), 5472), ((33, 70, 5000), 256)]
+
+
+class Library:
+    """The library on the stand-in, with a context and a workspace at an address nothing reads."""
+
+    def __init__(self, ws_bytes=1 << 40):
+        from unittest.mock import MagicMock
+        self.fake = C.CDLL(os.environ["FAKE_HIP"], mode=C.RTLD_GLOBAL)
+        self.fake.fake_name.restype = C.c_char_p
+        sys.modules["torch"] = MagicMock()          # the binding needs its names only
+        sys.path.insert(0, ROOT)
+        from paper_2510_03246_amd import strp
+        self.strp, self.lib, self.h = strp, strp.load_library(), C.c_void_p()
+        assert self.lib.strp_create(C.byref(self.h), 0, None) == strp.OK
+        self.workspace(ws_bytes)
+
+    def workspace(self, ws_bytes):
+        assert self.lib.strp_set_workspace(self.h, 1 << 40, ws_bytes) == self.strp.OK
+
+    def launches(self, call):
+        """status of call() and the (kernel, grid) it enqueued"""
+        self.fake.fake_clear()
+        st = call()
+        return st, [(self.fake.fake_name(i).decode(), tuple(self.fake.fake_grid(i, d) for d in range(3))) for i in range(self.fake.fake_count())]
+
+    def gram(self, s, T):
+        ld = (T + 7) // 8 * 8
+        return self.launches(lambda: self.lib.strp_gram(self.h, 1 << 50, self.strp.F32, s, T, ld, None, s, 1 << 51, s, None, 0))
+
+    def refit(self, m, s, T):
+        """fc2 refit of m outputs on s units with a factor in hand: one right-hand side"""
+        ld = (T + 7) // 8 * 8
+        return self.launches(lambda: self.lib.strp_refit(self.h, self.strp.SIDE_FC2, None, 0, 1.0, 1 << 52, 1, 1 << 50, self.strp.F32, ld, 1 << 51,
+                                                         self.strp.F32, ld, T, 1 << 53, s, 1 << 54, m, s))
+
+
+def splits_of(launches, M, N):
+    """tile rows (128 or 256) and K splits of the one token-contraction product among the launches"""
+    (name, grid), = [x for x in launches if "gemm_dma_kernel" in x[0] or "11gemm_kernel" in x[0]]
+    tile = 256 if "gemm_dma" in name else 128
+    tm, tn = -(-M // tile), -(-N // tile)
+    tiles = tm * (tm + 1) // 2 if M == N else tm * tn
+    assert grid[0] % tiles == 0
+    return tile, grid[0] // tiles
+
+
+def check_chains():
+    """No sum of products runs longer in fp32 than the bound of its shape."""
+    lib = Library()
+    for (M, N, T), chain in CHAINS:
+        st, launches = lib.gram(M, T) if M == N else lib.refit(M, N, T)
+        assert st == lib.strp.OK, (M, N, T)
+        tile, splits = splits_of(launches, M, N)
+        assert -(-T // splits) <= chain, (M, N, T, tile, splits)
+
+
+CHECKS = [check_chains]
+
+
+@pytest.fixture(scope="session")
+def fake_hip(tmp_path_factory):
+    so = str(tmp_path_factory.mktemp("fake") / "libfake_hip.so")
+    subprocess.run(["gcc", "-O1", "-Wall", "-shared", "-fPIC", "-o", so, os.path.join(ROOT, "tests", "fake_hip.c")], check=True, timeout=120)
+    return so
+
+
+@pytest.mark.parametrize("check", [c.__name__ for c in CHECKS])
+def test_host_side(fake_hip, check):
+    from paper_2510_03246_amd import strp
+    if not os.path.exists(strp.LIB_PATH):
+        import __graft_entry__
+        __graft_entry__.build()
+    out = subprocess.run([sys.executable, os.path.abspath(__file__), check], env=dict(os.environ, FAKE_HIP=fake_hip), capture_output=True, text=True,
+                         timeout=300)
+    assert out.returncode == 0, out.stdout + out.stderr
+
+
+if __name__ == "__main__":
+    globals()[sys.argv[1]]()
