@@ -726,6 +726,29 @@ static size_t nt_splits(int M, int N, long long K, int triangle) {
   return (size_t)p.splits;
 }
 static size_t nt_partial_elems(int M, int N, long long K, int triangle) { return nt_splits(M, N, K, triangle) * (size_t)M * (size_t)N; }
+// Most elements the split partials take where M or N or both (given as 0) are kept units, at most km of them.  The split count
+// is not monotone in their number; it changes between steps of 128 and at 256 (gemm_tile256_ok).
+static size_t nt_partial_most(int M, int N, long long K, int km) {
+  size_t most = 0;
+  for (int k0 = 0; k0 < km; k0 += 128) {
+    const int k1 = k0 + 128 < km ? k0 + 128 : km;
+    for (int k : {k0 + 1, k1}) {
+      const size_t e = nt_splits(M ? M : k, N ? N : k, K, !M && !N) * (size_t)(M ? M : k1) * (size_t)(N ? N : k1);
+      most = e > most ? e : most;
+    }
+  }
+  return most;
+}
+// The same for W W^T of d rows, a contraction over the kept units rounded up to 8: chunks go by stages of 32.
+static size_t nt_partial_most_over(int d, long long km) {
+  size_t most = 0;
+  for (long long k0 = 0; k0 < km; k0 += 32)
+    for (long long k : {k0 + 8, k0 + 32}) {
+      const size_t e = nt_partial_elems(d, d, k, 1);
+      most = e > most ? e : most;
+    }
+  return most;
+}
 
 // C = P Q^T over K (ROW planes); partials in the arena (by value: released on return), fp64 reduction into what r names.
 static strp_status nt_product(strp_ctx* ctx, Arena arena, const PlaneOp& P, const PlaneOp& Q, int M, int N, long long K, int triangle, ReduceP r) {
@@ -734,8 +757,8 @@ static strp_status nt_product(strp_ctx* ctx, Arena arena, const PlaneOp& P, cons
   p.P = P; p.Q = Q; p.M = M; p.N = N; p.K = K; p.triangle = triangle;
   p.epi = EPI_PARTIAL;
   plan_nt_product(p);
-  // a caller's workspace sized for other row counts may hold fewer partials than the plan's: as many as fit, but no
-  // chain longer than 8192 tokens
+  // a workspace below strp_workspace_bytes may hold fewer partials than the plan's: as many as fit, but no chain longer than
+  // 8192 tokens
   const long long chain = (K + 8191) / 8192, fit = (long long)(arena.room() / sizeof(float)) / ((long long)M * N);
   if (fit < p.splits && p.splits > chain) gemm_plan_tiles(p, (int)(fit > chain ? fit : chain), p.wt);
   STRP_TAKE(ctx, arena, part, float, (size_t)p.splits * M * N);
@@ -839,32 +862,38 @@ size_t strp_workspace_bytes(const strp_module_desc* desc) {
   const size_t tilesT = (size_t)((T + 127) / 128);
   const size_t red = al((((f + 127) / 128) * tilesT + f + 4096) * 16);
   // initialisation: weight planes, relu(Z0) planes, H partials
-  size_t init = 256 + 2 * (al(256) + 2 * al(plane_elems(f, d) * 2)) + 2 * al(plane_elems(T, f) * 2) + red +
+  size_t init = 256 + al(256) + 2 * al(plane_elems(f, d) * 2) + 2 * al(plane_elems(d, f) * 2) + 2 * al(plane_elems(T, f) * 2) + red +
                 al(nt_partial_elems((int)d, (int)d, T, 1) * 4) + al(d * 8) + al(invd_max) + 2 * al(d * d * 8);
   // one iteration: everything every stage carves (stages reuse the arena, so this is an upper bound)
   size_t part = 0;
   auto upd = [&](size_t e) { if (e > part) part = e; };
-  upd(nt_partial_elems((int)km, (int)km, T, 1));
-  upd(nt_partial_elems((int)d, (int)km, T, 0));
-  upd(nt_partial_elems((int)km, (int)d, T, 0));
-  upd(nt_partial_elems((int)d, (int)d, (long long)kp, 1));
-  upd(nt_partial_elems((int)d, (int)d, T, 1));   // E E^T of the objective
-  const size_t segs = (size_t)((T + 8191) / 8192);
-  size_t step = 256 + al(4 * f * 8) + al(d * kp * 4) + al(km * d * 4) +
-                /* the pruned rows' pass: its sums, the row list, the unit counter, the units' partial sums */
-                al(2 * f * 8) + al(f * 4) + 256 + al(f * segs * 6 * 8) +
-                (al(256) + 2 * al(plane_elems(d, km) * 2)) + 2 * (al(256) + 2 * al(plane_elems(km, d) * 2)) +
-                al(part * 4) + 3 * al(nmax * nmax * 8) + 2 * al(invd_max) + al(d * km * 8) * 4 + 2 * al(d * d * 8) +
+  upd(nt_partial_most(0, 0, T, (int)km));
+  upd(nt_partial_most((int)d, 0, T, (int)km));
+  upd(nt_partial_most(0, (int)d, T, (int)km));
+  upd(nt_partial_elems((int)d, (int)d, T, 1));   // H; E E^T of the objective
+  const size_t wwt = nt_partial_most_over((int)d, (long long)kp);
+  upd(wwt);
+  const size_t segs = (size_t)((T + 8191) / 8192), slots = (size_t)((T + 63) / 64);
+  const size_t w_blocks = ((d + 63) / 64 + 1) * ((km + 31) / 32 + 1) + ((km + 63) / 64 + 1) * ((d + 31) / 32 + 1) + 2048;
+  size_t step = 256 + al(256) + al(4 * f * 8) +
+                /* the refitted weights of the kept units and their sums of squares */
+                al(d * kp * 4) + al(km * d * 4) + al(w_blocks * 8) +
+                /* the pruned rows' pass: the row list, the units' partial sums, the workgroups' (or the rows') sums */
+                al(f * 4) + al(f * segs * 6 * 8) + al(2 * f * 8) +
+                /* planes of the kept weights (both orders of W2) and of B */
+                2 * al(plane_elems(d, km) * 2) + 3 * 2 * al(plane_elems(km, d) * 2) + al(km * d * 4) +
+                /* fc2 and fc1 refit: system and factor, their rows padded to 8, scratch of the chain, right-hand side and solve */
+                al(part * 4) + 3 * al(nmax * (nmax + 8) * 8) + 2 * al(invd_max) + 4 * al(d * km * 8) + 2 * al((d + km) * 8 * 8) + 2 * al(d * d * 8) +
                 2 * al(plane_elems(km, T) * 2) /* kept rows, token contraction */ +
                 2 * al(plane_elems(T, km) * 2) /* kept rows, channel contraction */ +
                 2 * al(plane_elems(T, d) * 2) /* E */ + red +
-                al(plane_elems(d, T) * 2) + al(d * d * 8) + al(d * d * 4) /* objective: E by tokens, E E^T, M^-2 */ +
-                /* the M-inverse chain keeps its block while the fc1 refit runs beside it */
-                al(nt_partial_elems((int)d, (int)d, (long long)kp, 1) * 4) + al(d * d * 8) + al(invd_max) +
-                2 * (al(256) + 2 * al(plane_elems(km, d) * 2)) + (al(256) + 2 * al(plane_elems(d, d) * 2)) + al(plane_elems(T, km) * 2) + 8192 +
+                /* objective: E by tokens, M^-2, the reduction's sums; without the identity A's plane */
+                al(plane_elems(d, T) * 2) + al(d * d * 4) + al((size_t)reduce_blocks((int)d, (int)d) * 8) + al(plane_elems(T, km) * 2) +
+                /* M, its factor's inverse, and the block of the M-inverse chain, which stays while the fc1 refit runs */
+                2 * al(d * d * 8) + al(wwt * 4) + al(invd_max) + 2 * al(plane_elems(d, d) * 2) + 8192 +
                 /* strip sums of the kept rows from the a- and z-update epilogues */
-                al(2 * (size_t)((T + 63) / 64) * km * 4) + al((size_t)((T + 63) / 64) * km * 4);
-  return (init > step ? init : step) + (1 << 20);
+                al(2 * slots * km * 4) + al(slots * km * 4);
+  return (init > step ? init : step) + (2 << 20);
 }
 
 strp_status strp_gram(strp_ctx* ctx, const void* A, strp_dtype dt, int32_t C, int64_t T, int64_t ldA, const int32_t* idx,

@@ -71,7 +71,52 @@ def check_chains():
         assert -(-T // splits) <= chain, (M, N, T, tile, splits)
 
 
-CHECKS = [check_chains]
+# d, f, tokens, k_max (0: f) of modules: configurations' widths, ragged ones, few tokens, and kept counts below k_max whose plans have more
+# splits than k_max's
+MODULES = [(64, 256, 512, 128), (768, 3072, 65536, 1536), (1000, 2312, 30011, 1013), (8, 16, 9, 0), (256, 2080, 92284, 520), (64, 1024, 200000, 300),
+           (2048, 8192, 3000, 3277), (4096, 16384, 2048, 4915), (136, 520, 1003, 0), (264, 1000, 70000, 259),
+           (48, 14912, 13, 9), (16, 8000, 13831, 1576)]
+
+
+def check_workspace_of_a_module():
+    """strp_workspace_bytes is enough for every call on the module, whatever its kept count, and no call's work depends on
+    how much more there is: the launches are those of an endless workspace."""
+    lib = Library()
+    strp = lib.strp
+    for d, f, T, k_max in MODULES:
+        ld = (T + 7) // 8 * 8
+        desc = strp.ModuleDesc(d, f, T, ld, ld, strp.F32, strp.F32, k_max)
+        need = lib.lib.strp_workspace_bytes(C.byref(desc))
+        top = k_max or f
+        kept = sorted({1, top // 3 + 1, top} | {min(top, k) for k in (2, 63, 129, 255, 256, 257, 300, 385, 510, 513, max(1, top - 1))})
+
+        def calls():
+            out = []
+            for k in kept:
+                st = strp.ModuleState()
+                for name, kind in strp.ModuleState._fields_:
+                    if kind is C.c_void_p:
+                        setattr(st, name, 1 << 50)
+                p = strp.Params(1.0, 1.0, 0.01, strp.GAIN, 1, k, 0)
+                out.append(lib.launches(lambda: lib.lib.strp_module_init(lib.h, C.byref(desc), C.byref(st), C.byref(p))))
+                for stages in (0, 1, 2, 4, 8 | 32, 16 | 32, 63 - 2, 63 - 8):
+                    p.stages = stages | (0 if st.s else 1)
+                    out.append(lib.launches(lambda: lib.lib.strp_admm_step(lib.h, C.byref(desc), C.byref(st), C.byref(p), None)))
+                out.append(lib.gram(k, T))
+                out.append(lib.refit(d, k, T))
+            out.append(lib.gram(d, T))
+            return out
+
+        lib.workspace(1 << 50)
+        endless = calls()
+        lib.workspace(need)
+        exact = calls()
+        for i, (a, b) in enumerate(zip(endless, exact)):
+            assert a[0] == b[0] == strp.OK, (d, f, T, k_max, i, a[0], b[0], lib.lib.strp_last_error(lib.h))
+            assert a[1] == b[1], (d, f, T, k_max, i, [x for x in zip(a[1], b[1]) if x[0] != x[1]])
+
+
+CHECKS = [check_chains, check_workspace_of_a_module]
 
 
 @pytest.fixture(scope="session")
