@@ -1047,7 +1047,14 @@ strp_status strp_module_init(strp_ctx* ctx, const strp_module_desc* desc, strp_m
     STRP_TRY(nt_product(ctx, a2, cv.Xt, cv.Xt, d, d, T, 1, r));
     hipLaunchKernelGGL(scaled_sum_kernel, dim3(1), dim3(1024), 0, ctx->stream, (const double*)diag, 1, d, params->delta / (double)d, sc + SC_TRH,
                        sc + SC_LAM1, Hd, (long long)d, d);
-    STRP_TRY(factor_and_invert(ctx, a2, Hd, d, st->cholH, d));
+    // the chain wants its result 16-byte aligned; cholH need not be
+    double* Linv = st->cholH;
+    if (!aligned16(Linv)) {
+      STRP_TAKE(ctx, a2, scratch, double, (size_t)d * d);
+      Linv = scratch;
+    }
+    STRP_TRY(factor_and_invert(ctx, a2, Hd, d, Linv, d));
+    if (Linv != st->cholH) STRP_TRY(copy_f64(ctx, Linv, d, st->cholH, d, d));
   }
   STRP_HIP(ctx, hipGetLastError());
   st->s = 0;

@@ -46,3 +46,23 @@ def test_factor_inverse_and_solve(ctx, n, m):
     W2 = torch.zeros_like(W)
     ctx.strp_refit(strp.SIDE_FC2, None, lam, dev(lhs), dev(rhs), T, idx, W2, chol=chol, chol_valid=True)
     assert torch.equal(W, W2)
+
+
+def test_module_with_an_unaligned_cached_factor():
+    """cholH at an address that is a multiple of 8 only: the same numbers as at one of 16."""
+    from paper_2510_03246_amd import inputs
+    cfg = inputs.CONFIGS["tiny"]
+    m = inputs.make_ffn_module(cfg, 0, 0, "cuda")
+    params = strp.Params(1.0, 1.0, 0.01, strp.WANDA, 1, 100, 0)
+    out = []
+    for off in (0, 1):
+        c = strp.Context(0)
+        mod = strp.FFNModule(c, m["W1hat"], m["W2hat"], m["X"], cfg.T)
+        room = torch.empty(cfg.d * cfg.d + off, dtype=torch.float64, device="cuda")
+        chol = room[off:].view(cfg.d, cfg.d)
+        mod.state.cholH = chol.data_ptr()
+        mod.init(params)
+        assert mod.step(params).status == strp.OK
+        out.append((chol.clone(), mod.W1.clone(), mod.W2.clone(), mod.A.clone(), mod.Z.clone()))
+    for a, b in zip(*out):
+        assert torch.equal(a, b)

@@ -116,7 +116,23 @@ def check_workspace_of_a_module():
             assert a[1] == b[1], (d, f, T, k_max, i, [x for x in zip(a[1], b[1]) if x[0] != x[1]])
 
 
-CHECKS = [check_chains, check_workspace_of_a_module]
+def check_cached_factor_needs_no_alignment():
+    """cholH is an array of doubles like any other, in exactly the workspace asked for."""
+    lib = Library()
+    strp = lib.strp
+    desc = strp.ModuleDesc(264, 520, 1000, 1000, 1000, strp.F32, strp.F32, 130)
+    lib.workspace(lib.lib.strp_workspace_bytes(C.byref(desc)))
+    st = strp.ModuleState()
+    for name, kind in strp.ModuleState._fields_:
+        if kind is C.c_void_p:
+            setattr(st, name, 1 << 50)
+    st.cholH = (1 << 50) + 8
+    p = strp.Params(1.0, 1.0, 0.01, strp.WANDA, 1, 130, 0)
+    assert lib.lib.strp_module_init(lib.h, C.byref(desc), C.byref(st), C.byref(p)) == strp.OK
+    assert lib.lib.strp_admm_step(lib.h, C.byref(desc), C.byref(st), C.byref(p), None) == strp.OK
+
+
+CHECKS = [check_chains, check_workspace_of_a_module, check_cached_factor_needs_no_alignment]
 
 
 @pytest.fixture(scope="session")
