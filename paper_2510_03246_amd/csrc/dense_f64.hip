@@ -290,7 +290,8 @@ struct StepShared {
 // Diagonal block: A = Lu D Lu^T (Lu unit lower) by 16-column panels, and W = Lu^-1.
 //   in : S = sh.a, pitch SL, lower triangle (rows past a ragged edge are the identity)
 //   out: sh.b, pitch SL: W (strict upper part of the 16 x 16 diagonal blocks zero, blocks above them untouched);
-//        sh.piv: the pivots D.  L^-1 = D^-1/2 W.
+//        sh.piv: the pivots D.  L^-1 = D^-1/2 W.  One that is not positive counts as 1 (pivot_or_one): the caller raises
+//        ENOTPD, and everything stays finite.
 // The chain of 64 dependent pivots is what bounds it, so one wavefront runs it out of registers: every 16-lane row of
 // the wavefront holds a copy of the panel's 16 x 16 diagonal block (d: lane = row, register = column), so pivots and
 // multiplier rows are broadcast by row_newbcast moves (no LDS, no barrier, no scalar registers); beside it lanes 16 .. 63
@@ -302,7 +303,9 @@ struct StepShared {
 struct PanelRegs {
   double d[16], a[16];
   double dj, y, e;      // pivot, its reciprocal (in the making)
+  bool ok;              // the pivot is positive
 };
+__device__ __forceinline__ double pivot_or_one(double d) { return d > 0.0 ? d : 1.0; }
 // v_rcp_f64 is good to 2^-23; y (1 + e + e^2), e = 1 - d y, leaves e^3
 constexpr int PIVOT_STAGES = 5;
 template <int STAGE>
@@ -313,8 +316,14 @@ __device__ __forceinline__ void pivot_stage(PanelRegs& g, double next, double* p
   }
   if constexpr (STAGE == 1) g.y = __builtin_amdgcn_rcp(g.dj);
   if constexpr (STAGE == 2) g.e = __builtin_fma(-g.dj, g.y, 1.0);
-  if constexpr (STAGE == 3) g.e = __builtin_fma(g.e, g.e, g.e);
-  if constexpr (STAGE == 4) g.y = __builtin_fma(g.e, g.y, g.y);
+  if constexpr (STAGE == 3) {
+    g.e = __builtin_fma(g.e, g.e, g.e);
+    g.ok = g.dj > 0.0;
+  }
+  if constexpr (STAGE == 4) {
+    const double y = __builtin_fma(g.e, g.y, g.y);
+    g.y = g.ok ? y : 1.0;
+  }
   __builtin_amdgcn_sched_barrier(0);
 }
 template <int STAGE>
@@ -382,7 +391,7 @@ __device__ __forceinline__ void diag_block(StepShared& sh, int tid) {
 #pragma unroll
     for (int s = 0; s < 4; ++s) {
       const int kk = 16 * p + 4 * s + lq;
-      acc[s & 1] = mma_f64(S[(16 * i + l16) * SL + kk], S[(16 * k + l16) * SL + kk] * sh.piv[kk], acc[s & 1]);
+      acc[s & 1] = mma_f64(S[(16 * i + l16) * SL + kk], S[(16 * k + l16) * SL + kk] * pivot_or_one(sh.piv[kk]), acc[s & 1]);
     }
 #pragma unroll
     for (int r = 0; r < 4; ++r) S[(16 * i + 4 * r + lq) * SL + 16 * k + l16] -= acc[0][r] + acc[1][r];
@@ -605,9 +614,8 @@ __device__ __forceinline__ void finish_diag(const StepP& p, int t, StepShared& s
   const int jb = p.n - t * NB < NB ? p.n - t * NB : NB;
   if (tid < NB) {
     const double d = sh.piv[tid];
-    const bool ok = d > 0.0;
-    if (__any(!ok) && tid == 0) atomicCAS(p.status, 0, (int)STRP_ENOTPD);
-    sh.piv[tid] = rsqrt_f64(ok ? d : 1.0);
+    if (__any(!(d > 0.0)) && tid == 0) atomicCAS(p.status, 0, (int)STRP_ENOTPD);
+    sh.piv[tid] = rsqrt_f64(pivot_or_one(d));
   }
   lds_barrier();
   double* vd = p.V + (long long)t * NB * p.ldv + (long long)t * NB;

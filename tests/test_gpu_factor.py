@@ -48,6 +48,38 @@ def test_factor_inverse_and_solve(ctx, n, m):
     assert torch.equal(W, W2)
 
 
+@pytest.mark.parametrize("n,bad", [(5, [0]), (64, [15, 16]), (70, [63]), (130, [64, 100]), (200, [17, 130, 199])])
+@pytest.mark.parametrize("kind", ["zero", "negative"])
+def test_pivots_that_are_not_positive(ctx, n, bad, kind):
+    """ENOTPD, and the factor of the elimination that goes on with 1 in their place: finite, like the weights.  A row and column
+    of zeros (pivot exactly 0), or a diagonal entry that leaves the pivot near -0.5.  fp64 elimination of a system whose
+    pivots lie between 0.05 and 3: 1e-10."""
+    rng = np.random.default_rng(n)
+    B = rng.normal(size=(n, 2 * n)) / np.sqrt(2 * n)
+    G = (B @ B.T + 0.5 * np.eye(n)).astype(np.float32)
+    for b in bad:
+        if kind == "zero":
+            G[b, :] = G[:, b] = 0.0
+        else:
+            G[b, b] -= np.float32(1.0 / np.linalg.inv(G[:b + 1, :b + 1].astype(np.float64))[b, b] + 0.5)
+    S, D, L = np.tril(G.astype(np.float64)), np.empty(n), np.eye(n)
+    for j in range(n):
+        D[j] = S[j, j] if S[j, j] > 0 else 1.0
+        L[j + 1:, j] = S[j + 1:, j] / D[j]
+        S[j + 1:, j + 1:] -= np.tril(np.outer(L[j + 1:, j], L[j + 1:, j]) * D[j])
+    ref = np.linalg.inv(L) / np.sqrt(D)[:, None]
+    T = 24
+    lhs, rhs = (torch.randint(-4, 5, (r, T), device="cuda").float() for r in (9, n))
+    idx = torch.arange(n, dtype=torch.int32, device="cuda")
+    W = torch.empty((9, n), device="cuda")
+    chol = torch.empty((n, n), dtype=torch.float64, device="cuda")
+    ctx.strp_refit(strp.SIDE_FC2, torch.from_numpy(G).cuda(), 0.0, lhs, rhs, T, idx, W, chol=chol, chol_valid=False)
+    assert ctx.poll() == strp.ENOTPD
+    got = chol.cpu().numpy()
+    assert np.isfinite(got).all() and bool(torch.isfinite(W).all())
+    assert np.linalg.norm(got - ref) <= 1e-10 * np.linalg.norm(ref)
+
+
 def test_module_with_an_unaligned_cached_factor():
     """cholH at an address that is a multiple of 8 only: the same numbers as at one of 16."""
     from paper_2510_03246_amd import inputs
