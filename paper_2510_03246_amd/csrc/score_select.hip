@@ -315,9 +315,9 @@ strp_status launch_unit_scores(strp_ctx* ctx, const double* sums, const double* 
 // ---------------------------------------------------------------------------------------------
 // weight statistics of a parameter group (Alg. 2 step 1): sum |w|, sum w, sum w^2 over every entry of a list of
 // matrices, folded into  energy += scale (|W|_1 + cv Var(W) + c2 |W|_2).
-// A model has a few hundred small groups (a head's four slices are 0.4 MB), so a call costs its launches: one launch takes
-// up to eight matrices, and its last workgroup (device counter) adds the workgroups' partial sums in order.
-// 12 layers of d = 768: 168 calls 3.5 -> 1.0 ms.
+// A model has a few hundred small groups (a head's four slices are 0.4 MB), so a call costs its launches: one for up to eight
+// matrices, and one that adds the workgroups' partial sums in order.  (The last workgroup of the first could add them
+// instead, told by a counter; the counter would have to survive in the caller's scratch between calls.)
 // ---------------------------------------------------------------------------------------------
 constexpr int WSTAT_BLOCKS = 256, WSTAT_MATS = 8;
 
@@ -328,8 +328,6 @@ struct WeightList {
   int block0[WSTAT_MATS + 1];            // workgroups block0[m] .. block0[m + 1] - 1 take matrix m
   unsigned char bf16[WSTAT_MATS], vec[WSTAT_MATS];
   int n;
-  int first, last;                       // first / last launch of the call
-  double count, var_coef, l2_coef, scale;
 };
 
 template <bool BF16>
@@ -363,8 +361,8 @@ __device__ __forceinline__ void weight_sums(const WeightList& l, int m, unsigned
   }
 }
 
-// partial: [WSTAT_BLOCKS][3]; run: the sums of earlier launches of the same call [3]; ticket: zero between launches
-__global__ __launch_bounds__(256) void weight_energy_kernel(const WeightList l, double* partial, double* run, unsigned int* ticket, double* energy) {
+// partial: [WSTAT_BLOCKS][3]; the first `filled` entries hold the sums of earlier launches of the same call
+__global__ __launch_bounds__(256) void weight_sums_kernel(const WeightList l, int filled, double* partial) {
   double s1 = 0.0, s = 0.0, s2 = 0.0;
   int m = 0;
   while (m + 1 < l.n && (int)blockIdx.x >= l.block0[m + 1]) ++m;
@@ -372,7 +370,6 @@ __global__ __launch_bounds__(256) void weight_energy_kernel(const WeightList l, 
   if (l.bf16[m]) weight_sums<true>(l, m, b, blocks, s1, s, s2);
   else weight_sums<false>(l, m, b, blocks, s1, s, s2);
   __shared__ double red[4][3];
-  __shared__ unsigned int last;
   s1 = wave_sum_d(s1);
   s = wave_sum_d(s);
   s2 = wave_sum_d(s2);
@@ -383,38 +380,36 @@ __global__ __launch_bounds__(256) void weight_energy_kernel(const WeightList l, 
     red[wave][2] = s2;
   }
   __syncthreads();
-  if (tid < 3) agent_put(&partial[3 * blockIdx.x + tid], red[0][tid] + red[1][tid] + red[2][tid] + red[3][tid]);
-  if (!last_block(ticket, &last) || tid >= 64) return;
+  if (tid < 3) {
+    double* p = &partial[3 * blockIdx.x + tid];
+    const double before = (int)blockIdx.x < filled ? *p : 0.0;
+    *p = before + (red[0][tid] + red[1][tid] + red[2][tid] + red[3][tid]);
+  }
+}
+
+__global__ __launch_bounds__(64) void weight_energy_kernel(const double* partial, int filled, double count, double var_coef, double l2_coef, double scale,
+                                                           double* energy) {
   double a[3] = {0.0, 0.0, 0.0};
-  for (int b = tid; b < (int)gridDim.x; b += 64)
+#pragma unroll 4
+  for (int b = threadIdx.x; b < filled; b += 64)
 #pragma unroll
-    for (int q = 0; q < 3; ++q) a[q] += agent_get(&partial[3 * b + q]);
+    for (int q = 0; q < 3; ++q) a[q] += partial[3 * b + q];
 #pragma unroll
   for (int q = 0; q < 3; ++q) a[q] = wave_allsum_d(a[q]);
-  if (tid != 0) return;
-  *ticket = 0u;
-  if (!l.first)
-    for (int q = 0; q < 3; ++q) a[q] += run[q];
-  if (!l.last) {
-    for (int q = 0; q < 3; ++q) run[q] = a[q];
-    return;
-  }
-  const double mean = a[1] / l.count;
-  const double var = a[2] / l.count - mean * mean;
-  *energy += l.scale * (a[0] + l.var_coef * var + l.l2_coef * sqrt(a[2]));
+  if (threadIdx.x != 0) return;
+  const double mean = a[1] / count;
+  const double var = a[2] / count - mean * mean;
+  *energy += scale * (a[0] + var_coef * var + l2_coef * sqrt(a[2]));
 }
 
 strp_status launch_weight_energy(strp_ctx* ctx, const strp_weight_ref* mats, int n_mats, double var_coef, double l2_coef, double scale,
                                  double* energy, double* partial) {
   WeightList l;
-  l.var_coef = var_coef; l.l2_coef = l2_coef; l.scale = scale;
-  l.count = 0.0;
-  for (int i = 0; i < n_mats; ++i) l.count += (double)mats[i].rows * (double)mats[i].cols;
-  unsigned int* ticket = (unsigned int*)ctx->status_dev + WS_TICKET;
+  double count = 0.0;
+  int filled = 0;
+  for (int i = 0; i < n_mats; ++i) count += (double)mats[i].rows * (double)mats[i].cols;
   for (int i0 = 0; i0 < n_mats; i0 += WSTAT_MATS) {
     l.n = n_mats - i0 < WSTAT_MATS ? n_mats - i0 : WSTAT_MATS;
-    l.first = i0 == 0;
-    l.last = i0 + l.n == n_mats;
     l.block0[0] = 0;
     for (int i = 0; i < l.n; ++i) {
       const strp_weight_ref& m = mats[i0 + i];
@@ -426,8 +421,10 @@ strp_status launch_weight_energy(strp_ctx* ctx, const strp_weight_ref* mats, int
       const int most = WSTAT_BLOCKS / (l.n > 2 ? l.n : 2);
       l.block0[i + 1] = l.block0[i] + (want < 1.0 ? 1 : want > most ? most : (int)want);
     }
-    hipLaunchKernelGGL(weight_energy_kernel, dim3(l.block0[l.n]), dim3(256), 0, ctx->stream, l, partial, (double*)(ctx->status_dev + WS_SUMS), ticket, energy);
+    hipLaunchKernelGGL(weight_sums_kernel, dim3(l.block0[l.n]), dim3(256), 0, ctx->stream, l, filled, partial);
+    filled = l.block0[l.n] > filled ? l.block0[l.n] : filled;
   }
+  hipLaunchKernelGGL(weight_energy_kernel, dim3(1), dim3(64), 0, ctx->stream, (const double*)partial, filled, count, var_coef, l2_coef, scale, energy);
   STRP_HIP(ctx, hipGetLastError());
   return STRP_OK;
 }

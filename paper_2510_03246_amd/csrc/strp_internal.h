@@ -57,10 +57,8 @@ strp_status fail(strp_ctx* ctx, strp_status st, const char* fmt, ...);
     if (s_ != STRP_OK) return s_;       \
   } while (0)
 
-// ---- workspace bump arena (256-byte granules); the first granule holds the status word and, WS_TICKET words on, a counter
-// of finished workgroups that every launch using it leaves at zero (strp_set_workspace clears the granule), and WS_SUMS words
-// on three doubles of running sums --
-constexpr int WS_TICKET = 16, WS_SUMS = 32;
+// ---- workspace bump arena (256-byte granules); the first granule holds the status word, the only thing in the workspace
+// that lasts from one call to the next ----
 struct Arena {
   char* base;
   size_t off, cap;

@@ -78,6 +78,23 @@ def test_weight_energy_lists(ctx, shapes):
     assert abs(float(energy.item()) - want) <= 1e-12 * want
 
 
+def test_weight_energy_in_a_used_workspace(ctx):
+    """The workspace is scratch: what lies in it beyond the status word does not matter to a call."""
+    g = torch.Generator(device="cuda").manual_seed(1)
+    mats = [torch.randn((40, 64), generator=g, device="cuda") for _ in range(9)]
+    got = []
+    for fill in (0, 1, 255):
+        energy = torch.zeros(1, dtype=torch.float64, device="cuda")
+        ctx.ensure_workspace(1 << 16)
+        ctx.ws[4:].fill_(fill)
+        ctx.strp_weight_energy(mats, 0.3, 0.7, 1.5, energy)
+        assert ctx.poll() == strp.OK
+        got.append(float(energy.item()))
+    w = torch.cat([m.double().reshape(-1) for m in mats])
+    want = 1.5 * float(w.abs().sum() + 0.3 * w.var(correction=0) + 0.7 * w.norm())
+    assert got == [got[0]] * 3 and abs(got[0] - want) <= 1e-12 * want
+
+
 @pytest.mark.parametrize("rows,cols,pad,dtype", [(1, 8, 0, torch.bfloat16), (129, 64, 0, torch.bfloat16), (300, 200, 8, torch.float32),
                                                  (130, 72, 3, torch.bfloat16), (77, 136, 0, torch.float32)])
 def test_scores_with_column_norms(ctx, rows, cols, pad, dtype):
