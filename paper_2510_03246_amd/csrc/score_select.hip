@@ -353,10 +353,16 @@ __device__ __forceinline__ void weight_sums(const WeightList& l, int m, unsigned
       for (int q = 0; q < 8; ++q) add(x[q]);
     }
   } else {
-    const long long n = (long long)l.rows[m] * cols;
-    for (long long e = (long long)b * 256 + threadIdx.x; e < n; e += step) {
-      const long long r = e / cols;
-      add(load1<BF16>(W, r * ld + (e - r * cols)));
+    // entry by entry; row and column go on by the step's own (a division per entry cost more than its load)
+    const unsigned int e = b * 256u + threadIdx.x, dr = step / cols, dc = step % cols;
+    unsigned int c = e % cols;
+    for (long long r = e / cols; r < l.rows[m]; r += dr) {
+      add(load1<BF16>(W, r * ld + c));
+      c += dc;
+      if (c >= (unsigned int)cols) {
+        c -= cols;
+        ++r;
+      }
     }
   }
 }
@@ -410,17 +416,22 @@ strp_status launch_weight_energy(strp_ctx* ctx, const strp_weight_ref* mats, int
   for (int i = 0; i < n_mats; ++i) count += (double)mats[i].rows * (double)mats[i].cols;
   for (int i0 = 0; i0 < n_mats; i0 += WSTAT_MATS) {
     l.n = n_mats - i0 < WSTAT_MATS ? n_mats - i0 : WSTAT_MATS;
-    l.block0[0] = 0;
+    double cost[WSTAT_MATS], total = 0.0;
     for (int i = 0; i < l.n; ++i) {
       const strp_weight_ref& m = mats[i0 + i];
       l.W[i] = m.W; l.rows[i] = m.rows; l.cols[i] = m.cols; l.ld[i] = m.ld;
       l.bf16[i] = m.dtype == STRP_BF16;
       l.vec[i] = ((uintptr_t)m.W & 15) == 0 && m.cols % 8 == 0 && m.ld % 8 == 0 && (double)m.rows * m.cols < 3.0e10;
-      // four groups of eight entries per thread and more, all requested at once; few workgroups, which add up one by one
-      const double want = (double)m.rows * m.cols / (32.0 * 256.0);
-      const int most = WSTAT_BLOCKS / (l.n > 2 ? l.n : 2);
-      l.block0[i + 1] = l.block0[i] + (want < 1.0 ? 1 : want > most ? most : (int)want);
+      // workgroups' worth of work: four groups of eight entries per thread, all requested at once; an entry that comes by
+      // itself takes about five times as long as one of a group (67 million: 298 us against 57 with 256 workgroups)
+      cost[i] = (double)m.rows * m.cols / (32.0 * 256.0) * (l.vec[i] ? 1.0 : 5.0) + 1.0;
+      total += cost[i];
     }
+    // the workgroups are dealt out by the work: with an even share by place in the list, a matrix of 2048 x 8193 behind seven
+    // small ones took 715 us instead of 81
+    l.block0[0] = 0;
+    for (int i = 0; i < l.n; ++i)
+      l.block0[i + 1] = l.block0[i] + (total <= WSTAT_BLOCKS ? (int)cost[i] : 1 + (int)((WSTAT_BLOCKS - l.n) * (cost[i] / total)));
     hipLaunchKernelGGL(weight_sums_kernel, dim3(l.block0[l.n]), dim3(256), 0, ctx->stream, l, filled, partial);
     filled = l.block0[l.n] > filled ? l.block0[l.n] : filled;
   }

@@ -56,9 +56,11 @@ def test_topk_groups_without_workspace(n, k, group, kind):
     assert bare.lib.strp_mask_topk(bare.h, s.data_ptr(), n, k, 1, mask.data_ptr(), idx.data_ptr(), tau.data_ptr()) == strp.ENOMEM
 
 
-@pytest.mark.parametrize("shapes", [[(1, 1)], [(7, 13)], [(64, 768)] * 4, [(33, 40)] * 8, [(5, 8)] * 9, [(3000, 264), (2, 3), (128, 8)] * 6])
+@pytest.mark.parametrize("shapes", [[(1, 1)], [(7, 13)], [(64, 768)] * 4, [(33, 40)] * 8, [(5, 8)] * 9, [(3000, 264), (2, 3), (128, 8)] * 6, [(1100, 1027)],
+                                    [(3, 5)] * 7 + [(700, 1501)], [(2048, 1024), (64, 65)]])
 def test_weight_energy_lists(ctx, shapes):
-    """Lists below, at and above what one launch takes; aligned, unaligned and one-entry matrices of both types.  fp64
+    """Lists below, at and above what one launch takes; aligned, unaligned and one-entry matrices of both types, alone
+    and beside others of another size.  fp64
     sums of at most 5e6 terms: 1e-12."""
     g = torch.Generator(device="cuda").manual_seed(len(shapes))
     mats = []

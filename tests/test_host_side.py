@@ -132,7 +132,30 @@ def check_cached_factor_needs_no_alignment():
     assert lib.lib.strp_admm_step(lib.h, C.byref(desc), C.byref(st), C.byref(p), None) == strp.OK
 
 
-CHECKS = [check_chains, check_workspace_of_a_module, check_cached_factor_needs_no_alignment]
+def check_weight_statistics_workgroups():
+    """A matrix has the workgroups its size calls for wherever it stands in a list: a large one nearly all 256, also
+    beside small ones, a small one few; never more than the scratch has sums for."""
+    lib = Library()
+    strp = lib.strp
+
+    def grid(shapes):
+        refs = (strp.WeightRef * len(shapes))(*[strp.WeightRef(1 << 50, strp.F32, r, c, c) for r, c in shapes])
+        st, launches = lib.launches(lambda: lib.lib.strp_weight_energy(lib.h, refs, len(shapes), 0.1, 0.1, 1.0, 1 << 51))
+        assert st == strp.OK
+        return launches[0][1][0]
+
+    for shape in ((4096, 16384), (4096, 16385), (1024, 1025)):
+        assert 240 <= grid([shape]) <= 256
+        assert 240 <= grid([shape] + [(8, 8)] * 7) <= 256 and 240 <= grid([(3, 5)] * 7 + [shape]) <= 256
+        assert 240 <= grid([shape] * 8) <= 256
+    assert grid([(64, 768)] * 4) <= 64 and grid([(1, 1)] * 8) == 8
+    rng = __import__("random").Random(3)
+    for _ in range(300):
+        n = rng.randint(1, 8)
+        assert n <= grid([(rng.randint(1, 3000), rng.randint(1, 3000)) for _ in range(n)]) <= 256
+
+
+CHECKS = [check_weight_statistics_workgroups, check_chains, check_workspace_of_a_module, check_cached_factor_needs_no_alignment]
 
 
 @pytest.fixture(scope="session")
