@@ -270,10 +270,10 @@ class Context:
         # a model has hundreds of small groups, so a call's cost is this marshalling: the WeightRef array is packed in one go
         args = []
         for m in mats:
-            rows, cols = m.shape
-            args += (m.data_ptr(), dtype_code(m), rows, cols, m.stride(0))
+            args += (m.data_ptr(), dtype_code(m), m.shape[0], m.shape[1], m.stride(0))
         refs = _pack_refs(len(mats))(*args)
-        self.check(self.lib.strp_weight_energy(self.h, refs, len(mats), var_coef, l2_coef, scale, energy.data_ptr()))
+        # float(): coefficients may be numpy scalars or one-element tensors, which ctypes does not take
+        self.check(self.lib.strp_weight_energy(self.h, refs, len(mats), float(var_coef), float(l2_coef), float(scale), _ptr(energy)))
 
     def strp_alloc_inverse(self, energies, n_units, rbar, temperature, rmax=0.95, group_id=None):
         L = energies.numel()

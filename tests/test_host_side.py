@@ -155,7 +155,40 @@ def check_weight_statistics_workgroups():
         assert n <= grid([(rng.randint(1, 3000), rng.randint(1, 3000)) for _ in range(n)]) <= 256
 
 
-CHECKS = [check_weight_statistics_workgroups, check_chains, check_workspace_of_a_module, check_cached_factor_needs_no_alignment]
+def check_weight_statistics_arguments():
+    """The binding takes what float() takes for the coefficients, matrices with further dimensions of 1, and answers a missing
+    energy or an empty list with the library's error."""
+    from fractions import Fraction
+
+    import numpy as np
+    lib = Library()
+    strp, torch = lib.strp, sys.modules["torch"]
+
+    class Tensor:
+        dtype = torch.float32
+
+        def __init__(self, *shape):
+            self.shape = shape
+
+        def data_ptr(self):
+            return 1 << 50
+
+        def stride(self, dim):
+            return self.shape[1]
+
+    ctx = strp.Context.__new__(strp.Context)
+    ctx.lib, ctx.h, ctx.ensure_workspace = lib.lib, lib.h, lambda n: None
+    for x in (np.float32(0.5), np.float64(0.5), Fraction(1, 2), np.array(0.5), 1):
+        ctx.strp_weight_energy([Tensor(4, 8), Tensor(4, 8, 1)], x, x, x, Tensor(1))
+    for mats, energy in (([Tensor(4, 8)], None), ([], Tensor(1))):
+        try:
+            ctx.strp_weight_energy(mats, 0.1, 0.1, 1.0, energy)
+            assert False
+        except strp.StrpError as e:
+            assert e.status == strp.EINVAL
+
+
+CHECKS = [check_weight_statistics_arguments, check_weight_statistics_workgroups, check_chains, check_workspace_of_a_module, check_cached_factor_needs_no_alignment]
 
 
 @pytest.fixture(scope="session")
