@@ -343,6 +343,7 @@ strp_status strp_module_init(strp_ctx* ctx, const strp_module_desc* desc, strp_m
  * it does, A is that update's exact minimiser and the same number is obtained as
  * (alpha/T)(beta/alpha)^2 <M^-2, E E^T>, E = Y - W2[:,S] relu(Z_S), M = (beta/alpha) I + W2[:,S] W2[:,S]^T
  * (Appendix A.1, "Updating activation": the normal equations of that step).
+ * A selection of k < f units takes f up to 65536 (STRP_EINVAL above).
  */
 strp_status strp_admm_step(strp_ctx* ctx, const strp_module_desc* desc, strp_module_state* st,
                            const strp_params* params, strp_report* report_host);

@@ -892,7 +892,7 @@ static void big_plan(long long n, int* blocks, long long* chunk) {
   *chunk = c;
 }
 
-size_t topk_scratch_bytes(int n) { return n <= 65536 ? 0 : ((sizeof(big::State) + 255) & ~size_t(255)); }
+size_t topk_scratch_bytes(int n) { return n <= SELECT_MAX ? 0 : ((sizeof(big::State) + 255) & ~size_t(255)); }
 
 // f(key, index) for this workgroup's chunk: eight consecutive scores per thread and trip
 template <typename F>
@@ -1120,10 +1120,11 @@ static void launch_topk_small(strp_ctx* ctx, float* score, int n, int k, int gro
 
 strp_status launch_select(strp_ctx* ctx, const double* sums, const double* n2, int mode, int n, int k, float* score, double* energy_out,
                           uint8_t* mask, int32_t* idx, float* tau, int32_t* rest) {
-  if (k >= n || n > 65536) {        // everything is kept, or too long for one block: in two steps
+  if (k >= n) {        // everything is kept, of a vector of any length: in two steps
     STRP_TRY(launch_unit_scores(ctx, sums, n2, n, 1, mode, score, energy_out));
     return launch_topk(ctx, score, n, k, 1, mask, idx, tau, nullptr, 0);
   }
+  if (n > SELECT_MAX) return fail(ctx, STRP_EINVAL, "select: %d scores, one block takes %d", n, SELECT_MAX);
   ProfScope ps(ctx, "topk", 0.0, 5.0 * (double)n + 4.0 * (double)k);
   launch_topk_small(ctx, score, n, k, 1, mask, idx, tau, ScoreSource{sums, n2, mode, energy_out}, rest);
   STRP_HIP(ctx, hipGetLastError());
@@ -1135,7 +1136,7 @@ strp_status launch_topk(strp_ctx* ctx, const float* score, int n, int k, int gro
   ProfScope ps(ctx, "topk", 0.0, 5.0 * (double)n + 4.0 * (double)k * group);
   if (k <= 0 || k >= n) {
     hipLaunchKernelGGL(topk_all_kernel, dim3(1), dim3(1024), 0, ctx->stream, score, n, k >= n ? 1 : 0, group, mask, idx, tau);
-  } else if (n <= 65536) {
+  } else if (n <= SELECT_MAX) {
     launch_topk_small(ctx, const_cast<float*>(score), n, k, group, mask, idx, tau, ScoreSource{nullptr, nullptr, 0, nullptr}, nullptr);
   } else {
     const int vec = (((uintptr_t)score & 15) == 0 && ((uintptr_t)mask & 7) == 0) ? 1 : 0;

@@ -1078,6 +1078,7 @@ strp_status strp_admm_step(strp_ctx* ctx, const strp_module_desc* desc, strp_mod
   const bool do_select = (stages & STRP_STAGE_SELECT) && (params->reselect || st->s == 0);
   if (do_select && (params->k <= 0 || params->k > f)) return fail(ctx, STRP_EINVAL, "admm_step: k outside [1, f]");
   if (desc->k_max > 0 && do_select && params->k > desc->k_max) return fail(ctx, STRP_EINVAL, "admm_step: k above desc.k_max");
+  if (do_select && f > SELECT_MAX && params->k < f) return fail(ctx, STRP_EINVAL, "admm_step: selects among at most %d units", SELECT_MAX);
   if (!do_select && st->s <= 0) return fail(ctx, STRP_ESTATE, "admm_step: no mask selected yet");
   if (!(params->alpha > 0.0) || !(params->beta > 0.0)) return fail(ctx, STRP_EINVAL, "admm_step: alpha, beta must be positive");
   if (params->mode < STRP_SCORE_WANDA || params->mode > STRP_SCORE_GAIN) return fail(ctx, STRP_EINVAL, "admm_step: unknown score mode");

@@ -251,7 +251,8 @@ strp_status launch_topk(strp_ctx* ctx, const float* score, int n, int k, int gro
                         float* tau, void* scratch, size_t scratch_bytes);
 size_t topk_scratch_bytes(int n);
 // One module's selection in one launch: unit scores from the token sums (layout of launch_row_sums), their mean, and the k
-// best of them; rest (optional): the n - k other indices, ascending.
+// best of them; rest (optional): the n - k other indices, ascending.  n <= SELECT_MAX unless k = n.
+constexpr int SELECT_MAX = 65536;     // scores one block selects from (64 per thread)
 strp_status launch_select(strp_ctx* ctx, const double* sums, const double* n2, int mode, int n, int k, float* score, double* energy_out,
                           uint8_t* mask, int32_t* idx, float* tau, int32_t* rest);
 

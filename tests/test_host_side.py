@@ -188,7 +188,25 @@ def check_weight_statistics_arguments():
             assert e.status == strp.EINVAL
 
 
-CHECKS = [check_weight_statistics_arguments, check_weight_statistics_workgroups, check_chains, check_workspace_of_a_module, check_cached_factor_needs_no_alignment]
+def check_selection_of_a_very_wide_module():
+    """One block selects a module's units: more than 65536 of them are refused before anything is enqueued, unless all are
+    kept."""
+    lib = Library()
+    strp = lib.strp
+    for f, k, want in ((65536, 100, strp.OK), (65544, 100, strp.EINVAL), (65544, 65543, strp.EINVAL), (65544, 65544, strp.OK)):
+        desc = strp.ModuleDesc(8, f, 16, 16, 16, strp.F32, strp.F32, 0)
+        st = strp.ModuleState()
+        for name, kind in strp.ModuleState._fields_:
+            if kind is C.c_void_p:
+                setattr(st, name, 1 << 50)
+        p = strp.Params(1.0, 1.0, 0.01, strp.WANDA, 1, k, 0)
+        assert lib.lib.strp_module_init(lib.h, C.byref(desc), C.byref(st), C.byref(p)) == strp.OK
+        status, launches = lib.launches(lambda: lib.lib.strp_admm_step(lib.h, C.byref(desc), C.byref(st), C.byref(p), None))
+        assert status == want, (f, k, status)
+        assert bool(launches) == (want == strp.OK)
+
+
+CHECKS = [check_selection_of_a_very_wide_module, check_weight_statistics_arguments, check_weight_statistics_workgroups, check_chains, check_workspace_of_a_module, check_cached_factor_needs_no_alignment]
 
 
 @pytest.fixture(scope="session")
