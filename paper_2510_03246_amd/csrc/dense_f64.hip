@@ -917,16 +917,16 @@ __global__ __launch_bounds__(256, 2) void chol_begin_kernel(const StepP p, int c
 // sub: ceil(n / NB) * NB * NB doubles of scratch.  ld and ldv even, A and Linv 16-byte aligned.
 strp_status chol_inverse(strp_ctx* ctx, double* A, int n, long long ld, double* sub, double* Linv, long long ldv, int32_t* status) {
   if (!aligned_vec(A, ld) || !aligned_vec(Linv, ldv)) return fail(ctx, STRP_EINVAL, "chol_inverse: operands not 16-byte aligned or odd leading dimension");
-  ProfScope ps(ctx, "chol_factor_f64", 2.0 * (double)n * n * n / 3.0, 16.0 * (double)n * n);
+  CoJob job;
+  memset(&job, 0, sizeof(job));
+  if (ctx->cojob) job = *ctx->cojob;
+  ctx->cojob = nullptr;
+  ProfScope ps(ctx, "chol_factor_f64", 2.0 * (double)n * n * n / 3.0, 16.0 * (double)n * n + (job.Z0 ? 16.0 : 12.0) * (double)job.nrows * (double)job.T);
   StepP p;
   memset(&p, 0, sizeof(p));
   p.A = A; p.ld = ld; p.V = Linv; p.ldv = ldv; p.sub = sub; p.n = n; p.N = (n + NB - 1) / NB; p.status = status;
   const int nt = p.N * (p.N - 1) / 2;
   const int clear = nt < 1024 ? nt : 1024;
-  CoJob job;
-  memset(&job, 0, sizeof(job));
-  if (ctx->cojob) job = *ctx->cojob;
-  ctx->cojob = nullptr;
   const unsigned int ride = job.units < 510u ? job.units : 510u;      // two workgroups of this kernel per CU, one place left to block 0
   hipLaunchKernelGGL(chol_begin_kernel, dim3(1 + clear + ride), dim3(256), 0, ctx->stream, p, clear, job);
   for (int t = 0; t < p.N; ++t) {

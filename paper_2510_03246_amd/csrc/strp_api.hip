@@ -91,98 +91,53 @@ __global__ __launch_bounds__(1024) void scaled_sum_kernel(const double* v, int s
     for (int i = threadIdx.x; i < nd; i += 1024) A[(long long)i * ld + i] += t * scale;
 }
 
-// The per-element rules of the pruned rows (pruned_elem) are in cojob.h.
-// rowsums (phase 2 only, may be null): the scoring sums of the row's NEW state, [0][j] = sum A^2 and, when Z0 is
-// given, [1][j] = sum A relu(Z0), [2][j] = sum Z0 Z, [3][j] = sum Z0^2, so that the next selection does not have
-// to stream the pruned rows again.
+// The pruned rows where the a- and z-stages come in separate calls, one block per row (rules: pruned_elem, cojob.h): phase 0 the
+// a-update, phase 1 the z-update (write) and the row's share of the objective, red[2 j].
 __global__ __launch_bounds__(256) void pruned_rows_kernel(const uint8_t* mask, float* Z, float* A, long long lda, long long T, int phase,
-                                                          float alpha, float beta, int write, double* red, const float* Z0,
-                                                          double* rowsums, int rows) {
+                                                          float alpha, float beta, int write, double* red) {
   const int j = blockIdx.x;
   double r0 = 0.0, r1 = 0.0;
-  double sg = 0.0, se = 0.0, su = 0.0, sv = 0.0;
-  const bool pruned = !mask[j];
-  if (pruned) {
+  if (!mask[j]) {
     float* z = Z + (long long)j * lda;
     float* a = A + (long long)j * lda;
-    const float* z0 = Z0 ? Z0 + (long long)j * lda : nullptr;
     const long long T4 = T >> 2;
     // two independent 16-byte groups per thread and trip: all loads of a trip are issued before its first store
-    auto body = [&](long long c, float4 zv, float4 av, float4 w) {
+    auto body = [&](long long c, float4 zv, float4 av) {
       pruned_elem(zv.x, av.x, phase, alpha, beta, write, r0, r1);
       pruned_elem(zv.y, av.y, phase, alpha, beta, write, r0, r1);
       pruned_elem(zv.z, av.z, phase, alpha, beta, write, r0, r1);
       pruned_elem(zv.w, av.w, phase, alpha, beta, write, r0, r1);
       if (phase != 1) ((float4*)a)[c] = av;
       if (phase != 0 && write) ((float4*)z)[c] = zv;
-      if (rowsums) {
-        const float aa[4] = {av.x, av.y, av.z, av.w};
-#pragma unroll
-        for (int q = 0; q < 4; ++q) sg = __builtin_fma((double)aa[q], (double)aa[q], sg);
-        if (z0) {
-          const float wa[4] = {w.x, w.y, w.z, w.w}, za[4] = {zv.x, zv.y, zv.z, zv.w};
-#pragma unroll
-          for (int q = 0; q < 4; ++q) {
-            const double z0d = wa[q];
-            se = __builtin_fma((double)aa[q], fmax(z0d, 0.0), se);
-            su = __builtin_fma(z0d, (double)za[q], su);
-            sv = __builtin_fma(z0d, z0d, sv);
-          }
-        }
-      }
     };
     const float4 zero4 = make_float4(0.f, 0.f, 0.f, 0.f);
     long long c = threadIdx.x;
     for (; c + 256 < T4; c += 512) {
       const float4 zv0 = ((const float4*)z)[c], zv1 = ((const float4*)z)[c + 256];
       const float4 av0 = phase == 1 ? ((const float4*)a)[c] : zero4, av1 = phase == 1 ? ((const float4*)a)[c + 256] : zero4;
-      const float4 w0 = z0 ? ((const float4*)z0)[c] : zero4, w1 = z0 ? ((const float4*)z0)[c + 256] : zero4;
-      body(c, zv0, av0, w0);
-      body(c + 256, zv1, av1, w1);
+      body(c, zv0, av0);
+      body(c + 256, zv1, av1);
     }
-    if (c < T4) body(c, ((const float4*)z)[c], phase == 1 ? ((const float4*)a)[c] : zero4, z0 ? ((const float4*)z0)[c] : zero4);
+    if (c < T4) body(c, ((const float4*)z)[c], phase == 1 ? ((const float4*)a)[c] : zero4);
     for (long long t = T4 * 4 + threadIdx.x; t < T; t += 256) {
       float zv = z[t], av = phase == 1 ? a[t] : 0.0f;
       pruned_elem(zv, av, phase, alpha, beta, write, r0, r1);
       if (phase != 1) a[t] = av;
       if (phase != 0 && write) z[t] = zv;
-      if (rowsums) {
-        sg = __builtin_fma((double)av, (double)av, sg);
-        if (z0) {
-          const double z0d = z0[t];
-          se = __builtin_fma((double)av, fmax(z0d, 0.0), se);
-          su = __builtin_fma(z0d, (double)zv, su);
-          sv = __builtin_fma(z0d, z0d, sv);
-        }
-      }
     }
   }
-  if (red || rowsums) {
-    __shared__ double sh[4][6];
+  if (red) {
+    __shared__ double sh[4][2];
     for (int o = 32; o > 0; o >>= 1) {
       r0 += __shfl_down(r0, o, 64);
       r1 += __shfl_down(r1, o, 64);
-      if (rowsums) {
-        sg += __shfl_down(sg, o, 64);
-        se += __shfl_down(se, o, 64);
-        su += __shfl_down(su, o, 64);
-        sv += __shfl_down(sv, o, 64);
-      }
     }
     if ((threadIdx.x & 63) == 0) {
-      double* w = sh[threadIdx.x >> 6];
-      w[0] = r0; w[1] = r1; w[2] = sg; w[3] = se; w[4] = su; w[5] = sv;
+      sh[threadIdx.x >> 6][0] = r0;
+      sh[threadIdx.x >> 6][1] = r1;
     }
     __syncthreads();
-    if (threadIdx.x < 6) {
-      const int q = threadIdx.x;
-      const double t = sh[0][q] + sh[1][q] + sh[2][q] + sh[3][q];
-      if (q < 2) {
-        if (red) red[2 * (long long)j + q] = t;
-      } else if (rowsums && pruned && (q == 2 || Z0)) {
-        rowsums[(long long)(q - 2) * rows + j] = t;
-      }
-    }
+    if (threadIdx.x < 2) red[2 * (long long)j + threadIdx.x] = sh[0][threadIdx.x] + sh[1][threadIdx.x] + sh[2][threadIdx.x] + sh[3][threadIdx.x];
   }
 }
 
@@ -1239,7 +1194,6 @@ strp_status strp_admm_step(strp_ctx* ctx, const strp_module_desc* desc, strp_mod
     }
     const size_t al = 255;
     const size_t cbytes = ((nt_partial_elems(d, d, sp, 1) * 4 + al) & ~al) + (((size_t)((d + NB - 1) / NB) * NB * NB * 8 + al) & ~al) +
-                          
                           2 * ((plane_elems(d, d) * 2 + al) & ~al) + 4096;
     STRP_TAKE(ctx, arena, cblock, char, cbytes);
     Arena a2(cblock, cbytes);
@@ -1384,8 +1338,7 @@ strp_status strp_admm_step(strp_ctx* ctx, const strp_module_desc* desc, strp_mod
     }
     if (!fuse_pruned) {
       ProfScope ps(ctx, "pruned_rows_a", 0.0, 8.0 * (double)(f - s) * (double)T);
-      hipLaunchKernelGGL(pruned_rows_kernel, dim3(f), dim3(256), 0, ctx->stream, st->mask, st->Z, st->A, lda, T, 0, alpha, beta, 1, (double*)nullptr,
-                         (const float*)nullptr, (double*)nullptr, f);
+      hipLaunchKernelGGL(pruned_rows_kernel, dim3(f), dim3(256), 0, ctx->stream, st->mask, st->Z, st->A, lda, T, 0, alpha, beta, 1, (double*)nullptr);
     }
   }
   // ---- S8 (+ objective terms 2, 3): z-update fused on Z1 = W1 X --------------------------------
@@ -1418,7 +1371,7 @@ strp_status strp_admm_step(strp_ctx* ctx, const strp_module_desc* desc, strp_mod
       STRP_TAKE(ctx, arena, redp, double, 2 * (size_t)f);
       ProfScope ps(ctx, "pruned_rows_z", 0.0, 8.0 * (double)(f - s) * (double)T);
       hipLaunchKernelGGL(pruned_rows_kernel, dim3(f), dim3(256), 0, ctx->stream, st->mask, st->Z, st->A, lda, T, 1, alpha, beta,
-                         zupd ? 1 : 0, redp, (const float*)nullptr, (double*)nullptr, f);
+                         zupd ? 1 : 0, redp);
       fin.red_p = redp; fin.np = f;
     }
   }
