@@ -5,6 +5,7 @@ import pytest
 import torch
 
 from paper_2510_03246_amd import strp
+from test_host_side import LARGE_SYSTEMS
 
 pytestmark = pytest.mark.gpu
 
@@ -46,6 +47,34 @@ def test_factor_inverse_and_solve(ctx, n, m):
     W2 = torch.zeros_like(W)
     ctx.strp_refit(strp.SIDE_FC2, None, lam, dev(lhs), dev(rhs), T, idx, W2, chol=chol, chol_valid=True)
     assert torch.equal(W, W2)
+
+
+@pytest.mark.parametrize("n,m", LARGE_SYSTEMS)
+def test_large_factor_and_solve(n, m):
+    """Orders with several trailing tiles per workgroup and right-hand sides on the larger tiles, all entries: Linv S Linv^T = I
+    (fp64, kappa below 100: n * kappa * 2^-53 < 1e-10) and W = R Linv^T Linv (R whole numbers, W rounded to fp32: 1e-7)."""
+    ctx = strp.Context(0)
+    ctx.set_workspace(2 << 30)
+    g = torch.Generator(device="cuda").manual_seed(n)
+    T = 24
+    lhs, rhs = (torch.randint(-4, 5, (r, T), generator=g, device="cuda").float() for r in (m, n))
+    B = torch.randn((n, n + 8), generator=g, device="cuda", dtype=torch.float64) / (n + 8) ** 0.5
+    G = (B @ B.T).float()
+    G = torch.tril(G) + torch.tril(G, -1).T
+    lam = 0.05
+    idx = torch.arange(n, dtype=torch.int32, device="cuda")
+    W = torch.full((m, n), 7.0, device="cuda")
+    chol = torch.full((n, n), 3.0, dtype=torch.float64, device="cuda")
+    ctx.strp_refit(strp.SIDE_FC2, G, lam, lhs, rhs, T, idx, W, chol=chol, chol_valid=False)
+    assert ctx.poll() == strp.OK
+    eye = torch.eye(n, dtype=torch.float64, device="cuda")
+    assert torch.count_nonzero(torch.triu(chol, 1)) == 0
+    off = chol @ (G.double() + lam * eye) @ chol.T - eye
+    assert float(off.abs().max()) <= 1e-10
+    ref = lhs.double() @ rhs.double().T @ chol.T @ chol
+    assert float((W.double() - ref).norm() / ref.norm()) <= 1e-7
+    assert float((W.double() - ref).abs().max()) <= 1e-6 * float(ref.abs().max())
+    ctx.close()
 
 
 @pytest.mark.parametrize("n,bad", [(5, [0]), (64, [15, 16]), (70, [63]), (130, [64, 100]), (200, [17, 130, 199])])

@@ -3,6 +3,7 @@ import pytest
 import torch
 
 from paper_2510_03246_amd import strp
+from test_host_side import GRAMS
 
 pytestmark = pytest.mark.gpu
 
@@ -15,10 +16,7 @@ def ctx():
     c.close()
 
 
-# both tile shapes with an even and an odd number of tile rows, one token group to several accumulation chains, a split
-# count that is and is not a multiple of what the reduction keeps in flight
-@pytest.mark.parametrize("s,T", [(64, 8), (129, 520), (255, 4104), (256, 256), (257, 264), (512, 8200), (640, 70000), (768, 16384), (1025, 2056),
-                                 (1280, 3000)])
+@pytest.mark.parametrize("s,T", GRAMS)
 @pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
 def test_gram_is_exact_on_small_integers(ctx, s, T, dtype):
     """Entries of at most 4: products and their sums stay below 2^24, so no step of the product rounds, in any order."""

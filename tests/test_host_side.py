@@ -16,6 +16,12 @@ CHAINS = [((64, 64, 512), 256), ((128, 128, 2000), 256), ((1536, 1536, 65536), 3
           ((3277, 3277, 262144), 8192), ((4915, 4915, 131072), 8192), ((768, 1536, 65536), 3648), ((768, 1536, 16384), 928),
           ((1000, 1013, 30011), 1888), ((2048, 3277, 262144), 8192), ((4096, 4915, 131072), 8192), ((2048, 832, 65536), 5472), ((33, 70, 5000), 256)]
 
+# rows and tokens of the Gram matrices that tests/test_gpu_gram_splits.py compares entry by entry
+GRAMS = [(64, 8), (129, 520), (255, 4104), (256, 256), (257, 264), (512, 8200), (640, 70000), (768, 16384), (1025, 2056), (1280, 3000),
+         (256, 65536), (512, 65536), (832, 65536), (1280, 16384), (300, 100000)]
+# order of the system and rows of the right-hand side in tests/test_gpu_factor.py where its launches change their shape
+LARGE_SYSTEMS = [(1409, 333), (2113, 65), (3137, 129), (2881, 2900), (4099, 4100)]
+
 
 class Library:
     """The library on the stand-in, with a context and a workspace at an address nothing reads."""
@@ -206,7 +212,44 @@ def check_selection_of_a_very_wide_module():
         assert bool(launches) == (want == strp.OK)
 
 
-CHECKS = [check_selection_of_a_very_wide_module, check_weight_statistics_arguments, check_weight_statistics_workgroups, check_chains, check_workspace_of_a_module, check_cached_factor_needs_no_alignment]
+def check_what_the_gram_matrices_cover():
+    """Both tile shapes with an even and an odd number of tile rows and with one; one accumulation chain and several; a number
+    of partials that is and is not a multiple of the four the reduction keeps in flight."""
+    lib = Library()
+    seen, parts = set(), set()
+    for s, T in GRAMS:
+        tile, splits = splits_of(lib.gram(s, T)[1], s, s)
+        rows = -(-s // tile)
+        seen.add((tile, "one" if rows == 1 else rows % 2))
+        parts.add("one" if splits == 1 else splits % 4 == 0)
+    assert seen >= {(t, r) for t in (128, 256) for r in (0, 1)} | {(128, "one"), (256, "one")}, seen
+    assert parts == {"one", True, False}
+
+
+def check_what_the_large_systems_cover():
+    """The three tiles of the fp64 products, the factorisation's launches with one, two and three trailing tiles per workgroup, and
+    those of more than 1024 trailing tiles."""
+    lib = Library()
+    tiles, each, long = set(), set(), False
+    for n, m in LARGE_SYSTEMS:
+        st, launches = lib.launches(lambda: lib.lib.strp_refit(lib.h, lib.strp.SIDE_FC2, 1 << 50, n, 1.0, None, 0, 1 << 51, lib.strp.F32, 24, 1 << 52,
+                                                               lib.strp.F32, 24, 24, 1 << 53, n, 1 << 54, m, n))
+        assert st == lib.strp.OK
+        tiles |= {name.split("ILi")[1][:3].rstrip("E") + "x" + name.split("ELi")[1].split("E")[0] for name, _ in launches if "dgemm_kernel" in name}
+        steps = [grid[0] for name, grid in launches if "chol_step_kernel" in name]
+        N = -(-n // 64)
+        assert len(steps) == N or len(steps) == N - 1
+        for t, grid in enumerate(steps):
+            behind = N - 1 - t
+            total = behind * (behind - 1) // 2 - (behind > 1) + behind * t if t else 0
+            long |= total > 1024
+            if total > 6:
+                each.add(-(-total // (grid - behind - t)))
+    assert tiles == {"64x32", "64x64", "128x128"}, tiles
+    assert each == {1, 2, 3} and long, each
+
+
+CHECKS = [check_what_the_gram_matrices_cover, check_what_the_large_systems_cover, check_selection_of_a_very_wide_module, check_weight_statistics_arguments, check_weight_statistics_workgroups, check_chains, check_workspace_of_a_module, check_cached_factor_needs_no_alignment]
 
 
 @pytest.fixture(scope="session")
