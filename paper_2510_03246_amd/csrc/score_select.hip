@@ -564,7 +564,7 @@ __device__ __forceinline__ float key_score(unsigned int k) {
 __global__ __launch_bounds__(1024) void topk_all_kernel(const float* score, int n, int keep, int group, uint8_t* mask, int32_t* idx, float* tau) {
   __shared__ float wmin[16];
   const int tid = threadIdx.x;
-  float t = __builtin_inff();
+  float t = keep ? __builtin_nanf("") : __builtin_inff();     // fminf passes over NaN: the minimum is NaN only if every score is
   for (int i = tid; i < n; i += 1024) {
     mask[i] = (uint8_t)keep;
     if (keep) {

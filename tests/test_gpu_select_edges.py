@@ -36,6 +36,16 @@ def test_topk_edges(ctx, n, k, group, kind):
     assert float(tau.item()) == np.float32(to)
 
 
+def test_threshold_of_everything(ctx):
+    """k = n: the lowest score that is a number, NaN where none is; k = 0: +inf."""
+    s = torch.full((1500,), float("nan"), device="cuda")
+    assert torch.isnan(ctx.strp_mask_topk(s, 1500)[2]).item()
+    assert float(ctx.strp_mask_topk(s, 0)[2].item()) == float("inf")
+    s[1400] = 3.0
+    s[7] = float("inf")
+    assert float(ctx.strp_mask_topk(s, 1500)[2].item()) == 3.0
+
+
 @pytest.mark.parametrize("n,k,group", [(65537, 9, 2), (65600, 65599, 3), (140003, 70001, 2)])
 @pytest.mark.parametrize("kind", ["spread", "ties"])
 def test_topk_groups_without_workspace(n, k, group, kind):
