@@ -230,7 +230,10 @@ __global__ __launch_bounds__(256, 2) void dgemm_kernel(const DgemmP p) {
 }
 
 // Tile of a product by its grid: 128 x 128 tiles read the fewest operand bytes per flop but need enough of them to fill
-// the chip; below that the longest tile (whole K) sets the run time and a smaller one ends sooner.
+// the chip; below that the longest tile (whole K) sets the run time and a smaller one ends sooner.  Solves X (L L^T)^-1 of
+// m x n (two products), us with 64 x 32 / 64 x 64 / 128 x 128 tiles:  768 x 1536 127 / 161 / 452;  2048 x 3277 (1664 tiles of
+// 64, 416 of 128) 824 / 846 / 1245;  3000 x 3000 (2209, 576) 1070 / 1033 / 1290;  3500 x 4000 (3465, 896) 2143 / 2105 / 2038;
+// 4096 x 4096 (4096, 1024) 2557 / 2550 / 2282;  4096 x 4915 (4928, 1248) 3743 / 3684 / 3489, 57 TFLOP/s.
 constexpr int DGEMM_T128 = 1000, DGEMM_T64 = 2000;
 
 static inline bool aligned_vec(const void* p, long long ld) { return ((uintptr_t)p & 15u) == 0 && (ld & 1) == 0; }
@@ -444,7 +447,8 @@ __device__ __forceinline__ void diag_block(StepShared& sh, int tid) {
 //   TV(i, c):  V(i, c) -= L(i, t-1) Linv(t-1, c),  i > t, c < t
 // No workgroup of a launch reads what another one of it writes: the tiles L(t+1, t) go to a buffer of their own (sub)
 // because P(t + 2) reads what they would replace.  A launch costs what P(t + 1) does while the others fit beside it: one
-// and a half 64^3 products at the 0.3 TFLOP/s of one CU and the diagonal tile's chain of 64 pivots.
+// and a half 64^3 products at the 0.3 TFLOP/s of one CU and the diagonal tile's chain of 64 pivots, 17 us up to n = 1536.
+// Larger orders are bound by the trailing tiles' traffic (39 us a launch on average at n = 4915).
 // Groups of two or four panels (fewer passes over the tiles behind) were slower at every order up to 4915.
 struct StepP {
   double* A; long long ld;
@@ -932,7 +936,10 @@ strp_status chol_inverse(strp_ctx* ctx, double* A, int n, long long ld, double* 
   for (int t = 0; t < p.N; ++t) {
     p.t = t;
     const int m = p.N - 1 - t;
-    // up to three tiles each, so that a launch of a small system leaves the critical workgroup a CU of its own
+    // up to three tiles each, so that a launch of a small system leaves the critical workgroup a CU of its own; beyond 1024
+    // tiles the launch is theirs and a workgroup that takes several only ends later.  One tile each / up to three / this, us
+    // for the whole chain: n = 1536 470 / 461 / 460, 2048 660 / 612 / 615, 2458 838 / 818 / 816, 3277 1213 / 1256 / 1235,
+    // 4096 1854 / 2094 / 1871, 4915 3019 / 3187 / 3039
     const int total = t > 0 ? m * (m - 1) / 2 - (m > 1) + m * t : 0;
     p.each = (total + 191) / 192;
     if (p.each > 3) p.each = total > 1024 ? 1 : 3;
