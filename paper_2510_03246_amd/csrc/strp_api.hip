@@ -690,21 +690,26 @@ static size_t nt_partial_most(int M, int N, long long K, int km) {
   size_t most = 0;
   for (int k0 = 0; k0 < km; k0 += 128) {
     const int k1 = k0 + 128 < km ? k0 + 128 : km;
-    for (int k : {k0 + 1, k1}) {
+    auto at = [&](int k) {
       const size_t e = nt_splits(M ? M : k, N ? N : k, K, !M && !N) * (size_t)(M ? M : k1) * (size_t)(N ? N : k1);
       most = e > most ? e : most;
-    }
+    };
+    at(k1);
+    if (k1 == 256) at(255);
   }
   return most;
 }
-// The same for W W^T of d rows, a contraction over the kept units rounded up to 8: chunks go by stages of 32.
+// The same for W W^T of d rows, a contraction over the kept units rounded up to 8: chunks go by stages of 32, the most splits by 256.
 static size_t nt_partial_most_over(int d, long long km) {
   size_t most = 0;
-  for (long long k0 = 0; k0 < km; k0 += 32)
-    for (long long k : {k0 + 8, k0 + 32}) {
-      const size_t e = nt_partial_elems(d, d, k, 1);
-      most = e > most ? e : most;
-    }
+  auto at = [&](long long k) {
+    const size_t e = nt_partial_elems(d, d, k, 1);
+    most = e > most ? e : most;
+  };
+  for (long long k = 32; k < km + 32; k += 32) {
+    at(k);
+    if (k % 256 == 0) at(k - 8);
+  }
   return most;
 }
 
