@@ -754,7 +754,8 @@ static strp_status factor_and_invert(strp_ctx* ctx, Arena arena, double* sys, in
   return chol_inverse(ctx, sys, n, f64_ld(n), sub, Linv, ldl, ctx->status_dev);
 }
 
-static strp_status ridge_solve(strp_ctx* ctx, Arena& arena, const RefitIn& in, const WeightsOut& out) {
+// clear: bytes of out.W to zero first, once everything of the caller's has been read (W may be the array that holds Gram)
+static strp_status ridge_solve(strp_ctx* ctx, Arena& arena, const RefitIn& in, const WeightsOut& out, size_t clear = 0) {
   const int n = in.n, m = in.m;
   const long long ld = f64_ld(n);
   const bool factor = !in.linv_ready;
@@ -767,6 +768,7 @@ static strp_status ridge_solve(strp_ctx* ctx, Arena& arena, const RefitIn& in, c
   STRP_TAKE(ctx, arena, R, double, (size_t)m * ld);
   STRP_TAKE(ctx, arena, tmp, double, (size_t)m * ld);
   STRP_TRY(nt_product(ctx, arena, in.Lhs, in.Rhs, m, n, in.T, 0, reduce_to(R, ld)));
+  if (clear) STRP_TRY(fill_zero(ctx, out.W, clear));
   return apply_inverse_right(ctx, in.Linv, n, in.ldl, R, m, ld, tmp, out);
 }
 
@@ -923,8 +925,7 @@ strp_status strp_refit(strp_ctx* ctx, strp_side side, const float* Gram, int32_t
     STRP_TRY(make_t_planes(ctx, arena, Rhs, rhs_dtype, ld_rhs, nullptr, in, T, 0, planes_for(rhs_dtype, prec), &ri.Rhs));
   }
   ri.m = m; ri.n = n; ri.T = T;
-  STRP_TRY(fill_zero(ctx, W, sizeof(float) * (size_t)out * (size_t)in));
-  STRP_TRY(ridge_solve(ctx, arena, ri, WeightsOut{side, idx, W, in, nullptr, 0, nullptr, nullptr}));
+  STRP_TRY(ridge_solve(ctx, arena, ri, WeightsOut{side, idx, W, in, nullptr, 0, nullptr, nullptr}, sizeof(float) * (size_t)out * (size_t)in));
   return chol && !chol_direct ? copy_f64(ctx, ri.Linv, ri.ldl, chol, n, n) : STRP_OK;
 }
 

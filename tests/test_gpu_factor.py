@@ -109,6 +109,20 @@ def test_pivots_that_are_not_positive(ctx, n, bad, kind):
     assert np.linalg.norm(got - ref) <= 1e-10 * np.linalg.norm(ref)
 
 
+def test_weights_in_the_array_of_their_gram_matrix(ctx):
+    """W and Gram of one size may be one array: Gram is read before W is written."""
+    n, T = 130, 520
+    g = torch.Generator(device="cuda").manual_seed(4)
+    lhs, rhs = (torch.randn((n, T), generator=g, device="cuda") for _ in range(2))
+    idx = torch.arange(n, dtype=torch.int32, device="cuda")
+    G = ctx.strp_gram(rhs, T)
+    want = ctx.strp_refit(strp.SIDE_FC2, G, 5.0, lhs, rhs, T, idx, torch.empty((n, n), device="cuda"))
+    assert float(want.abs().max()) > 0.0
+    got = ctx.strp_refit(strp.SIDE_FC2, G, 5.0, lhs, rhs, T, idx, G)
+    assert ctx.poll() == strp.OK
+    assert torch.equal(got, want)
+
+
 def test_module_with_an_unaligned_cached_factor():
     """cholH at an address that is a multiple of 8 only: the same numbers as at one of 16."""
     from paper_2510_03246_amd import inputs
