@@ -1038,12 +1038,12 @@ strp_status gather_weights(strp_ctx* ctx, const WeightsOut& io, int m, int n) {
 
 // several ranges in one launch: a launch costs more than clearing most of what is cleared here
 struct FillRanges {
-  uint32_t* p[5];
-  long long words[5];
+  uint32_t* p[3];
+  long long words[3];
 };
 __global__ __launch_bounds__(256) void fill_zero_kernel(const FillRanges f) {
   const long long stride = (long long)gridDim.x * 256, e0 = (long long)blockIdx.x * 256 + threadIdx.x;
-  for (int r = 0; r < 5; ++r) {
+  for (int r = 0; r < 3; ++r) {
     uint32_t* p = f.p[r];
     const long long quads = ((uintptr_t)p & 15) == 0 ? f.words[r] >> 2 : 0;
     for (long long e = e0; e < quads; e += stride) ((uint4*)p)[e] = make_uint4(0u, 0u, 0u, 0u);

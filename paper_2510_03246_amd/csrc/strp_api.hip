@@ -952,9 +952,8 @@ strp_status strp_module_init(strp_ctx* ctx, const strp_module_desc* desc, strp_m
   double* sc = st->scalars;
   STRP_TAKE(ctx, arena, wmax, unsigned int, 64);
   {
-    const FillRange z[5] = {{sc, SC_COUNT * sizeof(double)}, {wmax, 256}, {st->W1, sizeof(float) * (size_t)f * d}, {st->W2, sizeof(float) * (size_t)f * d},
-                            {st->mask, (size_t)f}};
-    STRP_TRY(fill_zero(ctx, z, 5));
+    const FillRange z[2] = {{sc, SC_COUNT * sizeof(double)}, {wmax, 256}};
+    STRP_TRY(fill_zero(ctx, z, 2));
   }
   STRP_TRY(launch_colnorm2(ctx, st->W2hat, desc->w_dtype, d, f, f, st->n2));
   // X planes (persistent)
@@ -1019,6 +1018,10 @@ strp_status strp_module_init(strp_ctx* ctx, const strp_module_desc* desc, strp_m
     }
     STRP_TRY(factor_and_invert(ctx, a2, Hd, d, Linv, d));
     if (Linv != st->cholH) STRP_TRY(copy_f64(ctx, Linv, d, st->cholH, d, d));
+  }
+  {  // last: fp32 weights may be refitted in the arrays of the dense ones
+    const FillRange z[3] = {{st->W1, sizeof(float) * (size_t)f * d}, {st->W2, sizeof(float) * (size_t)f * d}, {st->mask, (size_t)f}};
+    STRP_TRY(fill_zero(ctx, z, 3));
   }
   STRP_HIP(ctx, hipGetLastError());
   st->s = 0;

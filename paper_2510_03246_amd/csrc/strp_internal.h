@@ -262,7 +262,7 @@ struct FillRange {
   void* ptr;
   size_t bytes;      // multiple of 4
 };
-strp_status fill_zero(strp_ctx* ctx, const FillRange* ranges, int n);     // n <= 5, one launch
+strp_status fill_zero(strp_ctx* ctx, const FillRange* ranges, int n);     // n <= 3, one launch
 
 // "The last workgroup does the rest": true in every thread of the last workgroup of the grid to get here.  What the
 // workgroups hand to it goes through agent-scope atomics (agent_put / agent_get / atomicAdd), which act at the level all

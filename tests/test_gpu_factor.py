@@ -141,3 +141,26 @@ def test_module_with_an_unaligned_cached_factor():
         out.append((chol.clone(), mod.W1.clone(), mod.W2.clone(), mod.A.clone(), mod.Z.clone()))
     for a, b in zip(*out):
         assert torch.equal(a, b)
+
+
+def test_refitted_weights_in_the_arrays_of_the_dense_ones():
+    """W1 and W2 of fp32 modules may be W1hat and W2hat: the initialisation reads them before it clears the weights."""
+    from paper_2510_03246_amd import inputs
+    cfg = inputs.CONFIGS["tiny"]
+    m = inputs.make_ffn_module(cfg, 0, 0, "cuda")
+    params = strp.Params(1.0, 1.0, 0.01, strp.WANDA, 1, 100, 0)
+    out = []
+    for shared in (False, True):
+        c = strp.Context(0)
+        mod = strp.FFNModule(c, m["W1hat"].clone(), m["W2hat"].clone(), m["X"], cfg.T)
+        if shared:
+            mod.W1, mod.W2 = mod.W1hat, mod.W2hat
+            mod.state.W1, mod.state.W2 = mod.W1.data_ptr(), mod.W2.data_ptr()
+        mod.init(params)
+        assert torch.count_nonzero(mod.W1) == 0 and torch.count_nonzero(mod.W2) == 0
+        z0 = mod.Z0.clone()
+        assert mod.step(params).status == strp.OK
+        out.append((z0, mod.W1.clone(), mod.W2.clone(), mod.A.clone(), mod.Z.clone()))
+    assert float(out[0][0].abs().max()) > 0.0
+    for a, b in zip(*out):
+        assert torch.equal(a, b)
