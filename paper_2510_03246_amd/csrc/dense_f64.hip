@@ -287,150 +287,271 @@ constexpr int SL = NB + 1;                // pitch of the square working tiles o
 struct StepShared {
   double a[F64_IMG];
   double b[F64_IMG];
-  double piv[NB];
+  double y[NB];
 };
 
 // Diagonal block: A = Lu D Lu^T (Lu unit lower) by 16-column panels, and W = Lu^-1.
-//   in : S = sh.a, pitch SL, lower triangle (rows past a ragged edge are the identity)
-//   out: sh.b, pitch SL: W (strict upper part of the 16 x 16 diagonal blocks zero, blocks above them untouched);
-//        sh.piv: the pivots D.  L^-1 = D^-1/2 W.  One that is not positive counts as 1 (pivot_or_one): the caller raises
-//        ENOTPD, and everything stays finite.
+//   in : S = sh.b, pitch SL, its first 16 columns (rows past a ragged edge are the identity); block(q, i, k): the other 16 x 16
+//        blocks of the lower triangle in the accumulator layout, asked for when they are needed
+//   out: rows of L^-1 = D^-1/2 W, as they are finished.  A pivot that is not positive counts as 1 and raises ENOTPD:
+//        everything stays finite.
 // The chain of 64 dependent pivots is what bounds it, so one wavefront runs it out of registers: every 16-lane row of
 // the wavefront holds a copy of the panel's 16 x 16 diagonal block (d: lane = row, register = column), so pivots and
-// multiplier rows are broadcast by row_newbcast moves (no LDS, no barrier, no scalar registers); beside it lanes 16 .. 63
-// hold the rows below (a) and lanes 0 .. 15 the columns of an identity, which the same operation turns into the inverse of
-// the diagonal block.  The three other wavefronts meanwhile form the
-// finished rows of W on the matrix cores, and all four apply a finished panel to the columns behind it.
-// Source order is issue order here (sched_barrier): one piece of the next pivot's chain (broadcast, reciprocal, its
-// refinement) after each column update, so that its latency runs under the updates.
+// multiplier rows are broadcast by row_newbcast operands of the updates themselves (no LDS, no barrier, no move); beside it
+// lanes 16 .. 63 hold the rows below (a) and lanes 0 .. 15 the columns of an identity, which the same operation turns into the
+// inverse of the diagonal block.  A wavefront alone issues a 64-bit operation every 5.5 cycles, a reciprocal every 20 and a
+// store to LDS every 19 (two doubles: 27), so what it leaves to the others is what it would have to store or scale: it stores
+// the unscaled columns, two at a time, and 16 reciprocals per panel.  3200 cycles a panel became 2500.
+// The three other wavefronts meanwhile form what the finished panels allow of W on the matrix cores, scale it and store it,
+// so that only the last 16 rows are left when the chain ends.  16 x 16 blocks of S while it runs (i > p):
+//   S(i, p): Lu(i, p) D(p)      S(p, p): W(p, p) transposed      S(p, i), i < 3: W(i, p)      y: -1 / D
+constexpr int EYE = NB * SL + 16;         // behind S: 31 doubles with a 1 in the middle (rows of an identity)
+__device__ __forceinline__ void put_eye(StepShared& sh, int tid) {
+  if (tid < 31) sh.b[EYE + tid] = tid == 15 ? 1.0 : 0.0;
+}
 struct PanelRegs {
   double d[16], a[16];
-  double dj, y, e;      // pivot, its reciprocal (in the making)
-  bool ok;              // the pivot is positive
+  double dj, y, e;      // pivot, minus its reciprocal (in the making)
+  double yt[4];         // of pivot 4 b + q: lanes 4 b .. of every 16, register q
+  bool ok, all;         // the pivot is positive; all were
 };
-__device__ __forceinline__ double pivot_or_one(double d) { return d > 0.0 ? d : 1.0; }
 // v_rcp_f64 is good to 2^-23; y (1 + e + e^2), e = 1 - d y, leaves e^3
-constexpr int PIVOT_STAGES = 5;
+constexpr int PIVOT_STAGES = 4;
 template <int STAGE>
-__device__ __forceinline__ void pivot_stage(PanelRegs& g, double next, double* piv) {
-  if constexpr (STAGE == 0) {
-    g.dj = next;
-    *piv = next;
-  }
-  if constexpr (STAGE == 1) g.y = __builtin_amdgcn_rcp(g.dj);
-  if constexpr (STAGE == 2) g.e = __builtin_fma(-g.dj, g.y, 1.0);
-  if constexpr (STAGE == 3) {
+__device__ __forceinline__ void pivot_stage(PanelRegs& g) {
+  if constexpr (STAGE == 0) g.y = __builtin_amdgcn_rcp(g.dj);
+  if constexpr (STAGE == 1) g.e = __builtin_fma(-g.dj, g.y, 1.0);
+  if constexpr (STAGE == 2) {
     g.e = __builtin_fma(g.e, g.e, g.e);
     g.ok = g.dj > 0.0;
+    g.all &= g.ok;
   }
-  if constexpr (STAGE == 4) {
-    const double y = __builtin_fma(g.e, g.y, g.y);
-    g.y = g.ok ? y : 1.0;
+  if constexpr (STAGE == 3) {
+    const double y = __builtin_fma(g.e, -g.y, -g.y);
+    g.y = g.ok ? y : -1.0;
   }
   __builtin_amdgcn_sched_barrier(0);
 }
 template <int STAGE>
-__device__ __forceinline__ void pivot_rest(PanelRegs& g, double next, double* piv) {
+__device__ __forceinline__ void pivot_rest(PanelRegs& g) {
   if constexpr (STAGE < PIVOT_STAGES) {
-    pivot_stage<STAGE>(g, next, piv);
-    pivot_rest<STAGE + 1>(g, next, piv);
+    pivot_stage<STAGE>(g);
+    pivot_rest<STAGE + 1>(g);
   }
 }
-// x: the broadcast for column K, already under way
-template <int J, int K>
-__device__ __forceinline__ void panel_cols(PanelRegs& g, double x, double md, double ma, double* piv) {
-  if constexpr (K < 16) {
-    double xn = 0.0;
-    if constexpr (K < 15) xn = row_bcast<(K < 15 ? K + 1 : 15)>(g.d[J]);
-    g.d[K] = __builtin_fma(md, x, g.d[K]);
-    g.a[K] = __builtin_fma(ma, x, g.a[K]);
-    double next = 0.0;
-    if constexpr (K == J + 1) next = row_bcast<K>(g.d[K]);
-    if constexpr (K - J - 1 < PIVOT_STAGES) pivot_stage<K - J - 1>(g, next, piv + J + 1);
-    panel_cols<J, K + 1>(g, xn, md, ma, piv);
-  } else if constexpr (J < 15 && 15 - J < PIVOT_STAGES) {
-    pivot_rest<15 - J>(g, 0.0, piv + J + 1);
-  }
-}
+// A DPP operand must not be read within two VALU instructions of its being written, and the compiler does not see into these
+// statements: the first column's begins with the two multiplications that its operand needs anyway and ends with the broadcast
+// of the next pivot, two instructions behind it; no later one reads what was written since.
 template <int J>
-__device__ __forceinline__ void panel_steps(PanelRegs& g, double* lrow, double* piv) {
-  if constexpr (J < 16) {
-    double x = 0.0;
-    if constexpr (J < 15) x = row_bcast<(J < 15 ? J + 1 : 15)>(g.d[J]);
-    const double md = -(g.d[J] * g.y), ma = g.a[J] * g.y;
-    lrow[J] = ma;
-    panel_cols<J, J + 1>(g, x, md, -ma, piv);
-    panel_steps<J + 1>(g, lrow, piv);
+__device__ __forceinline__ void panel_first_col(PanelRegs& g, double& md, double& ma) {
+  asm("v_mul_f64 %0, %6, %8\n\t"
+      "v_mul_f64 %1, %7, %8\n\t"
+      "v_fmac_f64_dpp %2, %6, %0 row_newbcast:%9 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f64_dpp %3, %6, %1 row_newbcast:%9 row_mask:0xf bank_mask:0xf\n\t"
+      "v_mov_b64_dpp %4, %8 row_newbcast:0 row_mask:0xf bank_mask:%10\n\t"
+      "v_mov_b64_dpp %5, %2 row_newbcast:%9 row_mask:0xf bank_mask:0xf"
+      : "=&v"(md), "=&v"(ma), "+v"(g.d[J + 1]), "+v"(g.a[J + 1]), "+v"(g.yt[J & 3]), "=&v"(g.dj)
+      : "v"(g.d[J]), "v"(g.a[J]), "v"(g.y), "n"(J + 1), "n"(1 << (J >> 2)));
+  __builtin_amdgcn_sched_barrier(0);
+}
+template <int J, int K>
+__device__ __forceinline__ void panel_cols(PanelRegs& g, double md, double ma) {
+  if constexpr (K < 16) {
+    asm("v_fmac_f64_dpp %0, %2, %3 row_newbcast:%5 row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f64_dpp %1, %2, %4 row_newbcast:%5 row_mask:0xf bank_mask:0xf"
+        : "+v"(g.d[K]), "+v"(g.a[K]) : "v"(g.d[J]), "v"(md), "v"(ma), "n"(K));
+    if constexpr (K - J - 1 < PIVOT_STAGES) pivot_stage<K - J - 1>(g);
+    panel_cols<J, K + 1>(g, md, ma);
+  } else {
+    pivot_rest<(15 - J < PIVOT_STAGES ? 15 - J : PIVOT_STAGES)>(g);
   }
 }
-
-__device__ __forceinline__ void diag_block(StepShared& sh, int tid) {
-  double* S = sh.a;
-  double* W = sh.b;
-  const int lane = tid & 63, wave = tid >> 6;
+// out: where this lane's columns go
+template <int J>
+__device__ __forceinline__ void panel_steps(PanelRegs& g, double* out) {
+  if constexpr (J < 15) {
+    double md, ma;
+    panel_first_col<J>(g, md, ma);
+    pivot_stage<0>(g);
+    if constexpr (J & 1) {
+      out[J - 1] = g.a[J - 1];
+      out[J] = g.a[J];
+    }
+    panel_cols<J, J + 2>(g, md, ma);
+    panel_steps<J + 1>(g, out);
+  } else {
+    out[14] = g.a[14];
+    out[15] = g.a[15];
+    asm("s_nop 1\n\tv_mov_b64_dpp %0, %1 row_newbcast:0 row_mask:0xf bank_mask:0x8" : "+v"(g.yt[3]) : "v"(g.y));
+  }
+}
+// the wavefront that runs the chain
+__device__ __forceinline__ bool diag_chain(StepShared& sh, int lane) {
+  double* S = sh.b;
+  const int l16 = lane & 15;
+  PanelRegs g;
+  g.all = true;
+#pragma unroll
+  for (int q = 0; q < 4; ++q) asm("" : "=v"(g.yt[q]));
+  int d0 = l16 * SL, a0 = lane < 16 ? EYE + 15 - lane : lane * SL, out = lane * SL;
+#pragma unroll 1
+  for (int p = 0; p < 4; ++p) {
+#pragma unroll
+    for (int c = 0; c < 16; ++c) g.d[c] = S[d0 + c];
+#pragma unroll
+    for (int c = 0; c < 16; ++c) g.a[c] = S[a0 + c];
+    asm("s_nop 1\n\tv_mov_b64_dpp %0, %1 row_newbcast:0 row_mask:0xf bank_mask:0xf" : "=v"(g.dj) : "v"(g.d[0]));
+    pivot_rest<0>(g);
+    panel_steps<0>(g, S + out);
+    double* y = sh.y + 16 * p + 4 * (l16 >> 2);
+#pragma unroll
+    for (int q = 0; q < 4; ++q) y[q] = g.yt[q];
+    // rows below panel q sit in lanes 16 .. 63 - 16 q; lanes without one write to the blocks S(., 3)
+    // above the diagonal, which hold nothing
+    const int q = p + 1, row = (lane + 16 * q) & 63;
+    d0 += 16 * SL + 16;
+    if (lane >= 16) a0 = row * SL + 16 * q;
+    out = lane < 64 - 16 * q ? row * SL + 16 * q : (16 * (3 - (lane >> 4)) + l16) * SL + 48;
+    lds_barrier();
+    if (p < 3) lds_barrier();
+  }
+  return g.all;
+}
+// out: the tile's place in L^-1 (leading dimension ldo), of which rows and columns below jb exist; beside: what the wavefronts
+// still have to store
+template <typename Block, typename Beside>
+__device__ __forceinline__ void diag_block(StepShared& sh, int tid, double* out, long long ldo, int jb, int32_t* status, Block block, Beside beside) {
+  double* S = sh.b;
+  const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int l16 = lane & 15, lq = lane >> 4;
-  // W(i, c) = -W(i, i) sum_{k = c}^{i-1} Lu(i, k) W(k, c), 16 x 16 blocks; one wavefront
-  auto w_block = [&](int i, int c) {
-    doublex4 ts[4];
+  // rows 16 i .. of columns 16 c .. of L^-1: this lane's elements (4 r + lq, l16) of a block of W
+  auto put = [&](int i, int c, const doublex4& w) {
+    double rs[4];
 #pragma unroll
-    for (int s = 0; s < 4; ++s) ts[s] = doublex4{0.0, 0.0, 0.0, 0.0};
-    for (int k = c; k < i; ++k)
+    for (int r = 0; r < 4; ++r) {
+      const double v = -sh.y[16 * i + 4 * r + lq], q = rsqrt_f64(v), s = v * q;
+      rs[r] = __builtin_fma(__builtin_fma(-s, s, v), 0.5 * q, s);
+    }
 #pragma unroll
-      for (int s = 0; s < 4; ++s)
-        ts[s] = mma_f64(S[(16 * i + l16) * SL + 16 * k + 4 * s + lq], W[(16 * k + 4 * s + lq) * SL + 16 * c + l16], ts[s]);
-    const doublex4 t = (ts[0] + ts[1]) + (ts[2] + ts[3]);
+    for (int r = 0; r < 4; ++r) {
+      const int m = 16 * i + 4 * r + lq, k = 16 * c + l16;
+      if (m < jb && k < jb) out[(long long)m * ldo + k] = k <= m ? w[r] * rs[r] : 0.0;
+    }
+  };
+  auto put_diag = [&](int i) {
+    doublex4 w;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) w[r] = S[(16 * i + l16) * SL + 16 * i + 4 * r + lq];
+    put(i, i, w);
+  };
+  if (wave == 3) {
+    const bool all = diag_chain(sh, lane);
+    put_diag(3);
+    beside();
+    if (!all && lane == 0) atomicCAS(status, 0, (int)STRP_ENOTPD);
+    return;
+  }
+  // -Lu(i, k) as an A operand: columns 4 s + lq of row l16
+  auto lu = [&](int i, int k, int s) { return S[(16 * i + l16) * SL + 16 * k + 4 * s + lq] * sh.y[16 * k + 4 * s + lq]; };
+  // t += -Lu(i, k) W(k, c); one wavefront, 16 x 16 blocks.  A result register is the next product's B operand.
+  auto w_add = [&](doublex4& t, int i, int k, int c) {
+    doublex4 u = doublex4{0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+    for (int s = 0; s < 4; ++s) {
+      const double x = lu(i, k, s), y = k == c ? S[(16 * c + l16) * SL + 16 * c + 4 * s + lq] : S[(16 * c + 4 * s + lq) * SL + 16 * k + l16];
+      if (s & 1) u = mma_f64(x, y, u);
+      else t = mma_f64(x, y, t);
+    }
+    t += u;
+  };
+  // W(i, c) = W(i, i) t, t = -sum_{k = c}^{i - 1} Lu(i, k) W(k, c), into the image (unless it is the last row) and out
+  auto w_finish = [&](const doublex4& t, int i, int c) {
     doublex4 u[2];
     u[0] = u[1] = doublex4{0.0, 0.0, 0.0, 0.0};
 #pragma unroll
     for (int s = 0; s < 4; ++s)
-      u[s & 1] = mma_f64(W[(16 * i + l16) * SL + 16 * i + 4 * s + lq], t[s], u[s & 1]);     // a result register is the next B operand
+      u[s & 1] = mma_f64(S[(16 * i + 4 * s + lq) * SL + 16 * i + l16], t[s], u[s & 1]);
+    const doublex4 w = u[0] + u[1];
+    if (i < 3) {
 #pragma unroll
-    for (int r = 0; r < 4; ++r) W[(16 * i + 4 * r + lq) * SL + 16 * c + l16] = -(u[0][r] + u[1][r]);
+      for (int r = 0; r < 4; ++r) S[(16 * c + 4 * r + lq) * SL + 16 * i + l16] = w[r];
+    }
+    put(i, c, w);
   };
-  // S(i, k) -= Lu(i, p) D Lu(k, p)^T, one 16 x 16 block by one wavefront
-  auto s_update = [&](int i, int k, int p) {
-    doublex4 acc[2];
-    acc[0] = acc[1] = doublex4{0.0, 0.0, 0.0, 0.0};
+  // c = block (i, k) -= Lu(i, p) D Lu(k, p)^T
+  auto s_update = [&](doublex4& c, int i, int k, int p) {
+    doublex4 u = doublex4{0.0, 0.0, 0.0, 0.0};
 #pragma unroll
     for (int s = 0; s < 4; ++s) {
-      const int kk = 16 * p + 4 * s + lq;
-      acc[s & 1] = mma_f64(S[(16 * i + l16) * SL + kk], S[(16 * k + l16) * SL + kk] * pivot_or_one(sh.piv[kk]), acc[s & 1]);
+      const double x = lu(i, p, s), y = S[(16 * k + l16) * SL + 16 * p + 4 * s + lq];
+      if (s & 1) u = mma_f64(x, y, u);
+      else c = mma_f64(x, y, c);
     }
-#pragma unroll
-    for (int r = 0; r < 4; ++r) S[(16 * i + 4 * r + lq) * SL + 16 * k + l16] -= acc[0][r] + acc[1][r];
+    c += u;
   };
-#pragma unroll 1
-  for (int p = 0; p < 4; ++p) {
-    if (wave == 3) {
-      const int row = (lane + 16 * p) & 63;       // rows below the panel sit in lanes 16 .. 63 - 16 p
-      PanelRegs g;
+  auto s_put = [&](const doublex4& c, int i, int k) {
 #pragma unroll
-      for (int c = 0; c < 16; ++c) {
-        g.d[c] = S[(16 * p + l16) * SL + 16 * p + c];
-        g.a[c] = S[row * SL + 16 * p + c];
-        if (lane < 16) g.a[c] = l16 == c ? 1.0 : 0.0;
-      }
-      // lanes without a row below write their multipliers to the image's unused tail: no branches in the chain
-      double* lrow = S + (lane >= 16 && lane < 64 - 16 * p ? row * SL + 16 * p : NB * SL + lane);
-      pivot_rest<0>(g, row_bcast<0>(g.d[0]), sh.piv + 16 * p);
-      panel_steps<0>(g, lrow, sh.piv + 16 * p);
-      if (lane < 16) {
-#pragma unroll
-        for (int k = 0; k < 16; ++k) W[(16 * p + k) * SL + 16 * p + lane] = g.a[k];
-      }
-    } else {
-      // beside panel p: the updates by panel p - 1 that panel p does not need, and the next finished row of W
-      if (p == 1) s_update(wave == 0 ? 2 : 3, wave == 2 ? 3 : 2, 0);
-      if (p == 2 && wave == 2) s_update(3, 3, 1);
-      if (p >= 2 && wave < p - 1) w_block(p - 1, wave);
-    }
-    lds_barrier();
-    if (p == 3) break;
-    if (wave < 3 - p) s_update(p + 1 + wave, p + 1, p);     // the next panel's columns
-    lds_barrier();
-  }
-  if (wave < 3) w_block(3, wave);
+    for (int r = 0; r < 4; ++r) S[(16 * i + 4 * r + lq) * SL + 16 * k + l16] = c[r];
+  };
+  doublex4 t2, t3;                     // sums of wavefront c < 3 for W(2, c) and W(3, c)
+  t2 = t3 = doublex4{0.0, 0.0, 0.0, 0.0};
+  const int i2 = wave == 0 ? 2 : 3, k2 = wave == 2 ? 3 : 2;      // the wavefront's block of the last two block columns
+  // beside panel 0
+  doublex4 c1 = block(1, 1 + wave, 1);
+  beside();
   lds_barrier();
+  s_update(c1, 1 + wave, 1, 0);        // the next panel's columns
+  s_put(c1, 1 + wave, 1);
+  lds_barrier();
+  // beside panel 1
+  doublex4 c2 = block(2, i2, k2);
+  s_update(c2, i2, k2, 0);
+  if (wave == 0) put_diag(0);
+  lds_barrier();
+  if (wave < 2) {
+    s_update(c2, i2, k2, 1);
+    s_put(c2, i2, k2);
+  }
+  lds_barrier();
+  // beside panel 2
+  if (wave == 0) {
+    doublex4 t1 = doublex4{0.0, 0.0, 0.0, 0.0};
+    w_add(t1, 1, 0, 0);
+    w_finish(t1, 1, 0);
+    w_add(t2, 2, 0, 0);
+    w_add(t2, 2, 1, 0);
+  } else if (wave == 1) {
+    w_add(t2, 2, 1, 1);
+    w_add(t3, 3, 1, 1);
+    put_diag(1);
+  } else {
+    s_update(c2, 3, 3, 1);
+  }
+  lds_barrier();
+  if (wave == 2) {
+    s_update(c2, 3, 3, 2);
+    s_put(c2, 3, 3);
+  }
+  lds_barrier();
+  // beside panel 3
+  if (wave == 0) {
+    w_add(t3, 3, 0, 0);
+    w_add(t3, 3, 1, 0);
+  }
+  if (wave < 2) w_finish(t2, 2, wave);
+  else put_diag(2);
+  w_add(t3, 3, 2, wave);
+  // blocks of L^-1 above the diagonal
+#pragma unroll
+  for (int c = 1; c < 4; ++c)
+    if (wave < c)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int m = 16 * wave + 4 * r + lq, k = 16 * c + l16;
+        if (m < jb && k < jb) out[(long long)m * ldo + k] = 0.0;
+      }
+  lds_barrier();
+  w_finish(t3, 3, wave);
 }
 
 // One launch of the chain: everything that step t can do once the steps before it are complete.  Panels are 64 columns
@@ -440,39 +561,45 @@ __device__ __forceinline__ void diag_block(StepShared& sh, int tid) {
 //   P(t + 1):  L(t+1, t) = A(t+1, t) L(t, t)^-T,  A(t+1, t+1) -= L(t+1, t) L(t+1, t)^T, and the factor of that diagonal
 //              tile, inverted: Linv(t+1, t+1)
 //   P(i):      L(i, t) = (A(i, t) - L(i, t-1) L(t, t-1)^T) L(t, t)^-T,  A(i, i) -= L(i, t) L(i, t)^T
-//   P(t + 2):  the same, and what the next launch's first task would otherwise have to begin with: both panels' part of
-//              A(t+2, t+1), for which it forms L(t+1, t) a second time
+//   ahead(h):  rows 32 h .. of what the next launch's first task would otherwise have to begin with: both panels' part of
+//              A(t+2, t+1), for which it forms those rows of L(t+2, t) and L(t+1, t) a second time
 //   R(c):      Linv(t, c) = L(t, t)^-1 (V(t, c) - L(t, t-1) Linv(t-1, c)),  c < t
 //   TA(i, k):  A(i, k) -= L(i, t-1) L(k, t-1)^T,  i > k > t, (i, k) != (t + 2, t + 1)
 //   TV(i, c):  V(i, c) -= L(i, t-1) Linv(t-1, c),  i > t, c < t
-// No workgroup of a launch reads what another one of it writes: the tiles L(t+1, t) go to a buffer of their own (sub)
-// because P(t + 2) reads what they would replace.  A launch costs what P(t + 1) does while the others fit beside it: one
-// and a half 64^3 products at the 0.3 TFLOP/s of one CU and the diagonal tile's chain of 64 pivots, 17 us up to n = 1536.
-// Larger orders are bound by the trailing tiles' traffic (39 us a launch on average at n = 4915).
-// Groups of two or four panels (fewer passes over the tiles behind) were slower at every order up to 4915.
+// No workgroup of a launch reads what another one of it writes: L(t+1, t) and L(t+2, t) go to a buffer of their own (near_l)
+// because ahead reads what they would replace; the next launch is the last to read them.  A launch costs what P(t + 1) does
+// while the others fit beside it: 5 us for two 64^3 products at the 0.3 TFLOP/s of one CU and their operands, of which the
+// second needs only its first 16 columns before the diagonal tile's chain of 64 pivots can begin, and 6 us for that chain.
+// us a launch up to n = 1013: 17.5 with one workgroup for P(t + 2) and ahead, which took longer than P(t + 1), 14.0 with these
+// apart, 13.0 with fewer stores in the chain, 12.2 with the second product beside the chain; whole chain n = 768 227 -> 158,
+// 1536 460 -> 323, 2048 620 -> 509, 3277 1250 -> 1092.
+// Larger orders are bound by the trailing tiles' traffic (39 us a launch on average at n = 4915).  Two panels per pass over
+// them in every second launch: 3277 and below no faster, 4915 3.04 -> 2.76 ms; not kept for 0.4 ms of a step of 85.
 struct StepP {
   double* A; long long ld;
   double* V; long long ldv;     // Linv
-  double* sub;                  // [tiles][NB * NB] L(t, t - 1)
+  double* sub;                  // up to four tiles [NB * NB]: L(t+1, t) and L(t+2, t) of this launch and the last (near_l)
   int n, N;                     // order, tiles
   int t;
   int each;                     // tiles of TA and TV per workgroup
   int32_t* status;
 };
 
-// 64 x 64 global tile (row-major) -> registers; rows [0, rv) and columns [0, cv) are valid
+// 64 x 64 global tile (row-major) -> registers; rows [0, rv) and columns [0, cv) are valid.  src is the same for the whole
+// wavefront: one 32-bit offset per lane, the rows' distances are scalar.
 struct TileRegs {
   doublex2 r[8];
   __device__ __forceinline__ void load(const double* src, long long ld, int rv, int cv) {
     const int ch = threadIdx.x & 31, row0 = threadIdx.x >> 5;
+    const unsigned int off = ((unsigned int)row0 * (unsigned int)ld + 2u * ch) * 8u;
     if (rv >= NB && cv >= NB) {
 #pragma unroll
-      for (int q = 0; q < 8; ++q) r[q] = *(const doublex2*)(src + (long long)(row0 + 8 * q) * ld + 2 * ch);
+      for (int q = 0; q < 8; ++q) r[q] = *(const doublex2*)((const char*)(src + 8 * q * ld) + off);
     } else {
 #pragma unroll
       for (int q = 0; q < 8; ++q) {
         const int row = row0 + 8 * q;
-        const double* p = src + (long long)row * ld + 2 * ch;
+        const double* p = (const double*)((const char*)(src + 8 * q * ld) + off);
         r[q] = doublex2{(row < rv && 2 * ch < cv) ? p[0] : 0.0, (row < rv && 2 * ch + 1 < cv) ? p[1] : 0.0};
       }
     }
@@ -490,26 +617,26 @@ struct TileRegs {
 };
 
 // acc += tile product of two LDS images (A always KC)
-template <bool BKC>
-__device__ __forceinline__ void tile_mma(const double* ia, const double* ib, int wm, int wn, int lane, doublex4 (&acc)[2][2]) {
+template <bool BKC, int NI>
+__device__ __forceinline__ void tile_mma(const double* ia, const double* ib, int wm, int wn, int lane, doublex4 (&acc)[NI][2]) {
   const int l16 = lane & 15, lq = lane >> 4;
 #pragma unroll 2
   for (int c = 0; c < 8; ++c) {
     const int k = 8 * c + 2 * lq;
-    doublex2 af[2], bf[2];
+    doublex2 af[NI], bf[2];
 #pragma unroll
-    for (int i = 0; i < 2; ++i) af[i] = *(const doublex2*)(ia + kc_off<NB>(k, wm + 16 * i + l16));
+    for (int i = 0; i < NI; ++i) af[i] = *(const doublex2*)(ia + kc_off<NB>(k, wm + 16 * i + l16));
 #pragma unroll
     for (int j = 0; j < 2; ++j) {
       if (BKC) bf[j] = *(const doublex2*)(ib + kc_off<NB>(k, wn + 16 * j + l16));
       else bf[j] = doublex2{ib[rc_off<NB>(k, wn + 16 * j + l16)], ib[rc_off<NB>(k + 1, wn + 16 * j + l16)]};
     }
 #pragma unroll
-    for (int i = 0; i < 2; ++i)
+    for (int i = 0; i < NI; ++i)
 #pragma unroll
       for (int j = 0; j < 2; ++j) acc[i][j] = mma_f64(af[i].x, bf[j].x, acc[i][j]);
 #pragma unroll
-    for (int i = 0; i < 2; ++i)
+    for (int i = 0; i < NI; ++i)
 #pragma unroll
       for (int j = 0; j < 2; ++j) acc[i][j] = mma_f64(af[i].y, bf[j].y, acc[i][j]);
   }
@@ -520,28 +647,34 @@ __device__ __forceinline__ void tile_mma(const double* ia, const double* ib, int
 __device__ __forceinline__ int tri_tile(int half, int j) { return half ? 1 + j : 3 * j; }
 // acc[i][j] = T (rows wm + 16 i) times M^T (columns 16 tri_tile(half, j)), M lower triangular; both KC images.  Even and odd
 // contraction steps are summed apart: a chain on one accumulator runs at the instruction's latency, four keep it busy.
-__device__ __forceinline__ void mma_lower_t(const double* it, const double* im, int wm, int half, int lane, doublex4 (&acc)[2][2]) {
+template <int NI, int NT>
+__device__ __forceinline__ void mma_lower_t_col(const double* it, const double* im, int wm, int lane, doublex4 (&acc)[NI][2], int j) {
   const int l16 = lane & 15, lq = lane >> 4;
+  doublex4 s[NI][2];
 #pragma unroll
-  for (int j = 0; j < 2; ++j) {
-    const int nt = tri_tile(half, j);
-    doublex4 s[2][2];
+  for (int i = 0; i < NI; ++i) s[i][0] = s[i][1] = doublex4{0.0, 0.0, 0.0, 0.0};
 #pragma unroll
-    for (int i = 0; i < 2; ++i) s[i][0] = s[i][1] = doublex4{0.0, 0.0, 0.0, 0.0};
-    for (int c2 = 0; c2 <= nt; ++c2)
+  for (int c = 0; c < 2 * (NT + 1); ++c) {
+    const int k = 8 * c + 2 * lq;
+    const doublex2 b = *(const doublex2*)(im + kc_off<NB>(k, 16 * NT + l16));
 #pragma unroll
-    for (int c = 2 * c2; c < 2 * c2 + 2; ++c) {
-      const int k = 8 * c + 2 * lq;
-      const doublex2 b = *(const doublex2*)(im + kc_off<NB>(k, 16 * nt + l16));
-#pragma unroll
-      for (int i = 0; i < 2; ++i) {
-        const doublex2 a = *(const doublex2*)(it + kc_off<NB>(k, wm + 16 * i + l16));
-        s[i][0] = mma_f64(a.x, b.x, s[i][0]);
-        s[i][1] = mma_f64(a.y, b.y, s[i][1]);
-      }
+    for (int i = 0; i < NI; ++i) {
+      const doublex2 a = *(const doublex2*)(it + kc_off<NB>(k, wm + 16 * i + l16));
+      s[i][0] = mma_f64(a.x, b.x, s[i][0]);
+      s[i][1] = mma_f64(a.y, b.y, s[i][1]);
     }
+  }
 #pragma unroll
-    for (int i = 0; i < 2; ++i) acc[i][j] = s[i][0] + s[i][1];
+  for (int i = 0; i < NI; ++i) acc[i][j] = s[i][0] + s[i][1];
+}
+template <int NI>
+__device__ __forceinline__ void mma_lower_t(const double* it, const double* im, int wm, int half, int lane, doublex4 (&acc)[NI][2]) {
+  if (half) {
+    mma_lower_t_col<NI, 1>(it, im, wm, lane, acc, 0);
+    mma_lower_t_col<NI, 2>(it, im, wm, lane, acc, 1);
+  } else {
+    mma_lower_t_col<NI, 0>(it, im, wm, lane, acc, 0);
+    mma_lower_t_col<NI, 3>(it, im, wm, lane, acc, 1);
   }
 }
 // acc[i][j] = M (rows 16 tri_tile(half, i), lower triangular, KC image) times T (columns wn + 16 j, RC image)
@@ -570,84 +703,65 @@ __device__ __forceinline__ void mma_lower(const double* im, const double* it, in
 }
 
 // the 64 x 64 tile at `src` in the accumulator layout (this lane's 16 elements; past a ragged edge the edge's)
-__device__ __forceinline__ void load_acc(const double* src, long long ld, int rv, int cv, int wm, int wn, int lane, doublex4 (&c)[2][2]) {
+template <int NI>
+__device__ __forceinline__ void load_acc(const double* src, long long ld, int rv, int cv, int wm, int wn, int lane, doublex4 (&c)[NI][2]) {
   const int l16 = lane & 15, lq = lane >> 4;
   const bool full = rv >= NB && cv >= NB;
 #pragma unroll
-  for (int i = 0; i < 2; ++i)
+  for (int i = 0; i < NI; ++i)
 #pragma unroll
     for (int j = 0; j < 2; ++j)
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
-        // a clamped address keeps the ragged case free of branches
-        int m = wm + 16 * i + 4 * r + lq, k = wn + 16 * j + l16;
-        if (!full) {
-          m = m < rv ? m : rv - 1;
-          k = k < cv ? k : cv - 1;
+        const int m = wm + 16 * i + 4 * r, k = wn + 16 * j;
+        if (full) {
+          c[i][j][r] = *(const double*)((const char*)(src + m * ld + k) + ((unsigned int)lq * (unsigned int)ld + l16) * 8u);
+        } else {                // a clamped address keeps the ragged case free of branches
+          const unsigned int mc = m + lq < rv ? m + lq : rv - 1, kc = k + l16 < cv ? k + l16 : cv - 1;
+          c[i][j][r] = *(const double*)((const char*)src + (mc * (unsigned int)ld + kc) * 8u);
         }
-        c[i][j][r] = src[(long long)m * ld + k];
       }
 }
-__device__ __forceinline__ void store_acc(double* dst, long long ld, int rv, int cv, int wm, int wn, int lane, const doublex4 (&c)[2][2]) {
+template <int NI>
+__device__ __forceinline__ void store_acc(double* dst, long long ld, int rv, int cv, int wm, int wn, int lane, const doublex4 (&c)[NI][2]) {
   const int l16 = lane & 15, lq = lane >> 4;
   const bool full = rv >= NB && cv >= NB;
 #pragma unroll
-  for (int i = 0; i < 2; ++i)
+  for (int i = 0; i < NI; ++i)
 #pragma unroll
     for (int j = 0; j < 2; ++j)
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
-        const int m = wm + 16 * i + 4 * r + lq, k = wn + 16 * j + l16;
-        if (full || (m < rv && k < cv)) dst[(long long)m * ld + k] = c[i][j][r];
+        const int m = wm + 16 * i + 4 * r, k = wn + 16 * j;
+        if (full || (m + lq < rv && k + l16 < cv))
+          *(double*)((char*)(dst + m * ld + k) + ((unsigned int)lq * (unsigned int)ld + l16) * 8u) = c[i][j][r];
       }
 }
-__device__ __forceinline__ void zero_acc(doublex4 (&c)[2][2]) {
+template <int NI>
+__device__ __forceinline__ void zero_acc(doublex4 (&c)[NI][2]) {
 #pragma unroll
-  for (int i = 0; i < 2; ++i)
+  for (int i = 0; i < NI; ++i)
 #pragma unroll
     for (int j = 0; j < 2; ++j) c[i][j] = doublex4{0.0, 0.0, 0.0, 0.0};
 }
 
-// factor the diagonal tile in sh.a and write the inverse of its factor to Linv's diagonal tile
-template <typename Beside>
-__device__ __forceinline__ void finish_diag(const StepP& p, int t, StepShared& sh, Beside beside) {
-  const int tid = threadIdx.x;
-  if (tid < 192) beside();            // what the wavefronts off the pivot chain still have to store
-  diag_block(sh, tid);
-  if (tid >= 192) beside();
-  const int jb = p.n - t * NB < NB ? p.n - t * NB : NB;
-  if (tid < NB) {
-    const double d = sh.piv[tid];
-    if (__any(!(d > 0.0)) && tid == 0) atomicCAS(p.status, 0, (int)STRP_ENOTPD);
-    sh.piv[tid] = rsqrt_f64(pivot_or_one(d));
-  }
-  lds_barrier();
-  double* vd = p.V + (long long)t * NB * p.ldv + (long long)t * NB;
-  const int k = 2 * (tid & 31), i0 = tid >> 5;
-#pragma unroll
-  for (int q = 0; q < 8; ++q) {
-    const int i = i0 + 8 * q;
-    const double rs = sh.piv[i], w0 = sh.b[i * SL + k], w1 = sh.b[i * SL + k + 1];      // read whether used or not: no branch
-    const doublex2 v = doublex2{k <= i ? w0 * rs : 0.0, k + 1 <= i ? w1 * rs : 0.0};
-    if (i < jb && k + 1 < jb) *(doublex2*)(vd + (long long)i * p.ldv + k) = v;
-    else if (i < jb && k < jb) vd[(long long)i * p.ldv + k] = v.x;
-  }
-}
-
 // this lane's elements of a result whose columns are 16 tri_tile(half, j), into a KC image (row = m, k = n)
-__device__ __forceinline__ void put_kc_tri(double* img, int wm, int half, int lane, const doublex4 (&acc)[2][2]) {
+template <int NI>
+__device__ __forceinline__ void put_kc_tri(double* img, int wm, int half, int lane, const doublex4 (&acc)[NI][2]) {
 #pragma unroll
-  for (int i = 0; i < 2; ++i)
+  for (int i = 0; i < NI; ++i)
 #pragma unroll
     for (int j = 0; j < 2; ++j)
 #pragma unroll
       for (int r = 0; r < 4; ++r) img[kc_off<NB>(16 * tri_tile(half, j) + (lane & 15), wm + 16 * i + 4 * r + (lane >> 4))] = acc[i][j][r];
 }
 
-// P(i) of launch t.  FIRST: i = t + 1 (nothing pending, factors the diagonal tile).  lookahead: i = t + 2.
+// where L(t + 1 + far, t) is, t the launch that forms it
+__device__ __forceinline__ double* near_l(const StepP& p, int t, int far) { return p.sub + (2 * far + (t & 1)) * NB * NB; }
+// P(i) of launch t.  FIRST: i = t + 1 (nothing pending, factors the diagonal tile).
 template <bool FIRST>
-__device__ __forceinline__ void step_panel(const StepP& p, StepShared& sh, int i, bool lookahead) {
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+__device__ __forceinline__ void step_panel(const StepP& p, StepShared& sh, int i) {
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = (wave >> 1) * 32, wn = (wave & 1) * 32, half = wave & 1;
   const int l16 = lane & 15, lq = lane >> 4;
   const int t = p.t;
@@ -655,8 +769,7 @@ __device__ __forceinline__ void step_panel(const StepP& p, StepShared& sh, int i
   auto At = [&](int r, int c) { return p.A + (long long)r * NB * p.ld + (long long)c * NB; };
   const double* inv_t = p.V + (long long)t * NB * (p.ldv + 1);     // L(t, t)^-1
   TileRegs ra, rb;
-  doublex4 acc[2][2], acc2[2][2];
-  zero_acc(acc2);
+  doublex4 acc[2][2];
   if (FIRST || t == 0) {                  // nothing is pending: the tile goes to LDS as it is
     ra.load(At(i, t), p.ld, rows, NB);
     rb.load(inv_t, p.ldv, NB, NB);
@@ -665,22 +778,15 @@ __device__ __forceinline__ void step_panel(const StepP& p, StepShared& sh, int i
   } else {
     doublex4 c[2][2];
     ra.load(At(i, t - 1), p.ld, rows, NB);
-    rb.load(p.sub + (long long)t * NB * NB, NB, NB, NB);
+    rb.load(near_l(p, t - 1, 0), NB, NB, NB);
     load_acc(At(i, t), p.ld, rows, NB, wm, wn, lane, c);
     ra.store_kc(sh.a);
     rb.store_kc(sh.b);
     lds_barrier();
-    if (lookahead) ra.load(At(t + 1, t - 1), p.ld, NB, NB);
     rb.load(inv_t, p.ldv, NB, NB);
     zero_acc(acc);
     tile_mma<true>(sh.a, sh.b, wm, wn, lane, acc);
     lds_barrier();
-    if (lookahead) {
-      ra.store_kc(sh.b);
-      lds_barrier();
-      tile_mma<true>(sh.a, sh.b, wm, wn, lane, acc2);
-      lds_barrier();
-    }
 #pragma unroll
     for (int ii = 0; ii < 2; ++ii)
 #pragma unroll
@@ -689,11 +795,17 @@ __device__ __forceinline__ void step_panel(const StepP& p, StepShared& sh, int i
         for (int r = 0; r < 4; ++r) sh.a[kc_off<NB>(wn + 16 * j + l16, wm + 16 * ii + 4 * r + lq)] = c[ii][j][r] - acc[ii][j][r];
     rb.store_kc(sh.b);
   }
-  if (!FIRST && lookahead) ra.load(At(t + 1, t), p.ld, NB, NB);
-  // lower 16 x 16 tiles of the diagonal tile A(i, i): three for wavefronts 0 and 1, two (and one of them again) for 2 and 3
+  // 16 x 16 blocks of the diagonal tile A(i, i), lower triangle.  FIRST: block (wave, 0), which the chain begins with, and for
+  // wavefronts 0 .. 2 those that diag_block asks for.  Otherwise three for wavefronts 0 and 1, two (and one of them again) for 2 and 3
   const int dn = wave < 2 ? 3 : 2;
-  const auto drow = [&](int q) { return wave == 0 ? (q > 0) : wave == 1 ? 2 : 3; };
-  const auto dcol = [&](int q) { return wave == 0 ? (q > 1) : wave == 1 ? q : wave == 2 ? q : 2 + (q & 1); };
+  const auto drow = [&](int q) {
+    if (FIRST) return q == 0 ? wave : q == 1 ? (wave < 3 ? 1 + wave : 3) : wave == 0 ? 2 : 3;
+    return wave == 0 ? int(q > 0) : wave == 1 ? 2 : 3;
+  };
+  const auto dcol = [&](int q) {
+    if (FIRST) return q == 0 ? 0 : q == 1 ? 1 : wave < 2 ? 2 : 3;
+    return wave == 0 ? int(q > 1) : wave == 1 ? q : wave == 2 ? q : 2 + (q & 1);
+  };
   doublex4 dc[3];
 #pragma unroll
   for (int q = 0; q < 3; ++q)
@@ -709,8 +821,9 @@ __device__ __forceinline__ void step_panel(const StepP& p, StepShared& sh, int i
   lds_barrier();
   put_kc_tri(sh.a, wm, half, lane, acc);
   auto store_l = [&] {
-    double* out = FIRST ? p.sub + (long long)i * NB * NB : At(i, t);
-    const long long ldo = FIRST ? NB : p.ld;
+    const bool aside = i <= t + 2;
+    double* out = aside ? near_l(p, t, i - t - 1) : At(i, t);
+    const long long ldo = aside ? NB : p.ld;
 #pragma unroll
     for (int ii = 0; ii < 2; ++ii)
 #pragma unroll
@@ -718,16 +831,44 @@ __device__ __forceinline__ void step_panel(const StepP& p, StepShared& sh, int i
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
           const int m = wm + 16 * ii + 4 * r + lq;
-          if (FIRST || m < jb) out[(long long)m * ldo + 16 * tri_tile(half, j) + l16] = acc[ii][j][r];
+          if (aside || m < jb) out[(long long)m * ldo + 16 * tri_tile(half, j) + l16] = acc[ii][j][r];
         }
   };
   if (!FIRST) store_l();
   lds_barrier();
+  if constexpr (FIRST) {
+    // rows of L past the edge are zero: what is put there stays
+    auto block = [&](int q) {
+      doublex4 u[2];
+      u[0] = u[1] = doublex4{0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+      for (int cc = 0; cc < 8; ++cc) {
+        const int k = 8 * cc + 2 * lq;
+        const doublex2 x = *(const doublex2*)(sh.a + kc_off<NB>(k, 16 * drow(q) + l16)), y = *(const doublex2*)(sh.a + kc_off<NB>(k, 16 * dcol(q) + l16));
+        u[0] = mma_f64(x.x, y.x, u[0]);
+        u[1] = mma_f64(x.y, y.y, u[1]);
+      }
+      doublex4 v = dc[q];
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int m = 16 * drow(q) + 4 * r + lq, k = 16 * dcol(q) + l16;
+        if (jb < NB) v[r] = m < jb && k < jb ? v[r] : (m == k ? 1.0 : 0.0);
+      }
+      return v - (u[0] + u[1]);
+    };
+    put_eye(sh, tid);                     // sh.b: its readers are past the barrier before last
+    const doublex4 c0 = block(0);
+#pragma unroll
+    for (int r = 0; r < 4; ++r) sh.b[(16 * wave + 4 * r + lq) * SL + l16] = c0[r];
+    lds_barrier();
+    diag_block(sh, tid, p.V + (long long)i * NB * (p.ldv + 1), p.ldv, jb, p.status, [&](int q, int, int) { return block(q); }, store_l);
+    return;
+  }
   {
     doublex4 s[3][2];
 #pragma unroll
     for (int q = 0; q < 3; ++q) s[q][0] = s[q][1] = doublex4{0.0, 0.0, 0.0, 0.0};
-#pragma unroll 2
+#pragma unroll
     for (int cc = 0; cc < 8; ++cc) {
       const int k = 8 * cc + 2 * lq;
       doublex2 x[3], y[3];
@@ -744,20 +885,6 @@ __device__ __forceinline__ void step_panel(const StepP& p, StepShared& sh, int i
 #pragma unroll
     for (int q = 0; q < 3; ++q) dc[q] -= s[q][0] + s[q][1];
   }
-  if (FIRST) {
-    lds_barrier();
-#pragma unroll
-    for (int q = 0; q < 3; ++q)
-      if (q < dn)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          const int m = 16 * drow(q) + 4 * r + lq, k = 16 * dcol(q) + l16;
-          sh.a[m * SL + k] = m < jb && k < jb ? dc[q][r] : (m == k ? 1.0 : 0.0);
-        }
-    lds_barrier();
-    finish_diag(p, i, sh, store_l);
-    return;
-  }
 #pragma unroll
   for (int q = 0; q < 3; ++q)
     if (q < dn)
@@ -766,30 +893,75 @@ __device__ __forceinline__ void step_panel(const StepP& p, StepShared& sh, int i
         const int m = 16 * drow(q) + 4 * r + lq, k = 16 * dcol(q) + l16;
         if (m < jb && k < jb) At(i, i)[(long long)m * p.ld + k] = dc[q][r];
       }
-  if (!lookahead) return;
-  // A(t+2, t+1) -= L(t+2, t-1) L(t+1, t-1)^T (in acc2) + L(t+2, t) L(t+1, t)^T
-  doublex4 c[2][2], lx[2][2];
+}
+
+// What the next launch's first task would otherwise have to begin with, rows 32 h .. of the tile: both panels' part of
+// A(t+2, t+1), for which L(t+2, t) is formed once more (these rows), and L(t+1, t).
+__device__ __forceinline__ void step_ahead(const StepP& p, StepShared& sh, int h) {
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wm = 32 * h + (wave >> 1) * 16, wn = (wave & 1) * 32, half = wave & 1;
+  const int l16 = lane & 15, lq = lane >> 4;
+  const int t = p.t, i = t + 2, rows = p.n - i * NB;
+  auto At = [&](int r, int c) { return p.A + (long long)r * NB * p.ld + (long long)c * NB; };
+  const double* inv_t = p.V + (long long)t * NB * (p.ldv + 1);
+  TileRegs ra, rb;
+  doublex4 acc[1][2], acc2[1][2], c[1][2], lx[2][2];
+  zero_acc(acc2);
+  if (t == 0) {
+    ra.load(At(i, t), p.ld, rows, NB);
+    rb.load(inv_t, p.ldv, NB, NB);
+    ra.store_kc(sh.a);
+    rb.store_kc(sh.b);
+  } else {
+    ra.load(At(i, t - 1), p.ld, rows, NB);
+    rb.load(near_l(p, t - 1, 0), NB, NB, NB);
+    load_acc(At(i, t), p.ld, rows, NB, wm, wn, lane, c);
+    ra.store_kc(sh.a);
+    rb.store_kc(sh.b);
+    lds_barrier();
+    ra.load(near_l(p, t - 1, 1), NB, NB, NB);
+    rb.load(inv_t, p.ldv, NB, NB);
+    zero_acc(acc);
+    tile_mma<true>(sh.a, sh.b, wm, wn, lane, acc);
+    lds_barrier();
+    ra.store_kc(sh.b);
+    lds_barrier();
+    tile_mma<true>(sh.a, sh.b, wm, wn, lane, acc2);
+    lds_barrier();
+#pragma unroll
+    for (int j = 0; j < 2; ++j)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) sh.a[kc_off<NB>(wn + 16 * j + l16, wm + 4 * r + lq)] = c[0][j][r] - acc[0][j][r];
+    rb.store_kc(sh.b);
+  }
+  ra.load(At(t + 1, t), p.ld, NB, NB);
   load_acc(At(i, t + 1), p.ld, rows, NB, wm, wn, lane, c);
+  lds_barrier();
+  mma_lower_t(sh.a, sh.b, wm, half, lane, acc);
   lds_barrier();
   ra.store_kc(sh.a);
   lds_barrier();
-  mma_lower_t(sh.a, sh.b, wm, half, lane, lx);
+  mma_lower_t(sh.a, sh.b, (wave >> 1) * 32, half, lane, lx);
   lds_barrier();
   put_kc_tri(sh.a, wm, half, lane, acc);
-  put_kc_tri(sh.b, wm, half, lane, lx);
+  put_kc_tri(sh.b, (wave >> 1) * 32, half, lane, lx);
   lds_barrier();
   tile_mma<true>(sh.a, sh.b, wm, wn, lane, acc2);
 #pragma unroll
-  for (int ii = 0; ii < 2; ++ii)
-#pragma unroll
-    for (int j = 0; j < 2; ++j) c[ii][j] -= acc2[ii][j];
+  for (int j = 0; j < 2; ++j) c[0][j] -= acc2[0][j];
   store_acc(At(i, t + 1), p.ld, rows, NB, wm, wn, lane, c);
 }
 
+// tiles of TA, and of TA and TV, in launch t of a chain of N tiles
+__host__ __device__ static inline int step_ta_tiles(int N, int t) {
+  const int m = N - 1 - t;                       // tile rows (and columns of A) behind column t
+  return t > 0 && m > 1 ? m * (m - 1) / 2 - 1 : 0;      // without (t + 2, t + 1), the first of the enumeration
+}
+__host__ __device__ static inline int step_tiles(int N, int t) { return step_ta_tiles(N, t) + (N - 1 - t) * t; }
 __global__ __launch_bounds__(256, 2) void chol_step_kernel(const StepP p) {
   __shared__ __attribute__((aligned(16))) StepShared sh;
   int b = blockIdx.x;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = (wave >> 1) * 32, wn = (wave & 1) * 32;
   const int n = p.n, N = p.N, t = p.t;
   auto rows_of = [&](int i) { return n - i * NB; };
@@ -797,18 +969,25 @@ __global__ __launch_bounds__(256, 2) void chol_step_kernel(const StepP p) {
   auto Vt = [&](int i, int k) { return p.V + (long long)i * NB * p.ldv + (long long)k * NB; };
   const int nP = N - 1 - t;
   if (b < nP) {
-    if (b == 0) step_panel<true>(p, sh, t + 1, false);
-    else step_panel<false>(p, sh, t + 1 + b, b == 1);
+    if (b == 0) step_panel<true>(p, sh, t + 1);
+    else step_panel<false>(p, sh, t + 1 + b);
     return;
   }
   b -= nP;
+  if (nP > 1) {
+    if (b < 2) {
+      step_ahead(p, sh, b);
+      return;
+    }
+    b -= 2;
+  }
   doublex4 acc[2][2], c[2][2];
   zero_acc(acc);
   zero_acc(c);
   TileRegs ra, rb;
   if (b < t) {                                                        // ---- R(c)
     const int cc = b;
-    ra.load(p.sub + (long long)t * NB * NB, NB, NB, NB);
+    ra.load(near_l(p, t - 1, 0), NB, NB, NB);
     rb.load(Vt(t - 1, cc), p.ldv, NB, NB);
     if (cc < t - 1) load_acc(Vt(t, cc), p.ldv, rows_of(t), NB, wm, wn, lane, c);
     ra.store_kc(sh.a);
@@ -840,9 +1019,7 @@ __global__ __launch_bounds__(256, 2) void chol_step_kernel(const StepP p) {
   }
   b -= t;
   // what is left goes to each workgroup `each` tiles at a time
-  const int m = N - 1 - t;                       // tile rows (and columns of A) behind column t
-  const int nTA = m * (m - 1) / 2 - (m > 1);     // without (t + 2, t + 1), the first of the enumeration
-  const int total = nTA + m * t;
+  const int nTA = step_ta_tiles(N, t), total = step_tiles(N, t);
   for (int e = b * p.each, e1 = e + p.each < total ? e + p.each : total; e < e1; ++e) {
     if (e > b * p.each) {
       lds_barrier();
@@ -853,10 +1030,12 @@ __global__ __launch_bounds__(256, 2) void chol_step_kernel(const StepP p) {
       int i = (int)((__builtin_sqrtf(8.0f * (float)(e + 1) + 1.0f) - 1.0f) * 0.5f);
       while (i * (i + 1) / 2 > e + 1) --i;
       while ((i + 1) * (i + 2) / 2 <= e + 1) ++i;
+      i = __builtin_amdgcn_readfirstlane(i);
       const int k = e + 1 - i * (i + 1) / 2 + t + 1;
       i += t + 2;
       ra.load(At(i, t - 1), p.ld, rows_of(i), NB);
-      rb.load(At(k, t - 1), p.ld, NB, NB);
+      if (k == t + 1) rb.load(near_l(p, t - 1, 1), NB, NB, NB);
+      else rb.load(At(k, t - 1), p.ld, NB, NB);
       load_acc(At(i, k), p.ld, rows_of(i), NB, wm, wn, lane, c);
       ra.store_kc(sh.a);
       rb.store_kc(sh.b);
@@ -869,7 +1048,8 @@ __global__ __launch_bounds__(256, 2) void chol_step_kernel(const StepP p) {
       store_acc(At(i, k), p.ld, rows_of(i), NB, wm, wn, lane, c);
     } else {                                                          // ---- TV(i, c)
       const int i = t + 1 + (e - nTA) / t, cc = (e - nTA) % t;
-      ra.load(At(i, t - 1), p.ld, rows_of(i), NB);
+      if (i == t + 1) ra.load(near_l(p, t - 1, 1), NB, NB, NB);
+      else ra.load(At(i, t - 1), p.ld, rows_of(i), NB);
       rb.load(Vt(t - 1, cc), p.ldv, NB, NB);
       if (cc < t - 1) load_acc(Vt(i, cc), p.ldv, rows_of(i), NB, wm, wn, lane, c);
       ra.store_kc(sh.a);
@@ -893,13 +1073,23 @@ __global__ __launch_bounds__(256, 2) void chol_begin_kernel(const StepP p, int c
   if (blockIdx.x == 0) {
     const int jb = p.n < NB ? p.n : NB;
     const int k = tid & 63;
-#pragma unroll 4
+    put_eye(sh, tid);
+#pragma unroll
     for (int q = 0; q < 16; ++q) {
       const int i = (tid >> 6) + 4 * q;
-      sh.a[i * SL + k] = i < jb && k <= i ? p.A[(long long)i * p.ld + k] : (i == k ? 1.0 : 0.0);
+      const bool in = i < jb && k <= i;
+      const double v = p.A[in ? (long long)i * p.ld + k : 0];
+      sh.b[i * SL + k] = in ? v : (i == k ? 1.0 : 0.0);
     }
     lds_barrier();
-    finish_diag(p, 0, sh, [] {});
+    diag_block(sh, tid, p.V, p.ldv, jb, p.status,
+               [&](int, int i, int c) {
+                 doublex4 v;
+#pragma unroll
+                 for (int r = 0; r < 4; ++r) v[r] = sh.b[(16 * i + 4 * r + (tid >> 4 & 3)) * SL + 16 * c + (tid & 15)];
+                 return v;
+               },
+               [] {});
     return;
   }
   if ((int)blockIdx.x > clear) {
@@ -936,15 +1126,15 @@ strp_status chol_inverse(strp_ctx* ctx, double* A, int n, long long ld, double* 
   for (int t = 0; t < p.N; ++t) {
     p.t = t;
     const int m = p.N - 1 - t;
-    // up to three tiles each, so that a launch of a small system leaves the critical workgroup a CU of its own; beyond 1024
-    // tiles the launch is theirs and a workgroup that takes several only ends later.  One tile each / up to three / this, us
-    // for the whole chain: n = 1536 470 / 461 / 460, 2048 660 / 612 / 615, 2458 838 / 818 / 816, 3277 1213 / 1256 / 1235,
-    // 4096 1854 / 2094 / 1871, 4915 3019 / 3187 / 3039
-    const int total = t > 0 ? m * (m - 1) / 2 - (m > 1) + m * t : 0;
+    // up to three tiles each, so that a launch of a small system leaves the critical workgroup a CU of its own; beyond 512
+    // tiles the launch is theirs and a workgroup that takes several only ends later.  One tile each / up to three below 512 / up to
+    // three below 1024, us for the whole chain: n = 1536 341 / 323 / 325, 2048 517 / 509 / 512, 2458 654 / 639 / 683,
+    // 3277 1107 / 1092 / 1167, 4096 1851 / 1835 / 1876
+    const int total = step_tiles(p.N, t);
     p.each = (total + 191) / 192;
-    if (p.each > 3) p.each = total > 1024 ? 1 : 3;
+    if (p.each > 3) p.each = total > 512 ? 1 : 3;
     if (p.each < 1) p.each = 1;
-    const int blocks = m + t + (total + p.each - 1) / p.each;
+    const int blocks = m + (m > 1 ? 2 : 0) + t + (total + p.each - 1) / p.each;
     if (blocks > 0) hipLaunchKernelGGL(chol_step_kernel, dim3(blocks), dim3(256), 0, ctx->stream, p);      // none: a single tile, the first launch was all
   }
   STRP_HIP(ctx, hipGetLastError());

@@ -49,6 +49,24 @@ def test_factor_inverse_and_solve(ctx, n, m):
     assert torch.equal(W, W2)
 
 
+@pytest.mark.parametrize("n", [64, 128, 190, 200, 333, 768])
+def test_factor_is_the_same_every_time(ctx, n):
+    """No workgroup of a launch reads what another one of it writes: the same bits and status in every run."""
+    g = torch.Generator(device="cuda").manual_seed(n)
+    B = torch.randn((n, n + 8), generator=g, device="cuda") / (n + 8) ** 0.5
+    G = B @ B.T
+    lhs, rhs = (torch.randn((r, 24), generator=g, device="cuda") for r in (8, n))
+    idx = torch.arange(n, dtype=torch.int32, device="cuda")
+    W = torch.empty((8, n), device="cuda")
+    first = None
+    for _ in range(25):
+        chol = torch.empty((n, n), dtype=torch.float64, device="cuda")
+        ctx.strp_refit(strp.SIDE_FC2, G, 0.05, lhs, rhs, 24, idx, W, chol=chol, chol_valid=False)
+        assert ctx.poll() == strp.OK
+        first = chol if first is None else first
+        assert torch.equal(chol, first)
+
+
 @pytest.mark.parametrize("n,m", LARGE_SYSTEMS)
 def test_large_factor_and_solve(n, m):
     """Orders with several trailing tiles per workgroup and right-hand sides on the larger tiles, all entries: Linv S Linv^T = I
