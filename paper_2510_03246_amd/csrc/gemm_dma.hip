@@ -53,7 +53,13 @@ __device__ __forceinline__ void wait_vmcnt_lgkm0() {
 // the next one to three pairs are in flight (LDS holds two pairs of four planes, three of three, four of two), and the
 // slots of pair p are refilled as soon as every wavefront has its last fragment of the pair in registers.  The Q fragments of a pair stay in registers (double
 // buffered across pairs), the P fragments stream through two register sets.
-template <int NPP, int NPQ>
+// TOKENS: the accumulators are transposed (the instruction's operands exchanged), for the epilogues that move four consecutive
+// columns per lane (PARTIAL, AUPD, ZUPD); the others write operand planes, whose chunks are consecutive rows.
+// It is also the cheaper order for the matrix cores, which are bound by power on real data: the operand that stays the same over
+// four instructions is the second one.  Chains of 8192 tokens, M x N = 2048 x 3277: right-hand sides 7780 -> 7590 us (three
+// passes), 5310 -> 5200 (two); z-update of 3277 x 262144 over 2048 6230 -> 6035, a-update 8390 -> 8300.  At d = 768 the two
+// are even.
+template <int NPP, int NPQ, bool TOKENS>
 __global__ __launch_bounds__(512, 1) void gemm_dma_kernel(const GemmP p) {
   using namespace dma;
   constexpr int NW = 8;
@@ -136,7 +142,7 @@ __global__ __launch_bounds__(512, 1) void gemm_dma_kernel(const GemmP p) {
     if (NPP == 2) f.l = *(const uint4*)(st + PLANE_STAGE_BYTES + offP + i * 256);
   };
   auto mma = [&](uint4 a, uint4 b, floatx4 c) {
-    return __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(half8, a), __builtin_bit_cast(half8, b), c, 0, 0, 0);
+    return __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(half8, TOKENS ? b : a), __builtin_bit_cast(half8, TOKENS ? a : b), c, 0, 0, 0);
   };
   auto pass_hl = [&](floatx4 (&c)[4], const PF& a, const QF& b) {
     if (NPQ == 2) {
@@ -217,14 +223,21 @@ __global__ __launch_bounds__(512, 1) void gemm_dma_kernel(const GemmP p) {
   if (p.P.maxbits) unscale /= scale_of_max(*p.P.maxbits);
   if (p.Q.maxbits) unscale /= scale_of_max(*p.Q.maxbits);
   double red0 = 0.0, red1 = 0.0;
-  const int mbase = m0 + wm * 128 + 8 * (lane >> 5), nbase = n0 + wn * 64 + (lane & 31);
-  switch (p.epi) {
-    case EPI_PARTIAL: epilogue16<EPI_PARTIAL>(p, acc, unscale, mbase, nbase, split, srow, m0, red0, red1); break;
-    case EPI_STORE: epilogue16<EPI_STORE>(p, acc, unscale, mbase, nbase, split, srow, m0, red0, red1); break;
-    case EPI_INITZ: epilogue16<EPI_INITZ>(p, acc, unscale, mbase, nbase, split, srow, m0, red0, red1); break;
-    case EPI_RESID: epilogue16<EPI_RESID>(p, acc, unscale, mbase, nbase, split, srow, m0, red0, red1); break;
-    case EPI_AUPD: epilogue16<EPI_AUPD>(p, acc, unscale, mbase, nbase, split, srow, m0, red0, red1); break;
-    default: epilogue16<EPI_ZUPD>(p, acc, unscale, mbase, nbase, split, srow, m0, red0, red1); break;
+  if constexpr (TOKENS) {
+    const int m0w = m0 + wm * 128, n0w = n0 + wn * 64;
+    if (p.epi == EPI_PARTIAL) token_epilogue<EPI_PARTIAL, true, false>(p, acc, unscale, m0w, n0w, split, srow, m0, red0, red1);
+    else if (p.epi == EPI_AUPD && p.rs_z0) token_epilogue<EPI_AUPD, true, true>(p, acc, unscale, m0w, n0w, split, srow, m0, red0, red1);
+    else if (p.epi == EPI_AUPD) token_epilogue<EPI_AUPD, true, false>(p, acc, unscale, m0w, n0w, split, srow, m0, red0, red1);
+    else if (!p.write_out) token_epilogue<EPI_ZUPD, false, false>(p, acc, unscale, m0w, n0w, split, srow, m0, red0, red1);
+    else if (p.rs_z0) token_epilogue<EPI_ZUPD, true, true>(p, acc, unscale, m0w, n0w, split, srow, m0, red0, red1);
+    else token_epilogue<EPI_ZUPD, true, false>(p, acc, unscale, m0w, n0w, split, srow, m0, red0, red1);
+  } else {
+    const int mbase = m0 + wm * 128 + 8 * (lane >> 5), nbase = n0 + wn * 64 + (lane & 31);
+    switch (p.epi) {
+      case EPI_STORE: epilogue16<EPI_STORE>(p, acc, unscale, mbase, nbase, m0, red0, red1); break;
+      case EPI_INITZ: epilogue16<EPI_INITZ>(p, acc, unscale, mbase, nbase, m0, red0, red1); break;
+      default: epilogue16<EPI_RESID>(p, acc, unscale, mbase, nbase, m0, red0, red1); break;
+    }
   }
   if (p.maxbits) {
     store_maxbits<NW>(p, red0, sred);
@@ -249,15 +262,19 @@ __global__ __launch_bounds__(512, 1) void gemm_dma_kernel(const GemmP p) {
   }
 }
 
-void launch_gemm_dma(strp_ctx* ctx, const GemmP& p, int npp, int npq) {
+template <int NPP, int NPQ>
+static void launch_dma(strp_ctx* ctx, const GemmP& p) {
   const dim3 grid(gemm_grid_blocks(p)), block(512);
+  if (p.epi == EPI_PARTIAL || p.epi == EPI_AUPD || p.epi == EPI_ZUPD) hipLaunchKernelGGL((gemm_dma_kernel<NPP, NPQ, true>), grid, block, 0, ctx->stream, p);
+  else hipLaunchKernelGGL((gemm_dma_kernel<NPP, NPQ, false>), grid, block, 0, ctx->stream, p);
+}
+void launch_gemm_dma(strp_ctx* ctx, const GemmP& p, int npp, int npq) {
   switch (npp * 10 + npq) {
-    case 11: hipLaunchKernelGGL((gemm_dma_kernel<1, 1>), grid, block, 0, ctx->stream, p); break;
-    case 12: hipLaunchKernelGGL((gemm_dma_kernel<1, 2>), grid, block, 0, ctx->stream, p); break;
-    case 21: hipLaunchKernelGGL((gemm_dma_kernel<2, 1>), grid, block, 0, ctx->stream, p); break;
-    default: hipLaunchKernelGGL((gemm_dma_kernel<2, 2>), grid, block, 0, ctx->stream, p); break;
+    case 11: launch_dma<1, 1>(ctx, p); break;
+    case 12: launch_dma<1, 2>(ctx, p); break;
+    case 21: launch_dma<2, 1>(ctx, p); break;
+    default: launch_dma<2, 2>(ctx, p); break;
   }
 }
-
 
 }  // namespace strp

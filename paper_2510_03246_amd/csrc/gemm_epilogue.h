@@ -79,7 +79,7 @@ __device__ __forceinline__ void decode_tile(const GemmP& p, int bid, int nblocks
 // lane's share: lane % 32 selects the column, lane / 32 the row half).  LAYOUT 0 is the accumulator of one 32x32
 // matrix-core instruction (row offsets 0, 8, 16, 24; the upper half wavefront 4 rows further down); LAYOUT 1 is what
 // four 16x16 accumulators become after exchanging quarter wavefronts between horizontal neighbours (row offsets 0, 4,
-// 16, 20; the upper half wavefront 8 rows further down), see EpilogueWalk16.
+// 16, 20; the upper half wavefront 8 rows further down), see epilogue_walk16.
 //
 // Loads are branch-free and come first: rows and the column are clamped into range so that every address is
 // valid, and the 16 loads of the tile are issued back to back.  (A predicated load costs a wait per element, and
@@ -233,7 +233,6 @@ __device__ __forceinline__ void store_maxbits(const GemmP& p, double m, double (
 // wavefront's strip of columns (64 in both kernels).  A halving butterfly: each exchange keeps half of the values a lane still holds, so
 // 8 + 4 + 2 + 1 + 1 shuffles do what 16 five-step reductions would; a lane ends with position e = (lane / 2) % 16.
 // A strip that lies wholly past column N (last block of a ragged N) has no slot and is dropped.
-template <int LAYOUT>
 __device__ __forceinline__ void rowsum_flush(const GemmP& p, const float (&rs)[16], int q, int m_tile, int slot) {
   const int l5 = threadIdx.x & 31;
   const bool b4 = l5 & 16, b3 = l5 & 8, b2 = l5 & 4, b1 = l5 & 2;
@@ -247,7 +246,7 @@ __device__ __forceinline__ void rowsum_flush(const GemmP& p, const float (&rs)[1
   float v1 = (b1 ? v2[1] : v2[0]) + __shfl_xor(b1 ? v2[0] : v2[1], 2, 64);
   v1 += __shfl_xor(v1, 1, 64);
   const int e = (l5 >> 1) & 15;
-  const int row = m_tile + tile_rowoff<LAYOUT>(e >> 2) + (e & 3);
+  const int row = m_tile + tile_rowoff<0>(e >> 2) + (e & 3);
   if (!(l5 & 1) && row < p.M && slot < p.rs_slots) p.rs_out[((long long)q * p.rs_slots + slot) * p.M + row] = v1;
 }
 
@@ -270,10 +269,10 @@ struct EpilogueWalk {
     else epilogue_tile<EPI, ZWRITE, false>(p, acc[IJ / WTN][IJ % WTN], unscale, mt, nt, split, rowmap, m_blk, red0, red1, rs0, rs1);
     if (ROWSUMS && IJ % WTN == WTN - 1 && p.rs_out) {
       if (EPI == EPI_AUPD) {
-        rowsum_flush<0>(p, rs0, 0, mt, nbase / (32 * WTN));
-        if (p.rs_z0) rowsum_flush<0>(p, rs1, 1, mt, nbase / (32 * WTN));
+        rowsum_flush(p, rs0, 0, mt, nbase / (32 * WTN));
+        if (p.rs_z0) rowsum_flush(p, rs1, 1, mt, nbase / (32 * WTN));
       } else if (p.rs_z0) {
-        rowsum_flush<0>(p, rs0, 0, mt, nbase / (32 * WTN));
+        rowsum_flush(p, rs0, 0, mt, nbase / (32 * WTN));
       }
     }
     __builtin_amdgcn_sched_barrier(0);
@@ -309,17 +308,11 @@ __device__ __forceinline__ void quarter_swap(float a, float b, float& x, float& 
 }
 
 // acc[8][4]: the wavefront's 128 x 64 outputs as 8 x 4 tiles of 16 x 16.  IJ walks its 4 x 2 tiles of 32 x 32.
-template <int EPI, bool ZWRITE, int IJ>
-struct EpilogueWalk16 {
-  static __device__ __forceinline__ void run(const GemmP& p, floatx4 (&acc)[8][4], float unscale, int mbase, int nbase, int split,
-                                             const int* rowmap, int m_blk, double& red0, double& red1, float (&rs0)[16],
-                                             float (&rs1)[16]) {
-    constexpr bool ROWSUMS = (EPI == EPI_AUPD || EPI == EPI_ZUPD) && ZWRITE;
+template <int EPI, int IJ>
+__device__ __forceinline__ void epilogue_walk16(const GemmP& p, floatx4 (&acc)[8][4], float unscale, int mbase, int nbase, int m_blk, double& red0, double& red1) {
+  if constexpr (IJ < 8) {
     constexpr int I = IJ / 2, J = IJ % 2;
-    if (ROWSUMS && J == 0) {
-#pragma unroll
-      for (int e = 0; e < 16; ++e) rs0[e] = rs1[e] = 0.0f;
-    }
+    float none[16];                 // no sums of rows here
     floatx16 a16;
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
@@ -333,34 +326,171 @@ struct EpilogueWalk16 {
     }
     const int mt = mbase + 32 * I, nt = nbase + 32 * J;
     const bool edge = __builtin_amdgcn_readfirstlane(mt) + 32 > p.M || __builtin_amdgcn_readfirstlane(nt) + 32 > p.N;
-    if (edge) epilogue_tile<EPI, ZWRITE, true, 1>(p, a16, unscale, mt, nt, split, rowmap, m_blk, red0, red1, rs0, rs1);
-    else epilogue_tile<EPI, ZWRITE, false, 1>(p, a16, unscale, mt, nt, split, rowmap, m_blk, red0, red1, rs0, rs1);
-    if (ROWSUMS && J == 1 && p.rs_out) {
-      if (EPI == EPI_AUPD) {
-        rowsum_flush<1>(p, rs0, 0, mt, nbase >> 6);
-        if (p.rs_z0) rowsum_flush<1>(p, rs1, 1, mt, nbase >> 6);
-      } else if (p.rs_z0) {
-        rowsum_flush<1>(p, rs0, 0, mt, nbase >> 6);
-      }
-    }
+    if (edge) epilogue_tile<EPI, true, true, 1>(p, a16, unscale, mt, nt, 0, nullptr, m_blk, red0, red1, none, none);
+    else epilogue_tile<EPI, true, false, 1>(p, a16, unscale, mt, nt, 0, nullptr, m_blk, red0, red1, none, none);
     __builtin_amdgcn_sched_barrier(0);
-    EpilogueWalk16<EPI, ZWRITE, IJ + 1>::run(p, acc, unscale, mbase, nbase, split, rowmap, m_blk, red0, red1, rs0, rs1);
+    epilogue_walk16<EPI, IJ + 1>(p, acc, unscale, mbase, nbase, m_blk, red0, red1);
+  }
+}
+// mbase = first row of the wavefront's tile + 8 (lane / 32), nbase = first column + lane % 32.  STORE, INITZ, RESID
+template <int EPI>
+__device__ __forceinline__ void epilogue16(const GemmP& p, floatx4 (&acc)[8][4], float unscale, int mbase, int nbase, int m_blk, double& red0, double& red1) {
+  epilogue_walk16<EPI, 0>(p, acc, unscale, mbase, nbase, m_blk, red0, red1);
+}
+
+// ---- the same for transposed 16x16 accumulators -----------------------------------------------------------------------
+// With the operands of the matrix-core instruction exchanged, lane l of a 16x16 tile holds columns 4 (l / 16) .. + 3 of row
+// l % 16: four consecutive tokens, so that state tensors and partials move 16 bytes per lane.  A tile's row is 64 bytes;
+// exchanging the upper eight rows of a tile with the lower eight of its right-hand neighbour (one row_ror:8 move per
+// register) makes it 128 bytes of eight rows per instruction.  A lane then has rows l % 8 and l % 8 + 8 of each tile row, so a
+// row's address is formed once for 64 columns and its sums over the columns are three additions and two lane swaps.
+// The loads of up to four tile rows are under way while one is computed and stored.
+typedef float floatx4u __attribute__((ext_vector_type(4), aligned(4)));      // a partial's rows begin at any multiple of four bytes
+
+template <int EPI, bool ZWRITE, bool Z0>
+struct TokenRow {
+  floatx4 in0[2][2], in1[2][2];      // [row half][column half]: AUPD Z, ZUPD A; Z0 or, without ZWRITE, Z
+  unsigned int row[2];               // row of the tensor that is stored to (0 past M)
+  __device__ __forceinline__ unsigned long long at(const GemmP& p, int h) const {
+    return (unsigned long long)row[h] * (EPI == EPI_PARTIAL ? (unsigned)p.N : (unsigned)p.lda);
+  }
+  __device__ __forceinline__ void load(const GemmP& p, int m_tile, int n_lane, int split, const int* rowmap, int m_blk) {
+    const int l8 = threadIdx.x & 7;
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      const int m = m_tile + 8 * h + l8;
+      row[h] = EPI == EPI_PARTIAL ? (unsigned)split * (unsigned)p.M + (unsigned)m : (unsigned)rowmap[m - m_blk];
+    }
+    if (EPI == EPI_PARTIAL) return;
+    const float* src = EPI == EPI_AUPD ? p.Zs : p.As;
+    const float* src1 = Z0 ? p.rs_z0 : p.Zs;
+    const int n_last = (p.N - 1) & ~3;               // a row is readable up to a multiple of eight
+#pragma unroll
+    for (int h = 0; h < 2; ++h)
+#pragma unroll
+      for (int t = 0; t < 2; ++t) {
+        const int n = n_lane + 32 * t < n_last ? n_lane + 32 * t : n_last;
+        in0[h][t] = *(const floatx4*)(src + at(p, h) + n);
+        if (Z0 || (EPI == EPI_ZUPD && !ZWRITE)) in1[h][t] = *(const floatx4*)(src1 + at(p, h) + n);
+      }
   }
 };
-template <int EPI, bool ZWRITE>
-struct EpilogueWalk16<EPI, ZWRITE, 8> {
-  static __device__ __forceinline__ void run(const GemmP&, floatx4 (&)[8][4], float, int, int, int, const int*, int, double&, double&,
-                                             float (&)[16], float (&)[16]) {}
-};
-// mbase = first row of the wavefront's tile + 8 (lane / 32), nbase = first column + lane % 32
-template <int EPI>
-__device__ __forceinline__ void epilogue16(const GemmP& p, floatx4 (&acc)[8][4], float unscale, int mbase, int nbase, int split,
-                                           const int* rowmap, int m_blk, double& red0, double& red1) {
-  float rs0[16], rs1[16];
-  if (EPI == EPI_ZUPD && !p.write_out)
-    EpilogueWalk16<EPI, false, 0>::run(p, acc, unscale, mbase, nbase, split, rowmap, m_blk, red0, red1, rs0, rs1);
-  else
-    EpilogueWalk16<EPI, true, 0>::run(p, acc, unscale, mbase, nbase, split, rowmap, m_blk, red0, red1, rs0, rs1);
+
+// the sum of v over the lanes that hold columns of the same row
+__device__ __forceinline__ float row_lanes_sum(float v) {
+  v += __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), 0x128, 0xf, 0xf, true));     // row_ror:8
+  const unsigned int a = __builtin_bit_cast(unsigned int, v);
+  const auto r = __builtin_amdgcn_permlane16_swap(a, a, false, false);
+  v = __builtin_bit_cast(float, (unsigned int)r[0]) + __builtin_bit_cast(float, (unsigned int)r[1]);
+  const unsigned int b = __builtin_bit_cast(unsigned int, v);
+  const auto q = __builtin_amdgcn_permlane32_swap(b, b, false, false);
+  return __builtin_bit_cast(float, (unsigned int)q[0]) + __builtin_bit_cast(float, (unsigned int)q[1]);
+}
+
+template <int EPI, bool ZWRITE, bool Z0, bool EDGE>
+__device__ __forceinline__ void token_row(const GemmP& p, const floatx4 (&c)[4], const TokenRow<EPI, ZWRITE, Z0>& in, float unscale, int m_tile,
+                                          int n_lane, double& red0, double& red1) {
+  constexpr bool GATHER = EPI != EPI_PARTIAL;
+  const int l8 = threadIdx.x & 7;
+  const float inv_ab = 1.0f / (p.alpha + p.beta);
+  float s0 = 0.0f, s1 = 0.0f, rs0[2] = {0.0f, 0.0f}, rs1[2] = {0.0f, 0.0f};
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+    const bool mrow = !EDGE || m_tile + 8 * h + l8 < p.M;
+#pragma unroll
+    for (int t = 0; t < 2; ++t) {
+      const int n = n_lane + 32 * t;
+      floatx4 out;
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const float left = c[2 * t][r], right = c[2 * t + 1][r];      // a copy first: a bit cast of a vector's element takes its first
+        const int lo = __builtin_bit_cast(int, left), hi = __builtin_bit_cast(int, right);
+        const float v = __builtin_bit_cast(float, h == 0 ? __builtin_amdgcn_update_dpp(lo, hi, 0x128, 0xf, 0xc, false)
+                                                         : __builtin_amdgcn_update_dpp(hi, lo, 0x128, 0xf, 0x3, false)) * unscale;
+        const bool ok = !EDGE || (mrow && n + r < p.N);
+        if (EPI == EPI_PARTIAL) {
+          out[r] = v;
+        } else if (EPI == EPI_AUPD) {
+          const float a = __builtin_fmaxf(in.in0[h][t][r], 0.0f) + v;
+          out[r] = a;
+          rs0[h] += ok ? a * a : 0.0f;
+          if (Z0) rs1[h] += ok ? a * __builtin_fmaxf(in.in1[h][t][r], 0.0f) : 0.0f;
+        } else {
+          const float a = in.in0[h][t][r], z1 = v;
+          float z;
+          if (ZWRITE) {
+            const float z2 = (p.beta * a + p.alpha * z1) * inv_ab;
+            const float cm = __builtin_fminf(z1, 0.0f);
+            const float costm = p.beta * a * a + p.alpha * (cm - z1) * (cm - z1);
+            const float cp = __builtin_fmaxf(z2, 0.0f);
+            const float costp = p.beta * (a - cp) * (a - cp) + p.alpha * (cp - z1) * (cp - z1);
+            z = costm < costp ? cm : cp;
+            out[r] = z;
+            if (Z0) rs0[h] += ok ? in.in1[h][t][r] * z : 0.0f;
+          } else {
+            z = in.in1[h][t][r];
+          }
+          const float ra = ok ? a - __builtin_fmaxf(z, 0.0f) : 0.0f;
+          const float rz = ok ? z - z1 : 0.0f;
+          s0 += ra * ra;
+          s1 += rz * rz;
+        }
+      }
+      if (!GATHER || ZWRITE) {
+        float* dst = (EPI == EPI_PARTIAL ? p.out : EPI == EPI_AUPD ? p.As : p.Zs) + in.at(p, h) + n;
+        if (!EDGE || (mrow && n + 3 < p.N)) {
+          if (EPI == EPI_PARTIAL) *(floatx4u*)dst = out;
+          else *(floatx4*)dst = out;
+        } else if (mrow) {
+#pragma unroll
+          for (int r = 0; r < 4; ++r)
+            if (n + r < p.N) dst[r] = out[r];
+        }
+      }
+      __builtin_amdgcn_sched_barrier(0);   // bounds the live temporaries to one group of four columns
+    }
+  }
+  if (EPI == EPI_ZUPD) {             // 16 terms in fp32, then fp64
+    red0 += (double)s0;
+    red1 += (double)s1;
+  }
+  if (GATHER && ZWRITE && p.rs_out && (EPI == EPI_AUPD || Z0)) {
+    // lanes 0 .. 15 store the 16 rows' sums of this strip of 64 columns; a strip wholly past column N has no slot
+    const int lane = threadIdx.x & 63, m = m_tile + lane, slot = __builtin_amdgcn_readfirstlane(n_lane) >> 6;
+    const bool put = lane < 16 && m < p.M && slot < p.rs_slots;
+    const float a0 = row_lanes_sum(rs0[0]), a1 = row_lanes_sum(rs0[1]);
+    if (put) p.rs_out[(long long)slot * p.M + m] = lane < 8 ? a0 : a1;
+    if (EPI == EPI_AUPD && Z0) {
+      const float b0 = row_lanes_sum(rs1[0]), b1 = row_lanes_sum(rs1[1]);
+      if (put) p.rs_out[((long long)p.rs_slots + slot) * p.M + m] = lane < 8 ? b0 : b1;
+    }
+  }
+}
+
+// acc[8][4]: the wavefront's 128 x 64 outputs as 8 x 4 transposed tiles of 16 x 16; m0w, n0w: its first row and column
+template <int EPI, bool ZWRITE, bool Z0, int I, int AHEAD>
+__device__ __forceinline__ void token_walk(const GemmP& p, floatx4 (&acc)[8][4], TokenRow<EPI, ZWRITE, Z0> (&in)[AHEAD], float unscale, int m0w, int n0w,
+                                           int n_lane, int split, const int* rowmap, int m_blk, double& red0, double& red1) {
+  if constexpr (I < 8) {
+    if (m0w + 16 * I + 16 > p.M || n0w + 64 > p.N) token_row<EPI, ZWRITE, Z0, true>(p, acc[I], in[I % AHEAD], unscale, m0w + 16 * I, n_lane, red0, red1);
+    else token_row<EPI, ZWRITE, Z0, false>(p, acc[I], in[I % AHEAD], unscale, m0w + 16 * I, n_lane, red0, red1);
+    __builtin_amdgcn_sched_barrier(0);
+    if constexpr (I + AHEAD < 8) in[I % AHEAD].load(p, m0w + 16 * (I + AHEAD), n_lane, split, rowmap, m_blk);
+    __builtin_amdgcn_sched_barrier(0);
+    token_walk<EPI, ZWRITE, Z0, I + 1, AHEAD>(p, acc, in, unscale, m0w, n0w, n_lane, split, rowmap, m_blk, red0, red1);
+  }
+}
+template <int EPI, bool ZWRITE, bool Z0>
+__device__ __forceinline__ void token_epilogue(const GemmP& p, floatx4 (&acc)[8][4], float unscale, int m0w, int n0w, int split, const int* rowmap,
+                                               int m_blk, double& red0, double& red1) {
+  // as many tile rows in flight as fit beside the accumulators
+  constexpr int AHEAD = EPI == EPI_PARTIAL ? 1 : (Z0 || !ZWRITE) ? 1 : EPI == EPI_AUPD ? 4 : 2;
+  const int n_lane = n0w + ((threadIdx.x & 8) << 1) + 4 * ((threadIdx.x & 63) >> 4);
+  TokenRow<EPI, ZWRITE, Z0> in[AHEAD];
+#pragma unroll
+  for (int i = 0; i < AHEAD; ++i) in[i].load(p, m0w + 16 * i, n_lane, split, rowmap, m_blk);
+  __builtin_amdgcn_sched_barrier(0);
+  token_walk<EPI, ZWRITE, Z0, 0, AHEAD>(p, acc, in, unscale, m0w, n0w, n_lane, split, rowmap, m_blk, red0, red1);
 }
 
 }  // namespace strp

@@ -1,0 +1,53 @@
+"""The a- and z-update products and split partials of the pipelined kernel (256 x 256 tiles) at sizes that are a multiple of
+nothing: edges in rows, in tokens, within the four tokens of a lane, and a token count below one strip of 64 in the last tile."""
+import pytest
+import torch
+
+from paper_2510_03246_amd import inputs, strp
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("mode", [strp.WANDA, strp.GAIN])
+@pytest.mark.parametrize("d,f,T,k", [(264, 608, 24603, 301), (256, 520, 24577, 257), (520, 768, 17001, 512)])
+def test_update_of_the_kept_rows(d, f, T, k, mode):
+    """One iteration, then the rows it kept against the formulas in fp64 from the weights it left: A_S = relu(Z_S) + W^T M^-1 E and the z
+    rule on W1 X, to a quarter of the 2e-3 that the module is held to; columns past T stay as they were.  The next iteration's
+    scores come out of the sums these epilogues leave: fp32 sums over 64 tokens, added in fp64, of 24-bit values: 1e-5."""
+    ctx = strp.Context(0)
+    ld = (T + 7) // 8 * 8
+    cfg = inputs.WorkloadConfig("case", 1, d, f, 0, T, "bf16", "t3", 3, 0.5, 1)
+    m = inputs.make_ffn_module(cfg, 0, 5, "cuda", ld=ld)
+    mod = strp.FFNModule(ctx, m["W1hat"], m["W2hat"], m["X"], T, k_max=k)
+    p = strp.Params(1.0, 0.7, 0.01, mode, 1, k, 0)
+    mod.init(p)
+    mod.Z += 0.25 * torch.randn(mod.Z.shape, generator=torch.Generator(device="cuda").manual_seed(k), device="cuda")
+    mod.A.copy_(torch.relu(mod.Z))
+    for t in (mod.Z, mod.A):
+        t[:, T:] = 7.0
+    z_old = mod.Z.clone()
+    assert mod.step(p).status == strp.OK
+    S = mod.idx[:k].long()
+    W, W1 = mod.W2[:, S].double(), mod.W1[S].double()
+    zs = z_old[S, :T].double()
+    M = 0.7 * torch.eye(d, dtype=torch.float64, device="cuda") + W @ W.T
+    E = mod.Y[:, :T].double() - W @ torch.relu(zs)
+    a = torch.relu(zs) + W.T @ torch.linalg.solve(M, E)
+    z1 = W1 @ m["X"][:, :T].double()
+    cm, cp = z1.clamp(max=0.0), ((0.7 * a + z1) / 1.7).clamp(min=0.0)
+    z = torch.where(0.7 * a ** 2 + (cm - z1) ** 2 < 0.7 * (a - cp) ** 2 + (cp - z1) ** 2, cm, cp)
+    rel = lambda x, y: float((x.double() - y).norm() / y.norm())
+    assert rel(mod.A[S, :T], a) <= 5e-4 and rel(mod.Z[S, :T], z) <= 5e-4
+    if ld > T:
+        assert bool((mod.Z[:, T:] == 7.0).all()) and bool((mod.A[:, T:] == 7.0).all())
+    A, Z, Z0 = (t[:, :T].double() for t in (mod.A, mod.Z, mod.Z0))
+    n2 = mod.n2
+    if mode == strp.WANDA:
+        want = n2 * (A ** 2).sum(1)
+    else:
+        # eq. (78) with b = Z, u = Z0, D = What2 A, Y = What2 relu(Z0): 2 P - Q
+        want = 2.0 * ((Z0 * Z).sum(1) + n2 * (A * torch.relu(Z0)).sum(1)) - ((Z0 ** 2).sum(1) + n2 * (A ** 2).sum(1))
+    p2 = strp.Params(1.0, 0.7, 0.01, mode, 1, k, 1)      # the selection alone
+    mod.step(p2)
+    assert rel(mod.score, want) <= 1e-5
+    ctx.close()
