@@ -218,10 +218,123 @@ __global__ __launch_bounds__(256, WT == 4 ? 1 : 2) void gemm_kernel(const GemmP 
   }
 }
 
+// The same products where 128x128 tiles leave the chip idle and a launch is the time of one workgroup: each tile is cut into
+// 64x64 blocks (subM x subN of them), one 32x64 tile per wavefront.  The fragments come straight from memory -- the operand
+// layout is that of the fragments, 32 consecutive rows are 512 contiguous bytes -- with four contraction steps in flight, no LDS
+// image and no barrier; every element is summed in the order of the kernel above.
+template <int NPP, int NPQ>
+__global__ __launch_bounds__(128) void gemm_kernel(const GemmP p) {
+  constexpr int AHEAD = 4;
+  __shared__ double sred[2][2];
+  __shared__ int srow[64];
+  int tm, tn, split;
+  const int sub = p.subM * p.subN, b = (int)blockIdx.x / sub, within = (int)blockIdx.x - b * sub;
+  decode_tile(p, b, (int)gridDim.x / sub, tm, tn, split);
+  const int m0 = tm * 128 + within / p.subN * 64, n0 = tn * 128 + within % p.subN * 64;
+  if (m0 >= p.M || n0 >= p.N || (p.triangle && n0 > m0)) {      // nothing to compute
+    if (p.red && !p.maxbits && threadIdx.x < 2) p.red[2 * (long long)blockIdx.x + threadIdx.x] = 0.0;
+    return;
+  }
+  const long long k0 = (long long)split * p.kchunk;
+  const long long k1 = (k0 + p.kchunk < p.K) ? (k0 + p.kchunk) : p.K;
+  const int steps = (int)((k1 - k0 + 15) >> 4);        // k-groups past k1 inside the last step are zero padding
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  if (tid < 64) srow[tid] = (p.oidx && m0 + tid < p.M) ? p.oidx[m0 + tid] : 0;
+
+  // rows past M and columns past N lie in the operands' padding to whole panels
+  const long long g = (k0 >> 3) + (lane >> 5);
+  const int mr = m0 + 32 * wave + (lane & 31), nr = n0 + (lane & 31);
+  const long long offp = (((long long)(mr >> 7) * p.P.kg + g) * 128 + (mr & 127)) * 8;
+  long long offq[2];
+#pragma unroll
+  for (int j = 0; j < 2; ++j) offq[j] = (((long long)((nr + 32 * j) >> 7) * p.Q.kg + g) * 128 + ((nr + 32 * j) & 127)) * 8;
+  struct Frags { uint4 ph, pl, qh[2], ql[2]; } f[AHEAD];
+  auto load = [&](Frags& x, int s) {
+    const long long o = (long long)(s < steps ? s : steps - 1) * 2048;
+    x.ph = *(const uint4*)(p.P.hi + offp + o);
+    if (NPP == 2) x.pl = *(const uint4*)(p.P.lo + offp + o);
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+      x.qh[j] = *(const uint4*)(p.Q.hi + offq[j] + o);
+      if (NPQ == 2) x.ql[j] = *(const uint4*)(p.Q.lo + offq[j] + o);
+    }
+  };
+  floatx16 acc[1][2];
+#pragma unroll
+  for (int j = 0; j < 2; ++j)
+#pragma unroll
+    for (int e = 0; e < 16; ++e) acc[0][j][e] = 0.0f;
+  auto multiply = [&](const Frags& x) {
+#pragma unroll
+    for (int j = 0; j < 2; ++j)
+      if (NPQ == 2) acc[0][j] = mma(x.ph, x.ql[j], acc[0][j]);
+#pragma unroll
+    for (int j = 0; j < 2; ++j)
+      if (NPP == 2) acc[0][j] = mma(x.pl, x.qh[j], acc[0][j]);
+#pragma unroll
+    for (int j = 0; j < 2; ++j) acc[0][j] = mma(x.ph, x.qh[j], acc[0][j]);
+  };
+#pragma unroll
+  for (int u = 0; u < AHEAD; ++u) load(f[u], u);
+  int s = 0;
+  for (; s + AHEAD <= steps; s += AHEAD)
+#pragma unroll
+    for (int u = 0; u < AHEAD; ++u) {
+      multiply(f[u]);
+      load(f[u], s + AHEAD + u);
+    }
+#pragma unroll
+  for (int u = 0; u < AHEAD - 1; ++u)
+    if (s + u < steps) multiply(f[u]);
+  __syncthreads();
+
+  float unscale = 1.0f;
+  if (p.P.maxbits) unscale /= scale_of_max(*p.P.maxbits);
+  if (p.Q.maxbits) unscale /= scale_of_max(*p.Q.maxbits);
+  double red0 = 0.0, red1 = 0.0;
+  const int mbase = m0 + 32 * wave + 4 * (lane >> 5), nbase = n0 + (lane & 31);
+  switch (p.epi) {
+    case EPI_PARTIAL: epilogue<EPI_PARTIAL, 1, 2>(p, acc, unscale, mbase, nbase, split, srow, m0, red0, red1); break;
+    case EPI_STORE: epilogue<EPI_STORE, 1, 2>(p, acc, unscale, mbase, nbase, split, srow, m0, red0, red1); break;
+    case EPI_INITZ: epilogue<EPI_INITZ, 1, 2>(p, acc, unscale, mbase, nbase, split, srow, m0, red0, red1); break;
+    case EPI_RESID: epilogue<EPI_RESID, 1, 2>(p, acc, unscale, mbase, nbase, split, srow, m0, red0, red1); break;
+    case EPI_AUPD: epilogue<EPI_AUPD, 1, 2>(p, acc, unscale, mbase, nbase, split, srow, m0, red0, red1); break;
+    default: epilogue<EPI_ZUPD, 1, 2>(p, acc, unscale, mbase, nbase, split, srow, m0, red0, red1); break;
+  }
+  if (p.maxbits) {
+    store_maxbits<2>(p, red0, sred);
+  } else if (p.red) {
+    red0 = wave_sum(red0);
+    red1 = wave_sum(red1);
+    if (lane == 0) {
+      sred[wave][0] = red0;
+      sred[wave][1] = red1;
+    }
+    __syncthreads();
+    if (tid == 0) {
+      p.red[2 * (long long)blockIdx.x + 0] = sred[0][0] + sred[1][0];
+      p.red[2 * (long long)blockIdx.x + 1] = sred[0][1] + sred[1][1];
+    }
+  }
+}
+
 // ---------------------------------------------------------------------------------------------
 // host side
 // ---------------------------------------------------------------------------------------------
+// Fewer 128x128 workgroups than the chip runs at a time (512) are cut into 64x64 ones, up to half of that.  us of the product
+// alone, 128x128 / 64x64 (4 us of either are the timing): Gram matrices 128 x 512 12.4 / 7.9, 256 x 4000 13.2 / 8.7, 400 x 4000
+// (150 workgroups) 15.8 / 11.8; 1536 x 768 over 768 (72) 31 / 21.6, 768 x 768 (36) 27.6 / 14.6, 2048 x 2048 over 2048 (256)
+// 67 / 67.
+constexpr int SMALL_BLOCKS = 256;
+void gemm_small_tiles(GemmP& p) {
+  if (p.wt != 2 || p.ntiles * p.splits > SMALL_BLOCKS) return;
+  p.wt = 1;
+  p.subM = p.M > 64 ? 2 : 1;
+  p.subN = p.N > 64 ? 2 : 1;
+}
+
 void gemm_plan_tiles(GemmP& p, int want_splits, int wt) {
+  p.subM = p.subN = 1;
   if (wt) {
     p.wt = wt;
   } else {
@@ -258,9 +371,10 @@ void gemm_plan_tiles(GemmP& p, int want_splits, int wt) {
     p.kchunk = chunk;
     p.splits = (int)((p.K + chunk - 1) / chunk);
   }
+  if (!wt) gemm_small_tiles(p);
 }
 
-int gemm_grid_blocks(const GemmP& p) { return p.gridM * p.gridN * p.splits; }
+int gemm_grid_blocks(const GemmP& p) { return p.gridM * p.gridN * p.splits * (p.wt == 1 ? p.subM * p.subN : 1); }
 
 // zero the pad k-groups [g_first, kg) of a plane written by an epilogue (whose rows fill the groups below g_first)
 __global__ __launch_bounds__(256) void zero_pad_group_kernel(unsigned short* hi, unsigned short* lo, long long kg, int g_first, int npan) {
@@ -279,13 +393,15 @@ template <int NPP, int NPQ>
 static void launch_one(strp_ctx* ctx, const GemmP& p) {
   if (p.wt == 4)
     launch_gemm_dma(ctx, p, NPP, NPQ);
+  else if (p.wt == 1)
+    hipLaunchKernelGGL((gemm_kernel<NPP, NPQ>), dim3(gemm_grid_blocks(p)), dim3(128), 0, ctx->stream, p);
   else
     hipLaunchKernelGGL((gemm_kernel<NPP, NPQ, 2>), dim3(gemm_grid_blocks(p)), dim3(256), 0, ctx->stream, p);
 }
 
 strp_status launch_gemm(strp_ctx* ctx, GemmP& p) {
   if (p.M <= 0 || p.N <= 0 || p.K <= 0) return fail(ctx, STRP_EINVAL, "gemm: empty shape");
-  if (p.ntiles <= 0 || p.splits <= 0 || (p.wt != 2 && p.wt != 4)) return fail(ctx, STRP_EINVAL, "gemm: tiles not planned");
+  if (p.ntiles <= 0 || p.splits <= 0 || (p.wt != 1 && p.wt != 2 && p.wt != 4)) return fail(ctx, STRP_EINVAL, "gemm: tiles not planned");
   if (!p.P.hi || !p.Q.hi) return fail(ctx, STRP_EINVAL, "gemm: null operand plane");
   if (p.P.kg * 8 < p.K || p.Q.kg * 8 < p.K || (p.P.kg & 3) || (p.Q.kg & 3))
     return fail(ctx, STRP_EINVAL, "gemm: operand planes shorter than K or a group count that is not a multiple of four");

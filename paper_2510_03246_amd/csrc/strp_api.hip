@@ -724,6 +724,7 @@ static strp_status nt_product(strp_ctx* ctx, Arena arena, const PlaneOp& P, cons
   // 8192 tokens
   const long long chain = (K + 8191) / 8192, fit = (long long)(arena.room() / sizeof(float)) / ((long long)M * N);
   if (fit < p.splits && p.splits > chain) gemm_plan_tiles(p, (int)(fit > chain ? fit : chain), p.wt);
+  gemm_small_tiles(p);
   STRP_TAKE(ctx, arena, part, float, (size_t)p.splits * M * N);
   p.out = part;
   STRP_TRY(launch_gemm(ctx, p));

@@ -113,7 +113,9 @@ struct GemmP {
   PlaneOp P, Q;        // C[m, n] = sum_k P(k, m) Q(k, n)
   int M, N;
   long long K;
-  int wt;              // 32x32 MFMA tiles per wavefront per dimension: 2 (128x128 blocks) or 4 (256x256), set by gemm_plan_tiles
+  int wt;              // 32x32 MFMA tiles per wavefront per dimension: 2 (128x128 blocks) or 4 (256x256), set by gemm_plan_tiles; 1: the
+                       // plan of 2 with each tile cut into subM x subN blocks of 64x64 (gemm_small_tiles)
+  int subM, subN;
   int tilesM, tilesN, ntiles;
   int gridM, gridN;    // tile grid the blocks are laid over: tilesM x tilesN, or the folded triangle (see decode_tile)
   int gm, gn;          // tile group (gm x gn = tiles that are resident on one XCD together)
@@ -149,6 +151,8 @@ strp_status launch_gemm(strp_ctx* ctx, GemmP& p);
 int gemm_grid_blocks(const GemmP& p);
 // tile shape (wt = 0: by the number of tiles), tile grid and K splits of a product
 void gemm_plan_tiles(GemmP& p, int want_splits, int wt = 0);
+// smaller blocks for a plan that leaves the chip idle (part of gemm_plan_tiles with wt = 0)
+void gemm_small_tiles(GemmP& p);
 static inline bool gemm_tile256_ok(const GemmP& p) { return p.M >= 256 && p.N >= 256 && p.K >= 256; }
 
 // Sum split-K partials in fp64; optional symmetric completion from the computed lower half.
