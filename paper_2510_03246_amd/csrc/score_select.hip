@@ -316,9 +316,8 @@ strp_status launch_unit_scores(strp_ctx* ctx, const double* sums, const double* 
 // weight statistics of a parameter group (Alg. 2 step 1): sum |w|, sum w, sum w^2 over every entry of a list of
 // matrices, folded into  energy += scale (|W|_1 + cv Var(W) + c2 |W|_2).
 // A model has a few hundred small groups (a head's four slices are 0.4 MB), so a call costs its launches: one for up to eight
-// matrices, and one that adds the workgroups' partial sums in order.  (The last workgroup of the first could add them
-// instead, told by a counter; the counter would have to survive in the caller's scratch between calls.)
-// 12 layers of d = 768, 168 calls: 3.5 -> 1.4 .. 1.7 ms by host; the two kernels take 5 and 2 us a call.
+// matrices, whose last workgroup adds the partial sums in order.  The counter that tells it is the context's own (strp_ctx::ticket),
+// zero between calls; a context without one takes a second launch instead.
 // ---------------------------------------------------------------------------------------------
 constexpr int WSTAT_BLOCKS = 256, WSTAT_MATS = 8;
 
@@ -368,8 +367,31 @@ __device__ __forceinline__ void weight_sums(const WeightList& l, int m, unsigned
   }
 }
 
+// what becomes of the sums
+struct WeightEnd {
+  double count, var_coef, l2_coef, scale;
+  double* energy;
+  unsigned int* ticket;                  // null: another launch follows
+  int filled;                            // entries of partial once this launch is done
+};
+// by the first wavefront of a workgroup
+__device__ __forceinline__ void weight_energy(const double* partial, const WeightEnd& e) {
+  double a[3] = {0.0, 0.0, 0.0};
+#pragma unroll 4
+  for (int b = threadIdx.x; b < e.filled; b += 64)
+#pragma unroll
+    for (int q = 0; q < 3; ++q) a[q] += agent_get(&partial[3 * b + q]);
+#pragma unroll
+  for (int q = 0; q < 3; ++q) a[q] = wave_allsum_d(a[q]);
+  if (threadIdx.x != 0) return;
+  const double mean = a[1] / e.count;
+  const double var = a[2] / e.count - mean * mean;
+  *e.energy += e.scale * (a[0] + e.var_coef * var + e.l2_coef * sqrt(a[2]));
+}
+
 // partial: [WSTAT_BLOCKS][3]; the first `filled` entries hold the sums of earlier launches of the same call
-__global__ __launch_bounds__(256) void weight_sums_kernel(const WeightList l, int filled, double* partial) {
+__global__ __launch_bounds__(256) void weight_sums_kernel(const WeightList l, int filled, double* partial, const WeightEnd end) {
+  __shared__ unsigned int flag;
   double s1 = 0.0, s = 0.0, s2 = 0.0;
   int m = 0;
   while (m + 1 < l.n && (int)blockIdx.x >= l.block0[m + 1]) ++m;
@@ -390,31 +412,21 @@ __global__ __launch_bounds__(256) void weight_sums_kernel(const WeightList l, in
   if (tid < 3) {
     double* p = &partial[3 * blockIdx.x + tid];
     const double before = (int)blockIdx.x < filled ? *p : 0.0;
-    *p = before + (red[0][tid] + red[1][tid] + red[2][tid] + red[3][tid]);
+    agent_put(p, before + (red[0][tid] + red[1][tid] + red[2][tid] + red[3][tid]));
   }
+  if (!end.ticket || !last_block(end.ticket, &flag)) return;
+  if (tid == 64) *end.ticket = 0u;
+  if (tid < 64) weight_energy(partial, end);
 }
 
-__global__ __launch_bounds__(64) void weight_energy_kernel(const double* partial, int filled, double count, double var_coef, double l2_coef, double scale,
-                                                           double* energy) {
-  double a[3] = {0.0, 0.0, 0.0};
-#pragma unroll 4
-  for (int b = threadIdx.x; b < filled; b += 64)
-#pragma unroll
-    for (int q = 0; q < 3; ++q) a[q] += partial[3 * b + q];
-#pragma unroll
-  for (int q = 0; q < 3; ++q) a[q] = wave_allsum_d(a[q]);
-  if (threadIdx.x != 0) return;
-  const double mean = a[1] / count;
-  const double var = a[2] / count - mean * mean;
-  *energy += scale * (a[0] + var_coef * var + l2_coef * sqrt(a[2]));
-}
+__global__ __launch_bounds__(64) void weight_energy_kernel(const double* partial, const WeightEnd end) { weight_energy(partial, end); }
 
 strp_status launch_weight_energy(strp_ctx* ctx, const strp_weight_ref* mats, int n_mats, double var_coef, double l2_coef, double scale,
                                  double* energy, double* partial) {
   WeightList l;
-  double count = 0.0;
+  WeightEnd end{0.0, var_coef, l2_coef, scale, energy, nullptr, 0};
   int filled = 0;
-  for (int i = 0; i < n_mats; ++i) count += (double)mats[i].rows * (double)mats[i].cols;
+  for (int i = 0; i < n_mats; ++i) end.count += (double)mats[i].rows * (double)mats[i].cols;
   for (int i0 = 0; i0 < n_mats; i0 += WSTAT_MATS) {
     l.n = n_mats - i0 < WSTAT_MATS ? n_mats - i0 : WSTAT_MATS;
     double cost[WSTAT_MATS], total = 0.0;
@@ -434,10 +446,12 @@ strp_status launch_weight_energy(strp_ctx* ctx, const strp_weight_ref* mats, int
     l.block0[0] = 0;
     for (int i = 0; i < l.n; ++i)
       l.block0[i + 1] = l.block0[i] + (total <= WSTAT_BLOCKS ? (int)cost[i] : 1 + (int)((WSTAT_BLOCKS - l.n) * (cost[i] / total)));
-    hipLaunchKernelGGL(weight_sums_kernel, dim3(l.block0[l.n]), dim3(256), 0, ctx->stream, l, filled, partial);
-    filled = l.block0[l.n] > filled ? l.block0[l.n] : filled;
+    end.filled = l.block0[l.n] > filled ? l.block0[l.n] : filled;
+    if (i0 + WSTAT_MATS >= n_mats) end.ticket = ctx->ticket;
+    hipLaunchKernelGGL(weight_sums_kernel, dim3(l.block0[l.n]), dim3(256), 0, ctx->stream, l, filled, partial, end);
+    filled = end.filled;
   }
-  hipLaunchKernelGGL(weight_energy_kernel, dim3(1), dim3(64), 0, ctx->stream, (const double*)partial, filled, count, var_coef, l2_coef, scale, energy);
+  if (!end.ticket) hipLaunchKernelGGL(weight_energy_kernel, dim3(1), dim3(64), 0, ctx->stream, (const double*)partial, end);
   STRP_HIP(ctx, hipGetLastError());
   return STRP_OK;
 }

@@ -1,6 +1,7 @@
 // C ABI of libstrp.so: argument validation, workspace carving and the per-module ADMM drivers.
 #include <stdarg.h>
 
+#include <atomic>
 #include <cmath>
 #include <new>
 #include <string>
@@ -38,6 +39,11 @@ constexpr size_t TOPK_STATIC_BYTES = 1u << 20;
 static __device__ __align__(256) unsigned char topk_static_scratch[TOPK_STATIC_BYTES];
 constexpr int MAX_DEVICES = 64;
 static void* g_topk_scratch[MAX_DEVICES];
+// The contexts' counters (strp_ctx::ticket): each context takes the next one and keeps it.  None is used again, so work that is
+// still in flight when its context is destroyed meets nobody on it.
+constexpr unsigned int MAX_TICKETS = 16384;
+static __device__ unsigned int context_tickets[MAX_TICKETS];
+static std::atomic<unsigned int> g_tickets_taken{0};
 
 namespace strp {
 
@@ -328,6 +334,12 @@ strp_status strp_create(strp_ctx** out, int device, void* hip_stream) {
     }
     g_topk_scratch[device] = ptr;
   }
+  const unsigned int slot = g_tickets_taken.load() < MAX_TICKETS ? g_tickets_taken.fetch_add(1) : MAX_TICKETS;
+  void* tickets = nullptr;
+  if (slot < MAX_TICKETS && hipGetSymbolAddress(&tickets, HIP_SYMBOL(context_tickets)) == hipSuccess && tickets)
+    c->ticket = (unsigned int*)tickets + slot;
+  else
+    (void)hipGetLastError();
   *out = c;
   return STRP_OK;
 }

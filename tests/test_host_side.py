@@ -249,7 +249,24 @@ def check_what_the_large_systems_cover():
     assert each == {1, 2, 3} and long, each
 
 
-CHECKS = [check_what_the_gram_matrices_cover, check_what_the_large_systems_cover, check_selection_of_a_very_wide_module, check_weight_statistics_arguments, check_weight_statistics_workgroups, check_chains, check_workspace_of_a_module, check_cached_factor_needs_no_alignment]
+def check_weight_statistics_without_a_counter():
+    """A call is one launch for up to eight matrices; a context that found no counter left takes one more."""
+    lib = Library()
+    strp = lib.strp
+    refs = (strp.WeightRef * 9)(*[strp.WeightRef(1 << 50, strp.F32, 40, 64, 64) for _ in range(9)])
+    call = lambda h, n: lib.launches(lambda: lib.lib.strp_weight_energy(h, refs, n, 0.1, 0.1, 1.0, 1 << 51))
+    assert [len(call(lib.h, n)[1]) for n in (1, 8, 9)] == [1, 1, 2]
+    h = C.c_void_p()
+    for _ in range(16384):
+        assert lib.lib.strp_create(C.byref(h), 0, None) == strp.OK
+        last = C.c_void_p(h.value)
+        if _ < 16383:
+            lib.lib.strp_destroy(h)
+    assert lib.lib.strp_set_workspace(last, 1 << 40, 1 << 30) == strp.OK
+    assert [len(call(last, n)[1]) for n in (1, 8, 9)] == [2, 2, 3]
+
+
+CHECKS = [check_weight_statistics_without_a_counter, check_what_the_gram_matrices_cover, check_what_the_large_systems_cover, check_selection_of_a_very_wide_module, check_weight_statistics_arguments, check_weight_statistics_workgroups, check_chains, check_workspace_of_a_module, check_cached_factor_needs_no_alignment]
 
 
 @pytest.fixture(scope="session")
