@@ -11,6 +11,7 @@ namespace strp {
 
 typedef double doublex4 __attribute__((ext_vector_type(4)));
 typedef double doublex2 __attribute__((ext_vector_type(2)));
+typedef double doublex2u __attribute__((ext_vector_type(2), aligned(8)));      // two doubles anywhere: a caller's matrix may have odd rows
 
 // MFMA lane layout: A operand lane l = A[i = l % 16][k = l / 16], B operand lane l = B[k = l / 16][j = l % 16],
 // result register r of lane l = D[i = 4 r + l / 16][j = l % 16].
@@ -49,7 +50,6 @@ struct DgemmP {
   const double* B; long long ldb;
   double* C; long long ldc;
   int lower, tri;
-  int vec;                  // 16-byte loads: leading dimensions even and bases aligned
   unsigned int* maxbits;    // optional: atomic maximum of the bits of |C|
   WeightsOut w;             // w.W: the result as refitted weights instead of C (one fp64 matrix less to write and read)
 };
@@ -58,8 +58,29 @@ template <int R, int DK, bool KC>
 struct F64Loader {
   static constexpr int NCH = R * DK / 512;   // 16-byte pieces per thread and stage
   doublex2 r[NCH];
+  // A whole stage with 16-byte loads: the same instructions for every tile and stage, so that the wait for one stage leaves the
+  // next one's loads in flight (behind a branch the compiler has to wait for all of them).  Rows past the edge repeat the
+  // last one: what comes of them is not stored.
+  static __device__ __forceinline__ void offsets(unsigned int (&off)[NCH], long long ld, int rv) {
+#pragma unroll
+    for (int q = 0; q < NCH; ++q) {
+      const int e = (int)threadIdx.x + 256 * q;
+      if (KC) {
+        const int row = e / (DK / 2);
+        off[q] = ((unsigned int)(row < rv ? row : rv - 1) * (unsigned int)ld + 2u * (e % (DK / 2))) * 8u;
+      } else {
+        const int row = 2 * (e % (R / 2)), last = (rv - 1) & ~1;        // a row pair, which ends inside an even leading dimension
+        off[q] = ((unsigned int)(e / (R / 2)) * (unsigned int)ld + (unsigned int)(row < rv ? row : last)) * 8u;
+      }
+    }
+  }
+  // src: row 0 at the stage's first k
+  __device__ __forceinline__ void load_whole(const double* src, const unsigned int (&off)[NCH]) {
+#pragma unroll
+    for (int q = 0; q < NCH; ++q) r[q] = *(const doublex2u*)((const char*)src + off[q]);
+  }
   // rows [0, rv) and k in [k0, kend) are valid; src points at row 0
-  __device__ __forceinline__ void load(const double* src, long long ld, int rv, int k0, int kend, bool full) {
+  __device__ __forceinline__ void load(const double* src, long long ld, int rv, int k0, int kend) {
 #pragma unroll
     for (int q = 0; q < NCH; ++q) {
       const int e = (int)threadIdx.x + 256 * q;
@@ -67,14 +88,12 @@ struct F64Loader {
         const int ch = e % (DK / 2), row = e / (DK / 2);
         const int k = k0 + 2 * ch;
         const double* p = src + (long long)row * ld + k;
-        if (full) r[q] = *(const doublex2*)p;
-        else r[q] = doublex2{(row < rv && k < kend) ? p[0] : 0.0, (row < rv && k + 1 < kend) ? p[1] : 0.0};
+        r[q] = doublex2{(row < rv && k < kend) ? p[0] : 0.0, (row < rv && k + 1 < kend) ? p[1] : 0.0};
       } else {
         const int pr = e % (R / 2), kk = k0 + e / (R / 2);
         const int row = 2 * pr;
         const double* p = src + (long long)kk * ld + row;
-        if (full) r[q] = *(const doublex2*)p;
-        else r[q] = doublex2{(row < rv && kk < kend) ? p[0] : 0.0, (row + 1 < rv && kk < kend) ? p[1] : 0.0};
+        r[q] = doublex2{(row < rv && kk < kend) ? p[0] : 0.0, (row + 1 < rv && kk < kend) ? p[1] : 0.0};
       }
     }
   }
@@ -117,19 +136,9 @@ __global__ __launch_bounds__(256, 2) void dgemm_kernel(const DgemmP p) {
   const double* A = AKC ? p.A + (long long)m0 * p.lda : p.A + m0;
   const double* B = BKC ? p.B + (long long)n0 * p.ldb : p.B + n0;
   const int rvm = p.M - m0, rvn = p.N - n0;
-  const bool fa = p.vec && rvm >= TM, fb = p.vec && rvn >= TN;
-  // two stages in flight in registers besides the one in LDS that is multiplied: with few workgroups per CU a stage is
-  // multiplied in less time than a load takes
   F64Loader<TM, DK, AKC> la[2];
   F64Loader<TN, DK, BKC> lb[2];
-  auto gload = [&](int set, int k0) {
-    if (k0 >= kend) return;
-    const bool fk = k0 + DK <= kend;
-    la[set].load(A, p.lda, rvm, k0, kend, fa && fk);
-    lb[set].load(B, p.ldb, rvn, k0, kend, fb && fk);
-  };
-  auto stage = [&](int buf, int k0) {       // multiply the stage at k0, held in As[buf]; the next one is in set buf ^ 1
-    gload(buf, k0 + 2 * DK);
+  auto multiply = [&](int buf) {
     const double* as = As[buf];
     const double* bs = Bs[buf];
 #pragma unroll
@@ -155,22 +164,48 @@ __global__ __launch_bounds__(256, 2) void dgemm_kernel(const DgemmP p) {
 #pragma unroll
         for (int j = 0; j < WN; ++j) acc[i][j] = mma_f64(af[i].y, bf[j].y, acc[i][j]);
     }
-    if (k0 + DK < kend) {                   // the other buffer: its readers finished before the previous barrier
-      la[buf ^ 1].store(As[buf ^ 1]);
-      lb[buf ^ 1].store(Bs[buf ^ 1]);
-    }
-    lds_barrier();
   };
-  if (kbeg < kend) {
-    gload(0, kbeg);
-    gload(1, kbeg + DK);
+  const bool pairs = (AKC || rvm >= TM || p.lda % 2 == 0) && (BKC || rvn >= TN || p.ldb % 2 == 0);
+  const int whole = pairs && kend > kbeg ? (kend - kbeg) / DK : 0;
+  if (whole) {
+    // two stages in flight in registers besides the one in LDS that is multiplied: with few workgroups per CU a stage is
+    // multiplied in less time than a load takes
+    unsigned int offa[F64Loader<TM, DK, AKC>::NCH], offb[F64Loader<TN, DK, BKC>::NCH];
+    F64Loader<TM, DK, AKC>::offsets(offa, p.lda, rvm);
+    F64Loader<TN, DK, BKC>::offsets(offb, p.ldb, rvn);
+    auto gload = [&](int set, int s) {      // past the end: the last one again, never multiplied
+      const long long k = kbeg + (long long)(s < whole ? s : whole - 1) * DK;
+      la[set].load_whole(AKC ? A + k : A + k * p.lda, offa);
+      lb[set].load_whole(BKC ? B + k : B + k * p.ldb, offb);
+    };
+    auto stage = [&](int buf, int s) {      // multiply stage s, held in As[buf]; the next one is in set buf ^ 1
+      gload(buf, s + 2);
+      multiply(buf);
+      la[buf ^ 1].store(As[buf ^ 1]);       // its readers finished before the previous barrier
+      lb[buf ^ 1].store(Bs[buf ^ 1]);
+      lds_barrier();
+    };
+    gload(0, 0);
+    gload(1, 1);
     la[0].store(As[0]);
     lb[0].store(Bs[0]);
+    lds_barrier();
+    int s = 0;
+    for (; s + 2 <= whole; s += 2) {
+      stage(0, s);
+      stage(1, s + 1);
+    }
+    if (s < whole) stage(0, s);
   }
-  lds_barrier();
-  for (int k0 = kbeg; k0 < kend; k0 += 2 * DK) {
-    stage(0, k0);
-    if (k0 + DK < kend) stage(1, k0 + DK);
+  // what is left of K, and row pairs that would end past an odd matrix
+  for (int k0 = kbeg + whole * DK; k0 < kend; k0 += DK) {
+    la[0].load(A, p.lda, rvm, k0, kend);
+    lb[0].load(B, p.ldb, rvn, k0, kend);
+    la[0].store(As[0]);
+    lb[0].store(Bs[0]);
+    lds_barrier();
+    multiply(0);
+    lds_barrier();
   }
   double big = 0.0, sq = 0.0;
   if (p.w.W) {
@@ -231,9 +266,11 @@ __global__ __launch_bounds__(256, 2) void dgemm_kernel(const DgemmP p) {
 
 // Tile of a product by its grid: 128 x 128 tiles read the fewest operand bytes per flop but need enough of them to fill
 // the chip; below that the longest tile (whole K) sets the run time and a smaller one ends sooner.  Solves X (L L^T)^-1 of
-// m x n (two products), us with 64 x 32 / 64 x 64 / 128 x 128 tiles:  768 x 1536 127 / 161 / 452;  2048 x 3277 (1664 tiles of
-// 64, 416 of 128) 824 / 846 / 1245;  3000 x 3000 (2209, 576) 1070 / 1033 / 1290;  3500 x 4000 (3465, 896) 2143 / 2105 / 2038;
-// 4096 x 4096 (4096, 1024) 2557 / 2550 / 2282;  4096 x 4915 (4928, 1248) 3743 / 3684 / 3489, 57 TFLOP/s.
+// m x n (two products), us with 64 x 32 / 64 x 64 / 128 x 128 tiles:  768 x 1536 104 / 139 / 505;  2048 x 3277 (1664 tiles of
+// 64, 416 of 128) 722 / 708 / 1226;  3000 x 3000 (2209, 576) 1051 / 883 / 1222;  4096 x 4096 (4096, 1024) 2143 / 2090 / 2191;
+// 4096 x 4915 (4928, 1248) 3097 / 3025 / 3205, 62 TFLOP/s;  6000 x 6000 (8836, 2209) 7722 / 6669 / 6523;  8602 x 7168 (15232,
+// 3808) 16440 / 14544 / 13178.  64 and 128 are within 7 % of each other from 1000 tiles of 128 to 2000.
+// Before whole stages were loaded without a branch the tiles chosen took 127, 824, 1033, 2282 and 3489 us (first five).
 constexpr int DGEMM_T128 = 1000, DGEMM_T64 = 2000;
 
 static inline bool aligned_vec(const void* p, long long ld) { return ((uintptr_t)p & 15u) == 0 && (ld & 1) == 0; }
@@ -248,10 +285,8 @@ static int dgemm_blocks(int M, int N, DgemmTile t) { return ((M + t.tm - 1) / t.
 int weights_out_blocks(int m, int n) { return dgemm_blocks(m, n, dgemm_tile(m, n, 0)); }
 
 template <bool AKC, bool BKC>
-static strp_status dgemm_launch(strp_ctx* ctx, const DgemmP& pin) {
-  DgemmP p = pin;
+static strp_status dgemm_launch(strp_ctx* ctx, const DgemmP& p) {
   if (p.M <= 0 || p.N <= 0) return STRP_OK;
-  p.vec = aligned_vec(p.A, p.lda) && aligned_vec(p.B, p.ldb);
   const DgemmTile t = dgemm_tile(p.M, p.N, p.lower);
   const dim3 grid(dgemm_blocks(p.M, p.N, t));
   if (t.tm == 128) hipLaunchKernelGGL((dgemm_kernel<128, 128, 16, AKC, BKC>), grid, dim3(256), 0, ctx->stream, p);
