@@ -223,16 +223,16 @@ __global__ __launch_bounds__(256, WT == 4 ? 1 : 2) void gemm_kernel(const GemmP 
 // layout is that of the fragments, 32 consecutive rows are 512 contiguous bytes -- with four contraction steps in flight, no LDS
 // image and no barrier; every element is summed in the order of the kernel above.
 template <int NPP, int NPQ>
-__global__ __launch_bounds__(128) void gemm_kernel(const GemmP p) {
+__device__ __forceinline__ void gemm_small_block(const GemmP& p, int block, int blocks) {
   constexpr int AHEAD = 4;
   __shared__ double sred[2][2];
   __shared__ int srow[64];
   int tm, tn, split;
-  const int sub = p.subM * p.subN, b = (int)blockIdx.x / sub, within = (int)blockIdx.x - b * sub;
-  decode_tile(p, b, (int)gridDim.x / sub, tm, tn, split);
+  const int sub = p.subM * p.subN, b = block / sub, within = block - b * sub;
+  decode_tile(p, b, blocks / sub, tm, tn, split);
   const int m0 = tm * 128 + within / p.subN * 64, n0 = tn * 128 + within % p.subN * 64;
   if (m0 >= p.M || n0 >= p.N || (p.triangle && n0 > m0)) {      // nothing to compute
-    if (p.red && !p.maxbits && threadIdx.x < 2) p.red[2 * (long long)blockIdx.x + threadIdx.x] = 0.0;
+    if (p.red && !p.maxbits && threadIdx.x < 2) p.red[2 * (long long)block + threadIdx.x] = 0.0;
     return;
   }
   const long long k0 = (long long)split * p.kchunk;
@@ -312,10 +312,24 @@ __global__ __launch_bounds__(128) void gemm_kernel(const GemmP p) {
     }
     __syncthreads();
     if (tid == 0) {
-      p.red[2 * (long long)blockIdx.x + 0] = sred[0][0] + sred[1][0];
-      p.red[2 * (long long)blockIdx.x + 1] = sred[0][1] + sred[1][1];
+      p.red[2 * (long long)block + 0] = sred[0][0] + sred[1][0];
+      p.red[2 * (long long)block + 1] = sred[0][1] + sred[1][1];
     }
   }
+}
+
+template <int NPP, int NPQ>
+__global__ __launch_bounds__(128) void gemm_kernel(const GemmP p) { gemm_small_block<NPP, NPQ>(p, blockIdx.x, gridDim.x); }
+
+// two independent products, one behind the other in the grid: `first` workgroups are the first's
+struct GemmPair {
+  GemmP p[2];
+  int first;
+};
+template <int NPP, int NPQ>
+__global__ __launch_bounds__(128) void gemm_pair_kernel(const GemmPair g) {
+  const int second = (int)blockIdx.x >= g.first;
+  gemm_small_block<NPP, NPQ>(g.p[second], (int)blockIdx.x - second * g.first, second ? (int)gridDim.x - g.first : g.first);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -399,7 +413,7 @@ static void launch_one(strp_ctx* ctx, const GemmP& p) {
     hipLaunchKernelGGL((gemm_kernel<NPP, NPQ, 2>), dim3(gemm_grid_blocks(p)), dim3(256), 0, ctx->stream, p);
 }
 
-strp_status launch_gemm(strp_ctx* ctx, GemmP& p) {
+static strp_status check_gemm(strp_ctx* ctx, const GemmP& p) {
   if (p.M <= 0 || p.N <= 0 || p.K <= 0) return fail(ctx, STRP_EINVAL, "gemm: empty shape");
   if (p.ntiles <= 0 || p.splits <= 0 || (p.wt != 1 && p.wt != 2 && p.wt != 4)) return fail(ctx, STRP_EINVAL, "gemm: tiles not planned");
   if (!p.P.hi || !p.Q.hi) return fail(ctx, STRP_EINVAL, "gemm: null operand plane");
@@ -407,6 +421,11 @@ strp_status launch_gemm(strp_ctx* ctx, GemmP& p) {
     return fail(ctx, STRP_EINVAL, "gemm: operand planes shorter than K or a group count that is not a multiple of four");
   if ((long long)p.P.npan * 128 < p.M || (long long)p.Q.npan * 128 < p.N) return fail(ctx, STRP_EINVAL, "gemm: operand planes narrower than the output");
   if (p.epi != EPI_PARTIAL && p.splits != 1) return fail(ctx, STRP_EINVAL, "gemm: fused epilogues do not split K");
+  return STRP_OK;
+}
+
+strp_status launch_gemm(strp_ctx* ctx, GemmP& p) {
+  STRP_TRY(check_gemm(ctx, p));
   const int npp = p.P.lo ? 2 : 1, npq = p.Q.lo ? 2 : 1;
   static const char* const epi_names[] = {"partial", "store", "initz", "resid", "aupd", "zupd"};
   static char names[3][3][6][40];
@@ -435,20 +454,37 @@ strp_status launch_gemm(strp_ctx* ctx, GemmP& p) {
   return STRP_OK;
 }
 
+// Two products of which neither reads what the other writes: in one launch where both are small ones of two planes each, which
+// saves a launch (4 us) and fills the chip better; otherwise one after the other.
+strp_status launch_gemm_pair(strp_ctx* ctx, GemmP& p, GemmP& q) {
+  const bool one = p.wt == 1 && q.wt == 1 && p.P.lo && p.Q.lo && q.P.lo && q.Q.lo && !p.k8_hi && !q.k8_hi;
+  if (!one) {
+    STRP_TRY(launch_gemm(ctx, p));
+    return launch_gemm(ctx, q);
+  }
+  STRP_TRY(check_gemm(ctx, p));
+  STRP_TRY(check_gemm(ctx, q));
+  ProfScope ps(ctx, "gemm_h2x2_pair", 2.0 * (double)p.K * p.M * p.N * (p.triangle ? 0.5 : 1.0) + 2.0 * (double)q.K * q.M * q.N * (q.triangle ? 0.5 : 1.0), 0.0);
+  const GemmPair g{{p, q}, gemm_grid_blocks(p)};
+  hipLaunchKernelGGL((gemm_pair_kernel<2, 2>), dim3(g.first + gemm_grid_blocks(q)), dim3(128), 0, ctx->stream, g);
+  STRP_HIP(ctx, hipGetLastError());
+  return STRP_OK;
+}
+
 // ---- split-K reduction -----------------------------------------------------------------------
 // One block reduces a 16 x 64 output tile (thread = column tx, rows ty + 4 i): a wavefront load is 256 contiguous bytes
 // of one row of one partial.  Symmetric products: only tiles that reach the lower half are reduced; the strict lower
 // part is also written transposed through LDS, so the upper half is a bit-exact mirror and the partials are read once,
 // row-contiguously.  Bound by HBM where the output is large (4.7 TB/s); a small output (M = 832: 91 tiles of 64 x 64)
 // leaves few workgroups, each with a serial walk over the splits, so tiles are low and four splits are in flight.
-__global__ __launch_bounds__(256) void splitk_reduce_kernel(const ReduceP r) {
+__device__ __forceinline__ void splitk_reduce_block(const ReduceP& r, int bx, int by, int nx) {
   constexpr int TN = REDUCE_TILE_N, TM = REDUCE_TILE_M, NI = TM / 4, AHEAD = 4;
   __shared__ double tile[TM][TN + 1];
   const int tx = threadIdx.x & 63, ty = threadIdx.x >> 6;
-  const int n0 = blockIdx.x * TN, m0 = blockIdx.y * TM;
+  const int n0 = bx * TN, m0 = by * TM;
   const int M = r.M, N = r.N;
   if (r.triangle && n0 >= m0 + TM) {
-    if (r.dot && threadIdx.x == 0) r.red[blockIdx.y * gridDim.x + blockIdx.x] = 0.0;
+    if (r.dot && threadIdx.x == 0) r.red[by * nx + bx] = 0.0;
     return;
   }
   const long long MN = (long long)M * N;
@@ -500,7 +536,7 @@ __global__ __launch_bounds__(256) void splitk_reduce_kernel(const ReduceP r) {
       for (int o = 32; o > 0; o >>= 1) s += __shfl_down(s, o, 64);
       if (tx == 0) tile[0][ty] = s;
       __syncthreads();
-      if (threadIdx.x == 0) r.red[blockIdx.y * gridDim.x + blockIdx.x] = tile[0][0] + tile[0][1] + tile[0][2] + tile[0][3];
+      if (threadIdx.x == 0) r.red[by * nx + bx] = tile[0][0] + tile[0][1] + tile[0][2] + tile[0][3];
       return;
     }
   }
@@ -519,6 +555,18 @@ __global__ __launch_bounds__(256) void splitk_reduce_kernel(const ReduceP r) {
     if (lo_n < lo_m && lo_m < M && lo_n < N) put(lo_n, lo_m, tile[e & (TM - 1)][e / TM]);
   }
 }
+__global__ __launch_bounds__(256) void splitk_reduce_kernel(const ReduceP r) { splitk_reduce_block(r, blockIdx.x, blockIdx.y, gridDim.x); }
+// two of them, `first` workgroups for the first
+struct ReducePair {
+  ReduceP r[2];
+  int first;
+};
+__global__ __launch_bounds__(256) void splitk_reduce_pair_kernel(const ReducePair g) {
+  const int second = (int)blockIdx.x >= g.first;
+  const int b = (int)blockIdx.x - second * g.first, nx = (g.r[second].N + REDUCE_TILE_N - 1) / REDUCE_TILE_N;
+  const ReduceP r = g.r[second];
+  splitk_reduce_block(r, b % nx, b / nx, nx);
+}
 
 strp_status launch_splitk_reduce(strp_ctx* ctx, const ReduceP& r) {
   const double tot = (double)r.M * r.N;
@@ -526,6 +574,14 @@ strp_status launch_splitk_reduce(strp_ctx* ctx, const ReduceP& r) {
   if (r.dot && !r.triangle) return fail(ctx, STRP_EINVAL, "split-K reduce: the inner product is for symmetric products");
   ProfScope ps(ctx, "splitk_reduce", 0.0, 4.0 * tot * (double)r.splits * (r.triangle ? 0.5 : 1.0) + (r.outf ? 4.0 : 0.0) * tot + (r.outd ? 8.0 : 0.0) * tot);
   hipLaunchKernelGGL(splitk_reduce_kernel, dim3((r.N + REDUCE_TILE_N - 1) / REDUCE_TILE_N, (r.M + REDUCE_TILE_M - 1) / REDUCE_TILE_M), dim3(256), 0, ctx->stream, r);
+  STRP_HIP(ctx, hipGetLastError());
+  return STRP_OK;
+}
+
+strp_status launch_splitk_reduce_pair(strp_ctx* ctx, const ReduceP& r, const ReduceP& q) {
+  const ReducePair g{{r, q}, reduce_blocks(r.M, r.N)};
+  ProfScope ps(ctx, "splitk_reduce", 0.0, 4.0 * ((double)r.M * r.N * (r.splits + 2) + (double)q.M * q.N * (q.splits + 2)));
+  hipLaunchKernelGGL(splitk_reduce_pair_kernel, dim3(g.first + reduce_blocks(q.M, q.N)), dim3(256), 0, ctx->stream, g);
   STRP_HIP(ctx, hipGetLastError());
   return STRP_OK;
 }

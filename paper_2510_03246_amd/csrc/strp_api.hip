@@ -725,8 +725,8 @@ static size_t nt_partial_most_over(int d, long long km) {
   return most;
 }
 
-// C = P Q^T over K (ROW planes); partials in the arena (by value: released on return), fp64 reduction into what r names.
-static strp_status nt_product(strp_ctx* ctx, Arena arena, const PlaneOp& P, const PlaneOp& Q, int M, int N, long long K, int triangle, ReduceP r) {
+// C = P Q^T over K (ROW planes), planned; `room` elements for its partials
+static GemmP nt_plan(const PlaneOp& P, const PlaneOp& Q, int M, int N, long long K, int triangle, size_t room) {
   GemmP p;
   memset(&p, 0, sizeof(p));
   p.P = P; p.Q = Q; p.M = M; p.N = N; p.K = K; p.triangle = triangle;
@@ -734,14 +734,36 @@ static strp_status nt_product(strp_ctx* ctx, Arena arena, const PlaneOp& P, cons
   plan_nt_product(p);
   // a workspace below strp_workspace_bytes may hold fewer partials than the plan's: as many as fit, but no chain longer than
   // 8192 tokens
-  const long long chain = (K + 8191) / 8192, fit = (long long)(arena.room() / sizeof(float)) / ((long long)M * N);
+  const long long chain = (K + 8191) / 8192, fit = (long long)room / ((long long)M * N);
   if (fit < p.splits && p.splits > chain) gemm_plan_tiles(p, (int)(fit > chain ? fit : chain), p.wt);
   gemm_small_tiles(p);
+  return p;
+}
+static void reduce_of(const GemmP& p, ReduceP* r) {
+  r->part = p.out; r->splits = p.splits; r->M = p.M; r->N = p.N; r->triangle = p.triangle;
+}
+// The product's partials in the arena (by value: released on return), fp64 reduction into what r names.
+static strp_status nt_product(strp_ctx* ctx, Arena arena, const PlaneOp& P, const PlaneOp& Q, int M, int N, long long K, int triangle, ReduceP r) {
+  GemmP p = nt_plan(P, Q, M, N, K, triangle, arena.room() / sizeof(float));
   STRP_TAKE(ctx, arena, part, float, (size_t)p.splits * M * N);
   p.out = part;
   STRP_TRY(launch_gemm(ctx, p));
-  r.part = part; r.splits = p.splits; r.M = M; r.N = N; r.triangle = triangle;
+  reduce_of(p, &r);
   return launch_splitk_reduce(ctx, r);
+}
+// Two such products in two launches instead of four, where both are small ones with room for both sets of partials.
+// *done: 0 = nothing was launched.
+static strp_status nt_product_pair(strp_ctx* ctx, Arena arena, GemmP p, ReduceP r, GemmP q, ReduceP s, int* done) {
+  *done = 0;
+  if (p.wt != 1 || q.wt != 1 || !p.P.lo || !p.Q.lo || !q.P.lo || !q.Q.lo) return STRP_OK;
+  p.out = (float*)arena.take(sizeof(float) * (size_t)p.splits * p.M * p.N);
+  q.out = (float*)arena.take(sizeof(float) * (size_t)q.splits * q.M * q.N);
+  if (!p.out || !q.out) return STRP_OK;
+  *done = 1;
+  STRP_TRY(launch_gemm_pair(ctx, p, q));
+  reduce_of(p, &r);
+  reduce_of(q, &s);
+  return launch_splitk_reduce_pair(ctx, r, s);
 }
 static ReduceP reduce_to(double* outd, long long ldod) {
   ReduceP r;
@@ -758,6 +780,7 @@ struct RefitIn {
   double lam; const double* lam_dev;
   PlaneOp Lhs, Rhs;
   int m, n; long long T;
+  double* R; int r_ready;                 // [m x f64_ld(n)] the right-hand side (null: taken from the arena); 1: it has been formed
 };
 
 // Factor the system in `sys` (leading dimension f64_ld(n), holds Gram + lam I) and leave the inverse of its Cholesky factor in Linv.
@@ -778,9 +801,13 @@ static strp_status ridge_solve(strp_ctx* ctx, Arena& arena, const RefitIn& in, c
     STRP_TAKE(ctx, arena, fscratch, char, fbytes);
     STRP_TRY(factor_and_invert(ctx, Arena(fscratch, fbytes), in.sys, n, in.Linv, in.ldl));
   }
-  STRP_TAKE(ctx, arena, R, double, (size_t)m * ld);
+  double* R = in.R;
+  if (!R) {
+    STRP_TAKE(ctx, arena, R_, double, (size_t)m * ld);
+    R = R_;
+  }
   STRP_TAKE(ctx, arena, tmp, double, (size_t)m * ld);
-  STRP_TRY(nt_product(ctx, arena, in.Lhs, in.Rhs, m, n, in.T, 0, reduce_to(R, ld)));
+  if (!in.r_ready) STRP_TRY(nt_product(ctx, arena, in.Lhs, in.Rhs, m, n, in.T, 0, reduce_to(R, ld)));
   if (clear) STRP_TRY(fill_zero(ctx, out.W, clear));
   return apply_inverse_right(ctx, in.Linv, n, in.ldl, R, m, ld, tmp, out);
 }
@@ -851,6 +878,8 @@ size_t strp_workspace_bytes(const strp_module_desc* desc) {
   upd(nt_partial_elems((int)d, (int)d, T, 1));   // H; E E^T of the objective
   const size_t wwt = nt_partial_most_over((int)d, (long long)kp);
   upd(wwt);
+  // a small product's partials beside another's (nt_product_pair): at most 256 tiles of 128 x 128
+  const size_t part_small = part < ((size_t)256 << 14) ? part : (size_t)256 << 14;
   const size_t segs = (size_t)((T + 8191) / 8192), slots = (size_t)((T + 63) / 64);
   const size_t w_blocks = ((d + 63) / 64 + 1) * ((km + 31) / 32 + 1) + ((km + 63) / 64 + 1) * ((d + 31) / 32 + 1) + 2048;
   size_t step = 256 + al(256) + al(4 * f * 8) +
@@ -861,7 +890,7 @@ size_t strp_workspace_bytes(const strp_module_desc* desc) {
                 /* planes of the kept weights (both orders of W2) and of B */
                 2 * al(plane_elems(d, km) * 2) + 3 * 2 * al(plane_elems(km, d) * 2) + al(km * d * 4) +
                 /* fc2 and fc1 refit: system and factor, their rows padded to 8, scratch of the chain, right-hand side and solve */
-                al(part * 4) + 3 * al(nmax * (nmax + 8) * 8) + 2 * al(invd_max) + 4 * al(d * km * 8) + 2 * al((d + km) * 8 * 8) + 2 * al(d * d * 8) +
+                al(part * 4) + al(part_small * 4) + 3 * al(nmax * (nmax + 8) * 8) + 2 * al(invd_max) + 4 * al(d * km * 8) + 2 * al((d + km) * 8 * 8) + 2 * al(d * d * 8) +
                 2 * al(plane_elems(km, T) * 2) /* kept rows, token contraction */ +
                 2 * al(plane_elems(T, km) * 2) /* kept rows, channel contraction */ +
                 2 * al(plane_elems(T, d) * 2) /* E */ + red +
@@ -1170,7 +1199,6 @@ strp_status strp_admm_step(strp_ctx* ctx, const strp_module_desc* desc, strp_mod
     STRP_TRY(make_t_planes(ctx, a2, st->A, STRP_F32, lda, st->idx, s, T, 0, npa, &Arow));
     ReduceP r = reduce_to(Gd, lds);
     r.ridge_dev = sc + SC_LAM2;
-    STRP_TRY(nt_product(ctx, a2, operand_for(ctx, STRP_PROD_GRAM, 0, Arow), operand_for(ctx, STRP_PROD_GRAM, 1, Arow), s, s, T, 1, r));
     RefitIn ri;
     memset(&ri, 0, sizeof(ri));
     STRP_TAKE(ctx, a2, Ginv, double, (size_t)s * lds);
@@ -1178,6 +1206,13 @@ strp_status strp_admm_step(strp_ctx* ctx, const strp_module_desc* desc, strp_mod
     ri.Lhs = operand_for(ctx, STRP_PROD_RHS2, 0, cv.Yt);
     ri.Rhs = operand_for(ctx, STRP_PROD_RHS2, 1, Arow);
     ri.m = d; ri.n = s; ri.T = T;
+    STRP_TAKE(ctx, a2, R2, double, (size_t)d * lds);
+    const PlaneOp Gp = operand_for(ctx, STRP_PROD_GRAM, 0, Arow), Gq = operand_for(ctx, STRP_PROD_GRAM, 1, Arow);
+    const size_t room = a2.room() / sizeof(float);
+    int done = 0;
+    STRP_TRY(nt_product_pair(ctx, a2, nt_plan(Gp, Gq, s, s, T, 1, room), r, nt_plan(ri.Lhs, ri.Rhs, d, s, T, 0, room), reduce_to(R2, lds), &done));
+    ri.R = R2; ri.r_ready = done;
+    if (!done) STRP_TRY(nt_product(ctx, a2, Gp, Gq, s, s, T, 1, r));
     STRP_TRY(ridge_solve(ctx, a2, ri, w2out));
   } else if (W2S) {
     STRP_TRY(gather_weights(ctx, w2out, d, s));
@@ -1239,7 +1274,6 @@ strp_status strp_admm_step(strp_ctx* ctx, const strp_module_desc* desc, strp_mod
     p.M = s; p.N = d; p.K = d;
     p.epi = EPI_STORE; p.out = Bf; p.ldo = d; p.maxbits = wmax + MAX_B;
     gemm_plan_tiles(p, 1);
-    STRP_TRY(launch_gemm(ctx, p));
     if (term1_identity) {   // M^-2 for the first objective term (see the a-update below)
       GemmP q;
       memset(&q, 0, sizeof(q));
@@ -1247,7 +1281,9 @@ strp_status strp_admm_step(strp_ctx* ctx, const strp_module_desc* desc, strp_mod
       q.M = d; q.N = d; q.K = d;
       q.epi = EPI_STORE; q.out = M2f; q.ldo = d;
       gemm_plan_tiles(q, 1);
-      STRP_TRY(launch_gemm(ctx, q));
+      STRP_TRY(launch_gemm_pair(ctx, p, q));
+    } else {
+      STRP_TRY(launch_gemm(ctx, p));
     }
     STRP_TRY(weight_planes(ctx, arena, Bf, SRC_F32, d, s, d, 0, npa, wmax + MAX_B, &Bp, &job));
     STRP_TRY(split_small(ctx, &job, 1));

@@ -151,6 +151,8 @@ struct GemmP {
 };
 
 strp_status launch_gemm(strp_ctx* ctx, GemmP& p);
+// two products, neither of which reads what the other writes; launch_splitk_reduce_pair: two reductions
+strp_status launch_gemm_pair(strp_ctx* ctx, GemmP& p, GemmP& q);
 int gemm_grid_blocks(const GemmP& p);
 // tile shape (wt = 0: by the number of tiles), tile grid and K splits of a product
 void gemm_plan_tiles(GemmP& p, int want_splits, int wt = 0);
@@ -173,6 +175,7 @@ struct ReduceP {
   const float* dot; double* red;
 };
 strp_status launch_splitk_reduce(strp_ctx* ctx, const ReduceP& r);
+strp_status launch_splitk_reduce_pair(strp_ctx* ctx, const ReduceP& r, const ReduceP& q);
 constexpr int REDUCE_TILE_M = 16, REDUCE_TILE_N = 64;      // output tile of one workgroup of the split-K reduction
 static inline int reduce_blocks(int M, int N) { return ((M + REDUCE_TILE_M - 1) / REDUCE_TILE_M) * ((N + REDUCE_TILE_N - 1) / REDUCE_TILE_N); }
 // fp32 / bf16 activation rows (optionally gathered by idx) -> fp16 planes; any output pair may be null.
