@@ -110,13 +110,13 @@ template <int R, int DK, bool KC>
 constexpr int f64_img_elems() { return KC ? DK / 2 * (R + 1) * 2 : DK * (R + 4); }
 
 template <int TM, int TN, int DK, bool AKC, bool BKC>
-__global__ __launch_bounds__(256, 2) void dgemm_kernel(const DgemmP p) {
+__device__ __forceinline__ void dgemm_block(const DgemmP& p, int block) {
   constexpr int WM = TM / 32, WN = TN / 32;     // 16 x 16 tiles per wavefront
   __shared__ __attribute__((aligned(16))) double As[2][f64_img_elems<TM, DK, AKC>()];
   __shared__ __attribute__((aligned(16))) double Bs[2][f64_img_elems<TN, DK, BKC>()];
   const int tilesM = (p.M + TM - 1) / TM, tilesN = (p.N + TN - 1) / TN;
   // the rows of C walk fastest; column tiles go in order of decreasing K range
-  const int tn_ = (int)blockIdx.x / tilesM, tm_ = (int)blockIdx.x - tn_ * tilesM;
+  const int tn_ = block / tilesM, tm_ = block - tn_ * tilesM;
   const int m0 = tm_ * TM, n0 = (p.tri == 1 ? tilesN - 1 - tn_ : tn_) * TN;
   if (p.lower && n0 >= m0 + TM) return;
   int kbeg = 0, kend = p.K;
@@ -259,9 +259,23 @@ __global__ __launch_bounds__(256, 2) void dgemm_kernel(const DgemmP p) {
     lds_barrier();
     if (tid == 0) {
       if (maxbits) atomicMax(maxbits, __builtin_bit_cast(unsigned int, (float)fmax(fmax(red[0], red[2]), fmax(red[4], red[6]))));
-      if (p.w.sumsq) p.w.sumsq[blockIdx.x] = red[1] + red[3] + red[5] + red[7];
+      if (p.w.sumsq) p.w.sumsq[block] = red[1] + red[3] + red[5] + red[7];
     }
   }
+}
+
+template <int TM, int TN, int DK, bool AKC, bool BKC>
+__global__ __launch_bounds__(256, 2) void dgemm_kernel(const DgemmP p) { dgemm_block<TM, TN, DK, AKC, BKC>(p, blockIdx.x); }
+
+// two independent products, one behind the other in the grid: `first` workgroups are the first's
+struct DgemmPair {
+  DgemmP p[2];
+  int first;
+};
+template <int TM, int TN, int DK, bool AKC, bool BKC>
+__global__ __launch_bounds__(256, 2) void dgemm_pair_kernel(const DgemmPair g) {
+  const int second = (int)blockIdx.x >= g.first;
+  dgemm_block<TM, TN, DK, AKC, BKC>(g.p[second], (int)blockIdx.x - second * g.first);
 }
 
 // Tile of a product by its grid: 128 x 128 tiles read the fewest operand bytes per flop but need enough of them to fill
@@ -1176,18 +1190,43 @@ strp_status chol_inverse(strp_ctx* ctx, double* A, int n, long long ld, double* 
   return STRP_OK;
 }
 
+// tmp[m, j] = sum_{k <= j} X[m, k] Linv[j, k], then result[m, j] = sum_{k >= j} tmp[m, k] Linv[k, j]
+static void solve_products(const SolveIn& in, DgemmP (&p)[2]) {
+  memset(p, 0, sizeof(p));
+  for (int i = 0; i < 2; ++i) {
+    p[i].M = in.m; p[i].N = in.n; p[i].K = in.n;
+    p[i].A = i ? in.tmp : in.X; p[i].lda = in.ldx; p[i].B = in.Linv; p[i].ldb = in.ldl; p[i].tri = 1 + i;
+  }
+  p[0].C = in.tmp; p[0].ldc = in.ldx;
+  p[1].w = in.out;
+}
+
 strp_status apply_inverse_right(strp_ctx* ctx, const double* Linv, int n, long long ldl, const double* X, int m, long long ldx, double* tmp,
                                 const WeightsOut& out) {
   ProfScope ps(ctx, "chol_solve_f64", 2.0 * (double)m * n * n, 8.0 * ((double)n * n + 4.0 * (double)m * n));
-  DgemmP p;
-  memset(&p, 0, sizeof(p));
-  p.M = m; p.N = n; p.K = n;
-  // tmp[m, j] = sum_{k <= j} X[m, k] Linv[j, k]
-  p.A = X; p.lda = ldx; p.B = Linv; p.ldb = ldl; p.C = tmp; p.ldc = ldx; p.tri = 1;
-  STRP_TRY((dgemm_launch<true, true>(ctx, p)));
-  // result[m, j] = sum_{k >= j} tmp[m, k] Linv[k, j]
-  p.A = tmp; p.C = nullptr; p.tri = 2; p.w = out;
-  return dgemm_launch<true, false>(ctx, p);
+  DgemmP p[2];
+  solve_products(SolveIn{Linv, n, ldl, X, m, ldx, tmp, out}, p);
+  STRP_TRY((dgemm_launch<true, true>(ctx, p[0])));
+  return dgemm_launch<true, false>(ctx, p[1]);
+}
+
+// Two solves side by side pay where each has less than a workgroup a compute unit: one takes as long as the longest tile then
+// (64 x 128 beside 128 x 64: 15.8 + 13.5 us one after the other, 17.4 together).
+bool solve_is_small(int m, int n) {
+  return dgemm_tile(m, n, 0).tn == 32 && dgemm_blocks(m, n, {64, 32}) <= 256;
+}
+strp_status apply_inverse_right_pair(strp_ctx* ctx, const SolveIn& a, const SolveIn& b) {
+  if (!solve_is_small(a.m, a.n) || !solve_is_small(b.m, b.n)) return fail(ctx, STRP_EINVAL, "two solves in one launch: not small");
+  ProfScope ps(ctx, "chol_solve_f64", 2.0 * ((double)a.m * a.n * a.n + (double)b.m * b.n * b.n), 0.0);
+  DgemmP p[2], q[2];
+  solve_products(a, p);
+  solve_products(b, q);
+  const int first = dgemm_blocks(a.m, a.n, {64, 32}), blocks = first + dgemm_blocks(b.m, b.n, {64, 32});
+  const DgemmPair g0{{p[0], q[0]}, first}, g1{{p[1], q[1]}, first};
+  hipLaunchKernelGGL((dgemm_pair_kernel<64, 32, 32, true, true>), dim3(blocks), dim3(256), 0, ctx->stream, g0);
+  hipLaunchKernelGGL((dgemm_pair_kernel<64, 32, 32, true, false>), dim3(blocks), dim3(256), 0, ctx->stream, g1);
+  STRP_HIP(ctx, hipGetLastError());
+  return STRP_OK;
 }
 
 // ---------------------------------------------------------------------------------------------

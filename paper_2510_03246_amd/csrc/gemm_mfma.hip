@@ -222,7 +222,8 @@ __global__ __launch_bounds__(256, WT == 4 ? 1 : 2) void gemm_kernel(const GemmP 
 // 64x64 blocks (subM x subN of them), one 32x64 tile per wavefront.  The fragments come straight from memory -- the operand
 // layout is that of the fragments, 32 consecutive rows are 512 contiguous bytes -- with four contraction steps in flight, no LDS
 // image and no barrier; every element is summed in the order of the kernel above.
-template <int NPP, int NPQ>
+// ASK: an operand may have one plane only (its lo is then read from hi and not multiplied)
+template <int NPP, int NPQ, bool ASK>
 __device__ __forceinline__ void gemm_small_block(const GemmP& p, int block, int blocks) {
   constexpr int AHEAD = 4;
   __shared__ double sred[2][2];
@@ -249,14 +250,17 @@ __device__ __forceinline__ void gemm_small_block(const GemmP& p, int block, int 
 #pragma unroll
   for (int j = 0; j < 2; ++j) offq[j] = (((long long)((nr + 32 * j) >> 7) * p.Q.kg + g) * 128 + ((nr + 32 * j) & 127)) * 8;
   struct Frags { uint4 ph, pl, qh[2], ql[2]; } f[AHEAD];
+  const bool plo = !ASK || p.P.lo, qlo = !ASK || p.Q.lo;
+  const unsigned short* const p_lo = plo ? p.P.lo : p.P.hi;
+  const unsigned short* const q_lo = qlo ? p.Q.lo : p.Q.hi;
   auto load = [&](Frags& x, int s) {
     const long long o = (long long)(s < steps ? s : steps - 1) * 2048;
     x.ph = *(const uint4*)(p.P.hi + offp + o);
-    if (NPP == 2) x.pl = *(const uint4*)(p.P.lo + offp + o);
+    if (NPP == 2) x.pl = *(const uint4*)(p_lo + offp + o);
 #pragma unroll
     for (int j = 0; j < 2; ++j) {
       x.qh[j] = *(const uint4*)(p.Q.hi + offq[j] + o);
-      if (NPQ == 2) x.ql[j] = *(const uint4*)(p.Q.lo + offq[j] + o);
+      if (NPQ == 2) x.ql[j] = *(const uint4*)(q_lo + offq[j] + o);
     }
   };
   floatx16 acc[1][2];
@@ -265,12 +269,14 @@ __device__ __forceinline__ void gemm_small_block(const GemmP& p, int block, int 
 #pragma unroll
     for (int e = 0; e < 16; ++e) acc[0][j][e] = 0.0f;
   auto multiply = [&](const Frags& x) {
+    if (NPQ == 2 && qlo) {
 #pragma unroll
-    for (int j = 0; j < 2; ++j)
-      if (NPQ == 2) acc[0][j] = mma(x.ph, x.ql[j], acc[0][j]);
+      for (int j = 0; j < 2; ++j) acc[0][j] = mma(x.ph, x.ql[j], acc[0][j]);
+    }
+    if (NPP == 2 && plo) {
 #pragma unroll
-    for (int j = 0; j < 2; ++j)
-      if (NPP == 2) acc[0][j] = mma(x.pl, x.qh[j], acc[0][j]);
+      for (int j = 0; j < 2; ++j) acc[0][j] = mma(x.pl, x.qh[j], acc[0][j]);
+    }
 #pragma unroll
     for (int j = 0; j < 2; ++j) acc[0][j] = mma(x.ph, x.qh[j], acc[0][j]);
   };
@@ -319,17 +325,16 @@ __device__ __forceinline__ void gemm_small_block(const GemmP& p, int block, int 
 }
 
 template <int NPP, int NPQ>
-__global__ __launch_bounds__(128) void gemm_kernel(const GemmP p) { gemm_small_block<NPP, NPQ>(p, blockIdx.x, gridDim.x); }
+__global__ __launch_bounds__(128) void gemm_kernel(const GemmP p) { gemm_small_block<NPP, NPQ, false>(p, blockIdx.x, gridDim.x); }
 
-// two independent products, one behind the other in the grid: `first` workgroups are the first's
-struct GemmPair {
-  GemmP p[2];
-  int first;
+// up to three independent products, one behind the other in the grid: end[i] workgroups up to and with product i
+struct GemmGroup {
+  GemmP p[3];
+  int end[3];
 };
-template <int NPP, int NPQ>
-__global__ __launch_bounds__(128) void gemm_pair_kernel(const GemmPair g) {
-  const int second = (int)blockIdx.x >= g.first;
-  gemm_small_block<NPP, NPQ>(g.p[second], (int)blockIdx.x - second * g.first, second ? (int)gridDim.x - g.first : g.first);
+__global__ __launch_bounds__(128) void gemm_group_kernel(const GemmGroup g) {
+  const int b = (int)blockIdx.x, i = b >= g.end[1] ? 2 : b >= g.end[0] ? 1 : 0, start = i ? g.end[i - 1] : 0;
+  gemm_small_block<2, 2, true>(g.p[i], b - start, g.end[i] - start);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -454,19 +459,30 @@ strp_status launch_gemm(strp_ctx* ctx, GemmP& p) {
   return STRP_OK;
 }
 
-// Two products of which neither reads what the other writes: in one launch where both are small ones of two planes each, which
-// saves a launch (4 us) and fills the chip better; otherwise one after the other.
-strp_status launch_gemm_pair(strp_ctx* ctx, GemmP& p, GemmP& q) {
-  const bool one = p.wt == 1 && q.wt == 1 && p.P.lo && p.Q.lo && q.P.lo && q.Q.lo && !p.k8_hi && !q.k8_hi;
+// Up to three products of which none reads what another writes: in one launch where all are small ones, which saves launches
+// (4 us each) and fills the chip better; otherwise one after the other.
+bool gemm_is_small(const GemmP& p) { return p.wt == 1 && !p.k8_hi; }
+strp_status launch_gemm_group(strp_ctx* ctx, GemmP* p, int n) {
+  bool one = true;
+  for (int i = 0; i < n; ++i) one = one && gemm_is_small(p[i]);
   if (!one) {
-    STRP_TRY(launch_gemm(ctx, p));
-    return launch_gemm(ctx, q);
+    for (int i = 0; i < n; ++i) STRP_TRY(launch_gemm(ctx, p[i]));
+    return STRP_OK;
   }
-  STRP_TRY(check_gemm(ctx, p));
-  STRP_TRY(check_gemm(ctx, q));
-  ProfScope ps(ctx, "gemm_h2x2_pair", 2.0 * (double)p.K * p.M * p.N * (p.triangle ? 0.5 : 1.0) + 2.0 * (double)q.K * q.M * q.N * (q.triangle ? 0.5 : 1.0), 0.0);
-  const GemmPair g{{p, q}, gemm_grid_blocks(p)};
-  hipLaunchKernelGGL((gemm_pair_kernel<2, 2>), dim3(g.first + gemm_grid_blocks(q)), dim3(128), 0, ctx->stream, g);
+  GemmGroup g;
+  int blocks = 0;
+  double flops = 0.0;
+  for (int i = 0; i < 3; ++i) {
+    g.p[i] = p[i < n ? i : 0];
+    if (i < n) {
+      STRP_TRY(check_gemm(ctx, p[i]));
+      blocks += gemm_grid_blocks(p[i]);
+      flops += 2.0 * (double)p[i].K * p[i].M * p[i].N * (p[i].triangle ? 0.5 : 1.0);
+    }
+    g.end[i] = blocks;
+  }
+  ProfScope ps(ctx, "gemm_group", flops, 0.0);
+  hipLaunchKernelGGL(gemm_group_kernel, dim3(blocks), dim3(128), 0, ctx->stream, g);
   STRP_HIP(ctx, hipGetLastError());
   return STRP_OK;
 }
@@ -556,15 +572,15 @@ __device__ __forceinline__ void splitk_reduce_block(const ReduceP& r, int bx, in
   }
 }
 __global__ __launch_bounds__(256) void splitk_reduce_kernel(const ReduceP r) { splitk_reduce_block(r, blockIdx.x, blockIdx.y, gridDim.x); }
-// two of them, `first` workgroups for the first
-struct ReducePair {
-  ReduceP r[2];
-  int first;
+// up to three of them, end[i] workgroups up to and with reduction i
+struct ReduceGroup {
+  ReduceP r[3];
+  int end[3];
 };
-__global__ __launch_bounds__(256) void splitk_reduce_pair_kernel(const ReducePair g) {
-  const int second = (int)blockIdx.x >= g.first;
-  const int b = (int)blockIdx.x - second * g.first, nx = (g.r[second].N + REDUCE_TILE_N - 1) / REDUCE_TILE_N;
-  const ReduceP r = g.r[second];
+__global__ __launch_bounds__(256) void splitk_reduce_group_kernel(const ReduceGroup g) {
+  const int i = (int)blockIdx.x >= g.end[1] ? 2 : (int)blockIdx.x >= g.end[0] ? 1 : 0;
+  const ReduceP r = g.r[i];
+  const int b = (int)blockIdx.x - (i ? g.end[i - 1] : 0), nx = (r.N + REDUCE_TILE_N - 1) / REDUCE_TILE_N;
   splitk_reduce_block(r, b % nx, b / nx, nx);
 }
 
@@ -578,10 +594,20 @@ strp_status launch_splitk_reduce(strp_ctx* ctx, const ReduceP& r) {
   return STRP_OK;
 }
 
-strp_status launch_splitk_reduce_pair(strp_ctx* ctx, const ReduceP& r, const ReduceP& q) {
-  const ReducePair g{{r, q}, reduce_blocks(r.M, r.N)};
-  ProfScope ps(ctx, "splitk_reduce", 0.0, 4.0 * ((double)r.M * r.N * (r.splits + 2) + (double)q.M * q.N * (q.splits + 2)));
-  hipLaunchKernelGGL(splitk_reduce_pair_kernel, dim3(g.first + reduce_blocks(q.M, q.N)), dim3(256), 0, ctx->stream, g);
+strp_status launch_splitk_reduce_group(strp_ctx* ctx, const ReduceP* r, int n) {
+  ReduceGroup g;
+  int blocks = 0;
+  double bytes = 0.0;
+  for (int i = 0; i < 3; ++i) {
+    g.r[i] = r[i < n ? i : 0];
+    if (i < n) {
+      blocks += reduce_blocks(r[i].M, r[i].N);
+      bytes += 4.0 * (double)r[i].M * r[i].N * (r[i].splits + 2);
+    }
+    g.end[i] = blocks;
+  }
+  ProfScope ps(ctx, "splitk_reduce", 0.0, bytes);
+  hipLaunchKernelGGL(splitk_reduce_group_kernel, dim3(blocks), dim3(256), 0, ctx->stream, g);
   STRP_HIP(ctx, hipGetLastError());
   return STRP_OK;
 }

@@ -223,8 +223,8 @@ __device__ __forceinline__ double small_src(const unsigned short* s, long long i
 // 16-byte chunk (eight k of one row) of each plane, so stores are whole kilobytes per wavefront; sources that are
 // stored along k are read 32 (fp32) bytes at a time, the others along consecutive rows.
 struct SplitJobs {
-  SplitJob j[2];
-  long long chunk0[3];      // first chunk of each job
+  SplitJob j[3];
+  long long chunk0[4];      // first chunk of each job
 };
 template <typename TS>
 __device__ __forceinline__ void split_chunk(const SplitJob& b, long long e) {
@@ -258,8 +258,8 @@ __device__ __forceinline__ void split_chunk(const SplitJob& b, long long e) {
 }
 __global__ __launch_bounds__(256) void split_small_kernel(const SplitJobs jobs) {
   const long long e = (long long)blockIdx.x * 256 + threadIdx.x;      // chunk counts are multiples of 128
-  if (e >= jobs.chunk0[2]) return;
-  const int q = e >= jobs.chunk0[1];
+  if (e >= jobs.chunk0[3]) return;
+  const int q = (e >= jobs.chunk0[1]) + (e >= jobs.chunk0[2]);
   const SplitJob& b = jobs.j[q];
   const long long c = e - jobs.chunk0[q];
   if (b.kind == SRC_F64) split_chunk<double>(b, c);
@@ -270,11 +270,11 @@ __global__ __launch_bounds__(256) void split_small_kernel(const SplitJobs jobs) 
 strp_status split_small(strp_ctx* ctx, const SplitJob* jobs, int n) {
   SplitJobs s;
   memset(&s, 0, sizeof(s));
-  for (int i = 0; i < 2; ++i) {
+  for (int i = 0; i < 3; ++i) {
     if (i < n) s.j[i] = jobs[i];
     s.chunk0[i + 1] = s.chunk0[i] + (i < n ? (long long)plane_elems(jobs[i].rows, jobs[i].cols) / 8 : 0);
   }
-  hipLaunchKernelGGL(split_small_kernel, dim3((unsigned)((s.chunk0[2] + 255) / 256)), dim3(256), 0, ctx->stream, s);
+  hipLaunchKernelGGL(split_small_kernel, dim3((unsigned)((s.chunk0[3] + 255) / 256)), dim3(256), 0, ctx->stream, s);
   STRP_HIP(ctx, hipGetLastError());
   return STRP_OK;
 }

@@ -151,8 +151,9 @@ struct GemmP {
 };
 
 strp_status launch_gemm(strp_ctx* ctx, GemmP& p);
-// two products, neither of which reads what the other writes; launch_splitk_reduce_pair: two reductions
-strp_status launch_gemm_pair(strp_ctx* ctx, GemmP& p, GemmP& q);
+// n <= 3 products, none of which reads what another writes; launch_splitk_reduce_group: n <= 3 reductions
+strp_status launch_gemm_group(strp_ctx* ctx, GemmP* p, int n);
+bool gemm_is_small(const GemmP& p);
 int gemm_grid_blocks(const GemmP& p);
 // tile shape (wt = 0: by the number of tiles), tile grid and K splits of a product
 void gemm_plan_tiles(GemmP& p, int want_splits, int wt = 0);
@@ -175,7 +176,7 @@ struct ReduceP {
   const float* dot; double* red;
 };
 strp_status launch_splitk_reduce(strp_ctx* ctx, const ReduceP& r);
-strp_status launch_splitk_reduce_pair(strp_ctx* ctx, const ReduceP& r, const ReduceP& q);
+strp_status launch_splitk_reduce_group(strp_ctx* ctx, const ReduceP* r, int n);
 constexpr int REDUCE_TILE_M = 16, REDUCE_TILE_N = 64;      // output tile of one workgroup of the split-K reduction
 static inline int reduce_blocks(int M, int N) { return ((M + REDUCE_TILE_M - 1) / REDUCE_TILE_M) * ((N + REDUCE_TILE_N - 1) / REDUCE_TILE_N); }
 // fp32 / bf16 activation rows (optionally gathered by idx) -> fp16 planes; any output pair may be null.
@@ -197,7 +198,7 @@ struct SplitJob {
   unsigned short* hi;
   unsigned short* lo;
 };
-strp_status split_small(strp_ctx* ctx, const SplitJob* jobs, int n);      // n <= 2, one launch
+strp_status split_small(strp_ctx* ctx, const SplitJob* jobs, int n);      // n <= 3, one launch
 // *maxbits[i] = max(*maxbits[i], bits of max|src_i|) for fp32 / bf16 matrices; n <= 2, one launch
 struct MaxJob {
   const void* src;
@@ -229,6 +230,15 @@ struct WeightsOut {
 };
 strp_status apply_inverse_right(strp_ctx* ctx, const double* Linv, int n, long long ldl, const double* X, int m, long long ldx, double* tmp,
                                 const WeightsOut& out);
+// Two solves of which neither reads what the other writes, in two launches; both of solve_is_small: less than a wave of tiles each
+bool solve_is_small(int m, int n);
+struct SolveIn {
+  const double* Linv; int n; long long ldl;
+  const double* X; int m; long long ldx;
+  double* tmp;
+  WeightsOut out;
+};
+strp_status apply_inverse_right_pair(strp_ctx* ctx, const SolveIn& a, const SolveIn& b);
 int weights_out_blocks(int m, int n);
 // The compact weights Wc [m x ldc] of an earlier refit out of W, with the same by-products (gather_blocks(m, n) sums).
 strp_status gather_weights(strp_ctx* ctx, const WeightsOut& io, int m, int n);
