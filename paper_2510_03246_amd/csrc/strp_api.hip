@@ -1264,6 +1264,7 @@ strp_status strp_admm_step(strp_ctx* ctx, const strp_module_desc* desc, strp_mod
     STRP_TRY(make_t_planes(ctx, a2, st->A, STRP_F32, lda, st->idx, s, T, 0, npa, &Arow));
     ReduceP r = reduce_to(Gd, lds);
     r.ridge_dev = sc + SC_LAM2;
+    const Arena first = a2;                 // of a Gram product by itself: its partials are gone before the factor and R2 are written
     RefitIn ri;
     memset(&ri, 0, sizeof(ri));
     STRP_TAKE(ctx, a2, Ginv, double, (size_t)s * lds);
@@ -1282,7 +1283,7 @@ strp_status strp_admm_step(strp_ctx* ctx, const strp_module_desc* desc, strp_mod
       ri.r_ready = 1;
     }
     ri.R = R2;
-    if (!ri.r_ready) STRP_TRY(nt_product(ctx, a2, Gp, Gq, s, s, T, 1, r));
+    if (!ri.r_ready) STRP_TRY(nt_product(ctx, first, Gp, Gq, s, s, T, 1, r));
     STRP_TRY(ridge_solve(ctx, a2, ri, w2out));
   } else if (W2S) {
     STRP_TRY(gather_weights(ctx, w2out, d, s));

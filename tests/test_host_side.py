@@ -122,6 +122,30 @@ def check_workspace_of_a_module():
             assert a[1] == b[1], (d, f, T, k_max, i, [x for x in zip(a[1], b[1]) if x[0] != x[1]])
 
 
+# d, f, tokens, kept units; the bytes of workspace that an iteration, and a refit of fc2 alone, need with a launch for each product
+LEAST = [(64, 256, 512, 128, 1094144, 754176), (768, 3072, 65536, 1536, 919566592, 497811968), (64, 1024, 200000, 300, 567143424, 316930304),
+         (136, 520, 1003, 520, 9277184, 8657664), (512, 2048, 64, 100, 10825984, 1321984)]
+
+
+def check_least_workspace_of_a_step():
+    """A launch that several products share is taken where there is room for it, never refused for want of it."""
+    lib = Library()
+    strp = lib.strp
+    for d, f, T, k, *least in LEAST:
+        ld = (T + 7) // 8 * 8
+        desc = strp.ModuleDesc(d, f, T, ld, ld, strp.F32, strp.F32, k)
+        st = strp.ModuleState()
+        for name, kind in strp.ModuleState._fields_:
+            if kind is C.c_void_p:
+                setattr(st, name, 1 << 50)
+        p = strp.Params(1.0, 1.0, 0.01, strp.GAIN, 1, k, 0)
+        lib.workspace(1 << 50)
+        assert lib.lib.strp_module_init(lib.h, C.byref(desc), C.byref(st), C.byref(p)) == strp.OK
+        for p.stages, ws in zip((0, strp.STAGE_REFIT2), least):
+            lib.workspace(ws)
+            assert lib.lib.strp_admm_step(lib.h, C.byref(desc), C.byref(st), C.byref(p), None) == strp.OK, (d, f, T, k, ws, lib.lib.strp_last_error(lib.h))
+
+
 def check_cached_factor_needs_no_alignment():
     """cholH is an array of doubles like any other, in exactly the workspace asked for."""
     lib = Library()
@@ -266,7 +290,7 @@ def check_weight_statistics_without_a_counter():
     assert [len(call(last, n)[1]) for n in (1, 8, 9)] == [2, 2, 3]
 
 
-CHECKS = [check_weight_statistics_without_a_counter, check_what_the_gram_matrices_cover, check_what_the_large_systems_cover, check_selection_of_a_very_wide_module, check_weight_statistics_arguments, check_weight_statistics_workgroups, check_chains, check_workspace_of_a_module, check_cached_factor_needs_no_alignment]
+CHECKS = [check_weight_statistics_without_a_counter, check_what_the_gram_matrices_cover, check_what_the_large_systems_cover, check_selection_of_a_very_wide_module, check_weight_statistics_arguments, check_weight_statistics_workgroups, check_chains, check_workspace_of_a_module, check_least_workspace_of_a_step, check_cached_factor_needs_no_alignment]
 
 
 @pytest.fixture(scope="session")
