@@ -808,7 +808,7 @@ static strp_status ridge_solve(strp_ctx* ctx, Arena& arena, const RefitIn& in, c
 }
 
 // Both refits of a small module: their products, reductions and solves are independent of each other, and each leaves most of the
-// chip idle, so they share launches: 27 instead of 32 in an iteration of a 64 x 256 module over 512 tokens, 218 -> 192 us.
+// chip idle, so they share launches: 26 instead of 32 in an iteration of a 64 x 256 module over 512 tokens, 218 -> 190 us.
 // Y, X: the cached planes; Linv1: the inverse factor of the fc1 system.
 struct RefitsIn {
   const float* A; const float* Z; long long lda; const int* idx;
@@ -857,8 +857,7 @@ static strp_status refit_both(strp_ctx* ctx, Arena& arena, const RefitsIn& in, c
   *done = 1;
   arena = keep;
   *Zk = Zc;
-  STRP_TRY(split_act(ctx, in.A, STRP_F32, in.lda, in.idx, s, T, 0, 0, (unsigned short*)At.hi, (unsigned short*)At.lo, nullptr, nullptr));
-  STRP_TRY(split_act(ctx, in.Z, STRP_F32, in.lda, in.idx, s, T, 0, 1, (unsigned short*)Zt.hi, (unsigned short*)Zt.lo, (unsigned short*)Zc.hi, (unsigned short*)Zc.lo));
+  STRP_TRY(split_act_pair(ctx, in.A, in.Z, in.lda, in.idx, s, T, At, Zt, Zc));
   STRP_TRY(launch_gemm_group(ctx, p, 3));
   STRP_TRY(launch_splitk_reduce_group(ctx, r, 3));
   STRP_TRY(factor_and_invert(ctx, a2, G, s, Ginv, lds));

@@ -185,6 +185,9 @@ static inline int reduce_blocks(int M, int N) { return ((M + REDUCE_TILE_M - 1) 
 strp_status split_act(strp_ctx* ctx, const void* src, int src_dtype, long long lds, const int* idx, int rows, long long T,
                       int relu_t, int relu_c, unsigned short* t_hi, unsigned short* t_lo, unsigned short* c_hi,
                       unsigned short* c_lo);
+// Rows idx of two fp32 matrices in one launch: a -> t_* (At), z -> t_* (Zt) and, with relu, c_* (Zc); all of one plane or all of two.
+strp_status split_act_pair(strp_ctx* ctx, const float* a, const float* z, long long lds, const int* idx, int rows, long long T, const PlaneOp& At,
+                           const PlaneOp& Zt, const PlaneOp& Zc);
 // One fp16 plane of a [C x T] quantity with k = channel, r = token (plane_elems(T, C)) -> the plane with k = token,
 // r = channel (plane_elems(C, T)); padding tokens zero.
 strp_status plane_c_to_t(strp_ctx* ctx, const unsigned short* src, unsigned short* dst, int C, long long T);
