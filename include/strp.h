@@ -76,7 +76,9 @@ strp_status strp_set_product_planes(strp_ctx* ctx, strp_product product, int32_t
 /* Caller-owned scratch used by every entry point below (256-byte aligned).  strp_workspace_bytes(desc) is enough for every
  * call on a module, and results do not depend on how much more there is.  With less, strp_gram and strp_refit sum the tokens in
  * as many parts as fit, in fp32 chains of at most 8192 tokens each: the last bits of a Gram matrix or a right-hand
- * side then depend on the workspace's size.  STRP_ENOMEM when not even those fit. */
+ * side then depend on the workspace's size.  STRP_ENOMEM when not even those fit.
+ * Calls on one workspace run one after the other on the context's stream.  Captured calls that are replayed at the same time
+ * need workspaces of their own, set before each is captured. */
 strp_status strp_set_workspace(strp_ctx* ctx, void* dev_ptr, size_t bytes);
 /* Synchronise the stream and return the device status word (STRP_OK, STRP_ENOTPD, ...). */
 strp_status strp_poll(strp_ctx* ctx);

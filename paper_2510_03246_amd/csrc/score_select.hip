@@ -316,8 +316,8 @@ strp_status launch_unit_scores(strp_ctx* ctx, const double* sums, const double* 
 // weight statistics of a parameter group (Alg. 2 step 1): sum |w|, sum w, sum w^2 over every entry of a list of
 // matrices, folded into  energy += scale (|W|_1 + cv Var(W) + c2 |W|_2).
 // A model has a few hundred small groups (a head's four slices are 0.4 MB), so a call costs its launches: one for up to eight
-// matrices, whose last workgroup adds the partial sums in order.  The counter that tells it is the context's own (strp_ctx::ticket),
-// zero between calls; a context without one takes a second launch instead.
+// matrices, whose last workgroup adds the partial sums in order.  The counter that tells it belongs to the context and its
+// workspace, like the sums (strp_ctx::ticket), and is zero between calls; where none was left a second launch adds them.
 // ---------------------------------------------------------------------------------------------
 constexpr int WSTAT_BLOCKS = 256, WSTAT_MATS = 8;
 

@@ -39,11 +39,18 @@ constexpr size_t TOPK_STATIC_BYTES = 1u << 20;
 static __device__ __align__(256) unsigned char topk_static_scratch[TOPK_STATIC_BYTES];
 constexpr int MAX_DEVICES = 64;
 static void* g_topk_scratch[MAX_DEVICES];
-// The contexts' counters (strp_ctx::ticket): each context takes the next one and keeps it.  None is used again, so work that is
-// still in flight when its context is destroyed meets nobody on it.
+// Counters of the weight statistics (strp_ctx::ticket): a context takes the next one, and another for the first weight statistics on
+// another workspace.  Calls that may overlap in time -- captured ones, replayed on several streams -- have their scratch in
+// workspaces of their own, and so never meet on a counter.  None is used again, so work that is still in flight when its context
+// is destroyed or its workspace replaced meets nobody on it.
 constexpr unsigned int MAX_TICKETS = 16384;
 static __device__ unsigned int context_tickets[MAX_TICKETS];
 static std::atomic<unsigned int> g_tickets_taken{0};
+static unsigned int* next_ticket(unsigned int* tickets) {
+  if (!tickets || g_tickets_taken.load() >= MAX_TICKETS) return nullptr;
+  const unsigned int slot = g_tickets_taken.fetch_add(1);
+  return slot < MAX_TICKETS ? tickets + slot : nullptr;
+}
 
 namespace strp {
 
@@ -334,12 +341,13 @@ strp_status strp_create(strp_ctx** out, int device, void* hip_stream) {
     }
     g_topk_scratch[device] = ptr;
   }
-  const unsigned int slot = g_tickets_taken.load() < MAX_TICKETS ? g_tickets_taken.fetch_add(1) : MAX_TICKETS;
   void* tickets = nullptr;
-  if (slot < MAX_TICKETS && hipGetSymbolAddress(&tickets, HIP_SYMBOL(context_tickets)) == hipSuccess && tickets)
-    c->ticket = (unsigned int*)tickets + slot;
-  else
+  if (hipGetSymbolAddress(&tickets, HIP_SYMBOL(context_tickets)) != hipSuccess) {
     (void)hipGetLastError();
+    tickets = nullptr;
+  }
+  c->tickets = (unsigned int*)tickets;
+  c->ticket = next_ticket(c->tickets);
   *out = c;
   return STRP_OK;
 }
@@ -433,6 +441,7 @@ strp_status strp_set_workspace(strp_ctx* ctx, void* dev_ptr, size_t bytes) {
   if (!ctx) return STRP_EINVAL;
   if (!dev_ptr || bytes < 4096) return fail(ctx, STRP_EINVAL, "workspace: null or smaller than 4096 bytes");
   if ((uintptr_t)dev_ptr & 255u) return fail(ctx, STRP_EINVAL, "workspace: pointer not 256-byte aligned");
+  if (ctx->ws && ctx->ws != (char*)dev_ptr) ctx->ticket_due = 1;
   ctx->ws = (char*)dev_ptr;
   ctx->ws_bytes = bytes;
   ctx->status_dev = (int32_t*)dev_ptr;
@@ -507,6 +516,10 @@ strp_status strp_weight_energy(strp_ctx* ctx, const strp_weight_ref* mats, int32
   }
   Arena arena(ctx);
   STRP_TAKE(ctx, arena, partial, double, weight_energy_scratch_bytes() / sizeof(double));
+  if (ctx->ticket_due) {
+    ctx->ticket = next_ticket(ctx->tickets);
+    ctx->ticket_due = 0;
+  }
   return launch_weight_energy(ctx, mats, n_mats, var_coef, l2_coef, scale, energy, partial);
 }
 

@@ -26,9 +26,11 @@ struct strp_ctx {
   // Set by strp_admm_step while a streaming job waits for a launch to ride along with (see cojob.h); null everywhere else.
   // The next chol_inverse takes it.
   const strp::CoJob* cojob;
-  // A device counter that only this context's launches use, on its one stream: zero between calls, reset by the workgroup that
-  // reads its last count.  Null when the process has had more contexts than there are counters.
+  // A device counter that only this context's weight statistics on its present workspace use: zero between calls, reset by the
+  // workgroup that reads its last count.  Null when the process has taken all there are.
   unsigned int* ticket;
+  unsigned int* tickets;  // all of them, on this device
+  int ticket_due;         // another workspace has been set: the next weight statistics take the next counter
 };
 
 struct Profiler;

@@ -8,7 +8,7 @@
 typedef struct { uint32_t x, y, z; } dim3_t;
 static struct { const void* fn; const char* name; } kernels[512];
 static int n_kernels;
-static struct { const char* name; uint32_t grid[3]; } launches[4096];
+static struct { const char* name; uint32_t grid[3]; uint64_t word; } launches[4096];
 static int n_launches;
 static dim3_t cfg_grid, cfg_block;
 static char device_array[1];
@@ -17,6 +17,11 @@ void fake_clear(void) { n_launches = 0; }
 int fake_count(void) { return n_launches; }
 const char* fake_name(int i) { return launches[i].name; }
 uint32_t fake_grid(int i, int d) { return launches[i].grid[d]; }
+/* Of launches of the kernels whose name holds this, the eight bytes at `offset` of parameter `arg` are kept as well. */
+static const char* watched;
+static int watched_arg, watched_offset;
+void fake_watch(const char* name, int arg, int offset) { watched = strdup(name); watched_arg = arg; watched_offset = offset; }
+uint64_t fake_word(int i) { return launches[i].word; }
 
 void** __hipRegisterFatBinary(const void* data) { (void)data; static void* handle; return &handle; }
 void __hipUnregisterFatBinary(void** m) { (void)m; }
@@ -37,11 +42,13 @@ int __hipPopCallConfiguration(dim3_t* grid, dim3_t* block, size_t* shared, void*
   return 0;
 }
 int hipLaunchKernel(const void* fn, dim3_t grid, dim3_t block, void** args, size_t shared, void* stream) {
-  (void)block; (void)args; (void)shared; (void)stream;
+  (void)block; (void)shared; (void)stream;
   const char* name = "?";
   for (int i = 0; i < n_kernels; ++i) if (kernels[i].fn == fn) name = kernels[i].name;
   if (n_launches < 4096) {
     launches[n_launches].name = name;
+    launches[n_launches].word = 0;
+    if (watched && strstr(name, watched)) memcpy(&launches[n_launches].word, (const char*)args[watched_arg] + watched_offset, 8);
     launches[n_launches].grid[0] = grid.x; launches[n_launches].grid[1] = grid.y; launches[n_launches++].grid[2] = grid.z;
   }
   return 0;

@@ -290,7 +290,39 @@ def check_weight_statistics_without_a_counter():
     assert [len(call(last, n)[1]) for n in (1, 8, 9)] == [2, 2, 3]
 
 
-CHECKS = [check_weight_statistics_without_a_counter, check_what_the_gram_matrices_cover, check_what_the_large_systems_cover, check_selection_of_a_very_wide_module, check_weight_statistics_arguments, check_weight_statistics_workgroups, check_chains, check_workspace_of_a_module, check_least_workspace_of_a_step, check_cached_factor_needs_no_alignment]
+def check_weight_statistics_counter():
+    """Calls that may overlap in time, because their scratch is not the same, do not meet on a counter: each workspace a context is
+    given has one of its own, and so has each context.  Calls on one workspace share it."""
+    lib = Library()
+    strp = lib.strp
+    lib.fake.fake_word.restype = C.c_uint64
+    lib.fake.fake_watch(b"weight_sums_kernel", 3, 40)         # WeightEnd::ticket
+    refs = (strp.WeightRef * 4)(*[strp.WeightRef(1 << 50, strp.F32, 40, 64, 64) for _ in range(4)])
+
+    def counter(h, ws=None):
+        if ws:
+            assert lib.lib.strp_set_workspace(h, ws, 1 << 30) == strp.OK
+        st, launches = lib.launches(lambda: lib.lib.strp_weight_energy(h, refs, 4, 0.1, 0.1, 1.0, 1 << 51))
+        assert st == strp.OK and len(launches) == 1
+        return lib.fake.fake_word(0)
+
+    a = counter(lib.h)
+    assert a and counter(lib.h) == a
+    assert counter(lib.h, 1 << 40) == a                       # the workspace it has
+    b = counter(lib.h, 1 << 41)
+    assert b and b != a and counter(lib.h) == b
+    c = counter(lib.h, 1 << 40)                               # calls on the second one may still be under way
+    assert c and c != b
+    other = C.c_void_p()
+    assert lib.lib.strp_create(C.byref(other), 0, None) == strp.OK
+    assert counter(other, 1 << 42) not in (0, a, b, c)
+    # workspaces that no weight statistics run on take no counter
+    for i in range(20000):
+        lib.lib.strp_set_workspace(lib.h, (1 << 43) + (i << 20), 1 << 20)
+    assert counter(lib.h) not in (0, a, b, c)
+
+
+CHECKS = [check_weight_statistics_counter, check_weight_statistics_without_a_counter, check_what_the_gram_matrices_cover, check_what_the_large_systems_cover, check_selection_of_a_very_wide_module, check_weight_statistics_arguments, check_weight_statistics_workgroups, check_chains, check_workspace_of_a_module, check_least_workspace_of_a_step, check_cached_factor_needs_no_alignment]
 
 
 @pytest.fixture(scope="session")
