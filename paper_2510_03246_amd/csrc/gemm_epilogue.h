@@ -401,6 +401,7 @@ __device__ __forceinline__ void token_row(const GemmP& p, const floatx4 (&c)[4],
     for (int t = 0; t < 2; ++t) {
       const int n = n_lane + 32 * t;
       floatx4 out;
+      float q0[4], q1[4];            // the row sums' terms, added by pairs: a strip's 64 tokens are a tree of six levels, no chain
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
         const float left = c[2 * t][r], right = c[2 * t + 1][r];      // a copy first: a bit cast of a vector's element takes its first
@@ -413,8 +414,8 @@ __device__ __forceinline__ void token_row(const GemmP& p, const floatx4 (&c)[4],
         } else if (EPI == EPI_AUPD) {
           const float a = __builtin_fmaxf(in.in0[h][t][r], 0.0f) + v;
           out[r] = a;
-          rs0[h] += ok ? a * a : 0.0f;
-          if (Z0) rs1[h] += ok ? a * __builtin_fmaxf(in.in1[h][t][r], 0.0f) : 0.0f;
+          q0[r] = ok ? a * a : 0.0f;
+          if (Z0) q1[r] = ok ? a * __builtin_fmaxf(in.in1[h][t][r], 0.0f) : 0.0f;
         } else {
           const float a = in.in0[h][t][r], z1 = v;
           float z;
@@ -426,7 +427,7 @@ __device__ __forceinline__ void token_row(const GemmP& p, const floatx4 (&c)[4],
             const float costp = p.beta * (a - cp) * (a - cp) + p.alpha * (cp - z1) * (cp - z1);
             z = costm < costp ? cm : cp;
             out[r] = z;
-            if (Z0) rs0[h] += ok ? in.in1[h][t][r] * z : 0.0f;
+            if (Z0) q0[r] = ok ? in.in1[h][t][r] * z : 0.0f;
           } else {
             z = in.in1[h][t][r];
           }
@@ -436,6 +437,8 @@ __device__ __forceinline__ void token_row(const GemmP& p, const floatx4 (&c)[4],
           s1 += rz * rz;
         }
       }
+      if (EPI == EPI_AUPD || (EPI == EPI_ZUPD && ZWRITE && Z0)) rs0[h] += (q0[0] + q0[1]) + (q0[2] + q0[3]);
+      if (EPI == EPI_AUPD && Z0) rs1[h] += (q1[0] + q1[1]) + (q1[2] + q1[3]);
       if (!GATHER || ZWRITE) {
         float* dst = (EPI == EPI_PARTIAL ? p.out : EPI == EPI_AUPD ? p.As : p.Zs) + in.at(p, h) + n;
         if (!EDGE || (mrow && n + 3 < p.N)) {
