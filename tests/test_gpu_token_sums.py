@@ -23,9 +23,9 @@ def _tree(x, y):
 
 @pytest.mark.parametrize("mode", [strp.WANDA, strp.GAIN])
 def test_error_of_the_sums_of_a_strip(mode):
-    """The root mean square error over 3 x 16384 rows is known to half a percent; a chain of eight additions within the strip is 5 %
-    above the tree for terms of both signs (sum Z0 Z), so 2.5 % tells them apart.  The sums are fp64 [4][f] behind the first 256
-    bytes of the module's cache."""
+    """The root mean square error over 3 x 16384 rows is known to half a percent; a chain of eight additions within the strip is
+    2.5 % (sum Z0 Z) and 4.4 % (sum A^2) above the tree, so 1.5 % tells them apart.  The sums are fp64 [4][f] behind the first
+    256 bytes of the module's cache."""
     ctx = strp.Context(0)
     cfg = inputs.WorkloadConfig("case", 1, D, F, 0, T, "bf16", "t3", 3, 0.5, 1)
     err = {}
@@ -50,5 +50,5 @@ def test_error_of_the_sums_of_a_strip(mode):
         del mod
     ratio = {q: (err[q, "kernel"] / err[q, "tree"]) ** 0.5 for q, who in err if who == "tree"}
     print(ratio)
-    assert all(0.5 < r <= 1.025 for r in ratio.values()), ratio
+    assert all(0.5 < r <= 1.015 for r in ratio.values()), ratio
     ctx.close()
