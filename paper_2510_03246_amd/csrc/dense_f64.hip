@@ -136,8 +136,13 @@ __device__ __forceinline__ void dgemm_block(const DgemmP& p, int block) {
   const double* A = AKC ? p.A + (long long)m0 * p.lda : p.A + m0;
   const double* B = BKC ? p.B + (long long)n0 * p.ldb : p.B + n0;
   const int rvm = p.M - m0, rvn = p.N - n0;
-  F64Loader<TM, DK, AKC> la[2];
-  F64Loader<TN, DK, BKC> lb[2];
+  // Stages in flight in registers besides the one in LDS that is multiplied: two, since with few workgroups per CU a stage of a
+  // small tile is multiplied in less time than a load takes; one for the 128 x 128 tile, whose stage takes far longer than that and
+  // whose accumulators leave no room for a second (two spilled 52 registers: 6000 x 6000 6642 us instead of 6479, 8602 x 7168 13497
+  // instead of 13089).
+  constexpr int SETS = TM * TN >= 128 * 128 ? 1 : 2;
+  F64Loader<TM, DK, AKC> la[SETS];
+  F64Loader<TN, DK, BKC> lb[SETS];
   auto multiply = [&](int buf) {
     const double* as = As[buf];
     const double* bs = Bs[buf];
@@ -168,8 +173,6 @@ __device__ __forceinline__ void dgemm_block(const DgemmP& p, int block) {
   const bool pairs = (AKC || rvm >= TM || p.lda % 2 == 0) && (BKC || rvn >= TN || p.ldb % 2 == 0);
   const int whole = pairs && kend > kbeg ? (kend - kbeg) / DK : 0;
   if (whole) {
-    // two stages in flight in registers besides the one in LDS that is multiplied: with few workgroups per CU a stage is
-    // multiplied in less time than a load takes
     unsigned int offa[F64Loader<TM, DK, AKC>::NCH], offb[F64Loader<TN, DK, BKC>::NCH];
     F64Loader<TM, DK, AKC>::offsets(offa, p.lda, rvm);
     F64Loader<TN, DK, BKC>::offsets(offb, p.ldb, rvn);
@@ -178,17 +181,26 @@ __device__ __forceinline__ void dgemm_block(const DgemmP& p, int block) {
       la[set].load_whole(AKC ? A + k : A + k * p.lda, offa);
       lb[set].load_whole(BKC ? B + k : B + k * p.ldb, offb);
     };
-    auto stage = [&](int buf, int s) {      // multiply stage s, held in As[buf]; the next one is in set buf ^ 1
-      gload(buf, s + 2);
-      multiply(buf);
-      la[buf ^ 1].store(As[buf ^ 1]);       // its readers finished before the previous barrier
-      lb[buf ^ 1].store(Bs[buf ^ 1]);
+    auto put = [&](int set, int buf) {      // the buffer's readers finished before the previous barrier
+      la[set].store(As[buf]);
+      lb[set].store(Bs[buf]);
+    };
+    auto stage = [&](int buf, int s) {      // multiply stage s, held in As[buf]; the next one is in set buf ^ 1, or in the only one
+      if constexpr (SETS == 2) {
+        gload(buf, s + 2);
+        multiply(buf);
+        put(buf ^ 1, buf ^ 1);
+      } else {
+        put(0, buf ^ 1);
+        gload(0, s + 2);
+        multiply(buf);
+      }
       lds_barrier();
     };
     gload(0, 0);
-    gload(1, 1);
-    la[0].store(As[0]);
-    lb[0].store(Bs[0]);
+    if constexpr (SETS == 2) gload(1, 1);
+    put(0, 0);
+    if constexpr (SETS == 1) gload(0, 1);
     lds_barrier();
     int s = 0;
     for (; s + 2 <= whole; s += 2) {
@@ -280,19 +292,23 @@ __global__ __launch_bounds__(256, 2) void dgemm_pair_kernel(const DgemmPair g) {
 
 // Tile of a product by its grid: 128 x 128 tiles read the fewest operand bytes per flop but need enough of them to fill
 // the chip; below that the longest tile (whole K) sets the run time and a smaller one ends sooner.  Solves X (L L^T)^-1 of
-// m x n (two products), us with 64 x 32 / 64 x 64 / 128 x 128 tiles:  768 x 1536 104 / 139 / 505;  2048 x 3277 (1664 tiles of
-// 64, 416 of 128) 722 / 708 / 1226;  3000 x 3000 (2209, 576) 1051 / 883 / 1222;  4096 x 4096 (4096, 1024) 2143 / 2090 / 2191;
-// 4096 x 4915 (4928, 1248) 3097 / 3025 / 3205, 62 TFLOP/s;  6000 x 6000 (8836, 2209) 7722 / 6669 / 6523;  8602 x 7168 (15232,
-// 3808) 16440 / 14544 / 13178.  64 and 128 are within 7 % of each other from 1000 tiles of 128 to 2000.
-// Before whole stages were loaded without a branch the tiles chosen took 127, 824, 1033, 2282 and 3489 us (first five).
-constexpr int DGEMM_T128 = 1000, DGEMM_T64 = 2000;
+// m x n (two products), us with 64 x 32 / 64 x 64 / 128 x 128 tiles (in brackets the tiles of 64, of 128):
+//   768 x 1536 (288) 104 / 139 / 433;  2048 x 2048 (1024) 296 / 312 / 573;  2200 x 2200 (1225) 429 / 398 / 698;
+//   2304 x 2304 (1296) 400 / 417 / 726;  2496 x 2496 (1521) 591 / 521 / 861;  2048 x 3277 (1664) 717 / 726 / 1144;
+//   3000 x 3000 (2209, 576) 1059 / 888 / 1161;  4096 x 4096 (4096, 1024) 2174 / 2119 / 2240;  4096 x 4915 (4928, 1248)
+//   3192 / 3070 / 3088, 65 TFLOP/s;  4864 x 4864 (5776, 1444) 3657 / 3528 / 3528;  5120 x 5120 (6400, 1600) 4219 / 4139 / 4059;
+//   6000 x 6000 (8836, 2209) 7783 / 6968 / 6479;  8602 x 7168 (15120, 3808) 16774 / 14895 / 13089.
+// From 1000 to 1700 tiles of 64 the 64 x 32 one is up to 5 % faster or 12 % slower, as its last round of workgroups fills.
+// Linv^T Linv (half the tiles, order):  2600 (840) 162 / 158 / 361;  3000 (1104) 249 / 260 / 494;  3400 (1458) 361 / 284 / 616;
+// 6000 (4418, 1104) 1765 / 1328 / 1743;  8192 (8192, 2048) 4195 / 3212 / 3335;  10240 (12800, 3200) 8134 / 6575 / 5665.
+constexpr int DGEMM_T128 = 1450, DGEMM_T128_LOWER = 2500, DGEMM_T64 = 1200;
 
 static inline bool aligned_vec(const void* p, long long ld) { return ((uintptr_t)p & 15u) == 0 && (ld & 1) == 0; }
 
 struct DgemmTile { int tm, tn; };
 static DgemmTile dgemm_tile(int M, int N, int lower) {
   auto tiles = [&](int tm, int tn) { return (long long)((M + tm - 1) / tm) * ((N + tn - 1) / tn) / (lower ? 2 : 1); };
-  if (tiles(128, 128) >= DGEMM_T128) return {128, 128};
+  if (tiles(128, 128) >= (lower ? DGEMM_T128_LOWER : DGEMM_T128)) return {128, 128};
   return tiles(64, 64) >= DGEMM_T64 ? DgemmTile{64, 64} : DgemmTile{64, 32};
 }
 static int dgemm_blocks(int M, int N, DgemmTile t) { return ((M + t.tm - 1) / t.tm) * ((N + t.tn - 1) / t.tn); }

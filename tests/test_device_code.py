@@ -1,5 +1,6 @@
-"""What the compiler does not check in statements written as assembly: a DPP operand must not be read within two wait states of
-its being written by a vector instruction (no GPU needed: the built library's own device code is listed)."""
+"""What can be told from the built library's own device code, without a GPU.  No kernel keeps registers in scratch memory.  And what
+the compiler does not check in statements written as assembly: a DPP operand must not be read within two wait states of its being
+written by a vector instruction."""
 import glob
 import os
 import re
@@ -8,7 +9,7 @@ import subprocess
 
 import pytest
 
-OBJDUMP = "/opt/rocm/llvm/bin/llvm-objdump"
+OBJDUMP, READELF = "/opt/rocm/llvm/bin/llvm-objdump", "/opt/rocm/llvm/bin/llvm-readelf"
 REG = re.compile(r"^v(?:\[(\d+):(\d+)\]|(\d+))$")
 
 
@@ -48,17 +49,34 @@ def test_the_scan_sees_a_distance_that_is_too_short():
     assert _too_close(close)[0] and not _too_close(close.replace("s_nop 0", "s_nop 1"))[0]
 
 
-def test_dpp_operands_are_read_two_wait_states_after_they_were_written(tmp_path):
+@pytest.fixture(scope="module")
+def device_objects(tmp_path_factory):
     if not os.path.exists(OBJDUMP):
         pytest.skip("no llvm-objdump")
     from paper_2510_03246_amd import strp
     if not os.path.exists(strp.LIB_PATH):
         import __graft_entry__
         __graft_entry__.build()
+    tmp_path = tmp_path_factory.mktemp("device")
     lib = shutil.copy(strp.LIB_PATH, tmp_path / "lib.so")
     subprocess.run([OBJDUMP, "--offloading", str(lib)], check=True, capture_output=True, cwd=tmp_path)
+    return sorted(glob.glob(str(tmp_path / "*gfx950*")))
+
+
+def test_no_kernel_uses_scratch(device_objects):
+    kernels = {}
+    for obj in device_objects:
+        notes = subprocess.run([READELF, "--notes", obj], check=True, capture_output=True, text=True).stdout
+        for entry in notes.split("- .agpr_count")[1:]:
+            fields = dict(re.findall(r"^ *\.(name|private_segment_fixed_size|vgpr_spill_count): +(\S+)$", entry, re.M))
+            kernels[fields["name"]] = (int(fields["private_segment_fixed_size"]), int(fields["vgpr_spill_count"]))
+    assert len(kernels) > 50
+    assert not {k: v for k, v in kernels.items() if v != (0, 0)}
+
+
+def test_dpp_operands_are_read_two_wait_states_after_they_were_written(device_objects):
     found = 0
-    for obj in glob.glob(str(tmp_path / "*gfx950*")):
+    for obj in device_objects:
         bad, n = _too_close(subprocess.run([OBJDUMP, "-d", "--no-show-raw-insn", obj], check=True, capture_output=True, text=True).stdout)
         assert not bad, bad[:5]
         found += n

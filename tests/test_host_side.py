@@ -20,7 +20,7 @@ CHAINS = [((64, 64, 512), 256), ((128, 128, 2000), 256), ((1536, 1536, 65536), 3
 GRAMS = [(64, 8), (129, 520), (255, 4104), (256, 256), (257, 264), (512, 8200), (640, 70000), (768, 16384), (1025, 2056), (1280, 3000),
          (256, 65536), (512, 65536), (832, 65536), (1280, 16384), (300, 100000)]
 # order of the system and rows of the right-hand side in tests/test_gpu_factor.py where its launches change their shape
-LARGE_SYSTEMS = [(1409, 333), (2113, 65), (3137, 129), (2881, 2900), (4099, 4100)]
+LARGE_SYSTEMS = [(1409, 333), (2113, 65), (3137, 129), (2881, 2900), (4099, 4100), (4866, 4870)]
 
 
 class Library:
