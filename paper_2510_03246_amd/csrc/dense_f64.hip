@@ -1173,7 +1173,7 @@ __global__ __launch_bounds__(256, 2) void chol_begin_kernel(const StepP p, int c
 }
 
 // Linv [n x n, ldv] = L^-1 of A = L L^T (lower part of A [n x n, ld], destroyed); upper part of Linv zero.
-// sub: ceil(n / NB) * NB * NB doubles of scratch.  ld and ldv even, A and Linv 16-byte aligned.
+// sub: chol_scratch_elems(n) doubles of scratch.  ld and ldv even, A and Linv 16-byte aligned.
 strp_status chol_inverse(strp_ctx* ctx, double* A, int n, long long ld, double* sub, double* Linv, long long ldv, int32_t* status) {
   if (!aligned_vec(A, ld) || !aligned_vec(Linv, ldv)) return fail(ctx, STRP_EINVAL, "chol_inverse: operands not 16-byte aligned or odd leading dimension");
   CoJob job;

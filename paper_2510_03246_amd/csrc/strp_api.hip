@@ -793,8 +793,7 @@ struct RefitIn {
 
 // Factor the system in `sys` (leading dimension f64_ld(n), holds Gram + lam I) and leave the inverse of its Cholesky factor in Linv.
 static strp_status factor_and_invert(strp_ctx* ctx, Arena arena, double* sys, int n, double* Linv, long long ldl) {
-  const int nblk = (n + NB - 1) / NB;
-  STRP_TAKE(ctx, arena, sub, double, (size_t)nblk * NB * NB);
+  STRP_TAKE(ctx, arena, sub, double, chol_scratch_elems(n));
   return chol_inverse(ctx, sys, n, f64_ld(n), sub, Linv, ldl, ctx->status_dev);
 }
 
@@ -805,9 +804,7 @@ static strp_status ridge_solve(strp_ctx* ctx, Arena& arena, const RefitIn& in, c
   const bool factor = !in.linv_ready;
   if (factor) {
     if (in.sys_ready == 0) STRP_TRY(f32_to_f64_ridge(ctx, in.Gram, in.ldg, in.sys, ld, n, in.lam, in.lam_dev));
-    const size_t fbytes = ((size_t)((n + NB - 1) / NB) * NB * NB * 8 + 255) & ~size_t(255);
-    STRP_TAKE(ctx, arena, fscratch, char, fbytes);
-    STRP_TRY(factor_and_invert(ctx, Arena(fscratch, fbytes), in.sys, n, in.Linv, in.ldl));
+    STRP_TRY(factor_and_invert(ctx, arena, in.sys, n, in.Linv, in.ldl));
   }
   double* R = in.R;
   if (!R) {
@@ -859,7 +856,7 @@ static strp_status refit_both(strp_ctx* ctx, Arena& arena, const RefitsIn& in, c
   double* const R1 = matrix(s, ldd);
   double* const tmp2 = matrix(d, lds);
   double* const tmp1 = matrix(s, ldd);
-  if (!ok || a2.room() < (size_t)((s + NB - 1) / NB) * NB * NB * sizeof(double)) return STRP_OK;
+  if (!ok || a2.room() < chol_scratch_elems(s) * sizeof(double)) return STRP_OK;
   const size_t room = a2.room() / sizeof(float);
   GemmP p[3] = {nt_plan(operand_for(ctx, STRP_PROD_GRAM, 0, At), operand_for(ctx, STRP_PROD_GRAM, 1, At), s, s, T, 1, room),
                 nt_plan(operand_for(ctx, STRP_PROD_RHS2, 0, in.Y), operand_for(ctx, STRP_PROD_RHS2, 1, At), d, s, T, 0, room),
@@ -928,7 +925,7 @@ size_t strp_workspace_bytes(const strp_module_desc* desc) {
   const long long T = desc->T;
   auto al = [](size_t bytes) { return (bytes + 255) & ~size_t(255); };
   const size_t nmax = km > d ? km : d;
-  const size_t invd_max = ((nmax + NB - 1) / NB) * NB * NB * 8;
+  const size_t invd_max = chol_scratch_elems((long long)nmax) * 8;
   const size_t tilesT = (size_t)((T + 127) / 128);
   const size_t red = al((((f + 127) / 128) * tilesT + f + 4096) * 16);
   // initialisation: weight planes, relu(Z0) planes, H partials
@@ -1338,7 +1335,7 @@ strp_status strp_admm_step(strp_ctx* ctx, const strp_module_desc* desc, strp_mod
       M2f = m2;
     }
     const size_t al = 255;
-    const size_t cbytes = ((nt_partial_elems(d, d, sp, 1) * 4 + al) & ~al) + (((size_t)((d + NB - 1) / NB) * NB * NB * 8 + al) & ~al) +
+    const size_t cbytes = ((nt_partial_elems(d, d, sp, 1) * 4 + al) & ~al) + ((chol_scratch_elems(d) * 8 + al) & ~al) +
                           2 * ((plane_elems(d, d) * 2 + al) & ~al) + 4096;
     STRP_TAKE(ctx, arena, cblock, char, cbytes);
     Arena a2(cblock, cbytes);

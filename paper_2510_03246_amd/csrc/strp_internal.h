@@ -217,8 +217,13 @@ strp_status abs_max(strp_ctx* ctx, const MaxJob* jobs, int n);
 constexpr int NB = 64;  // block order of the factorisation
 // leading dimension of the fp64 work matrices: rows 16-byte aligned whatever the order
 static inline long long f64_ld(long long n) { return (n + 7) & ~7LL; }
+// doubles of scratch of a factorisation: the tiles of two launches that the next panel reads, two each
+static inline size_t chol_scratch_elems(long long n) {
+  const long long tiles = (n + NB - 1) / NB;
+  return (size_t)(tiles < 4 ? tiles : 4) * NB * NB;
+}
 // Linv [n x n, ldv] = L^-1 (upper part zero) of the SPD matrix A [n x n, ld] = L L^T whose lower triangle is given (the
-// caller has added the ridge) and destroyed.  sub: ceil(n / NB) * NB * NB doubles of scratch.  ld and ldv even, A and Linv
+// caller has added the ridge) and destroyed.  sub: chol_scratch_elems(n) doubles of scratch.  ld and ldv even, A and Linv
 // 16-byte aligned.  A pivot that is not positive sets ENOTPD in status (device word).
 strp_status chol_inverse(strp_ctx* ctx, double* A, int n, long long ld, double* sub, double* Linv, long long ldv, int32_t* status);
 // X (L L^T)^-1 = (X Linv^T) Linv for X [m x n] (ldx), as refitted weights; tmp: m x ldx scratch.

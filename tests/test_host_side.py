@@ -146,6 +146,19 @@ def check_least_workspace_of_a_step():
             assert lib.lib.strp_admm_step(lib.h, C.byref(desc), C.byref(st), C.byref(p), None) == strp.OK, (d, f, T, k, ws, lib.lib.strp_last_error(lib.h))
 
 
+def check_workspace_of_a_factorisation():
+    """A factorisation keeps the system, the inverse factor and four tiles of 64 x 64 beside them, whatever its order: with the planes
+    (8 + 8192 rows of 32 tokens, twice 2 bytes), the right-hand side, the solve's other array and the partials of an order of 8192."""
+    lib = Library()
+    n, m = 8192, 8
+    refit = lambda: lib.lib.strp_refit(lib.h, lib.strp.SIDE_FC2, 1 << 50, n, 1.0, None, 0, 1 << 51, lib.strp.F32, 8, 1 << 52, lib.strp.F32, 8, 8,
+                                       1 << 53, n, 1 << 54, m, n)
+    lib.workspace(2 * 8 * n * n + 4 * 64 * 64 * 8 + 65 * 128 * 32 * 4 + 2 * 8 * m * n + 4 * m * n + 4096)
+    assert refit() == lib.strp.OK, lib.lib.strp_last_error(lib.h)
+    lib.workspace(2 * 8 * n * n)
+    assert refit() == lib.strp.ENOMEM
+
+
 def check_cached_factor_needs_no_alignment():
     """cholH is an array of doubles like any other, in exactly the workspace asked for."""
     lib = Library()
@@ -322,7 +335,7 @@ def check_weight_statistics_counter():
     assert counter(lib.h) not in (0, a, b, c)
 
 
-CHECKS = [check_weight_statistics_counter, check_weight_statistics_without_a_counter, check_what_the_gram_matrices_cover, check_what_the_large_systems_cover, check_selection_of_a_very_wide_module, check_weight_statistics_arguments, check_weight_statistics_workgroups, check_chains, check_workspace_of_a_module, check_least_workspace_of_a_step, check_cached_factor_needs_no_alignment]
+CHECKS = [check_weight_statistics_counter, check_weight_statistics_without_a_counter, check_what_the_gram_matrices_cover, check_what_the_large_systems_cover, check_selection_of_a_very_wide_module, check_weight_statistics_arguments, check_weight_statistics_workgroups, check_chains, check_workspace_of_a_module, check_least_workspace_of_a_step, check_workspace_of_a_factorisation, check_cached_factor_needs_no_alignment]
 
 
 @pytest.fixture(scope="session")
