@@ -343,9 +343,6 @@ __device__ __forceinline__ double rsqrt_f64(double d) {
   y = y * (1.5 - 0.5 * d * y * y);
   return y;
 }
-// lane L of every 16-lane row, to that row's lanes
-template <int L>
-__device__ __forceinline__ double row_bcast(double x) { return __builtin_amdgcn_mov_dpp(x, 0x150 + L, 0xf, 0xf, true); }
 
 constexpr int F64_IMG = NB * (NB + 4);    // doubles of the larger image of a 64 x 64 tile
 constexpr int SL = NB + 1;                // pitch of the square working tiles of the diagonal block

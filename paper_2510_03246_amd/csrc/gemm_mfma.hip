@@ -22,25 +22,18 @@
 
 namespace strp {
 
-// Tile shapes (WT = 32x32 MFMA tiles per wavefront per dimension):
-//   WT = 2: 128x128 block (one panel per operand), K tile 64, two blocks per CU
-//   WT = 4: 256x256 block (two panels per operand), K tile 32, one block per CU
-template <int WT>
-struct Tile {
-  static constexpr int ROWS = 64 * WT;             // rows of P and columns of Q per block
-  static constexpr int BK = WT == 2 ? 64 : 32;
-  static constexpr int G = BK / 8;                 // k-groups per K tile
-  static constexpr int PANS = ROWS / 128;
-  static constexpr int NCH = ROWS * G / 256;       // 16-byte chunks per thread per plane per K tile (= 4)
-  static constexpr int GSTEP = 256 / ROWS;         // k-groups covered by one pass of the block's threads (2 or 1)
-};
+// The 128x128 tile: one panel per operand, K tile 64, two blocks per CU.  (256x256 ones: gemm_dma.hip.)
+constexpr int ROWS = 128;               // rows of P and columns of Q per block
+constexpr int BK = 64;
+constexpr int NCH = ROWS * BK / 8 / 256; // 16-byte chunks per thread per plane per K tile
+constexpr int GSTEP = 256 / ROWS;       // k-groups covered by one pass of the block's threads
+constexpr int WT = 2;                   // 32x32 MFMA tiles per wavefront per dimension
 
-// Operand tile loader: thread t owns row t % 128 of panel (t / 128) % PANS and k-groups g0 + GSTEP * i.
+// Operand tile loader: thread t owns row t % 128 of the panel and k-groups t / 128 + GSTEP * i.
 // Loads are unconditional (panel clamped to the last one, k-groups past the end read group 0 and are zeroed
 // by select) and pointers advance by one K tile per iteration.
-template <int NP, int WT>
+template <int NP>
 struct PlaneLoader {
-  static constexpr int NCH = Tile<WT>::NCH, BK = Tile<WT>::BK, ROWS = Tile<WT>::ROWS, GSTEP = Tile<WT>::GSTEP;
   const unsigned short* bp[NP];     // chunk (group of the next tile + g0, this thread's row)
   const unsigned short* safe[NP];   // same row, group 0
   uint4 r[NP][NCH];
@@ -50,10 +43,9 @@ struct PlaneLoader {
   __device__ __forceinline__ void init(const PlaneOp& op, int row0, long long k0) {
     const int t = threadIdx.x;
     const int rr = t & 127;
-    const int q = t >> 7;
-    int pan = (row0 >> 7) + (Tile<WT>::PANS == 2 ? q : 0);
+    const int g0 = t >> 7;
+    int pan = row0 >> 7;
     pan = pan < op.npan ? pan : op.npan - 1;
-    const int g0 = Tile<WT>::PANS == 2 ? 0 : q;
     gnext = (k0 >> 3) + g0;
     const long long base = ((long long)pan * op.kg * 128 + rr) * 8;
     bp[0] = op.hi + base + gnext * 1024;
@@ -62,7 +54,7 @@ struct PlaneLoader {
       bp[NP - 1] = op.lo + base + gnext * 1024;
       safe[NP - 1] = op.lo + base;
     }
-    lds_off = (g0 * ROWS + (Tile<WT>::PANS == 2 ? q * 128 : 0) + rr) * 8;
+    lds_off = (g0 * ROWS + rr) * 8;
   }
   __device__ __forceinline__ void load(long long g_end) {
 #pragma unroll
@@ -90,9 +82,9 @@ __device__ __forceinline__ floatx16 mma(uint4 a, uint4 b, floatx16 c) {
   return __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(half8, a), __builtin_bit_cast(half8, b), c, 0, 0, 0);
 }
 
-template <int NPP, int NPQ, int WT>
-__global__ __launch_bounds__(256, WT == 4 ? 1 : 2) void gemm_kernel(const GemmP p) {
-  constexpr int ROWS = Tile<WT>::ROWS, BK = Tile<WT>::BK, KS = BK / 16;
+template <int NPP, int NPQ>
+__global__ __launch_bounds__(256, 2) void gemm_tile_kernel(const GemmP p) {
+  constexpr int KS = BK / 16;
   __shared__ __attribute__((aligned(16))) unsigned short sP[NPP][ROWS * BK];
   __shared__ __attribute__((aligned(16))) unsigned short sQ[NPQ][ROWS * BK];
   __shared__ double sred[4][2];
@@ -111,9 +103,9 @@ __global__ __launch_bounds__(256, WT == 4 ? 1 : 2) void gemm_kernel(const GemmP 
   const int wm = wave >> 1, wn = wave & 1;
   constexpr int WROWS = 32 * WT;   // rows (and columns) of the output owned by one wavefront
 
-  PlaneLoader<NPP, WT> lp;
+  PlaneLoader<NPP> lp;
   lp.init(p.P, m0, k0);
-  PlaneLoader<NPQ, WT> lq;
+  PlaneLoader<NPQ> lq;
   lq.init(p.Q, n0, k0);
 
   floatx16 acc[WT][WT];
@@ -415,7 +407,7 @@ static void launch_one(strp_ctx* ctx, const GemmP& p) {
   else if (p.wt == 1)
     hipLaunchKernelGGL((gemm_kernel<NPP, NPQ>), dim3(gemm_grid_blocks(p)), dim3(128), 0, ctx->stream, p);
   else
-    hipLaunchKernelGGL((gemm_kernel<NPP, NPQ, 2>), dim3(gemm_grid_blocks(p)), dim3(256), 0, ctx->stream, p);
+    hipLaunchKernelGGL((gemm_tile_kernel<NPP, NPQ>), dim3(gemm_grid_blocks(p)), dim3(256), 0, ctx->stream, p);
 }
 
 static strp_status check_gemm(strp_ctx* ctx, const GemmP& p) {

@@ -59,7 +59,7 @@ class Library:
 
 def splits_of(launches, M, N):
     """tile rows (128 or 256) and K splits of the one token-contraction product among the launches"""
-    (name, grid), = [x for x in launches if "gemm_dma_kernel" in x[0] or "11gemm_kernel" in x[0]]
+    (name, grid), = [x for x in launches if "gemm_dma_kernel" in x[0] or "gemm_tile_kernel" in x[0] or "11gemm_kernel" in x[0]]
     tile = 256 if "gemm_dma" in name else 128
     tm, tn = -(-M // tile), -(-N // tile)
     tiles = tm * (tm + 1) // 2 if M == N else tm * tn
