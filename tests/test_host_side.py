@@ -58,11 +58,14 @@ class Library:
 
 
 def splits_of(launches, M, N):
-    """tile rows (128 or 256) and K splits of the one token-contraction product among the launches"""
+    """tile rows (128 or 256) and K splits of the one token-contraction product among the launches; a small one's tiles of 128 are
+    cut into 64 x 64 blocks"""
     (name, grid), = [x for x in launches if "gemm_dma_kernel" in x[0] or "gemm_tile_kernel" in x[0] or "11gemm_kernel" in x[0]]
     tile = 256 if "gemm_dma" in name else 128
     tm, tn = -(-M // tile), -(-N // tile)
     tiles = tm * (tm + 1) // 2 if M == N else tm * tn
+    if "11gemm_kernel" in name:
+        tiles *= (2 if M > 64 else 1) * (2 if N > 64 else 1)
     assert grid[0] % tiles == 0
     return tile, grid[0] // tiles
 
