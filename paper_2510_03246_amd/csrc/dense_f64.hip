@@ -1214,9 +1214,12 @@ static void solve_products(const SolveIn& in, DgemmP (&p)[2]) {
   p[1].w = in.out;
 }
 
+// algorithmic bytes of a solve: L^-1 once, X and the result of either product written and read once
+static double solve_bytes(int m, int n) { return 8.0 * ((double)n * n + 4.0 * (double)m * n); }
+
 strp_status apply_inverse_right(strp_ctx* ctx, const double* Linv, int n, long long ldl, const double* X, int m, long long ldx, double* tmp,
                                 const WeightsOut& out) {
-  ProfScope ps(ctx, "chol_solve_f64", 2.0 * (double)m * n * n, 8.0 * ((double)n * n + 4.0 * (double)m * n));
+  ProfScope ps(ctx, "chol_solve_f64", 2.0 * (double)m * n * n, solve_bytes(m, n));
   DgemmP p[2];
   solve_products(SolveIn{Linv, n, ldl, X, m, ldx, tmp, out}, p);
   STRP_TRY((dgemm_launch<true, true>(ctx, p[0])));
@@ -1230,7 +1233,7 @@ bool solve_is_small(int m, int n) {
 }
 strp_status apply_inverse_right_pair(strp_ctx* ctx, const SolveIn& a, const SolveIn& b) {
   if (!solve_is_small(a.m, a.n) || !solve_is_small(b.m, b.n)) return fail(ctx, STRP_EINVAL, "two solves in one launch: not small");
-  ProfScope ps(ctx, "chol_solve_f64", 2.0 * ((double)a.m * a.n * a.n + (double)b.m * b.n * b.n), 0.0);
+  ProfScope ps(ctx, "chol_solve_f64", 2.0 * ((double)a.m * a.n * a.n + (double)b.m * b.n * b.n), solve_bytes(a.m, a.n) + solve_bytes(b.m, b.n));
   DgemmP p[2], q[2];
   solve_products(a, p);
   solve_products(b, q);

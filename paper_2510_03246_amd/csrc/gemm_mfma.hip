@@ -421,13 +421,10 @@ static strp_status check_gemm(strp_ctx* ctx, const GemmP& p) {
   return STRP_OK;
 }
 
-strp_status launch_gemm(strp_ctx* ctx, GemmP& p) {
-  STRP_TRY(check_gemm(ctx, p));
+// algorithmic operations and bytes of a product: operand planes once, outputs (and what an epilogue reads beside them) once
+struct GemmWork { double flops, bytes; };
+static GemmWork gemm_work(const GemmP& p) {
   const int npp = p.P.lo ? 2 : 1, npq = p.Q.lo ? 2 : 1;
-  static const char* const epi_names[] = {"partial", "store", "initz", "resid", "aupd", "zupd"};
-  static char names[3][3][6][40];
-  char* name = names[npp][npq][p.epi];
-  if (!name[0]) snprintf(name, 40, "gemm_h%dx%d_%s", npp, npq, epi_names[p.epi]);
   const double mn = p.triangle ? 0.5 * (double)p.M * ((double)p.M + 1.0) : (double)p.M * (double)p.N;
   static const double out_words[] = {1.0, 1.0, 3.0, 2.0, 2.0, 2.0};
   double obytes = 4.0 * out_words[p.epi] * (double)p.M * (double)p.N * (p.epi == EPI_PARTIAL ? (double)p.splits : 1.0);
@@ -435,7 +432,18 @@ strp_status launch_gemm(strp_ctx* ctx, GemmP& p) {
   if (p.k8_hi) obytes += (p.k8_lo ? 4.0 : 2.0) * (double)p.M * (double)p.N;
   const double ibytes = p.triangle ? 2.0 * npp * (double)p.M * (double)p.K
                                    : 2.0 * npp * (double)p.M * (double)p.K + 2.0 * npq * (double)p.N * (double)p.K;
-  ProfScope ps(ctx, name, 2.0 * mn * (double)p.K, ibytes + obytes);
+  return {2.0 * mn * (double)p.K, ibytes + obytes};
+}
+
+strp_status launch_gemm(strp_ctx* ctx, GemmP& p) {
+  STRP_TRY(check_gemm(ctx, p));
+  const int npp = p.P.lo ? 2 : 1, npq = p.Q.lo ? 2 : 1;
+  static const char* const epi_names[] = {"partial", "store", "initz", "resid", "aupd", "zupd"};
+  static char names[3][3][6][40];
+  char* name = names[npp][npq][p.epi];
+  if (!name[0]) snprintf(name, 40, "gemm_h%dx%d_%s", npp, npq, epi_names[p.epi]);
+  const GemmWork work = gemm_work(p);
+  ProfScope ps(ctx, name, work.flops, work.bytes);
   if (p.k8_hi && (p.M + 7) / 8 < p.k8_kg) {
     const int npan = (p.N + 127) / 128;
     hipLaunchKernelGGL(zero_pad_group_kernel, dim3((npan * 128 + 255) / 256), dim3(256), 0, ctx->stream, p.k8_hi, p.k8_lo, p.k8_kg,
@@ -463,17 +471,19 @@ strp_status launch_gemm_group(strp_ctx* ctx, GemmP* p, int n) {
   }
   GemmGroup g;
   int blocks = 0;
-  double flops = 0.0;
+  GemmWork work{0.0, 0.0};
   for (int i = 0; i < 3; ++i) {
     g.p[i] = p[i < n ? i : 0];
     if (i < n) {
       STRP_TRY(check_gemm(ctx, p[i]));
       blocks += gemm_grid_blocks(p[i]);
-      flops += 2.0 * (double)p[i].K * p[i].M * p[i].N * (p[i].triangle ? 0.5 : 1.0);
+      const GemmWork w = gemm_work(p[i]);
+      work.flops += w.flops;
+      work.bytes += w.bytes;
     }
     g.end[i] = blocks;
   }
-  ProfScope ps(ctx, "gemm_group", flops, 0.0);
+  ProfScope ps(ctx, "gemm_group", work.flops, work.bytes);
   hipLaunchKernelGGL(gemm_group_kernel, dim3(blocks), dim3(128), 0, ctx->stream, g);
   STRP_HIP(ctx, hipGetLastError());
   return STRP_OK;
@@ -576,11 +586,14 @@ __global__ __launch_bounds__(256) void splitk_reduce_group_kernel(const ReduceGr
   splitk_reduce_block(r, b % nx, b / nx, nx);
 }
 
+// algorithmic bytes: the partials (of a symmetric product half of them) once, the results once
+static double reduce_bytes(const ReduceP& r) {
+  return (double)r.M * r.N * (4.0 * (double)r.splits * (r.triangle ? 0.5 : 1.0) + (r.outf ? 4.0 : 0.0) + (r.outd ? 8.0 : 0.0));
+}
 strp_status launch_splitk_reduce(strp_ctx* ctx, const ReduceP& r) {
-  const double tot = (double)r.M * r.N;
   if (r.triangle && r.M != r.N) return fail(ctx, STRP_EINVAL, "split-K reduce: a symmetric product must be square");
   if (r.dot && !r.triangle) return fail(ctx, STRP_EINVAL, "split-K reduce: the inner product is for symmetric products");
-  ProfScope ps(ctx, "splitk_reduce", 0.0, 4.0 * tot * (double)r.splits * (r.triangle ? 0.5 : 1.0) + (r.outf ? 4.0 : 0.0) * tot + (r.outd ? 8.0 : 0.0) * tot);
+  ProfScope ps(ctx, "splitk_reduce", 0.0, reduce_bytes(r));
   hipLaunchKernelGGL(splitk_reduce_kernel, dim3((r.N + REDUCE_TILE_N - 1) / REDUCE_TILE_N, (r.M + REDUCE_TILE_M - 1) / REDUCE_TILE_M), dim3(256), 0, ctx->stream, r);
   STRP_HIP(ctx, hipGetLastError());
   return STRP_OK;
@@ -594,7 +607,7 @@ strp_status launch_splitk_reduce_group(strp_ctx* ctx, const ReduceP* r, int n) {
     g.r[i] = r[i < n ? i : 0];
     if (i < n) {
       blocks += reduce_blocks(r[i].M, r[i].N);
-      bytes += 4.0 * (double)r[i].M * r[i].N * (r[i].splits + 2);
+      bytes += reduce_bytes(r[i]);
     }
     g.end[i] = blocks;
   }

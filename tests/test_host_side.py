@@ -149,6 +149,47 @@ def check_least_workspace_of_a_step():
             assert lib.lib.strp_admm_step(lib.h, C.byref(desc), C.byref(st), C.byref(p), None) == strp.OK, (d, f, T, k, ws, lib.lib.strp_last_error(lib.h))
 
 
+def _step_records(lib, d, f, T, k, ws, stages=0):
+    """What one iteration enqueues on a workspace of ws bytes: [(class, algorithmic flops, algorithmic bytes)] and the kernels' names"""
+    strp = lib.strp
+    ld = (T + 7) // 8 * 8
+    desc = strp.ModuleDesc(d, f, T, ld, ld, strp.F32, strp.F32, k)
+    st = strp.ModuleState()
+    for name, kind in strp.ModuleState._fields_:
+        if kind is C.c_void_p:
+            setattr(st, name, 1 << 50)
+    p = strp.Params(1.0, 1.0, 0.01, strp.GAIN, 1, k, 0)
+    lib.workspace(1 << 50)
+    assert lib.lib.strp_module_init(lib.h, C.byref(desc), C.byref(st), C.byref(p)) == strp.OK
+    lib.workspace(ws)
+    assert lib.lib.strp_profile_enable(lib.h, 1) == strp.OK
+    p.stages = stages
+    status, launches = lib.launches(lambda: lib.lib.strp_admm_step(lib.h, C.byref(desc), C.byref(st), C.byref(p), None))
+    assert status == strp.OK
+    buf, n = (strp.ProfileEntry * 4096)(), C.c_int32(0)
+    assert lib.lib.strp_profile_launches(lib.h, buf, 4096, C.byref(n)) == strp.OK
+    assert lib.lib.strp_profile_enable(lib.h, 0) == strp.OK
+    names = subprocess.run(["c++filt"], input="\n".join(x[0] for x in launches), check=True, capture_output=True, text=True).stdout.split("\n")
+    return [(buf[i].name.decode(), buf[i].flops, buf[i].bytes) for i in range(n.value)], names
+
+
+def check_work_of_shared_launches():
+    """The records of a launch that several products share carry the work of all of them: an iteration's operations and bytes are the
+    same where the workspace just does not hold what both refits need at a time."""
+    lib = Library()
+    for d, f, T, k, least, _ in (LEAST[0], LEAST[3]):
+        ws = 4 * least
+        shared = apart = _step_records(lib, d, f, T, k, ws)[0]
+        while len(apart) == len(shared) and ws > least:
+            ws -= 4096
+            apart = _step_records(lib, d, f, T, k, ws)[0]
+        solves = [sum(r[0] == "chol_solve_f64" for r in records) for records in (shared, apart)]
+        assert solves == [1, 2], (d, f, T, k, ws)
+        for q in (1, 2):
+            a, b = (sum(r[q] for r in records) for records in (shared, apart))
+            assert abs(a - b) <= 1e-12 * b, (d, f, T, k, q, a, b)
+
+
 def check_workspace_of_a_factorisation():
     """A factorisation keeps the system, the inverse factor and four tiles of 64 x 64 beside them, whatever its order: with the planes
     (8 + 8192 rows of 32 tokens, twice 2 bytes), the right-hand side, the solve's other array and the partials of an order of 8192."""
@@ -338,7 +379,7 @@ def check_weight_statistics_counter():
     assert counter(lib.h) not in (0, a, b, c)
 
 
-CHECKS = [check_weight_statistics_counter, check_weight_statistics_without_a_counter, check_what_the_gram_matrices_cover, check_what_the_large_systems_cover, check_selection_of_a_very_wide_module, check_weight_statistics_arguments, check_weight_statistics_workgroups, check_chains, check_workspace_of_a_module, check_least_workspace_of_a_step, check_workspace_of_a_factorisation, check_cached_factor_needs_no_alignment]
+CHECKS = [check_weight_statistics_counter, check_weight_statistics_without_a_counter, check_what_the_gram_matrices_cover, check_what_the_large_systems_cover, check_selection_of_a_very_wide_module, check_weight_statistics_arguments, check_weight_statistics_workgroups, check_chains, check_workspace_of_a_module, check_least_workspace_of_a_step, check_work_of_shared_launches, check_workspace_of_a_factorisation, check_cached_factor_needs_no_alignment]
 
 
 @pytest.fixture(scope="session")
