@@ -258,7 +258,7 @@ def main():
     tokens_per_s = cfg.T * args.steps / dt
     # dominant kernel class by time inside the timed region (HIP events on the library's stream)
     dom_name, dom = max(prof.items(), key=lambda kv: kv[1]["ms"])
-    is_gemm = dom_name.startswith("gemm")
+    is_gemm = dom_name.startswith("gemm_h")
     avg_ms = dom["ms"] / dom["launches"]
     traffic, traffic_note = measured_traffic(args.workload, dom_name)
     if is_gemm:

@@ -33,8 +33,11 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 
 # kernels whose every launch belongs to one class of the library's records
-KERNEL_CLASS = {"pruned_rows_kernel": "pruned_rows", "split_t_kernel": "split_act", "split_c_kernel": "split_act",
-                "row_sums_kernel": "row_sums", "plane_c_to_t_kernel": "plane_c_to_t", "splitk_reduce_kernel": "splitk_reduce"}
+KERNEL_CLASS = {"pruned_rows_kernel": "pruned_rows", "split_t_kernel": "split_act", "split_t_pair_kernel": "split_act", "split_c_kernel": "split_act",
+                "row_sums_kernel": "row_sums", "plane_c_to_t_kernel": "plane_c_to_t", "splitk_reduce_kernel": "splitk_reduce",
+                "splitk_reduce_group_kernel": "splitk_reduce"}
+# kernels that run the fp16 products: one launch of one of them per record of a class gemm_*
+GEMM_KERNELS = ("gemm_dma_kernel", "gemm_tile_kernel", "gemm_kernel", "gemm_group_kernel")
 
 
 # how the counters accumulate over the chip: SQ_BUSY_CYCLES once per shader engine, SQ_VALU_MFMA_BUSY_CYCLES once per
@@ -74,7 +77,7 @@ def load_counters(directory: str):
 
 
 def is_gemm(name: str) -> bool:
-    return "strp::gemm_dma_kernel" in name or "strp::gemm_kernel" in name
+    return any(f"strp::{kernel}" in name for kernel in GEMM_KERNELS)
 
 
 def classify(dispatches, launches):

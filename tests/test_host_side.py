@@ -190,6 +190,27 @@ def check_work_of_shared_launches():
             assert abs(a - b) <= 1e-12 * b, (d, f, T, k, q, a, b)
 
 
+def check_profile_classes():
+    """The kernels of an iteration in their order and the library's records of them, as the profile's tables are made from: every
+    product's launch gets its own record, whichever kernel runs it, and what else has a class gets that."""
+    lib = Library()
+    from paper_2510_03246_amd import profile_summary as ps
+    ran = set()
+    for d, f, T, k in [(64, 256, 512, 128), (720, 1440, 1000, 720), (768, 3072, 16384, 1536), (1000, 2312, 3001, 1013), (4096, 16384, 131072, 4915)]:
+        records, names = _step_records(lib, d, f, T, k, 1 << 50)
+        classes = [r[0] for r in records]
+        products = [c for c in classes if c.startswith("gemm_")]
+        dispatches = [dict(name=ps.short_name(n)) for n in names if n]
+        assert sum(ps.is_gemm(x["name"]) for x in dispatches) == len(products)
+        ps.classify(dispatches, classes)
+        assert [x["cls"] for x in dispatches if ps.is_gemm(x["name"])] == products
+        assert all(("gemm_group_kernel" in x["name"]) == (x["cls"] == "gemm_group") for x in dispatches if ps.is_gemm(x["name"]))
+        for cls in ("split_act", "splitk_reduce", "plane_c_to_t"):
+            assert sum(x.get("cls") == cls for x in dispatches) == classes.count(cls), (d, cls)
+        ran |= {g for g in ps.GEMM_KERNELS for x in dispatches if f"strp::{g}" in x["name"]}
+    assert ran == set(ps.GEMM_KERNELS), ran
+
+
 def check_workspace_of_a_factorisation():
     """A factorisation keeps the system, the inverse factor and four tiles of 64 x 64 beside them, whatever its order: with the planes
     (8 + 8192 rows of 32 tokens, twice 2 bytes), the right-hand side, the solve's other array and the partials of an order of 8192."""
@@ -379,7 +400,7 @@ def check_weight_statistics_counter():
     assert counter(lib.h) not in (0, a, b, c)
 
 
-CHECKS = [check_weight_statistics_counter, check_weight_statistics_without_a_counter, check_what_the_gram_matrices_cover, check_what_the_large_systems_cover, check_selection_of_a_very_wide_module, check_weight_statistics_arguments, check_weight_statistics_workgroups, check_chains, check_workspace_of_a_module, check_least_workspace_of_a_step, check_work_of_shared_launches, check_workspace_of_a_factorisation, check_cached_factor_needs_no_alignment]
+CHECKS = [check_weight_statistics_counter, check_weight_statistics_without_a_counter, check_what_the_gram_matrices_cover, check_what_the_large_systems_cover, check_selection_of_a_very_wide_module, check_weight_statistics_arguments, check_weight_statistics_workgroups, check_chains, check_workspace_of_a_module, check_least_workspace_of_a_step, check_work_of_shared_launches, check_profile_classes, check_workspace_of_a_factorisation, check_cached_factor_needs_no_alignment]
 
 
 @pytest.fixture(scope="session")
