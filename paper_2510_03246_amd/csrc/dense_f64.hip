@@ -1226,8 +1226,11 @@ strp_status apply_inverse_right(strp_ctx* ctx, const double* Linv, int n, long l
   return dgemm_launch<true, false>(ctx, p[1]);
 }
 
-// Two solves side by side pay where each has less than a workgroup a compute unit: one takes as long as the longest tile then
-// (64 x 128 beside 128 x 64: 15.8 + 13.5 us one after the other, 17.4 together).
+// Two solves side by side pay where each has no more than a workgroup a compute unit: one takes as long as the longest tile then
+// (64 x 128 beside 128 x 64: 15.8 + 13.5 us one after the other, 17.4 together).  A whole step, the solves apart / together,
+// d x kept units (tiles of either): 64 x 128 182 / 174 us;  256 x 512 (64) 364 / 345;  384 x 768 (144) 478 / 456;  512 x 512 (128) 445 / 416;
+// 64 x 1000 (32) 434 / 423;  512 x 1000 (256) 607 / 583.  The line is where this argument ends and not
+// the gain: 720 x 720 (276) 615 / 592, 768 x 1000 (384) 696 / 661, 1000 x 1000 (512) 800 / 773 if it were further up.
 bool solve_is_small(int m, int n) {
   return dgemm_tile(m, n, 0).tn == 32 && dgemm_blocks(m, n, {64, 32}) <= 256;
 }

@@ -343,7 +343,7 @@ __device__ __forceinline__ void epilogue16(const GemmP& p, floatx4 (&acc)[8][4],
 // l % 16: four consecutive tokens, so that state tensors and partials move 16 bytes per lane.  A tile's row is 64 bytes;
 // exchanging the upper eight rows of a tile with the lower eight of its right-hand neighbour (one row_ror:8 move per
 // register) makes it 128 bytes of eight rows per instruction.  A lane then has rows l % 8 and l % 8 + 8 of each tile row, so a
-// row's address is formed once for 64 columns and its sums over the columns are three additions and two lane swaps.
+// row's address is formed once for 64 columns and its sums over them are three levels of pairs in the lane and three across lanes.
 // The loads of up to four tile rows are under way while one is computed and stored.
 typedef float floatx4u __attribute__((ext_vector_type(4), aligned(4)));      // a partial's rows begin at any multiple of four bytes
 

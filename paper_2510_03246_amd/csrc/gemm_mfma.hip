@@ -319,7 +319,10 @@ __device__ __forceinline__ void gemm_small_block(const GemmP& p, int block, int 
 template <int NPP, int NPQ>
 __global__ __launch_bounds__(128) void gemm_kernel(const GemmP p) { gemm_small_block<NPP, NPQ, false>(p, blockIdx.x, gridDim.x); }
 
-// up to three independent products, one behind the other in the grid: end[i] workgroups up to and with product i
+// up to three independent products, one behind the other in the grid: end[i] workgroups up to and with product i.  One kernel
+// for all combinations of planes: an operand of one plane is loaded twice, the second time for nothing, which a small product has
+// room for (all operands of one plane, us a step with a launch for either product of the fc2 refit / one for both: 64 x 128 over
+// 512 tokens 208 / 201, 256 x 512 over 2048 389 / 382, 512 x 1000 over 1024 600 / 597; with two planes 213 / 206, 407 / 399, 629 / 622).
 struct GemmGroup {
   GemmP p[3];
   int end[3];

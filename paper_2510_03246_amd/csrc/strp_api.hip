@@ -819,6 +819,10 @@ static strp_status ridge_solve(strp_ctx* ctx, Arena& arena, const RefitIn& in, c
 
 // Both refits of a small module: their products, reductions and solves are independent of each other, and each leaves most of the
 // chip idle, so they share launches: 26 instead of 32 in an iteration of a 64 x 256 module over 512 tokens, 218 -> 190 us.
+// One refit after the other / both together, us a step of d x kept units over the tokens, fp32 inputs:  64 x 128, 512 206 / 174;
+// 128 x 256, 2048 281 / 248;  200 x 400, 1500 380 / 339;  256 x 512, 2048 399 / 355;  512 x 512, 512 463 / 416;  512 x 1000, 1024 622 / 583;
+// 64 x 1000, 512 456 / 423;  768 x 600, 768 596 / 553.  The same with bf16 inputs, and 4 to 12 % with one plane per operand.  More tokens
+// have products that fill the chip by themselves (gemm_is_small): 256 x 512, 8192 take them one by one.
 // Y, X: the cached planes; Linv1: the inverse factor of the fc1 system.
 struct RefitsIn {
   const float* A; const float* Z; long long lda; const int* idx;
