@@ -293,15 +293,18 @@ __global__ __launch_bounds__(256, 2) void dgemm_pair_kernel(const DgemmPair g) {
 // Tile of a product by its grid: 128 x 128 tiles read the fewest operand bytes per flop but need enough of them to fill
 // the chip; below that the longest tile (whole K) sets the run time and a smaller one ends sooner.  Solves X (L L^T)^-1 of
 // m x n (two products), us with 64 x 32 / 64 x 64 / 128 x 128 tiles (in brackets the tiles of 64, of 128):
-//   768 x 1536 (288) 104 / 139 / 433;  2048 x 2048 (1024) 296 / 312 / 573;  2200 x 2200 (1225) 429 / 398 / 698;
-//   2304 x 2304 (1296) 400 / 417 / 726;  2496 x 2496 (1521) 591 / 521 / 861;  2048 x 3277 (1664) 717 / 726 / 1144;
-//   3000 x 3000 (2209, 576) 1059 / 888 / 1161;  4096 x 4096 (4096, 1024) 2174 / 2119 / 2240;  4096 x 4915 (4928, 1248)
-//   3192 / 3070 / 3088, 65 TFLOP/s;  4864 x 4864 (5776, 1444) 3657 / 3528 / 3528;  5120 x 5120 (6400, 1600) 4219 / 4139 / 4059;
-//   6000 x 6000 (8836, 2209) 7783 / 6968 / 6479;  8602 x 7168 (15120, 3808) 16774 / 14895 / 13089.
-// From 1000 to 1700 tiles of 64 the 64 x 32 one is up to 5 % faster or 12 % slower, as its last round of workgroups fills.
+//   768 x 1536 (288) 104 / 139 / 433;  3000 x 3000 (2209, 576) 1059 / 888 / 1161;  4096 x 4096 (4096, 1024) 2174 / 2119 / 2240;
+//   4096 x 4915 (4928, 1248) 3192 / 3070 / 3088, 65 TFLOP/s;  4864 x 4864 (5776, 1444) 3657 / 3528 / 3528;  5120 x 5120 (6400, 1600)
+//   4219 / 4139 / 4059;  6000 x 6000 (8836, 2209) 7783 / 6968 / 6479;  8602 x 7168 (15120, 3808) 16774 / 14895 / 13089.
+// Between the two small ones the number of tile rows decides: workgroups go to the 8 XCDs in turn, so that with an even number an
+// XCD meets only some rows of A, again and again, and with an odd one all of them, which costs the tile that reads A for fewer
+// columns.  64 x 32 / 64 x 64, even: 1656 x 2688 (1092) 399 / 407;  2048 x 2458 (1248) 393 / 414;  3072 x 2048 (1536) 406 / 425;
+// 3277 x 2048 (1664) 442 / 455;  2048 x 3277 686 / 703;  2680 x 2880 (1890) 725 / 717;  3448 x 2624 (2214) 814 / 766.  Odd: 1088 x 1656 (442)
+// 135 / 164;  1344 x 1848 (609) 199 / 200;  1728 x 1656 (702) 202 / 189;  2880 x 1144 (810) 160 / 163;  2112 x 2112 (1089) 358 / 328;
+// 2496 x 2496 (1521) 590 / 517;  2880 x 2880 (2025) 887 / 763.
 // Linv^T Linv (half the tiles, order):  2600 (840) 162 / 158 / 361;  3000 (1104) 249 / 260 / 494;  3400 (1458) 361 / 284 / 616;
 // 6000 (4418, 1104) 1765 / 1328 / 1743;  8192 (8192, 2048) 4195 / 3212 / 3335;  10240 (12800, 3200) 8134 / 6575 / 5665.
-constexpr int DGEMM_T128 = 1450, DGEMM_T128_LOWER = 2500, DGEMM_T64 = 1200;
+constexpr int DGEMM_T128 = 1450, DGEMM_T128_LOWER = 2500, DGEMM_T64 = 2000, DGEMM_T64_ODD = 680, DGEMM_T64_LOWER = 1200;
 
 static inline bool aligned_vec(const void* p, long long ld) { return ((uintptr_t)p & 15u) == 0 && (ld & 1) == 0; }
 
@@ -309,7 +312,8 @@ struct DgemmTile { int tm, tn; };
 static DgemmTile dgemm_tile(int M, int N, int lower) {
   auto tiles = [&](int tm, int tn) { return (long long)((M + tm - 1) / tm) * ((N + tn - 1) / tn) / (lower ? 2 : 1); };
   if (tiles(128, 128) >= (lower ? DGEMM_T128_LOWER : DGEMM_T128)) return {128, 128};
-  return tiles(64, 64) >= DGEMM_T64 ? DgemmTile{64, 64} : DgemmTile{64, 32};
+  const int t64 = lower ? DGEMM_T64_LOWER : (M + 63) / 64 % 2 ? DGEMM_T64_ODD : DGEMM_T64;
+  return tiles(64, 64) >= t64 ? DgemmTile{64, 64} : DgemmTile{64, 32};
 }
 static int dgemm_blocks(int M, int N, DgemmTile t) { return ((M + t.tm - 1) / t.tm) * ((N + t.tn - 1) / t.tn); }
 int weights_out_blocks(int m, int n) { return dgemm_blocks(m, n, dgemm_tile(m, n, 0)); }
