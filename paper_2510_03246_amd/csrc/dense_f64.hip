@@ -1192,14 +1192,13 @@ strp_status chol_inverse(strp_ctx* ctx, double* A, int n, long long ld, double* 
   for (int t = 0; t < p.N; ++t) {
     p.t = t;
     const int m = p.N - 1 - t;
-    // up to three tiles each, so that a launch of a small system leaves the critical workgroup a CU of its own; beyond 512
-    // tiles the launch is theirs and a workgroup that takes several only ends later.  One tile each / up to three below 512 / up to
-    // three below 1024, us for the whole chain: n = 1536 341 / 323 / 325, 2048 517 / 509 / 512, 2458 654 / 639 / 683,
+    // up to three tiles each, so that a launch of a small system leaves the critical workgroup a CU of its own; beyond 576
+    // tiles the launch is theirs and a workgroup that takes several only ends later.  One tile each / up to three below 577 / up to
+    // three below 1025, us for the whole chain: n = 1536 341 / 323 / 325, 2048 517 / 509 / 512, 2458 654 / 639 / 683,
     // 3277 1107 / 1092 / 1167, 4096 1851 / 1835 / 1876
     const int total = step_tiles(p.N, t);
     p.each = (total + 191) / 192;
-    if (p.each > 3) p.each = total > 512 ? 1 : 3;
-    if (p.each < 1) p.each = 1;
+    if (p.each > 3 || p.each < 1) p.each = 1;
     const int blocks = m + (m > 1 ? 2 : 0) + t + (total + p.each - 1) / p.each;
     if (blocks > 0) hipLaunchKernelGGL(chol_step_kernel, dim3(blocks), dim3(256), 0, ctx->stream, p);      // none: a single tile, the first launch was all
   }

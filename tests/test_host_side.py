@@ -330,7 +330,7 @@ def check_what_the_gram_matrices_cover():
 
 def check_what_the_large_systems_cover():
     """The three tiles of the fp64 products, the factorisation's launches with one, two and three trailing tiles per workgroup, and
-    those of more than 1024 trailing tiles."""
+    those of more than 576 trailing tiles, which are back at one."""
     lib = Library()
     tiles, each, long = set(), set(), False
     for n, m in LARGE_SYSTEMS:
@@ -344,9 +344,11 @@ def check_what_the_large_systems_cover():
         for t, grid in enumerate(steps):
             behind = N - 1 - t
             total = behind * (behind - 1) // 2 - (behind > 1) + behind * t if t else 0
-            long |= total > 1024
-            if total > 6:
-                each.add(-(-total // (grid - behind - t)))
+            if total > 0:
+                q = -(-total // (grid - behind - 2 * (behind > 1) - t))
+                assert q == (1 if total > 576 else -(-total // 192)), (n, t, total, q)
+                long |= total > 576
+                each.add(q)
     assert tiles == {"64x32", "64x64", "128x128"}, tiles
     assert each == {1, 2, 3} and long, each
 
