@@ -1,5 +1,5 @@
 // MFMA GEMM family for gfx950 on 16-bit operand planes: v_mfma_f32_32x32x16_f16 matrix-core instructions,
-// LDS-staged tiles, fp32 accumulation, 2x2 wavefronts per block.
+// fp32 accumulation; LDS-staged tiles with 2x2 wavefronts per block, and small products straight from memory.
 //
 // fp32 quantities (ADMM auxiliaries, refitted weights, targets) are kept for the matrix cores as TWO fp16
 // planes, x*scale = hi + lo with hi = fp16(x*scale), lo = fp16(x*scale - hi) (fp16 subnormals are honoured by
@@ -10,7 +10,7 @@
 //
 // Every operand uses one memory layout, chosen for the matrix cores and for HBM:
 //   element (k, r)   k = contraction index, r = output row (P operand) or output column (Q operand)
-//   offset(k, r) = (((r / 128) * KG + k / 8) * 128 + r % 128) * 8 + k % 8,   KG = ceil(K / 8)
+//   offset(k, r) = (((r / 128) * KG + k / 8) * 128 + r % 128) * 8 + k % 8,   KG = ceil(K / 8), up to a multiple of four
 // i.e. panels of 128 rows; inside a panel the 8 k-values a matrix-core lane needs are one 16-byte chunk, the 128
 // chunks of a k-group are contiguous (a wavefront load is 1 KB contiguous, an LDS image needs no transpose and
 // no padding), and walking k walks memory sequentially (one stream per panel, TLB- and DRAM-page-friendly).
