@@ -12,7 +12,7 @@ ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 OBJ = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libstrp.so")
-SOURCES = ["gemm_mfma.hip", "gemm_dma.hip", "split_planes.hip", "dense_f64.hip", "score_select.hip", "strp_api.hip"]
+SOURCES = ["gemm_mfma.hip", "gemm_dma.hip", "split_planes.hip", "dense_f64.hip", "chol_flow.hip", "score_select.hip", "strp_api.hip"]
 BENCH_LIB = os.path.join(HERE, "libstrp_bench.so")
 BENCH_SOURCES = ["bench_probe.hip"]
 FLAGS = ["--offload-arch=gfx950", "-O3", "-fPIC", "-std=c++17", "-Wall", "-Wno-unused-function",

@@ -51,23 +51,18 @@ __device__ __forceinline__ void pruned_elem(float& zv, float& av, int phase, flo
   }
 }
 
-// One unit, by a workgroup of 256 threads (every thread must call it; ends with a barrier).
-__device__ __forceinline__ void cojob_unit(const CoJob& job, unsigned int u) {
-  __shared__ double cj_sh[4][6];
-  const int tid = threadIdx.x;
-  const unsigned int p = u / (unsigned int)job.segs, g = u - p * (unsigned int)job.segs;
-  const long long row = job.rows[p];
-  if (row < 0) {   // no such row (see pruned_list_kernel): the unit's sums are zero
-    if (tid < 6) job.partial[(unsigned long long)u * 6 + tid] = 0.0;
-    __syncthreads();
-    return;
-  }
-  float* z = job.Z + row * job.lda;
-  float* a = job.A + row * job.lda;
-  const float* z0 = job.Z0 ? job.Z0 + row * job.lda : nullptr;
+// One unit, by 256 threads (tid) that share cj_sh; every thread of the workgroup must call it, with take = false where
+// there is no unit left.  Ends with a barrier.
+__device__ __forceinline__ void cojob_unit(const CoJob& job, unsigned int u, int tid, bool take, double (*cj_sh)[6]) {
+  const unsigned int p = take ? u / (unsigned int)job.segs : 0u, g = u - p * (unsigned int)job.segs;
+  const long long row = take ? job.rows[p] : -1;
+  const bool there = row >= 0;   // no such row (see pruned_list_kernel): the unit's sums are zero
+  float* z = job.Z + (there ? row : 0) * job.lda;
+  float* a = job.A + (there ? row : 0) * job.lda;
+  const float* z0 = job.Z0 ? job.Z0 + (there ? row : 0) * job.lda : nullptr;
   const long long s0 = (long long)g * job.seg_tokens;
-  const bool last = s0 + job.seg_tokens >= job.T;
-  const long long v0 = s0 >> 2, v1 = last ? (job.T >> 2) : ((s0 + job.seg_tokens) >> 2);
+  const bool last = there && s0 + job.seg_tokens >= job.T;
+  const long long v0 = s0 >> 2, v1 = !there ? v0 : last ? (job.T >> 2) : ((s0 + job.seg_tokens) >> 2);
   const float alpha = job.alpha, beta = job.beta;
   double r0 = 0.0, r1 = 0.0, sg = 0.0, se = 0.0, su = 0.0, sv = 0.0;
   auto sums = [&](float av, float zv, float w) {
@@ -131,13 +126,14 @@ __device__ __forceinline__ void cojob_unit(const CoJob& job, unsigned int u) {
     w[0] = r0; w[1] = r1; w[2] = sg; w[3] = se; w[4] = su; w[5] = sv;
   }
   __syncthreads();
-  if (tid < 6) job.partial[(unsigned long long)u * 6 + tid] = cj_sh[0][tid] + cj_sh[1][tid] + cj_sh[2][tid] + cj_sh[3][tid];
+  if (take && tid < 6) job.partial[(unsigned long long)u * 6 + tid] = cj_sh[0][tid] + cj_sh[1][tid] + cj_sh[2][tid] + cj_sh[3][tid];
   __syncthreads();
 }
 
 // Workgroup b of nb (256 threads, all of them call this) takes every nb-th unit.
 __device__ __forceinline__ void cojob_run(const CoJob& job, unsigned int b, unsigned int nb) {
-  for (unsigned int u = b; u < job.units; u += nb) cojob_unit(job, u);
+  __shared__ double cj_sh[4][6];
+  for (unsigned int u = b; u < job.units; u += nb) cojob_unit(job, u, threadIdx.x, true, cj_sh);
 }
 
 }  // namespace strp

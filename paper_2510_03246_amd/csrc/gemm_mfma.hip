@@ -515,7 +515,7 @@ __device__ __forceinline__ void splitk_reduce_block(const ReduceP& r, int bx, in
       float* o = r.outf + (long long)m * r.ldof + n;
       *o = r.accumulate ? (float)((double)*o + s) : (float)s;
     }
-    if (r.outd) r.outd[(long long)m * r.ldod + n] = m == n ? s + ridge : s;
+    if (r.outd) r.outd[(long long)m * r.ldod + n] = m == n ? s + ridge : r.factored && m < NB && n >= NB ? 0.0 : s;
     if (r.diag && m == n) r.diag[m] = s;
   };
   const int n = n0 + tx;

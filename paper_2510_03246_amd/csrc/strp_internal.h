@@ -172,6 +172,7 @@ struct ReduceP {
   int splits, M, N, triangle;
   float* outf; long long ldof;
   double* outd; long long ldod;
+  int factored;          // outd is for chol_inverse: zeros in columns 64 .. of rows 0 .. 63
   double* diag;
   int accumulate;
   double ridge; const double* ridge_dev;
@@ -223,9 +224,12 @@ static inline size_t chol_scratch_elems(long long n) {
   return (size_t)(tiles < 4 ? tiles : 4) * NB * NB;
 }
 // Linv [n x n, ldv] = L^-1 (upper part zero) of the SPD matrix A [n x n, ld] = L L^T whose lower triangle is given (the
-// caller has added the ridge) and destroyed.  sub: chol_scratch_elems(n) doubles of scratch.  ld and ldv even, A and Linv
+// caller has added the ridge) and destroyed, with zeros in columns 64 .. of rows 0 .. 63.  sub: chol_scratch_elems(n) doubles of scratch.  ld and ldv even, A and Linv
 // 16-byte aligned.  A pivot that is not positive sets ENOTPD in status (device word).
 strp_status chol_inverse(strp_ctx* ctx, double* A, int n, long long ld, double* sub, double* Linv, long long ldv, int32_t* status);
+// The same in one launch, where that is the faster way.
+bool chol_flow_ok(const double* A, int n, long long ld, bool job);
+strp_status chol_flow(strp_ctx* ctx, double* A, int n, long long ld, double* Linv, long long ldv, int32_t* status, const CoJob& job);
 // X (L L^T)^-1 = (X Linv^T) Linv for X [m x n] (ldx), as refitted weights; tmp: m x ldx scratch.
 //   FC2: W[i, idx[j]] = result[i, j] (m rows of W);  FC1: W[idx[i], j] = result[i, j];  other entries of W are not written.
 //   Wc (optional): the result itself, [m x ldc]; maxbits (optional): atomic maximum of the bits of its magnitudes; sumsq

@@ -182,3 +182,30 @@ def test_refitted_weights_in_the_arrays_of_the_dense_ones():
     assert float(out[0][0].abs().max()) > 0.0
     for a, b in zip(*out):
         assert torch.equal(a, b)
+
+
+@pytest.mark.parametrize("n", [71, 72, 80, 1407, 1424, 2064, 3072])
+def test_factor_in_one_launch(n):
+    """Orders at the edges of the one-launch factorisation (host side: check_which_factorisation_runs), a caller's array of whole cache
+    lines and one that shares them: Linv S Linv^T = I (fp64, kappa below 100: n * kappa * 2^-53 < 1e-10), the same bits every time."""
+    ctx = strp.Context(0)
+    ctx.set_workspace(1 << 30)
+    g = torch.Generator(device="cuda").manual_seed(n)
+    B = torch.randn((n, n + 8), generator=g, device="cuda", dtype=torch.float64) / (n + 8) ** 0.5
+    G = (B @ B.T).float()
+    G = torch.tril(G) + torch.tril(G, -1).T
+    lhs, rhs = (torch.randn((r, 24), generator=g, device="cuda") for r in (8, n))
+    idx = torch.arange(n, dtype=torch.int32, device="cuda")
+    W = torch.empty((8, n), device="cuda")
+    room = torch.full((n * n + 2,), 3.0, dtype=torch.float64, device="cuda")
+    first = None
+    for off in (0, 2, 0):
+        chol = room[off:off + n * n].view(n, n)
+        ctx.strp_refit(strp.SIDE_FC2, G, 0.05, lhs, rhs, 24, idx, W, chol=chol, chol_valid=False)
+        assert ctx.poll() == strp.OK
+        first = chol.clone() if first is None else first
+        assert torch.equal(chol, first)
+    eye = torch.eye(n, dtype=torch.float64, device="cuda")
+    assert torch.count_nonzero(torch.triu(first, 1)) == 0
+    assert float((first @ (G.double() + 0.05 * eye) @ first.T - eye).abs().max()) <= 1e-10
+    ctx.close()

@@ -353,6 +353,22 @@ def check_what_the_large_systems_cover():
     assert each == {1, 2, 3} and long, each
 
 
+def check_which_factorisation_runs():
+    """One launch for orders from 72 to 1408, and above them for rows of whole cache lines: to 3072, or, with the pruned rows' pass of a step
+    riding along, any.  A launch per panel otherwise."""
+    lib = Library()
+    strp = lib.strp
+    for n, one in [(64, False), (71, False), (72, True), (200, True), (1408, True), (1409, False), (1424, True), (3072, True), (3088, False)]:
+        st, launches = lib.launches(lambda: lib.lib.strp_refit(lib.h, strp.SIDE_FC2, 1 << 50, n, 1.0, None, 0, 1 << 51, strp.F32, 24, 1 << 52, strp.F32,
+                                                               24, 24, 1 << 53, n, 1 << 54, 8, n))
+        assert st == strp.OK
+        flow, steps = (sum(name in x[0] for x in launches) for name in ("chol_flow_kernel", "chol_begin_kernel"))
+        assert (flow, steps) == (int(one), int(not one)), (n, flow, steps)
+    for d, k, want in [(64, 128, (1, 1)), (768, 1536, (2, 0)), (4096, 4915, (1, 1))]:
+        names = _step_records(lib, d, 16384 if d > 1000 else 4 * d, 4096, k, 1 << 50)[1]
+        assert tuple(sum(kernel in n for n in names) for kernel in ("chol_flow_kernel", "chol_begin_kernel")) == want, (d, k)
+
+
 def check_tiles_of_the_solves():
     """Which tile a solve of m x n takes: below 2000 tiles of 64 x 64 the number of tile rows decides between the two small ones."""
     lib = Library()
@@ -413,7 +429,7 @@ def check_weight_statistics_counter():
     assert counter(lib.h) not in (0, a, b, c)
 
 
-CHECKS = [check_tiles_of_the_solves, check_weight_statistics_counter, check_weight_statistics_without_a_counter, check_what_the_gram_matrices_cover, check_what_the_large_systems_cover, check_selection_of_a_very_wide_module, check_weight_statistics_arguments, check_weight_statistics_workgroups, check_chains, check_workspace_of_a_module, check_least_workspace_of_a_step, check_work_of_shared_launches, check_profile_classes, check_workspace_of_a_factorisation, check_cached_factor_needs_no_alignment]
+CHECKS = [check_which_factorisation_runs, check_tiles_of_the_solves, check_weight_statistics_counter, check_weight_statistics_without_a_counter, check_what_the_gram_matrices_cover, check_what_the_large_systems_cover, check_selection_of_a_very_wide_module, check_weight_statistics_arguments, check_weight_statistics_workgroups, check_chains, check_workspace_of_a_module, check_least_workspace_of_a_step, check_work_of_shared_launches, check_profile_classes, check_workspace_of_a_factorisation, check_cached_factor_needs_no_alignment]
 
 
 @pytest.fixture(scope="session")
