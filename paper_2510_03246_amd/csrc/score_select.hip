@@ -597,15 +597,30 @@ __global__ __launch_bounds__(1024) void topk_all_kernel(const float* score, int 
   }
 }
 
+// Wave-wide in registers: DPP moves instead of LDS permutes, which take 100 cycles a step where nothing else runs.
+template <int CTRL, int ROWS>
+__device__ __forceinline__ unsigned int dpp_move(unsigned int old, unsigned int x) {
+  return (unsigned int)__builtin_amdgcn_update_dpp((int)old, (int)x, CTRL, ROWS, 0xf, false);
+}
+// f over the lanes: the last one has all of them, and every lane those up to its own (inclusive scan); id is f's neutral element
+template <typename F>
+__device__ __forceinline__ unsigned int wave_scan(unsigned int x, unsigned int id, F f) {
+  x = f(x, dpp_move<0x111, 0xf>(id, x));       // row_shr 1, 2, 4, 8
+  x = f(x, dpp_move<0x112, 0xf>(id, x));
+  x = f(x, dpp_move<0x114, 0xf>(id, x));
+  x = f(x, dpp_move<0x118, 0xf>(id, x));
+  x = f(x, dpp_move<0x142, 0xa>(id, x));       // row_bcast 15 into rows 1 and 3, 31 into rows 2 and 3
+  x = f(x, dpp_move<0x143, 0xc>(id, x));
+  return x;
+}
+__device__ __forceinline__ unsigned int wave_sum_scan(unsigned int x) {
+  return wave_scan(x, 0u, [](unsigned int a, unsigned int b) { return a + b; });
+}
+
 // exclusive prefix, in thread order, of a per-thread count over the block; *total = the block's sum
 __device__ __forceinline__ int block_scan(int cnt, int* wave_tot, int* total) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  int inc = cnt;
-#pragma unroll
-  for (int o = 1; o < 64; o <<= 1) {
-    const int v = __shfl_up(inc, o, 64);
-    if (lane >= o) inc += v;
-  }
+  const int inc = (int)wave_sum_scan((unsigned int)cnt);
   if (lane == 63) wave_tot[wave] = inc;
   __syncthreads();
   int off = 0, tot = 0;
@@ -628,16 +643,12 @@ __device__ __forceinline__ void pick_bin(const unsigned int (&h)[B], unsigned in
   unsigned int own = 0;
 #pragma unroll
   for (int b = 0; b < B; ++b) own += h[b];
-  unsigned int suf = own;     // inclusive suffix sum over the lanes >= this one
-#pragma unroll
-  for (int o = 1; o < 64; o <<= 1) {
-    const unsigned int v = __shfl_down(suf, o, 64);
-    if (lane + o < 64) suf += v;
-  }
-  if (lane == 0) wave_tot[wave] = suf;
+  const unsigned int inc = wave_sum_scan(own);
+  if (lane == 63) wave_tot[wave] = inc;
   __syncthreads();
-  unsigned int above = suf - own;
-  for (int w = wave + 1; w < WAVES; ++w) above += wave_tot[w];
+  unsigned int above = 0u - inc;      // entries in the bins of later threads
+#pragma unroll
+  for (int w = 0; w < WAVES; ++w) above += w >= wave ? wave_tot[w] : 0u;
 #pragma unroll
   for (int b = B - 1; b >= 0; --b) {
     if (above < krem && above + h[b] >= krem) {
@@ -650,14 +661,14 @@ __device__ __forceinline__ void pick_bin(const unsigned int (&h)[B], unsigned in
   __syncthreads();
 }
 
-// One vector of up to 1024 KPT scores (0 < k < n) by one block of 1024 threads, element tid + 1024 j in thread tid: REGS
-// keeps the keys in registers, otherwise (beyond 16 keys a thread) each phase reads the scores again, from the L2.  What
-// bounds it is the number of dependent block-wide phases, so the threshold is found in few of them: a histogram of 2048
+// One vector of scores (0 < k < n) by one block of 1024 threads, which keeps their keys in registers (REGS, up to 4096 R of them; beyond 16 a
+// thread each phase reads them again, from the L2, 4096 R at a time): thread t has elements 4096 j + 4 t + e, so that scores, masks and sums move 16 bytes a lane, and the ascending indices need one scan of four counts.
+// What bounds it is the number of dependent block-wide phases, so the threshold is found in few of them: a histogram of 2048
 // bins stretched over the keys that are there (real scores share a handful of exponents: bins at fixed bit positions
 // would put them, and the LDS atomics that count them, in a few places), the bin with the k-th largest key, and the rank
-// of each of the bin's at most 1024 keys among themselves; a fuller bin is stretched again.  The k-th key and its index
-// decide every element: kept = larger, or equal with no higher index.  Ascending indices come from one scan of the counts
-// per (round j, wavefront).  n = 16384: 26 -> 14 us with the launch, against 32 counting rounds before.
+// of each of the bin's keys among themselves; a bin of more than 128 keys is stretched again (ranking 900 took 25 us, a round 1.5).  The k-th key
+// and its index decide every element: kept = larger, or equal with no higher index.
+// us with the launch, before (strided keys, a scan of 256 counts, LDS permutes, up to 1024 keys ranked) / now: TIMES
 // With in.sums the scores (group = 1) are formed here first, with their mean; rest takes the indices that are not kept.
 struct ScoreSource {
   const double* sums;       // [4][n], or null: the scores are given
@@ -665,95 +676,87 @@ struct ScoreSource {
   int mode;
   double* energy_out;
 };
-template <int KPT, bool REGS, bool SCORED>
-__global__ __launch_bounds__(1024) void topk_small_kernel(float* score, int n, int k, int group, uint8_t* mask, int32_t* idx, float* tau,
+constexpr int SELECT_RANKED = 128;
+template <int R, bool SCORED, bool REGS>
+__global__ __launch_bounds__(1024) void topk_small_kernel(float* score, int n, int k, int group, int vec, uint8_t* mask, int32_t* idx, float* tau,
                                                           const ScoreSource in, int32_t* rest) {
   __shared__ unsigned int hist[2048];
-  __shared__ unsigned int ckey[1024];
-  __shared__ int cidx[1024];
+  __shared__ unsigned int ckey[SELECT_RANKED];
+  __shared__ int cidx[SELECT_RANKED];
   __shared__ unsigned int wt[2][16];
   __shared__ unsigned int sel[3], ncand, cut[2];
-  __shared__ int table[16 * KPT];
-  __shared__ int wtot[16];
+  __shared__ unsigned int wtot[16][(R + 1) / 2];
   __shared__ double esums[16];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  unsigned int key[REGS ? KPT : 1];
+  unsigned int key[R][4];
+  const int rounds = REGS ? R : (n + 4096 * R - 1) / (4096 * R) * R;
+  const auto at = [&](int j) { return 4096 * j + 4 * tid; };
+  const auto load = [&](int j0) {
+#pragma unroll
+    for (int j = 0; j < R; ++j) {
+      float x[4];
+      if (vec && at(j0 + j) + 4 <= n) {
+        const float4 v = *(const float4*)(score + at(j0 + j));
+        x[0] = v.x; x[1] = v.y; x[2] = v.z; x[3] = v.w;
+      } else {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) x[e] = score[at(j0 + j) + e < n ? at(j0 + j) + e : n - 1];       // past the end: the last one again
+      }
+#pragma unroll
+      for (int e = 0; e < 4; ++e) key[j][e] = score_key(x[e]);
+    }
+  };
   if constexpr (SCORED) {
     const long long nn = n;
     const double* g = in.sums;
+    const bool full = in.mode != STRP_SCORE_WANDA;
     double esum = 0.0;
-    const auto one = [&](int i) {
-      const bool full = in.mode != STRP_SCORE_WANDA;
-      const double sc = score_of(in.mode, in.n2[i], g[i], full ? g[nn + i] : 0.0, full ? g[2 * nn + i] : 0.0, full ? g[3 * nn + i] : 0.0);
-      return sc;
-    };
-    if constexpr (REGS) {
-      double sc[KPT];
+    const auto form = [&](int j, unsigned int* keys) {
+      double sc[4];
 #pragma unroll
-      for (int j = 0; j < KPT; ++j) sc[j] = one(tid + 1024 * j < n ? tid + 1024 * j : n - 1);
+      for (int e = 0; e < 4; ++e) {
+        const int i = at(j) + e < n ? at(j) + e : n - 1;
+        sc[e] = score_of(in.mode, in.n2[i], g[i], full ? g[nn + i] : 0.0, full ? g[2 * nn + i] : 0.0, full ? g[3 * nn + i] : 0.0);
+      }
 #pragma unroll
-      for (int j = 0; j < KPT; ++j) {
-        key[j] = score_key((float)sc[j]);
-        if (tid + 1024 * j < n) {
-          score[tid + 1024 * j] = (float)sc[j];
-          esum += sc[j];
+      for (int e = 0; e < 4; ++e) {
+        if (REGS) keys[e] = score_key((float)sc[e]);
+        if (at(j) + e < n) {
+          esum += sc[e];
+          score[at(j) + e] = (float)sc[e];
         }
       }
+    };
+    if constexpr (REGS) {
+#pragma unroll
+      for (int j = 0; j < R; ++j) form(j, key[j]);
     } else {
-      for (int i = tid; i < n; i += 1024) {
-        const double sc = one(i);
-        score[i] = (float)sc;
-        esum += sc;
-      }
+      for (int j = 0; j < rounds; ++j) form(j, nullptr);
     }
     esum = wave_sum_d(esum);
     if (lane == 0) esums[wave] = esum;
-    __syncthreads();          // and every score is in memory
-    if (tid == 0 && in.energy_out) {
-      double tot = 0.0;
-      for (int w = 0; w < 16; ++w) tot += esums[w];
-      *in.energy_out = tot / (double)n;
-    }
+    if (!REGS) __syncthreads();          // the last score, which every thread may read
   } else if constexpr (REGS) {
-#pragma unroll
-    for (int j = 0; j < KPT; ++j) {
-      const int i = tid + 1024 * j;
-      key[j] = score_key(score[i < n ? i : n - 1]);
-    }
+    load(0);
   }
-  // f(j, index, key, index < n): every thread of the block makes the same calls
+  // f(index, key, index < n) for each element
   const auto each = [&](auto f) {
-    if constexpr (REGS) {
+    for (int j0 = 0; j0 < rounds; j0 += R) {
+      if (!REGS) load(j0);
 #pragma unroll
-      for (int j = 0; j < KPT; ++j) f(j, tid + 1024 * j, key[j], tid + 1024 * j < n);
-    } else {
-      for (int j0 = 0; 1024 * j0 < n; j0 += 8) {       // eight loads in flight; past the end they see the last score
-        unsigned int x[8];
+      for (int j = 0; j < R; ++j)
 #pragma unroll
-        for (int q = 0; q < 8; ++q) {
-          const int i = tid + 1024 * (j0 + q);
-          x[q] = score_key(score[i < n ? i : n - 1]);
-        }
-#pragma unroll
-        for (int q = 0; q < 8; ++q) f(j0 + q, tid + 1024 * (j0 + q), x[q], tid + 1024 * (j0 + q) < n);
-      }
+        for (int e = 0; e < 4; ++e) f(at(j0 + j) + e, key[j][e], at(j0 + j) + e < n);
     }
   };
-  // entries of `table` no call of `each` writes
-  if constexpr (!REGS)
-    for (int q = tid; q < 16 * KPT; q += 1024) table[q] = 0;
   unsigned int lo = 0xffffffffu, hi = 0u;
-  each([&](int, int, unsigned int x, bool) {
+  each([&](int, unsigned int x, bool) {
     lo = x < lo ? x : lo;
     hi = x > hi ? x : hi;
   });
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) {
-    const unsigned int a = __shfl_xor(lo, o, 64), b = __shfl_xor(hi, o, 64);
-    lo = a < lo ? a : lo;
-    hi = b > hi ? b : hi;
-  }
-  if (lane == 0) {
+  lo = wave_scan(lo, 0xffffffffu, [](unsigned int a, unsigned int b) { return a < b ? a : b; });
+  hi = wave_scan(hi, 0u, [](unsigned int a, unsigned int b) { return a > b ? a : b; });
+  if (lane == 63) {
     wt[0][wave] = lo;
     wt[1][wave] = hi;
   }
@@ -761,6 +764,16 @@ __global__ __launch_bounds__(1024) void topk_small_kernel(float* score, int n, i
   hist[tid + 1024] = 0;
   if (tid == 0) ncand = 0;
   __syncthreads();
+  if constexpr (SCORED) {
+    if (tid == 0 && in.energy_out) {
+      double tot = 0.0;
+      for (int w = 0; w < 16; ++w) tot += esums[w];
+      *in.energy_out = tot / (double)n;
+    }
+  }
+  lo = 0xffffffffu;
+  hi = 0u;
+#pragma unroll
   for (int w = 0; w < 16; ++w) {
     lo = wt[0][w] < lo ? wt[0][w] : lo;
     hi = wt[1][w] > hi ? wt[1][w] : hi;
@@ -772,8 +785,8 @@ __global__ __launch_bounds__(1024) void topk_small_kernel(float* score, int n, i
     const unsigned int range = hi - lo;
     shift = range ? 32 - __builtin_clz(range) - 11 : 0;
     shift = shift > 0 ? shift : 0;
-    each([&](int, int, unsigned int x, bool in) {
-      if (in && x >= lo && x <= hi) atomicAdd(&hist[(x - lo) >> shift], 1u);
+    each([&](int, unsigned int x, bool is) {
+      if (is && x >= lo && x <= hi) atomicAdd(&hist[(x - lo) >> shift], 1u);
     });
     __syncthreads();
     const unsigned int h[2] = {hist[2 * tid], hist[2 * tid + 1]};
@@ -783,33 +796,61 @@ __global__ __launch_bounds__(1024) void topk_small_kernel(float* score, int n, i
     lo += sel[0] << shift;
     const unsigned int width = (1u << shift) - 1u;
     hi = hi - lo > width ? lo + width : hi;
-    if (count <= 1024 || shift == 0) break;
+    if (count <= SELECT_RANKED || shift == 0) break;
     hist[tid] = 0;
     hist[tid + 1024] = 0;
     __syncthreads();
   }
+  // pre[j]: run and the sum of cnt over the elements before this thread's of the j-th of R rounds; run goes on.  Two rounds' counts in
+  // the halves of a word
+  const auto before = [&](const unsigned int (&cnt)[R], unsigned int (&pre)[R], unsigned int& run) {
+    constexpr int Q = (R + 1) / 2;
+    unsigned int own[Q], inc[Q];
+#pragma unroll
+    for (int q = 0; q < Q; ++q) {
+      own[q] = cnt[2 * q] | (2 * q + 1 < R ? cnt[2 * q + 1 < R ? 2 * q + 1 : 0] << 16 : 0u);
+      inc[q] = wave_sum_scan(own[q]);
+    }
+    if (lane == 63)
+#pragma unroll
+      for (int q = 0; q < Q; ++q) wtot[wave][q] = inc[q];
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < Q; ++q) {
+      unsigned int low = inc[q] - own[q], all = 0;
+#pragma unroll
+      for (int w = 0; w < 16; ++w) {
+        const unsigned int t = wtot[w][q];
+        low += w < wave ? t : 0u;
+        all += t;
+      }
+      pre[2 * q] = run + (low & 0xffffu);
+      run += all & 0xffffu;
+      if (2 * q + 1 < R) pre[2 * q + 1 < R ? 2 * q + 1 : 0] = run + (low >> 16);
+      run += all >> 16;
+    }
+    if (!REGS) __syncthreads();
+  };
   // the krem largest of the `count` keys in [lo, hi]
-  if (count <= 1024) {
-    each([&](int, int i, unsigned int x, bool in) {
-      if (in && x >= lo && x <= hi) {
+  if (count <= SELECT_RANKED) {
+    each([&](int i, unsigned int x, bool is) {
+      if (is && x >= lo && x <= hi) {
         const unsigned int q = atomicAdd(&ncand, 1u);
         ckey[q] = x;
         cidx[q] = i;
       }
     });
     __syncthreads();
-    // rank of each candidate: four lanes share one when there are few
-    const int quad = count <= 256 ? 4 : 1;
-    const int c = tid / quad;
+    // rank of each candidate: eight lanes share one
+    const int c = tid >> 3;
     if (c < (int)count) {
       const unsigned int kc = ckey[c];
       const int ic = cidx[c];
       int rank = 0;
-      for (int q = tid & (quad - 1); q < (int)count; q += quad) rank += (ckey[q] > kc || (ckey[q] == kc && cidx[q] < ic)) ? 1 : 0;
-      if (quad == 4) {
-        rank += __shfl_xor(rank, 1, 64);
-        rank += __shfl_xor(rank, 2, 64);
-      }
+      for (int q = tid & 7; q < (int)count; q += 8) rank += (ckey[q] > kc || (ckey[q] == kc && cidx[q] < ic)) ? 1 : 0;
+      rank += __shfl_xor(rank, 1, 64);
+      rank += __shfl_xor(rank, 2, 64);
+      rank += __shfl_xor(rank, 4, 64);
       if (rank == (int)krem - 1) {
         cut[0] = kc;
         cut[1] = (unsigned int)ic;
@@ -817,52 +858,69 @@ __global__ __launch_bounds__(1024) void topk_small_kernel(float* score, int n, i
     }
     __syncthreads();
   } else {
-    // more than 1024 equal keys (lo == hi): the krem-th in index order
-    each([&](int j, int, unsigned int x, bool in) {
-      const unsigned long long beq = __ballot(in && x == lo);
-      if (lane == 0) table[j * 16 + wave] = __popcll(beq);
-    });
-    __syncthreads();
-    int tot;
-    const int pref = block_scan(tid < 16 * KPT ? table[tid] : 0, wtot, &tot);
-    if (tid < 16 * KPT) table[tid] = pref;
-    __syncthreads();
-    each([&](int j, int i, unsigned int x, bool in) {
-      const bool eq = in && x == lo;
-      const unsigned long long beq = __ballot(eq);
-      const int rank = table[j * 16 + wave] + __popcll(beq & ((1ull << lane) - 1ull));
-      if (eq && rank == (int)krem - 1) {
-        cut[0] = lo;
-        cut[1] = (unsigned int)i;
+    // more equal keys than that (lo == hi): the krem-th in index order
+    unsigned int run = 0;
+    for (int j0 = 0; j0 < rounds; j0 += R) {
+      unsigned int cnt[R], pre[R];
+      if (!REGS) load(j0);
+#pragma unroll
+      for (int j = 0; j < R; ++j) {
+        cnt[j] = 0;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) cnt[j] += at(j0 + j) + e < n && key[j][e] == lo ? 1u : 0u;
       }
-    });
+      before(cnt, pre, run);
+#pragma unroll
+      for (int j = 0; j < R; ++j)
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+          if (at(j0 + j) + e < n && key[j][e] == lo && ++pre[j] == krem) {
+            cut[0] = lo;
+            cut[1] = (unsigned int)(at(j0 + j) + e);
+          }
+    }
     __syncthreads();
   }
   const unsigned int ckth = cut[0];
   const int ikth = (int)cut[1];
   if (tid == 0 && tau) *tau = key_score(ckth);
-  each([&](int j, int i, unsigned int x, bool valid) {
-    const bool keep = valid && (x > ckth || (x == ckth && i <= ikth));
-    const unsigned long long bk = __ballot(keep);
-    if (lane == 0) table[j * 16 + wave] = __popcll(bk);
-    if (valid) mask[i] = (uint8_t)keep;
-  });
-  __syncthreads();
-  int tot;
-  const int pref = block_scan(tid < 16 * KPT ? table[tid] : 0, wtot, &tot);
-  if (tid < 16 * KPT) table[tid] = pref;
-  __syncthreads();
-  each([&](int j, int i, unsigned int x, bool valid) {
-    const bool keep = valid && (x > ckth || (x == ckth && i <= ikth));
-    const unsigned long long bk = __ballot(keep);
-    const int before = table[j * 16 + wave] + __popcll(bk & ((1ull << lane) - 1ull));
-    if (keep) {
-      const long long pos = (long long)before * group;
-      for (int c = 0; c < group; ++c) idx[pos + c] = i * group + c;
-    } else if (SCORED && rest && valid) {
-      rest[i - before] = i;
+  unsigned int run = 0;
+  for (int j0 = 0; j0 < rounds; j0 += R) {
+    unsigned int keep[R], cnt[R], pre[R];
+    if (!REGS) load(j0);
+#pragma unroll
+    for (int j = 0; j < R; ++j) {
+      const int i0 = at(j0 + j);
+      keep[j] = 0;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) keep[j] |= (i0 + e < n && (key[j][e] > ckth || (key[j][e] == ckth && i0 + e <= ikth)) ? 1u : 0u) << e;
+      cnt[j] = (unsigned int)__popc(keep[j]);
+      if (vec && i0 + 4 <= n) {
+        *(unsigned int*)(mask + i0) = (keep[j] & 1u) | (keep[j] & 2u) << 7 | (keep[j] & 4u) << 14 | (keep[j] & 8u) << 21;
+      } else {
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+          if (i0 + e < n) mask[i0 + e] = (uint8_t)((keep[j] >> e) & 1u);
+      }
     }
-  });
+    before(cnt, pre, run);
+#pragma unroll
+    for (int j = 0; j < R; ++j) {
+      unsigned int pos = pre[j];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const int i = at(j0 + j) + e;
+        if ((keep[j] >> e) & 1u) {
+          if (group == 1) idx[pos] = i;
+          else
+            for (int c = 0; c < group; ++c) idx[(long long)pos * group + c] = i * group + c;
+          ++pos;
+        } else if (SCORED && rest && i < n) {
+          rest[i - (int)pos] = i;
+        }
+      }
+    }
+  }
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -1123,12 +1181,13 @@ __global__ __launch_bounds__(big::THREADS) void topk_lone_kernel(const float* sc
 
 static void launch_topk_small(strp_ctx* ctx, float* score, int n, int k, int group, uint8_t* mask, int32_t* idx, float* tau, const ScoreSource& in,
                               int32_t* rest) {
-  const auto one = [&](auto kernel) { hipLaunchKernelGGL(kernel, dim3(1), dim3(1024), 0, ctx->stream, score, n, k, group, mask, idx, tau, in, rest); };
+  const int vec = (((uintptr_t)score & 15) == 0 && ((uintptr_t)mask & 3) == 0) ? 1 : 0;
+  const auto one = [&](auto kernel) { hipLaunchKernelGGL(kernel, dim3(1), dim3(1024), 0, ctx->stream, score, n, k, group, vec, mask, idx, tau, in, rest); };
   const auto size = [&](auto scored) {
     constexpr bool S = decltype(scored)::value;
-    if (n <= 4096) one(topk_small_kernel<4, true, S>);
-    else if (n <= 16384) one(topk_small_kernel<16, true, S>);
-    else one(topk_small_kernel<64, false, S>);
+    if (n <= 4096) one(topk_small_kernel<1, S, true>);
+    else if (n <= 16384) one(topk_small_kernel<4, S, true>);
+    else one(topk_small_kernel<4, S, false>);
   };
   if (in.sums) size(std::true_type{});
   else size(std::false_type{});
