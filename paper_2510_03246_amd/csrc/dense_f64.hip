@@ -84,6 +84,7 @@ struct F64Loader {
 template <int R, int DK, bool KC>
 constexpr int f64_img_elems() { return KC ? DK / 2 * (R + 1) * 2 : DK * (R + 4); }
 
+constexpr int CUS = 256;
 template <int TM, int TN, int DK, bool AKC, bool BKC>
 __device__ __forceinline__ void dgemm_block(const DgemmP& p, int block) {
   constexpr int WM = TM / 32, WN = TN / 32;     // 16 x 16 tiles per wavefront
@@ -91,7 +92,16 @@ __device__ __forceinline__ void dgemm_block(const DgemmP& p, int block) {
   __shared__ __attribute__((aligned(16))) double Bs[2][f64_img_elems<TN, DK, BKC>()];
   const int tilesM = (p.M + TM - 1) / TM, tilesN = (p.N + TN - 1) / TN;
   // the rows of C walk fastest; column tiles go in order of decreasing K range
-  const int tn_ = block / tilesM, tm_ = block - tn_ * tilesM;
+  int tn_ = block / tilesM, tm_ = block - tn_ * tilesM;
+  // Of a solve with up to three workgroups per CU all run from the start, and a CU has those that are 256 apart: every other 256
+  // go in order of increasing K range, so that a CU with a long tile has short ones beside it.  With more of them the longest
+  // first end the soonest, since a CU takes the next when it has done with one.  In order / turned, us of both products: 576 x 928
+  // (261 tiles) 50.1 / 50.8, 1000 x 1013 (512) 65.4 / 59.5, 768 x 1536 (576) 96.8 / 89.4,
+  // 640 x 2000 (630) 133.2 / 125.5, 200 x 4000 (500) 213.1 / 188.3, 1024 x 1536 (768) 109.9 / 102.7.
+  if (TN == 32 && p.tri != 3 && tilesM <= CUS && tilesM * tilesN > CUS && tilesM * tilesN <= 3 * CUS) {
+    const int turn = CUS / tilesM, beg = tn_ / turn * turn, end = beg + turn < tilesN ? beg + turn : tilesN;
+    if (tn_ / turn & 1) tn_ = beg + end - 1 - tn_;
+  }
   const int m0 = tm_ * TM, n0 = (p.tri == 1 ? tilesN - 1 - tn_ : tn_) * TN;
   if (p.lower && n0 >= m0 + TM) return;
   int kbeg = 0, kend = p.K;
@@ -246,7 +256,7 @@ __device__ __forceinline__ void dgemm_block(const DgemmP& p, int block) {
     lds_barrier();
     if (tid == 0) {
       if (maxbits) atomicMax(maxbits, __builtin_bit_cast(unsigned int, (float)fmax(fmax(red[0], red[2]), fmax(red[4], red[6]))));
-      if (p.w.sumsq) p.w.sumsq[block] = red[1] + red[3] + red[5] + red[7];
+      if (p.w.sumsq) p.w.sumsq[tn_ * tilesM + tm_] = red[1] + red[3] + red[5] + red[7];
     }
   }
 }

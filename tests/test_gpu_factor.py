@@ -209,3 +209,23 @@ def test_factor_in_one_launch(n):
     assert torch.count_nonzero(torch.triu(first, 1)) == 0
     assert float((first @ (G.double() + 0.05 * eye) @ first.T - eye).abs().max()) <= 1e-10
     ctx.close()
+
+
+@pytest.mark.parametrize("m,n", [(1024, 512), (1024, 513), (700, 1400), (1024, 1536), (1088, 1472), (16448, 40), (130, 4097)])
+def test_solve_in_the_order_of_its_tiles(m, n):
+    """Solves at the ends of the range whose column tiles go in turns (256 and 768 tiles of 64 x 32, ragged ones, more tile rows than
+    CUs): W = R Linv^T Linv for an arbitrary lower triangle Linv in hand (R whole numbers; fp64 sums of n terms, W rounded to fp32: 1e-7)."""
+    ctx = strp.Context(0)
+    ctx.set_workspace(1 << 30)
+    g = torch.Generator(device="cuda").manual_seed(m + n)
+    T = 24
+    lhs, rhs = (torch.randint(-4, 5, (r, T), generator=g, device="cuda").float() for r in (m, n))
+    chol = torch.tril(torch.randn((n, n), generator=g, device="cuda", dtype=torch.float64))
+    idx = torch.arange(n, dtype=torch.int32, device="cuda")
+    W = torch.full((m, n), 7.0, device="cuda")
+    ctx.strp_refit(strp.SIDE_FC2, None, 0.0, lhs, rhs, T, idx, W, chol=chol, chol_valid=True)
+    assert ctx.poll() == strp.OK
+    ref = lhs.double() @ rhs.double().T @ chol.T @ chol
+    assert float((W.double() - ref).norm() / ref.norm()) <= 1e-7
+    assert float((W.double() - ref).abs().max()) <= 1e-6 * float(ref.abs().max())
+    ctx.close()
