@@ -12,7 +12,7 @@ namespace strp {
 
 // ---------------------------------------------------------------------------------------------
 // dgemm: C[m, n] = sum_k A(m, k) B(k, n), C row-major.
-//   block = 4 wavefronts (2 x 2), TM x TN output tile, K staged DK at a time through double-buffered LDS; the next
+//   block = 4 wavefronts (2 x 2) or two such shares of K, TM x TN output tile, K staged DK at a time through double-buffered LDS; the next
 //   stage's 16-byte loads are in flight while a stage is multiplied.
 //   A: AKC ? A[m * lda + k] : A[k * lda + m];   B: BKC ? B[n * ldb + k] : B[k * ldb + n].
 //   tri restricts the K range of a tile to where a triangular operand is non-zero:
@@ -29,9 +29,9 @@ struct DgemmP {
   WeightsOut w;             // w.W: the result as refitted weights instead of C (one fp64 matrix less to write and read)
 };
 
-template <int R, int DK, bool KC>
+template <int R, int DK, bool KC, int NT>
 struct F64Loader {
-  static constexpr int NCH = R * DK / 512;   // 16-byte pieces per thread and stage
+  static constexpr int NCH = R * DK / 2 / NT;   // 16-byte pieces per thread and stage
   doublex2 r[NCH];
   // A whole stage with 16-byte loads: the same instructions for every tile and stage, so that the wait for one stage leaves the
   // next one's loads in flight (behind a branch the compiler has to wait for all of them).  Rows past the edge repeat the
@@ -39,7 +39,7 @@ struct F64Loader {
   static __device__ __forceinline__ void offsets(unsigned int (&off)[NCH], long long ld, int rv) {
 #pragma unroll
     for (int q = 0; q < NCH; ++q) {
-      const int e = (int)threadIdx.x + 256 * q;
+      const int e = (int)threadIdx.x + NT * q;
       if (KC) {
         const int row = e / (DK / 2);
         off[q] = ((unsigned int)(row < rv ? row : rv - 1) * (unsigned int)ld + 2u * (e % (DK / 2))) * 8u;
@@ -58,7 +58,7 @@ struct F64Loader {
   __device__ __forceinline__ void load(const double* src, long long ld, int rv, int k0, int kend) {
 #pragma unroll
     for (int q = 0; q < NCH; ++q) {
-      const int e = (int)threadIdx.x + 256 * q;
+      const int e = (int)threadIdx.x + NT * q;
       if (KC) {
         const int ch = e % (DK / 2), row = e / (DK / 2);
         const int k = k0 + 2 * ch;
@@ -75,7 +75,7 @@ struct F64Loader {
   __device__ __forceinline__ void store(double* img) const {
 #pragma unroll
     for (int q = 0; q < NCH; ++q) {
-      const int e = (int)threadIdx.x + 256 * q;
+      const int e = (int)threadIdx.x + NT * q;
       if (KC) *(doublex2*)(img + kc_off<R>(2 * (e % (DK / 2)), e / (DK / 2))) = r[q];
       else *(doublex2*)(img + rc_off<R>(e / (R / 2), 2 * (e % (R / 2)))) = r[q];
     }
@@ -85,9 +85,15 @@ template <int R, int DK, bool KC>
 constexpr int f64_img_elems() { return KC ? DK / 2 * (R + 1) * 2 : DK * (R + 4); }
 
 constexpr int CUS = 256;
+// The two small tiles have eight wavefronts: two shares of every stage's K, whose sums are added at the end.  With four, a long tile that
+// is left alone on its CU has one wavefront and two to four chains of products per SIMD, and nothing to issue while that one reads LDS or
+// waits at a barrier.  Both products of a solve, us, four / eight wavefronts: 256 x 512 28.7 / 25.2, 1000 x 1013 59.5 / 51.3, 768 x 1536
+// 89.4 / 78.7, 2048 x 3277 700 / 681, 4096 x 4915 (64 x 64) 3190 / 3032 (65 TFLOP/s).  The 128 x 128 tile has 16 chains a wavefront.
+constexpr int k_shares(int TM, int TN) { return TM * TN >= 128 * 128 ? 1 : 2; }
 template <int TM, int TN, int DK, bool AKC, bool BKC>
 __device__ __forceinline__ void dgemm_block(const DgemmP& p, int block) {
   constexpr int WM = TM / 32, WN = TN / 32;     // 16 x 16 tiles per wavefront
+  constexpr int KS = k_shares(TM, TN);
   __shared__ __attribute__((aligned(16))) double As[2][f64_img_elems<TM, DK, AKC>()];
   __shared__ __attribute__((aligned(16))) double Bs[2][f64_img_elems<TN, DK, BKC>()];
   const int tilesM = (p.M + TM - 1) / TM, tilesN = (p.N + TN - 1) / TN;
@@ -110,7 +116,7 @@ __device__ __forceinline__ void dgemm_block(const DgemmP& p, int block) {
   if (p.tri == 3) kbeg = m0;
 
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int wm = (wave >> 1) * (TM / 2), wn = (wave & 1) * (TN / 2);
+  const int wm = (wave >> 1 & 1) * (TM / 2), wn = (wave & 1) * (TN / 2), share = wave >> 2;
   const int l16 = lane & 15, lq = lane >> 4;
   doublex4 acc[WM][WN];
 #pragma unroll
@@ -126,15 +132,15 @@ __device__ __forceinline__ void dgemm_block(const DgemmP& p, int block) {
   // whose accumulators leave no room for a second (two spilled 52 registers: 6000 x 6000 6642 us instead of 6479, 8602 x 7168 13497
   // instead of 13089).
   constexpr int SETS = TM * TN >= 128 * 128 ? 1 : 2;
-  F64Loader<TM, DK, AKC> la[SETS];
-  F64Loader<TN, DK, BKC> lb[SETS];
+  F64Loader<TM, DK, AKC, 256 * KS> la[SETS];
+  F64Loader<TN, DK, BKC, 256 * KS> lb[SETS];
   auto multiply = [&](int buf) {
     const double* as = As[buf];
     const double* bs = Bs[buf];
 #pragma unroll
-    for (int c = 0; c < DK / 8; ++c) {
+    for (int c = 0; c < DK / 8 / KS; ++c) {
       doublex2 af[WM], bf[WN];
-      const int k = 8 * c + 2 * lq;
+      const int k = DK / KS * share + 8 * c + 2 * lq;
 #pragma unroll
       for (int i = 0; i < WM; ++i) {
         if (AKC) af[i] = *(const doublex2*)(as + kc_off<TM>(k, wm + 16 * i + l16));
@@ -158,9 +164,9 @@ __device__ __forceinline__ void dgemm_block(const DgemmP& p, int block) {
   const bool pairs = (AKC || rvm >= TM || p.lda % 2 == 0) && (BKC || rvn >= TN || p.ldb % 2 == 0);
   const int whole = pairs && kend > kbeg ? (kend - kbeg) / DK : 0;
   if (whole) {
-    unsigned int offa[F64Loader<TM, DK, AKC>::NCH], offb[F64Loader<TN, DK, BKC>::NCH];
-    F64Loader<TM, DK, AKC>::offsets(offa, p.lda, rvm);
-    F64Loader<TN, DK, BKC>::offsets(offb, p.ldb, rvn);
+    unsigned int offa[F64Loader<TM, DK, AKC, 256 * KS>::NCH], offb[F64Loader<TN, DK, BKC, 256 * KS>::NCH];
+    F64Loader<TM, DK, AKC, 256 * KS>::offsets(offa, p.lda, rvm);
+    F64Loader<TN, DK, BKC, 256 * KS>::offsets(offb, p.ldb, rvn);
     auto gload = [&](int set, int s) {      // past the end: the last one again, never multiplied
       const long long k = kbeg + (long long)(s < whole ? s : whole - 1) * DK;
       la[set].load_whole(AKC ? A + k : A + k * p.lda, offa);
@@ -204,8 +210,22 @@ __device__ __forceinline__ void dgemm_block(const DgemmP& p, int block) {
     multiply(0);
     lds_barrier();
   }
+  if constexpr (KS == 2) {         // the second share's sums to the first, through LDS that nobody reads any more
+    static_assert(TM * TN <= 2 * f64_img_elems<TM, DK, AKC>(), "");
+    double* x = As[0] + (wave & 3) * (WM * WN * 4 * 64) + lane;
+    if (share) {
+#pragma unroll
+      for (int e = 0; e < WM * WN * 4; ++e) x[64 * e] = acc[e / 4 / WN][e / 4 % WN][e % 4];
+    }
+    lds_barrier();
+    if (!share) {
+#pragma unroll
+      for (int e = 0; e < WM * WN * 4; ++e) acc[e / 4 / WN][e / 4 % WN][e % 4] += x[64 * e];
+    }
+  }
   double big = 0.0, sq = 0.0;
-  if (p.w.W) {
+  if (share) {
+  } else if (p.w.W) {
     const bool fc2 = p.w.side == STRP_SIDE_FC2;
 #pragma unroll
     for (int j = 0; j < WN; ++j) {
@@ -249,7 +269,8 @@ __device__ __forceinline__ void dgemm_block(const DgemmP& p, int block) {
       big = fmax(big, __shfl_down(big, o, 64));
       sq += __shfl_down(sq, o, 64);
     }
-    if (lane == 0) {
+    if constexpr (KS == 2) lds_barrier();
+    if (lane == 0 && !share) {
       red[2 * wave] = big;
       red[2 * wave + 1] = sq;
     }
@@ -262,7 +283,7 @@ __device__ __forceinline__ void dgemm_block(const DgemmP& p, int block) {
 }
 
 template <int TM, int TN, int DK, bool AKC, bool BKC>
-__global__ __launch_bounds__(256, 2) void dgemm_kernel(const DgemmP p) { dgemm_block<TM, TN, DK, AKC, BKC>(p, blockIdx.x); }
+__global__ __launch_bounds__(256 * k_shares(TM, TN), 2) void dgemm_kernel(const DgemmP p) { dgemm_block<TM, TN, DK, AKC, BKC>(p, blockIdx.x); }
 
 // two independent products, one behind the other in the grid: `first` workgroups are the first's
 struct DgemmPair {
@@ -270,23 +291,23 @@ struct DgemmPair {
   int first;
 };
 template <int TM, int TN, int DK, bool AKC, bool BKC>
-__global__ __launch_bounds__(256, 2) void dgemm_pair_kernel(const DgemmPair g) {
+__global__ __launch_bounds__(256 * k_shares(TM, TN), 2) void dgemm_pair_kernel(const DgemmPair g) {
   const int second = (int)blockIdx.x >= g.first;
   dgemm_block<TM, TN, DK, AKC, BKC>(g.p[second], (int)blockIdx.x - second * g.first);
 }
 
 // Tile of a product by its grid: 128 x 128 tiles read the fewest operand bytes per flop but need enough of them to fill
 // the chip; below that the longest tile (whole K) sets the run time and a smaller one ends sooner.  Solves X (L L^T)^-1 of
-// m x n (two products), us with 64 x 32 / 64 x 64 / 128 x 128 tiles (in brackets the tiles of 64, of 128):
+// m x n (two products), us with 64 x 32 / 64 x 64 / 128 x 128 tiles of four wavefronts (in brackets the tiles of 64, of 128):
 //   768 x 1536 (288) 104 / 139 / 433;  3000 x 3000 (2209, 576) 1059 / 888 / 1161;  4096 x 4096 (4096, 1024) 2174 / 2119 / 2240;
 //   4096 x 4915 (4928, 1248) 3192 / 3070 / 3088, 65 TFLOP/s;  4864 x 4864 (5776, 1444) 3657 / 3528 / 3528;  5120 x 5120 (6400, 1600)
 //   4219 / 4139 / 4059;  6000 x 6000 (8836, 2209) 7783 / 6968 / 6479;  8602 x 7168 (15120, 3808) 16774 / 14895 / 13089.
 // Between the two small ones the number of tile rows decides: workgroups go to the 8 XCDs in turn, so that with an even number an
 // XCD meets only some rows of A, again and again, and with an odd one all of them, which costs the tile that reads A for fewer
-// columns.  64 x 32 / 64 x 64, even: 1656 x 2688 (1092) 399 / 407;  2048 x 2458 (1248) 393 / 414;  3072 x 2048 (1536) 406 / 425;
-// 3277 x 2048 (1664) 442 / 455;  2048 x 3277 686 / 703;  2680 x 2880 (1890) 725 / 717;  3448 x 2624 (2214) 814 / 766.  Odd: 1088 x 1656 (442)
-// 135 / 164;  1344 x 1848 (609) 199 / 200;  1728 x 1656 (702) 202 / 189;  2880 x 1144 (810) 160 / 163;  2112 x 2112 (1089) 358 / 328;
-// 2496 x 2496 (1521) 590 / 517;  2880 x 2880 (2025) 887 / 763.
+// columns.  64 x 32 / 64 x 64, even: 1656 x 2688 (1092) 396 / 404;  2048 x 2458 (1248) 386 / 411;  3072 x 2048 (1536) 398 / 421;
+// 2048 x 3277 (1664) 667 / 692;  2680 x 2880 (1890) 711 / 697;  3448 x 2624 (2214) 799 / 739.  Odd: 1088 x 1656 (442)
+// 133 / 130;  1344 x 1848 (609) 188 / 179;  1728 x 1656 (702) 197 / 189;  2880 x 1144 (810) 158 / 159;  2112 x 2112 (1089) 363 / 327;
+// 2496 x 2496 (1521) 591 / 504.  The lines to 128 x 128 and those of Linv^T Linv stand where tiles of four wavefronts put them:
 // Linv^T Linv (half the tiles, order):  2600 (840) 162 / 158 / 361;  3000 (1104) 249 / 260 / 494;  3400 (1458) 361 / 284 / 616;
 // 6000 (4418, 1104) 1765 / 1328 / 1743;  8192 (8192, 2048) 4195 / 3212 / 3335;  10240 (12800, 3200) 8134 / 6575 / 5665.
 constexpr int DGEMM_T128 = 1450, DGEMM_T128_LOWER = 2500, DGEMM_T64 = 2000, DGEMM_T64_ODD = 680, DGEMM_T64_LOWER = 1200;
@@ -309,8 +330,8 @@ static strp_status dgemm_launch(strp_ctx* ctx, const DgemmP& p) {
   const DgemmTile t = dgemm_tile(p.M, p.N, p.lower);
   const dim3 grid(dgemm_blocks(p.M, p.N, t));
   if (t.tm == 128) hipLaunchKernelGGL((dgemm_kernel<128, 128, 16, AKC, BKC>), grid, dim3(256), 0, ctx->stream, p);
-  else if (t.tn == 64) hipLaunchKernelGGL((dgemm_kernel<64, 64, 32, AKC, BKC>), grid, dim3(256), 0, ctx->stream, p);
-  else hipLaunchKernelGGL((dgemm_kernel<64, 32, 32, AKC, BKC>), grid, dim3(256), 0, ctx->stream, p);
+  else if (t.tn == 64) hipLaunchKernelGGL((dgemm_kernel<64, 64, 32, AKC, BKC>), grid, dim3(512), 0, ctx->stream, p);
+  else hipLaunchKernelGGL((dgemm_kernel<64, 32, 32, AKC, BKC>), grid, dim3(512), 0, ctx->stream, p);
   STRP_HIP(ctx, hipGetLastError());
   return STRP_OK;
 }
@@ -778,8 +799,8 @@ strp_status apply_inverse_right_pair(strp_ctx* ctx, const SolveIn& a, const Solv
   solve_products(b, q);
   const int first = dgemm_blocks(a.m, a.n, {64, 32}), blocks = first + dgemm_blocks(b.m, b.n, {64, 32});
   const DgemmPair g0{{p[0], q[0]}, first}, g1{{p[1], q[1]}, first};
-  hipLaunchKernelGGL((dgemm_pair_kernel<64, 32, 32, true, true>), dim3(blocks), dim3(256), 0, ctx->stream, g0);
-  hipLaunchKernelGGL((dgemm_pair_kernel<64, 32, 32, true, false>), dim3(blocks), dim3(256), 0, ctx->stream, g1);
+  hipLaunchKernelGGL((dgemm_pair_kernel<64, 32, 32, true, true>), dim3(blocks), dim3(512), 0, ctx->stream, g0);
+  hipLaunchKernelGGL((dgemm_pair_kernel<64, 32, 32, true, false>), dim3(blocks), dim3(512), 0, ctx->stream, g1);
   STRP_HIP(ctx, hipGetLastError());
   return STRP_OK;
 }
