@@ -668,7 +668,8 @@ __device__ __forceinline__ void pick_bin(const unsigned int (&h)[B], unsigned in
 // would put them, and the LDS atomics that count them, in a few places), the bin with the k-th largest key, and the rank
 // of each of the bin's keys among themselves; a bin of more than 128 keys is stretched again (ranking 900 took 25 us, a round 1.5).  The k-th key
 // and its index decide every element: kept = larger, or equal with no higher index.
-// us with the launch, before (strided keys, a scan of 256 counts, LDS permutes, up to 1024 keys ranked) / now: TIMES
+// Before (strided keys, a scan of 256 counts, LDS permutes, up to 1024 keys ranked) / now: 16384 scores 13.9 / 9.3 us with the launch;
+// in a step, with the scores formed first, 2312 35.7 / 11.3 and 256 8.3 / 5.7.
 // With in.sums the scores (group = 1) are formed here first, with their mean; rest takes the indices that are not kept.
 struct ScoreSource {
   const double* sums;       // [4][n], or null: the scores are given
@@ -933,7 +934,9 @@ __global__ __launch_bounds__(1024) void topk_small_kernel(float* score, int n, i
 //            then the threshold itself, and per workgroup where its kept entries go and how many of its entries equal to
 //            the threshold are kept (lower indices first)
 //   write    mask and ascending indices
-// Every input takes the same path, also one of equal scores.  48 x 28672 scores: 66 -> 34 us against eight launches.
+// Every input takes the same path, also one of equal scores.  48 x 28672 scores: 66 -> 34 us against eight launches, 31.7 with a trip's
+// scores on their way while the one before is counted and the bins of a workgroup read and cleared 16 bytes or 16 counts at a time;
+// 70 thousand 28.2 -> 20.4 by that and by the number of workgroups (big_plan).
 // ---------------------------------------------------------------------------------------------
 namespace big {
 constexpr int BINS = 8192;          // 13 bits
@@ -955,55 +958,81 @@ struct State {
 }  // namespace big
 
 static void big_plan(long long n, int* blocks, long long* chunk) {
-  // two trips per workgroup and more: every workgroup adds its counts of the same few hundred bins to the global histogram,
-  // and adds to one address go one after another
-  long long b = n / (16 * big::THREADS);
-  if (b > big::MAXBLOCKS) b = big::MAXBLOCKS;
-  if (b < 1) b = 1;
-  long long c = (n + b - 1) / b;
-  c = (c + 8 * big::THREADS - 1) / (8 * big::THREADS) * (8 * big::THREADS);
+  // A trip of a workgroup is 4096 scores.  More workgroups read faster, but each adds its counts of the same few hundred bins to the
+  // global histogram, and adds to one address go one after another: about 0.02 us a workgroup and launch, against 5 us a trip for the
+  // four together.  us, one trip / two: 300 thousand scores 22.9 / 24.5, 500 thousand 25.5 / 25.5, 1.04 million 32.4 / 29.3; two / three
+  // at 2.09 million 36.6 / 35.7; 128 / 256 workgroups at 1.7 million 35.0 / 33.6, 256 / 512 at 6 million 53.4 / 60.8, at 12 million 76.9 (367) / 89.2.
+  long long trips = 1;
+  auto most = [&]() { return trips > 8 ? (long long)big::MAXBLOCKS : trips > 2 ? 256ll : 96 * trips; };
+  while ((n + big::THREADS * 8 * trips - 1) / (big::THREADS * 8 * trips) > most()) ++trips;
+  const long long c = trips * (8 * big::THREADS);
   *blocks = (int)((n + c - 1) / c);
   *chunk = c;
 }
 
 size_t topk_scratch_bytes(int n) { return n <= SELECT_MAX ? 0 : ((sizeof(big::State) + 255) & ~size_t(255)); }
 
-// f(key, index) for this workgroup's chunk: eight consecutive scores per thread and trip
-template <typename F>
-__device__ __forceinline__ void big_scan(const float* score, long long beg, long long end, int vec, F f) {
-  for (long long i0 = beg + 8 * (long long)threadIdx.x; i0 < end; i0 += 8 * big::THREADS) {
-    float x[8];
-    if (vec && i0 + 8 <= end) {
-      const float4 a = *(const float4*)(score + i0), b = *(const float4*)(score + i0 + 4);
-      x[0] = a.x; x[1] = a.y; x[2] = a.z; x[3] = a.w; x[4] = b.x; x[5] = b.y; x[6] = b.z; x[7] = b.w;
+// eight consecutive scores of a thread
+struct BigTrip {
+  float4 a, b;
+  bool whole;
+  __device__ __forceinline__ void load(const float* score, long long i0, long long end, int vec) {
+    whole = vec && i0 + 8 <= end;
+    if (whole) {
+      a = *(const float4*)(score + i0);
+      b = *(const float4*)(score + i0 + 4);
+    }
+  }
+  template <typename F>
+  __device__ __forceinline__ void each(const float* score, long long i0, long long end, F f) const {
+    if (whole) {
+      const float x[8] = {a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w};
 #pragma unroll
       for (int e = 0; e < 8; ++e) f(score_key(x[e]));
     } else {
       for (long long i = i0; i < end && i < i0 + 8; ++i) f(score_key(score[i]));
     }
   }
+};
+// f(key) for this workgroup's chunk; first: the thread's first trip, which the kernel asks for before anything else.  The next trip
+// is on its way while one is counted: with one at a time in flight a launch was two round trips to memory longer.
+template <typename F>
+__device__ __forceinline__ void big_scan(BigTrip t, const float* score, long long beg, long long end, int vec, F f) {
+  for (long long i0 = beg + 8 * (long long)threadIdx.x; i0 < end; i0 += 8 * big::THREADS) {
+    BigTrip next;
+    next.load(score, i0 + 8 * big::THREADS, end, vec);
+    t.each(score, i0, end, f);
+    t = next;
+  }
+}
+__device__ __forceinline__ void clear_bins(unsigned int (&hist)[big::BINS]) {
+#pragma unroll
+  for (int q = 0; q < big::BINS / 4 / big::THREADS; ++q) ((uint4*)hist)[threadIdx.x + big::THREADS * q] = make_uint4(0, 0, 0, 0);
 }
 template <int LEVEL>
 __global__ __launch_bounds__(big::THREADS) void topk_hist_kernel(const float* score, long long n, long long k, long long chunk, int vec, big::State* st) {
-  __shared__ unsigned int hist[big::BINS];
+  __shared__ __attribute__((aligned(16))) unsigned int hist[big::BINS];
   __shared__ unsigned int wt[8], sel[3], flag;
   const int tid = threadIdx.x;
-  for (int i = tid; i < big::BINS; i += big::THREADS) hist[i] = 0;
+  const long long beg = (long long)blockIdx.x * chunk, end = beg + chunk < n ? beg + chunk : n;
+  BigTrip first;
+  first.load(score, beg + 8 * tid, end, vec);
+  clear_bins(hist);
   const unsigned int prefix = LEVEL ? st->prefix[0] : 0u;
   __syncthreads();
-  const long long beg = (long long)blockIdx.x * chunk, end = beg + chunk < n ? beg + chunk : n;
-  big_scan(score, beg, end, vec, [&](unsigned int key) {
+  big_scan(first, score, beg, end, vec, [&](unsigned int key) {
     if (LEVEL == 0) atomicAdd(&hist[key >> 19], 1u);
     else if (key >> 19 == prefix) atomicAdd(&hist[(key >> 6) & 8191u], 1u);
   });
   __syncthreads();
-  for (int i = tid; i < big::BINS; i += big::THREADS) {
-    const unsigned int h = hist[i];
-    if (h) atomicAdd(&st->ghist[LEVEL][i], h);
-  }
+  unsigned int h[16];
+#pragma unroll
+  for (int b = 0; b < 16; ++b) h[b] = hist[tid + big::THREADS * b];
+#pragma unroll
+  for (int b = 0; b < 16; ++b)
+    if (h[b]) atomicAdd(&st->ghist[LEVEL][tid + big::THREADS * b], h[b]);
   if (!last_block(&st->done[LEVEL], &flag)) return;
   // through LDS: consecutive threads read consecutive counts
-  unsigned int h[16];
 #pragma unroll
   for (int b = 0; b < 16; ++b) h[b] = agent_get(&st->ghist[LEVEL][tid + big::THREADS * b]);
 #pragma unroll
@@ -1023,13 +1052,15 @@ __global__ __launch_bounds__(big::THREADS) void topk_count_kernel(const float* s
   __shared__ unsigned int low[64], gts, flag, s_low, s_above;
   __shared__ int wtot[8];
   const int tid = threadIdx.x;
+  const long long beg = (long long)blockIdx.x * chunk, end = beg + chunk < n ? beg + chunk : n;
+  BigTrip first;
+  first.load(score, beg + 8 * tid, end, vec);
   if (tid < 64) low[tid] = 0;
   if (tid == 0) gts = 0;
   const unsigned int prefix = st->prefix[1];
   __syncthreads();
-  const long long beg = (long long)blockIdx.x * chunk, end = beg + chunk < n ? beg + chunk : n;
   unsigned int above = 0;
-  big_scan(score, beg, end, vec, [&](unsigned int key) {
+  big_scan(first, score, beg, end, vec, [&](unsigned int key) {
     const unsigned int p = key >> 6;
     above += p > prefix ? 1u : 0u;
     if (p == prefix) atomicAdd(&low[key & 63u], 1u);
@@ -1090,30 +1121,22 @@ __global__ __launch_bounds__(big::THREADS) void topk_count_kernel(const float* s
 }
 
 // mask and ascending indices of [beg, end): the keys above thr and the first eqkeep equal to it; run = kept entries before beg
-__device__ __forceinline__ void big_write(const float* score, long long beg, long long end, int vec, int group, uint8_t* mask, int32_t* idx,
+__device__ __forceinline__ void big_write(const BigTrip& first, const float* score, long long beg, long long end, int vec, int group, uint8_t* mask, int32_t* idx,
                                           unsigned int thr, unsigned int eqkeep, unsigned int run, int* wtot) {
   unsigned int eqrun = 0;
+  BigTrip t = first;
   for (long long base = beg; base < end; base += 8 * big::THREADS) {
     const long long i0 = base + 8 * (long long)threadIdx.x;
-    const bool whole = vec && i0 + 8 <= end;
-    unsigned int gt = 0, eq = 0;
-    if (whole) {
-      const float4 a = *(const float4*)(score + i0), b = *(const float4*)(score + i0 + 4);
-      const float x[8] = {a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w};
-#pragma unroll
-      for (int e = 0; e < 8; ++e) {
-        const unsigned int key = score_key(x[e]);
-        gt |= (key > thr ? 1u : 0u) << e;
-        eq |= (key == thr ? 1u : 0u) << e;
-      }
-    } else {
-      for (int e = 0; e < 8; ++e)
-        if (i0 + e < end) {
-          const unsigned int key = score_key(score[i0 + e]);
-          gt |= (key > thr ? 1u : 0u) << e;
-          eq |= (key == thr ? 1u : 0u) << e;
-        }
-    }
+    const bool whole = t.whole;
+    unsigned int gt = 0, eq = 0, e8 = 0;
+    BigTrip next;
+    next.load(score, i0 + 8 * big::THREADS, end, vec);
+    t.each(score, i0, end, [&](unsigned int key) {
+      gt |= (key > thr ? 1u : 0u) << e8;
+      eq |= (key == thr ? 1u : 0u) << e8;
+      ++e8;
+    });
+    t = next;
     // both prefixes in one scan: at most 4096 entries each
     int tot;
     const int pre = block_scan((int)((unsigned)__popc(gt) | ((unsigned)__popc(eq) << 16)), wtot, &tot);
@@ -1147,23 +1170,27 @@ __global__ __launch_bounds__(big::THREADS) void topk_write_kernel(const float* s
                                                                   int32_t* idx, const big::State* st) {
   __shared__ int wtot[8];
   const long long beg = (long long)blockIdx.x * chunk, end = beg + chunk < n ? beg + chunk : n;
-  big_write(score, beg, end, vec, group, mask, idx, st->thr, st->eqkeep[blockIdx.x], st->kpre[blockIdx.x], wtot);
+  BigTrip first;
+  first.load(score, beg + 8 * threadIdx.x, end, vec);
+  big_write(first, score, beg, end, vec, group, mask, idx, st->thr, st->eqkeep[blockIdx.x], st->kpre[blockIdx.x], wtot);
 }
 
 // The same select by one workgroup with its histograms in LDS, for a caller of groups (group > 1) who has set no workspace
 // large enough for the four launches.  One CU's loads bound it, so it is taken for nothing else.
 __global__ __launch_bounds__(big::THREADS) void topk_lone_kernel(const float* score, long long n, long long k, int vec, int group, uint8_t* mask,
                                                                  int32_t* idx, float* tau) {
-  __shared__ unsigned int hist[big::BINS];
+  __shared__ __attribute__((aligned(16))) unsigned int hist[big::BINS];
   __shared__ unsigned int wt[8], sel[3];
   __shared__ int wtot[8];
   const int tid = threadIdx.x;
+  BigTrip first;
+  first.load(score, 8 * tid, n, vec);
   unsigned int prefix = 0, krem = (unsigned int)k;
   for (int level = 0; level < 3; ++level) {      // key bits 31 .. 19, 18 .. 6, 5 .. 0
     const int shift = level == 0 ? 19 : level == 1 ? 6 : 0, bits = level == 2 ? 6 : 13;
-    for (int i = tid; i < big::BINS; i += big::THREADS) hist[i] = 0;
+    clear_bins(hist);
     __syncthreads();
-    big_scan(score, 0, n, vec, [&](unsigned int key) {
+    big_scan(first, score, 0, n, vec, [&](unsigned int key) {
       if (level == 0 || key >> (shift + bits) == prefix) atomicAdd(&hist[(key >> shift) & ((1u << bits) - 1u)], 1u);
     });
     __syncthreads();
@@ -1176,7 +1203,7 @@ __global__ __launch_bounds__(big::THREADS) void topk_lone_kernel(const float* sc
     __syncthreads();
   }
   if (tid == 0 && tau) *tau = key_score(prefix);
-  big_write(score, 0, n, vec, group, mask, idx, prefix, krem, 0, wtot);
+  big_write(first, score, 0, n, vec, group, mask, idx, prefix, krem, 0, wtot);
 }
 
 static void launch_topk_small(strp_ctx* ctx, float* score, int n, int k, int group, uint8_t* mask, int32_t* idx, float* tau, const ScoreSource& in,

@@ -36,6 +36,22 @@ def test_topk_edges(ctx, n, k, group, kind):
     assert float(tau.item()) == np.float32(to)
 
 
+@pytest.mark.parametrize("at", [0, 1])
+@pytest.mark.parametrize("n", [96 * 4096, 96 * 4096 + 1, 192 * 8192 + 1, 3 * 256 * 4096 + 8, 8 * 256 * 4096 + 3])
+def test_topk_at_the_edges_of_its_plan(ctx, n, at):
+    """One, two, three and more trips a workgroup, a last workgroup of one score, scores at an address that is no multiple of 16: many
+    equal ones, so that the lower indices decide.  Whole numbers: exact, against a stable sort."""
+    g = torch.Generator(device="cuda").manual_seed(n)
+    score = torch.randint(-500, 500, (n + at,), generator=g, device="cuda").float()[at:]
+    k = n * 3 // 10
+    mask, idx, tau = ctx.strp_mask_topk(score, k)
+    order = torch.sort(score, descending=True, stable=True)
+    want = torch.sort(order.indices[:k]).values
+    assert torch.equal(idx.long(), want)
+    assert int(mask.sum()) == k and bool(mask[want].all())
+    assert float(tau.item()) == float(order.values[k - 1])
+
+
 def test_threshold_of_everything(ctx):
     """k = n: the lowest score that is a number, NaN where none is; k = 0: +inf."""
     s = torch.full((1500,), float("nan"), device="cuda")
