@@ -223,7 +223,7 @@ def main():
             classes[cls] = dict(launches=n, fetch_gb=pc["fetch_gb"] / n, write_gb=pc["write_gb"] / n,
                                 traffic_gb=(pc["fetch_gb"] + pc["write_gb"]) / n, avg_ms_under_counters=pc["ms"] / n)
         md += ["", "Launches shorter than 0.3 ms of the timed region, summed per kernel (the pruned rows' pass rides in "
-               "the first launch of the first factorisation chain, chol_begin_kernel in the table above):", "",
+               "the factorisation of the fc2 system: chol_flow_kernel, or the chain's chol_begin_kernel, in the table above):", "",
                "| kernel | launches | total ms | fetch GB | write GB |", "|---|---|---|---|---|"]
         for name, sh in sorted(short.items(), key=lambda kv: -(kv[1]["fetch_gb"] + kv[1]["write_gb"])):
             if sh["fetch_gb"] + sh["write_gb"] >= 0.05:
