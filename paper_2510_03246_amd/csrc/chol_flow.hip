@@ -778,18 +778,21 @@ static int flow_row_lines(int n) {
   return s;
 }
 static bool flow_lines(const double* M, long long ld) { return ld % 16 == 0 && ((uintptr_t)M & 127) == 0; }
-// us of the whole chain, a launch per panel / one launch:  n = 128 33.6 / 29.8, 256 58.6 / 50.6, 333 82.5 / 69.7, 600 130 / 113,
-// 1013 211 / 175, 1536 322 / 255, 2048 502 / 377, 3277 1105 / 1107, 4096 1823 / 1886: above 3072 the tiles behind the panel bound both, and
-// a tile that is read by whole launches at a time is read from the L2 more often.  With a pass that rides along (cojob.h) the launch is
-// ahead at every order, because the pass runs beside the whole chain and not beside its first tile: steps of 768 x 3072 over 65536
-// tokens 3842 -> 3610 us, 1000 x 2312 over 30011 2185 -> 2028, 2048 x 8192 over 262144 (system of 3277) 54503 -> 53632, 4096 x 16384
-// over 131072 (4915) 83646 -> 81966.  Tiles that share cache lines are read past the caches, for which large orders read too much
-// (Linv is the caller's: where it lies must not decide which bits come out).
-constexpr int FLOW_SHARED_LINES = 22, FLOW_ALONE = 48;
-bool chol_flow_ok(const double* A, int n, long long ld, bool job) {
+// Which way an order goes: by the order alone, so that the factor's bits depend neither on a pass that rides along, on what else is done
+// in the call, nor on where the caller's factor lies.  us, a launch per panel / one launch, rows of whole cache lines:  n = 72 33.1 / 28.5,
+// 136 47.0 / 39.1, 333 84 / 71, 600 133 / 114, 1000 211 / 175, 1408 293 / 237, 2048 505 / 383, 3072 953 / 856, 3600 1392 / 1312,
+// 3968 1702 / 1549, 4416 2213 / 2214, 4912 2945 / 2730, 5312 3589 / 3273, 5888 4750 / 4710, 6272 5658 / 5407, 7168 8252 / 7446,
+// 8192 12537 / 11973, 10240 24.7 / 19.1 ms; tiles that share cache lines, which are read past the caches:  1384 296 / 243,
+// 1672 369 / 291, 2056 564 / 405, 3080 1011 / 898, 4915 3131 / 2729, 8600 15.8 / 13.3 ms.  The launch loses where the stages that its 255
+// other workgroups hold at a time fall from four to three and from three to two (N tasks each), since what the chain waits
+// for next is then handed out later:  4032 1770 / 1797, 4160 1902 / 1983, 4288 2056 / 2082; 5376 3685 / 3854, 5568 4092 / 4238,
+// 5696 4373 / 4430.  With more tiles they bound it themselves, and at the third fall (8064 12.2 / 11.4 ms) it stays ahead.
+// A pass beside it (cojob.h) runs beside the whole launch, or beside the chain's first one: k = 4912, 1.9 GB, 3403 / 3148; in the gap
+// k = 4096, 0.2 GB, 1926 / 1955, 1.6 GB, 2222 / 2171.
+bool chol_flow_ok(int n) {
   const int N = (n + NB - 1) / NB;
   if (n < NB + 8 || flow_lines_needed(N) > NB << flow_row_lines(n)) return false;
-  return N <= FLOW_SHARED_LINES || ((job || N <= FLOW_ALONE) && flow_lines(A, ld));
+  return !(N >= 63 && N <= 68) && !(N >= 84 && N <= 90);
 }
 
 strp_status chol_flow(strp_ctx* ctx, double* A, int n, long long ld, double* Linv, long long ldv, int32_t* status, const CoJob& job) {

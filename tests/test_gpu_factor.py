@@ -184,10 +184,11 @@ def test_refitted_weights_in_the_arrays_of_the_dense_ones():
         assert torch.equal(a, b)
 
 
-@pytest.mark.parametrize("n", [71, 72, 80, 1407, 1424, 2064, 3072])
+@pytest.mark.parametrize("n", [71, 72, 80, 1407, 1409, 1424, 1674, 2064, 3072, 3968, 4353, 5761])
 def test_factor_in_one_launch(n):
-    """Orders at the edges of the one-launch factorisation (host side: check_which_factorisation_runs), a caller's array of whole cache
-    lines and one that shares them: Linv S Linv^T = I (fp64, kappa below 100: n * kappa * 2^-53 < 1e-10), the same bits every time."""
+    """Orders at the edges of the one-launch factorisation (host side: check_which_factorisation_runs), systems of whole cache lines and
+    some that share them, a caller's array at two addresses: Linv S Linv^T = I (fp64, kappa below 100: n * kappa * 2^-53 < 1e-10), the
+    same bits every time."""
     ctx = strp.Context(0)
     ctx.set_workspace(1 << 30)
     g = torch.Generator(device="cuda").manual_seed(n)

@@ -329,10 +329,10 @@ def check_what_the_gram_matrices_cover():
 
 
 def check_what_the_large_systems_cover():
-    """The three tiles of the fp64 products, the factorisation's launches with one, two and three trailing tiles per workgroup, and
-    those of more than 576 trailing tiles, which are back at one."""
+    """The three tiles of the fp64 products, the factorisation in one launch, and its launches per panel with one, two and three trailing
+    tiles per workgroup and with more than 576, which are back at one."""
     lib = Library()
-    tiles, each, long = set(), set(), False
+    tiles, each, long, one = set(), set(), False, 0
     for n, m in LARGE_SYSTEMS:
         st, launches = lib.launches(lambda: lib.lib.strp_refit(lib.h, lib.strp.SIDE_FC2, 1 << 50, n, 1.0, None, 0, 1 << 51, lib.strp.F32, 24, 1 << 52,
                                                                lib.strp.F32, 24, 24, 1 << 53, n, 1 << 54, m, n))
@@ -340,6 +340,9 @@ def check_what_the_large_systems_cover():
         tiles |= {name.split("ILi")[1][:3].rstrip("E") + "x" + name.split("ELi")[1].split("E")[0] for name, _ in launches if "dgemm_kernel" in name}
         steps = [grid[0] for name, grid in launches if "chol_step_kernel" in name]
         N = -(-n // 64)
+        one += sum("chol_flow_kernel" in name for name, _ in launches)
+        if not steps:
+            continue
         assert len(steps) == N or len(steps) == N - 1
         for t, grid in enumerate(steps):
             behind = N - 1 - t
@@ -350,23 +353,32 @@ def check_what_the_large_systems_cover():
                 long |= total > 576
                 each.add(q)
     assert tiles == {"64x32", "64x64", "128x128"}, tiles
-    assert each == {1, 2, 3} and long, each
+    assert each == {1, 2, 3} and long and 0 < one < len(LARGE_SYSTEMS), (each, long, one)
 
 
 def check_which_factorisation_runs():
-    """One launch for orders from 72 to 1408, and above them for rows of whole cache lines: to 3072, or, with the pruned rows' pass of a step
-    riding along, any.  A launch per panel otherwise."""
+    """One launch or a launch per panel by the order alone: not by a pruned rows' pass that rides along, where rows end or where the
+    caller's factor lies, so none of these changes the factor's bits."""
     lib = Library()
     strp = lib.strp
-    for n, one in [(64, False), (71, False), (72, True), (200, True), (1408, True), (1409, False), (1424, True), (3072, True), (3088, False)]:
-        st, launches = lib.launches(lambda: lib.lib.strp_refit(lib.h, strp.SIDE_FC2, 1 << 50, n, 1.0, None, 0, 1 << 51, strp.F32, 24, 1 << 52, strp.F32,
-                                                               24, 24, 1 << 53, n, 1 << 54, 8, n))
-        assert st == strp.OK
-        flow, steps = (sum(name in x[0] for x in launches) for name in ("chol_flow_kernel", "chol_begin_kernel"))
-        assert (flow, steps) == (int(one), int(not one)), (n, flow, steps)
+
+    def ran(launches):
+        return tuple(sum(kernel in x for x in launches) for kernel in ("chol_flow_kernel", "chol_begin_kernel"))
+
+    for n, one in [(64, 0), (71, 0), (72, 1), (200, 1), (1408, 1), (1409, 1), (2074, 1), (3072, 1), (3088, 1), (3968, 1), (3969, 0), (4096, 0), (4352, 0),
+                   (4353, 1), (4915, 1), (5312, 1), (5313, 0), (5760, 0), (5761, 1), (8602, 1)]:
+        for chol in (None, 1 << 55, (1 << 55) + 8, (1 << 55) + 16):
+            st, launches = lib.launches(lambda: lib.lib.strp_refit(lib.h, strp.SIDE_FC2, 1 << 50, n, 1.0, chol, 0, 1 << 51, strp.F32, 24, 1 << 52, strp.F32,
+                                                                   24, 24, 1 << 53, n, 1 << 54, 8, n))
+            assert st == strp.OK
+            assert ran([x[0] for x in launches]) == (one, 1 - one), (n, chol)
+        # a whole iteration with pruned rows and without, and the refit alone
+        if n % 8 == 0:
+            for f, stages in ((n + 512, 0), (n, 0), (n + 512, strp.STAGE_SELECT | strp.STAGE_REFIT2)):
+                names = _step_records(lib, 64, f, 4096, n, 1 << 50, stages)[1]
+                assert ran(names) == (one, 1 - one + (stages == 0)), (n, f, stages)
     for d, k, want in [(64, 128, (1, 1)), (768, 1536, (2, 0)), (4096, 4915, (1, 1))]:
-        names = _step_records(lib, d, 16384 if d > 1000 else 4 * d, 4096, k, 1 << 50)[1]
-        assert tuple(sum(kernel in n for n in names) for kernel in ("chol_flow_kernel", "chol_begin_kernel")) == want, (d, k)
+        assert ran(_step_records(lib, d, 16384 if d > 1000 else 4 * d, 4096, k, 1 << 50)[1]) == want, (d, k)
 
 
 def check_tiles_of_the_solves():
