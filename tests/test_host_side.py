@@ -127,7 +127,8 @@ def check_workspace_of_a_module():
 
 # d, f, tokens, kept units; the bytes of workspace that an iteration, and a refit of fc2 alone, need with a launch for each product
 LEAST = [(64, 256, 512, 128, 1094144, 754176), (768, 3072, 65536, 1536, 919566592, 497811968), (64, 1024, 200000, 300, 567143424, 316930304),
-         (136, 520, 1003, 520, 9277184, 8657664), (512, 2048, 64, 100, 10825984, 1321984)]
+         (136, 520, 1003, 520, 9277184, 8657664), (512, 2048, 64, 100, 10825984, 1321984), (64, 4096, 512, 1025, 21295872, 20604160),
+         (2048, 8192, 64, 3281, 601627648, 308078592)]
 
 
 def check_least_workspace_of_a_step():
