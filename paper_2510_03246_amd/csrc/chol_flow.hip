@@ -787,8 +787,9 @@ static bool flow_lines(const double* M, long long ld) { return ld % 16 == 0 && (
 // other workgroups hold at a time fall from four to three and from three to two (N tasks each), since what the chain waits
 // for next is then handed out later:  4032 1770 / 1797, 4160 1902 / 1983, 4288 2056 / 2082; 5376 3685 / 3854, 5568 4092 / 4238,
 // 5696 4373 / 4430.  With more tiles they bound it themselves, and at the third fall (8064 12.2 / 11.4 ms) it stays ahead.
-// A pass beside it (cojob.h) runs beside the whole launch, or beside the chain's first one: k = 4912, 1.9 GB, 3403 / 3148; in the gap
-// k = 4096, 0.2 GB, 1926 / 1955, 1.6 GB, 2222 / 2171.
+// A pass beside it (cojob.h) runs beside the whole launch, or beside the chain's first one: n = 1000 of 2312 units over 30011 tokens 288 / 193,
+// 3281 of 8192 over 65536 1985 / 1691, 4912, 1.9 GB, 3403 / 3148; in the gap 4096, 0.2 GB, 1926 / 1955, 1.6 GB, 2222 / 2171.  With a pass beside
+// them tiles that share lines cost the launch its lead (1000 331, 1544 744 / 728, 3281 2113 / 2043): a step pads its rows (system_ld).
 bool chol_flow_ok(int n) {
   const int N = (n + NB - 1) / NB;
   if (n < NB + 8 || flow_lines_needed(N) > NB << flow_row_lines(n)) return false;

@@ -780,31 +780,56 @@ static ReduceP reduce_to(double* outd, long long ldod) {
   return r;
 }
 
+// Leading dimension of the fc2 system of a step, its factor and both sides of its solve.  The pruned rows' pass runs beside the
+// factorisation, and tiles that share cache lines are read past the caches, from the memory that the pass is bound by; so rows are whole
+// lines wherever the workspace holds them beside the partials of every product's plan (np: planes per operand).  us of the
+// factorisation with its pass, rows padded to 8 / 16, and as a launch per panel:  kept 1000 of 2312 over 30011 tokens 331 / 193, 290;
+// 1160 of 3072 over 65536 512 / 357, 527; 1544 of 4096 744 / 498, 728; 2056 648 / 633, 857; 3281 of 8192 2113 / 1691, 2043; 4915 of 16384 over
+// 131072 5589 / 5501, 7054.  The factor's bits are the same.
+static long long system_ld(Arena a, int d, int s, long long T, int np) {
+  const long long ld = round_up(s, 16);
+  if (ld == f64_ld(s)) return ld;
+  bool fits = true;
+  auto take = [&](Arena& from, size_t bytes) { fits = from.take(bytes) && fits; };
+  take(a, 8 * (size_t)s * ld);
+  for (int i = 0; i < np; ++i) take(a, 2 * plane_elems(s, T));
+  Arena gram = a;
+  take(gram, 4 * nt_partial_elems(s, s, T, 1));
+  take(a, 8 * (size_t)s * ld);
+  take(a, 8 * (size_t)d * ld);
+  Arena chain = a;
+  take(chain, 8 * chol_scratch_elems(s));
+  take(a, 8 * (size_t)d * ld);
+  take(a, 4 * nt_partial_elems(d, s, T, 0));
+  return fits ? ld : f64_ld(s);
+}
+
 // Solve Wsub (Gram + lam I) = R with R = Lhs Rhs^T over the tokens.
 struct RefitIn {
   const float* Gram; long long ldg;       // fp32 Gram (used when sys_ready == 0)
-  double* sys; int sys_ready;             // [n x f64_ld(n)] fp64 scratch: 0 = empty, 1 = holds Gram + lam I
+  long long ld;                           // leading dimension of sys and R
+  double* sys; int sys_ready;             // [n x ld] fp64 scratch: 0 = empty, 1 = holds Gram + lam I
   double* Linv; long long ldl; int linv_ready;   // [n x ldl] fp64 inverse of the Cholesky factor (output, or input if linv_ready)
   double lam; const double* lam_dev;
   PlaneOp Lhs, Rhs;
   int m, n; long long T;
-  double* R; int r_ready;                 // [m x f64_ld(n)] the right-hand side (null: taken from the arena); 1: it has been formed
+  double* R; int r_ready;                 // [m x ld] the right-hand side (null: taken from the arena); 1: it has been formed
 };
 
-// Factor the system in `sys` (leading dimension f64_ld(n), holds Gram + lam I) and leave the inverse of its Cholesky factor in Linv.
-static strp_status factor_and_invert(strp_ctx* ctx, Arena arena, double* sys, int n, double* Linv, long long ldl) {
+// Factor the system in `sys` (leading dimension ld, holds Gram + lam I) and leave the inverse of its Cholesky factor in Linv.
+static strp_status factor_and_invert(strp_ctx* ctx, Arena arena, double* sys, int n, long long ld, double* Linv, long long ldl) {
   STRP_TAKE(ctx, arena, sub, double, chol_scratch_elems(n));
-  return chol_inverse(ctx, sys, n, f64_ld(n), sub, Linv, ldl, ctx->status_dev);
+  return chol_inverse(ctx, sys, n, ld, sub, Linv, ldl, ctx->status_dev);
 }
 
 // clear: bytes of out.W to zero first, once everything of the caller's has been read (W may be the array that holds Gram)
 static strp_status ridge_solve(strp_ctx* ctx, Arena& arena, const RefitIn& in, const WeightsOut& out, size_t clear = 0) {
   const int n = in.n, m = in.m;
-  const long long ld = f64_ld(n);
+  const long long ld = in.ld;
   const bool factor = !in.linv_ready;
   if (factor) {
     if (in.sys_ready == 0) STRP_TRY(f32_to_f64_ridge(ctx, in.Gram, in.ldg, in.sys, ld, n, in.lam, in.lam_dev));
-    STRP_TRY(factor_and_invert(ctx, arena, in.sys, n, in.Linv, in.ldl));
+    STRP_TRY(factor_and_invert(ctx, arena, in.sys, n, ld, in.Linv, in.ldl));
   }
   double* R = in.R;
   if (!R) {
@@ -874,7 +899,7 @@ static strp_status refit_both(strp_ctx* ctx, Arena& arena, const RefitsIn& in, c
   STRP_TRY(split_act_pair(ctx, in.A, in.Z, in.lda, in.idx, s, T, At, Zt, Zc));
   STRP_TRY(launch_gemm_group(ctx, p, 3));
   STRP_TRY(launch_splitk_reduce_group(ctx, r, 3));
-  STRP_TRY(factor_and_invert(ctx, a2, G, s, Ginv, lds));
+  STRP_TRY(factor_and_invert(ctx, a2, G, s, lds, Ginv, lds));
   return apply_inverse_right_pair(ctx, SolveIn{Ginv, s, lds, R2, d, lds, tmp2, w2}, SolveIn{in.Linv1, d, d, R1, s, ldd, tmp1, w1});
 }
 
@@ -1032,7 +1057,7 @@ strp_status strp_refit(strp_ctx* ctx, strp_side side, const float* Gram, int32_t
     STRP_TRY(make_t_planes(ctx, arena, Lhs, lhs_dtype, ld_lhs, idx, s, T, 0, planes_for(lhs_dtype, prec), &ri.Lhs));
     STRP_TRY(make_t_planes(ctx, arena, Rhs, rhs_dtype, ld_rhs, nullptr, in, T, 0, planes_for(rhs_dtype, prec), &ri.Rhs));
   }
-  ri.m = m; ri.n = n; ri.T = T;
+  ri.m = m; ri.n = n; ri.ld = f64_ld(n); ri.T = T;
   STRP_TRY(ridge_solve(ctx, arena, ri, WeightsOut{side, idx, W, in, nullptr, 0, nullptr, nullptr}, sizeof(float) * (size_t)out * (size_t)in));
   return chol && !chol_direct ? copy_f64(ctx, ri.Linv, ri.ldl, chol, n, n) : STRP_OK;
 }
@@ -1124,7 +1149,7 @@ strp_status strp_module_init(strp_ctx* ctx, const strp_module_desc* desc, strp_m
       STRP_TAKE(ctx, a2, scratch, double, (size_t)d * d);
       Linv = scratch;
     }
-    STRP_TRY(factor_and_invert(ctx, a2, Hd, d, Linv, d));
+    STRP_TRY(factor_and_invert(ctx, a2, Hd, d, d, Linv, d));
     if (Linv != st->cholH) STRP_TRY(copy_f64(ctx, Linv, d, st->cholH, d, d));
   }
   {  // last: fp32 weights may be refitted in the arrays of the dense ones
@@ -1271,7 +1296,7 @@ strp_status strp_admm_step(strp_ctx* ctx, const strp_module_desc* desc, strp_mod
     // the fc2 weights are there
   } else if (stages & STRP_STAGE_REFIT2) {
     Arena a2 = arena;
-    const long long lds = f64_ld(s);
+    const long long lds = system_ld(arena, d, s, T, npa);
     STRP_TAKE(ctx, a2, Gd, double, (size_t)s * lds);
     PlaneOp Arow;
     STRP_TRY(make_t_planes(ctx, a2, st->A, STRP_F32, lda, st->idx, s, T, 0, npa, &Arow));
@@ -1284,7 +1309,7 @@ strp_status strp_admm_step(strp_ctx* ctx, const strp_module_desc* desc, strp_mod
     ri.sys = Gd; ri.sys_ready = 1; ri.Linv = Ginv; ri.ldl = lds; ri.linv_ready = 0;
     ri.Lhs = operand_for(ctx, STRP_PROD_RHS2, 0, cv.Yt);
     ri.Rhs = operand_for(ctx, STRP_PROD_RHS2, 1, Arow);
-    ri.m = d; ri.n = s; ri.T = T;
+    ri.m = d; ri.n = s; ri.ld = lds; ri.T = T;
     STRP_TAKE(ctx, a2, R2, double, (size_t)d * lds);
     const PlaneOp Gp = operand_for(ctx, STRP_PROD_GRAM, 0, Arow), Gq = operand_for(ctx, STRP_PROD_GRAM, 1, Arow);
     const size_t room = a2.room() / sizeof(float);
@@ -1346,7 +1371,7 @@ strp_status strp_admm_step(strp_ctx* ctx, const strp_module_desc* desc, strp_mod
     ReduceP r = reduce_to(Md, d);
     r.ridge = params->beta / params->alpha; r.factored = 1;
     STRP_TRY(nt_product(ctx, a2, W2Sp, W2Sp, d, d, sp, 1, r));
-    STRP_TRY(factor_and_invert(ctx, a2, Md, d, Linv, d));
+    STRP_TRY(factor_and_invert(ctx, a2, Md, d, d, Linv, d));
     // M is well conditioned (its spectrum lies in [beta/alpha, beta/alpha + |W|^2]): form M^-1 = Linv^T Linv
     // (lower half, fp64) and B = W^T M^-1 on the fp16-split matrix cores instead of a third fp64 solve
     STRP_TRY(gram_of_inverse(ctx, Linv, d, d, Md, d, wmax + MAX_MI));
@@ -1407,7 +1432,7 @@ strp_status strp_admm_step(strp_ctx* ctx, const strp_module_desc* desc, strp_mod
     ri.Linv = st->cholH; ri.ldl = d; ri.linv_ready = 1;
     ri.Lhs = operand_for(ctx, STRP_PROD_RHS1, 0, Zrow);
     ri.Rhs = operand_for(ctx, STRP_PROD_RHS1, 1, cv.Xt);
-    ri.m = s; ri.n = d; ri.T = T;
+    ri.m = s; ri.n = d; ri.ld = f64_ld(d); ri.T = T;
     STRP_TRY(ridge_solve(ctx, a2, ri, w1out));
   } else if (W1S) {
     STRP_TRY(gather_weights(ctx, w1out, s, d));

@@ -150,6 +150,38 @@ def check_least_workspace_of_a_step():
             assert lib.lib.strp_admm_step(lib.h, C.byref(desc), C.byref(st), C.byref(p), None) == strp.OK, (d, f, T, k, ws, lib.lib.strp_last_error(lib.h))
 
 
+def check_rows_of_the_fc2_system():
+    """Rows of whole cache lines (16 doubles) where the workspace is what the library asks for, of whole pairs of 16-byte pieces (8) on
+    the least: FlowP::ld of the first factorisation."""
+    lib = Library()
+    strp = lib.strp
+    lib.fake.fake_word.restype = C.c_uint64
+    lib.fake.fake_watch(b"chol_flow_kernel", 0, 8)
+    seen = set()
+    for d, f, T, k, *least in [(d, f, T, k) for d, f, T, k_max in MODULES for k in {k_max or f, (k_max or f) // 3 + 1, 73, 129}] + LEAST:
+        if k > f or k < 72:
+            continue
+        ld = (T + 7) // 8 * 8
+        desc = strp.ModuleDesc(d, f, T, ld, ld, strp.F32, strp.F32, k)
+        st = strp.ModuleState()
+        for name, kind in strp.ModuleState._fields_:
+            if kind is C.c_void_p:
+                setattr(st, name, 1 << 50)
+        p = strp.Params(1.0, 1.0, 0.01, strp.GAIN, 1, k, 0)
+        need = lib.lib.strp_workspace_bytes(C.byref(desc))
+        lib.workspace(need)
+        assert lib.lib.strp_module_init(lib.h, C.byref(desc), C.byref(st), C.byref(p)) == strp.OK
+        for p.stages, ws, pad in [(strp.STAGE_REFIT2 | strp.STAGE_SELECT, need, 16)] + [(strp.STAGE_REFIT2, w, 8) for w in least[1:]]:
+            lib.workspace(ws)
+            status, launches = lib.launches(lambda: lib.lib.strp_admm_step(lib.h, C.byref(desc), C.byref(st), C.byref(p), None))
+            assert status == strp.OK
+            lds = [lib.fake.fake_word(i) for i, x in enumerate(launches) if "chol_flow_kernel" in x[0]]
+            if lds and not (pad == 8 and k % 16 == 0):
+                assert lds == [-(-k // pad) * pad], (d, f, T, k, ws, lds)
+                seen.add((pad, 0 < k % 16 <= 8))
+    assert seen >= {(8, True), (16, True), (16, False)}, seen
+
+
 def _step_records(lib, d, f, T, k, ws, stages=0):
     """What one iteration enqueues on a workspace of ws bytes: [(class, algorithmic flops, algorithmic bytes)] and the kernels' names"""
     strp = lib.strp
@@ -442,7 +474,7 @@ def check_weight_statistics_counter():
     assert counter(lib.h) not in (0, a, b, c)
 
 
-CHECKS = [check_which_factorisation_runs, check_tiles_of_the_solves, check_weight_statistics_counter, check_weight_statistics_without_a_counter, check_what_the_gram_matrices_cover, check_what_the_large_systems_cover, check_selection_of_a_very_wide_module, check_weight_statistics_arguments, check_weight_statistics_workgroups, check_chains, check_workspace_of_a_module, check_least_workspace_of_a_step, check_work_of_shared_launches, check_profile_classes, check_workspace_of_a_factorisation, check_cached_factor_needs_no_alignment]
+CHECKS = [check_which_factorisation_runs, check_tiles_of_the_solves, check_weight_statistics_counter, check_weight_statistics_without_a_counter, check_what_the_gram_matrices_cover, check_what_the_large_systems_cover, check_selection_of_a_very_wide_module, check_weight_statistics_arguments, check_weight_statistics_workgroups, check_chains, check_workspace_of_a_module, check_least_workspace_of_a_step, check_rows_of_the_fc2_system, check_work_of_shared_launches, check_profile_classes, check_workspace_of_a_factorisation, check_cached_factor_needs_no_alignment]
 
 
 @pytest.fixture(scope="session")
