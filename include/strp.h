@@ -40,7 +40,9 @@ typedef enum {
   STRP_ENOMEM = 2,     /* workspace missing or too small                                        */
   STRP_ENOTPD = 3,     /* Cholesky met a non-positive pivot                                      */
   STRP_ENONFINITE = 4, /* NaN/Inf, or a magnitude above 65504 (the fp16 operand range), in an input       */
-  STRP_EHIP = 5,       /* a HIP runtime call failed                                               */
+  STRP_EHIP = 5,       /* a HIP runtime call failed; as a device status (strp_poll, strp_report): a     */
+                       /* factorisation's workgroups waited ten seconds for each other and gave up:     */
+                       /* what the call wrote since, state included, is not to be used                   */
   STRP_ESTATE = 6      /* call sequence error (e.g. admm_step before module_init)                 */
 } strp_status;
 
@@ -80,7 +82,8 @@ strp_status strp_set_product_planes(strp_ctx* ctx, strp_product product, int32_t
  * Calls on one workspace run one after the other on the context's stream.  Captured calls that are replayed at the same time
  * need workspaces of their own, set before each is captured. */
 strp_status strp_set_workspace(strp_ctx* ctx, void* dev_ptr, size_t bytes);
-/* Synchronise the stream and return the device status word (STRP_OK, STRP_ENOTPD, ...). */
+/* Synchronise the stream and return the device status word (STRP_OK, STRP_ENOTPD, STRP_ENONFINITE, STRP_EHIP), which it clears;
+ * also STRP_EHIP where the synchronisation itself fails. */
 strp_status strp_poll(strp_ctx* ctx);
 
 /* Optional per-kernel timing (HIP events on the context's stream), for benchmarks and profiles.
