@@ -779,6 +779,12 @@ static ReduceP reduce_to(double* outd, long long ldod) {
   r.outd = outd; r.ldod = ldod;
   return r;
 }
+// a system that factor_and_invert takes next: with the zeros that chol_inverse wants, where the one launch keeps its counters
+static ReduceP reduce_to_system(double* sys, long long ld) {
+  ReduceP r = reduce_to(sys, ld);
+  r.factored = 1;
+  return r;
+}
 
 // Leading dimension of the fc2 system of a step, its factor and both sides of its solve.  The pruned rows' pass runs beside the
 // factorisation, and tiles that share cache lines are read past the caches, from the memory that the pass is bound by; so rows are whole
@@ -816,7 +822,7 @@ struct RefitIn {
   double* R; int r_ready;                 // [m x ld] the right-hand side (null: taken from the arena); 1: it has been formed
 };
 
-// Factor the system in `sys` (leading dimension ld, holds Gram + lam I) and leave the inverse of its Cholesky factor in Linv.
+// Factor the system in `sys` (leading dimension ld, holds Gram + lam I from reduce_to_system or f32_to_f64_ridge) and leave the inverse of its Cholesky factor in Linv.
 static strp_status factor_and_invert(strp_ctx* ctx, Arena arena, double* sys, int n, long long ld, double* Linv, long long ldl) {
   STRP_TAKE(ctx, arena, sub, double, chol_scratch_elems(n));
   return chol_inverse(ctx, sys, n, ld, sub, Linv, ldl, ctx->status_dev);
@@ -890,8 +896,8 @@ static strp_status refit_both(strp_ctx* ctx, Arena& arena, const RefitsIn& in, c
   GemmP p[3] = {nt_plan(operand_for(ctx, STRP_PROD_GRAM, 0, At), operand_for(ctx, STRP_PROD_GRAM, 1, At), s, s, T, 1, room),
                 nt_plan(operand_for(ctx, STRP_PROD_RHS2, 0, in.Y), operand_for(ctx, STRP_PROD_RHS2, 1, At), d, s, T, 0, room),
                 nt_plan(operand_for(ctx, STRP_PROD_RHS1, 0, Zt), operand_for(ctx, STRP_PROD_RHS1, 1, in.X), s, d, T, 0, room)};
-  ReduceP r[3] = {reduce_to(G, lds), reduce_to(R2, lds), reduce_to(R1, ldd)};
-  r[0].ridge_dev = in.lam2_dev; r[0].factored = 1;
+  ReduceP r[3] = {reduce_to_system(G, lds), reduce_to(R2, lds), reduce_to(R1, ldd)};
+  r[0].ridge_dev = in.lam2_dev;
   if (!group_fits(a2, p, r, 3)) return STRP_OK;
   *done = 1;
   arena = keep;
@@ -1138,8 +1144,8 @@ strp_status strp_module_init(strp_ctx* ctx, const strp_module_desc* desc, strp_m
     Arena a2 = arena;
     STRP_TAKE(ctx, a2, diag, double, (size_t)d);
     STRP_TAKE(ctx, a2, Hd, double, (size_t)d * d);
-    ReduceP r = reduce_to(Hd, d);
-    r.outf = st->H; r.ldof = d; r.diag = diag; r.factored = 1;
+    ReduceP r = reduce_to_system(Hd, d);
+    r.outf = st->H; r.ldof = d; r.diag = diag;
     STRP_TRY(nt_product(ctx, a2, cv.Xt, cv.Xt, d, d, T, 1, r));
     hipLaunchKernelGGL(scaled_sum_kernel, dim3(1), dim3(1024), 0, ctx->stream, (const double*)diag, 1, d, params->delta / (double)d, sc + SC_TRH,
                        sc + SC_LAM1, Hd, (long long)d, d);
@@ -1300,8 +1306,8 @@ strp_status strp_admm_step(strp_ctx* ctx, const strp_module_desc* desc, strp_mod
     STRP_TAKE(ctx, a2, Gd, double, (size_t)s * lds);
     PlaneOp Arow;
     STRP_TRY(make_t_planes(ctx, a2, st->A, STRP_F32, lda, st->idx, s, T, 0, npa, &Arow));
-    ReduceP r = reduce_to(Gd, lds);
-    r.ridge_dev = sc + SC_LAM2; r.factored = 1;
+    ReduceP r = reduce_to_system(Gd, lds);
+    r.ridge_dev = sc + SC_LAM2;
     const Arena first = a2;                 // of a Gram product by itself: its partials are gone before the factor and R2 are written
     RefitIn ri;
     memset(&ri, 0, sizeof(ri));
@@ -1368,8 +1374,8 @@ strp_status strp_admm_step(strp_ctx* ctx, const strp_module_desc* desc, strp_mod
                           2 * ((plane_elems(d, d) * 2 + al) & ~al) + 4096;
     STRP_TAKE(ctx, arena, cblock, char, cbytes);
     Arena a2(cblock, cbytes);
-    ReduceP r = reduce_to(Md, d);
-    r.ridge = params->beta / params->alpha; r.factored = 1;
+    ReduceP r = reduce_to_system(Md, d);
+    r.ridge = params->beta / params->alpha;
     STRP_TRY(nt_product(ctx, a2, W2Sp, W2Sp, d, d, sp, 1, r));
     STRP_TRY(factor_and_invert(ctx, a2, Md, d, d, Linv, d));
     // M is well conditioned (its spectrum lies in [beta/alpha, beta/alpha + |W|^2]): form M^-1 = Linv^T Linv

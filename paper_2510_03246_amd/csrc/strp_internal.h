@@ -172,7 +172,7 @@ struct ReduceP {
   int splits, M, N, triangle;
   float* outf; long long ldof;
   double* outd; long long ldod;
-  int factored;          // outd is for chol_inverse: zeros in columns 64 .. of rows 0 .. 63
+  int factored;          // outd is for chol_inverse: zeros in columns 64 .. of rows 0 .. 63 (reduce_to_system)
   double* diag;
   int accumulate;
   double ridge; const double* ridge_dev;
@@ -224,8 +224,10 @@ static inline size_t chol_scratch_elems(long long n) {
   return (size_t)(tiles < 4 ? tiles : 4) * NB * NB;
 }
 // Linv [n x n, ldv] = L^-1 (upper part zero) of the SPD matrix A [n x n, ld] = L L^T whose lower triangle is given (the
-// caller has added the ridge) and destroyed, with zeros in columns 64 .. of rows 0 .. 63.  sub: chol_scratch_elems(n) doubles of scratch.  ld and ldv even, A and Linv
-// 16-byte aligned.  A pivot that is not positive sets ENOTPD in status (device word).
+// caller has added the ridge) and destroyed.  Columns 64 .. of rows 0 .. 63 of A hold zeros, which become counters: with anything else
+// there tiles are taken for finished and the factor is wrong, so A comes from a reduction with `factored` or from
+// f32_to_f64_ridge.  sub: chol_scratch_elems(n) doubles of scratch.  ld and ldv even, A and Linv 16-byte aligned.  A pivot that
+// is not positive sets ENOTPD in status (device word); a wait that takes ten seconds, EHIP.
 strp_status chol_inverse(strp_ctx* ctx, double* A, int n, long long ld, double* sub, double* Linv, long long ldv, int32_t* status);
 // The same in one launch, for the orders that are faster so.
 bool chol_flow_ok(int n);
@@ -261,7 +263,7 @@ int gather_blocks(int m, int n);
 strp_status gram_of_inverse(strp_ctx* ctx, const double* Linv, int n, long long ldl, double* S, long long lds, unsigned int* maxbits);
 // dst [n x n, ldd] = src [n x n, lds]
 strp_status copy_f64(strp_ctx* ctx, const double* src, long long lds, double* dst, long long ldd, int n);
-// Ad[i*ld+j] = (double)Af[i*ldf+j] + (i==j ? lam (or *lam_dev if non-null) : 0)
+// Ad[i*ld+j] = (double)Af[i*ldf+j] + (i==j ? lam (or *lam_dev if non-null) : 0), for chol_inverse: zeros in columns 64 .. of rows 0 .. 63
 strp_status f32_to_f64_ridge(strp_ctx* ctx, const float* Af, long long ldf, double* Ad, long long ld, int n,
                              double lam, const double* lam_dev);
 

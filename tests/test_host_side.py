@@ -182,6 +182,70 @@ def check_rows_of_the_fc2_system():
     assert seen >= {(8, True), (16, True), (16, False)}, seen
 
 
+def check_systems_of_the_factorisations():
+    """A factorisation in one launch keeps its counters in the system's columns 64 .. of rows 0 .. 63: what wrote the system last,
+    a reduction that says so (ReduceP::factored) or the conversion of a Gram matrix, has left zeros there."""
+    lib = Library()
+    strp = lib.strp
+    lib.fake.fake_word.restype = C.c_uint64
+    OUTD, FACTORED, REDUCEP = 40, 56, 112             # bytes: ReduceP::outd, ::factored, sizeof
+    WATCHES = {"system": (b"chol_flow_kernel", 0, 0), "ridge": (b"f32_to_f64_ridge_kernel", 2, 0)}
+    for i in range(3):
+        WATCHES[f"outd{i}"] = (b"splitk_reduce_group_kernel", 0, REDUCEP * i + OUTD)
+        WATCHES[f"factored{i}"] = (b"splitk_reduce_group_kernel", 0, REDUCEP * i + FACTORED)
+    WATCHES["outd"] = (b"splitk_reduce_kernel", 0, OUTD)
+    WATCHES["factored"] = (b"splitk_reduce_kernel", 0, FACTORED)
+
+    def words(call, watch):
+        lib.fake.fake_watch(*WATCHES[watch])
+        st, launches = lib.launches(call)
+        assert st == strp.OK
+        return [lib.fake.fake_word(i) if WATCHES[watch][0].decode() in x[0] else None for i, x in enumerate(launches)]
+
+    def check(call):
+        got = {w: words(call, w) for w in WATCHES}
+        factored = 0
+        for at, system in enumerate(got["system"]):
+            if system is None:
+                continue
+            zeros = None
+            for i in range(at):
+                for q in ("", "0", "1", "2"):
+                    if got["outd" + q][i] == system:
+                        zeros = bool(got["factored" + q][i] & 0xffffffff)
+                if got["ridge"][i] == system:
+                    zeros = True
+            assert zeros, (at, hex(system))
+            factored += 1
+        return factored
+
+    for n in (72, 1000, 3072):
+        assert check(lambda: lib.lib.strp_refit(lib.h, strp.SIDE_FC2, 1 << 50, n, 1.0, None, 0, 1 << 51, strp.F32, 24, 1 << 52, strp.F32, 24, 24, 1 << 53, n,
+                                                1 << 54, 8, n)) == 1
+    for d, f, T, k in [(64, 256, 512, 128), (128, 520, 1003, 131), (768, 3072, 65536, 1536), (1000, 2312, 30011, 1013)]:
+        ld = (T + 7) // 8 * 8
+        desc = strp.ModuleDesc(d, f, T, ld, ld, strp.F32, strp.F32, k)
+
+        def state():
+            st = strp.ModuleState()
+            for name, kind in strp.ModuleState._fields_:
+                if kind is C.c_void_p:
+                    setattr(st, name, 1 << 50)
+            return st
+
+        p = strp.Params(1.0, 1.0, 0.01, strp.GAIN, 1, k, 0)
+        assert check(lambda: lib.lib.strp_module_init(lib.h, C.byref(desc), C.byref(state()), C.byref(p))) == (d >= 72)
+        for stages in (0, strp.STAGE_SELECT | strp.STAGE_REFIT2, strp.STAGE_SELECT | strp.STAGE_AUPD):
+            p.stages = stages
+
+            def step():
+                st = state()
+                st.precision = 1 + strp.PREC_SPLIT
+                return lib.lib.strp_admm_step(lib.h, C.byref(desc), C.byref(st), C.byref(p), None)
+
+            assert check(step) == (stages != strp.STAGE_SELECT | strp.STAGE_AUPD) + (d >= 72 and not stages & strp.STAGE_REFIT2)
+
+
 def _step_records(lib, d, f, T, k, ws, stages=0):
     """What one iteration enqueues on a workspace of ws bytes: [(class, algorithmic flops, algorithmic bytes)] and the kernels' names"""
     strp = lib.strp
@@ -474,7 +538,7 @@ def check_weight_statistics_counter():
     assert counter(lib.h) not in (0, a, b, c)
 
 
-CHECKS = [check_which_factorisation_runs, check_tiles_of_the_solves, check_weight_statistics_counter, check_weight_statistics_without_a_counter, check_what_the_gram_matrices_cover, check_what_the_large_systems_cover, check_selection_of_a_very_wide_module, check_weight_statistics_arguments, check_weight_statistics_workgroups, check_chains, check_workspace_of_a_module, check_least_workspace_of_a_step, check_rows_of_the_fc2_system, check_work_of_shared_launches, check_profile_classes, check_workspace_of_a_factorisation, check_cached_factor_needs_no_alignment]
+CHECKS = [check_systems_of_the_factorisations, check_which_factorisation_runs, check_tiles_of_the_solves, check_weight_statistics_counter, check_weight_statistics_without_a_counter, check_what_the_gram_matrices_cover, check_what_the_large_systems_cover, check_selection_of_a_very_wide_module, check_weight_statistics_arguments, check_weight_statistics_workgroups, check_chains, check_workspace_of_a_module, check_least_workspace_of_a_step, check_rows_of_the_fc2_system, check_work_of_shared_launches, check_profile_classes, check_workspace_of_a_factorisation, check_cached_factor_needs_no_alignment]
 
 
 @pytest.fixture(scope="session")
