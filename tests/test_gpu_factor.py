@@ -1,5 +1,6 @@
-"""The fp64 factorisation chain (factor and inverse of the triangular factor in one pass over 64 x 64 tiles) and the two-stage
-solve, through strp_refit, at the orders where the tiling can go wrong."""
+"""The fp64 factorisation (factor and inverse of the triangular factor in one pass over 64 x 64 tiles, in one launch or in a launch
+per panel) and the two-stage solve, through strp_refit, at the orders where the tiling can go wrong.  Orders below 72, 3969 .. 4352
+and 5313 .. 5760 take the launches per panel (host side: check_which_factorisation_runs)."""
 import numpy as np
 import pytest
 import torch
@@ -49,9 +50,11 @@ def test_factor_inverse_and_solve(ctx, n, m):
     assert torch.equal(W, W2)
 
 
-@pytest.mark.parametrize("n", [64, 128, 190, 200, 333, 768])
+@pytest.mark.parametrize("n", [64, 67, 128, 190, 200, 333, 768, 1409, 3969])
 def test_factor_is_the_same_every_time(ctx, n):
-    """No workgroup of a launch reads what another one of it writes: the same bits and status in every run."""
+    """In one launch a workgroup reads what others write once they have said so, and sums in a fixed order; of the launches per panel (64, 67,
+    3969) none reads what another workgroup of the launch writes.  The same bits and status in every run."""
+    ctx.ensure_workspace(1 << 29)
     g = torch.Generator(device="cuda").manual_seed(n)
     B = torch.randn((n, n + 8), generator=g, device="cuda") / (n + 8) ** 0.5
     G = B @ B.T
@@ -125,6 +128,40 @@ def test_pivots_that_are_not_positive(ctx, n, bad, kind):
     got = chol.cpu().numpy()
     assert np.isfinite(got).all() and bool(torch.isfinite(W).all())
     assert np.linalg.norm(got - ref) <= 1e-10 * np.linalg.norm(ref)
+
+
+@pytest.mark.parametrize("n,bad", [(71, [64]), (1409, [700, 1408]), (3969, [2000, 3968]), (4100, [63, 64, 4099])])
+@pytest.mark.parametrize("kind", ["zero", "negative"])
+def test_pivots_that_are_not_positive_in_later_panels(n, bad, kind):
+    """The same in panels behind the first, and in the last, ragged one, of either way: a pivot that counts as 1 is that of the system
+    with its diagonal entry moved by the difference, whose factor this is: Linv S' Linv^T = I (eigenvalues between 0.4 and 4, so
+    n * kappa * 2^-53 < 1e-10; the pivot that is replaced, from an fp64 solve, is good to the same)."""
+    ctx = strp.Context(0)
+    ctx.set_workspace(1 << 30)
+    g = torch.Generator(device="cuda").manual_seed(n)
+    B = torch.randn((n, 2 * n), generator=g, device="cuda") / (2 * n) ** 0.5
+    G = (B @ B.T + 0.5 * torch.eye(n, device="cuda")).cpu().numpy()
+    G = np.tril(G) + np.tril(G, -1).T
+    if kind == "zero":
+        for b in bad:
+            G[b, :] = G[:, b] = 0.0
+    S = G.astype(np.float64)
+    for b in bad:
+        pivot = lambda: S[b, b] - (S[b, :b] @ np.linalg.solve(S[:b, :b], S[:b, b]) if b else 0.0)
+        if kind == "negative":
+            G[b, b] -= np.float32(pivot() + 0.5)
+            S[b, b] = G[b, b]
+            assert pivot() < -0.4
+        S[b, b] += 1.0 - pivot()
+    lhs, rhs = (torch.randint(-4, 5, (r, 24), generator=g, device="cuda").float() for r in (9, n))
+    idx = torch.arange(n, dtype=torch.int32, device="cuda")
+    W = torch.empty((9, n), device="cuda")
+    chol = torch.empty((n, n), dtype=torch.float64, device="cuda")
+    ctx.strp_refit(strp.SIDE_FC2, torch.from_numpy(G).cuda(), 0.0, lhs, rhs, 24, idx, W, chol=chol, chol_valid=False)
+    assert ctx.poll() == strp.ENOTPD
+    assert bool(torch.isfinite(chol).all()) and bool(torch.isfinite(W).all()) and torch.count_nonzero(torch.triu(chol, 1)) == 0
+    assert float((chol @ torch.from_numpy(S).cuda() @ chol.T - torch.eye(n, dtype=torch.float64, device="cuda")).abs().max()) <= 1e-10
+    ctx.close()
 
 
 def test_weights_in_the_array_of_their_gram_matrix(ctx):
