@@ -298,19 +298,19 @@ __global__ __launch_bounds__(256 * k_shares(TM, TN), 2) void dgemm_pair_kernel(c
 
 // Tile of a product by its grid: 128 x 128 tiles read the fewest operand bytes per flop but need enough of them to fill
 // the chip; below that the longest tile (whole K) sets the run time and a smaller one ends sooner.  Solves X (L L^T)^-1 of
-// m x n (two products), us with 64 x 32 / 64 x 64 / 128 x 128 tiles of four wavefronts (in brackets the tiles of 64, of 128):
-//   768 x 1536 (288) 104 / 139 / 433;  3000 x 3000 (2209, 576) 1059 / 888 / 1161;  4096 x 4096 (4096, 1024) 2174 / 2119 / 2240;
-//   4096 x 4915 (4928, 1248) 3192 / 3070 / 3088, 65 TFLOP/s;  4864 x 4864 (5776, 1444) 3657 / 3528 / 3528;  5120 x 5120 (6400, 1600)
-//   4219 / 4139 / 4059;  6000 x 6000 (8836, 2209) 7783 / 6968 / 6479;  8602 x 7168 (15120, 3808) 16774 / 14895 / 13089.
+// m x n (two products, rows of whole cache lines), us with 64 x 64 / 128 x 128 tiles (in brackets the tiles of 128):  4096 x 4915 (1248) 3053 / 3231,
+// 64 TFLOP/s;  4915 x 4096 2515 / 2677;  5100 x 5100 (1600) 4065 / 4171;  6000 x 5990 (2209) 6588 / 6628;  6400 x 6300 (2500) 7757 / 7784;
+// 8000 x 5000 (2520) 6090 / 6286;  7000 x 7000 (3025) 11049 / 10630;  8602 x 7168 (3808) 13723 / 13082.
 // Between the two small ones the number of tile rows decides: workgroups go to the 8 XCDs in turn, so that with an even number an
 // XCD meets only some rows of A, again and again, and with an odd one all of them, which costs the tile that reads A for fewer
-// columns.  64 x 32 / 64 x 64, even: 1656 x 2688 (1092) 396 / 404;  2048 x 2458 (1248) 386 / 411;  3072 x 2048 (1536) 398 / 421;
-// 2048 x 3277 (1664) 667 / 692;  2680 x 2880 (1890) 711 / 697;  3448 x 2624 (2214) 799 / 739.  Odd: 1088 x 1656 (442)
-// 133 / 130;  1344 x 1848 (609) 188 / 179;  1728 x 1656 (702) 197 / 189;  2880 x 1144 (810) 158 / 159;  2112 x 2112 (1089) 363 / 327;
-// 2496 x 2496 (1521) 591 / 504.  The lines to 128 x 128 and those of Linv^T Linv stand where tiles of four wavefronts put them:
-// Linv^T Linv (half the tiles, order):  2600 (840) 162 / 158 / 361;  3000 (1104) 249 / 260 / 494;  3400 (1458) 361 / 284 / 616;
-// 6000 (4418, 1104) 1765 / 1328 / 1743;  8192 (8192, 2048) 4195 / 3212 / 3335;  10240 (12800, 3200) 8134 / 6575 / 5665.
-constexpr int DGEMM_T128 = 1450, DGEMM_T128_LOWER = 2500, DGEMM_T64 = 2000, DGEMM_T64_ODD = 680, DGEMM_T64_LOWER = 1200;
+// columns.  64 x 32 / 64 x 64 (tiles of 64), even:  768 x 1536 (288) 80 / 122;  2048 x 2458 (1248) 394 / 407;  1784 x 3611 (1596) 746 / 764;  2048 x 3277
+// (1664) 694 / 699;  1912 x 3637 (1710) 833 / 815;  2424 x 2869 (1710) 645 / 633;  3320 x 2101 (1716) 469 / 473;  2680 x 2869 (1890) 723 / 700.  Of
+// 17 such numbers of rows 11 have 64 x 64 ahead at about 1700 tiles, 3 at 1500.  Odd:  1344 x 1653 (546) 156 / 169;  1088 x 2229 (595) 217 / 226;
+// 1984 x 1205 (589) 134 / 133;  1344 x 1909 (630) 199 / 201;  1728 x 1525 (648) 170 / 166;  960 x 2741 (645) 298 / 283;  576 x 4853 (684) 544 / 505.
+// Linv^T Linv (half the tiles), order, 64 x 32 / 64 x 64:  1536 (288) 41 / 68;  2200 (612) 102 / 120;  2600 (840) 159 / 145;  2800 (968) 152 / 158;
+// 2904 (1058) 208 / 175;  3104 (1200) 251 / 209;  4096 (2048) 514 / 440;  64 x 64 / 128 x 128 (tiles of 128):  7168 (1568) 2180 / 2313;
+// 8192 (2048) 3384 / 3507;  8704 (2312) 3822 / 3812;  9216 (2592) 4554 / 4439;  10240 (3200) 6720 / 6056.
+constexpr int DGEMM_T128 = 2600, DGEMM_T128_LOWER = 2500, DGEMM_T64 = 1700, DGEMM_T64_ODD = 630, DGEMM_T64_LOWER = 1000;
 
 static inline bool aligned_vec(const void* p, long long ld) { return ((uintptr_t)p & 15u) == 0 && (ld & 1) == 0; }
 

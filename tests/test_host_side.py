@@ -20,7 +20,7 @@ CHAINS = [((64, 64, 512), 256), ((128, 128, 2000), 256), ((1536, 1536, 65536), 3
 GRAMS = [(64, 8), (129, 520), (255, 4104), (256, 256), (257, 264), (512, 8200), (640, 70000), (768, 16384), (1025, 2056), (1280, 3000),
          (256, 65536), (512, 65536), (832, 65536), (1280, 16384), (300, 100000)]
 # order of the system and rows of the right-hand side in tests/test_gpu_factor.py where its launches change their shape
-LARGE_SYSTEMS = [(1409, 333), (2113, 65), (3137, 129), (1655, 1697), (2881, 2900), (4099, 4100), (4866, 4870)]
+LARGE_SYSTEMS = [(1409, 333), (2113, 65), (3137, 129), (1655, 1697), (2881, 2900), (4099, 4100), (4866, 4870), (1655, 25613)]
 
 
 class Library:
@@ -479,10 +479,11 @@ def check_which_factorisation_runs():
 
 
 def check_tiles_of_the_solves():
-    """Which tile a solve of m x n takes: below 2000 tiles of 64 x 64 the number of tile rows decides between the two small ones."""
+    """Which tile a solve of m x n takes: below 1700 tiles of 64 x 64 the number of tile rows decides between the two small ones."""
     lib = Library()
-    for m, n, tile in [(768, 1536, "64x32"), (1728, 1400, "64x32"), (1728, 1656, "64x64"), (2496, 2496, "64x64"), (2048, 3277, "64x32"),
-                       (3277, 2048, "64x32"), (2752, 2752, "64x64"), (2944, 2944, "64x64"), (4096, 4915, "64x64"), (5120, 5120, "128x128")]:
+    for m, n, tile in [(768, 1536, "64x32"), (1728, 1400, "64x32"), (1344, 1845, "64x32"), (1344, 1920, "64x64"), (1728, 1656, "64x64"), (2496, 2496, "64x64"),
+                       (2048, 3277, "64x32"), (3277, 2048, "64x32"), (2048, 3393, "64x64"), (2752, 2752, "64x64"), (2944, 2944, "64x64"), (4096, 4915, "64x64"),
+                       (5120, 5120, "64x64"), (6400, 6528, "64x64"), (6528, 6528, "128x128"), (8602, 7168, "128x128")]:
         st, launches = lib.launches(lambda: lib.lib.strp_refit(lib.h, lib.strp.SIDE_FC2, None, 0, 1.0, 1 << 52, 1, 1 << 50, lib.strp.F32, 24, 1 << 51,
                                                                lib.strp.F32, 24, 24, 1 << 53, n, 1 << 54, m, n))
         tiles = {name.split("ILi")[1][:3].rstrip("E") + "x" + name.split("ELi")[1].split("E")[0] for name, _ in launches if "dgemm_kernel" in name}
