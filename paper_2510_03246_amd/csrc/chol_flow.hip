@@ -141,6 +141,7 @@ struct FlowShared {
   double job[2][4][6];
   unsigned int ticket, unit;
 };
+static_assert(sizeof(FlowShared) <= 160 * 1024, "of the CU's LDS 3 KB are left: a workgroup has it to itself");
 
 __device__ __forceinline__ double* flow_at(double* M, long long ld, int i, int k) { return M + (long long)i * NB * ld + (long long)k * NB; }
 

@@ -361,11 +361,9 @@ strp_status gram_of_inverse(strp_ctx* ctx, const double* Linv, int n, long long 
 // because ahead reads what they would replace; the next launch is the last to read them.  A launch costs what P(t + 1) does
 // while the others fit beside it: 5 us for two 64^3 products at the 0.3 TFLOP/s of one CU and their operands, of which the
 // second needs only its first 16 columns before the diagonal tile's chain of 64 pivots can begin, and 6 us for that chain.
-// us a launch up to n = 1013: 17.5 with one workgroup for P(t + 2) and ahead, which took longer than P(t + 1), 14.0 with these
-// apart, 13.0 with fewer stores in the chain, 12.2 with the second product beside the chain; whole chain n = 768 227 -> 158,
-// 1536 460 -> 323, 2048 620 -> 509, 3277 1250 -> 1092.
-// Larger orders are bound by the trailing tiles' traffic (39 us a launch on average at n = 4915).  Two panels per pass over
-// them in every second launch: 3277 and below no faster, 4915 3.04 -> 2.76 ms; not kept for 0.4 ms of a step of 85.
+// us a launch of few tiles: 17.5 with one workgroup for P(t + 2) and ahead, which took longer than P(t + 1), 14.0 with these
+// apart, 13.0 with fewer stores in the chain, 12.2 with the second product beside the chain.  Larger orders are bound by the trailing
+// tiles' traffic: 29 us a launch on average at n = 4096 (1.85 ms), 44 at 5376 (3.69).
 struct StepP {
   double* A; long long ld;
   double* V; long long ldv;     // Linv
@@ -747,10 +745,9 @@ strp_status chol_inverse(strp_ctx* ctx, double* A, int n, long long ld, double* 
   for (int t = 0; t < p.N; ++t) {
     p.t = t;
     const int m = p.N - 1 - t;
-    // up to three tiles each, so that a launch of a small system leaves the critical workgroup a CU of its own; beyond 576
+    // up to three tiles each, so that a launch of few tiles leaves the critical workgroup a CU of its own; beyond 576
     // tiles the launch is theirs and a workgroup that takes several only ends later.  One tile each / up to three below 577 / up to
-    // three below 1025, us for the whole chain: n = 1536 341 / 323 / 325, 2048 517 / 509 / 512, 2458 654 / 639 / 683,
-    // 3277 1107 / 1092 / 1167, 4096 1851 / 1835 / 1876
+    // three below 1025, us for the whole chain of 4096: 1851 / 1835 / 1876
     const int total = step_tiles(p.N, t);
     p.each = (total + 191) / 192;
     if (p.each > 3 || p.each < 1) p.each = 1;

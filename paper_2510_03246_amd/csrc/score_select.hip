@@ -669,7 +669,8 @@ __device__ __forceinline__ void pick_bin(const unsigned int (&h)[B], unsigned in
 // of each of the bin's keys among themselves; a bin of more than 128 keys is stretched again (ranking 900 took 25 us, a round 1.5).  The k-th key
 // and its index decide every element: kept = larger, or equal with no higher index.
 // Before (strided keys, a scan of 256 counts, LDS permutes, up to 1024 keys ranked) / now: 16384 scores 13.9 / 9.3 us with the launch;
-// in a step, with the scores formed first, 2312 35.7 / 11.3 and 256 8.3 / 5.7.
+// in a step, with the scores formed first, 2312 35.7 / 11.3 and 256 8.3 / 5.7; read again in each phase, 20480 23.1 / 18.9, 32768 31.7 / 19.9,
+// 32769 35.7 / 26.9, 49152 44.4 / 27.5, 65536 57.9 / 39.2 (65537, in four launches, 29.1 / 21.3).
 // With in.sums the scores (group = 1) are formed here first, with their mean; rest takes the indices that are not kept.
 struct ScoreSource {
   const double* sums;       // [4][n], or null: the scores are given
