@@ -349,6 +349,8 @@ strp_status strp_module_init(strp_ctx* ctx, const strp_module_desc* desc, strp_m
  * (alpha/T)(beta/alpha)^2 <M^-2, E E^T>, E = Y - W2[:,S] relu(Z_S), M = (beta/alpha) I + W2[:,S] W2[:,S]^T
  * (Appendix A.1, "Updating activation": the normal equations of that step).
  * A selection of k < f units takes f up to 65536 (STRP_EINVAL above).
+ * With 3969 to 4352 or 5313 to 5760 kept units the last bits of W2 depend on the stages of the call: where a- and z-update are in
+ * it and read and write 1 GB or 4 GB of pruned rows beside the fc2 factorisation, that one sums in another order.
  */
 strp_status strp_admm_step(strp_ctx* ctx, const strp_module_desc* desc, strp_module_state* st,
                            const strp_params* params, strp_report* report_host);

@@ -779,8 +779,9 @@ static int flow_row_lines(int n) {
   return s;
 }
 static bool flow_lines(const double* M, long long ld) { return ld % 16 == 0 && ((uintptr_t)M & 127) == 0; }
-// Which way an order goes: by the order alone, so that the factor's bits depend neither on a pass that rides along, on what else is done
-// in the call, nor on where the caller's factor lies.  us, a launch per panel / one launch, rows of whole cache lines:  n = 72 33.1 / 28.5,
+// Which way a system goes: by its order, so that the factor's bits depend neither on what else is done in the call nor on where the
+// caller's factor lies, but in two ranges where a long pass that rides along (cojob.h) turns the comparison.
+// us, a launch per panel / one launch, rows of whole cache lines:  n = 72 33.1 / 28.5,
 // 136 47.0 / 39.1, 333 84 / 71, 600 133 / 114, 1000 211 / 175, 1408 293 / 237, 2048 505 / 383, 3072 953 / 856, 3600 1392 / 1312,
 // 3968 1702 / 1549, 4416 2213 / 2214, 4912 2945 / 2730, 5312 3589 / 3273, 5888 4750 / 4710, 6272 5658 / 5407, 7168 8252 / 7446,
 // 8192 12537 / 11973, 10240 24.7 / 19.1 ms; tiles that share cache lines, which are read past the caches:  1384 296 / 243,
@@ -788,13 +789,18 @@ static bool flow_lines(const double* M, long long ld) { return ld % 16 == 0 && (
 // other workgroups hold at a time fall from four to three and from three to two (N tasks each), since what the chain waits
 // for next is then handed out later:  4032 1770 / 1797, 4160 1902 / 1983, 4288 2056 / 2082; 5376 3685 / 3854, 5568 4092 / 4238,
 // 5696 4373 / 4430.  With more tiles they bound it themselves, and at the third fall (8064 12.2 / 11.4 ms) it stays ahead.
-// A pass beside it (cojob.h) runs beside the whole launch, or beside the chain's first one: n = 1000 of 2312 units over 30011 tokens 288 / 193,
-// 3281 of 8192 over 65536 1985 / 1691, 4912, 1.9 GB, 3403 / 3148; in the gap 4096, 0.2 GB, 1926 / 1955, 1.6 GB, 2222 / 2171.  With a pass beside
+// A pass runs beside the whole launch, or beside the chain's first one, so there it pays from about 1 and 4 GB on (bytes read and written):
+// 3976, 0.5 GB 1849 / 1862, 1.0 1938 / 1932, 2.0 2233 / 2193, 8.0 3516 / 3136;  4200, 0.5 2104 / 2120, 1.0 2195 / 2162;  4096, 1.0 2052 / 2078, 2.0
+// 2365 / 2333, 19 5225 / 4862;  5328, 2.0 4294 / 4354, 4.0 4694 / 4667, 8.0 5477 / 5197;  5560, 2.0 4744 / 4908, 4.0 5145 / 5137, 16 7499 / 6518;
+// 5400, 4.0 4885 / 4982, 8.0 5612 / 5360, 17 6877 / 6166.  Elsewhere it widens the lead:  1000 of 2312 units over 30011 tokens 288 / 193, 3281 of 8192
+// over 65536 1985 / 1691, 4912, 1.9 GB, 3403 / 3148.  With a pass beside
 // them tiles that share lines cost the launch its lead (1000 331, 1544 744 / 728, 3281 2113 / 2043): a step pads its rows (system_ld).
-bool chol_flow_ok(int n) {
+bool chol_flow_ok(int n, double pass_bytes) {
   const int N = (n + NB - 1) / NB;
   if (n < NB + 8 || flow_lines_needed(N) > NB << flow_row_lines(n)) return false;
-  return !(N >= 63 && N <= 68) && !(N >= 84 && N <= 90);
+  if (N >= 63 && N <= 68) return pass_bytes >= 1e9;
+  if (N >= 84 && N <= 90) return pass_bytes >= 4e9;
+  return true;
 }
 
 strp_status chol_flow(strp_ctx* ctx, double* A, int n, long long ld, double* Linv, long long ldv, int32_t* status, const CoJob& job) {

@@ -344,7 +344,8 @@ strp_status gram_of_inverse(strp_ctx* ctx, const double* Linv, int n, long long 
   return dgemm_launch<false, false>(ctx, p);
 }
 
-// The chain, for the orders that chol_flow_ok leaves to it (65 .. 71, 63 .. 68 and 84 .. 90 tiles); a single tile is its first launch alone.
+// The chain, for what chol_flow_ok leaves to it: orders 65 .. 71, and 63 .. 68 and 84 .. 90 tiles without a long pass; a single tile is
+// its first launch alone.
 // One launch of it: everything that step t can do once the steps before it are complete.  Panels are 64 columns
 // (tile index = row or column / 64); A is factored in place below its diagonal tiles, Linv is built beside it by
 // carrying the identity through the same elimination (its row i holds partial sums V until step i).  Panel t - 1 is
@@ -733,8 +734,9 @@ strp_status chol_inverse(strp_ctx* ctx, double* A, int n, long long ld, double* 
   memset(&job, 0, sizeof(job));
   if (ctx->cojob) job = *ctx->cojob;
   ctx->cojob = nullptr;
-  ProfScope ps(ctx, "chol_factor_f64", 2.0 * (double)n * n * n / 3.0, 16.0 * (double)n * n + (job.Z0 ? 16.0 : 12.0) * (double)job.nrows * (double)job.T);
-  if (chol_flow_ok(n)) return chol_flow(ctx, A, n, ld, Linv, ldv, status, job);
+  const double pass_bytes = (job.Z0 ? 16.0 : 12.0) * (double)job.nrows * (double)job.T;
+  ProfScope ps(ctx, "chol_factor_f64", 2.0 * (double)n * n * n / 3.0, 16.0 * (double)n * n + pass_bytes);
+  if (chol_flow_ok(n, pass_bytes)) return chol_flow(ctx, A, n, ld, Linv, ldv, status, job);
   StepP p;
   memset(&p, 0, sizeof(p));
   p.A = A; p.ld = ld; p.V = Linv; p.ldv = ldv; p.sub = sub; p.n = n; p.N = (n + NB - 1) / NB; p.status = status;

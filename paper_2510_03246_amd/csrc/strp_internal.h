@@ -229,8 +229,8 @@ static inline size_t chol_scratch_elems(long long n) {
 // f32_to_f64_ridge.  sub: chol_scratch_elems(n) doubles of scratch.  ld and ldv even, A and Linv 16-byte aligned.  A pivot that
 // is not positive sets ENOTPD in status (device word); a wait that takes ten seconds, EHIP.
 strp_status chol_inverse(strp_ctx* ctx, double* A, int n, long long ld, double* sub, double* Linv, long long ldv, int32_t* status);
-// The same in one launch, for the orders that are faster so.
-bool chol_flow_ok(int n);
+// The same in one launch, for the orders that are faster so beside a pass of these bytes (0: none).
+bool chol_flow_ok(int n, double pass_bytes);
 strp_status chol_flow(strp_ctx* ctx, double* A, int n, long long ld, double* Linv, long long ldv, int32_t* status, const CoJob& job);
 // X (L L^T)^-1 = (X Linv^T) Linv for X [m x n] (ldx), as refitted weights; tmp: m x ldx scratch.
 //   FC2: W[i, idx[j]] = result[i, j] (m rows of W);  FC1: W[idx[i], j] = result[i, j];  other entries of W are not written.

@@ -454,8 +454,9 @@ def check_what_the_large_systems_cover():
 
 
 def check_which_factorisation_runs():
-    """One launch or a launch per panel by the order alone: not by a pruned rows' pass that rides along, where rows end or where the
-    caller's factor lies, so none of these changes the factor's bits."""
+    """One launch or a launch per panel by the order: not by where rows end or where the caller's factor lies, nor, but for two
+    ranges, by the pruned rows' pass that rides along, so none of these changes the factor's bits.  In 3969 .. 4352 and 5313 .. 5760
+    a pass of 1 and of 4 GB (16 bytes a token and pruned unit) takes the launch."""
     lib = Library()
     strp = lib.strp
 
@@ -474,6 +475,9 @@ def check_which_factorisation_runs():
             for f, stages in ((n + 512, 0), (n, 0), (n + 512, strp.STAGE_SELECT | strp.STAGE_REFIT2)):
                 names = _step_records(lib, 64, f, 4096, n, 1 << 50, stages)[1]
                 assert ran(names) == (one, 1 - one + (stages == 0)), (n, f, stages)
+    for f, T, n, one in [(16384, 4096, 4096, 0), (16384, 8192, 4096, 1), (5016, 65536, 3976, 1), (4352, 65536, 4352, 0), (16384, 16384, 5400, 0),
+                         (16384, 32768, 5400, 1), (16384, 4096, 5768, 1), (16384, 4096, 3968, 1)]:
+        assert ran(_step_records(lib, 64, f, T, n, 1 << 50)[1]) == (one, 2 - one), (f, T, n)
     for d, k, want in [(64, 128, (1, 1)), (768, 1536, (2, 0)), (4096, 4915, (1, 1))]:
         assert ran(_step_records(lib, d, 16384 if d > 1000 else 4 * d, 4096, k, 1 << 50)[1]) == want, (d, k)
 
