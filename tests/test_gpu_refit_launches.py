@@ -78,3 +78,38 @@ def test_products_of_the_fc2_refit_together_and_apart(d, f, T, k, prec, planes):
     assert len(products) == 2 and "gemm_group" not in products, products
     assert torch.equal(together, apart)
     ctx.close()
+
+
+@pytest.mark.parametrize("d,f,T,k", [(72, 264, 1003, 131), (256, 1536, 2000, 1032), (64, 1600, 700, 1465)])
+def test_rows_of_the_fc2_system_change_no_bit(d, f, T, k):
+    """The system's rows are whole cache lines where the workspace holds them (host side: check_rows_of_the_fc2_system), tiles that share
+    lines are read past the caches where it does not.  The smallest workspace that holds every product's partials in full, which the
+    shorter rows just fit: the same bits as on the one the library asks for."""
+    ld = (T + 7) // 8 * 8
+    cfg = inputs.WorkloadConfig("case", 1, d, f, 0, T, "f32", "t3", 3, 0.5, 1)
+    m = inputs.make_ffn_module(cfg, 0, 7, "cuda", ld=ld)
+    ctx = strp.Context(0)
+    mod = strp.FFNModule(ctx, m["W1hat"], m["W2hat"], m["X"], T, k_max=k)
+    mod.init(strp.Params(1.0, 0.7, 0.01, strp.WANDA, 1, k, 0))
+    mod.step(strp.Params(1.0, 0.7, 0.01, strp.WANDA, 1, k, strp.STAGE_SELECT))
+    space = torch.empty(ctx.workspace_bytes(mod.desc), dtype=torch.uint8, device="cuda")
+
+    def refit(nbytes):
+        """weights and the bytes that the reductions read and write, or None where the workspace is too small"""
+        ctx.check(ctx.lib.strp_set_workspace(ctx.h, space.data_ptr(), nbytes))
+        ctx.profile_enable(True)
+        par = strp.Params(1.0, 0.7, 0.01, strp.WANDA, 0, k, strp.STAGE_REFIT2)
+        status = ctx.lib.strp_admm_step(ctx.h, C.byref(mod.desc), C.byref(mod.state), C.byref(par), None)
+        reduced = sum(r[3] for r in ctx.profile_launches() if r[0] == "splitk_reduce")
+        assert ctx.poll() == strp.OK and status in (strp.OK, strp.ENOMEM)
+        return (mod.W2.clone(), reduced) if status == strp.OK else None
+
+    want, reduced = refit(space.numel())
+    lo, hi = 15, space.numel() // 256                 # the workspace in units of 256 bytes: partials cut short or none, all in full
+    while hi - lo > 1:
+        mid = (lo + hi) // 2
+        got = refit(mid * 256)
+        lo, hi = (lo, mid) if got is not None and abs(got[1] - reduced) < 1.0 else (mid, hi)
+    got, _ = refit(hi * 256)
+    assert bool(got.any()) and torch.equal(got, want)
+    ctx.close()
