@@ -262,8 +262,219 @@ __global__ __launch_bounds__(512, 1) void gemm_dma_kernel(const GemmP p) {
   }
 }
 
+// ---------------------------------------------------------------------------------------------------------------------
+// The same products in tiles of 128 x 256 by four wavefronts, two workgroups on a CU: one has matrix instructions to issue while the
+// other fills its pipeline or moves the state tensors of its epilogue.  The wavefronts lie side by side, so a wavefront's 64 columns
+// of Q are its own: their fragments come straight from memory into registers (the operand layout is the fragments': four runs of
+// 256 bytes an instruction), a pair of stages ahead, and only P, which all four read, passes through LDS: 16 KB of fragment reads a
+// wavefront and 32 steps instead of 24.  What bounds it is power, as the kernel above, on large products (A_S of 768 x 1536 x 65536 434 us,
+// 1.07 PFLOP/s executed, whatever the wavefronts' priorities or a staggered start), and on smaller ones the start and epilogue of the last
+// round, which are half as long.  The sums are those of the kernel above, bit for bit.
+#pragma clang diagnostic push
+#pragma clang diagnostic ignored "-Winline-asm"
+__device__ __forceinline__ void lds_dma_16s(const void* base, unsigned lane_off, unsigned lds_addr) {
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" : : "s"(lds_addr), "v"(lane_off), "s"(base) : "memory", "m0");
+}
+#pragma clang diagnostic pop
+template <int NPP, int NPQ, bool TOKENS>
+__global__ __launch_bounds__(256, 2) void gemm_half_kernel(const GemmP p) {
+  constexpr int NW = 4, PM = 128, PN = 256;
+  constexpr int PAIR = 8192;                       // bytes of one plane of 128 rows over 32 contraction steps, contiguous in memory too
+  __shared__ __attribute__((aligned(1024))) unsigned char smem[2][NPP * PAIR];
+  __shared__ double sred[NW][2];
+  __shared__ int srow[PM];
+
+  int tm, tn, split;
+  decode_tile(p, (int)blockIdx.x, (int)gridDim.x, tm, tn, split);
+  const int m0 = tm * PM, n0 = tn * PN;
+  const long long k0 = (long long)split * p.kchunk;                 // a multiple of 32
+  const long long k1 = (k0 + p.kchunk < p.K) ? (k0 + p.kchunk) : p.K;
+  const int npairs = (int)((k1 - k0 + 31) / 32);                    // k-groups past k1 inside the last pair are zero padding
+  const long long g0 = k0 >> 3;
+
+  const int tid = threadIdx.x, lane = tid & 63;
+  int my_row = 0;
+  if (p.oidx && tid < PM && m0 + tid < p.M) my_row = p.oidx[m0 + tid];
+  const int wn = __builtin_amdgcn_readfirstlane(tid >> 6);
+
+  // P: this wavefront moves two KB of each plane of a pair
+  const char* pp[NPP];
+  const unsigned lds_base = (unsigned)(size_t)(__attribute__((address_space(3))) unsigned char*)&smem[0][0];
+#pragma unroll
+  for (int pl = 0; pl < NPP; ++pl) pp[pl] = (const char*)((pl ? p.P.lo : p.P.hi) + ((long long)tm * p.P.kg + g0) * 1024) + wn * 2048;
+  auto issue_p = [&](int pr) {
+    const long long o = (long long)(pr < npairs ? pr : npairs - 1) * PAIR;
+#pragma unroll
+    for (int pl = 0; pl < NPP; ++pl)
+#pragma unroll
+      for (int i = 0; i < 2; ++i)
+        lds_dma_16s(pp[pl] + o + i * 1024, lane * 16, lds_base + (unsigned)((pr & 1) * NPP + pl) * PAIR + wn * 2048 + i * 1024);
+  };
+  // lane l has the chunk of k-group l / 16 and row l % 16 of a fragment
+  const unsigned frag = (unsigned)((lane >> 4) * 128 + (lane & 15)) * 16;
+  const char* qp[NPQ];
+  {
+    const int n = n0 + wn * 64;
+    int pan = n >> 7;
+    pan = pan < p.Q.npan ? pan : p.Q.npan - 1;
+#pragma unroll
+    for (int pl = 0; pl < NPQ; ++pl) qp[pl] = (const char*)((pl ? p.Q.lo : p.Q.hi) + ((long long)pan * p.Q.kg + g0) * 1024) + (n & 127) * 16;
+  }
+  typedef unsigned int uintx4 __attribute__((ext_vector_type(4)));
+  struct QF { uintx4 h[4], l[4]; };
+  struct PF { uintx4 h, l; };
+  auto load_q = [&](QF& f, int pr) {
+    const long long o = (long long)(pr < npairs ? pr : npairs - 1) * PAIR;
+    const char* const h = qp[0] + o;
+    const char* const l = qp[NPQ - 1] + o;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      f.h[j] = *(const uintx4*)(h + frag + j * 256);
+      if (NPQ == 2) f.l[j] = *(const uintx4*)(l + frag + j * 256);
+    }
+  };
+  auto read_p = [&](PF& f, int pr, int i) {
+    const unsigned char* st = smem[pr & 1];
+    f.h = *(const uintx4*)(st + frag + i * 256);
+    if (NPP == 2) f.l = *(const uintx4*)(st + PAIR + frag + i * 256);
+  };
+
+  floatx4 acc[8][4];
+#pragma unroll
+  for (int i = 0; i < 8; ++i)
+#pragma unroll
+    for (int j = 0; j < 4; ++j) acc[i][j] = floatx4{0.0f, 0.0f, 0.0f, 0.0f};
+  auto mma = [&](uintx4 a, uintx4 b, floatx4 c) {
+    return __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(half8, TOKENS ? b : a), __builtin_bit_cast(half8, TOKENS ? a : b), c, 0, 0, 0);
+  };
+  auto pass_hl = [&](floatx4 (&c)[4], const PF& a, const QF& b) {
+    if (NPQ == 2) {
+#pragma unroll
+      for (int j = 0; j < 4; ++j) c[j] = mma(a.h, b.l[j], c[j]);
+    }
+  };
+  auto pass_lh = [&](floatx4 (&c)[4], const PF& a, const QF& b) {
+    if (NPP == 2) {
+#pragma unroll
+      for (int j = 0; j < 4; ++j) c[j] = mma(a.l, b.h[j], c[j]);
+    }
+  };
+  auto pass_hh = [&](floatx4 (&c)[4], const PF& a, const QF& b) {
+#pragma unroll
+    for (int j = 0; j < 4; ++j) c[j] = mma(a.h, b.h[j], c[j]);
+  };
+  PF pa, pb;
+  // One pair: b holds its Q fragments, pa its first P fragment; on return pa holds that of the next pair, and b's registers are being
+  // filled for the one behind it.
+  // The compiler does not see that P's loads are in flight: it is made to wait for the next pair's Q fragments where everything
+  // that has been asked for is waited for, since behind that it would count too few loads after them.
+  auto arrived = [&](QF& f) {
+    asm volatile("" : "+v"(f.h[0]), "+v"(f.h[1]), "+v"(f.h[2]), "+v"(f.h[3]));
+    if (NPQ == 2) asm volatile("" : "+v"(f.l[0]), "+v"(f.l[1]), "+v"(f.l[2]), "+v"(f.l[3]));
+  };
+  auto pair_step = [&](int pr, QF& b, QF& bn) {
+#define STRP_ROW(i, cur, nxt)                \
+    read_p(nxt, pr, (i) + 1);                \
+    __builtin_amdgcn_sched_barrier(0);       \
+    pass_hl(acc[i], cur, b);                 \
+    pass_lh(acc[i], cur, b);                 \
+    pass_hh(acc[i], cur, b);                 \
+    __builtin_amdgcn_sched_barrier(0);
+    STRP_ROW(0, pa, pb)
+    STRP_ROW(1, pb, pa)
+    STRP_ROW(2, pa, pb)
+    STRP_ROW(3, pb, pa)
+    STRP_ROW(4, pa, pb)
+    STRP_ROW(5, pb, pa)
+    STRP_ROW(6, pa, pb)
+#undef STRP_ROW
+    wait_vmcnt_lgkm0<0>();         // the next pair has landed; this wavefront's fragment reads of this pair are complete
+    arrived(bn);
+    __syncthreads();               // ... and so for every wavefront: the pair's slot may be overwritten
+    pass_hh(acc[7], pb, b);
+    __builtin_amdgcn_sched_barrier(0);
+    issue_p(pr + 2);
+    read_p(pa, pr + 1, 0);         // past the last pair this reads a slot that is never multiplied
+    __builtin_amdgcn_sched_barrier(0);
+    pass_hl(acc[7], pb, b);
+    pass_lh(acc[7], pb, b);
+    __builtin_amdgcn_sched_barrier(0);
+    load_q(b, pr + 2);
+    __builtin_amdgcn_sched_barrier(0);
+  };
+
+  QF q0, q1;
+  issue_p(0);
+  load_q(q0, 0);
+  issue_p(1);
+  load_q(q1, 1);
+  wait_vmcnt<0>();
+  arrived(q0);
+  arrived(q1);
+  __syncthreads();
+  read_p(pa, 0, 0);
+  int pr = 0;
+#pragma unroll 1
+  for (; pr + 1 < npairs; pr += 2) {
+    pair_step(pr, q0, q1);
+    pair_step(pr + 1, q1, q0);
+  }
+  if (pr < npairs) pair_step(pr, q0, q1);
+  wait_vmcnt<0>();
+  if (tid < PM) srow[tid] = my_row;
+  __syncthreads();
+
+  float unscale = 1.0f;
+  if (p.P.maxbits) unscale /= scale_of_max(*p.P.maxbits);
+  if (p.Q.maxbits) unscale /= scale_of_max(*p.Q.maxbits);
+  double red0 = 0.0, red1 = 0.0;
+  if constexpr (TOKENS) {
+    const int m0w = m0, n0w = n0 + wn * 64;
+    if (p.epi == EPI_PARTIAL) token_epilogue<EPI_PARTIAL, true, false>(p, acc, unscale, m0w, n0w, split, srow, m0, red0, red1);
+    else if (p.epi == EPI_AUPD && p.rs_z0) token_epilogue<EPI_AUPD, true, true>(p, acc, unscale, m0w, n0w, split, srow, m0, red0, red1);
+    else if (p.epi == EPI_AUPD) token_epilogue<EPI_AUPD, true, false>(p, acc, unscale, m0w, n0w, split, srow, m0, red0, red1);
+    else if (!p.write_out) token_epilogue<EPI_ZUPD, false, false>(p, acc, unscale, m0w, n0w, split, srow, m0, red0, red1);
+    else if (p.rs_z0) token_epilogue<EPI_ZUPD, true, true>(p, acc, unscale, m0w, n0w, split, srow, m0, red0, red1);
+    else token_epilogue<EPI_ZUPD, true, false>(p, acc, unscale, m0w, n0w, split, srow, m0, red0, red1);
+  } else {
+    const int mbase = m0 + 8 * (lane >> 5), nbase = n0 + wn * 64 + (lane & 31);
+    switch (p.epi) {
+      case EPI_STORE: epilogue16<EPI_STORE>(p, acc, unscale, mbase, nbase, m0, red0, red1); break;
+      case EPI_INITZ: epilogue16<EPI_INITZ>(p, acc, unscale, mbase, nbase, m0, red0, red1); break;
+      default: epilogue16<EPI_RESID>(p, acc, unscale, mbase, nbase, m0, red0, red1); break;
+    }
+  }
+  if (p.maxbits) {
+    store_maxbits<NW>(p, red0, sred);
+  } else if (p.red) {
+    red0 = wave_sum(red0);
+    red1 = wave_sum(red1);
+    if (lane == 0) {
+      sred[wn][0] = red0;
+      sred[wn][1] = red1;
+    }
+    __syncthreads();
+    if (tid == 0) {
+      double r0 = 0.0, r1 = 0.0;
+#pragma unroll
+      for (int w = 0; w < NW; ++w) {
+        r0 += sred[w][0];
+        r1 += sred[w][1];
+      }
+      p.red[2 * (long long)blockIdx.x + 0] = r0;
+      p.red[2 * (long long)blockIdx.x + 1] = r1;
+    }
+  }
+}
+
 template <int NPP, int NPQ>
 static void launch_dma(strp_ctx* ctx, const GemmP& p) {
+  if (p.wt == 3) {
+    const dim3 grid(gemm_grid_blocks(p)), block(256);
+    if (p.epi == EPI_PARTIAL || p.epi == EPI_AUPD || p.epi == EPI_ZUPD) hipLaunchKernelGGL((gemm_half_kernel<NPP, NPQ, true>), grid, block, 0, ctx->stream, p);
+    else hipLaunchKernelGGL((gemm_half_kernel<NPP, NPQ, false>), grid, block, 0, ctx->stream, p);
+    return;
+  }
   const dim3 grid(gemm_grid_blocks(p)), block(512);
   if (p.epi == EPI_PARTIAL || p.epi == EPI_AUPD || p.epi == EPI_ZUPD) hipLaunchKernelGGL((gemm_dma_kernel<NPP, NPQ, true>), grid, block, 0, ctx->stream, p);
   else hipLaunchKernelGGL((gemm_dma_kernel<NPP, NPQ, false>), grid, block, 0, ctx->stream, p);

@@ -34,7 +34,7 @@ __device__ __forceinline__ double wave_sum(double v) {
 // Which output tile and K split a block works on.
 //
 // Blocks are dealt round-robin to the 8 XCDs (block b runs on XCD b % 8) and each XCD keeps 32 blocks of the
-// pipelined kernel resident, starting the next of its blocks when one retires.  Each XCD has its own L2, so the
+// pipelined kernel resident (64 of 128 x 256), starting the next of its blocks when one retires.  Each XCD has its own L2, so the
 // 32 blocks resident on an XCD should share operand panels: the work list is ordered tile group by tile group
 // (gm x gn tiles, all of one K split, then the next split of the same group), and XCD x takes entries
 // [256 c + 32 x, 256 c + 32 x + 32) of it in its c-th round; the last round's entries are dealt out the same way, as
@@ -43,11 +43,11 @@ __device__ __forceinline__ double wave_sum(double v) {
 // ceil(n/2) x (2 h + 1) tiles, h = floor(n/2) (row r holds triangle row r + h followed by triangle row h - 1 - r), so that
 // the same grouping applies and no workgroup is empty.
 __device__ __forceinline__ void decode_tile(const GemmP& p, int bid, int nblocks, int& tm, int& tn, int& split) {
-  const int full = nblocks & ~255;
+  const int ls = p.wt == 3 ? 6 : 5, full = nblocks & ~((8 << ls) - 1);
   int q = bid;
   if (bid < full) {
     const int x = bid & 7, j = bid >> 3;
-    q = ((j >> 5) << 8) + (x << 5) + (j & 31);
+    q = ((j >> ls) << (ls + 3)) + (x << ls) + (j & ((1 << ls) - 1));
   } else {
     const int x = bid & 7, rem = nblocks - full;
     q = full + x * (rem >> 3) + (x < (rem & 7) ? x : (rem & 7)) + ((bid - full) >> 3);

@@ -347,6 +347,21 @@ void gemm_small_tiles(GemmP& p) {
   p.subN = p.N > 64 ? 2 : 1;
 }
 
+// Products of the state's kept rows in 128x256 tiles, two workgroups on a CU (gemm_half_kernel).  us, the tile before / this one (E, A_S, Z1):
+// 768 over 1536 units and 65536 tokens 373 / 371, 446 / 434, 361 / 337;  2048, 3277, 65536 1904 / 1855, 2107 / 2104, 1558 / 1454;  1000, 1013,
+// 30011, fp32 X 183 / 180, 208 / 200, 207 / 198.  More where 256-row tiles pad (264, 270, 66000, fp32 X 119 / 79, 142 / 93, 144 / 100) or
+// fill their last round badly (1600, 2500, 8000: A_S 222 / 179, Z1 172 / 142) and where fewer than 192 of them left the product
+// to 128x128 ones (1536, 2304, 4096: A_S 139 / 112, Z1 107 / 77).  Not where 256x256 tiles fill one round and both operands
+// have two planes, since half a round of each is then the same work with a longer start (768, 1536, 16384: E 119 / 127; 2048, 3277, 4096: A_S 144 / 150;
+// with one plane of X 63 / 55 and 109 / 106 for Z1), nor for fewer workgroups than CUs (512, 700, 8192: A_S 192 of them 35 / 34, E 33 / 42), nor
+// where 128 rows or six pairs of stages are all there is (130 kept of 128 over 70000: 37 / 41, 43 / 43, 46 / 48).  The initialisation's products,
+// which write three tensors or run over all units, are no faster (2048 x 6824 x 16384: 657 / 746, 622 / 664).
+static bool half_tiles_pay(const GemmP& p, long long n4) {
+  if (p.epi != EPI_RESID && p.epi != EPI_AUPD && p.epi != EPI_ZUPD) return false;
+  if (p.M <= 128 || p.K < 192 || (long long)((p.M + 127) / 128) * ((p.N + 255) / 256) < 256) return false;
+  return n4 < 192 || n4 > 256 || !p.P.lo || !p.Q.lo;
+}
+
 void gemm_plan_tiles(GemmP& p, int want_splits, int wt) {
   p.subM = p.subN = 1;
   if (wt) {
@@ -355,10 +370,11 @@ void gemm_plan_tiles(GemmP& p, int want_splits, int wt) {
     // 256x256 tiles with the LDS-DMA pipeline when they still give most CUs a block
     const long long n4 = (long long)((p.M + 255) / 256) * ((p.N + 255) / 256);
     p.wt = gemm_tile256_ok(p) && n4 >= 192 ? 4 : 2;
+    if (half_tiles_pay(p, n4)) p.wt = 3;
   }
-  const int ROWS = 64 * p.wt, BK = p.wt == 2 ? 64 : 32;
-  p.tilesM = (p.M + ROWS - 1) / ROWS;
-  p.tilesN = (p.N + ROWS - 1) / ROWS;
+  const int RM = p.wt == 3 ? 128 : 64 * p.wt, RN = p.wt == 3 ? 256 : 64 * p.wt, BK = p.wt == 2 ? 64 : 32;
+  p.tilesM = (p.M + RM - 1) / RM;
+  p.tilesN = (p.N + RN - 1) / RN;
   p.ntiles = p.triangle ? p.tilesM * (p.tilesM + 1) / 2 : p.tilesM * p.tilesN;
   if (p.triangle) {
     p.gridM = (p.tilesM + 1) / 2;
@@ -369,9 +385,9 @@ void gemm_plan_tiles(GemmP& p, int want_splits, int wt) {
   }
   {
     // tile group: 32 tiles, shaped to the grid
-    int gm = 4;
+    int gm = p.wt == 3 ? 8 : 4;
     while (gm > 1 && gm > p.gridM) gm >>= 1;
-    int gn = 32 / gm;
+    int gn = (p.wt == 3 ? 64 : 32) / gm;
     while (gn > 1 && gn / 2 >= p.gridN) { gn >>= 1; if (gm * 2 <= p.gridM) gm <<= 1; }
     p.gm = gm;
     p.gn = gn;
@@ -405,7 +421,7 @@ void launch_gemm_dma(strp_ctx* ctx, const GemmP& p, int npp, int npq);   // gemm
 
 template <int NPP, int NPQ>
 static void launch_one(strp_ctx* ctx, const GemmP& p) {
-  if (p.wt == 4)
+  if (p.wt >= 3)
     launch_gemm_dma(ctx, p, NPP, NPQ);
   else if (p.wt == 1)
     hipLaunchKernelGGL((gemm_kernel<NPP, NPQ>), dim3(gemm_grid_blocks(p)), dim3(128), 0, ctx->stream, p);
@@ -415,7 +431,7 @@ static void launch_one(strp_ctx* ctx, const GemmP& p) {
 
 static strp_status check_gemm(strp_ctx* ctx, const GemmP& p) {
   if (p.M <= 0 || p.N <= 0 || p.K <= 0) return fail(ctx, STRP_EINVAL, "gemm: empty shape");
-  if (p.ntiles <= 0 || p.splits <= 0 || (p.wt != 1 && p.wt != 2 && p.wt != 4)) return fail(ctx, STRP_EINVAL, "gemm: tiles not planned");
+  if (p.ntiles <= 0 || p.splits <= 0 || p.wt < 1 || p.wt > 4) return fail(ctx, STRP_EINVAL, "gemm: tiles not planned");
   if (!p.P.hi || !p.Q.hi) return fail(ctx, STRP_EINVAL, "gemm: null operand plane");
   if (p.P.kg * 8 < p.K || p.Q.kg * 8 < p.K || (p.P.kg & 3) || (p.Q.kg & 3))
     return fail(ctx, STRP_EINVAL, "gemm: operand planes shorter than K or a group count that is not a multiple of four");

@@ -37,7 +37,7 @@ KERNEL_CLASS = {"pruned_rows_kernel": "pruned_rows", "split_t_kernel": "split_ac
                 "row_sums_kernel": "row_sums", "plane_c_to_t_kernel": "plane_c_to_t", "splitk_reduce_kernel": "splitk_reduce",
                 "splitk_reduce_group_kernel": "splitk_reduce"}
 # kernels that run the fp16 products: one launch of one of them per record of a class gemm_*
-GEMM_KERNELS = ("gemm_dma_kernel", "gemm_tile_kernel", "gemm_kernel", "gemm_group_kernel")
+GEMM_KERNELS = ("gemm_dma_kernel", "gemm_half_kernel", "gemm_tile_kernel", "gemm_kernel", "gemm_group_kernel")
 
 
 # how the counters accumulate over the chip: SQ_BUSY_CYCLES once per shader engine, SQ_VALU_MFMA_BUSY_CYCLES once per

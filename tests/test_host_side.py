@@ -494,6 +494,21 @@ def check_tiles_of_the_solves():
         assert st == lib.strp.OK and tiles == {tile}, (m, n, tiles)
 
 
+def check_tiles_of_the_kept_rows():
+    """Which kernel makes E, A_S and Z1: 128 x 256 tiles from 256 of them on, but for one round of 256 x 256 ones on two planes each, and not
+    for a contraction below 192 or 128 rows.  Every tile size at the token counts where the rule turns."""
+    lib = Library()
+    for d, f, T, k, want in [(392, 800, 21845, 385, "hhh"), (256, 1000, 32512, 257, "tdd"), (256, 1000, 32513, 257, "hdd"), (256, 1000, 32769, 257, "hhh"), (256, 1000, 32768, 600, "hhh"), (768, 3072, 16384, 1536, "dhh"), (768, 3072, 21760, 1536, "dhh"),
+                             (768, 3072, 21768, 1536, "hhh"), (1000, 2312, 30011, 1013, "hhh"), (512, 1704, 16384, 1000, "hdd"), (512, 1704, 16640, 1000, "hhh"), (136, 400, 140000, 128, "ttt"), (192, 400, 140000, 192, "hhh")]:
+        records, names = _step_records(lib, d, f, T, k, 1 << 50)
+        from paper_2510_03246_amd import profile_summary as ps
+        dispatches = [dict(name=ps.short_name(n)) for n in names if n]
+        ps.classify(dispatches, [r[0] for r in records])
+        got = {x["cls"][10:]: x["name"] for x in dispatches if x.get("cls", "").startswith("gemm_h2x2")}
+        kinds = "".join({"gemm_half_kernel": "h", "gemm_dma_kernel": "d", "gemm_tile_kernel": "t"}[got[c].split("::")[1].split("<")[0]] for c in ("resid", "aupd", "zupd"))
+        assert kinds == want, (d, f, T, k, kinds, want)
+
+
 def check_weight_statistics_without_a_counter():
     """A call is one launch for up to eight matrices; a context that found no counter left takes one more."""
     lib = Library()
@@ -543,7 +558,7 @@ def check_weight_statistics_counter():
     assert counter(lib.h) not in (0, a, b, c)
 
 
-CHECKS = [check_systems_of_the_factorisations, check_which_factorisation_runs, check_tiles_of_the_solves, check_weight_statistics_counter, check_weight_statistics_without_a_counter, check_what_the_gram_matrices_cover, check_what_the_large_systems_cover, check_selection_of_a_very_wide_module, check_weight_statistics_arguments, check_weight_statistics_workgroups, check_chains, check_workspace_of_a_module, check_least_workspace_of_a_step, check_rows_of_the_fc2_system, check_work_of_shared_launches, check_profile_classes, check_workspace_of_a_factorisation, check_cached_factor_needs_no_alignment]
+CHECKS = [check_systems_of_the_factorisations, check_which_factorisation_runs, check_tiles_of_the_solves, check_tiles_of_the_kept_rows, check_weight_statistics_counter, check_weight_statistics_without_a_counter, check_what_the_gram_matrices_cover, check_what_the_large_systems_cover, check_selection_of_a_very_wide_module, check_weight_statistics_arguments, check_weight_statistics_workgroups, check_chains, check_workspace_of_a_module, check_least_workspace_of_a_step, check_rows_of_the_fc2_system, check_work_of_shared_launches, check_profile_classes, check_workspace_of_a_factorisation, check_cached_factor_needs_no_alignment]
 
 
 @pytest.fixture(scope="session")
