@@ -64,7 +64,9 @@ typedef enum { STRP_PROD_GRAM = 0, STRP_PROD_RHS2 = 1, STRP_PROD_RHS1 = 2, STRP_
 
 typedef struct strp_ctx strp_ctx;
 
-/* Context: host object holding the device id, the caller's stream and the workspace. */
+/* Context: host object holding the device id, the caller's stream and the workspace.  Some calls use a second stream of the context's own for
+ * part of their work; it waits for the caller's stream first and the caller's waits for it before the call returns, so that everything
+ * a call does is ordered by the caller's stream, also in a graph captured from it. */
 strp_status strp_create(strp_ctx** out, int device, void* hip_stream);
 strp_status strp_destroy(strp_ctx* ctx);
 const char* strp_last_error(const strp_ctx* ctx);
@@ -86,7 +88,7 @@ strp_status strp_set_workspace(strp_ctx* ctx, void* dev_ptr, size_t bytes);
  * also STRP_EHIP where the synchronisation itself fails. */
 strp_status strp_poll(strp_ctx* ctx);
 
-/* Optional per-kernel timing (HIP events on the context's stream), for benchmarks and profiles.
+/* Optional per-kernel timing (HIP events on the context's streams), for benchmarks and profiles.
  * strp_profile_enable(ctx, on) clears the records and switches recording on or off;
  * strp_profile_read synchronises the stream and returns one aggregated entry per kernel class:
  * launches, total milliseconds, algorithmic flops and algorithmic bytes.  out_host is HOST memory. */

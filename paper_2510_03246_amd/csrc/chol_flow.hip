@@ -772,6 +772,14 @@ __global__ __launch_bounds__(512, 2) void chol_flow_kernel(const FlowP p, const 
   if (job.units) flow_ride(p, sh, job);
 }
 
+__global__ __launch_bounds__(256) void cojob_kernel(const CoJob job) { cojob_run(job, blockIdx.x, gridDim.x); }
+strp_status launch_cojob(strp_ctx* ctx, const CoJob& job) {
+  ProfScope ps(ctx, "pruned_rows", 0.0, (job.Z0 ? 16.0 : 12.0) * (double)job.nrows * (double)job.T);
+  hipLaunchKernelGGL(cojob_kernel, dim3(job.units < 2048u ? job.units : 2048u), dim3(256), 0, ctx->stream, job);
+  STRP_HIP(ctx, hipGetLastError());
+  return STRP_OK;
+}
+
 // the counters' lines in a row: columns 64 .. of rows 0 .. 63, which no task reads
 static int flow_row_lines(int n) {
   int s = 0;
@@ -795,9 +803,10 @@ static bool flow_lines(const double* M, long long ld) { return ld % 16 == 0 && (
 // 5400, 4.0 4885 / 4982, 8.0 5612 / 5360, 17 6877 / 6166.  Elsewhere it widens the lead:  1000 of 2312 units over 30011 tokens 288 / 193, 3281 of 8192
 // over 65536 1985 / 1691, 4912, 1.9 GB, 3403 / 3148.  With a pass beside
 // them tiles that share lines cost the launch its lead (1000 331, 1544 744 / 728, 3281 2113 / 2043): a step pads its rows (system_ld).
+bool chol_flow_can(int n) { return n >= NB + 8 && flow_lines_needed((n + NB - 1) / NB) <= NB << flow_row_lines(n); }
 bool chol_flow_ok(int n, double pass_bytes) {
   const int N = (n + NB - 1) / NB;
-  if (n < NB + 8 || flow_lines_needed(N) > NB << flow_row_lines(n)) return false;
+  if (!chol_flow_can(n)) return false;
   if (N >= 63 && N <= 68) return pass_bytes >= 1e9;
   if (N >= 84 && N <= 90) return pass_bytes >= 4e9;
   return true;
@@ -811,8 +820,8 @@ strp_status chol_flow(strp_ctx* ctx, double* A, int n, long long ld, double* Lin
   p.lines_a = flow_lines(A, ld);
   p.lines_v = flow_lines(Linv, ldv);
   p.limit = 1000000000ull;      // ten seconds
-  const unsigned int wanted = 1 + p.tasks;
-  const int grid = job.units ? 256 : (int)(wanted < 256 ? wanted : 256);
+  const unsigned int wanted = 1 + p.tasks, most = ctx->flow_workers ? ctx->flow_workers : 256;
+  const int grid = job.units ? 256 : (int)(wanted < most ? wanted : most);
   hipLaunchKernelGGL(chol_flow_kernel, dim3(grid), dim3(512), 0, ctx->stream, p, job, job.units ? 1 : 0);
   STRP_HIP(ctx, hipGetLastError());
   return STRP_OK;

@@ -355,6 +355,10 @@ strp_status strp_create(strp_ctx** out, int device, void* hip_stream) {
 strp_status strp_destroy(strp_ctx* ctx) {
   if (!ctx) return STRP_EINVAL;
   if (ctx->pinned) (void)hipHostFree(ctx->pinned);
+  if (ctx->side_state > 0) {
+    (void)hipStreamDestroy(ctx->side);
+    for (hipEvent_t e : ctx->side_event) (void)hipEventDestroy(e);
+  }
   delete ctx->prof;
   delete ctx;
   return STRP_OK;
@@ -810,6 +814,78 @@ static long long system_ld(Arena a, int d, int s, long long T, int np) {
   return fits ? ld : f64_ld(s);
 }
 
+// Work of one call on the context's second stream, beside what the call's own stream does meanwhile.  A factorisation is a chain of
+// dependent pivots that holds a few dozen CUs; in one launch it keeps them while the kernels of the other stream run on the rest,
+// where its launches per panel would each wait for CUs again.  The call's own stream has waited for the other one when the call
+// returns, so that to the caller everything is on his stream, captured or not.
+struct Aside {
+  strp_ctx* const ctx;
+  hipStream_t const own;
+  bool open = false;
+  explicit Aside(strp_ctx* c) : ctx(c), own(c->stream) {}
+  ~Aside() {
+    (void)join();
+  }
+  Aside(const Aside&) = delete;
+  Aside& operator=(const Aside&) = delete;
+  // whether there is a second stream; none is made while the call is being captured
+  bool ready() const {
+    if (ctx->side_state == 0) {
+      hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+      if (hipStreamIsCapturing(own, &capture) != hipSuccess || capture != hipStreamCaptureStatusNone) {
+        (void)hipGetLastError();
+        return false;
+      }
+      // the events order kernels of one device: no fence for the host or other devices (6 us less each)
+      const unsigned int flags = hipEventDisableTiming | hipEventDisableSystemFence;
+      ctx->side_state = -1;
+      if (hipStreamCreateWithFlags(&ctx->side, hipStreamNonBlocking) == hipSuccess) {
+        if (hipEventCreateWithFlags(&ctx->side_event[0], flags) == hipSuccess) {
+          if (hipEventCreateWithFlags(&ctx->side_event[1], flags) == hipSuccess) ctx->side_state = 1;
+          else (void)hipEventDestroy(ctx->side_event[0]);
+        }
+        if (ctx->side_state < 0) (void)hipStreamDestroy(ctx->side);
+      }
+      if (ctx->side_state < 0) (void)hipGetLastError();
+    }
+    return ctx->side_state > 0;
+  }
+  // what follows on `to` waits for what `from` has been given so far
+  strp_status order(hipStream_t from, hipStream_t to, int e) {
+    if (hipEventRecord(ctx->side_event[e], from) != hipSuccess || hipStreamWaitEvent(to, ctx->side_event[e], 0) != hipSuccess)
+      STRP_HIP(ctx, hipStreamSynchronize(from));
+    return STRP_OK;
+  }
+  strp_status follow() {          // the second stream waits for the call's own
+    open = true;
+    return order(own, ctx->side, 0);
+  }
+  strp_status await() { return order(ctx->side, own, 1); }
+  strp_status join() {            // ... and this is all it was given
+    leave();
+    const bool had = open;
+    open = false;
+    return had ? await() : STRP_OK;
+  }
+  void enter() { ctx->stream = ctx->side; }
+  void leave() { ctx->stream = own; }
+};
+
+// Workgroups of a factorisation that has other kernels beside it: it holds a CU for each, most of them waiting.  us of factor + inverse alone with 16, 32, 64,
+// 128 and 255 of them:  440 83 / 83 / 82 / 82 / 82, 600 139 / 115 / 112 / 112 / 112, 1000 392 / 262 / 191 / 175 / 174, 1536 1098 / 595 / 401 / 283 / 253, 2500 4571 /
+// 2254 / 1308 / 823 / 581.  A step, us, with 48, 64, 80, 96, 128 and 192 for the fc2 system:  768 x 1536 over 16384 1389 / 1312 / 1288 / 1323 / 1328 / 1392, 1600 x
+// 2500 over 8000 3574 / 3274 / 3227 / 2946 / 2877 / 2908, 2048 x 3277 over 65536 15728 / 15539 / 15531 / 15521 / 15574 / 15900; for M, 24, 48, 64, 96, 128:
+// 768 1333 / 1312 / 1315 / 1370 / 1366, 1600 3597 / 3274 / 3162 / 3077 / 3058.
+static int flow_workers_beside(int n) {
+  const int w = 4 * ((n + NB - 1) / NB);
+  return w < 128 ? w : 128;
+}
+struct FlowWorkers {
+  strp_ctx* const ctx;
+  FlowWorkers(strp_ctx* c, int w) : ctx(c) { c->flow_workers = w; }
+  ~FlowWorkers() { ctx->flow_workers = 0; }
+};
+
 // Solve Wsub (Gram + lam I) = R with R = Lhs Rhs^T over the tokens.
 struct RefitIn {
   const float* Gram; long long ldg;       // fp32 Gram (used when sys_ready == 0)
@@ -907,6 +983,114 @@ static strp_status refit_both(strp_ctx* ctx, Arena& arena, const RefitsIn& in, c
   STRP_TRY(launch_splitk_reduce_group(ctx, r, 3));
   STRP_TRY(factor_and_invert(ctx, a2, G, s, lds, Ginv, lds));
   return apply_inverse_right_pair(ctx, SolveIn{Ginv, s, lds, R2, d, lds, tmp2, w2}, SolveIn{in.Linv1, d, d, R1, s, ldd, tmp1, w1});
+}
+
+// A refit by itself: what runs beside the factorisation is the planes of both sides and their product, where they take longer than the
+// two waits.  us of a head pruning's four calls, one after the other / so:  2048 rows x 832 kept over 65536 tokens, bf16 1112 / 1016, 2240 x 960, 20000
+// 701 / 614, 800 x 320, 40000, fp32 433 / 398, 2560 x 1152, 100000 2314 / 2198, 1024 x 512, 3000 204 / 204.
+static bool refit_beside_pays(int m, int n, long long T, int planes_l, int planes_r) {
+  const double product_us = 2.0 * (planes_l + planes_r - 1) * m * n * (double)T / 1.2e9, planes_us = 8.0 * ((double)m + n) * (double)T / 4e6;
+  return n >= 2 * NB && product_us + planes_us >= 20.0;
+}
+// the block of the M^-1 chain: partials of W W^T, scratch of the factorisation, planes of M^-1
+static size_t m_chain_bytes(int d, long long sp) {
+  auto al = [](size_t bytes) { return (bytes + 255) & ~size_t(255); };
+  return al(nt_partial_elems(d, d, sp, 1) * 4) + al(chol_scratch_elems(d) * 8) + 2 * al(plane_elems(d, d) * 2) + 4096;
+}
+// What strp_admm_step takes of the arena behind the refits: planes of the weights and of B, M^-1 and what comes of it, sums, E, and E by tokens
+static size_t bytes_after_refits(int d, int s, long long T, int np) {
+  auto al = [](size_t bytes) { return (bytes + 255) & ~size_t(255); };
+  const size_t D = d, S = s, slots = (size_t)((T + 63) / 64);
+  return np * (al(2 * plane_elems(D, S)) + 3 * al(2 * plane_elems(S, D))) + al(8 * (size_t)reduce_blocks(d, d)) + 2 * al(8 * D * D) + al(4 * S * D) +
+         al(4 * D * D) + al(m_chain_bytes(d, round_up(s, 8))) + al(8 * slots * S) + al(4 * slots * S) + np * al(2 * plane_elems(T, D)) +
+         al(2 * plane_elems(D, T)) + al(64 * ((S + 127) / 128) * ((size_t)(T + 127) / 128));
+}
+// Both refits of a larger module: while the fc2 system is factored on the call's own stream, the second one has the pruned rows' pass, the
+// right-hand side of fc2, and all of the fc1 refit.  The own stream waits for R2 and goes on to W2; what the other one has left then runs beside
+// that and beside what comes of W2.  us of a step, one after the other / so:  440 x 600 over 9000 tokens 604 / 489, 768 x 1536 over 16384 1564 / 1318, 1600 x 2500
+// over 8000 2991 / 2652, 1000 x 1013 over 30011 (fp32, GAIN) 1949 / 1729, 768 x 1536 over 65536 3547 / 3387, 2048 x 3277 over 65536 15740 / 15520.
+// What it hides is the factorisations' time, so not where the products' is many times that: 2048 x 3277 over 262144 52.2 / 52.3 ms, 4096 x 4915 over
+// 131072 79.3 / 79.8.  The bits are the same, but for those of the factor in the two ranges of orders that go by launches per panel otherwise (chol_flow_ok).
+static bool refits_beside_pay(int d, int s, long long T) {
+  const double N = (s + NB - 1) / NB, factor_us = 11.0 * N + N * N * N / 260.0, product_us = 6.0 * d * s * (double)T / 1.2e9;
+  return product_us <= 4.0 * factor_us;
+}
+// later: bytes of the arena that the rest of the step takes.  *done: 0 = nothing was launched or taken.  Otherwise *Zk as in refit_both, *W1p: the
+// planes of W1's kept rows, *part: room for partials on the second stream.
+static strp_status refits_beside(strp_ctx* ctx, Aside& aside, Arena& arena, const RefitsIn& in, const WeightsOut& w2, const WeightsOut& w1, size_t later,
+                                 PlaneOp* Zk, PlaneOp* W1p, Arena* part, int* done) {
+  const int s = in.s, d = in.d;
+  const long long T = in.T, lds = round_up(s, 16), ldd = f64_ld(d);
+  *done = 0;
+  if (!refits_beside_pay(d, s, T) || !aside.ready()) return STRP_OK;
+  Arena a = arena;
+  bool ok = true;
+  auto take = [&](size_t bytes) {
+    void* p = a.take(bytes);
+    ok = ok && p;
+    return p;
+  };
+  auto planes = [&](long long r, long long k) {
+    PlaneOp op{(unsigned short*)take(2 * plane_elems(r, k)), nullptr, plane_kg(k), (int)((r + 127) / 128), nullptr};
+    if (in.planes == 2) op.lo = (unsigned short*)take(2 * plane_elems(r, k));
+    return op;
+  };
+  auto matrix = [&](int rows, long long ld) { return (double*)take(sizeof(double) * (size_t)rows * ld); };
+  const PlaneOp Zc = planes(T, s), At = planes(s, T), Zt = At;      // A's planes are read by the two products before Z's are written
+  double* const G = matrix(s, lds);
+  double* const Ginv = matrix(s, lds);
+  double* const R2 = matrix(d, lds);
+  double* const R1 = matrix(s, ldd);
+  double* const tmp2 = matrix(d, lds);
+  double* const tmp1 = matrix(s, ldd);
+  double* const sub = (double*)take(sizeof(double) * chol_scratch_elems(s));
+  const size_t most = ~size_t(0) >> 8;
+  const PlaneOp none{nullptr, nullptr, 0, 0, nullptr};
+  GemmP p[3] = {nt_plan(operand_for(ctx, STRP_PROD_GRAM, 0, At), operand_for(ctx, STRP_PROD_GRAM, 1, At), s, s, T, 1, most),
+                nt_plan(operand_for(ctx, STRP_PROD_RHS2, 0, in.Y), operand_for(ctx, STRP_PROD_RHS2, 1, At), d, s, T, 0, most),
+                nt_plan(operand_for(ctx, STRP_PROD_RHS1, 0, Zt), operand_for(ctx, STRP_PROD_RHS1, 1, in.X), s, d, T, 0, most)};
+  size_t partials = sizeof(float) * (size_t)nt_plan(none, none, d, d, T, 1, most).splits * d * d;      // E E^T
+  for (const GemmP& q : p) {
+    const size_t b = sizeof(float) * (size_t)q.splits * q.M * q.N;
+    partials = b > partials ? b : partials;
+  }
+  partials = (partials + 255) & ~size_t(255);
+  float* const pt = (float*)take(partials);
+  if (!ok || a.room() < later) return STRP_OK;
+  *done = 1;
+  arena = a;
+  *Zk = Zc;
+  *part = Arena(pt, partials);
+  auto product = [&](GemmP& q, ReduceP r) {
+    q.out = pt;
+    STRP_TRY(launch_gemm(ctx, q));
+    reduce_of(q, &r);
+    return launch_splitk_reduce(ctx, r);
+  };
+  STRP_TRY(split_act(ctx, in.A, STRP_F32, in.lda, in.idx, s, T, 0, 0, (unsigned short*)At.hi, (unsigned short*)At.lo, nullptr, nullptr));
+  ReduceP g = reduce_to_system(G, lds);
+  g.ridge_dev = in.lam2_dev;
+  STRP_TRY(product(p[0], g));
+  const CoJob* const pass = ctx->cojob;
+  ctx->cojob = nullptr;
+  // the factorisation first, so that it finds its CUs free
+  STRP_TRY(aside.follow());
+  {
+    const FlowWorkers few(ctx, flow_workers_beside(s));
+    STRP_TRY(factor_and_invert(ctx, Arena(sub, sizeof(double) * chol_scratch_elems(s)), G, s, lds, Ginv, lds));
+  }
+  aside.enter();
+  if (pass) STRP_TRY(launch_cojob(ctx, *pass));
+  STRP_TRY(product(p[1], reduce_to(R2, lds)));
+  STRP_TRY(aside.await());
+  STRP_TRY(split_act(ctx, in.Z, STRP_F32, in.lda, in.idx, s, T, 0, 1, (unsigned short*)Zt.hi, (unsigned short*)Zt.lo, (unsigned short*)Zc.hi, (unsigned short*)Zc.lo));
+  STRP_TRY(product(p[2], reduce_to(R1, ldd)));
+  STRP_TRY(apply_inverse_right(ctx, in.Linv1, d, d, R1, s, ldd, tmp1, w1));
+  SplitJob job;
+  STRP_TRY(weight_planes(ctx, arena, w1.Wc, SRC_F32, w1.ldc, s, d, 0, in.planes, w1.maxbits, W1p, &job));
+  STRP_TRY(split_small(ctx, &job, 1));
+  aside.leave();
+  return apply_inverse_right(ctx, Ginv, s, lds, R2, d, lds, tmp2, w2);
 }
 
 // Persistent per-module planes (caller-owned strp_module_state::cache), fixed at initialisation:
@@ -1055,15 +1239,46 @@ strp_status strp_refit(strp_ctx* ctx, strp_side side, const float* Gram, int32_t
     STRP_TAKE(ctx, arena, sys, double, (size_t)n * f64_ld(n));
     ri.sys = sys;
   }
-  const int prec = ctx->precision;
-  if (side == STRP_SIDE_FC2) {
-    STRP_TRY(make_t_planes(ctx, arena, Lhs, lhs_dtype, ld_lhs, nullptr, out, T, 0, planes_for(lhs_dtype, prec), &ri.Lhs));
-    STRP_TRY(make_t_planes(ctx, arena, Rhs, rhs_dtype, ld_rhs, idx, s, T, 0, planes_for(rhs_dtype, prec), &ri.Rhs));
-  } else {
-    STRP_TRY(make_t_planes(ctx, arena, Lhs, lhs_dtype, ld_lhs, idx, s, T, 0, planes_for(lhs_dtype, prec), &ri.Lhs));
-    STRP_TRY(make_t_planes(ctx, arena, Rhs, rhs_dtype, ld_rhs, nullptr, in, T, 0, planes_for(rhs_dtype, prec), &ri.Rhs));
-  }
+  const int prec = ctx->precision, npl = planes_for(lhs_dtype, prec), npr = planes_for(rhs_dtype, prec);
   ri.m = m; ri.n = n; ri.ld = f64_ld(n); ri.T = T;
+  // Neither the planes nor the right-hand side need the factor: they are made on the second stream beside it.  Where the workspace
+  // holds everything at once, with all of the product's partials: what is summed in which order does not depend on it.
+  Aside aside(ctx);
+  if (!chol_valid && refit_beside_pays(m, n, T, npl, npr)) {
+    Arena a = arena;
+    bool fits = true;
+    auto take = [&](size_t bytes) { fits = a.take(bytes) && fits; };
+    double* const sub = (double*)a.take(sizeof(double) * chol_scratch_elems(n));
+    double* const R = (double*)a.take(sizeof(double) * (size_t)m * ri.ld);
+    const Arena rest = a;
+    for (int i = 0; i < npl; ++i) take(2 * plane_elems(m, T));
+    for (int i = 0; i < npr; ++i) take(2 * plane_elems(n, T));
+    take(sizeof(double) * (size_t)m * ri.ld);
+    take(sizeof(float) * nt_partial_elems(m, n, T, 0));
+    if (sub && R && fits && aside.ready()) {
+      STRP_TRY(f32_to_f64_ridge(ctx, Gram, ldg, ri.sys, ri.ld, n, lambda, nullptr));
+      STRP_TRY(aside.follow());
+      {
+        const FlowWorkers few(ctx, flow_workers_beside(n));
+        STRP_TRY(factor_and_invert(ctx, Arena(sub, sizeof(double) * chol_scratch_elems(n)), ri.sys, n, ri.ld, ri.Linv, ri.ldl));
+      }
+      ri.linv_ready = ri.r_ready = 1;
+      ri.R = R;
+      arena = rest;
+      aside.enter();
+    }
+  }
+  if (side == STRP_SIDE_FC2) {
+    STRP_TRY(make_t_planes(ctx, arena, Lhs, lhs_dtype, ld_lhs, nullptr, out, T, 0, npl, &ri.Lhs));
+    STRP_TRY(make_t_planes(ctx, arena, Rhs, rhs_dtype, ld_rhs, idx, s, T, 0, npr, &ri.Rhs));
+  } else {
+    STRP_TRY(make_t_planes(ctx, arena, Lhs, lhs_dtype, ld_lhs, idx, s, T, 0, npl, &ri.Lhs));
+    STRP_TRY(make_t_planes(ctx, arena, Rhs, rhs_dtype, ld_rhs, nullptr, in, T, 0, npr, &ri.Rhs));
+  }
+  if (ri.r_ready) {
+    STRP_TRY(nt_product(ctx, arena, ri.Lhs, ri.Rhs, m, n, T, 0, reduce_to(ri.R, ri.ld)));
+    STRP_TRY(aside.join());
+  }
   STRP_TRY(ridge_solve(ctx, arena, ri, WeightsOut{side, idx, W, in, nullptr, 0, nullptr, nullptr}, sizeof(float) * (size_t)out * (size_t)in));
   return chol && !chol_direct ? copy_f64(ctx, ri.Linv, ri.ldl, chol, n, n) : STRP_OK;
 }
@@ -1098,8 +1313,11 @@ strp_status strp_module_init(strp_ctx* ctx, const strp_module_desc* desc, strp_m
   // X planes (persistent)
   STRP_TRY(split_act(ctx, st->X, desc->x_dtype, desc->ldx, nullptr, d, T, 0, 0, (unsigned short*)cv.Xt.hi, (unsigned short*)cv.Xt.lo,
                      (unsigned short*)cv.Xc.hi, (unsigned short*)cv.Xc.lo));
-  {
-    Arena a2 = arena;
+  auto al = [](size_t bytes) { return (bytes + 255) & ~size_t(255); };
+  const size_t targets_bytes = npw * (al(2 * plane_elems(f, d)) + al(2 * plane_elems(d, f))) + npa * al(2 * plane_elems(T, f)) +
+                               al(64 * (((size_t)f + 127) / 128) * (((size_t)T + 127) / 128));
+  // Z0, A, Y and Y's planes
+  auto targets = [&](Arena a2) -> strp_status {
     PlaneOp W1p, W2p, A0k8;
     SplitJob jobs[2];
     STRP_TRY(weight_planes(ctx, a2, st->W1hat, wkind, d, f, d, 0, npw, wmax, &W1p, &jobs[0]));
@@ -1137,26 +1355,53 @@ strp_status strp_module_init(strp_ctx* ctx, const strp_module_desc* desc, strp_m
       gemm_plan_tiles(p, 1);
       STRP_TRY(launch_gemm(ctx, p));
     }
-  }
-  STRP_TRY(split_act(ctx, st->Y, STRP_F32, lda, nullptr, d, T, 0, 0, (unsigned short*)cv.Yt.hi, (unsigned short*)cv.Yt.lo, nullptr,
-                     nullptr));
-  {  // H = X X^T (fp32 copy and fp64 system), lam1 = delta tr(H)/d, factor of H + lam1 I
-    Arena a2 = arena;
-    STRP_TAKE(ctx, a2, diag, double, (size_t)d);
-    STRP_TAKE(ctx, a2, Hd, double, (size_t)d * d);
+    return split_act(ctx, st->Y, STRP_F32, lda, nullptr, d, T, 0, 0, (unsigned short*)cv.Yt.hi, (unsigned short*)cv.Yt.lo, nullptr, nullptr);
+  };
+  // H = X X^T (fp32 copy and fp64 system), lam1 = delta tr(H)/d
+  auto gram = [&](Arena a2, double* diag, double* Hd) -> strp_status {
     ReduceP r = reduce_to_system(Hd, d);
     r.outf = st->H; r.ldof = d; r.diag = diag;
     STRP_TRY(nt_product(ctx, a2, cv.Xt, cv.Xt, d, d, T, 1, r));
     hipLaunchKernelGGL(scaled_sum_kernel, dim3(1), dim3(1024), 0, ctx->stream, (const double*)diag, 1, d, params->delta / (double)d, sc + SC_TRH,
                        sc + SC_LAM1, Hd, (long long)d, d);
-    // the chain wants its result 16-byte aligned; cholH need not be
-    double* Linv = st->cholH;
-    if (!aligned16(Linv)) {
-      STRP_TAKE(ctx, a2, scratch, double, (size_t)d * d);
-      Linv = scratch;
-    }
+    return STRP_OK;
+  };
+  // factor of H + lam1 I; the chain wants its result 16-byte aligned, cholH need not be: then it goes to scratch first
+  auto factor = [&](Arena a2, double* Hd, double* scratch) -> strp_status {
+    double* const Linv = scratch ? scratch : st->cholH;
     STRP_TRY(factor_and_invert(ctx, a2, Hd, d, d, Linv, d));
-    if (Linv != st->cholH) STRP_TRY(copy_f64(ctx, Linv, d, st->cholH, d, d));
+    return scratch ? copy_f64(ctx, Linv, d, st->cholH, d, d) : STRP_OK;
+  };
+  // The factor needs nothing of the targets, nor they of it: where the workspace holds both they are made beside it on the second stream,
+  // behind the product, so that it finds its CUs free (us of the initialisation, 128 x 520 over 1000 tokens 90 -> 85, 440 x 1440, 9000 259 -> 200, 768 x
+  // 3072, 16384 639 -> 546, 1000 x 3000, 30000, fp32 1696 -> 1553; 64 x 256, 512 65 either way).
+  Aside aside(ctx);
+  Arena ah = arena;
+  double* const diag = (double*)ah.take(sizeof(double) * (size_t)d);
+  double* const Hd = (double*)ah.take(sizeof(double) * (size_t)d * d);
+  if (!diag || !Hd) return fail(ctx, STRP_ENOMEM, "workspace too small for H");
+  const bool copied = !aligned16(st->cholH);
+  Arena both = ah;
+  double* const sub = (double*)both.take(sizeof(double) * chol_scratch_elems(d));
+  double* scratch = copied ? (double*)both.take(sizeof(double) * (size_t)d * d) : nullptr;
+  if (d >= 2 * NB && sub && (scratch || !copied) && both.room() >= targets_bytes && both.room() >= sizeof(float) * nt_partial_elems(d, d, T, 1) && aside.ready()) {
+    STRP_TRY(gram(both, diag, Hd));
+    STRP_TRY(aside.follow());
+    {
+      const FlowWorkers few(ctx, flow_workers_beside(d));
+      STRP_TRY(factor(Arena(sub, sizeof(double) * chol_scratch_elems(d)), Hd, scratch));
+    }
+    aside.enter();
+    STRP_TRY(targets(both));
+    STRP_TRY(aside.join());
+  } else {
+    STRP_TRY(targets(arena));
+    STRP_TRY(gram(ah, diag, Hd));
+    if (copied) {
+      STRP_TAKE(ctx, ah, linv, double, (size_t)d * d);
+      scratch = linv;
+    }
+    STRP_TRY(factor(ah, Hd, scratch));
   }
   {  // last: fp32 weights may be refitted in the arrays of the dense ones
     const FillRange z[3] = {{st->W1, sizeof(float) * (size_t)f * d}, {st->W2, sizeof(float) * (size_t)f * d}, {st->mask, (size_t)f}};
@@ -1293,10 +1538,20 @@ strp_status strp_admm_step(strp_ctx* ctx, const strp_module_desc* desc, strp_mod
   PlaneOp Zk8pre;
   memset(&Zk8pre, 0, sizeof(Zk8pre));
   const bool z_planes_once = (stages & STRP_STAGE_REFIT1) && (stages & STRP_STAGE_AUPD);
-  int refits_done = 0;
+  int refits_done = 0, beside = 0;
+  PlaneOp W2Sp, W2Tp, W1Sp;      // planes of the kept weights, shared by the stages below
+  memset(&W2Sp, 0, sizeof(W2Sp));
+  memset(&W2Tp, 0, sizeof(W2Tp));
+  memset(&W1Sp, 0, sizeof(W1Sp));
+  Aside aside(ctx);
+  Arena side_part;
   if (z_planes_once && (stages & STRP_STAGE_REFIT2)) {
     const RefitsIn in{st->A, st->Z, lda, st->idx, s, d, T, npa, cv.Yt, cv.Xt, st->cholH, sc + SC_LAM2};
     STRP_TRY(refit_both(ctx, arena, in, w2out, w1out, &Zk8pre, &refits_done));
+    if (!refits_done && W1S) {
+      STRP_TRY(refits_beside(ctx, aside, arena, in, w2out, w1out, bytes_after_refits(d, s, T, npa), &Zk8pre, &W1Sp, &side_part, &beside));
+      refits_done = beside;
+    }
   }
   if (refits_done) {
     // the fc2 weights are there
@@ -1332,18 +1587,13 @@ strp_status strp_admm_step(strp_ctx* ctx, const strp_module_desc* desc, strp_mod
   } else if (W2S) {
     STRP_TRY(gather_weights(ctx, w2out, d, s));
   }
-  // planes of the kept weights (shared by the stages below)
-  PlaneOp W2Sp, W2Tp, W1Sp;
-  memset(&W2Sp, 0, sizeof(W2Sp));
-  memset(&W2Tp, 0, sizeof(W2Tp));
-  memset(&W1Sp, 0, sizeof(W1Sp));
   if (W2S) {
     SplitJob jobs[3];
     STRP_TRY(weight_planes(ctx, arena, W2S, SRC_F32, sp, d, s, 0, npa, wmax + MAX_W2, &W2Sp, &jobs[0]));
     const bool both = (stages & STRP_STAGE_AUPD) != 0;
     if (both) STRP_TRY(weight_planes(ctx, arena, W2S, SRC_F32, sp, s, d, 1, npa, wmax + MAX_W2, &W2Tp, &jobs[1]));
     int n = both ? 2 : 1;
-    if (refits_done && W1S) STRP_TRY(weight_planes(ctx, arena, W1S, SRC_F32, d, s, d, 0, npa, wmax + MAX_W1, &W1Sp, &jobs[n++]));
+    if (refits_done && !beside && W1S) STRP_TRY(weight_planes(ctx, arena, W1S, SRC_F32, d, s, d, 0, npa, wmax + MAX_W1, &W1Sp, &jobs[n++]));
     STRP_TRY(split_small(ctx, jobs, n));
   }
   // ---- a-update, part 1: B = W^T M^-1 with M = (beta/alpha) I + W W^T, W = W2[:, S] -------------------------
@@ -1355,6 +1605,7 @@ strp_status strp_admm_step(strp_ctx* ctx, const strp_module_desc* desc, strp_mod
   // and |Y - W A_S|_F^2 = (beta/alpha)^2 <M^-2, E E^T>: a d x d Gram of E over the tokens (half the work of the product
   // W A_S) and two d x d matrices.  One fp16 plane of E is ample for a sum reported to 1e-3.
   const bool term1_identity = (stages & STRP_STAGE_AUPD) && (stages & STRP_STAGE_OBJ);
+  bool residual_aside = false;
   float* M2f = nullptr;
   double* red_t1 = nullptr;
   if (term1_identity) {
@@ -1369,15 +1620,21 @@ strp_status strp_admm_step(strp_ctx* ctx, const strp_module_desc* desc, strp_mod
       STRP_TAKE(ctx, arena, m2, float, (size_t)d * d);
       M2f = m2;
     }
-    const size_t al = 255;
-    const size_t cbytes = ((nt_partial_elems(d, d, sp, 1) * 4 + al) & ~al) + ((chol_scratch_elems(d) * 8 + al) & ~al) +
-                          2 * ((plane_elems(d, d) * 2 + al) & ~al) + 4096;
+    const size_t cbytes = m_chain_bytes(d, sp);
     STRP_TAKE(ctx, arena, cblock, char, cbytes);
     Arena a2(cblock, cbytes);
     ReduceP r = reduce_to_system(Md, d);
     r.ridge = params->beta / params->alpha;
     STRP_TRY(nt_product(ctx, a2, W2Sp, W2Sp, d, d, sp, 1, r));
-    STRP_TRY(factor_and_invert(ctx, a2, Md, d, d, Linv, d));
+    // With both refits done E is next, which needs nothing of this chain: it runs on the second stream, from where M is factored on
+    // (us a step, 440 x 600 over 9000 tokens 546 -> 496, 200 x 300 over 4000 302 -> 288, 96 x 200 over 4000 247 -> 238; with one tile of M the
+    // two waits cost what there is to hide: 64 x 128 over 512 172.7 / 173.7).
+    residual_aside = refits_done && (beside || d > NB) && aside.ready();
+    if (residual_aside) STRP_TRY(aside.follow());
+    {
+      const FlowWorkers few(ctx, residual_aside ? flow_workers_beside(d) : 0);
+      STRP_TRY(factor_and_invert(ctx, a2, Md, d, d, Linv, d));
+    }
     // M is well conditioned (its spectrum lies in [beta/alpha, beta/alpha + |W|^2]): form M^-1 = Linv^T Linv
     // (lower half, fp64) and B = W^T M^-1 on the fp16-split matrix cores instead of a third fp64 solve
     STRP_TRY(gram_of_inverse(ctx, Linv, d, d, Md, d, wmax + MAX_MI));
@@ -1478,6 +1735,7 @@ strp_status strp_admm_step(strp_ctx* ctx, const strp_module_desc* desc, strp_mod
       STRP_TAKE(ctx, a2, ekl2, unsigned short, plane_elems(T, d));
       ekl = ekl2;
     }
+    if (residual_aside) aside.enter();
     {  // E = Y - W relu(Z_S), kept only as K8 planes
       GemmP p;
       memset(&p, 0, sizeof(p));
@@ -1494,12 +1752,20 @@ strp_status strp_admm_step(strp_ctx* ctx, const strp_module_desc* desc, strp_mod
       STRP_TAKE(ctx, a3, eth, unsigned short, plane_elems(d, T));
       STRP_TRY(plane_c_to_t(ctx, ekh, eth, d, T));
       const PlaneOp Et{eth, nullptr, plane_kg(T), (int)((d + 127) / 128), nullptr};
+      if (beside) a3 = side_part;
+      GemmP p = nt_plan(Et, Et, d, d, T, 1, a3.room() / sizeof(float));
+      STRP_TAKE(ctx, a3, part, float, (size_t)p.splits * d * d);
+      p.out = part;
+      STRP_TRY(launch_gemm(ctx, p));
+      STRP_TRY(aside.join());        // the sum below is with M^-2
       ReduceP r = reduce_to(nullptr, 0);
       r.dot = M2f; r.red = red_t1;
-      STRP_TRY(nt_product(ctx, a3, Et, Et, d, d, T, 1, r));
+      reduce_of(p, &r);
+      STRP_TRY(launch_splitk_reduce(ctx, r));
       const double c = params->beta / params->alpha;
       fin.do_1 = 1; fin.red_1 = red_t1; fin.n1 = reduce_blocks(d, d); fin.stride1 = 1; fin.c1 = params->alpha / (double)T * c * c;
     }
+    STRP_TRY(aside.join());
     {  // A_S = relu(Z_S) + B E
       GemmP p;
       memset(&p, 0, sizeof(p));

@@ -31,6 +31,12 @@ struct strp_ctx {
   unsigned int* ticket;
   unsigned int* tickets;  // all of them, on this device
   int ticket_due;         // another workspace has been set: the next weight statistics take the next counter
+  // A second stream for work that a call's latency-bound part leaves the chip to (see Aside in strp_api.hip), and the events that order the two.
+  // Made by the first call that can use them; side_state: 0 not yet, 1 there, -1 not to be had.
+  hipStream_t side;
+  hipEvent_t side_event[2];
+  int side_state;
+  int flow_workers;       // workgroups of the next factorisation in one launch, which has other kernels beside it; 0: it has the chip to itself
 };
 
 struct Profiler;
@@ -231,7 +237,10 @@ static inline size_t chol_scratch_elems(long long n) {
 strp_status chol_inverse(strp_ctx* ctx, double* A, int n, long long ld, double* sub, double* Linv, long long ldv, int32_t* status);
 // The same in one launch, for the orders that are faster so beside a pass of these bytes (0: none).
 bool chol_flow_ok(int n, double pass_bytes);
+bool chol_flow_can(int n);
 strp_status chol_flow(strp_ctx* ctx, double* A, int n, long long ld, double* Linv, long long ldv, int32_t* status, const CoJob& job);
+// a pass that rides with nothing: a launch of its own
+strp_status launch_cojob(strp_ctx* ctx, const CoJob& job);
 // X (L L^T)^-1 = (X Linv^T) Linv for X [m x n] (ldx), as refitted weights; tmp: m x ldx scratch.
 //   FC2: W[i, idx[j]] = result[i, j] (m rows of W);  FC1: W[idx[i], j] = result[i, j];  other entries of W are not written.
 //   Wc (optional): the result itself, [m x ldc]; maxbits (optional): atomic maximum of the bits of its magnitudes; sumsq

@@ -509,6 +509,56 @@ def check_tiles_of_the_kept_rows():
         assert kinds == want, (d, f, T, k, kinds, want)
 
 
+def _ordered_step(lib, d, f, T, k, ws):
+    """an iteration's launches on a workspace of ws bytes, demangled, by what they are: products by what they make"""
+    strp = lib.strp
+    records, names = _step_records(lib, d, f, T, k, ws)
+    names = [n.split("(")[0].replace("void ", "").replace("strp::", "").split("<")[0] for n in names if n]
+    gemm = iter(r[0] for r in records if r[0].startswith("gemm_"))
+    return [next(gemm) if n.startswith("gemm_") else n for n in names]
+
+
+def check_second_stream():
+    """What runs beside what, and what waits for what, in an iteration whose refits go beside the factorisation.  All of it is over before
+    what the caller's stream gets next, and the workspace that the library asks for is enough."""
+    lib = Library()
+    strp, fake = lib.strp, lib.fake
+    fake.fake_streams(1)
+    seen = set()
+    for d, f, T, k_max in MODULES + [(440, 1440, 9000, 600), (264, 1000, 70000, 401), (768, 1536, 2000, 1408)]:
+        k = k_max or f
+        ld = (T + 7) // 8 * 8
+        need = lib.lib.strp_workspace_bytes(C.byref(strp.ModuleDesc(d, f, T, ld, ld, strp.F32, strp.F32, k_max)))
+        ops = _ordered_step(lib, d, f, T, k, need)
+        side = [i for i in range(len(ops)) if fake.fake_stream(i)]
+        seen.add(len(side) > 5)
+        assert ops == _ordered_step(lib, d, f, T, k, 1 << 50), (d, f, T, k)
+        before = fake.fake_before
+        assert lib.lib.strp_set_workspace(lib.h, 1 << 40, 1 << 50) == strp.OK          # its clearing launch comes last
+        last = len(ops)
+        assert fake.fake_stream(last) == 0 and all(before(i, last) for i in range(last))
+        if len(side) <= 5:
+            continue
+        at = lambda name, nth=0: [i for i, o in enumerate(ops) if o == name][nth]
+        own = [i for i in range(len(ops)) if not fake.fake_stream(i)]
+        factors = [i for i, o in enumerate(ops) if o in ("chol_flow_kernel", "chol_begin_kernel")]
+        solves = [i for i, o in enumerate(ops) if o.startswith("dgemm_kernel")]
+        resid = at("gemm_h2x2_resid")
+        own_solve, side_solve = min(i for i in solves if i in own), min(i for i in solves if i in side)
+        rhs2, rhs1 = [i for i, o in enumerate(ops) if o == "gemm_h2x2_partial" and i in side][:2]
+        planes = [i for i, o in enumerate(ops) if o == "split_t_kernel"]
+        small = [i for i, o in enumerate(ops) if o == "split_small_kernel"]
+        assert factors[0] in own and factors[-1] in own
+        assert not before(factors[0], rhs2) and not before(factors[0], rhs1) and not before(factors[-1], resid)       # beside it
+        assert before(rhs2 + 1, own_solve) and before(factors[0], own_solve) and ops[rhs2 + 1] == "splitk_reduce_kernel"
+        assert not before(rhs1, own_solve)
+        assert before(planes[0], rhs2) and before(rhs2, planes[1]) and before(planes[1], rhs1) and before(rhs1 + 1, side_solve)
+        assert before(min(i for i in small if i in own), resid) and before(planes[1], resid)
+        for update in (at("gemm_h2x2_aupd"), at("gemm_h2x2_zupd")):
+            assert update in own and all(before(i, update) for i in range(update))
+    assert seen == {True, False}
+
+
 def check_weight_statistics_without_a_counter():
     """A call is one launch for up to eight matrices; a context that found no counter left takes one more."""
     lib = Library()
@@ -558,7 +608,7 @@ def check_weight_statistics_counter():
     assert counter(lib.h) not in (0, a, b, c)
 
 
-CHECKS = [check_systems_of_the_factorisations, check_which_factorisation_runs, check_tiles_of_the_solves, check_tiles_of_the_kept_rows, check_weight_statistics_counter, check_weight_statistics_without_a_counter, check_what_the_gram_matrices_cover, check_what_the_large_systems_cover, check_selection_of_a_very_wide_module, check_weight_statistics_arguments, check_weight_statistics_workgroups, check_chains, check_workspace_of_a_module, check_least_workspace_of_a_step, check_rows_of_the_fc2_system, check_work_of_shared_launches, check_profile_classes, check_workspace_of_a_factorisation, check_cached_factor_needs_no_alignment]
+CHECKS = [check_systems_of_the_factorisations, check_which_factorisation_runs, check_tiles_of_the_solves, check_tiles_of_the_kept_rows, check_second_stream, check_weight_statistics_counter, check_weight_statistics_without_a_counter, check_what_the_gram_matrices_cover, check_what_the_large_systems_cover, check_selection_of_a_very_wide_module, check_weight_statistics_arguments, check_weight_statistics_workgroups, check_chains, check_workspace_of_a_module, check_least_workspace_of_a_step, check_rows_of_the_fc2_system, check_work_of_shared_launches, check_profile_classes, check_workspace_of_a_factorisation, check_cached_factor_needs_no_alignment]
 
 
 @pytest.fixture(scope="session")
