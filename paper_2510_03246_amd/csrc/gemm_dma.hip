@@ -270,17 +270,22 @@ __global__ __launch_bounds__(512, 1) void gemm_dma_kernel(const GemmP p) {
 // wavefront and 32 steps instead of 24.  What bounds it is power, as the kernel above, on large products (A_S of 768 x 1536 x 65536 434 us,
 // 1.07 PFLOP/s executed, whatever the wavefronts' priorities or a staggered start), and on smaller ones the start and epilogue of the last
 // round, which are half as long.  The sums are those of the kernel above, bit for bit.
+// NI: 16-row tiles of P a workgroup has, 8 (128 x 256) or, for products with few tiles, 4 (64 x 256).
 #pragma clang diagnostic push
 #pragma clang diagnostic ignored "-Winline-asm"
 __device__ __forceinline__ void lds_dma_16s(const void* base, unsigned lane_off, unsigned lds_addr) {
   asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" : : "s"(lds_addr), "v"(lane_off), "s"(base) : "memory", "m0");
 }
 #pragma clang diagnostic pop
-template <int NPP, int NPQ, bool TOKENS>
+template <int NPP, int NPQ, bool TOKENS, int NI>
 __global__ __launch_bounds__(256, 2) void gemm_half_kernel(const GemmP p) {
-  constexpr int NW = 4, PM = 128, PN = 256;
-  constexpr int PAIR = 8192;                       // bytes of one plane of 128 rows over 32 contraction steps, contiguous in memory too
-  __shared__ __attribute__((aligned(1024))) unsigned char smem[2][NPP * PAIR];
+  constexpr int NW = 4, PM = 16 * NI, PN = 256;
+  constexpr int PAIR = 8192;                       // bytes of one plane of a panel of 128 rows over 32 contraction steps, contiguous in memory
+  constexpr int PLANE = 64 * PM;                   // the tile's rows of them, in LDS
+  // pairs of stages in flight or in use: with 64 rows a pair is multiplied in half the time, and there are registers for twice as many
+  constexpr int DEPTH = NI == 8 ? 2 : 4;
+  constexpr int LP = NPP * NI / 4, LQ = 4 * NPQ;   // a wavefront's requests for a pair
+  __shared__ __attribute__((aligned(1024))) unsigned char smem[DEPTH][NPP * PLANE];
   __shared__ double sred[NW][2];
   __shared__ int srow[PM];
 
@@ -297,21 +302,22 @@ __global__ __launch_bounds__(256, 2) void gemm_half_kernel(const GemmP p) {
   if (p.oidx && tid < PM && m0 + tid < p.M) my_row = p.oidx[m0 + tid];
   const int wn = __builtin_amdgcn_readfirstlane(tid >> 6);
 
-  // P: this wavefront moves two KB of each plane of a pair
+  // P: this wavefront moves its share of each plane of a pair, a KB at a time: 64 rows of a k-group
   const char* pp[NPP];
   const unsigned lds_base = (unsigned)(size_t)(__attribute__((address_space(3))) unsigned char*)&smem[0][0];
 #pragma unroll
-  for (int pl = 0; pl < NPP; ++pl) pp[pl] = (const char*)((pl ? p.P.lo : p.P.hi) + ((long long)tm * p.P.kg + g0) * 1024) + wn * 2048;
+  for (int pl = 0; pl < NPP; ++pl)
+    pp[pl] = (const char*)((pl ? p.P.lo : p.P.hi) + ((long long)(m0 >> 7) * p.P.kg + g0) * 1024) + wn * 2048 + (m0 & 127) * 16;
   auto issue_p = [&](int pr) {
     const long long o = (long long)(pr < npairs ? pr : npairs - 1) * PAIR;
 #pragma unroll
     for (int pl = 0; pl < NPP; ++pl)
 #pragma unroll
-      for (int i = 0; i < 2; ++i)
-        lds_dma_16s(pp[pl] + o + i * 1024, lane * 16, lds_base + (unsigned)((pr & 1) * NPP + pl) * PAIR + wn * 2048 + i * 1024);
+      for (int i = 0; i < NI / 4; ++i)
+        lds_dma_16s(pp[pl] + o + i * 1024, lane * 16, lds_base + (unsigned)((pr & (DEPTH - 1)) * NPP + pl) * PLANE + wn * (16 * PM) + i * 1024);
   };
   // lane l has the chunk of k-group l / 16 and row l % 16 of a fragment
-  const unsigned frag = (unsigned)((lane >> 4) * 128 + (lane & 15)) * 16;
+  const unsigned frag = (unsigned)((lane >> 4) * 128 + (lane & 15)) * 16, frag_p = (unsigned)((lane >> 4) * PM + (lane & 15)) * 16;
   const char* qp[NPQ];
   {
     const int n = n0 + wn * 64;
@@ -334,14 +340,14 @@ __global__ __launch_bounds__(256, 2) void gemm_half_kernel(const GemmP p) {
     }
   };
   auto read_p = [&](PF& f, int pr, int i) {
-    const unsigned char* st = smem[pr & 1];
-    f.h = *(const uintx4*)(st + frag + i * 256);
-    if (NPP == 2) f.l = *(const uintx4*)(st + PAIR + frag + i * 256);
+    const unsigned char* st = smem[pr & (DEPTH - 1)];
+    f.h = *(const uintx4*)(st + frag_p + i * 256);
+    if (NPP == 2) f.l = *(const uintx4*)(st + PLANE + frag_p + i * 256);
   };
 
-  floatx4 acc[8][4];
+  floatx4 acc[NI][4];
 #pragma unroll
-  for (int i = 0; i < 8; ++i)
+  for (int i = 0; i < NI; ++i)
 #pragma unroll
     for (int j = 0; j < 4; ++j) acc[i][j] = floatx4{0.0f, 0.0f, 0.0f, 0.0f};
   auto mma = [&](uintx4 a, uintx4 b, floatx4 c) {
@@ -373,53 +379,50 @@ __global__ __launch_bounds__(256, 2) void gemm_half_kernel(const GemmP p) {
     if (NPQ == 2) asm volatile("" : "+v"(f.l[0]), "+v"(f.l[1]), "+v"(f.l[2]), "+v"(f.l[3]));
   };
   auto pair_step = [&](int pr, QF& b, QF& bn) {
-#define STRP_ROW(i, cur, nxt)                \
-    read_p(nxt, pr, (i) + 1);                \
-    __builtin_amdgcn_sched_barrier(0);       \
-    pass_hl(acc[i], cur, b);                 \
-    pass_lh(acc[i], cur, b);                 \
-    pass_hh(acc[i], cur, b);                 \
-    __builtin_amdgcn_sched_barrier(0);
-    STRP_ROW(0, pa, pb)
-    STRP_ROW(1, pb, pa)
-    STRP_ROW(2, pa, pb)
-    STRP_ROW(3, pb, pa)
-    STRP_ROW(4, pa, pb)
-    STRP_ROW(5, pb, pa)
-    STRP_ROW(6, pa, pb)
-#undef STRP_ROW
-    wait_vmcnt_lgkm0<0>();         // the next pair has landed; this wavefront's fragment reads of this pair are complete
+    // the fragments of a row of tiles are read ahead of the matrix-core instructions of the row before it
+#pragma unroll
+    for (int i = 0; i < NI - 1; ++i) {
+      PF& cur = i & 1 ? pb : pa;
+      read_p(i & 1 ? pa : pb, pr, i + 1);
+      __builtin_amdgcn_sched_barrier(0);
+      pass_hl(acc[i], cur, b);
+      pass_lh(acc[i], cur, b);
+      pass_hh(acc[i], cur, b);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    wait_vmcnt_lgkm0<(DEPTH - 2) * (LP + LQ)>();         // the next pair has landed; this wavefront's fragment reads of this pair are complete
     arrived(bn);
     __syncthreads();               // ... and so for every wavefront: the pair's slot may be overwritten
-    pass_hh(acc[7], pb, b);
+    pass_hh(acc[NI - 1], pb, b);
     __builtin_amdgcn_sched_barrier(0);
-    issue_p(pr + 2);
+    issue_p(pr + DEPTH);
     read_p(pa, pr + 1, 0);         // past the last pair this reads a slot that is never multiplied
     __builtin_amdgcn_sched_barrier(0);
-    pass_hl(acc[7], pb, b);
-    pass_lh(acc[7], pb, b);
+    pass_hl(acc[NI - 1], pb, b);
+    pass_lh(acc[NI - 1], pb, b);
     __builtin_amdgcn_sched_barrier(0);
-    load_q(b, pr + 2);
+    load_q(b, pr + DEPTH);
     __builtin_amdgcn_sched_barrier(0);
   };
 
-  QF q0, q1;
-  issue_p(0);
-  load_q(q0, 0);
-  issue_p(1);
-  load_q(q1, 1);
-  wait_vmcnt<0>();
-  arrived(q0);
-  arrived(q1);
+  QF q[DEPTH];
+#pragma unroll
+  for (int d = 0; d < DEPTH; ++d) {
+    issue_p(d);
+    load_q(q[d], d);
+  }
+  wait_vmcnt<(DEPTH - 1) * (LP + LQ)>();
+  arrived(q[0]);
   __syncthreads();
   read_p(pa, 0, 0);
   int pr = 0;
 #pragma unroll 1
-  for (; pr + 1 < npairs; pr += 2) {
-    pair_step(pr, q0, q1);
-    pair_step(pr + 1, q1, q0);
-  }
-  if (pr < npairs) pair_step(pr, q0, q1);
+  for (; pr + DEPTH <= npairs; pr += DEPTH)
+#pragma unroll
+    for (int d = 0; d < DEPTH; ++d) pair_step(pr + d, q[d], q[(d + 1) % DEPTH]);
+#pragma unroll
+  for (int d = 0; d < DEPTH - 1; ++d)
+    if (pr + d < npairs) pair_step(pr + d, q[d], q[d + 1]);
   wait_vmcnt<0>();
   if (tid < PM) srow[tid] = my_row;
   __syncthreads();
@@ -469,10 +472,11 @@ __global__ __launch_bounds__(256, 2) void gemm_half_kernel(const GemmP p) {
 
 template <int NPP, int NPQ>
 static void launch_dma(strp_ctx* ctx, const GemmP& p) {
-  if (p.wt == 3) {
-    const dim3 grid(gemm_grid_blocks(p)), block(256);
-    if (p.epi == EPI_PARTIAL || p.epi == EPI_AUPD || p.epi == EPI_ZUPD) hipLaunchKernelGGL((gemm_half_kernel<NPP, NPQ, true>), grid, block, 0, ctx->stream, p);
-    else hipLaunchKernelGGL((gemm_half_kernel<NPP, NPQ, false>), grid, block, 0, ctx->stream, p);
+  if (p.wt == 3 || p.wt == 5) {
+    const auto go = [&](auto kernel) { hipLaunchKernelGGL(kernel, dim3(gemm_grid_blocks(p)), dim3(256), 0, ctx->stream, p); };
+    const bool tokens = p.epi == EPI_PARTIAL || p.epi == EPI_AUPD || p.epi == EPI_ZUPD;
+    if (p.wt == 3) tokens ? go(gemm_half_kernel<NPP, NPQ, true, 8>) : go(gemm_half_kernel<NPP, NPQ, false, 8>);
+    else tokens ? go(gemm_half_kernel<NPP, NPQ, true, 4>) : go(gemm_half_kernel<NPP, NPQ, false, 4>);
     return;
   }
   const dim3 grid(gemm_grid_blocks(p)), block(512);

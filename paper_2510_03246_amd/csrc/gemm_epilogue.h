@@ -34,7 +34,7 @@ __device__ __forceinline__ double wave_sum(double v) {
 // Which output tile and K split a block works on.
 //
 // Blocks are dealt round-robin to the 8 XCDs (block b runs on XCD b % 8) and each XCD keeps 32 blocks of the
-// pipelined kernel resident (64 of 128 x 256), starting the next of its blocks when one retires.  Each XCD has its own L2, so the
+// pipelined kernel resident (64 of 128 x 256 or 64 x 256), starting the next of its blocks when one retires.  Each XCD has its own L2, so the
 // 32 blocks resident on an XCD should share operand panels: the work list is ordered tile group by tile group
 // (gm x gn tiles, all of one K split, then the next split of the same group), and XCD x takes entries
 // [256 c + 32 x, 256 c + 32 x + 32) of it in its c-th round; the last round's entries are dealt out the same way, as
@@ -43,7 +43,7 @@ __device__ __forceinline__ double wave_sum(double v) {
 // ceil(n/2) x (2 h + 1) tiles, h = floor(n/2) (row r holds triangle row r + h followed by triangle row h - 1 - r), so that
 // the same grouping applies and no workgroup is empty.
 __device__ __forceinline__ void decode_tile(const GemmP& p, int bid, int nblocks, int& tm, int& tn, int& split) {
-  const int ls = p.wt == 3 ? 6 : 5, full = nblocks & ~((8 << ls) - 1);
+  const int ls = p.wt == 3 || p.wt == 5 ? 6 : 5, full = nblocks & ~((8 << ls) - 1);
   int q = bid;
   if (bid < full) {
     const int x = bid & 7, j = bid >> 3;
@@ -307,10 +307,10 @@ __device__ __forceinline__ void quarter_swap(float a, float b, float& x, float& 
   y = __builtin_bit_cast(float, (unsigned int)r[1]);
 }
 
-// acc[8][4]: the wavefront's 128 x 64 outputs as 8 x 4 tiles of 16 x 16.  IJ walks its 4 x 2 tiles of 32 x 32.
-template <int EPI, int IJ>
-__device__ __forceinline__ void epilogue_walk16(const GemmP& p, floatx4 (&acc)[8][4], float unscale, int mbase, int nbase, int m_blk, double& red0, double& red1) {
-  if constexpr (IJ < 8) {
+// acc[NI][4]: the wavefront's 16 NI x 64 outputs as NI x 4 tiles of 16 x 16.  IJ walks its NI / 2 x 2 tiles of 32 x 32.
+template <int EPI, int IJ, int NI>
+__device__ __forceinline__ void epilogue_walk16(const GemmP& p, floatx4 (&acc)[NI][4], float unscale, int mbase, int nbase, int m_blk, double& red0, double& red1) {
+  if constexpr (IJ < NI) {
     constexpr int I = IJ / 2, J = IJ % 2;
     float none[16];                 // no sums of rows here
     floatx16 a16;
@@ -329,13 +329,13 @@ __device__ __forceinline__ void epilogue_walk16(const GemmP& p, floatx4 (&acc)[8
     if (edge) epilogue_tile<EPI, true, true, 1>(p, a16, unscale, mt, nt, 0, nullptr, m_blk, red0, red1, none, none);
     else epilogue_tile<EPI, true, false, 1>(p, a16, unscale, mt, nt, 0, nullptr, m_blk, red0, red1, none, none);
     __builtin_amdgcn_sched_barrier(0);
-    epilogue_walk16<EPI, IJ + 1>(p, acc, unscale, mbase, nbase, m_blk, red0, red1);
+    epilogue_walk16<EPI, IJ + 1, NI>(p, acc, unscale, mbase, nbase, m_blk, red0, red1);
   }
 }
 // mbase = first row of the wavefront's tile + 8 (lane / 32), nbase = first column + lane % 32.  STORE, INITZ, RESID
-template <int EPI>
-__device__ __forceinline__ void epilogue16(const GemmP& p, floatx4 (&acc)[8][4], float unscale, int mbase, int nbase, int m_blk, double& red0, double& red1) {
-  epilogue_walk16<EPI, 0>(p, acc, unscale, mbase, nbase, m_blk, red0, red1);
+template <int EPI, int NI>
+__device__ __forceinline__ void epilogue16(const GemmP& p, floatx4 (&acc)[NI][4], float unscale, int mbase, int nbase, int m_blk, double& red0, double& red1) {
+  epilogue_walk16<EPI, 0, NI>(p, acc, unscale, mbase, nbase, m_blk, red0, red1);
 }
 
 // ---- the same for transposed 16x16 accumulators -----------------------------------------------------------------------
@@ -470,30 +470,30 @@ __device__ __forceinline__ void token_row(const GemmP& p, const floatx4 (&c)[4],
   }
 }
 
-// acc[8][4]: the wavefront's 128 x 64 outputs as 8 x 4 transposed tiles of 16 x 16; m0w, n0w: its first row and column
-template <int EPI, bool ZWRITE, bool Z0, int I, int AHEAD>
-__device__ __forceinline__ void token_walk(const GemmP& p, floatx4 (&acc)[8][4], TokenRow<EPI, ZWRITE, Z0> (&in)[AHEAD], float unscale, int m0w, int n0w,
+// acc[NI][4]: the wavefront's 16 NI x 64 outputs as NI x 4 transposed tiles of 16 x 16; m0w, n0w: its first row and column
+template <int EPI, bool ZWRITE, bool Z0, int I, int AHEAD, int NI>
+__device__ __forceinline__ void token_walk(const GemmP& p, floatx4 (&acc)[NI][4], TokenRow<EPI, ZWRITE, Z0> (&in)[AHEAD], float unscale, int m0w, int n0w,
                                            int n_lane, int split, const int* rowmap, int m_blk, double& red0, double& red1) {
-  if constexpr (I < 8) {
+  if constexpr (I < NI) {
     if (m0w + 16 * I + 16 > p.M || n0w + 64 > p.N) token_row<EPI, ZWRITE, Z0, true>(p, acc[I], in[I % AHEAD], unscale, m0w + 16 * I, n_lane, red0, red1);
     else token_row<EPI, ZWRITE, Z0, false>(p, acc[I], in[I % AHEAD], unscale, m0w + 16 * I, n_lane, red0, red1);
     __builtin_amdgcn_sched_barrier(0);
-    if constexpr (I + AHEAD < 8) in[I % AHEAD].load(p, m0w + 16 * (I + AHEAD), n_lane, split, rowmap, m_blk);
+    if constexpr (I + AHEAD < NI) in[I % AHEAD].load(p, m0w + 16 * (I + AHEAD), n_lane, split, rowmap, m_blk);
     __builtin_amdgcn_sched_barrier(0);
-    token_walk<EPI, ZWRITE, Z0, I + 1, AHEAD>(p, acc, in, unscale, m0w, n0w, n_lane, split, rowmap, m_blk, red0, red1);
+    token_walk<EPI, ZWRITE, Z0, I + 1, AHEAD, NI>(p, acc, in, unscale, m0w, n0w, n_lane, split, rowmap, m_blk, red0, red1);
   }
 }
-template <int EPI, bool ZWRITE, bool Z0>
-__device__ __forceinline__ void token_epilogue(const GemmP& p, floatx4 (&acc)[8][4], float unscale, int m0w, int n0w, int split, const int* rowmap,
+template <int EPI, bool ZWRITE, bool Z0, int NI>
+__device__ __forceinline__ void token_epilogue(const GemmP& p, floatx4 (&acc)[NI][4], float unscale, int m0w, int n0w, int split, const int* rowmap,
                                                int m_blk, double& red0, double& red1) {
-  // as many tile rows in flight as fit beside the accumulators
-  constexpr int AHEAD = EPI == EPI_PARTIAL ? 1 : (Z0 || !ZWRITE) ? 1 : EPI == EPI_AUPD ? 4 : 2;
+  // as many tile rows in flight as fit beside the accumulators: of four all, or three with a second input
+  constexpr int AHEAD = EPI == EPI_PARTIAL ? 1 : NI == 4 && !Z0 && ZWRITE ? 4 : NI == 4 ? 3 : (Z0 || !ZWRITE) ? 1 : EPI == EPI_AUPD ? 4 : 2;
   const int n_lane = n0w + ((threadIdx.x & 8) << 1) + 4 * ((threadIdx.x & 63) >> 4);
   TokenRow<EPI, ZWRITE, Z0> in[AHEAD];
 #pragma unroll
   for (int i = 0; i < AHEAD; ++i) in[i].load(p, m0w + 16 * i, n_lane, split, rowmap, m_blk);
   __builtin_amdgcn_sched_barrier(0);
-  token_walk<EPI, ZWRITE, Z0, 0, AHEAD>(p, acc, in, unscale, m0w, n0w, n_lane, split, rowmap, m_blk, red0, red1);
+  token_walk<EPI, ZWRITE, Z0, 0, AHEAD, NI>(p, acc, in, unscale, m0w, n0w, n_lane, split, rowmap, m_blk, red0, red1);
 }
 
 }  // namespace strp

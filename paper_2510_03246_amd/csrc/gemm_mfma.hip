@@ -362,6 +362,21 @@ static bool half_tiles_pay(const GemmP& p, long long n4) {
   return n4 < 192 || n4 > 256 || !p.P.lo || !p.Q.lo;
 }
 
+// Products that 256x256 and 128x256 tiles leave to 128x128 ones and to 64x64 blocks, in 64x256 tiles (gemm_half_kernel too, four pairs of stages in
+// flight where the 128x128 kernel has one).  us, 128x128 (or 64x64, marked *) / this tile:  448 over 400 units and 9000 tokens A_S 30.4 / 21.5, Z1 27.9 / 21.3;  896,
+// 400, 9000 49 / 30, 41 / 28;  1024, 1536, 4096 57 / 49, 45 / 36, E* 97 / 72;  72, 40, 150000 (fp32, GAIN) 50 / 36, 55 / 46, E 43 / 44;  1536,
+// 2000, 2048 59 / 44, 47 / 37, E* 107 / 79, Y* 178 / 120;  440, 1440 units, 9000 Y 53 / 44.  The blocks of 64x64 read their operands again for every 64
+// rows and columns, which costs nothing while a launch is the time of one of them: the line is at 160 thousand tiles of 128x128 times steps (768, 1200,
+// 4096, 230 thousand, E 47 / 36;  600, 800, 5000, 160, 47 / 34;  896, 400, 4096, 115, A_S 23 / 26;  512, 640, 4000, 82, 20.6 / 21.2).  E and Y, whose
+// epilogues write planes, gain from long contractions only, and not where 128x128 tiles fill their two places a CU (256, 512, 30000 E 40 / 48, Y 52 / 66;  96, 150,
+// 40000 E 22.7 / 25.0).
+static bool quarter_tiles_pay(const GemmP& p) {
+  if (p.N < 256 || (p.epi != EPI_AUPD && p.epi != EPI_ZUPD && p.epi != EPI_RESID && p.epi != EPI_STORE)) return false;
+  const long long n2 = (long long)((p.M + 127) / 128) * ((p.N + 127) / 128);
+  if (n2 <= SMALL_BLOCKS) return (double)n2 * (double)p.K >= 1.6e5;
+  return p.epi == EPI_AUPD || p.epi == EPI_ZUPD || p.K >= 1000 || (n2 <= 384 && p.K >= 500);
+}
+
 void gemm_plan_tiles(GemmP& p, int want_splits, int wt) {
   p.subM = p.subN = 1;
   if (wt) {
@@ -371,8 +386,9 @@ void gemm_plan_tiles(GemmP& p, int want_splits, int wt) {
     const long long n4 = (long long)((p.M + 255) / 256) * ((p.N + 255) / 256);
     p.wt = gemm_tile256_ok(p) && n4 >= 192 ? 4 : 2;
     if (half_tiles_pay(p, n4)) p.wt = 3;
+    else if (p.wt == 2 && quarter_tiles_pay(p)) p.wt = 5;
   }
-  const int RM = p.wt == 3 ? 128 : 64 * p.wt, RN = p.wt == 3 ? 256 : 64 * p.wt, BK = p.wt == 2 ? 64 : 32;
+  const int RM = p.wt == 3 ? 128 : p.wt == 5 ? 64 : 64 * p.wt, RN = p.wt == 3 || p.wt == 5 ? 256 : 64 * p.wt, BK = p.wt == 2 ? 64 : 32;
   p.tilesM = (p.M + RM - 1) / RM;
   p.tilesN = (p.N + RN - 1) / RN;
   p.ntiles = p.triangle ? p.tilesM * (p.tilesM + 1) / 2 : p.tilesM * p.tilesN;
@@ -385,9 +401,9 @@ void gemm_plan_tiles(GemmP& p, int want_splits, int wt) {
   }
   {
     // tile group: 32 tiles, shaped to the grid
-    int gm = p.wt == 3 ? 8 : 4;
+    int gm = p.wt == 3 || p.wt == 5 ? 8 : 4;
     while (gm > 1 && gm > p.gridM) gm >>= 1;
-    int gn = (p.wt == 3 ? 64 : 32) / gm;
+    int gn = (p.wt == 3 || p.wt == 5 ? 64 : 32) / gm;
     while (gn > 1 && gn / 2 >= p.gridN) { gn >>= 1; if (gm * 2 <= p.gridM) gm <<= 1; }
     p.gm = gm;
     p.gn = gn;
@@ -431,7 +447,7 @@ static void launch_one(strp_ctx* ctx, const GemmP& p) {
 
 static strp_status check_gemm(strp_ctx* ctx, const GemmP& p) {
   if (p.M <= 0 || p.N <= 0 || p.K <= 0) return fail(ctx, STRP_EINVAL, "gemm: empty shape");
-  if (p.ntiles <= 0 || p.splits <= 0 || p.wt < 1 || p.wt > 4) return fail(ctx, STRP_EINVAL, "gemm: tiles not planned");
+  if (p.ntiles <= 0 || p.splits <= 0 || p.wt < 1 || p.wt > 5) return fail(ctx, STRP_EINVAL, "gemm: tiles not planned");
   if (!p.P.hi || !p.Q.hi) return fail(ctx, STRP_EINVAL, "gemm: null operand plane");
   if (p.P.kg * 8 < p.K || p.Q.kg * 8 < p.K || (p.P.kg & 3) || (p.Q.kg & 3))
     return fail(ctx, STRP_EINVAL, "gemm: operand planes shorter than K or a group count that is not a multiple of four");

@@ -1049,6 +1049,11 @@ static strp_status refits_beside(strp_ctx* ctx, Aside& aside, Arena& arena, cons
   GemmP p[3] = {nt_plan(operand_for(ctx, STRP_PROD_GRAM, 0, At), operand_for(ctx, STRP_PROD_GRAM, 1, At), s, s, T, 1, most),
                 nt_plan(operand_for(ctx, STRP_PROD_RHS2, 0, in.Y), operand_for(ctx, STRP_PROD_RHS2, 1, At), d, s, T, 0, most),
                 nt_plan(operand_for(ctx, STRP_PROD_RHS1, 0, Zt), operand_for(ctx, STRP_PROD_RHS1, 1, in.X), s, d, T, 0, most)};
+  // The right-hand sides have not all of the CUs: a grid that fills the chip once would take two rounds, of half as high tiles one and a third.  us of a
+  // step with 256x256 / 128x256 tiles, the same splits:  440 x 600 over 9000 tokens 484 / 479, 600 x 800 over 9000 714 / 689, 768 x 1536 over 16384
+  // 1374 / 1348, 1000 x 1013 over 30011 1811 / 1818, 768 x 1536 over 65536 3512 / 3517.
+  for (int i = 1; i < 3; ++i)
+    if (p[i].wt == 4) gemm_plan_tiles(p[i], p[i].splits, 3);
   size_t partials = sizeof(float) * (size_t)nt_plan(none, none, d, d, T, 1, most).splits * d * d;      // E E^T
   for (const GemmP& q : p) {
     const size_t b = sizeof(float) * (size_t)q.splits * q.M * q.N;

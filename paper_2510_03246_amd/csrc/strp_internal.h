@@ -124,7 +124,7 @@ struct GemmP {
   PlaneOp P, Q;        // C[m, n] = sum_k P(k, m) Q(k, n)
   int M, N;
   long long K;
-  int wt;              // 32x32 MFMA tiles per wavefront per dimension: 2 (128x128 blocks) or 4 (256x256), set by gemm_plan_tiles; 3: 128x256; 1: the
+  int wt;              // 32x32 MFMA tiles per wavefront per dimension: 2 (128x128 blocks) or 4 (256x256), set by gemm_plan_tiles; 3: 128x256, 5: 64x256; 1: the
                        // plan of 2 with each tile cut into subM x subN blocks of 64x64 (gemm_small_tiles)
   int subM, subN;
   int tilesM, tilesN, ntiles;

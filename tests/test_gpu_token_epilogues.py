@@ -2,7 +2,8 @@
 nothing: edges in rows, in tokens, within the four tokens of a lane, and a token count below one strip of 64 in the last tile.
 The same of the 64 x 64 blocks that small products are cut into: one, two and three of them, edges in both directions, an
 odd number of contraction steps.  And of the 128 x 256 tiles that two workgroups of a CU share: an odd and an even number of pairs
-of stages, one row in the last tile, fewer than 64 of its 256 tokens and more, contractions that end within a pair."""
+of stages, one row in the last tile, fewer than 64 of its 256 tokens and more, contractions that end within a pair; and of the 64 x 256
+ones, with fewer pairs than they have in flight too."""
 import pytest
 import torch
 
@@ -14,7 +15,8 @@ pytestmark = pytest.mark.gpu
 @pytest.mark.parametrize("mode", [strp.WANDA, strp.GAIN])
 @pytest.mark.parametrize("d,f,T,k", [(264, 608, 24603, 301), (256, 520, 24577, 257), (520, 768, 17001, 512), (64, 256, 512, 128),
                                        (8, 40, 83, 9), (72, 200, 131, 65), (136, 520, 1003, 129), (200, 400, 2050, 191),
-                                       (200, 696, 33003, 250), (392, 800, 21845, 385), (256, 1000, 22050, 641), (1000, 1400, 8250, 1100)])
+                                       (200, 696, 33003, 250), (392, 800, 21845, 385), (256, 1000, 22050, 641), (1000, 1400, 8250, 1100),
+                                       (72, 264, 33003, 130), (136, 400, 20003, 193), (200, 1000, 17003, 600), (520, 1704, 5003, 1100), (40, 160, 33025, 33)])
 def test_update_of_the_kept_rows(d, f, T, k, mode):
     """One iteration, then the rows it kept against the formulas in fp64 from the weights it left: A_S = relu(Z_S) + W^T M^-1 E and the z
     rule on W1 X, to a quarter of the 2e-3 that the module is held to; columns past T stay as they were.  The next iteration's
