@@ -138,47 +138,6 @@ strp_status launch_row_sums(strp_ctx* ctx, const void* A, int a_dtype, const flo
   return STRP_OK;
 }
 
-// Scoring sums of the kept rows from the strips the a- and z-update epilogues wrote: part[q][strip][m] (fp32, one value
-// per output row m and 64-column strip) -> rowsums[qdst[q] * f + idx[m]] (fp64).  One workgroup sums 64 rows: a wavefront
-// takes every 16th strip (256 contiguous bytes of each), the sixteen sums are added in order.
-__global__ __launch_bounds__(1024) void rowsum_kernel(const float* part, int slots, int M, const int32_t* idx, double* rowsums, int f, int qdst0,
-                                                      int qdst1, int32_t* status) {
-  __shared__ double sh[16][64];
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int m = blockIdx.x * 64 + lane, q = blockIdx.y;
-  const float* src = part + (long long)q * slots * M + (m < M ? m : M - 1);
-  double a[8];
-#pragma unroll
-  for (int u = 0; u < 8; ++u) a[u] = 0.0;
-  int sidx = wave;
-  for (; sidx + 7 * 16 < slots; sidx += 8 * 16) {       // eight loads in flight
-    float v[8];
-#pragma unroll
-    for (int u = 0; u < 8; ++u) v[u] = src[(long long)(sidx + 16 * u) * M];
-#pragma unroll
-    for (int u = 0; u < 8; ++u) a[u] += (double)v[u];
-  }
-  for (; sidx < slots; sidx += 16) a[0] += (double)src[(long long)sidx * M];
-  sh[wave][lane] = ((a[0] + a[1]) + (a[2] + a[3])) + ((a[4] + a[5]) + (a[6] + a[7]));
-  __syncthreads();
-  if (wave == 0 && m < M) {
-    double t = 0.0;
-#pragma unroll
-    for (int w = 0; w < 16; ++w) t += sh[w][lane];
-    rowsums[(long long)(q == 0 ? qdst0 : qdst1) * f + idx[m]] = t;
-    if (!(fabs(t) <= 1.79e308)) atomicCAS(status, 0, (int)STRP_ENONFINITE);
-  }
-}
-
-strp_status launch_rowsum_reduce(strp_ctx* ctx, const float* part, int nq, int slots, int M, const int32_t* idx, double* rowsums, int f,
-                                 int qdst0, int qdst1) {
-  if (nq <= 0 || M <= 0 || slots <= 0) return STRP_OK;
-  ProfScope ps(ctx, "rowsum_reduce", 0.0, 4.0 * (double)nq * (double)slots * (double)M);
-  hipLaunchKernelGGL(rowsum_kernel, dim3((M + 63) / 64, nq), dim3(1024), 0, ctx->stream, part, slots, M, idx, rowsums, f, qdst0, qdst1, ctx->status_dev);
-  STRP_HIP(ctx, hipGetLastError());
-  return STRP_OK;
-}
-
 // ---------------------------------------------------------------------------------------------
 // squared column norms: block = 64 columns, each wavefront 8 rows x 8 groups of 8 columns at a time (128 rows per trip of
 // the block: a weight matrix has too few 64-column blocks to fill the chip, so the depth of one block's loop is what it

@@ -186,10 +186,13 @@ enum { SUMS_G = 1, SUMS_EU = 2, SUMS_V = 4 };
 enum { SC_LAM1 = 0, SC_LAM2 = 1, SC_SUMA0 = 2, SC_TRH = 3, SC_T1 = 4, SC_T2 = 5, SC_T3 = 6, SC_T4 = 7, SC_T5 = 8,
        SC_TAU = 9, SC_ENERGY = 10, SC_W2SQ = 15, SC_W1SQ = 16, SC_COUNT = 32 };
 
-// ---- the end of a step in one launch -------------------------------------------------------------------------------
-// Every workgroup adds up 256 pruned rows: the units' sums in segment order -> the row's scoring sums, and the rows' share
-// of the objective.  The last one then sums what the step's kernels left per workgroup into the objective's terms, and
-// writes the scalars and the status word to the report's host memory (two copies and their launches otherwise).
+// The end of an iteration, in one launch: the pruned rows' sums from the units of their pass, the kept rows' scoring sums from the strips that the a- and
+// z-update epilogues wrote, the objective's terms from the workgroups' sums, and the report's read-back.  What bounds it is the round trips to memory
+// that follow each other, so everything that is independent is another workgroup or is asked for at once, and the last workgroup to end puts it together.
+// A launch for the strips' sums of either update and one workgroup that formed the objective's seven sums one after the other before: us of
+// a step's end, 768 x 1536 units over 65536 tokens 30 -> 12, 1000 x 1013 over 30011 (GAIN) 28 -> 12, 64 x 128 over 512 8.7 -> 9.5 (a launch less).
+constexpr int FINISH_THREADS = 1024, FINISH_ROWS = FINISH_THREADS / 6, FINISH_SUMS = 7;
+static inline int finish_row_blocks(int nrows) { return (nrows + 2 * FINISH_ROWS - 1) / (2 * FINISH_ROWS); }      // two rows one after the other
 struct FinishP {
   double* sc;
   // pruned rows of a fused a/z pass (nrows = 0: none)
@@ -197,7 +200,13 @@ struct FinishP {
   const double* partial;
   int nrows, segs, f, z0;
   double* rowsums;
-  double* blk;                               // [gridDim.x][2]
+  // the kept rows' strips: strips[q][slots][M], fp32, a value per row and 64 tokens, are sum q of row idx[m] (null: not collected)
+  const float* strips[3];
+  int slots, M, n_strips;
+  const int32_t* idx;
+  double* blk;                               // [row_blocks][2]
+  double* sums;                              // [FINISH_SUMS]
+  int row_blocks;
   unsigned int* ticket;
   // per-workgroup sums: terms 2 and 3 (kept rows, pruned rows when their pass was a kernel of its own), term 1, weights
   const double* red_z; int nz;               // pairs
@@ -208,92 +217,146 @@ struct FinishP {
   double c1, c2, c3;
   int do_z, do_1, do_w;
   double* host;                              // pinned: [SC_COUNT] scalars, then the status word; null: no report
-  const int32_t* status;
+  int32_t* status;
 };
-__device__ __forceinline__ double finish_block_sum(double a, double* sh) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) a += __shfl_down(a, o, 64);
-  __syncthreads();
-  if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = a;
-  __syncthreads();
-  return sh[0] + sh[1] + sh[2] + sh[3];
-}
-__global__ __launch_bounds__(256) void step_finish_kernel(const FinishP p) {
-  __shared__ double sh[4];
-  __shared__ unsigned int flag;
+// sums of v over the workgroup, in out (LDS) for everybody
+template <int K>
+__device__ __forceinline__ void finish_sums(double (&v)[K], double (&sh)[FINISH_SUMS][16], double* out) {
   const int tid = threadIdx.x;
-  double r0 = 0.0, r1 = 0.0;
-  if (p.nrows > 0) {
-    const int q = blockIdx.x * 256 + tid;
-    if (q < p.nrows) {
-      const int j = p.rows[q];
-      double t[6] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
-      const double* src = p.partial + (unsigned long long)q * p.segs * 6;
-      for (int g = 0; g < p.segs; ++g)
 #pragma unroll
-        for (int e = 0; e < 6; ++e) t[e] += src[g * 6 + e];
-      if (j >= 0) {
-        r0 = t[0];
-        r1 = t[1];
-        p.rowsums[j] = t[2];
-        if (p.z0) {
-          p.rowsums[(long long)p.f + j] = t[3];
-          p.rowsums[2 * (long long)p.f + j] = t[4];
-          p.rowsums[3 * (long long)p.f + j] = t[5];
-        }
-      }
-    }
-    r0 = finish_block_sum(r0, sh);
-    r1 = finish_block_sum(r1, sh);
-    if (gridDim.x > 1) {
-      if (tid == 0) {
-        agent_put(&p.blk[2 * blockIdx.x], r0);
-        agent_put(&p.blk[2 * blockIdx.x + 1], r1);
-      }
-      if (!last_block(p.ticket, &flag)) return;
-      if (tid == 0) *p.ticket = 0u;
-      r0 = r1 = 0.0;
-      for (int b = tid; b < (int)gridDim.x; b += 256) {
-        r0 += agent_get(&p.blk[2 * b]);
-        r1 += agent_get(&p.blk[2 * b + 1]);
-      }
-      r0 = finish_block_sum(r0, sh);
-      r1 = finish_block_sum(r1, sh);
-    }
-  }
-  auto sum = [&](const double* v, int n, int stride, int off) {
+  for (int o = 32; o > 0; o >>= 1)
+#pragma unroll
+    for (int q = 0; q < K; ++q) v[q] += __shfl_down(v[q], o, 64);
+  if ((tid & 63) == 0)
+#pragma unroll
+    for (int q = 0; q < K; ++q) sh[q][tid >> 6] = v[q];
+  __syncthreads();
+  if (tid < K) {
     double a = 0.0;
+#pragma unroll
+    for (int w = 0; w < 16; ++w) a += sh[tid][w];
+    out[tid] = a;
+  }
+  __syncthreads();
+}
+// a pruned row has six lanes, a sum each, added over its segments in their order
+__device__ __forceinline__ void finish_rows(const FinishP& p, int b, double (&r)[2]) {
+  const int e = threadIdx.x % 6, in = threadIdx.x / 6, q0 = 2 * b * FINISH_ROWS + in;
+  r[0] = r[1] = 0.0;
+  if (in >= FINISH_ROWS) return;
+  double t[2] = {0.0, 0.0};
+  int j[2];
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+    const int q = q0 + h * FINISH_ROWS;
+    j[h] = q < p.nrows ? p.rows[q] : -1;
+    if (q >= p.nrows) continue;
+    const double* src = p.partial + (unsigned long long)q * p.segs * 6 + e;
 #pragma unroll 8
-    for (int i = tid; i < n; i += 256) a += v[(long long)i * stride + off];
-    return finish_block_sum(a, sh);
-  };
-  if (p.do_z) {
-    const double z0 = sum(p.red_z, p.nz, 2, 0), z1 = sum(p.red_z, p.nz, 2, 1);
-    if (p.np) {
-      r0 = sum(p.red_p, p.np, 2, 0);
-      r1 = sum(p.red_p, p.np, 2, 1);
+    for (int g = 0; g < p.segs; ++g) t[h] += src[6 * g];
+  }
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+    if (j[h] < 0) continue;
+    r[0] += e == 0 ? t[h] : 0.0;
+    r[1] += e == 1 ? t[h] : 0.0;
+    if (e == 2 || (e > 2 && p.z0)) p.rowsums[(long long)(e - 2) * p.f + j[h]] = t[h];
+  }
+}
+// One workgroup sums 64 kept rows: a wavefront takes every 16th strip (256 contiguous bytes of each), the sixteen sums are added in order.
+__device__ __forceinline__ void finish_strips(const FinishP& p, int b, double (&sh)[16][64]) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, per = (p.M + 63) / 64, q = b / per;
+  const int m = (b - q * per) * 64 + lane;
+  const long long M = p.M;
+  const float* strips = q == 0 ? p.strips[0] : q == 1 ? p.strips[1] : p.strips[2];
+  const int sum = q == 0 ? 0 : q == 1 ? 1 : 2;
+  const float* src = strips + (m < p.M ? m : p.M - 1);
+  double a[8];
+#pragma unroll
+  for (int u = 0; u < 8; ++u) a[u] = 0.0;
+  int sidx = wave;
+  for (; sidx + 7 * 16 < p.slots; sidx += 8 * 16) {       // eight loads in flight
+    float v[8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) v[u] = src[(sidx + 16 * u) * M];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) a[u] += (double)v[u];
+  }
+  for (; sidx < p.slots; sidx += 16) a[0] += (double)src[sidx * M];
+  sh[wave][lane] = ((a[0] + a[1]) + (a[2] + a[3])) + ((a[4] + a[5]) + (a[6] + a[7]));
+  __syncthreads();
+  if (wave == 0 && m < p.M) {
+    double t = 0.0;
+#pragma unroll
+    for (int w = 0; w < 16; ++w) t += sh[w][lane];
+    p.rowsums[(long long)sum * p.f + p.idx[m]] = t;
+    if (!(fabs(t) <= 1.79e308)) atomicCAS(p.status, 0, (int)STRP_ENONFINITE);
+  }
+}
+__global__ __launch_bounds__(FINISH_THREADS) void step_finish_kernel(const FinishP p) {
+  __shared__ double strips[16][64], sh[FINISH_SUMS][16], tot[FINISH_SUMS], rtot[2];
+  __shared__ unsigned int flag;
+  const int tid = threadIdx.x, b = blockIdx.x;
+  const double scalar = tid < SC_COUNT ? p.sc[tid] : 0.0;
+  double r[2] = {0.0, 0.0};
+  if (b < p.row_blocks) {
+    finish_rows(p, b, r);
+    finish_sums<2>(r, sh, rtot);
+    if (tid < 2) agent_put(&p.blk[2 * b + tid], rtot[tid]);
+  } else if (b == p.row_blocks) {
+    double v[FINISH_SUMS];
+#pragma unroll
+    for (int q = 0; q < FINISH_SUMS; ++q) v[q] = 0.0;
+    const auto pairs = [&](const double* x, int n, double& v0, double& v1) {
+#pragma unroll 4
+      for (int i = tid; i < n; i += FINISH_THREADS) {
+        const double2 d = *(const double2*)(x + 2 * (long long)i);
+        v0 += d.x;
+        v1 += d.y;
+      }
+    };
+    const auto every = [&](const double* x, int n, int stride, double& v0) {
+#pragma unroll 4
+      for (int i = tid; i < n; i += FINISH_THREADS) v0 += x[(long long)i * stride];
+    };
+    if (p.do_z) pairs(p.red_z, p.nz, v[0], v[1]);
+    if (p.do_z && p.np) pairs(p.red_p, p.np, v[2], v[3]);
+    if (p.do_1) every(p.red_1, p.n1, p.stride1, v[4]);
+    if (p.do_w) {
+      every(p.w2, p.nw2, 1, v[5]);
+      every(p.w1, p.nw1, 1, v[6]);
     }
-    if (tid == 0) {
-      p.sc[SC_T2] = p.c2 * (z0 + r0);
-      p.sc[SC_T3] = p.c3 * (z1 + r1);
+    finish_sums<FINISH_SUMS>(v, sh, tot);
+    if (gridDim.x > 1 && tid < FINISH_SUMS) agent_put(&p.sums[tid], tot[tid]);
+  } else {
+    finish_strips(p, b - p.row_blocks - 1, strips);
+  }
+  if (gridDim.x > 1) {
+    if (!last_block(p.ticket, &flag)) return;
+    if (tid == 0) *p.ticket = 0u;
+    if (tid < FINISH_SUMS) tot[tid] = agent_get(&p.sums[tid]);
+    r[0] = r[1] = 0.0;
+    for (int i = tid; i < p.row_blocks; i += FINISH_THREADS) {
+      r[0] += agent_get(&p.blk[2 * i]);
+      r[1] += agent_get(&p.blk[2 * i + 1]);
     }
+    finish_sums<2>(r, sh, rtot);
   }
-  if (p.do_1) {
-    const double t = sum(p.red_1, p.n1, p.stride1, 0);
-    if (tid == 0) p.sc[SC_T1] = p.c1 * t;
+  // one lane a scalar: those that are new go to the state, all of them to the report
+  if (tid < SC_COUNT) {
+    const double r0 = gridDim.x > 1 ? rtot[0] : 0.0, r1 = gridDim.x > 1 ? rtot[1] : 0.0;
+    double v = scalar;
+    bool fresh = true;
+    if (p.do_z && tid == SC_T2) v = p.c2 * (tot[0] + (p.np ? tot[2] : r0));
+    else if (p.do_z && tid == SC_T3) v = p.c3 * (tot[1] + (p.np ? tot[3] : r1));
+    else if (p.do_1 && tid == SC_T1) v = p.c1 * tot[4];
+    else if (p.do_w && tid == SC_W2SQ) v = tot[5];
+    else if (p.do_w && tid == SC_W1SQ) v = tot[6];
+    else fresh = false;
+    if (fresh) p.sc[tid] = v;
+    if (p.host) __hip_atomic_store(&p.host[tid], v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
   }
-  if (p.do_w) {
-    const double a = sum(p.w2, p.nw2, 1, 0), b = sum(p.w1, p.nw1, 1, 0);
-    if (tid == 0) {
-      p.sc[SC_W2SQ] = a;
-      p.sc[SC_W1SQ] = b;
-    }
-  }
-  if (p.host) {
-    __syncthreads();
-    if (tid < SC_COUNT) __hip_atomic_store(&p.host[tid], p.sc[tid], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
-    if (tid == SC_COUNT) __hip_atomic_store((int32_t*)(p.host + SC_COUNT), agent_get(p.status), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
-  }
+  if (p.host && tid == SC_COUNT) __hip_atomic_store((int32_t*)(p.host + SC_COUNT), agent_get(p.status), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
 static strp_status check_desc(strp_ctx* ctx, const strp_module_desc* d) {
@@ -1506,7 +1569,7 @@ strp_status strp_admm_step(strp_ctx* ctx, const strp_module_desc* desc, strp_mod
     constexpr long long SEG = 8192;
     const int segs = (int)((T + SEG - 1) / SEG);
     STRP_TAKE(ctx, arena, partial, double, (size_t)(f - s) * segs * 6);
-    STRP_TAKE(ctx, arena, blk, double, 2 * (size_t)((f - s + 255) / 256));
+    STRP_TAKE(ctx, arena, blk, double, 2 * (size_t)finish_row_blocks(f - s));
     finish_blk = blk;
     if (!prow_done) hipLaunchKernelGGL(pruned_list_kernel, dim3(1), dim3(1024), 0, ctx->stream, st->mask, f, prow);
     pjob.units = (unsigned int)(f - s) * (unsigned int)segs;
@@ -1781,7 +1844,6 @@ strp_status strp_admm_step(strp_ctx* ctx, const strp_module_desc* desc, strp_mod
       p.rs_out = rsA; p.rs_z0 = (rsA && !wanda) ? st->Z0 : nullptr; p.rs_slots = rs_slots;
       gemm_plan_tiles(p, 1);
       STRP_TRY(launch_gemm(ctx, p));
-      if (rsA) STRP_TRY(launch_rowsum_reduce(ctx, rsA, wanda ? 1 : 2, rs_slots, s, st->idx, cv.rowsums, f, 0, 1));
     }
     if (!fuse_pruned) {
       ProfScope ps(ctx, "pruned_rows_a", 0.0, 8.0 * (double)(f - s) * (double)T);
@@ -1805,11 +1867,10 @@ strp_status strp_admm_step(strp_ctx* ctx, const strp_module_desc* desc, strp_mod
     p.red = red;
     STRP_TRY(launch_gemm(ctx, p));
     fin.do_z = 1; fin.red_z = red; fin.nz = nb; fin.c2 = params->beta / (double)T; fin.c3 = params->alpha / (double)T;
-    if (p.rs_out) STRP_TRY(launch_rowsum_reduce(ctx, rsZ, 1, rs_slots, s, st->idx, cv.rowsums, f, 2, 2));
     if (fuse_pruned) {
       if (pjob.units) {      // the rows' sums are added at the end
-        fin.rows = prow; fin.partial = pjob.partial; fin.nrows = pjob.nrows; fin.segs = pjob.segs; fin.f = f; fin.z0 = pjob.Z0 != nullptr;
-        fin.rowsums = cv.rowsums; fin.blk = finish_blk; fin.ticket = ticket;
+        fin.rows = prow; fin.partial = pjob.partial; fin.nrows = pjob.nrows; fin.segs = pjob.segs; fin.z0 = pjob.Z0 != nullptr;
+        fin.blk = finish_blk;
       }
       // every row's sums are then in place: the kept rows' from the two epilogues, the pruned rows' from this pass
       // (which also rewrites their sum Z0^2; the kept rows' is only there if it was streamed before)
@@ -1845,11 +1906,23 @@ strp_status strp_admm_step(strp_ctx* ctx, const strp_module_desc* desc, strp_mod
   }
   if (report_host) {
     fin.host = (double*)ctx->pinned;
-    fin.status = ctx->status_dev;
   }
   if (fin.nrows || fin.do_z || fin.do_1 || fin.do_w || fin.host) {
+    if (rsA) {
+      fin.strips[0] = rsA;
+      fin.strips[1] = rsA + (size_t)rs_slots * s;
+      fin.strips[2] = rsZ;
+      fin.n_strips = wanda ? 1 : 3;
+    }
+    fin.slots = rs_slots; fin.M = s; fin.idx = st->idx; fin.rowsums = cv.rowsums; fin.f = f;
+    fin.row_blocks = finish_row_blocks(fin.nrows);
+    fin.ticket = ticket;
+    fin.sums = (double*)(wmax + 40);
+    fin.status = ctx->status_dev;
     ProfScope ps(ctx, fin.nrows ? "pruned_rows_drain" : "step_finish", 0.0, 0.0);
-    hipLaunchKernelGGL(step_finish_kernel, dim3(fin.nrows ? (fin.nrows + 255) / 256 : 1), dim3(256), 0, ctx->stream, fin);
+    const int strips = fin.n_strips ? prof_begin(ctx, "rowsum_reduce", 0.0, 4.0 * (double)fin.n_strips * (double)rs_slots * (double)s) : -1;
+    hipLaunchKernelGGL(step_finish_kernel, dim3(fin.row_blocks + 1 + fin.n_strips * ((s + 63) / 64)), dim3(FINISH_THREADS), 0, ctx->stream, fin);
+    prof_end(ctx, strips);
   }
   STRP_HIP(ctx, hipGetLastError());
   st->iter += 1;

@@ -279,9 +279,6 @@ strp_status f32_to_f64_ridge(strp_ctx* ctx, const float* Af, long long ldf, doub
 // ---- reductions, scores, allocation, select (score_select.hip) ------------------------------
 strp_status launch_row_sums(strp_ctx* ctx, const void* A, int a_dtype, const float* Z, const float* Z0,
                             long long ld, long long T, int rows, int mode, double* sums /*[4][rows]*/);
-// part[nq][slots][M] fp32 strip sums written by the AUPD / ZUPD epilogues -> rowsums[qdst * f + idx[m]] (fp64).
-strp_status launch_rowsum_reduce(strp_ctx* ctx, const float* part, int nq, int slots, int M, const int32_t* idx, double* rowsums, int f,
-                                 int qdst0, int qdst1);
 strp_status launch_colnorm2(strp_ctx* ctx, const void* W, int w_dtype, int rows, int cols, long long ldw,
                             double* n2);
 strp_status launch_unit_scores(strp_ctx* ctx, const double* sums, const double* n2, int n_channels, int group,
