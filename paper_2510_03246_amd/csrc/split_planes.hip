@@ -1,6 +1,7 @@
 // Split kernels: fp32 / bf16 / fp64 sources -> fp16 operand planes in the panel-major chunk layout
 //   offset(k, r) = (((r / 128) * KG + k / 8) * 128 + r % 128) * 8 + k % 8
 // (see gemm_mfma.hip).  All padding (rows up to a full panel, k up to a full group) is written as zero.
+#include "splitk_reduce.h"
 #include "strp_internal.h"
 
 namespace strp {
@@ -303,7 +304,7 @@ __device__ __forceinline__ void split_chunk(const SplitJob& b, long long e, unsi
   *(uint4*)(b.hi + e * 8) = make_uint4(sp_pack2(h[0], h[1]), sp_pack2(h[2], h[3]), sp_pack2(h[4], h[5]), sp_pack2(h[6], h[7]));
   if (b.lo) *(uint4*)(b.lo + e * 8) = make_uint4(sp_pack2(l[0], l[1]), sp_pack2(l[2], l[3]), sp_pack2(l[4], l[5]), sp_pack2(l[6], l[7]));
 }
-__global__ __launch_bounds__(256) void split_small_kernel(const SplitJobs jobs) {
+__device__ __forceinline__ void split_small_block(const SplitJobs& jobs) {
   // chunk counts are multiples of 128: a wavefront's chunks are of one job and one k-group
   const unsigned int half = 2 * blockIdx.x + __builtin_amdgcn_readfirstlane(threadIdx.x >> 7);
   const long long e0 = 128ll * half;
@@ -316,14 +317,19 @@ __global__ __launch_bounds__(256) void split_small_kernel(const SplitJobs jobs) 
   else if (b.kind == SRC_F32) split_chunk<float>(b, c, pg);
   else split_chunk<unsigned short>(b, c, pg);
 }
+__global__ __launch_bounds__(256) void split_small_kernel(const SplitJobs jobs) { split_small_block(jobs); }
 
-strp_status split_small(strp_ctx* ctx, const SplitJob* jobs, int n) {
+static SplitJobs split_jobs(const SplitJob* jobs, int n) {
   SplitJobs s;
   memset(&s, 0, sizeof(s));
   for (int i = 0; i < 3; ++i) {
     if (i < n) s.j[i] = jobs[i];
     s.chunk0[i + 1] = s.chunk0[i] + (i < n ? (long long)plane_elems(jobs[i].rows, jobs[i].cols) / 8 : 0);
   }
+  return s;
+}
+strp_status split_small(strp_ctx* ctx, const SplitJob* jobs, int n) {
+  const SplitJobs s = split_jobs(jobs, n);
   hipLaunchKernelGGL(split_small_kernel, dim3((unsigned)((s.chunk0[3] + 255) / 256)), dim3(256), 0, ctx->stream, s);
   STRP_HIP(ctx, hipGetLastError());
   return STRP_OK;
@@ -385,13 +391,11 @@ strp_status abs_max(strp_ctx* ctx, const MaxJob* jobs, int n) {
 // (16 k-groups of one channel panel) are contiguous 32 KB runs; the 2-byte transposition happens in LDS.
 // Tokens >= T are written as zero (they are contraction padding on the output side).
 // ---------------------------------------------------------------------------------------------
-__global__ __launch_bounds__(256) void plane_c_to_t_kernel(const unsigned short* src, unsigned short* dst, int C, long long T,
-                                                           long long kg_src, long long kg_dst) {
+__device__ __forceinline__ void plane_c_to_t_block(const unsigned short* src, unsigned short* dst, long long T, long long kg_src, long long kg_dst, long long pt,
+                                                   int pc) {
   constexpr int GS = 1024 + 8;                    // elements per source k-group in LDS (+16 B against bank conflicts)
   __shared__ __attribute__((aligned(16))) unsigned short sm[16 * GS];
   const int tid = threadIdx.x;
-  const long long pt = blockIdx.x;                // token panel
-  const int pc = blockIdx.y;                      // channel panel
   // load: source k-groups 16 pc .. 16 pc + 15 (those below kg_src) of token panel pt
   for (int q = tid; q < 2048; q += 256) {
     const int g = q >> 7, piece = q & 127;        // 128 16-byte pieces (one token each) per k-group
@@ -420,13 +424,45 @@ __global__ __launch_bounds__(256) void plane_c_to_t_kernel(const unsigned short*
     v.w = e[6] | ((unsigned)e[7] << 16);
     *(uint4*)(dst + (((long long)pc * kg_dst + tgg) * 128 + cl) * 8) = v;
   }
-  (void)C;
+}
+__global__ __launch_bounds__(256) void plane_c_to_t_kernel(const unsigned short* src, unsigned short* dst, long long T, long long kg_src, long long kg_dst) {
+  plane_c_to_t_block(src, dst, T, kg_src, kg_dst, blockIdx.x, blockIdx.y);        // token panel, channel panel
 }
 
 strp_status plane_c_to_t(strp_ctx* ctx, const unsigned short* src, unsigned short* dst, int C, long long T) {
   ProfScope ps(ctx, "plane_c_to_t", 0.0, 4.0 * (double)C * (double)T);
   dim3 grid((unsigned)((T + 127) / 128), (unsigned)((C + 127) / 128));
-  hipLaunchKernelGGL(plane_c_to_t_kernel, grid, dim3(256), 0, ctx->stream, src, dst, C, T, plane_kg(C), plane_kg(T));
+  hipLaunchKernelGGL(plane_c_to_t_kernel, grid, dim3(256), 0, ctx->stream, src, dst, T, plane_kg(C), plane_kg(T));
+  STRP_HIP(ctx, hipGetLastError());
+  return STRP_OK;
+}
+
+// Planes of a small matrix with, in the same launch, what a small module's step has to do for its residual at that point: turn a plane of it, or
+// sum a product's partials.  All of them are the time of a launch and of one workgroup (2.8 to 4.7 us each by itself).
+__global__ __launch_bounds__(256) void split_turn_kernel(const SplitJobs jobs, int split_end, const unsigned short* src, unsigned short* dst, long long T, long long kg_src,
+                                                         long long kg_dst, int panels) {
+  const int b = (int)blockIdx.x - split_end, pc = b / panels;
+  if (b < 0) split_small_block(jobs);
+  else plane_c_to_t_block(src, dst, T, kg_src, kg_dst, b - pc * panels, pc);
+}
+strp_status split_small_turn(strp_ctx* ctx, const SplitJob& job, const unsigned short* src, unsigned short* dst, int C, long long T) {
+  const SplitJobs s = split_jobs(&job, 1);
+  const int split_end = (int)((s.chunk0[3] + 255) / 256), panels = (int)((T + 127) / 128);
+  ProfScope ps(ctx, "plane_c_to_t", 0.0, 4.0 * (double)C * (double)T);
+  hipLaunchKernelGGL(split_turn_kernel, dim3(split_end + panels * ((C + 127) / 128)), dim3(256), 0, ctx->stream, s, split_end, src, dst, T, plane_kg(C), plane_kg(T), panels);
+  STRP_HIP(ctx, hipGetLastError());
+  return STRP_OK;
+}
+__global__ __launch_bounds__(256) void split_reduce_kernel(const SplitJobs jobs, int split_end, const ReduceP r) {
+  const int b = (int)blockIdx.x - split_end, nx = (r.N + REDUCE_TILE_N - 1) / REDUCE_TILE_N;
+  if (b < 0) split_small_block(jobs);
+  else splitk_reduce_block(r, b % nx, b / nx, nx);
+}
+strp_status split_small_reduce(strp_ctx* ctx, const SplitJob& job, const ReduceP& r) {
+  const SplitJobs s = split_jobs(&job, 1);
+  const int split_end = (int)((s.chunk0[3] + 255) / 256);
+  ProfScope ps(ctx, "splitk_reduce", 0.0, 2.0 * (double)r.splits * r.M * r.N);
+  hipLaunchKernelGGL(split_reduce_kernel, dim3(split_end + reduce_blocks(r.M, r.N)), dim3(256), 0, ctx->stream, s, split_end, r);
   STRP_HIP(ctx, hipGetLastError());
   return STRP_OK;
 }

@@ -1673,13 +1673,37 @@ strp_status strp_admm_step(strp_ctx* ctx, const strp_module_desc* desc, strp_mod
   // and |Y - W A_S|_F^2 = (beta/alpha)^2 <M^-2, E E^T>: a d x d Gram of E over the tokens (half the work of the product
   // W A_S) and two d x d matrices.  One fp16 plane of E is ample for a sum reported to 1e-3.
   const bool term1_identity = (stages & STRP_STAGE_AUPD) && (stages & STRP_STAGE_OBJ);
-  bool residual_aside = false;
+  bool residual_aside = false, residual_shared = false;
   float* M2f = nullptr;
   double* red_t1 = nullptr;
+  unsigned short *ekh = nullptr, *ekl = nullptr, *eth = nullptr;      // planes of E by channels, one of them by tokens
+  GemmP eet;                                                          // E E^T
+  auto take_residual = [&](Arena& from) {
+    ekh = (unsigned short*)from.take(2 * plane_elems(T, d));
+    ekl = npa == 2 ? (unsigned short*)from.take(2 * plane_elems(T, d)) : nullptr;
+    return ekh && (ekl || npa < 2);
+  };
+  auto residual = [&](const PlaneOp& Zk) {      // E = Y - W relu(Z_S), kept only as K8 planes
+    GemmP p;
+    memset(&p, 0, sizeof(p));
+    p.P = operand_for(ctx, STRP_PROD_RESID, 0, W2Sp);
+    p.Q = operand_for(ctx, STRP_PROD_RESID, 1, Zk);
+    p.M = d; p.N = (int)T; p.K = s;
+    p.epi = EPI_RESID; p.Yin = st->Y; p.ldy = lda;
+    p.k8_hi = ekh; p.k8_lo = ekl; p.k8_kg = plane_kg(d);
+    gemm_plan_tiles(p, 1);
+    return p;
+  };
   if (term1_identity) {
     STRP_TAKE(ctx, arena, rt1, double, (size_t)reduce_blocks(d, d));
     red_t1 = rt1;
   }
+  auto term1 = [&](const GemmP& p) {            // <M^-2, E E^T>
+    ReduceP r = reduce_to(nullptr, 0);
+    r.dot = M2f; r.red = red_t1;
+    reduce_of(p, &r);
+    return r;
+  };
   if (stages & STRP_STAGE_AUPD) {
     STRP_TAKE(ctx, arena, Md, double, (size_t)d * d);
     STRP_TAKE(ctx, arena, Linv, double, (size_t)d * d);
@@ -1693,11 +1717,32 @@ strp_status strp_admm_step(strp_ctx* ctx, const strp_module_desc* desc, strp_mod
     Arena a2(cblock, cbytes);
     ReduceP r = reduce_to_system(Md, d);
     r.ridge = params->beta / params->alpha;
-    STRP_TRY(nt_product(ctx, a2, W2Sp, W2Sp, d, d, sp, 1, r));
-    // With both refits done E is next, which needs nothing of this chain: it runs on the second stream, from where M is factored on
-    // (us a step, 440 x 600 over 9000 tokens 546 -> 496, 200 x 300 over 4000 302 -> 288, 96 x 200 over 4000 247 -> 238; with one tile of M the
-    // two waits cost what there is to hide: 64 x 128 over 512 172.7 / 173.7).
-    residual_aside = refits_done && (beside || d > NB) && aside.ready();
+    Arena a3 = a2;
+    GemmP first[2] = {nt_plan(W2Sp, W2Sp, d, d, sp, 1, a3.room() / sizeof(float))};
+    STRP_TAKE(ctx, a3, part, float, (size_t)first[0].splits * d * d);
+    first[0].out = part;
+    // A small module's chain is launches of a few workgroups, so E, its turned plane, E E^T and the sum with M^-2 share them: E that of W W^T, the
+    // plane that of M^-1's planes, E E^T that of B, the sum that of B's planes: 19 launches in an iteration of a 64 x 256 module over 512 tokens where
+    // there were 23, the same bits.  us a step of d x kept units over the tokens, in launches of their own (at d <= 64) or on the second stream /
+    // shared:  64 x 128, 512 173.8 / 157.0;  64 x 128, 30000 260 / 240;  48 x 90, 3000 177 / 159;  72 x 128, 512 182 / 173;  128 x 256, 2048 223 / 213;
+    // 200 x 400, 4000 310 / 300;  256 x 512, 2048 307 / 298;  512 x 1000, 1024 517 / 514;  768 x 600, 768 473 / 469.
+    if (term1_identity && refits_done && !beside) {
+      Arena a4 = arena;
+      eth = take_residual(a4) ? (unsigned short*)a4.take(2 * plane_elems(d, T)) : nullptr;
+      const PlaneOp Et{eth, nullptr, plane_kg(T), (int)((d + 127) / 128), nullptr};
+      eet = nt_plan(Et, Et, d, d, T, 1, ~size_t(0) >> 8);
+      eet.out = eth ? (float*)a4.take(sizeof(float) * (size_t)eet.splits * d * d) : nullptr;
+      first[1] = residual(Zk8pre);
+      residual_shared = eet.out && a4.room() >= bytes_after_refits(d, s, T, npa) && gemm_is_small(first[0]) && gemm_is_small(first[1]) && gemm_is_small(eet);
+      if (residual_shared) arena = a4;
+    }
+    STRP_TRY(residual_shared ? launch_gemm_group(ctx, first, 2) : launch_gemm(ctx, first[0]));
+    reduce_of(first[0], &r);
+    STRP_TRY(launch_splitk_reduce(ctx, r));
+    // With both refits done E is next, which needs nothing of this chain.  Where it could not share the chain's launches it runs on the second
+    // stream, from where M is factored on (us a step, 440 x 600 over 9000 tokens 546 -> 496; with one tile of M the two waits cost what there is
+    // to hide: 64 x 128 over 512 172.7 / 173.7).
+    residual_aside = refits_done && !residual_shared && (beside || d > NB) && aside.ready();
     if (residual_aside) STRP_TRY(aside.follow());
     {
       const FlowWorkers few(ctx, residual_aside ? flow_workers_beside(d) : 0);
@@ -1709,7 +1754,7 @@ strp_status strp_admm_step(strp_ctx* ctx, const strp_module_desc* desc, strp_mod
     SplitJob job;
     PlaneOp Mi;
     STRP_TRY(weight_planes(ctx, a2, Md, SRC_F64, d, d, d, 2, npa, wmax + MAX_MI, &Mi, &job));
-    STRP_TRY(split_small(ctx, &job, 1));
+    STRP_TRY(residual_shared ? split_small_turn(ctx, job, ekh, eth, d, T) : split_small(ctx, &job, 1));
     GemmP p;
     memset(&p, 0, sizeof(p));
     p.P = W2Tp; p.Q = Mi;
@@ -1723,13 +1768,13 @@ strp_status strp_admm_step(strp_ctx* ctx, const strp_module_desc* desc, strp_mod
       q.M = d; q.N = d; q.K = d;
       q.epi = EPI_STORE; q.out = M2f; q.ldo = d;
       gemm_plan_tiles(q, 1);
-      GemmP both[2] = {p, q};
-      STRP_TRY(launch_gemm_group(ctx, both, 2));
+      GemmP group[3] = {p, q, eet};
+      STRP_TRY(launch_gemm_group(ctx, group, residual_shared ? 3 : 2));
     } else {
       STRP_TRY(launch_gemm(ctx, p));
     }
     STRP_TRY(weight_planes(ctx, arena, Bf, SRC_F32, d, s, d, 0, npa, wmax + MAX_B, &Bp, &job));
-    STRP_TRY(split_small(ctx, &job, 1));
+    STRP_TRY(residual_shared ? split_small_reduce(ctx, job, term1(eet)) : split_small(ctx, &job, 1));
   }
   if (z_planes_once && !refits_done) {
     STRP_TAKE(ctx, arena, zch, unsigned short, plane_elems(T, s));
@@ -1797,39 +1842,26 @@ strp_status strp_admm_step(strp_ctx* ctx, const strp_module_desc* desc, strp_mod
     if (!z_planes_once) {
       STRP_TRY(make_c_planes(ctx, a2, st->Z, STRP_F32, lda, st->idx, s, T, 1, npa, &Zk8));
     }
-    STRP_TAKE(ctx, a2, ekh, unsigned short, plane_elems(T, d));
-    unsigned short* ekl = nullptr;
-    if (npa == 2) {
-      STRP_TAKE(ctx, a2, ekl2, unsigned short, plane_elems(T, d));
-      ekl = ekl2;
-    }
-    if (residual_aside) aside.enter();
-    {  // E = Y - W relu(Z_S), kept only as K8 planes
-      GemmP p;
-      memset(&p, 0, sizeof(p));
-      p.P = operand_for(ctx, STRP_PROD_RESID, 0, W2Sp);
-      p.Q = operand_for(ctx, STRP_PROD_RESID, 1, Zk8);
-      p.M = d; p.N = (int)T; p.K = s;
-      p.epi = EPI_RESID; p.Yin = st->Y; p.ldy = lda;
-      p.k8_hi = ekh; p.k8_lo = ekl; p.k8_kg = plane_kg(d);
-      gemm_plan_tiles(p, 1);
+    if (!residual_shared) {
+      if (!take_residual(a2)) return fail(ctx, STRP_ENOMEM, "workspace too small for the residual");
+      if (residual_aside) aside.enter();
+      GemmP p = residual(Zk8);
       STRP_TRY(launch_gemm(ctx, p));
     }
     if (term1_identity) {   // (alpha/T) |Y - W A_S|^2 = (alpha/T) (beta/alpha)^2 <M^-2, E E^T>
-      Arena a3 = a2;
-      STRP_TAKE(ctx, a3, eth, unsigned short, plane_elems(d, T));
-      STRP_TRY(plane_c_to_t(ctx, ekh, eth, d, T));
-      const PlaneOp Et{eth, nullptr, plane_kg(T), (int)((d + 127) / 128), nullptr};
-      if (beside) a3 = side_part;
-      GemmP p = nt_plan(Et, Et, d, d, T, 1, a3.room() / sizeof(float));
-      STRP_TAKE(ctx, a3, part, float, (size_t)p.splits * d * d);
-      p.out = part;
-      STRP_TRY(launch_gemm(ctx, p));
-      STRP_TRY(aside.join());        // the sum below is with M^-2
-      ReduceP r = reduce_to(nullptr, 0);
-      r.dot = M2f; r.red = red_t1;
-      reduce_of(p, &r);
-      STRP_TRY(launch_splitk_reduce(ctx, r));
+      if (!residual_shared) {
+        Arena a3 = a2;
+        STRP_TAKE(ctx, a3, et, unsigned short, plane_elems(d, T));
+        STRP_TRY(plane_c_to_t(ctx, ekh, et, d, T));
+        const PlaneOp Et{et, nullptr, plane_kg(T), (int)((d + 127) / 128), nullptr};
+        if (beside) a3 = side_part;
+        eet = nt_plan(Et, Et, d, d, T, 1, a3.room() / sizeof(float));
+        STRP_TAKE(ctx, a3, part, float, (size_t)eet.splits * d * d);
+        eet.out = part;
+        STRP_TRY(launch_gemm(ctx, eet));
+        STRP_TRY(aside.join());        // the sum below is with M^-2
+        STRP_TRY(launch_splitk_reduce(ctx, term1(eet)));
+      }
       const double c = params->beta / params->alpha;
       fin.do_1 = 1; fin.red_1 = red_t1; fin.n1 = reduce_blocks(d, d); fin.stride1 = 1; fin.c1 = params->alpha / (double)T * c * c;
     }

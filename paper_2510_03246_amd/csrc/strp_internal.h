@@ -211,6 +211,9 @@ struct SplitJob {
   unsigned short* lo;
 };
 strp_status split_small(strp_ctx* ctx, const SplitJob* jobs, int n);      // n <= 3, one launch
+// The planes of one matrix, and in the same launch plane_c_to_t of something else / the reduction of a symmetric product with an inner product.
+strp_status split_small_turn(strp_ctx* ctx, const SplitJob& job, const unsigned short* src, unsigned short* dst, int C, long long T);
+strp_status split_small_reduce(strp_ctx* ctx, const SplitJob& job, const ReduceP& r);
 // *maxbits[i] = max(*maxbits[i], bits of max|src_i|) for fp32 / bf16 matrices; n <= 2, one launch
 struct MaxJob {
   const void* src;

@@ -35,7 +35,7 @@ CSRC = os.path.join(HERE, "csrc")
 # kernels whose every launch belongs to one class of the library's records
 KERNEL_CLASS = {"pruned_rows_kernel": "pruned_rows", "cojob_kernel": "pruned_rows", "split_t_kernel": "split_act", "split_t_pair_kernel": "split_act", "split_c_kernel": "split_act",
                 "row_sums_kernel": "row_sums", "plane_c_to_t_kernel": "plane_c_to_t", "splitk_reduce_kernel": "splitk_reduce",
-                "splitk_reduce_group_kernel": "splitk_reduce"}
+                "splitk_reduce_group_kernel": "splitk_reduce", "split_turn_kernel": "plane_c_to_t", "split_reduce_kernel": "splitk_reduce"}
 # kernels that run the fp16 products: one launch of one of them per record of a class gemm_*
 GEMM_KERNELS = ("gemm_dma_kernel", "gemm_half_kernel", "gemm_tile_kernel", "gemm_kernel", "gemm_group_kernel")
 

@@ -1,5 +1,5 @@
 """Work on the context's second stream (the refits beside a factorisation, E beside the one of M, the targets of the initialisation
-beside that of H, a refit's right-hand side beside its own) against the same calls on a workspace that just does not hold both at a
+beside that of H, a refit's right-hand side beside its own) and E in the launches of a small M's chain, against the same calls on a workspace that just does not hold both at a
 time, and under capture: the same bits."""
 import ctypes as C
 
@@ -49,10 +49,8 @@ class _Space:
         return self.run(granules)[1]
 
 
-@pytest.mark.parametrize("d,f,T,k,mode,dtype", [(440, 1440, 9003, 600, strp.WANDA, "bf16"), (264, 1000, 30011, 401, strp.GAIN, "f32"), (72, 264, 70001, 131, strp.GAIN, "bf16"),
-                                                (40, 160, 100000, 60, strp.WANDA, "f32"), (768, 1536, 2000, 1408, strp.WANDA, "bf16")])
-def test_step_beside_and_in_turn(d, f, T, k, mode, dtype):
-    """Two iterations each.  The passes ride with the fc2 factorisation where the refits go in turn, and are a launch of their own beside it."""
+def _step_both_ways(d, f, T, k, mode, dtype, beside_by):
+    """Two iterations each, at the full workspace, the least on which beside_by(the launches' names) holds, and 256 bytes below."""
     ctx = strp.Context(0)
     mod = _module(ctx, d, f, T, k, dtype)
     mod.init(strp.Params(1.0, 0.7, 0.01, mode, 1, k, 0))
@@ -72,9 +70,9 @@ def test_step_beside_and_in_turn(d, f, T, k, mode, dtype):
                 assert st == strp.ENOMEM
                 return None
             terms.append(tuple(rep.terms))
-        return [getattr(mod, n).clone() for n in NAMES] + [torch.tensor(terms)]
+        return [t.clone() for t in (mod.A[:, :T], mod.Z[:, :T], mod.W1, mod.W2, mod.score, mod.mask)] + [torch.tensor(terms)]      # what lies behind a row's tokens may be NaN
 
-    w = _Space(ctx, ctx.workspace_bytes(mod.desc), call, lambda names: "pruned_rows" in names)
+    w = _Space(ctx, ctx.workspace_bytes(mod.desc), call, beside_by)
     full, beside = w.run(w.top)
     assert beside
     least = _smallest(w)
@@ -82,6 +80,20 @@ def test_step_beside_and_in_turn(d, f, T, k, mode, dtype):
         got, beside = w.run(granules)
         assert beside == want and all(torch.equal(a, b) for a, b in zip(got, full)), (granules, want)
     ctx.close()
+
+
+@pytest.mark.parametrize("d,f,T,k,mode,dtype", [(440, 1440, 9003, 600, strp.WANDA, "bf16"), (264, 1000, 30011, 401, strp.GAIN, "f32"), (72, 264, 70001, 131, strp.GAIN, "bf16"),
+                                                (40, 160, 100000, 60, strp.WANDA, "f32"), (768, 1536, 2000, 1408, strp.WANDA, "bf16")])
+def test_step_beside_and_in_turn(d, f, T, k, mode, dtype):
+    """Two iterations each.  The passes ride with the fc2 factorisation where the refits go in turn, and are a launch of their own beside it."""
+    _step_both_ways(d, f, T, k, mode, dtype, lambda names: "pruned_rows" in names)
+
+
+@pytest.mark.parametrize("d,f,T,k,mode,dtype", [(64, 256, 512, 128, strp.WANDA, "f32"), (40, 160, 333, 33, strp.GAIN, "f32"), (8, 64, 30011, 9, strp.WANDA, "bf16"),
+                                                (200, 704, 1111, 301, strp.GAIN, "bf16"), (512, 1504, 513, 500, strp.WANDA, "f32")])
+def test_residual_in_the_launches_of_the_chain(d, f, T, k, mode, dtype):
+    """E, its turned plane, E E^T and the sum with M^-2 share the launches of M's chain where all are small, and go by themselves where there is no room."""
+    _step_both_ways(d, f, T, k, mode, dtype, lambda names: not any(n.endswith("resid") for n in names))
 
 
 @pytest.mark.parametrize("side,m,n,T", [(strp.SIDE_FC2, 333, 200, 20003), (strp.SIDE_FC2, 64, 1000, 10000), (strp.SIDE_FC1, 300, 136, 30000)])
