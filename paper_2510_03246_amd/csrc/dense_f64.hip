@@ -878,31 +878,23 @@ strp_status gather_weights(strp_ctx* ctx, const WeightsOut& io, int m, int n) {
   return STRP_OK;
 }
 
-// several ranges in one launch: a launch costs more than clearing most of what is cleared here
-struct FillRanges {
-  uint32_t* p[3];
-  long long words[3];
-};
-__global__ __launch_bounds__(256) void fill_zero_kernel(const FillRanges f) {
-  const long long stride = (long long)gridDim.x * 256, e0 = (long long)blockIdx.x * 256 + threadIdx.x;
-  for (int r = 0; r < 3; ++r) {
-    uint32_t* p = f.p[r];
-    const long long quads = ((uintptr_t)p & 15) == 0 ? f.words[r] >> 2 : 0;
-    for (long long e = e0; e < quads; e += stride) ((uint4*)p)[e] = make_uint4(0u, 0u, 0u, 0u);
-    for (long long e = 4 * quads + e0; e < f.words[r]; e += stride) p[e] = 0u;
-  }
-}
+__global__ __launch_bounds__(256) void fill_zero_kernel(const FillRanges f) { fill_block(f, blockIdx.x, gridDim.x); }
 
-strp_status fill_zero(strp_ctx* ctx, const FillRange* ranges, int n) {
-  FillRanges f;
-  memset(&f, 0, sizeof(f));
-  long long most = 0;
+strp_status fill_ranges(strp_ctx* ctx, const FillRange* ranges, int n, FillRanges* f, long long* most) {
+  memset(f, 0, sizeof(*f));
+  *most = 0;
   for (int i = 0; i < n; ++i) {
     if (ranges[i].bytes % 4 != 0) return fail(ctx, STRP_EINVAL, "fill_zero: size not a multiple of 4");
-    f.p[i] = (uint32_t*)ranges[i].ptr;
-    f.words[i] = (long long)(ranges[i].bytes / 4);
-    most = f.words[i] > most ? f.words[i] : most;
+    f->p[i] = (uint32_t*)ranges[i].ptr;
+    f->words[i] = (long long)(ranges[i].bytes / 4);
+    *most = f->words[i] > *most ? f->words[i] : *most;
   }
+  return STRP_OK;
+}
+strp_status fill_zero(strp_ctx* ctx, const FillRange* ranges, int n) {
+  FillRanges f;
+  long long most;
+  STRP_TRY(fill_ranges(ctx, ranges, n, &f, &most));
   if (most == 0) return STRP_OK;
   long long blocks = (most + 1023) / 1024;
   if (blocks > 4096) blocks = 4096;

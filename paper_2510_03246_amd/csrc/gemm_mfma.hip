@@ -215,6 +215,20 @@ __global__ __launch_bounds__(256, 2) void gemm_tile_kernel(const GemmP p) {
 // 64x64 blocks (subM x subN of them), one 32x64 tile per wavefront.  The fragments come straight from memory -- the operand
 // layout is that of the fragments, 32 consecutive rows are 512 contiguous bytes -- with four contraction steps in flight, no LDS
 // image and no barrier; every element is summed in the order of the kernel above.
+// A symmetric product in a single split, straight to what a factorisation takes next: fp64 with the ridge on its diagonal, both triangles, and the
+// zeros of rows 0 .. 63 (reduce_to_system).
+__device__ __forceinline__ void system_epilogue(const GemmP& p, const floatx16 (&acc)[2], float unscale, int mbase, int nbase) {
+#pragma unroll
+  for (int j = 0; j < 2; ++j)
+#pragma unroll
+    for (int e = 0; e < 16; ++e) {
+      const int m = mbase + tile_rowoff<0>(e >> 2) + (e & 3), n = nbase + 32 * j;
+      const double v = 0.0 + (double)(acc[j][e] * unscale);
+      if (m >= p.M || n > m) continue;
+      p.sys[(long long)m * p.ldo + n] = m == n ? v + p.ridge : v;
+      if (n < m) p.sys[(long long)n * p.ldo + m] = n < NB && m >= NB ? 0.0 : v;
+    }
+}
 // ASK: an operand may have one plane only (its lo is then read from hi and not multiplied)
 template <int NPP, int NPQ, bool ASK>
 __device__ __forceinline__ void gemm_small_block(const GemmP& p, int block, int blocks) {
@@ -298,6 +312,7 @@ __device__ __forceinline__ void gemm_small_block(const GemmP& p, int block, int 
     case EPI_INITZ: epilogue<EPI_INITZ, 1, 2>(p, acc, unscale, mbase, nbase, split, srow, m0, red0, red1); break;
     case EPI_RESID: epilogue<EPI_RESID, 1, 2>(p, acc, unscale, mbase, nbase, split, srow, m0, red0, red1); break;
     case EPI_AUPD: epilogue<EPI_AUPD, 1, 2>(p, acc, unscale, mbase, nbase, split, srow, m0, red0, red1); break;
+    case EPI_SYSTEM: system_epilogue(p, acc[0], unscale, mbase, nbase); break;
     default: epilogue<EPI_ZUPD, 1, 2>(p, acc, unscale, mbase, nbase, split, srow, m0, red0, red1); break;
   }
   if (p.maxbits) {
@@ -453,6 +468,7 @@ static strp_status check_gemm(strp_ctx* ctx, const GemmP& p) {
   if (p.P.kg * 8 < p.K || p.Q.kg * 8 < p.K || (p.P.kg & 3) || (p.Q.kg & 3))
     return fail(ctx, STRP_EINVAL, "gemm: operand planes shorter than K or a group count that is not a multiple of four");
   if ((long long)p.P.npan * 128 < p.M || (long long)p.Q.npan * 128 < p.N) return fail(ctx, STRP_EINVAL, "gemm: operand planes narrower than the output");
+  if (p.epi == EPI_SYSTEM && (p.wt != 1 || !p.triangle)) return fail(ctx, STRP_EINVAL, "gemm: a system comes of a small symmetric product");
   if (p.epi != EPI_PARTIAL && p.splits != 1) return fail(ctx, STRP_EINVAL, "gemm: fused epilogues do not split K");
   return STRP_OK;
 }
@@ -462,7 +478,7 @@ struct GemmWork { double flops, bytes; };
 static GemmWork gemm_work(const GemmP& p) {
   const int npp = p.P.lo ? 2 : 1, npq = p.Q.lo ? 2 : 1;
   const double mn = p.triangle ? 0.5 * (double)p.M * ((double)p.M + 1.0) : (double)p.M * (double)p.N;
-  static const double out_words[] = {1.0, 1.0, 3.0, 2.0, 2.0, 2.0};
+  static const double out_words[] = {1.0, 1.0, 3.0, 2.0, 2.0, 2.0, 4.0};
   double obytes = 4.0 * out_words[p.epi] * (double)p.M * (double)p.N * (p.epi == EPI_PARTIAL ? (double)p.splits : 1.0);
   if (p.epi == EPI_RESID) obytes *= 0.5;
   if (p.k8_hi) obytes += (p.k8_lo ? 4.0 : 2.0) * (double)p.M * (double)p.N;
@@ -480,8 +496,8 @@ static void zero_pad_groups(strp_ctx* ctx, const GemmP& p) {
 strp_status launch_gemm(strp_ctx* ctx, GemmP& p) {
   STRP_TRY(check_gemm(ctx, p));
   const int npp = p.P.lo ? 2 : 1, npq = p.Q.lo ? 2 : 1;
-  static const char* const epi_names[] = {"partial", "store", "initz", "resid", "aupd", "zupd"};
-  static char names[3][3][6][40];
+  static const char* const epi_names[] = {"partial", "store", "initz", "resid", "aupd", "zupd", "system"};
+  static char names[3][3][7][40];
   char* name = names[npp][npq][p.epi];
   if (!name[0]) snprintf(name, 40, "gemm_h%dx%d_%s", npp, npq, epi_names[p.epi]);
   const GemmWork work = gemm_work(p);

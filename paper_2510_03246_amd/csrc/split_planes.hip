@@ -139,13 +139,15 @@ __global__ __launch_bounds__(256) void split_t_kernel(const void* src, long long
   split_t_block<SRC_BF16, WITH_C>(sh, sl, src, lds, idx, rows, T, relu, t_hi, t_lo, TGa, relu_c, c_hi, c_lo, KGc, status);
 }
 // The same rows of two fp32 matrices, as the refits of a small module need them: blockIdx.z = 0 the T-planes of a, 1 the T-planes
-// of z and the C-planes of relu(z).
+// of z and the C-planes of relu(z); from 2 on, the step's clearing.
 __global__ __launch_bounds__(256) void split_t_pair_kernel(const float* a, const float* z, long long lds, const int* idx, int rows, long long T,
                                                            unsigned short* a_hi, unsigned short* a_lo, unsigned short* z_hi, unsigned short* z_lo,
-                                                           long long TGa, unsigned short* c_hi, unsigned short* c_lo, int KGc, int32_t* status) {
+                                                           long long TGa, unsigned short* c_hi, unsigned short* c_lo, int KGc, int32_t* status,
+                                                           const FillRanges clear) {
   __shared__ __attribute__((aligned(16))) unsigned char sh[8 * SPLIT_GP];
   __shared__ __attribute__((aligned(16))) unsigned char sl[8 * SPLIT_GP];
-  if (blockIdx.z == 0) split_t_block<false, false>(sh, sl, a, lds, idx, rows, T, 0, a_hi, a_lo, TGa, 0, nullptr, nullptr, 0, status);
+  if (blockIdx.z >= 2) fill_block(clear, ((blockIdx.z - 2) * gridDim.y + blockIdx.y) * gridDim.x + blockIdx.x, (gridDim.z - 2) * gridDim.y * gridDim.x);
+  else if (blockIdx.z == 0) split_t_block<false, false>(sh, sl, a, lds, idx, rows, T, 0, a_hi, a_lo, TGa, 0, nullptr, nullptr, 0, status);
   else split_t_block<false, true>(sh, sl, z, lds, idx, rows, T, 0, z_hi, z_lo, TGa, 1, c_hi, c_lo, KGc, status);
 }
 
@@ -187,17 +189,24 @@ __global__ __launch_bounds__(256) void split_c_kernel(const void* src, long long
   }
 }
 
-// Two passes that each leave most of the chip idle, in one launch: a model of two d = 64 layers 12.90 -> 12.50 ms, a step 197 -> 194 us.
+// Two passes that each leave most of the chip idle, in one launch: a model of two d = 64 layers 12.90 -> 12.50 ms, a step 197 -> 194 us.  With the
+// clearing of the step's buffers in it as well: steps of 64 x 128 kept units over 512 tokens 150.8 -> 148.8 us, 200 x 400, 4000 302.7 -> 299.2, 768 x 600 of
+// 3400, 768 (21 MB to clear) 474.7 -> 471.9.
 strp_status split_act_pair(strp_ctx* ctx, const float* a, const float* z, long long lds, const int* idx, int rows, long long T, const PlaneOp& At,
-                           const PlaneOp& Zt, const PlaneOp& Zc) {
+                           const PlaneOp& Zt, const PlaneOp& Zc, const FillRange* clear) {
   if (rows <= 0 || T <= 0) return fail(ctx, STRP_EINVAL, "split_act: empty");
   if (!ctx->status_dev) return fail(ctx, STRP_ENOMEM, "split_act: no workspace set");
   if (lds % 8 || lds < T) return fail(ctx, STRP_EINVAL, "split_act: source pitch must be a multiple of 8 and at least T");
   ProfScope ps(ctx, "split_act", 0.0, (2.0 * 4.0 + 3.0 * (At.lo ? 4.0 : 2.0)) * (double)rows * (double)T);
+  FillRanges f;
+  long long most;
+  STRP_TRY(fill_ranges(ctx, clear, 3, &f, &most));
   // both reach the end of the last 128-token panel (the C-planes' padding), which the T-planes end in
-  hipLaunchKernelGGL(split_t_pair_kernel, dim3((unsigned)(2 * ((T + 127) / 128)), (unsigned)((rows + 127) / 128), 2), dim3(256), 0, ctx->stream, a, z, lds, idx,
+  const dim3 grid((unsigned)(2 * ((T + 127) / 128)), (unsigned)((rows + 127) / 128), 2);
+  const long long layer = (long long)grid.x * grid.y, layers = ((most + 1023) / 1024 + layer - 1) / layer;      // a kilobyte of words a workgroup, as far as sixteen layers go
+  hipLaunchKernelGGL(split_t_pair_kernel, dim3(grid.x, grid.y, 2 + (unsigned)(layers < 16 ? layers : 16)), dim3(256), 0, ctx->stream, a, z, lds, idx,
                      rows, T, (unsigned short*)At.hi, (unsigned short*)At.lo, (unsigned short*)Zt.hi, (unsigned short*)Zt.lo, plane_kg(T),
-                     (unsigned short*)Zc.hi, (unsigned short*)Zc.lo, (int)plane_kg(rows), ctx->status_dev);
+                     (unsigned short*)Zc.hi, (unsigned short*)Zc.lo, (int)plane_kg(rows), ctx->status_dev, f);
   STRP_HIP(ctx, hipGetLastError());
   return STRP_OK;
 }

@@ -1000,6 +1000,7 @@ struct RefitsIn {
   int planes;
   PlaneOp Y, X;
   const double* Linv1; const double* lam2_dev;
+  const FillRange* clear;      // three ranges that the step needs cleared (refit_both)
 };
 // *done: 0 = not small, or no room for what both hold at a time (the workspace of one refit after the other stays enough);
 // nothing was launched and nothing taken.  Otherwise *Zk: the planes of relu(Z_S) by channels, kept in the arena.
@@ -1041,7 +1042,7 @@ static strp_status refit_both(strp_ctx* ctx, Arena& arena, const RefitsIn& in, c
   *done = 1;
   arena = keep;
   *Zk = Zc;
-  STRP_TRY(split_act_pair(ctx, in.A, in.Z, in.lda, in.idx, s, T, At, Zt, Zc));
+  STRP_TRY(split_act_pair(ctx, in.A, in.Z, in.lda, in.idx, s, T, At, Zt, Zc, in.clear));
   STRP_TRY(launch_gemm_group(ctx, p, 3));
   STRP_TRY(launch_splitk_reduce_group(ctx, r, 3));
   STRP_TRY(factor_and_invert(ctx, a2, G, s, lds, Ginv, lds));
@@ -1543,16 +1544,13 @@ strp_status strp_admm_step(strp_ctx* ctx, const strp_module_desc* desc, strp_mod
   const int s = st->s;
   const long long sp = round_up(s, 8);
 
-  // ---- everything the step needs cleared, in one launch: the refitted weights outside the kept rows and columns, the
+  // ---- everything the step needs cleared, in one launch (that of the small refits' first planes, or its own): the refitted weights outside the kept rows and columns, the
   // maxima of the weights' planes, the finishing kernel's counter
   enum { MAX_W2 = 0, MAX_MI = 1, MAX_B = 2, MAX_W1 = 3 };
   STRP_TAKE(ctx, arena, wmax, unsigned int, 64);
   unsigned int* const ticket = wmax + 32;
-  {
-    const size_t wbytes = sizeof(float) * (size_t)f * d;
-    const FillRange z[3] = {{wmax, 256}, {st->W2, (stages & STRP_STAGE_REFIT2) ? wbytes : 0}, {st->W1, (stages & STRP_STAGE_REFIT1) ? wbytes : 0}};
-    STRP_TRY(fill_zero(ctx, z, 3));
-  }
+  const size_t wbytes = sizeof(float) * (size_t)f * d;
+  const FillRange clear[3] = {{wmax, 256}, {st->W2, (stages & STRP_STAGE_REFIT2) ? wbytes : 0}, {st->W1, (stages & STRP_STAGE_REFIT1) ? wbytes : 0}};
 
   // ---- the pruned rows' fused a/z pass as a ride-along job ------------------------------------------------------
   // It touches only rows outside S, which nothing else in the step reads or writes, so it may run any time from
@@ -1614,13 +1612,15 @@ strp_status strp_admm_step(strp_ctx* ctx, const strp_module_desc* desc, strp_mod
   Aside aside(ctx);
   Arena side_part;
   if (z_planes_once && (stages & STRP_STAGE_REFIT2)) {
-    const RefitsIn in{st->A, st->Z, lda, st->idx, s, d, T, npa, cv.Yt, cv.Xt, st->cholH, sc + SC_LAM2};
+    const RefitsIn in{st->A, st->Z, lda, st->idx, s, d, T, npa, cv.Yt, cv.Xt, st->cholH, sc + SC_LAM2, clear};
     STRP_TRY(refit_both(ctx, arena, in, w2out, w1out, &Zk8pre, &refits_done));
+    if (!refits_done) STRP_TRY(fill_zero(ctx, clear, 3));
     if (!refits_done && W1S) {
       STRP_TRY(refits_beside(ctx, aside, arena, in, w2out, w1out, bytes_after_refits(d, s, T, npa), &Zk8pre, &W1Sp, &side_part, &beside));
       refits_done = beside;
     }
   }
+  else STRP_TRY(fill_zero(ctx, clear, 3));
   if (refits_done) {
     // the fc2 weights are there
   } else if (stages & STRP_STAGE_REFIT2) {
@@ -1736,9 +1736,15 @@ strp_status strp_admm_step(strp_ctx* ctx, const strp_module_desc* desc, strp_mod
       residual_shared = eet.out && a4.room() >= bytes_after_refits(d, s, T, npa) && gemm_is_small(first[0]) && gemm_is_small(first[1]) && gemm_is_small(eet);
       if (residual_shared) arena = a4;
     }
+    // below some 500 kept units there is one partial, and the product of a small module writes the system by itself, with no reduction behind it
+    // (us a step of d x kept units over the tokens  64 x 128, 512 151.4 / 148.8;  200 x 400, 4000 302.4 / 299.2;  768 x 300, 768 389.7 / 386.5)
+    const bool direct = gemm_is_small(first[0]) && first[0].splits == 1;
+    if (direct) {
+      first[0].epi = EPI_SYSTEM; first[0].sys = Md; first[0].ldo = d; first[0].ridge = r.ridge;
+    }
     STRP_TRY(residual_shared ? launch_gemm_group(ctx, first, 2) : launch_gemm(ctx, first[0]));
     reduce_of(first[0], &r);
-    STRP_TRY(launch_splitk_reduce(ctx, r));
+    if (!direct) STRP_TRY(launch_splitk_reduce(ctx, r));
     // With both refits done E is next, which needs nothing of this chain.  Where it could not share the chain's launches it runs on the second
     // stream, from where M is factored on (us a step, 440 x 600 over 9000 tokens 546 -> 496; with one tile of M the two waits cost what there is
     // to hide: 64 x 128 over 512 172.7 / 173.7).

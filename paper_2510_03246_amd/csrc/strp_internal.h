@@ -117,7 +117,7 @@ static inline size_t plane_elems(long long rows, long long K) {
   return (size_t)((rows + 127) / 128) * (size_t)plane_kg(K) * 1024;
 }
 
-enum { EPI_PARTIAL = 0, EPI_STORE = 1, EPI_INITZ = 2, EPI_RESID = 3, EPI_AUPD = 4, EPI_ZUPD = 5 };
+enum { EPI_PARTIAL = 0, EPI_STORE = 1, EPI_INITZ = 2, EPI_RESID = 3, EPI_AUPD = 4, EPI_ZUPD = 5, EPI_SYSTEM = 6 };
 enum { SRC_F64 = 0, SRC_F32 = 1, SRC_BF16 = 2 };
 
 struct GemmP {
@@ -156,6 +156,9 @@ struct GemmP {
   float* rs_out;
   const float* rs_z0;
   int rs_slots;
+  // SYSTEM (64x64 blocks only): what the reduction of a single partial by reduce_to_system would write, leading dimension ldo
+  double* sys;
+  double ridge;
 };
 
 strp_status launch_gemm(strp_ctx* ctx, GemmP& p);
@@ -195,8 +198,10 @@ strp_status split_act(strp_ctx* ctx, const void* src, int src_dtype, long long l
                       int relu_t, int relu_c, unsigned short* t_hi, unsigned short* t_lo, unsigned short* c_hi,
                       unsigned short* c_lo);
 // Rows idx of two fp32 matrices in one launch: a -> t_* (At), z -> t_* (Zt) and, with relu, c_* (Zc); all of one plane or all of two.
+// clear: three ranges that the same launch clears.
+struct FillRange;
 strp_status split_act_pair(strp_ctx* ctx, const float* a, const float* z, long long lds, const int* idx, int rows, long long T, const PlaneOp& At,
-                           const PlaneOp& Zt, const PlaneOp& Zc);
+                           const PlaneOp& Zt, const PlaneOp& Zc, const FillRange* clear);
 // One fp16 plane of a [C x T] quantity with k = channel, r = token (plane_elems(T, C)) -> the plane with k = token,
 // r = channel (plane_elems(C, T)); padding tokens zero.
 strp_status plane_c_to_t(strp_ctx* ctx, const unsigned short* src, unsigned short* dst, int C, long long T);
@@ -308,6 +313,23 @@ struct FillRange {
   size_t bytes;      // multiple of 4
 };
 strp_status fill_zero(strp_ctx* ctx, const FillRange* ranges, int n);     // n <= 3, one launch
+// several ranges in one launch: a launch costs more than clearing most of what is cleared here
+struct FillRanges {
+  uint32_t* p[3];
+  long long words[3];
+};
+// bytes of 4 or more -> *f, in words; the longest of them in *most
+strp_status fill_ranges(strp_ctx* ctx, const FillRange* ranges, int n, FillRanges* f, long long* most);
+// by workgroup `block` of `blocks` of 256 threads
+__device__ __forceinline__ void fill_block(const FillRanges& f, unsigned int block, unsigned int blocks) {
+  const long long stride = (long long)blocks * 256, e0 = (long long)block * 256 + threadIdx.x;
+  for (int r = 0; r < 3; ++r) {
+    uint32_t* p = f.p[r];
+    const long long quads = ((uintptr_t)p & 15) == 0 ? f.words[r] >> 2 : 0;
+    for (long long e = e0; e < quads; e += stride) ((uint4*)p)[e] = make_uint4(0u, 0u, 0u, 0u);
+    for (long long e = 4 * quads + e0; e < f.words[r]; e += stride) p[e] = 0u;
+  }
+}
 
 // "The last workgroup does the rest": true in every thread of the last workgroup of the grid to get here.  What the
 // workgroups hand to it goes through agent-scope atomics (agent_put / agent_get / atomicAdd), which act at the level all

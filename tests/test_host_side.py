@@ -184,7 +184,7 @@ def check_rows_of_the_fc2_system():
 
 def check_systems_of_the_factorisations():
     """A factorisation in one launch keeps its counters in the system's columns 64 .. of rows 0 .. 63: what wrote the system last,
-    a reduction that says so (ReduceP::factored) or the conversion of a Gram matrix, has left zeros there."""
+    a reduction that says so (ReduceP::factored), a product that writes a system (GemmP::sys) or the conversion of a Gram matrix, has left zeros there."""
     lib = Library()
     strp = lib.strp
     lib.fake.fake_word.restype = C.c_uint64
@@ -193,6 +193,10 @@ def check_systems_of_the_factorisations():
     for i in range(3):
         WATCHES[f"outd{i}"] = (b"splitk_reduce_group_kernel", 0, REDUCEP * i + OUTD)
         WATCHES[f"factored{i}"] = (b"splitk_reduce_group_kernel", 0, REDUCEP * i + FACTORED)
+    SYS, GEMMP = 312, 328                             # bytes: GemmP::sys (set where the product writes the system, with its zeros), sizeof
+    WATCHES["sys"] = (b"11gemm_kernel", 0, SYS)
+    for i in range(3):
+        WATCHES[f"sys{i}"] = (b"gemm_group_kernel", 0, GEMMP * i + SYS)
     WATCHES["outd"] = (b"splitk_reduce_kernel", 0, OUTD)
     WATCHES["factored"] = (b"splitk_reduce_kernel", 0, FACTORED)
 
@@ -213,7 +217,7 @@ def check_systems_of_the_factorisations():
                 for q in ("", "0", "1", "2"):
                     if got["outd" + q][i] == system:
                         zeros = bool(got["factored" + q][i] & 0xffffffff)
-                if got["ridge"][i] == system:
+                if system in [got[w][i] for w in ("ridge", "sys", "sys0", "sys1", "sys2")]:
                     zeros = True
             assert zeros, (at, hex(system))
             factored += 1
