@@ -197,8 +197,9 @@ __device__ __forceinline__ void epilogue_tile(const GemmP& p, const floatx16 a16
       }
     }
     // optional operand-plane copy of the produced tile (its rows are the contraction axis of the consumer):
-    // this lane's four rows are half of one 16-byte chunk; rows past M inside the last chunk are written as zeros
-    if ((EPI == EPI_STORE || EPI == EPI_INITZ || EPI == EPI_RESID) && p.k8_hi && ncol && (!EDGE || (mq & ~7) < p.M)) {
+    // this lane's four rows are half of one 16-byte chunk.  Rows past M up to the planes' last group are written as zeros: that is 32 rows at most
+    // and they lie in the tile of row M - 1 (a launch of its own for them took 3 to 5 us of every step whose d is no multiple of 32)
+    if ((EPI == EPI_STORE || EPI == EPI_INITZ || EPI == EPI_RESID) && p.k8_hi && ncol && (!EDGE || mq < 8 * (int)p.k8_kg)) {
       unsigned short h[4], l[4];
 #pragma unroll
       for (int r = 0; r < 4; ++r) split_half(outv[r], h[r], l[r]);

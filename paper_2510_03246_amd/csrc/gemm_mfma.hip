@@ -438,17 +438,6 @@ void gemm_plan_tiles(GemmP& p, int want_splits, int wt) {
 
 int gemm_grid_blocks(const GemmP& p) { return p.gridM * p.gridN * p.splits * (p.wt == 1 ? p.subM * p.subN : 1); }
 
-// zero the pad k-groups [g_first, kg) of a plane written by an epilogue (whose rows fill the groups below g_first)
-__global__ __launch_bounds__(256) void zero_pad_group_kernel(unsigned short* hi, unsigned short* lo, long long kg, int g_first, int npan) {
-  const long long e = (long long)blockIdx.x * 256 + threadIdx.x;   // 16-byte chunk index over npan x 128
-  if (e >= (long long)npan * 128) return;
-  for (long long g = g_first; g < kg; ++g) {
-    const long long o = (((e >> 7) * kg + g) * 128 + (e & 127)) * 8;
-    *(uint4*)(hi + o) = make_uint4(0, 0, 0, 0);
-    if (lo) *(uint4*)(lo + o) = make_uint4(0, 0, 0, 0);
-  }
-}
-
 void launch_gemm_dma(strp_ctx* ctx, const GemmP& p, int npp, int npq);   // gemm_dma.hip
 
 template <int NPP, int NPQ>
@@ -468,6 +457,7 @@ static strp_status check_gemm(strp_ctx* ctx, const GemmP& p) {
   if (p.P.kg * 8 < p.K || p.Q.kg * 8 < p.K || (p.P.kg & 3) || (p.Q.kg & 3))
     return fail(ctx, STRP_EINVAL, "gemm: operand planes shorter than K or a group count that is not a multiple of four");
   if ((long long)p.P.npan * 128 < p.M || (long long)p.Q.npan * 128 < p.N) return fail(ctx, STRP_EINVAL, "gemm: operand planes narrower than the output");
+  if (p.k8_hi && p.k8_kg != plane_kg(p.M)) return fail(ctx, STRP_EINVAL, "gemm: planes of another height than the output");
   if (p.epi == EPI_SYSTEM && (p.wt != 1 || !p.triangle)) return fail(ctx, STRP_EINVAL, "gemm: a system comes of a small symmetric product");
   if (p.epi != EPI_PARTIAL && p.splits != 1) return fail(ctx, STRP_EINVAL, "gemm: fused epilogues do not split K");
   return STRP_OK;
@@ -487,12 +477,6 @@ static GemmWork gemm_work(const GemmP& p) {
   return {2.0 * mn * (double)p.K, ibytes + obytes};
 }
 
-static void zero_pad_groups(strp_ctx* ctx, const GemmP& p) {
-  if (!p.k8_hi || (p.M + 7) / 8 >= p.k8_kg) return;
-  const int npan = (p.N + 127) / 128;
-  hipLaunchKernelGGL(zero_pad_group_kernel, dim3((npan * 128 + 255) / 256), dim3(256), 0, ctx->stream, p.k8_hi, p.k8_lo, p.k8_kg, (p.M + 7) / 8, npan);
-}
-
 strp_status launch_gemm(strp_ctx* ctx, GemmP& p) {
   STRP_TRY(check_gemm(ctx, p));
   const int npp = p.P.lo ? 2 : 1, npq = p.Q.lo ? 2 : 1;
@@ -502,7 +486,6 @@ strp_status launch_gemm(strp_ctx* ctx, GemmP& p) {
   if (!name[0]) snprintf(name, 40, "gemm_h%dx%d_%s", npp, npq, epi_names[p.epi]);
   const GemmWork work = gemm_work(p);
   ProfScope ps(ctx, name, work.flops, work.bytes);
-  zero_pad_groups(ctx, p);
   switch (npp * 10 + npq) {
     case 11: launch_one<1, 1>(ctx, p); break;
     case 12: launch_one<1, 2>(ctx, p); break;
@@ -531,7 +514,6 @@ strp_status launch_gemm_group(strp_ctx* ctx, GemmP* p, int n) {
     if (i < n) {
       STRP_TRY(check_gemm(ctx, p[i]));
       blocks += gemm_grid_blocks(p[i]);
-      zero_pad_groups(ctx, p[i]);
       const GemmWork w = gemm_work(p[i]);
       work.flops += w.flops;
       work.bytes += w.bytes;

@@ -148,7 +148,7 @@ struct GemmP {
   int write_out;       // ZUPD: 1 = update Z, 0 = only accumulate the objective sums
   unsigned int* maxbits;  // STORE, optional: atomic maximum of the bits of |C|
   unsigned short* k8_hi;  // optional operand planes of the produced values with k = output row, r = output column
-  unsigned short* k8_lo;  //   (STORE: C, INITZ: relu(C), RESID: Y - C; not offered by AUPD / ZUPD); k8_kg = M / 8 groups, ceil(N/128) panels
+  unsigned short* k8_lo;  //   (STORE: C, INITZ: relu(C), RESID: Y - C; not offered by AUPD / ZUPD); k8_kg = plane_kg(M) groups, ceil(N/128) panels
   long long k8_kg;
   // AUPD / ZUPD, optional: scoring sums of the rows being written, one fp32 partial per output row and 64-column strip,
   //   rs_out[(q * rs_slots + strip) * M + m];  AUPD: q = 0 sum a^2, q = 1 sum a relu(z0) (iff rs_z0); ZUPD: q = 0 sum z0 z

@@ -58,3 +58,22 @@ def test_update_of_the_kept_rows(d, f, T, k, mode):
     mod.step(p2)
     assert rel(mod.score, want) <= 1e-5
     ctx.close()
+
+
+@pytest.mark.parametrize("d,f,T,k", [(40, 168, 333, 33), (200, 800, 9000, 400), (72, 264, 70001, 131), (264, 1000, 66000, 270), (600, 1608, 5000, 800), (968, 2400, 16384, 1500)])
+def test_planes_that_epilogues_write_are_whole(d, f, T, k):
+    """Where d or f is no multiple of 32 the planes of E and of relu(Z0) end in groups past the last row, which the next products read: zeros, whatever the
+    workspace held (each tile of E: 64x64, 128x128, 128x256, 64x256, 256x256)."""
+    ctx = strp.Context(0)
+    g = torch.Generator(device="cuda").manual_seed(k)
+    W1, W2, X = (0.05 * torch.randn(s, generator=g, device="cuda") for s in ((f, d), (d, f), (d, (T + 7) // 8 * 8)))
+    mod = strp.FFNModule(ctx, W1, W2, 20 * X, T, k_max=k)
+    par, got = strp.Params(1.0, 0.7, 0.01, strp.WANDA, 1, k, 0), []
+    for byte in (0, 255):                # 255: NaN in fp16, fp32 and fp64
+        ctx.set_workspace(ctx.workspace_bytes(mod.desc))
+        ctx.ws[256:] = byte
+        mod.init(par)
+        rep = mod.step(par)
+        got.append([t.clone() for t in (mod.Y[:, :T], mod.A[:, :T], mod.Z[:, :T], mod.W1, mod.W2, mod.H)] + [torch.tensor(list(rep.terms))])
+    assert all(torch.equal(a, b) for a, b in zip(*got)) and bool(torch.isfinite(got[0][1]).all())
+    ctx.close()
