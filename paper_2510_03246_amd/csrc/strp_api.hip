@@ -190,7 +190,8 @@ enum { SC_LAM1 = 0, SC_LAM2 = 1, SC_SUMA0 = 2, SC_TRH = 3, SC_T1 = 4, SC_T2 = 5,
 // z-update epilogues wrote, the objective's terms from the workgroups' sums, and the report's read-back.  What bounds it is the round trips to memory
 // that follow each other, so everything that is independent is another workgroup or is asked for at once, and the last workgroup to end puts it together.
 // A launch for the strips' sums of either update and one workgroup that formed the objective's seven sums one after the other before: us of
-// a step's end, 768 x 1536 units over 65536 tokens 30 -> 12, 1000 x 1013 over 30011 (GAIN) 28 -> 12, 64 x 128 over 512 8.7 -> 9.5 (a launch less).
+// a step's end, 768 x 1536 units over 65536 tokens 30 -> 12, 1000 x 1013 over 30011 (GAIN) 28 -> 12, 64 x 128 over 512 8.7 -> 9.4 (a launch less), and 7.2 since
+// wavefronts without a summand exchange nothing.
 constexpr int FINISH_THREADS = 1024, FINISH_ROWS = FINISH_THREADS / 6, FINISH_SUMS = 7;
 static inline int finish_row_blocks(int nrows) { return (nrows + 2 * FINISH_ROWS - 1) / (2 * FINISH_ROWS); }      // two rows one after the other
 struct FinishP {
@@ -219,14 +220,17 @@ struct FinishP {
   double* host;                              // pinned: [SC_COUNT] scalars, then the status word; null: no report
   int32_t* status;
 };
-// sums of v over the workgroup, in out (LDS) for everybody
+// sums of v over the workgroup, in out (LDS) for everybody; threads from `active` on hold zeros, and a wavefront of them exchanges nothing (the
+// exchanges of sixteen wavefronts go through one LDS: 84 of each for seven sums)
 template <int K>
-__device__ __forceinline__ void finish_sums(double (&v)[K], double (&sh)[FINISH_SUMS][16], double* out) {
+__device__ __forceinline__ void finish_sums(double (&v)[K], double (&sh)[FINISH_SUMS][16], double* out, int active) {
   const int tid = threadIdx.x;
+  if ((int)__builtin_amdgcn_readfirstlane(tid) < active) {
 #pragma unroll
-  for (int o = 32; o > 0; o >>= 1)
+    for (int o = 32; o > 0; o >>= 1)
 #pragma unroll
-    for (int q = 0; q < K; ++q) v[q] += __shfl_down(v[q], o, 64);
+      for (int q = 0; q < K; ++q) v[q] += __shfl_down(v[q], o, 64);
+  }
   if ((tid & 63) == 0)
 #pragma unroll
     for (int q = 0; q < K; ++q) sh[q][tid >> 6] = v[q];
@@ -301,7 +305,7 @@ __global__ __launch_bounds__(FINISH_THREADS) void step_finish_kernel(const Finis
   double r[2] = {0.0, 0.0};
   if (b < p.row_blocks) {
     finish_rows(p, b, r);
-    finish_sums<2>(r, sh, rtot);
+    finish_sums<2>(r, sh, rtot, 6 * (p.nrows - 2 * b * FINISH_ROWS));
     if (tid < 2) agent_put(&p.blk[2 * b + tid], rtot[tid]);
   } else if (b == p.row_blocks) {
     double v[FINISH_SUMS];
@@ -326,7 +330,10 @@ __global__ __launch_bounds__(FINISH_THREADS) void step_finish_kernel(const Finis
       every(p.w2, p.nw2, 1, v[5]);
       every(p.w1, p.nw1, 1, v[6]);
     }
-    finish_sums<FINISH_SUMS>(v, sh, tot);
+    int most = p.do_1 ? p.n1 : 0;
+    if (p.do_z) most = max(most, max(p.nz, p.np));
+    if (p.do_w) most = max(most, max(p.nw2, p.nw1));
+    finish_sums<FINISH_SUMS>(v, sh, tot, most);
     if (gridDim.x > 1 && tid < FINISH_SUMS) agent_put(&p.sums[tid], tot[tid]);
   } else {
     finish_strips(p, b - p.row_blocks - 1, strips);
@@ -340,7 +347,7 @@ __global__ __launch_bounds__(FINISH_THREADS) void step_finish_kernel(const Finis
       r[0] += agent_get(&p.blk[2 * i]);
       r[1] += agent_get(&p.blk[2 * i + 1]);
     }
-    finish_sums<2>(r, sh, rtot);
+    finish_sums<2>(r, sh, rtot, p.row_blocks);
   }
   // one lane a scalar: those that are new go to the state, all of them to the report
   if (tid < SC_COUNT) {
