@@ -227,10 +227,33 @@ __device__ __forceinline__ void dgemm_block(const DgemmP& p, int block) {
   if (share) {
   } else if (p.w.W) {
     const bool fc2 = p.w.side == STRP_SIDE_FC2;
+    // where rows and columns go, all indices asked for at once and clamped (under the condition of the store each one was waited for: 64 rows of 128
+    // 8.2 / 7.5 us, 200 of 400 14.1 / 13.3)
+    int wrow[WM][4], wcol[WN];
+#pragma unroll
+    for (int i = 0; i < WM; ++i)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int m = m0 + wm + 16 * i + 4 * r + lq;
+        wrow[i][r] = m < p.M ? m : p.M - 1;
+      }
 #pragma unroll
     for (int j = 0; j < WN; ++j) {
       const int n = n0 + wn + 16 * j + l16;
-      const long long wcol = n < p.N ? (fc2 ? (long long)p.w.idx[n] : (long long)n) : 0;
+      wcol[j] = n < p.N ? n : p.N - 1;
+    }
+    if (fc2) {
+#pragma unroll
+      for (int j = 0; j < WN; ++j) wcol[j] = p.w.idx[wcol[j]];
+    } else {
+#pragma unroll
+      for (int i = 0; i < WM; ++i)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) wrow[i][r] = p.w.idx[wrow[i][r]];
+    }
+#pragma unroll
+    for (int j = 0; j < WN; ++j) {
+      const int n = n0 + wn + 16 * j + l16;
 #pragma unroll
       for (int i = 0; i < WM; ++i)
 #pragma unroll
@@ -238,7 +261,7 @@ __device__ __forceinline__ void dgemm_block(const DgemmP& p, int block) {
           const int m = m0 + wm + 16 * i + 4 * r + lq;
           if (m < p.M && n < p.N) {
             const float v = (float)acc[i][j][r];
-            p.w.W[(fc2 ? (long long)m : (long long)p.w.idx[m]) * p.w.ldw + wcol] = v;
+            p.w.W[(long long)wrow[i][r] * p.w.ldw + wcol[j]] = v;
             if (p.w.Wc) p.w.Wc[(long long)m * p.w.ldc + n] = v;
             big = fmax(big, fabs((double)v));
             sq = __builtin_fma((double)v, (double)v, sq);
