@@ -1729,9 +1729,10 @@ strp_status strp_admm_step(strp_ctx* ctx, const strp_module_desc* desc, strp_mod
     STRP_TAKE(ctx, a3, part, float, (size_t)first[0].splits * d * d);
     first[0].out = part;
     // A small module's chain is launches of a few workgroups, so E, its turned plane, E E^T and the sum with M^-2 share them: E that of W W^T, the
-    // plane that of M^-1's planes, E E^T that of B, the sum that of B's planes: four launches fewer, the same bits.  us a step of d x kept units over the tokens, in launches of their own (at d <= 64) or on the second stream /
-    // shared:  64 x 128, 512 173.8 / 157.0;  64 x 128, 30000 260 / 240;  48 x 90, 3000 177 / 159;  72 x 128, 512 182 / 173;  128 x 256, 2048 223 / 213;
-    // 200 x 400, 4000 310 / 300;  256 x 512, 2048 307 / 298;  512 x 1000, 1024 517 / 514;  768 x 600, 768 473 / 469.
+    // plane that of M^-1's planes, E E^T that of B, the sum that of B's planes: four launches fewer, the same bits.  us a step of d x kept units over
+    // the tokens, in launches of their own (at d <= 64) or on the second stream / shared:  64 x 128, 512 173.8 / 157.0;  64 x 128, 30000 260 / 240;
+    // 48 x 90, 3000 177 / 159;  72 x 128, 512 182 / 173;  128 x 256, 2048 223 / 213;  200 x 400, 4000 310 / 300;  256 x 512, 2048 307 / 298;
+    // 512 x 1000, 1024 517 / 514;  768 x 600, 768 473 / 469.
     if (term1_identity && refits_done && !beside) {
       Arena a4 = arena;
       eth = take_residual(a4) ? (unsigned short*)a4.take(2 * plane_elems(d, T)) : nullptr;
