@@ -906,19 +906,25 @@ struct Aside {
         (void)hipGetLastError();
         return false;
       }
-      // the events order kernels of one device: no fence for the host or other devices (6 us less each)
-      const unsigned int flags = hipEventDisableTiming | hipEventDisableSystemFence;
-      ctx->side_state = -1;
-      if (hipStreamCreateWithFlags(&ctx->side, hipStreamNonBlocking) == hipSuccess) {
-        if (hipEventCreateWithFlags(&ctx->side_event[0], flags) == hipSuccess) {
-          if (hipEventCreateWithFlags(&ctx->side_event[1], flags) == hipSuccess) ctx->side_state = 1;
-          else (void)hipEventDestroy(ctx->side_event[0]);
-        }
-        if (ctx->side_state < 0) (void)hipStreamDestroy(ctx->side);
-      }
+      // streams and events belong to the device that is current in the calling thread as they are made, which need not be the context's
+      int current = 0;
+      const bool known = hipGetDevice(&current) == hipSuccess;
+      ctx->side_state = known && hipSetDevice(ctx->device) == hipSuccess && make() ? 1 : -1;
+      if (known) (void)hipSetDevice(current);
       if (ctx->side_state < 0) (void)hipGetLastError();
     }
     return ctx->side_state > 0;
+  }
+  // the events order kernels of one device: no fence for the host or other devices (6 us less each)
+  bool make() const {
+    const unsigned int flags = hipEventDisableTiming | hipEventDisableSystemFence;
+    if (hipStreamCreateWithFlags(&ctx->side, hipStreamNonBlocking) != hipSuccess) return false;
+    if (hipEventCreateWithFlags(&ctx->side_event[0], flags) == hipSuccess) {
+      if (hipEventCreateWithFlags(&ctx->side_event[1], flags) == hipSuccess) return true;
+      (void)hipEventDestroy(ctx->side_event[0]);
+    }
+    (void)hipStreamDestroy(ctx->side);
+    return false;
   }
   // what follows on `to` waits for what `from` has been given so far
   strp_status order(hipStream_t from, hipStream_t to, int e) {

@@ -32,7 +32,7 @@ struct strp_ctx {
   unsigned int* tickets;  // all of them, on this device
   int ticket_due;         // another workspace has been set: the next weight statistics take the next counter
   // A second stream for work that a call's latency-bound part leaves the chip to (see Aside in strp_api.hip), and the events that order the two.
-  // Made by the first call that can use them; side_state: 0 not yet, 1 there, -1 not to be had.
+  // Made by the first call that can use them, on the context's device; side_state: 0 not yet, 1 there, -1 not to be had.
   hipStream_t side;
   hipEvent_t side_event[2];
   int side_state;

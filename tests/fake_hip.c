@@ -74,8 +74,12 @@ int hipLaunchKernel(const void* fn, dim3_t grid, dim3_t block, void** args, size
   }
   return 0;
 }
-int hipGetDeviceCount(int* n) { *n = 1; return 0; }
-int hipSetDevice(int d) { (void)d; return 0; }
+/* Two devices, one of them current; streams and events belong to the one that is current as they are made. */
+static int device, made[2];
+int fake_made(int d) { return made[d]; }
+int hipGetDeviceCount(int* n) { *n = 2; return 0; }
+int hipSetDevice(int d) { device = d; return 0; }
+int hipGetDevice(int* d) { *d = device; return 0; }
 int hipGetLastError(void) { return 0; }
 const char* hipGetErrorString(int e) { (void)e; return "fake"; }
 int hipHostMalloc(void** p, size_t n, unsigned flags) { (void)flags; *p = calloc(1, n); return 0; }
@@ -84,7 +88,7 @@ int hipGetSymbolAddress(void** p, const void* s) { (void)s; *p = device_array; r
 int hipMemcpyAsync(void* d, const void* s, size_t n, int kind, void* stream) { (void)d; (void)s; (void)n; (void)kind; (void)stream; return 0; }
 int hipStreamSynchronize(void* s) { (void)s; return 0; }
 int hipEventCreate(void** e) { *e = device_array; return 0; }
-int hipEventCreateWithFlags(void** e, unsigned flags) { (void)flags; *e = calloc(1, sizeof(order_t)); return 0; }
+int hipEventCreateWithFlags(void** e, unsigned flags) { (void)flags; *e = calloc(1, sizeof(order_t)); ++made[device]; return 0; }
 int hipEventDestroy(void* e) { (void)e; return 0; }
 int hipEventRecord(void* e, void* s) { if (e != device_array) *(order_t*)e = streams[stream_of(s)].order; return 0; }
 int hipStreamWaitEvent(void* s, void* e, unsigned flags) {
@@ -93,7 +97,7 @@ int hipStreamWaitEvent(void* s, void* e, unsigned flags) {
   for (int i = 0; i < 8; ++i) if (o->over[i] < ((order_t*)e)->over[i]) o->over[i] = ((order_t*)e)->over[i];
   return 0;
 }
-int hipStreamCreateWithFlags(void** s, unsigned flags) { (void)flags; *s = malloc(1); return !streams_on; }
+int hipStreamCreateWithFlags(void** s, unsigned flags) { (void)flags; *s = malloc(1); made[device] += streams_on; return !streams_on; }
 int hipStreamDestroy(void* s) { (void)s; return 0; }
 int hipStreamIsCapturing(void* s, int* status) { (void)s; *status = 0; return 0; }
 int hipEventElapsedTime(float* ms, void* a, void* b) { (void)a; (void)b; *ms = 0; return 0; }

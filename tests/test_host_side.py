@@ -565,6 +565,27 @@ def check_second_stream():
     assert seen == {True, False}
 
 
+def check_second_stream_is_on_the_device_of_its_context():
+    """A stream and an event belong to the device that is current as they are made, and a context may be used from a thread whose current
+    device is another one: its second stream and its two events are made on its own device, and the thread keeps the one it had."""
+    lib = Library()
+    strp, fake = lib.strp, lib.fake
+    fake.fake_streams(1)
+    for device, current in ((1, 0), (0, 1)):
+        h = C.c_void_p()
+        assert lib.lib.strp_create(C.byref(h), device, None) == strp.OK
+        assert lib.lib.strp_set_workspace(h, 1 << 40, 1 << 50) == strp.OK
+        fake.hipSetDevice(current)
+        before = [fake.fake_made(i) for i in (0, 1)]
+        for _ in range(2):
+            st, launches = lib.launches(lambda: lib.lib.strp_refit(h, strp.SIDE_FC2, 1 << 52, 832, 1.0, None, 0, 1 << 50, strp.F32, 65536, 1 << 51, strp.BF16, 65536,
+                                                                   65536, 1 << 53, 832, 1 << 54, 2048, 832))
+            assert st == strp.OK and any(fake.fake_stream(i) for i in range(len(launches)))
+        assert [fake.fake_made(i) - n for i, n in enumerate(before)] == [3 * (device == i) for i in (0, 1)]
+        now = C.c_int(-1)
+        assert fake.hipGetDevice(C.byref(now)) == 0 and now.value == current
+
+
 def check_weight_statistics_without_a_counter():
     """A call is one launch for up to eight matrices; a context that found no counter left takes one more."""
     lib = Library()
@@ -614,7 +635,7 @@ def check_weight_statistics_counter():
     assert counter(lib.h) not in (0, a, b, c)
 
 
-CHECKS = [check_systems_of_the_factorisations, check_which_factorisation_runs, check_tiles_of_the_solves, check_tiles_of_the_kept_rows, check_second_stream, check_weight_statistics_counter, check_weight_statistics_without_a_counter, check_what_the_gram_matrices_cover, check_what_the_large_systems_cover, check_selection_of_a_very_wide_module, check_weight_statistics_arguments, check_weight_statistics_workgroups, check_chains, check_workspace_of_a_module, check_least_workspace_of_a_step, check_rows_of_the_fc2_system, check_work_of_shared_launches, check_profile_classes, check_workspace_of_a_factorisation, check_cached_factor_needs_no_alignment]
+CHECKS = [check_systems_of_the_factorisations, check_which_factorisation_runs, check_tiles_of_the_solves, check_tiles_of_the_kept_rows, check_second_stream, check_second_stream_is_on_the_device_of_its_context, check_weight_statistics_counter, check_weight_statistics_without_a_counter, check_what_the_gram_matrices_cover, check_what_the_large_systems_cover, check_selection_of_a_very_wide_module, check_weight_statistics_arguments, check_weight_statistics_workgroups, check_chains, check_workspace_of_a_module, check_least_workspace_of_a_step, check_rows_of_the_fc2_system, check_work_of_shared_launches, check_profile_classes, check_workspace_of_a_factorisation, check_cached_factor_needs_no_alignment]
 
 
 @pytest.fixture(scope="session")
