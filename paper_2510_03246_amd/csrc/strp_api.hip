@@ -915,7 +915,10 @@ struct Aside {
     }
     return ctx->side_state > 0;
   }
-  // the events order kernels of one device: no fence for the host or other devices (6 us less each)
+  // The events order kernels of one device: no fence for the host or for other devices.  What makes the results of one stream visible to the other is then
+  // what does so from kernel to kernel within a stream, the release at device scope as a kernel ends and the acquire as the next begins: that is relied on.
+  // us a call with this flag / with hipEventReleaseToDevice / with neither:  a step of 440 x 600 over 9000 tokens 457 / 465 / 461, a head pruning of
+  // 1280 x 512 over 20000 283 / 290 / 289.
   bool make() const {
     const unsigned int flags = hipEventDisableTiming | hipEventDisableSystemFence;
     if (hipStreamCreateWithFlags(&ctx->side, hipStreamNonBlocking) != hipSuccess) return false;
