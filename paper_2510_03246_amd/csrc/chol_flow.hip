@@ -803,14 +803,14 @@ static bool flow_lines(const double* M, long long ld) { return ld % 16 == 0 && (
 // 5400, 4.0 4885 / 4982, 8.0 5612 / 5360, 17 6877 / 6166.  Elsewhere it widens the lead:  1000 of 2312 units over 30011 tokens 288 / 193, 3281 of 8192
 // over 65536 1985 / 1691, 4912, 1.9 GB, 3403 / 3148.  With a pass beside
 // them tiles that share lines cost the launch its lead (1000 331, 1544 744 / 728, 3281 2113 / 2043): a step pads its rows (system_ld).
-bool chol_flow_can(int n) { return n >= NB + 8 && flow_lines_needed((n + NB - 1) / NB) <= NB << flow_row_lines(n); }
 bool chol_flow_ok(int n, double pass_bytes) {
   const int N = (n + NB - 1) / NB;
-  if (!chol_flow_can(n)) return false;
+  if (n < NB + 8 || flow_lines_needed(N) > NB << flow_row_lines(n)) return false;
   if (N >= 63 && N <= 68) return pass_bytes >= 1e9;
   if (N >= 84 && N <= 90) return pass_bytes >= 4e9;
   return true;
 }
+bool chol_by_order(int n) { return chol_flow_ok(n, 0.0) == chol_flow_ok(n, 1e30); }
 
 strp_status chol_flow(strp_ctx* ctx, double* A, int n, long long ld, double* Linv, long long ldv, int32_t* status, const CoJob& job) {
   FlowP p;

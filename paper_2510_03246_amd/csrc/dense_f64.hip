@@ -759,8 +759,7 @@ strp_status chol_inverse(strp_ctx* ctx, double* A, int n, long long ld, double* 
   ctx->cojob = nullptr;
   const double pass_bytes = (job.Z0 ? 16.0 : 12.0) * (double)job.nrows * (double)job.T;
   ProfScope ps(ctx, "chol_factor_f64", 2.0 * (double)n * n * n / 3.0, 16.0 * (double)n * n + pass_bytes);
-  // beside other kernels a launch per panel would wait for the CUs that those hold, each launch anew
-  if (ctx->flow_workers ? chol_flow_can(n) : chol_flow_ok(n, pass_bytes)) return chol_flow(ctx, A, n, ld, Linv, ldv, status, job);
+  if (chol_flow_ok(n, pass_bytes)) return chol_flow(ctx, A, n, ld, Linv, ldv, status, job);
   StepP p;
   memset(&p, 0, sizeof(p));
   p.A = A; p.ld = ld; p.V = Linv; p.ldv = ldv; p.sub = sub; p.n = n; p.N = (n + NB - 1) / NB; p.status = status;

@@ -886,7 +886,11 @@ static long long system_ld(Arena a, int d, int s, long long T, int np) {
 
 // Work of one call on the context's second stream, beside what the call's own stream does meanwhile.  A factorisation is a chain of
 // dependent pivots that holds a few dozen CUs; in one launch it keeps them while the kernels of the other stream run on the rest,
-// where its launches per panel would each wait for CUs again.  The call's own stream has waited for the other one when the call
+// where its launches per panel would each wait for CUs again.  Which of the two a system takes is chol_inverse's to say, with company or without, so that
+// the factor's bits depend neither on the room in the workspace nor on whether there is a second stream.  An order that takes launches per panel where no pass
+// rides along (chol_by_order) stays in turn (us, in turn / beside those launches:  an initialisation of 4096 x 16384 over 2048 tokens 3299 / 3273, 5504 x 8000
+// over 8000 6795 / 6839, refits of 512 x 4096 over 5000 2271 / 2251, 4096 x 4096 over 65536 8381 / 8435), but for M's, beside which E runs in any case
+// (d = 4096, 4915 kept units over 2048 and 16384 tokens 13.04 / 12.99 and 20.22 / 20.16 ms).  The call's own stream has waited for the other one when the call
 // returns, so that to the caller everything is on his stream, captured or not.
 struct Aside {
   strp_ctx* const ctx;
@@ -1090,7 +1094,7 @@ static size_t bytes_after_refits(int d, int s, long long T, int np) {
 // that and beside what comes of W2.  us of a step, one after the other / so:  440 x 600 over 9000 tokens 604 / 489, 768 x 1536 over 16384 1564 / 1318, 1600 x 2500
 // over 8000 2991 / 2652, 1000 x 1013 over 30011 (fp32, GAIN) 1949 / 1729, 768 x 1536 over 65536 3547 / 3387, 2048 x 3277 over 65536 15740 / 15520.
 // What it hides is the factorisations' time, so not where the products' is many times that: 2048 x 3277 over 262144 52.2 / 52.3 ms, 4096 x 4915 over
-// 131072 79.3 / 79.8.  The bits are the same, but for those of the factor in the two ranges of orders that go by launches per panel otherwise (chol_flow_ok).
+// 131072 79.3 / 79.8.  The bits are the same.
 static bool refits_beside_pay(int d, int s, long long T) {
   const double N = (s + NB - 1) / NB, factor_us = 11.0 * N + N * N * N / 260.0, product_us = 6.0 * d * s * (double)T / 1.2e9;
   return product_us <= 4.0 * factor_us;
@@ -1102,7 +1106,7 @@ static strp_status refits_beside(strp_ctx* ctx, Aside& aside, Arena& arena, cons
   const int s = in.s, d = in.d;
   const long long T = in.T, lds = round_up(s, 16), ldd = f64_ld(d);
   *done = 0;
-  if (!refits_beside_pay(d, s, T) || !aside.ready()) return STRP_OK;
+  if (!chol_by_order(s) || !refits_beside_pay(d, s, T) || !aside.ready()) return STRP_OK;
   Arena a = arena;
   bool ok = true;
   auto take = [&](size_t bytes) {
@@ -1329,7 +1333,7 @@ strp_status strp_refit(strp_ctx* ctx, strp_side side, const float* Gram, int32_t
   // Neither the planes nor the right-hand side need the factor: they are made on the second stream beside it.  Where the workspace
   // holds everything at once, with all of the product's partials: what is summed in which order does not depend on it.
   Aside aside(ctx);
-  if (!chol_valid && refit_beside_pays(m, n, T, npl, npr)) {
+  if (!chol_valid && chol_by_order(n) && refit_beside_pays(m, n, T, npl, npr)) {
     Arena a = arena;
     bool fits = true;
     auto take = [&](size_t bytes) { fits = a.take(bytes) && fits; };
@@ -1469,7 +1473,7 @@ strp_status strp_module_init(strp_ctx* ctx, const strp_module_desc* desc, strp_m
   Arena both = ah;
   double* const sub = (double*)both.take(sizeof(double) * chol_scratch_elems(d));
   double* scratch = copied ? (double*)both.take(sizeof(double) * (size_t)d * d) : nullptr;
-  if (d >= 2 * NB && sub && (scratch || !copied) && both.room() >= targets_bytes && both.room() >= sizeof(float) * nt_partial_elems(d, d, T, 1) && aside.ready()) {
+  if (d >= 2 * NB && chol_by_order(d) && sub && (scratch || !copied) && both.room() >= targets_bytes && both.room() >= sizeof(float) * nt_partial_elems(d, d, T, 1) && aside.ready()) {
     STRP_TRY(gram(both, diag, Hd));
     STRP_TRY(aside.follow());
     {

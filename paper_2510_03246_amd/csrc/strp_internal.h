@@ -245,7 +245,8 @@ static inline size_t chol_scratch_elems(long long n) {
 strp_status chol_inverse(strp_ctx* ctx, double* A, int n, long long ld, double* sub, double* Linv, long long ldv, int32_t* status);
 // The same in one launch, for the orders that are faster so beside a pass of these bytes (0: none).
 bool chol_flow_ok(int n, double pass_bytes);
-bool chol_flow_can(int n);
+// whether the order alone decides that
+bool chol_by_order(int n);
 strp_status chol_flow(strp_ctx* ctx, double* A, int n, long long ld, double* Linv, long long ldv, int32_t* status, const CoJob& job);
 // a pass that rides with nothing: a launch of its own
 strp_status launch_cojob(strp_ctx* ctx, const CoJob& job);

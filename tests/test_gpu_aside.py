@@ -212,3 +212,34 @@ def test_contexts_on_streams_of_their_own():
     for a, b in zip(both, alone):
         assert all(torch.equal(getattr(a, n), getattr(b, n)) for n in NAMES)
         assert a.ctx.poll() == strp.OK
+
+
+@pytest.mark.parametrize("m,n,T", [(64, 1000, 10000), (333, 4100, 4001), (16, 5320, 3000)])
+def test_first_call_captured(m, n, T):
+    """A context makes its second stream with the first call that can use it, but not while that is captured, which then goes in turn: the same bits as of
+    the eager call that has it, also where the system takes launches per panel (63 to 68 and 84 to 90 tiles)."""
+    s = torch.cuda.Stream()
+    with torch.cuda.stream(s):
+        ctx, twin = strp.Context(0, 1 << 30), strp.Context(0, 1 << 30)
+        g = torch.Generator(device="cuda").manual_seed(n)
+        ld = (T + 7) // 8 * 8
+        lhs, rhs = (torch.randn((rows, ld), generator=g, device="cuda") for rows in (m, n))
+        G = rhs[:, :T] @ rhs[:, :T].T
+        idx = torch.arange(n, dtype=torch.int32, device="cuda")
+        out = [[torch.zeros((m, n), device="cuda"), torch.zeros((n, n), dtype=torch.float64, device="cuda")] for _ in (0, 1)]
+        call = lambda c, o: c.strp_refit(strp.SIDE_FC2, G, 0.01 * T, lhs, rhs, T, idx, o[0], chol=o[1])
+        torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=s):
+        call(ctx, out[0])
+    with torch.cuda.stream(s):
+        for _ in range(3):
+            for t in out[0]:
+                t.zero_()
+            graph.replay()
+            call(twin, out[1])
+            torch.cuda.synchronize()
+            assert ctx.poll() == strp.OK and twin.poll() == strp.OK
+            assert all(torch.equal(a, b) for a, b in zip(*out))
+    ctx.close()
+    twin.close()

@@ -565,6 +565,56 @@ def check_second_stream():
     assert seen == {True, False}
 
 
+def check_second_stream_leaves_the_way_of_a_factorisation():
+    """One launch or launches per panel: the same with a second stream and without one, so that the factor's bits do not depend on it.  In the two
+    ranges of orders that take launches per panel without a long pass nothing runs beside them, but for the residual beside M's; on either side of the
+    ranges something does."""
+    lib = Library()
+    strp, fake = lib.strp, lib.fake
+
+    def way(launches):
+        return [x for x, _ in launches if "chol_flow_kernel" in x or "chol_begin_kernel" in x or "chol_step_kernel" in x]
+
+    def init(d):
+        desc, st = strp.ModuleDesc(d, d, 16384, 16384, 16384, strp.F32, strp.F32, d), strp.ModuleState()
+        for name, kind in strp.ModuleState._fields_:
+            if kind is C.c_void_p:
+                setattr(st, name, 1 << 50)
+        p = strp.Params(1.0, 1.0, 0.01, strp.WANDA, 1, d, 0)
+        return lambda: lib.lib.strp_module_init(lib.h, C.byref(desc), C.byref(st), C.byref(p))
+
+    def refit(n):
+        return lambda: lib.lib.strp_refit(lib.h, strp.SIDE_FC2, 1 << 52, n, 1.0, None, 0, 1 << 50, strp.F32, 65536, 1 << 51, strp.F32, 65536, 65536, 1 << 53, n, 1 << 54,
+                                          4096, n)
+
+    def step(d, k, f=8192, T=8192):
+        desc, st = strp.ModuleDesc(d, f, T, T, T, strp.F32, strp.F32, k), strp.ModuleState()
+        for name, kind in strp.ModuleState._fields_:
+            if kind is C.c_void_p:
+                setattr(st, name, 1 << 50)
+        p = strp.Params(1.0, 1.0, 0.01, strp.WANDA, 1, k, 0)
+
+        def call():
+            assert lib.lib.strp_module_init(lib.h, C.byref(desc), C.byref(st), C.byref(p)) == strp.OK
+            fake.fake_clear()
+            return lib.lib.strp_admm_step(lib.h, C.byref(desc), C.byref(st), C.byref(p), None)
+
+        return call
+
+    calls = [(make(n), beside) for make in (init, refit) for n, beside in ((1000, 1), (3968, 1), (3976, 0), (4096, 0), (4352, 0), (4360, 1), (5312, 1), (5320, 0), (5760, 0), (5768, 1))]
+    calls += [(step(2048, 3200), 1), (step(2048, 3976), 0), (step(2048, 4352), 0), (step(4096, 3200), 1), (step(4096, 4096), 0), (step(64, 4200, T=30000), 0)]
+    seen = {}
+    for streams in (0, 1):
+        assert lib.lib.strp_destroy(lib.h) == strp.OK
+        fake.fake_streams(streams)
+        assert lib.lib.strp_create(C.byref(lib.h), 0, None) == strp.OK
+        lib.workspace(1 << 50)
+        for i, (call, beside) in enumerate(calls):
+            st, launches = lib.launches(call)
+            assert st == strp.OK and any(fake.fake_stream(j) for j in range(len(launches))) == (streams and beside), (i, streams)
+            assert way(launches) and seen.setdefault(i, way(launches)) == way(launches), i
+
+
 def check_second_stream_is_on_the_device_of_its_context():
     """A stream and an event belong to the device that is current as they are made, and a context may be used from a thread whose current
     device is another one: its second stream and its two events are made on its own device, and the thread keeps the one it had."""
@@ -635,7 +685,7 @@ def check_weight_statistics_counter():
     assert counter(lib.h) not in (0, a, b, c)
 
 
-CHECKS = [check_systems_of_the_factorisations, check_which_factorisation_runs, check_tiles_of_the_solves, check_tiles_of_the_kept_rows, check_second_stream, check_second_stream_is_on_the_device_of_its_context, check_weight_statistics_counter, check_weight_statistics_without_a_counter, check_what_the_gram_matrices_cover, check_what_the_large_systems_cover, check_selection_of_a_very_wide_module, check_weight_statistics_arguments, check_weight_statistics_workgroups, check_chains, check_workspace_of_a_module, check_least_workspace_of_a_step, check_rows_of_the_fc2_system, check_work_of_shared_launches, check_profile_classes, check_workspace_of_a_factorisation, check_cached_factor_needs_no_alignment]
+CHECKS = [check_systems_of_the_factorisations, check_which_factorisation_runs, check_tiles_of_the_solves, check_tiles_of_the_kept_rows, check_second_stream, check_second_stream_leaves_the_way_of_a_factorisation, check_second_stream_is_on_the_device_of_its_context, check_weight_statistics_counter, check_weight_statistics_without_a_counter, check_what_the_gram_matrices_cover, check_what_the_large_systems_cover, check_selection_of_a_very_wide_module, check_weight_statistics_arguments, check_weight_statistics_workgroups, check_chains, check_workspace_of_a_module, check_least_workspace_of_a_step, check_rows_of_the_fc2_system, check_work_of_shared_launches, check_profile_classes, check_workspace_of_a_factorisation, check_cached_factor_needs_no_alignment]
 
 
 @pytest.fixture(scope="session")
