@@ -954,14 +954,65 @@ struct Aside {
   void leave() { ctx->stream = own; }
 };
 
-// Workgroups of a factorisation that has other kernels beside it: it holds a CU for each, most of them waiting.  us of factor + inverse alone with 16, 32, 64,
-// 128 and 255 of them:  440 83 / 83 / 82 / 82 / 82, 600 139 / 115 / 112 / 112 / 112, 1000 392 / 262 / 191 / 175 / 174, 1536 1098 / 595 / 401 / 283 / 253, 2500 4571 /
-// 2254 / 1308 / 823 / 581.  A step, us, with 48, 64, 80, 96, 128 and 192 for the fc2 system:  768 x 1536 over 16384 1389 / 1312 / 1288 / 1323 / 1328 / 1392, 1600 x
-// 2500 over 8000 3574 / 3274 / 3227 / 2946 / 2877 / 2908, 2048 x 3277 over 65536 15728 / 15539 / 15531 / 15521 / 15574 / 15900; for M, 24, 48, 64, 96, 128:
-// 768 1333 / 1312 / 1315 / 1370 / 1366, 1600 3597 / 3274 / 3162 / 3077 / 3058.
-static int flow_workers_beside(int n) {
-  const int w = 4 * ((n + NB - 1) / NB);
-  return w < 128 ? w : 128;
+// How long things take, in us, as far as the choice between two ways of doing them needs it.
+// Factor + inverse in one launch of that many workgroups, alone: the chain of its pivots, and tasks that grow as the cube of the order.  Measured / so, with 64, 128,
+// 192 and 256 of them:  1000 192 / 206, 179 / 181, 181 / 172, 179 / 168;  2048 830 / 798, 540 / 561, 427 / 481, 377 / 441;  3277 2541 / 2652, 1584 / 1609, 1297 / 1260, 1100 /
+// 1086;  4915 7400 / 7707, 4459 / 4320, 3359 / 3191, 2736 / 2626;  6144 13889 / 14377, 7622 / 7804, 6787 / 5613, 5149 / 4517;  7800 28.0 / 28.9, 14.7 / 15.2, 11.1 / 10.7, 9.2 / 8.5 ms.
+// It goes in steps, by how many stages of tasks the workgroups hold at a time.
+static double flow_us(int n, int workers) {
+  const double N = (n + NB - 1) / NB;
+  return 16.0 + 7.5 * N + 0.06 * N * N + 0.95 * N * N * N / workers;
+}
+constexpr double LAUNCH_US = 8.0;      // a small one with its gap
+static double pass_us(double bytes) { return bytes / 5e6; }
+static double product_us(double m, double n, double k, int passes) { return 2.0 * passes * m * n * k / 1.2e9; }      // 1.2 PFLOP/s executed
+// ... over the tokens, which are split, with its reduction; over units or channels, which are not: a tile takes 0.9 us for 64 of them
+static double nt_us(double m, double n, double T, int passes) { return product_us(m, n, T, passes) + 2.0 * LAUNCH_US; }
+static double nn_us(double m, double T, double k, int passes) {
+  const double us = product_us(m, T, k, passes);
+  return (us > 0.014 * k ? us : 0.014 * k) + LAUNCH_US;
+}
+// planes of Z_S both ways, right-hand side, the two triangular products with H's factor, planes of the weights
+static double fc1_us(int d, int s, long long T, int planes, int planes_x) {
+  return pass_us(12.0 * s * (double)T) + nt_us(s, d, (double)T, planes + planes_x - 1) + 2.0 * s * (double)d * d / 5.5e7 + 4.0 * LAUNCH_US;
+}
+// the weights' largest magnitudes and planes, Z0 with A and Z, Y and its planes
+static double targets_us(int d, int f, long long T, int planes_w, int planes_x, int planes_a) {
+  return pass_us(24.0 * f * (double)T + 12.0 * planes_w * f * (double)d) + nn_us(f, (double)T, d, planes_w + planes_x - 1) +
+         nn_us(d, (double)T, f, planes_w + planes_a - 1) + 3.0 * LAUNCH_US;
+}
+// E, one plane of it turned, E E^T
+static double residual_us(int d, int s, long long T, int planes) {
+  return nn_us(d, (double)T, s, 2 * planes - 1) + pass_us(4.0 * d * (double)T) + 0.5 * product_us(d, d, (double)T, 1) + 3.0 * LAUNCH_US;
+}
+
+// Workgroups of a factorisation that has other_us of kernels beside it: a workgroup holds a CU, waiting or not, and the others work on the rest.  So
+// it ends no earlier than it would alone on that many, nor before the others have had their time on what CUs it left them.  Four a tile row or 128 are enough for
+// the chain of pivots, 192 where an order has work for more; 0: all of them, where what fewer cost is more than what they let the others hide.  A choice has to
+// be ahead of the one before by a twentieth of the factorisation (step of 1000 x 1000 over 1000, 64 / 192 workgroups, 640 / 660).  us, all / 128 / 192 / this rule's:
+//   refits, rows x order over the tokens:  64 x 1500, 20000 395 / 367 / 344 / 192;  512 x 2500, 5000 820 / 988 / 860 / all;  2048 x 2500, 8000 1236 / 1283 / 1152 / 192;  64 x 5000, 4000
+//   3224 / 5006 / 3842 / all;  2048 x 3000, 30000 2185 / 2041 / 2158 / 128;  4096 x 5000, 16000 7566 / 8496 / 6790 / 192;  128 x 7168, 8000 7790 / 12160 / 9633 / all;
+//   initialisations, d x f:  2048 x 8192, 2048 838 / 697 / 791 / 128;  3968 x 8000, 4000 2624 / 3187 / 2464 / 192;  5120 x 20480, 2048 5427 / 5756 / 4967 / 192, over
+//   8192 8970 / 7642 / 7960 / 128;  6144 x 6144, 2048 6189 / 8209 / 7299 / all;  7168 x 28672, 8000 18.2 / 16.1 / 16.2 / 128 ms;
+//   steps, d x kept units:  2048 x 3277, 4096 4229 / 3912 / 3897 / 128;  2560 x 5000, 10000 11403 / 10972 / 10577 / 128;  3000 x 7800, 5000 23.6 / 26.6 / 21.7 / 192 ms;
+//   1024 x 8000, 3000 14.1 / 21.1 / 15.5 / all.
+// Up to some 1600 four a tile row:  440 alone with 16, 32, 64, 128 and 255 of them 83 / 83 / 82 / 82 / 82, 600 139 / 115 / 112 / 112 / 112, 1000 392 / 262 / 191 / 175 / 174;
+// a step with 48, 64, 80, 96, 128 and 192 for the fc2 system  768 x 1536 over 16384 1389 / 1312 / 1288 / 1323 / 1328 / 1392, 1600 x 2500 over 8000 3574 / 3274 / 3227 /
+// 2946 / 2877 / 2908, 2048 x 3277 over 65536 15728 / 15539 / 15531 / 15521 / 15574 / 15900.
+static int flow_workers_beside(int n, double other_us) {
+  const int few = 4 * ((n + NB - 1) / NB);
+  const int choice[2] = {few < 128 ? few : 128, 192};
+  const double sure = 0.05 * flow_us(n, 256);
+  double least = flow_us(n, 256) + other_us;
+  int workers = 0;
+  for (int w : choice) {
+    const double alone = flow_us(n, w), both = other_us + alone * w / 256.0, us = alone > both ? alone : both;
+    if (us < least - sure) {
+      least = us;
+      workers = w;
+    }
+  }
+  return workers;
 }
 struct FlowWorkers {
   strp_ctx* const ctx;
@@ -1069,12 +1120,11 @@ static strp_status refit_both(strp_ctx* ctx, Arena& arena, const RefitsIn& in, c
   return apply_inverse_right_pair(ctx, SolveIn{Ginv, s, lds, R2, d, lds, tmp2, w2}, SolveIn{in.Linv1, d, d, R1, s, ldd, tmp1, w1});
 }
 
-// A refit by itself: what runs beside the factorisation is the planes of both sides and their product, where they take longer than the
+// A refit by itself: what runs beside the factorisation is the planes of both sides and their product, where they take longer (25 us) than the
 // two waits.  us of a head pruning's four calls, one after the other / so:  2048 rows x 832 kept over 65536 tokens, bf16 1112 / 1016, 2240 x 960, 20000
 // 701 / 614, 800 x 320, 40000, fp32 433 / 398, 2560 x 1152, 100000 2314 / 2198, 1024 x 512, 3000 204 / 204.
-static bool refit_beside_pays(int m, int n, long long T, int planes_l, int planes_r) {
-  const double product_us = 2.0 * (planes_l + planes_r - 1) * m * n * (double)T / 1.2e9, planes_us = 8.0 * ((double)m + n) * (double)T / 4e6;
-  return n >= 2 * NB && product_us + planes_us >= 20.0;
+static double refit_beside_us(int m, int n, long long T, int planes_l, int planes_r) {
+  return nt_us(m, n, (double)T, planes_l + planes_r - 1) + pass_us(4.0 * ((double)planes_l * m + (double)planes_r * n) * (double)T);
 }
 // the block of the M^-1 chain: partials of W W^T, scratch of the factorisation, planes of M^-1
 static size_t m_chain_bytes(int d, long long sp) {
@@ -1094,10 +1144,11 @@ static size_t bytes_after_refits(int d, int s, long long T, int np) {
 // that and beside what comes of W2.  us of a step, one after the other / so:  440 x 600 over 9000 tokens 604 / 489, 768 x 1536 over 16384 1564 / 1318, 1600 x 2500
 // over 8000 2991 / 2652, 1000 x 1013 over 30011 (fp32, GAIN) 1949 / 1729, 768 x 1536 over 65536 3547 / 3387, 2048 x 3277 over 65536 15740 / 15520.
 // What it hides is the factorisations' time, so not where the products' is many times that: 2048 x 3277 over 262144 52.2 / 52.3 ms, 4096 x 4915 over
-// 131072 79.3 / 79.8.  The bits are the same.
-static bool refits_beside_pay(int d, int s, long long T) {
-  const double N = (s + NB - 1) / NB, factor_us = 11.0 * N + N * N * N / 260.0, product_us = 6.0 * d * s * (double)T / 1.2e9;
-  return product_us <= 4.0 * factor_us;
+// 131072 79.3 / 79.8.  Nor where the factorisation is so much that it had better have all of the chip (flow_workers_beside), since the pass can then ride
+// along.  The bits are the same.
+static bool refits_beside_pay(int d, int s, long long T, int workers) {
+  const double N = (s + NB - 1) / NB, factor_us = 11.0 * N + N * N * N / 260.0;
+  return product_us(d, s, (double)T, 3) <= 4.0 * factor_us && (workers || !chol_flow_ok(s, 0.0));
 }
 // later: bytes of the arena that the rest of the step takes.  *done: 0 = nothing was launched or taken.  Otherwise *Zk as in refit_both, *W1p: the
 // planes of W1's kept rows, *part: room for partials on the second stream.
@@ -1106,7 +1157,8 @@ static strp_status refits_beside(strp_ctx* ctx, Aside& aside, Arena& arena, cons
   const int s = in.s, d = in.d;
   const long long T = in.T, lds = round_up(s, 16), ldd = f64_ld(d);
   *done = 0;
-  if (!chol_by_order(s) || !refits_beside_pay(d, s, T) || !aside.ready()) return STRP_OK;
+  const int workers = flow_workers_beside(s, nt_us(d, s, (double)T, 2 * in.planes - 1) + fc1_us(d, s, T, in.planes, in.X.lo ? 2 : 1));
+  if (!chol_by_order(s) || !refits_beside_pay(d, s, T, workers) || !aside.ready()) return STRP_OK;
   Arena a = arena;
   bool ok = true;
   auto take = [&](size_t bytes) {
@@ -1165,7 +1217,7 @@ static strp_status refits_beside(strp_ctx* ctx, Aside& aside, Arena& arena, cons
   // the factorisation first, so that it finds its CUs free
   STRP_TRY(aside.follow());
   {
-    const FlowWorkers few(ctx, flow_workers_beside(s));
+    const FlowWorkers few(ctx, workers);
     STRP_TRY(factor_and_invert(ctx, Arena(sub, sizeof(double) * chol_scratch_elems(s)), G, s, lds, Ginv, lds));
   }
   aside.enter();
@@ -1333,7 +1385,8 @@ strp_status strp_refit(strp_ctx* ctx, strp_side side, const float* Gram, int32_t
   // Neither the planes nor the right-hand side need the factor: they are made on the second stream beside it.  Where the workspace
   // holds everything at once, with all of the product's partials: what is summed in which order does not depend on it.
   Aside aside(ctx);
-  if (!chol_valid && chol_by_order(n) && refit_beside_pays(m, n, T, npl, npr)) {
+  const double beside_us = refit_beside_us(m, n, T, npl, npr);
+  if (!chol_valid && n >= 2 * NB && chol_by_order(n) && beside_us >= 25.0) {
     Arena a = arena;
     bool fits = true;
     auto take = [&](size_t bytes) { fits = a.take(bytes) && fits; };
@@ -1348,7 +1401,7 @@ strp_status strp_refit(strp_ctx* ctx, strp_side side, const float* Gram, int32_t
       STRP_TRY(f32_to_f64_ridge(ctx, Gram, ldg, ri.sys, ri.ld, n, lambda, nullptr));
       STRP_TRY(aside.follow());
       {
-        const FlowWorkers few(ctx, flow_workers_beside(n));
+        const FlowWorkers few(ctx, flow_workers_beside(n, beside_us));
         STRP_TRY(factor_and_invert(ctx, Arena(sub, sizeof(double) * chol_scratch_elems(n)), ri.sys, n, ri.ld, ri.Linv, ri.ldl));
       }
       ri.linv_ready = ri.r_ready = 1;
@@ -1477,7 +1530,7 @@ strp_status strp_module_init(strp_ctx* ctx, const strp_module_desc* desc, strp_m
     STRP_TRY(gram(both, diag, Hd));
     STRP_TRY(aside.follow());
     {
-      const FlowWorkers few(ctx, flow_workers_beside(d));
+      const FlowWorkers few(ctx, flow_workers_beside(d, targets_us(d, f, T, npw, cv.Xt.lo ? 2 : 1, npa)));
       STRP_TRY(factor(Arena(sub, sizeof(double) * chol_scratch_elems(d)), Hd, scratch));
     }
     aside.enter();
@@ -1771,7 +1824,8 @@ strp_status strp_admm_step(strp_ctx* ctx, const strp_module_desc* desc, strp_mod
     residual_aside = refits_done && !residual_shared && (beside || d > NB) && aside.ready();
     if (residual_aside) STRP_TRY(aside.follow());
     {
-      const FlowWorkers few(ctx, residual_aside ? flow_workers_beside(d) : 0);
+      const double beside_us = residual_us(d, s, T, npa) + (beside ? fc1_us(d, s, T, npa, cv.Xt.lo ? 2 : 1) : 0.0);      // what the second stream has left
+      const FlowWorkers few(ctx, residual_aside ? flow_workers_beside(d, beside_us) : 0);
       STRP_TRY(factor_and_invert(ctx, a2, Md, d, d, Linv, d));
     }
     // M is well conditioned (its spectrum lies in [beta/alpha, beta/alpha + |W|^2]): form M^-1 = Linv^T Linv

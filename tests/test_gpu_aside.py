@@ -83,7 +83,7 @@ def _step_both_ways(d, f, T, k, mode, dtype, beside_by):
 
 
 @pytest.mark.parametrize("d,f,T,k,mode,dtype", [(440, 1440, 9003, 600, strp.WANDA, "bf16"), (264, 1000, 30011, 401, strp.GAIN, "f32"), (72, 264, 70001, 131, strp.GAIN, "bf16"),
-                                                (40, 160, 100000, 60, strp.WANDA, "f32"), (768, 1536, 2000, 1408, strp.WANDA, "bf16")])
+                                                (40, 160, 100000, 60, strp.WANDA, "f32"), (768, 1536, 2000, 1408, strp.WANDA, "bf16"), (256, 3072, 1024, 2000, strp.WANDA, "bf16")])
 def test_step_beside_and_in_turn(d, f, T, k, mode, dtype):
     """Two iterations each.  The passes ride with the fc2 factorisation where the refits go in turn, and are a launch of their own beside it."""
     _step_both_ways(d, f, T, k, mode, dtype, lambda names: "pruned_rows" in names)
@@ -96,7 +96,7 @@ def test_residual_in_the_launches_of_the_chain(d, f, T, k, mode, dtype):
     _step_both_ways(d, f, T, k, mode, dtype, lambda names: not any(n.endswith("resid") for n in names))
 
 
-@pytest.mark.parametrize("side,m,n,T", [(strp.SIDE_FC2, 333, 200, 20003), (strp.SIDE_FC2, 64, 1000, 10000), (strp.SIDE_FC1, 300, 136, 30000)])
+@pytest.mark.parametrize("side,m,n,T", [(strp.SIDE_FC2, 333, 200, 20003), (strp.SIDE_FC2, 64, 1000, 10000), (strp.SIDE_FC2, 64, 1500, 20000), (strp.SIDE_FC2, 40, 2500, 5000), (strp.SIDE_FC1, 300, 136, 30000)])
 def test_refit_beside_and_in_turn(side, m, n, T):
     ctx = strp.Context(0)
     g = torch.Generator(device="cuda").manual_seed(n)

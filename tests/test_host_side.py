@@ -615,6 +615,51 @@ def check_second_stream_leaves_the_way_of_a_factorisation():
             assert way(launches) and seen.setdefault(i, way(launches)) == way(launches), i
 
 
+def _module_calls(lib, d, f, T, k, dtype):
+    """an initialisation, and the iteration behind it"""
+    strp = lib.strp
+    ld = (T + 7) // 8 * 8
+    desc, st = strp.ModuleDesc(d, f, T, ld, ld, dtype, dtype, k), strp.ModuleState()
+    for name, kind in strp.ModuleState._fields_:
+        if kind is C.c_void_p:
+            setattr(st, name, 1 << 50)
+    p = strp.Params(1.0, 1.0, 0.01, strp.WANDA, 1, k, 0)
+    return (lambda: lib.lib.strp_module_init(lib.h, C.byref(desc), C.byref(st), C.byref(p)),
+            lambda: lib.lib.strp_admm_step(lib.h, C.byref(desc), C.byref(st), C.byref(p), None))
+
+
+def check_workgroups_of_a_factorisation_with_company():
+    """A factorisation that others run beside gives up no more workgroups than what it so lets them hide is worth: four a tile row up to 128, 192, or, where it
+    had better have all of them, none; an iteration's refits then go in turn."""
+    lib = Library()
+    strp, fake = lib.strp, lib.fake
+    fake.fake_streams(1)
+
+    def flow(call):
+        st, launches = lib.launches(call)
+        assert st == strp.OK
+        return [(grid[0], fake.fake_stream(i)) for i, (name, grid) in enumerate(launches) if "chol_flow_kernel" in name], [fake.fake_stream(i) for i in range(len(launches))]
+
+    lib.workspace(1 << 50)
+    for m, n, T, workers in [(333, 200, 20003, 14), (2048, 832, 65536, 52), (1024, 1664, 65536, 104), (64, 1000, 10000, 192), (64, 1500, 20000, 192), (512, 2500, 5000, 256),
+                             (512, 2500, 30000, 192), (2048, 3000, 30000, 128), (64, 3500, 16000, 256), (64, 5000, 4000, 256), (2048, 5000, 8000, 256), (4096, 5000, 16000, 192),
+                             (128, 7168, 8000, 256), (7168, 2150, 8000, 128)]:
+        ld = (T + 7) // 8 * 8
+        (got,), side = flow(lambda: lib.lib.strp_refit(lib.h, strp.SIDE_FC2, 1 << 52, n, 1.0, None, 0, 1 << 50, strp.F32, ld, 1 << 51, strp.BF16, ld, T, 1 << 53, n, 1 << 54, m, n))
+        assert got == (workers, 0) and any(side), (m, n, T, got)
+    for d, f, T, workers in [(136, 520, 3001, 7), (440, 1440, 9000, 28), (1024, 4096, 1200, 64), (1384, 4264, 695, 88), (2048, 8192, 2048, 128), (3600, 2000, 1000, 256), (3968, 8000, 4000, 192),
+                             (5120, 20480, 2048, 192), (5120, 20480, 8192, 128), (6144, 6144, 2048, 256), (7168, 28672, 8000, 128)]:
+        (got,), side = flow(_module_calls(lib, d, f, T, f, strp.BF16)[0])
+        assert got == (workers, 0) and any(side), (d, f, T, got)
+    # the fc2 system's and M's
+    for d, f, T, k, fc2, m, beside in [(440, 1440, 9000, 600, 40, 28, 1), (768, 3072, 65536, 1536, 96, 48, 1), (768, 3072, 1024, 2000, 192, 48, 1), (2048, 8192, 4096, 3277, 128, 128, 1),
+                                       (3000, 13000, 5000, 7800, 192, 128, 1), (1024, 16384, 3000, 8000, 256, 254, 0), (512, 8192, 2000, 4400, 256, 62, 0)]:
+        init, step = _module_calls(lib, d, f, T, k, strp.BF16)
+        assert init() == strp.OK
+        got, side = flow(step)
+        assert [w for w, _ in got] == [fc2, m] and (sum(side) > 5) == beside, (d, f, T, k, got, sum(side))
+
+
 def check_second_stream_is_on_the_device_of_its_context():
     """A stream and an event belong to the device that is current as they are made, and a context may be used from a thread whose current
     device is another one: its second stream and its two events are made on its own device, and the thread keeps the one it had."""
@@ -685,7 +730,7 @@ def check_weight_statistics_counter():
     assert counter(lib.h) not in (0, a, b, c)
 
 
-CHECKS = [check_systems_of_the_factorisations, check_which_factorisation_runs, check_tiles_of_the_solves, check_tiles_of_the_kept_rows, check_second_stream, check_second_stream_leaves_the_way_of_a_factorisation, check_second_stream_is_on_the_device_of_its_context, check_weight_statistics_counter, check_weight_statistics_without_a_counter, check_what_the_gram_matrices_cover, check_what_the_large_systems_cover, check_selection_of_a_very_wide_module, check_weight_statistics_arguments, check_weight_statistics_workgroups, check_chains, check_workspace_of_a_module, check_least_workspace_of_a_step, check_rows_of_the_fc2_system, check_work_of_shared_launches, check_profile_classes, check_workspace_of_a_factorisation, check_cached_factor_needs_no_alignment]
+CHECKS = [check_workgroups_of_a_factorisation_with_company, check_systems_of_the_factorisations, check_which_factorisation_runs, check_tiles_of_the_solves, check_tiles_of_the_kept_rows, check_second_stream, check_second_stream_leaves_the_way_of_a_factorisation, check_second_stream_is_on_the_device_of_its_context, check_weight_statistics_counter, check_weight_statistics_without_a_counter, check_what_the_gram_matrices_cover, check_what_the_large_systems_cover, check_selection_of_a_very_wide_module, check_weight_statistics_arguments, check_weight_statistics_workgroups, check_chains, check_workspace_of_a_module, check_least_workspace_of_a_step, check_rows_of_the_fc2_system, check_work_of_shared_launches, check_profile_classes, check_workspace_of_a_factorisation, check_cached_factor_needs_no_alignment]
 
 
 @pytest.fixture(scope="session")
