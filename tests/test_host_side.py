@@ -499,12 +499,14 @@ def check_tiles_of_the_solves():
 
 
 def check_tiles_of_the_kept_rows():
-    """Which kernel makes E, A_S and Z1: 128 x 256 tiles (h) from 256 of them on, but for one round of 256 x 256 ones (d) on two planes each, and not
-    for a contraction below 192 or 128 rows; then 64 x 256 (q), 128 x 128 (t) or blocks of 64 x 64 (s).  Each where its rule turns."""
+    """Which kernel makes E, A_S and Z1: 128 x 256 tiles (h) from 256 of them on, but for one round of 256 x 256 ones (d) on two planes each, for E and A_S
+    of long contractions in sixteen rounds or more, and not for a contraction below 192 or 128 rows; then 64 x 256 (q), 128 x 128 (t) or blocks of 64 x 64 (s).  Each where its rule turns."""
     lib = Library()
     for d, f, T, k, want in [(392, 800, 21845, 385, "hhh"), (256, 1000, 32512, 257, "tdd"), (256, 1000, 32513, 257, "hdd"), (256, 1000, 32769, 257, "hhh"), (256, 1000, 32768, 600, "hhh"), (768, 3072, 16384, 1536, "dhh"), (768, 3072, 21760, 1536, "dhh"),
                              (768, 3072, 21768, 1536, "hhh"), (1000, 2312, 30011, 1013, "hhh"), (512, 1704, 16384, 1000, "hdd"), (512, 1704, 16640, 1000, "hhh"), (136, 400, 140000, 128, "tqq"), (192, 400, 140000, 192, "hhh"),
-                             (768, 2560, 4096, 1200, "qqq"), (512, 1704, 4000, 640, "sss"), (256, 848, 30000, 512, "tdd"), (440, 1440, 9000, 600, "qqq"), (440, 1440, 9000, 496, "tqq"), (448, 1440, 16000, 256, "tss")]:
+                             (768, 2560, 4096, 1200, "qqq"), (512, 1704, 4000, 640, "sss"), (256, 848, 30000, 512, "tdd"), (440, 1440, 9000, 600, "qqq"), (440, 1440, 9000, 496, "tqq"), (448, 1440, 16000, 256, "tss"),
+                             (4096, 16384, 262144, 4915, "ddh"), (4088, 16384, 262144, 4915, "dhh"), (4096, 8192, 131072, 2048, "hdh"), (4096, 8192, 130816, 2048, "hhh"),
+                             (2048, 8192, 262144, 3277, "hhh"), (4096, 8192, 120000, 2600, "hhh"), (4096, 8192, 1100000, 200, "hhh")]:
         records, names = _step_records(lib, d, f, T, k, 1 << 50)
         from paper_2510_03246_amd import profile_summary as ps
         dispatches = [dict(name=ps.short_name(n)) for n in names if n]
