@@ -890,8 +890,9 @@ static long long system_ld(Arena a, int d, int s, long long T, int np) {
 // the factor's bits depend neither on the room in the workspace nor on whether there is a second stream.  An order that takes launches per panel where no pass
 // rides along (chol_by_order) stays in turn (us, in turn / beside those launches:  an initialisation of 4096 x 16384 over 2048 tokens 3299 / 3273, 5504 x 8000
 // over 8000 6795 / 6839, refits of 512 x 4096 over 5000 2271 / 2251, 4096 x 4096 over 65536 8381 / 8435), but for M's, beside which E runs in any case
-// (d = 4096, 4915 kept units over 2048 and 16384 tokens 13.04 / 12.99 and 20.22 / 20.16 ms).  The call's own stream has waited for the other one when the call
-// returns, so that to the caller everything is on his stream, captured or not.
+// (d = 4096, 4915 kept units over 2048 and 16384 tokens 13.04 / 12.99 and 20.22 / 20.16 ms).  HIP maps all streams of a process to four hardware queues; where both
+// of a context's come to lie on one, what is meant to be beside runs in turn, with the fewer workgroups: slower, with the same results.
+// The call's own stream has waited for the other one when the call returns, so that to the caller everything is on his stream, captured or not.
 struct Aside {
   strp_ctx* const ctx;
   hipStream_t const own;

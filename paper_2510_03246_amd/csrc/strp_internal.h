@@ -36,7 +36,7 @@ struct strp_ctx {
   hipStream_t side;
   hipEvent_t side_event[2];
   int side_state;
-  int flow_workers;       // workgroups of the next factorisation in one launch, which has other kernels beside it; 0: it has the chip to itself
+  int flow_workers;       // workgroups of the next factorisation in one launch, which has other kernels beside it; 0: as many as it has use for
 };
 
 struct Profiler;
