@@ -1,13 +1,13 @@
 // A streaming pass that rides along with another kernel.
 //
 // A factorisation leaves most of the chip idle (it begins with one workgroup that factors one diagonal tile).  So a pass that is bound by
-// HBM and independent of the chain is cut into units, which workgroups of the factorisation's own launch take.  Where a step has more than the pass
-// to do meanwhile, the pass is a launch of its own (launch_cojob) ahead of that on the second stream (Aside in strp_api.hip); where the products are many times
-// the factorisation, or that needs all of the chip, kernels of two streams only take each other's CUs and it rides.  Then, where the whole factorisation is one launch (chol_flow.hip) every other
-// workgroup streams units before it takes tasks, and all of them when the tasks are gone; where it is a launch per panel, the
-// first launch carries workgroups that stream them all.  Spread over all launches of a chain instead it was slower: every launch then ended with its own ramp of the memory
-// system (n = 2458 and 2048 with a pass of 15 GB: 5.7 ms for 73 launches of 80 us, against 1.5 ms for the chains alone
-// and 2.7 ms for the pass at its 5.8 TB/s).
+// HBM and independent of the chain is cut into units, which workgroups of the factorisation's own launch take.  Where a step has more than the
+// pass to do meanwhile, the pass is a launch of its own (launch_cojob) ahead of that on the second stream (Aside in strp_api.hip); where the
+// products are many times the factorisation, or that needs all of the chip, kernels of two streams only take each other's CUs and it rides.
+// Then, where the whole factorisation is one launch (chol_flow.hip), every other workgroup streams units before it takes tasks, and all of
+// them when the tasks are gone; where it is a launch per panel, the first launch carries workgroups that stream them all.  Spread over all
+// launches of a chain instead it was slower: every launch then ended with its own ramp of the memory system (n = 2458 and 2048 with a pass of
+// 15 GB: 5.7 ms for 73 launches of 80 us, against 1.5 ms for the chains alone and 2.7 ms for the pass at its 5.8 TB/s).
 //
 // The one pass built this way is the fused a/z update of the PRUNED rows (Appendix A.1 with W2[:, j] = 0, W1[j, :] = 0:
 // A_j = relu(Z_j), then the z rule with z1 = 0), which touches only rows outside S and can therefore run at any time

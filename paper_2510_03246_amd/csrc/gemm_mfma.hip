@@ -372,12 +372,12 @@ void gemm_small_tiles(GemmP& p) {
 // with one plane of X 63 / 55 and 109 / 106 for Z1), nor for fewer workgroups than CUs (512, 700, 8192: A_S 192 of them 35 / 34, E 33 / 42), nor
 // where 128 rows or six pairs of stages are all there is (130 kept of 128 over 70000: 37 / 41, 43 / 43, 46 / 48).  The initialisation's products,
 // which write three tensors or run over all units, are no faster (2048 x 6824 x 16384: 657 / 746, 622 / 664).
-// Nor for E and A_S of two planes each from sixteen rounds of 256x256 tiles and contractions of 4096 on, where those pad by no more than a thirty-second.  Power bounds either tile there, but the 64 workgroups of
-// an XCD drift apart over a long contraction and fetch their panels again, A_S of 4096 x 4915 x 262144 79 GB where the 32 of the larger tiles fetch 42.  ms of a step,
-// 128x256 / 256x256 tiles for both:  4096, 4915, 262144 148.1 / 147.6 (A_S 24.36 / 24.03, E 22.24 / 22.33);  7168, 8602, 65536 157.4 / 155.0 (18.11 / 17.64, 26.23 /
-// 25.46);  5120, 4608, 131072 90.35 / 89.74;  4096, 4915, 131072 79.96 / 80.01, 65536 46.74 / 46.63; below both lines  4096, 4100, 24000 20.06 / 20.20;  2048, 3277, 262144 52.30 /
-// 52.38;  2560, 3072, 200000 46.56 / 46.59.  Z1 keeps this tile: 87.09 / 87.38 with it changed as well (4096, 4915, 131072, fp32 X), and 15.7 / 16.7 of its own
-// with one plane of X (4096, 4915, 262144).
+// Nor for E and A_S of two planes each from sixteen rounds of 256x256 tiles and contractions of 4096 on, where those pad by no more than a
+// thirty-second.  Power bounds either tile there, but the 64 workgroups of an XCD drift apart over a long contraction and fetch their panels again: A_S of
+// 4096 x 4915 x 262144 79 GB where the 32 of the larger tiles fetch 39 to 42, at 1.66 and 1.76 GHz.  ms of a step, 128x256 / 256x256 tiles for both:  7168, 8602, 65536
+// 157.4 / 155.5 (A_S 18.11 / 17.64, E 26.23 / 25.46);  5120, 4608, 131072 91.7 / 91.4;  no more than two runs differ  4096, 4915, 262144 148.2 / 148.1, 131072 79.96 /
+// 80.01, 65536 46.74 / 46.63;  below both lines  4096, 4100, 24000 20.06 / 20.20;  2048, 3277, 262144 52.30 / 52.38;  2560, 3072, 200000 46.56 / 46.59.  Z1 keeps
+// this tile: 87.09 / 87.38 with it changed as well (4096, 4915, 131072, fp32 X), and 15.7 / 16.7 of its own with one plane of X (4096, 4915, 262144).
 static bool half_tiles_pay(const GemmP& p, long long n4) {
   if (p.epi != EPI_RESID && p.epi != EPI_AUPD && p.epi != EPI_ZUPD) return false;
   if (p.M <= 128 || p.K < 192 || (long long)((p.M + 127) / 128) * ((p.N + 255) / 256) < 256) return false;
